@@ -1,7 +1,9 @@
-"""ctypes binding for include/conv2d_int8.h: same names, argument marshalling only.
+"""Binding for include/conv2d_int8.h: same names, argument marshalling only.
 
-torch is used for device memory and streams, nothing else.  There is no CPU fallback:
-if the HIP library has not been built, `load()` raises.
+The tensor-taking calls of a program's inner loop go through the extension module `_native` (csrc/py_native.cpp: checks,
+result tensor, stream and library call in one native step; in Python they took 7 us of a 10-us call).  Size and
+selection queries and the calls made once per layer use ctypes.  torch is used for device memory and streams, nothing
+else.  There is no CPU fallback: if the HIP library has not been built, `load()` raises.
 """
 from __future__ import annotations
 
@@ -45,6 +47,21 @@ class ConvError(RuntimeError):
 
 
 _lib = None
+_native = None
+
+
+def _calls():
+    """The native entry points (loads them on the first call; never builds, never falls back)."""
+    global _native
+    if _native is None:
+        load()
+        if not os.path.exists(_build.NATIVE):
+            raise RuntimeError(f"{_build.NATIVE} is missing: run `python -m paper_2104_04731_amd.build` "
+                               "(or __graft_entry__.build()) first")
+        from . import _native as native
+        native.set_error_class(ConvError)
+        _native = native
+    return _native
 
 
 def load(path: str | None = None):
@@ -146,17 +163,7 @@ def _require(t, dtype, what):
 
 # ---- one-shot -------------------------------------------------------------------------------
 def conv2d_int8(x: torch.Tensor, w: torch.Tensor, stride: int, pad: int, out=None, stream=None):
-    _require(x, torch.int8, "input"); _require(w, torch.int8, "weights")
-    N, C, H, W = x.shape
-    K, C2, R, S = w.shape
-    if C2 != C:
-        raise ValueError("channel mismatch")
-    P, Q = out_hw(H, W, R, S, stride, pad)
-    if out is None:
-        out = torch.empty((N, K, max(P, 0), max(Q, 0)), dtype=torch.int32, device=x.device)
-    _check(load().conv2d_int8(N, C, H, W, K, R, S, stride, pad, _ptr(x), _ptr(w), _ptr(out),
-                              _stream(stream)), "conv2d_int8")
-    return out
+    return (_native or _calls()).conv2d_int8(x, w, stride, pad, out, stream)
 
 
 STATIC_WORKSPACE_BYTES = 8 << 20
@@ -164,61 +171,27 @@ STATIC_WORKSPACE_BYTES = 8 << 20
 
 def conv2d_int8_static(x: torch.Tensor, w: torch.Tensor, stride: int, pad: int, out: torch.Tensor, stream=None):
     """conv2d_int8 through the library's fixed device array: the call allocates nothing (`out` is the caller's)."""
-    _require(x, torch.int8, "input"); _require(w, torch.int8, "weights"); _require(out, torch.int32, "output")
-    N, C, H, W = x.shape
-    K, C2, R, S = w.shape
-    if C2 != C:
-        raise ValueError("channel mismatch")
-    _check(load().conv2d_int8_static(N, C, H, W, K, R, S, stride, pad, _ptr(x), _ptr(w), _ptr(out),
-                                     _stream(stream)), "conv2d_int8_static")
-    return out
+    return (_native or _calls()).conv2d_int8_static(x, w, stride, pad, out, stream)
 
 
 def conv2d_int8_nhwc(x: torch.Tensor, w: torch.Tensor, stride: int, pad: int, out=None, stream=None):
     """x: [N, H, W, C] int8, w: KCRS int8 -> [N, P, Q, K] int32."""
-    _require(x, torch.int8, "input"); _require(w, torch.int8, "weights")
-    N, H, W, C = x.shape
-    K, C2, R, S = w.shape
-    if C2 != C:
-        raise ValueError("channel mismatch")
-    P, Q = out_hw(H, W, R, S, stride, pad)
-    if out is None:
-        out = torch.empty((N, max(P, 0), max(Q, 0), K), dtype=torch.int32, device=x.device)
-    _check(load().conv2d_int8_nhwc(N, C, H, W, K, R, S, stride, pad, _ptr(x), _ptr(w), _ptr(out),
-                                   _stream(stream)), "conv2d_int8_nhwc")
-    return out
+    return (_native or _calls()).conv2d_int8_nhwc(x, w, stride, pad, out, stream)
 
 
 def unpack_nhwc_int32(x: torch.Tensor, out=None, stream=None):
     """[N, K, P, Q] int32 -> [N, P, Q, K] int32."""
-    _require(x, torch.int32, "NKPQ tensor")
-    N, K, P, Q = x.shape
-    if out is None:
-        out = torch.empty((N, P, Q, K), dtype=torch.int32, device=x.device)
-    _check(load().unpack_nhwc_int32(N, K, P, Q, _ptr(x), _ptr(out), _stream(stream)), "unpack_nhwc_int32")
-    return out
+    return (_native or _calls()).unpack_nhwc_int32(x, out, stream)
 
 
 def requant_int8(x: torch.Tensor, shift: int, relu: bool, out=None, stream=None):
     """int32 tensor -> int8 tensor of the same shape: clip(relu(floor(x / 2^shift + 1/2)))."""
-    _require(x, torch.int32, "accumulator tensor")
-    if out is None:
-        out = torch.empty(x.shape, dtype=torch.int8, device=x.device)
-    _check(load().requant_int8(x.numel(), _ptr(x), _ptr(out), shift, int(relu), _stream(stream)), "requant_int8")
-    return out
+    return (_native or _calls()).requant_int8(x, shift, relu, out, stream)
 
 
 def requant_pack_layout(x: torch.Tensor, cb: int, pad: int, shift: int, relu: bool, out=None, stream=None):
     """[N, K, P, Q] int32 -> [N, ceil(K/cb), P+2pad, Q+2pad, cb] int8: activation + the next layer's blocking."""
-    _require(x, torch.int32, "accumulator tensor")
-    N, K, P, Q = x.shape
-    if out is None:
-        if cb % 16:
-            _check(ERR_UNSUPPORTED, "requant_pack_layout")
-        out = torch.empty((N, (K + cb - 1) // cb, P + 2 * pad, Q + 2 * pad, cb), dtype=torch.int8, device=x.device)
-    _check(load().requant_pack_layout(N, K, P, Q, cb, pad, shift, int(relu), _ptr(x), _ptr(out), _stream(stream)),
-           "requant_pack_layout")
-    return out
+    return (_native or _calls()).requant_pack_layout(x, cb, pad, shift, relu, out, stream)
 
 
 def conv2d_int8_workspace_bytes(dims, layout=LAYOUT_AUTO, cb=0, wt_is_packed=False) -> int:
@@ -227,27 +200,16 @@ def conv2d_int8_workspace_bytes(dims, layout=LAYOUT_AUTO, cb=0, wt_is_packed=Fal
 
 
 def conv2d_int8_ex(dims, layout, cb, x, w, out, workspace, wt_is_packed=False, stream=None):
-    d = _desc(*dims)
-    ws_ptr = _ptr(workspace) if workspace is not None else ctypes.c_void_p(0)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _check(load().conv2d_int8_ex(ctypes.byref(d), layout, cb, _ptr(x), _ptr(w), int(wt_is_packed),
-                                 _ptr(out), ws_ptr, ws_bytes, _stream(stream)), "conv2d_int8_ex")
-    return out
+    return (_native or _calls()).conv2d_int8_ex(dims, layout, cb, x, w, out, workspace, wt_is_packed, stream)
 
 
 def conv2d_int8_packed(dims, layout, cb, x_packed, w_packed, out, tile=-1, split_k=0, stream=None):
-    d = _desc(*dims)
-    _check(load().conv2d_int8_packed(ctypes.byref(d), layout, cb, _ptr(x_packed), _ptr(w_packed),
-                                     _ptr(out), tile, split_k, _stream(stream)), "conv2d_int8_packed")
-    return out
+    return (_native or _calls()).conv2d_int8_packed(dims, layout, cb, x_packed, w_packed, out, tile, split_k, stream)
 
 
 def conv2d_int8_packed_nhwc(dims, layout, cb, x_packed, w_packed, out, tile=-1, split_k=0, stream=None):
     """GEMM stage writing int32 [N][P][Q][K]."""
-    d = _desc(*dims)
-    _check(load().conv2d_int8_packed_nhwc(ctypes.byref(d), layout, cb, _ptr(x_packed), _ptr(w_packed),
-                                          _ptr(out), tile, split_k, _stream(stream)), "conv2d_int8_packed_nhwc")
-    return out
+    return (_native or _calls()).conv2d_int8_packed_nhwc(dims, layout, cb, x_packed, w_packed, out, tile, split_k, stream)
 
 
 def tile_applies(dims, layout, cb, tile, split_k=1):
@@ -286,29 +248,12 @@ def pack_layout_bytes(N, C, H, W, cb, pad) -> int:
 
 
 def pack_layout(x: torch.Tensor, cb: int, pad: int, out=None, stream=None):
-    _require(x, torch.int8, "input")
-    N, C, H, W = x.shape
-    nbytes = pack_layout_bytes(N, C, H, W, cb, pad)
-    if out is None:
-        if nbytes == 0:
-            _check(ERR_UNSUPPORTED, "pack_layout")
-        out = torch.empty((N, (C + cb - 1) // cb, H + 2 * pad, W + 2 * pad, cb), dtype=torch.int8,
-                          device=x.device)
-    _check(load().pack_layout(N, C, H, W, cb, pad, _ptr(x), _ptr(out), _stream(stream)), "pack_layout")
-    return out
+    return (_native or _calls()).pack_layout(x, cb, pad, out, stream)
 
 
 def pack_layout_nhwc(x: torch.Tensor, cb: int, pad: int, out=None, stream=None):
     """x: [N, H, W, C] int8."""
-    _require(x, torch.int8, "input")
-    N, H, W, C = x.shape
-    if out is None:
-        if pack_layout_bytes(N, C, H, W, cb, pad) == 0 or cb % 16:
-            _check(ERR_UNSUPPORTED, "pack_layout_nhwc")
-        out = torch.empty((N, (C + cb - 1) // cb, H + 2 * pad, W + 2 * pad, cb), dtype=torch.int8,
-                          device=x.device)
-    _check(load().pack_layout_nhwc(N, C, H, W, cb, pad, _ptr(x), _ptr(out), _stream(stream)), "pack_layout_nhwc")
-    return out
+    return (_native or _calls()).pack_layout_nhwc(x, cb, pad, out, stream)
 
 
 def pack_weights_depth(C, R, S, layout, cb) -> int:
@@ -320,16 +265,7 @@ def pack_weights_bytes(K, C, R, S, layout, cb) -> int:
 
 
 def pack_weights(w: torch.Tensor, layout: int, cb: int, out=None, stream=None):
-    _require(w, torch.int8, "weights")
-    K, C, R, S = w.shape
-    if out is None:
-        depth = pack_weights_depth(C, R, S, layout, cb)
-        if depth == 0:
-            _check(ERR_UNSUPPORTED, "pack_weights")
-        out = torch.empty((K, depth), dtype=torch.int8, device=w.device)
-    _check(load().pack_weights(K, C, R, S, layout, cb, _ptr(w), _ptr(out), _stream(stream)),
-           "pack_weights")
-    return out
+    return (_native or _calls()).pack_weights(w, layout, cb, out, stream)
 
 
 def im2col_bytes(N, C, H, W, R, S, stride, pad, kg_pad) -> int:
@@ -337,30 +273,12 @@ def im2col_bytes(N, C, H, W, R, S, stride, pad, kg_pad) -> int:
 
 
 def im2col_int8(x: torch.Tensor, R, S, stride, pad, kg_pad=None, out=None, stream=None):
-    _require(x, torch.int8, "input")
-    N, C, H, W = x.shape
-    if kg_pad is None:
-        kg_pad = (C * R * S + 63) // 64 * 64
-    if out is None:
-        P, Q = out_hw(H, W, R, S, stride, pad)
-        out = torch.empty((N * max(P, 0) * max(Q, 0), kg_pad), dtype=torch.int8, device=x.device)
-    _check(load().im2col_int8(N, C, H, W, R, S, stride, pad, kg_pad, _ptr(x), _ptr(out),
-                              _stream(stream)), "im2col_int8")
-    return out
+    return (_native or _calls()).im2col_int8(x, R, S, stride, pad, kg_pad, out, stream)
 
 
 def im2col_nhwc_int8(xh: torch.Tensor, R, S, stride, pad, kg_pad=None, out=None, stream=None):
     """xh: [N, H, W, C] int8 -> [N*P*Q, kg_pad], depth index (r*S + s)*C + c."""
-    _require(xh, torch.int8, "input")
-    N, H, W, C = xh.shape
-    if kg_pad is None:
-        kg_pad = -(-C * R * S // 64) * 64
-    if out is None:
-        P, Q = out_hw(H, W, R, S, stride, pad)
-        out = torch.empty((N * max(P, 0) * max(Q, 0), kg_pad), dtype=torch.int8, device=xh.device)
-    _check(load().im2col_nhwc_int8(N, C, H, W, R, S, stride, pad, kg_pad, _ptr(xh), _ptr(out), _stream(stream)),
-           "im2col_nhwc_int8")
-    return out
+    return (_native or _calls()).im2col_nhwc_int8(xh, R, S, stride, pad, kg_pad, out, stream)
 
 
 def pack_weights_rsc(w: torch.Tensor, out=None, stream=None):
@@ -403,14 +321,7 @@ def image_pack_weights(dims, w: torch.Tensor, out=None, stream=None):
 def conv2d_int8_packed_requant(dims, layout, cb, x_packed: torch.Tensor, w_packed: torch.Tensor, out_cb, out_pad, shift, relu,
                                out=None, stream=None):
     """GEMM stage with the activation in its epilogue: returns the next layer's blocked int8 input."""
-    N, C, H, W, K, R, S, stride, pad = dims
-    if out is None:
-        P, Q = out_hw(H, W, R, S, stride, pad)
-        out = torch.empty((N, -(-K // out_cb), P + 2 * out_pad, Q + 2 * out_pad, out_cb), dtype=torch.int8, device=x_packed.device)
-    _check(load().conv2d_int8_packed_requant(ctypes.byref(_desc(*dims)), int(layout), int(cb), _ptr(x_packed), _ptr(w_packed),
-                                             _ptr(out), int(out_cb), int(out_pad), int(shift), int(bool(relu)),
-                                             _stream(stream)), "conv2d_int8_packed_requant")
-    return out
+    return (_native or _calls()).conv2d_int8_packed_requant(dims, layout, cb, x_packed, w_packed, out_cb, out_pad, shift, relu, out, stream)
 
 
 def dilated_desc(dims, dilation):
@@ -454,36 +365,12 @@ def conv2d_int8_dilated_workspace_bytes(dims, dilation, layout=LAYOUT_AUTO, cb=0
 def conv2d_int8_dilated(dims, dilation, x: torch.Tensor, w: torch.Tensor, layout=LAYOUT_AUTO, cb=0, out=None,
                         workspace=None, stream=None):
     """Stride-1 convolution with dilation >= 2: sub-images into the batch, dense convolution, interleave."""
-    _require(x, torch.int8, "input"); _require(w, torch.int8, "weights")
-    d = _desc(*dims)
-    if out is None:
-        P, Q = dilated_out_hw(dims, dilation)
-        out = torch.empty((dims[0], dims[4], max(P, 0), max(Q, 0)), dtype=torch.int32, device=x.device)
-    if workspace is None:
-        need = conv2d_int8_dilated_workspace_bytes(dims, dilation, layout, cb)
-        workspace = torch.empty(need + 256, dtype=torch.int8, device=x.device)
-        workspace = workspace[(-workspace.data_ptr()) % 256:]
-    _check(load().conv2d_int8_dilated(ctypes.byref(d), int(dilation), int(layout), int(cb), _ptr(x), _ptr(w), _ptr(out),
-                                      _ptr(workspace), workspace.numel(), _stream(stream)), "conv2d_int8_dilated")
-    return out
+    return (_native or _calls()).conv2d_int8_dilated(dims, dilation, x, w, layout, cb, out, workspace, stream)
 
 
 def conv2d_int8_dilated_direct(dims, dilation, x: torch.Tensor, w: torch.Tensor, cb=0, out=None, workspace=None, stream=None):
     """Dilated convolution (any stride) with the dilation as an address multiplier of the GEMM stage."""
-    _require(x, torch.int8, "input"); _require(w, torch.int8, "weights")
-    N, C, H, W, K, R, S, stride, pad = dims
-    d = _desc(*dims)
-    if out is None:
-        P = (H + 2 * pad - dilation * (R - 1) - 1) // stride + 1
-        Q = (W + 2 * pad - dilation * (S - 1) - 1) // stride + 1
-        out = torch.empty((N, K, max(P, 0), max(Q, 0)), dtype=torch.int32, device=x.device)
-    if workspace is None:
-        need = int(load().conv2d_int8_dilated_direct_workspace_bytes(ctypes.byref(d), int(dilation), int(cb)))
-        workspace = torch.empty(need + 256, dtype=torch.int8, device=x.device)
-        workspace = workspace[(-workspace.data_ptr()) % 256:]
-    _check(load().conv2d_int8_dilated_direct(ctypes.byref(d), int(dilation), int(cb), _ptr(x), _ptr(w), _ptr(out),
-                                             _ptr(workspace), workspace.numel(), _stream(stream)), "conv2d_int8_dilated_direct")
-    return out
+    return (_native or _calls()).conv2d_int8_dilated_direct(dims, dilation, x, w, 0, cb, out, workspace, stream)
 
 
 def mfma_probe_int8(blocks: int, iters: int, out=None, stream=None, device="cuda:0"):
@@ -495,15 +382,7 @@ def mfma_probe_int8(blocks: int, iters: int, out=None, stream=None, device="cuda
 
 
 def gemm_int8_nt(A: torch.Tensor, B: torch.Tensor, out=None, stream=None):
-    _require(A, torch.int8, "A"); _require(B, torch.int8, "B")
-    X, Z = A.shape
-    Y, Z2 = B.shape
-    if Z != Z2:
-        raise ValueError("depth mismatch")
-    if out is None:
-        out = torch.empty((X, Y), dtype=torch.int32, device=A.device)
-    _check(load().gemm_int8_nt(X, Y, Z, _ptr(A), _ptr(B), _ptr(out), _stream(stream)), "gemm_int8_nt")
-    return out
+    return (_native or _calls()).gemm_int8_nt(A, B, out, stream)
 
 
 # ---- selection (host only) --------------------------------------------------------------------

@@ -13,6 +13,9 @@ SOURCES = ["api.cpp", "selector.cpp", "igemm_mfma.hip", "band_mfma.hip", "layout
 HEADERS = [os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "rewrite_bodies.h"), os.path.join(CSRC, "act_requant.h"), os.path.join(CSRC, "desc_check.h"),
            os.path.join(os.path.dirname(PKG), "include", "conv2d_int8.h")]
 
+NATIVE_SOURCE = "py_native.cpp"                    # the Python side of the tensor-taking calls: host code, no kernels
+NATIVE = os.path.join(PKG, "_native.so")
+
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
     "-Wno-unused-command-line-argument",
@@ -22,11 +25,28 @@ HIPCC_FLAGS = [
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not (os.path.exists(LIB) and os.path.exists(NATIVE)):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    deps = [os.path.join(CSRC, s) for s in [*SOURCES, NATIVE_SOURCE]] + HEADERS
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def native_commands():
+    """Compile and link lines of the extension module: torch's headers, the library beside it ($ORIGIN)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    obj = os.path.join(CSRC, "py_native.o")
+    compile_cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                   f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                   "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                   "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
+                   "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
+    link_cmd = ["g++", "-shared", "-fPIC", "-o", NATIVE, obj, "-L" + PKG, "-lconv2d_int8", "-Wl,-rpath,$ORIGIN",
+                "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip"]
+    return compile_cmd, link_cmd
 
 
 def build_library(verbose: bool = False) -> str:
@@ -42,12 +62,18 @@ def build_library(verbose: bool = False) -> str:
         return obj
 
     # the translation units are independent: compile them side by side (the GEMM kernel's file dominates)
-    with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1, 8)) as pool:
+    native_compile, native_link = native_commands()
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, os.cpu_count() or 1, 8)) as pool:
+        native = pool.submit(subprocess.check_call, native_compile)
         objs = list(pool.map(compile_one, SOURCES))
+        native.result()
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+    if verbose:
+        print(" ".join(native_link), flush=True)
+    subprocess.check_call(native_link)
     return LIB
 
 
