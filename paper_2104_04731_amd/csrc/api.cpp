@@ -3,6 +3,7 @@
 #include "../../include/conv2d_int8.h"
 #include "desc_check.h"
 #include "kernels.h"
+#include "launch.h"
 
 #include <mutex>
 
@@ -173,7 +174,16 @@ int resolve_layout(const conv_desc_t *d, int *layout, int *cb)
     if (*layout != CONV_LAYOUT_AUTO) return CONV_OK;
     int rc = check_desc(d);
     if (rc != CONV_OK) return rc;
-    return select_layout(d, layout, cb, nullptr);
+    struct Choice {
+        int layout, cb;
+    };
+    static thread_local PlanTable<conv_desc_t, Choice, 64> chosen;
+    const Choice *kept = chosen.get(*d, [&](Choice *n) { return (rc = select_layout(d, &n->layout, &n->cb, nullptr)) == CONV_OK; });
+    if (kept) {
+        *layout = kept->layout;
+        *cb = kept->cb;
+    }
+    return rc;
 }
 
 GemmProblem gemm_problem(const conv_desc_t *d, const Plan &pl, const int8_t *x, const int8_t *w,
@@ -211,7 +221,7 @@ struct GemmChoice {
     int tile, split_k;  // tile == CONV_TILE_BAND: the band kernel (split_k 1)
 };
 
-int choose_gemm(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
+int choose_gemm_now(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
 {
     if (tile == CONV_TILE_BAND) {
         if (split_k < 0 || split_k > 1 || !band_applies(g)) return split_k < 0 ? CONV_ERR_INVALID_ARG : CONV_ERR_UNSUPPORTED;
@@ -240,13 +250,46 @@ int choose_gemm(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
     return CONV_OK;
 }
 
+// The library's own choice is kept per problem (the tile model looks at 45 tiles x 9 splits: 3-4 us of host time).
+int choose_gemm(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
+{
+    if (tile != -1 || split_k != 0) return choose_gemm_now(g, tile, split_k, c);
+    static thread_local PlanTable<GemmKey, GemmChoice, 64> chosen;
+    int rc = CONV_OK;
+    const GemmChoice *kept = chosen.get(gemm_key(g), [&](GemmChoice *n) { return (rc = choose_gemm_now(g, tile, split_k, n)) == CONV_OK; });
+    if (kept) *c = *kept;
+    return rc;
+}
+
+// The same without a depth split (an epilogue that needs the whole sum): the band kernel, or the best tile of the
+// general one.
+int choose_gemm_unsplit(const GemmProblem &g, GemmChoice *c)
+{
+    static thread_local PlanTable<GemmKey, GemmChoice, 64> chosen;
+    const GemmChoice *kept = chosen.get(gemm_key(g), [&](GemmChoice *n) {
+        int t = -1, s = 1;
+        double cost = 0;
+        const bool tiled = gemm_pick(g, &t, &s, &cost);
+        if (band_applies(g) && (!tiled || band_cost(g) < cost)) *n = GemmChoice{CONV_TILE_BAND, 1};
+        else *n = GemmChoice{t, 1};
+        return tiled || n->tile == CONV_TILE_BAND;
+    });
+    if (!kept) return CONV_ERR_UNSUPPORTED;
+    *c = *kept;
+    return CONV_OK;
+}
+
+int launch_choice(const GemmProblem &g, const GemmChoice &c, hipStream_t st)
+{
+    if (c.tile == CONV_TILE_BAND) return gemm_status(launch_band_conv(g, st));
+    return gemm_status(launch_gemm(g, c.tile, c.split_k, st));
+}
+
 int run_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t st)
 {
     GemmChoice c;
     const int rc = choose_gemm(g, tile, split_k, &c);
-    if (rc != CONV_OK) return rc;
-    if (c.tile == CONV_TILE_BAND) return gemm_status(launch_band_conv(g, st));
-    return gemm_status(launch_gemm(g, c.tile, c.split_k, st));
+    return rc == CONV_OK ? launch_choice(g, c, st) : rc;
 }
 
 int rewrite_weights(const conv_desc_t *d, const Plan &pl, const int8_t *wt, int8_t *dst, hipStream_t st)
@@ -636,13 +679,9 @@ int conv2d_int8_dilated(const conv_desc_t *desc, int dilation, int layout, int c
     g.il_d = dilation;
     g.il_P = dp.P;
     g.il_Q = dp.Q;
-    // no depth split (the activation needs the whole sum): the band kernel, or the best tile of the general one
-    int t = -1, s = 1;
-    double cost = 0;
-    const bool tiled = gemm_pick(g, &t, &s, &cost);
-    if (band_applies(g) && (!tiled || band_cost(g) < cost)) return gemm_status(launch_band_conv(g, st));
-    if (!tiled) return CONV_ERR_UNSUPPORTED;
-    return gemm_status(launch_gemm(g, t, 1, st));
+    GemmChoice c;
+    rc = choose_gemm_unsplit(g, &c);
+    return rc == CONV_OK ? launch_choice(g, c, st) : rc;
 }
 
 // Dilation as an address multiplier: the plan of the undilated problem with the dilated layer's output extents.
@@ -796,13 +835,9 @@ int conv2d_int8_packed_requant(const conv_desc_t *desc, int layout, int cb, cons
     g.act_relu = relu != 0;
     g.o_cb = out_cb;
     g.o_pad = out_pad;
-    // no depth split (the activation needs the whole sum): the band kernel, or the best tile of the general one
-    int t = -1, s = 1;
-    double cost = 0;
-    const bool tiled = gemm_pick(g, &t, &s, &cost);
-    if (band_applies(g) && (!tiled || band_cost(g) < cost)) return gemm_status(launch_band_conv(g, st));
-    if (!tiled) return CONV_ERR_UNSUPPORTED;
-    return gemm_status(launch_gemm(g, t, 1, st));
+    GemmChoice c;
+    rc = choose_gemm_unsplit(g, &c);
+    return rc == CONV_OK ? launch_choice(g, c, st) : rc;
 }
 
 int conv2d_int8_query_tiling(const conv_desc_t *desc, int layout, int cb, int *tile, int *split_k)

@@ -27,6 +27,7 @@
 // Both LDS operands are XOR-swizzled per 64-byte row ((row/4)%4 on the 16-byte chunk index), done
 // by the lanes' choice of source chunk, so the column-wise fragment reads spread over all banks.
 #include "kernels.h"
+#include "launch.h"
 #include "rewrite_bodies.h"
 
 #include <type_traits>
@@ -624,8 +625,7 @@ hipError_t launch_band(const BandPlan &bp, hipStream_t st)
         if (e != hipSuccess) return e;
         raised = true;
     }
-    hipLaunchKernelGGL(kern, dim3(bp.grid), dim3(BAND_WAVES * 64), bp.lds, st, bp.a);
-    return hipGetLastError();
+    return launch(kern, dim3(bp.grid), dim3(BAND_WAVES * 64), bp.lds, st, bp.a);
 }
 
 }  // namespace
@@ -666,8 +666,15 @@ double band_cost(const GemmProblem &g)
 
 hipError_t launch_band_conv(const GemmProblem &g, hipStream_t st)
 {
-    BandPlan bp;
-    if (!band_plan(g, &bp)) return hipErrorInvalidValue;
+    // the plan (a table entry per workgroup among it) is kept per problem; the operands are this call's
+    static thread_local PlanTable<GemmKey, BandPlan, 16> plans;
+    const BandPlan *kept = plans.get(gemm_key(g), [&](BandPlan *p) { return band_plan(g, p); });
+    if (!kept) return hipErrorInvalidValue;
+    BandPlan bp = *kept;
+    bp.a.act = g.act;
+    bp.a.wq = g.wq;
+    bp.a.out = g.out;
+    bp.a.aout.out = g.act_out;
 #define C2I8_BAND_CASE(SROW, GPW, PB)                       \
     if (bp.srow == SROW && bp.gpw == GPW && bp.pb == PB)    \
         return bp.full ? launch_band<SROW, GPW, PB, true>(bp, st) : launch_band<SROW, GPW, PB, false>(bp, st);

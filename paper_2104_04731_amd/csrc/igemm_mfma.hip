@@ -19,6 +19,7 @@
 // unrolled matrix in memory); for a row-major matrix (im2col output) it is 16*chunk.
 #include "act_requant.h"
 #include "kernels.h"
+#include "launch.h"
 
 #include <type_traits>
 
@@ -765,8 +766,7 @@ static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
         if (e != hipSuccess) return e;
         raised[mode] = 160 * 1024;
     }
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NT), lds, st, a);
-    return hipGetLastError();
+    return launch(kern, dim3(grid), dim3(NT), lds, st, a);
 }
 
 static int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -1032,8 +1032,7 @@ __global__ void __launch_bounds__(256) mfma_probe_kernel(int iters, int32_t *out
 
 hipError_t launch_mfma_probe(int blocks, int iters, int32_t *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(mfma_probe_kernel, dim3(blocks), dim3(256), 0, st, iters, out);
-    return hipGetLastError();
+    return launch(mfma_probe_kernel, dim3(blocks), dim3(256), 0, st, iters, out);
 }
 
 }  // namespace c2i8

@@ -37,6 +37,17 @@ struct GemmProblem {
     int out_nhwc;  // `out` is [N][PQ][K] (channels innermost) instead of [N][K][PQ]; a depth split clears the same bytes
 };
 
+// A problem without its operands: what the choice of kernel, tile and split depends on.
+struct GemmKey {
+    int v[24];
+};
+inline GemmKey gemm_key(const GemmProblem &g)
+{
+    const int wide = (reinterpret_cast<uintptr_t>(g.out) & 15) == 0;
+    return GemmKey{{g.K, g.M, g.depth, g.PQ, g.Q, g.mode, g.stride, g.cb, g.Cb, g.R, g.S, g.Hp, g.Wp, g.act_out != nullptr, g.act_shift,
+                    g.act_relu, g.o_cb, g.o_pad, g.il_d, g.il_P, g.il_Q, g.dil, g.out_nhwc, wide}};
+}
+
 struct TileInfo {
     int rows, cols, threads, steps;
 };

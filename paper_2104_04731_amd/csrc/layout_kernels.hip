@@ -2,6 +2,7 @@
 // (zero padding included) is written exactly once, in 16-byte pieces, and source reads run
 // along the contiguous W axis across the lanes of a wave.
 #include "kernels.h"
+#include "launch.h"
 #include "rewrite_bodies.h"
 
 namespace c2i8 {
@@ -226,36 +227,32 @@ hipError_t launch_pack_layout(int N, int C, int H, int W, int cb, int pad,
         const bool dst_ok = plan_pack_wave(N, C, H, W, cb, pad, src, dst, &a, &blocks);
         const bool src_ok = plan_pack_src(N, C, H, W, cb, pad, src, dst, &as, &blocks_s);
         if (src_ok && !(dst_ok && a.waves >= 256 * 16)) {
-            hipLaunchKernelGGL(pack_layout_src_kernel, dim3((unsigned)blocks_s), dim3(256), 0, st, as);
-            return hipGetLastError();
+            return launch(pack_layout_src_kernel, dim3((unsigned)blocks_s), dim3(256), 0, st, as);
         }
         if (dst_ok) {
-            hipLaunchKernelGGL(pack_layout_wave_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
-            return hipGetLastError();
+            return launch(pack_layout_wave_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
         }
     }
     {
         PackArgs a;
         long long blocks;
         if (plan_pack_tiled(N, C, H, W, cb, pad, src, dst, &a, &blocks)) {
-            hipLaunchKernelGGL(pack_layout_tiled_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
-            return hipGetLastError();
+            return launch(pack_layout_tiled_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
         }
     }
     if (cb % 16 == 0) {
         const long long items = pixels * (cb / 16);
-        hipLaunchKernelGGL(pack_layout_kernel<16>, dim3(grid_for(items, 256)), dim3(256), 0, st,
-                           src, dst, C, H, W, cb, pad, Hp, Wp, Cb, pixels);
-    } else if (cb % 8 == 0) {
-        const long long items = pixels * (cb / 8);
-        hipLaunchKernelGGL(pack_layout_kernel<8>, dim3(grid_for(items, 256)), dim3(256), 0, st,
-                           src, dst, C, H, W, cb, pad, Hp, Wp, Cb, pixels);
-    } else {
-        const long long items = pixels * (cb / 4);
-        hipLaunchKernelGGL(pack_layout_kernel<4>, dim3(grid_for(items, 256)), dim3(256), 0, st,
-                           src, dst, C, H, W, cb, pad, Hp, Wp, Cb, pixels);
+        return launch(pack_layout_kernel<16>, dim3(grid_for(items, 256)), dim3(256), 0, st,
+                      src, dst, C, H, W, cb, pad, Hp, Wp, Cb, pixels);
     }
-    return hipGetLastError();
+    if (cb % 8 == 0) {
+        const long long items = pixels * (cb / 8);
+        return launch(pack_layout_kernel<8>, dim3(grid_for(items, 256)), dim3(256), 0, st,
+                      src, dst, C, H, W, cb, pad, Hp, Wp, Cb, pixels);
+    }
+    const long long items = pixels * (cb / 4);
+    return launch(pack_layout_kernel<4>, dim3(grid_for(items, 256)), dim3(256), 0, st,
+                  src, dst, C, H, W, cb, pad, Hp, Wp, Cb, pixels);
 }
 
 // ---- pack_weights -----------------------------------------------------------------------
@@ -269,9 +266,8 @@ hipError_t launch_pack_weights_blocked(int K, int C, int R, int S, int cb, int d
 {
     const long long items = (long long)K * (depth / 16);
     if (items >= (1LL << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(pack_weights_blocked_kernel, dim3(grid_for(items, 256)), dim3(256), 0, st,
-                       weight_args_blocked(K, C, R, S, cb, depth, src, dst));
-    return hipGetLastError();
+    return launch(pack_weights_blocked_kernel, dim3(grid_for(items, 256)), dim3(256), 0, st,
+                  weight_args_blocked(K, C, R, S, cb, depth, src, dst));
 }
 
 // Row-padded copy: dst[k][j] = j < CRS ? src[k][j] : 0 (the (c,r,s) order is KCRS itself).
@@ -311,9 +307,8 @@ hipError_t launch_pack_weights_rows(int K, int CRS, int depth, const int8_t *src
     const long long items = (long long)K * (depth / 16);
     if (items >= (1LL << 31)) return hipErrorInvalidValue;
     // the row copy only needs the product C*R*S: pass it as C with R = S = 1
-    hipLaunchKernelGGL(pack_weights_rows_kernel, dim3(grid_for(items, 256)), dim3(256), 0, st,
-                       WeightArgs{src, dst, K, CRS, 1, 1, 0, depth, 0, magic_for(depth / 16), 0u, 0u});
-    return hipGetLastError();
+    return launch(pack_weights_rows_kernel, dim3(grid_for(items, 256)), dim3(256), 0, st,
+                  WeightArgs{src, dst, K, CRS, 1, 1, 0, depth, 0, magic_for(depth / 16), 0u, 0u});
 }
 
 // ---- im2col -----------------------------------------------------------------------------
@@ -704,13 +699,11 @@ hipError_t launch_im2col(int N, int C, int H, int W, int R, int S, int stride, i
         long long blocks;
         size_t lds;
         if (plan_im2col_tiled(N, C, H, W, R, S, stride, pad, P, Q, kg_pad, src, dst, &a, &blocks, &lds)) {
-            hipLaunchKernelGGL(im2col_tiled_kernel, dim3((unsigned)blocks), dim3(256), lds, st, a);
-            return hipGetLastError();
+            return launch(im2col_tiled_kernel, dim3((unsigned)blocks), dim3(256), lds, st, a);
         }
     }
-    hipLaunchKernelGGL(im2col_kernel, dim3(grid_for(items, 256)), dim3(256), 0, st,
-                       src, dst, C, H, W, R, S, stride, pad, P, Q, C * R * S, kg_pad, M);
-    return hipGetLastError();
+    return launch(im2col_kernel, dim3(grid_for(items, 256)), dim3(256), 0, st,
+                  src, dst, C, H, W, R, S, stride, pad, P, Q, C * R * S, kg_pad, M);
 }
 
 // ---- input rewrite + weight rewrite in one launch ----------------------------------------
@@ -776,8 +769,7 @@ hipError_t launch_rewrite_fused(bool im2col, int N, int C, int H, int W, int K, 
     a.in_is_im2col = im2col;
     a.w_is_blocked = !im2col;
     if (blocks + a.w_blocks >= (1LL << 31)) return hipErrorNotSupported;
-    hipLaunchKernelGGL(rewrite_fused_kernel, dim3((unsigned)(blocks + a.w_blocks)), dim3(256), lds, st, a);
-    return hipGetLastError();
+    return launch(rewrite_fused_kernel, dim3((unsigned)(blocks + a.w_blocks)), dim3(256), lds, st, a);
 }
 
 // ---- channel blocking from an NHWC source (Sec. 5.2: source layouts other than NCHW) -------
@@ -858,8 +850,7 @@ hipError_t launch_pack_layout_nhwc(int N, int C, int H, int W, int cb, int pad, 
                                    hipStream_t st)
 {
     const PackNhwcArgs a = pack_nhwc_args(N, C, H, W, cb, pad, src, dst);
-    hipLaunchKernelGGL(pack_layout_nhwc_kernel, dim3(grid_for(a.total, 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
+    return launch(pack_layout_nhwc_kernel, dim3(grid_for(a.total, 256)), dim3(256), 0, st, a);
 }
 
 // hipErrorNotSupported: more weight pieces than the blocked body indexes with 32 bits (the caller then
@@ -872,8 +863,7 @@ hipError_t launch_rewrite_fused_nhwc(int N, int C, int H, int W, int K, int R, i
     if (w_items >= (1LL << 31)) return hipErrorNotSupported;
     const WeightArgs w = weight_args_blocked(K, C, R, S, cb, depth, wt, wq);
     const int in_blocks = grid_for(a.total, 256), w_blocks = grid_for(w_items, 256);
-    hipLaunchKernelGGL(rewrite_fused_nhwc_kernel, dim3(in_blocks + w_blocks), dim3(256), 0, st, a, w, in_blocks, w_blocks);
-    return hipGetLastError();
+    return launch(rewrite_fused_nhwc_kernel, dim3(in_blocks + w_blocks), dim3(256), 0, st, a, w, in_blocks, w_blocks);
 }
 
 // ---- stencil unrolling from an NHWC source (Sec. 5.2) ------------------------------------------------
@@ -964,15 +954,13 @@ hipError_t launch_im2col_nhwc(int N, int C, int H, int W, int R, int S, int stri
     a.total = (long long)N * P * Q * a.chunks;
     a.m_C = magic_for(C); a.m_S = magic_for(S);
     a.m_chunks = magic_for(a.chunks); a.m_Q = magic_for(Q); a.m_P = magic_for(P);
-    hipLaunchKernelGGL(im2col_nhwc_kernel, dim3(grid_for(a.total, 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
+    return launch(im2col_nhwc_kernel, dim3(grid_for(a.total, 256)), dim3(256), 0, st, a);
 }
 
 hipError_t launch_pack_weights_rsc(int K, int C, int R, int S, int depth, const int8_t *src, int8_t *dst, hipStream_t st)
 {
-    hipLaunchKernelGGL(pack_weights_rsc_kernel, dim3(grid_for((long long)K * depth, 256)), dim3(256), 0, st, src, dst, K, C,
-                       R, S, depth);
-    return hipGetLastError();
+    return launch(pack_weights_rsc_kernel, dim3(grid_for((long long)K * depth, 256)), dim3(256), 0, st, src, dst, K, C,
+                  R, S, depth);
 }
 
 // ---- unpacking for an NHWC consumer: [N][K][PQ] int32 -> [N][PQ][K] ---------------------------
@@ -1017,9 +1005,8 @@ hipError_t launch_unpack_nhwc(int N, int K, long long PQ, const int32_t *src, in
 {
     const int tiles_k = (K + 63) / 64, tiles_p = (int)((PQ + 31) / 32);
     const long long ntiles = (long long)N * tiles_k * tiles_p;
-    hipLaunchKernelGGL(unpack_nhwc_kernel, dim3(grid_for(ntiles * 256, 256)), dim3(256), 0, st, src, dst, K, (int)PQ,
-                       tiles_k, tiles_p, ntiles);
-    return hipGetLastError();
+    return launch(unpack_nhwc_kernel, dim3(grid_for(ntiles * 256, 256)), dim3(256), 0, st, src, dst, K, (int)PQ,
+                  tiles_k, tiles_p, ntiles);
 }
 
 // ---- activation between two int8 layers (Sec. 5.1: the accelerator's ALU; the benchmark's step
@@ -1097,9 +1084,8 @@ __global__ void __launch_bounds__(256) requant_pack_kernel(const RequantPackArgs
 
 hipError_t launch_requant(long long count, const int32_t *src, int8_t *dst, int shift, int relu, hipStream_t st)
 {
-    hipLaunchKernelGGL(requant_kernel, dim3(grid_for((count + 15) / 16, 256)), dim3(256), 0, st, src, dst, count, shift,
-                       relu);
-    return hipGetLastError();
+    return launch(requant_kernel, dim3(grid_for((count + 15) / 16, 256)), dim3(256), 0, st, src, dst, count, shift,
+                  relu);
 }
 
 hipError_t launch_requant_pack(int N, int K, int P, int Q, int cb, int pad, int shift, int relu, const int32_t *src,
@@ -1113,8 +1099,7 @@ hipError_t launch_requant_pack(int N, int K, int P, int Q, int cb, int pad, int 
     a.g16 = cb / 16;
     a.total = (long long)N * a.Cb * a.Hp * a.Wp * a.g16;
     a.m_g16 = magic_for(a.g16); a.m_Wp = magic_for(a.Wp); a.m_Hp = magic_for(a.Hp); a.m_Cb = magic_for(a.Cb);
-    hipLaunchKernelGGL(requant_pack_kernel, dim3(grid_for(a.total, 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
+    return launch(requant_pack_kernel, dim3(grid_for(a.total, 256)), dim3(256), 0, st, a);
 }
 
 static hipError_t launch_phase_split(int N, int C, int H, int W, int pad, int s, int H2, int W2, long long pn, long long pc,
@@ -1262,10 +1247,9 @@ hipError_t launch_image_pack(int N, int C, int H, int W, int stride, int pad, in
                                             (long long)stride * stride, stride, 1, src, dst, st);
     if (e != hipErrorNotSupported) return e;
     if (stride == 2 && a.total < (1LL << 31) - 4)
-        hipLaunchKernelGGL(image_pack_s2_kernel, dim3(grid_for((a.total + 3) / 4, 256)), dim3(256), 0, st, a);
+        return launch(image_pack_s2_kernel, dim3(grid_for((a.total + 3) / 4, 256)), dim3(256), 0, st, a);
     else
-        hipLaunchKernelGGL(image_pack_kernel, dim3(grid_for((a.total + 3) / 4, 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
+        return launch(image_pack_kernel, dim3(grid_for((a.total + 3) / 4, 256)), dim3(256), 0, st, a);
 }
 
 hipError_t launch_image_pack_weights(int K, int C, int R, int S, int stride, const int8_t *src, int8_t *dst,
@@ -1273,9 +1257,8 @@ hipError_t launch_image_pack_weights(int K, int C, int R, int S, int stride, con
 {
     const int R2 = (R + stride - 1) / stride, S2 = (S + stride - 1) / stride;
     const long long total = (long long)K * C * stride * stride * R2 * S2;
-    hipLaunchKernelGGL(image_pack_weights_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, src, dst, K, C, R, S,
-                       stride, R2, S2);
-    return hipGetLastError();
+    return launch(image_pack_weights_kernel, dim3(grid_for(total, 256)), dim3(256), 0, st, src, dst, K, C, R, S,
+                  stride, R2, S2);
 }
 
 // ---- dilation as Image Pack into the batch (Sec. 6.1; Table 2 row 1, [N, I] => [N*s, I/s]) --------
@@ -1384,8 +1367,7 @@ hipError_t launch_dilation_pack(int N, int C, int H, int W, int pad, int d, int 
     a.m_W2 = magic_for(W2);
     // dword stores when every plane starts on a dword
     const int words = ((long long)H2 * W2) % 4 == 0 && (reinterpret_cast<uintptr_t>(dst) & 3) == 0;
-    hipLaunchKernelGGL(dilation_pack_kernel, dim3(grid_for(a.planes * a.chunks * 256, 256)), dim3(256), 0, st, a, words);
-    return hipGetLastError();
+    return launch(dilation_pack_kernel, dim3(grid_for(a.planes * a.chunks * 256, 256)), dim3(256), 0, st, a, words);
 }
 
 // Dilation 2: output row p = 2i + a takes its even columns from row i of sub-result (a, 0) and its odd columns from
@@ -1446,8 +1428,7 @@ hipError_t launch_dilation_unpack(int N, int K, int P, int Q, int d, int P2, int
         b.m_ngrp = magic_for(b.ngrp), b.m_P = magic_for(P), b.m_K = magic_for(K);
         const long long blocks = (b.items + 255) / 256;
         if (b.items <= 2147483647LL) {
-            hipLaunchKernelGGL(dilation_unpack2_kernel, dim3((unsigned)blocks), dim3(256), 0, st, b);
-            return hipGetLastError();
+            return launch(dilation_unpack2_kernel, dim3((unsigned)blocks), dim3(256), 0, st, b);
         }
     }
     DilationArgs a{};
@@ -1461,8 +1442,7 @@ hipError_t launch_dilation_unpack(int N, int K, int P, int Q, int d, int P2, int
     a.m_K = magic_for(K);
     a.m_Q = magic_for(Q);
     a.m_d = magic_for(d);
-    hipLaunchKernelGGL(dilation_unpack_kernel, dim3(grid_for(a.planes * a.chunks * 256, 256)), dim3(256), 0, st, a);
-    return hipGetLastError();
+    return launch(dilation_unpack_kernel, dim3(grid_for(a.planes * a.chunks * 256, 256)), dim3(256), 0, st, a);
 }
 
 // ---- Image Pack through LDS: both forms of Table 2 row 1 (phases to channels, phases to batch) ------
@@ -1712,8 +1692,7 @@ static hipError_t launch_phase_split(int N, int C, int H, int W, int pad, int s,
         const long long nblocks = b.both ? ((long long)b.total + b.slots - 1) / b.slots : 2LL * b.total;
         if (nblocks <= 2147483647LL) {   // (larger tensors take the tile kernel below)
             b.m_H2 = magic_for(H2), b.m_C = magic_for(C);
-            hipLaunchKernelGGL(phase_split2_kernel, dim3((unsigned)nblocks), dim3(256), 0, st, b);
-            return hipGetLastError();
+            return launch(phase_split2_kernel, dim3((unsigned)nblocks), dim3(256), 0, st, b);
         }
     }
     PhaseSplitArgs a{};
@@ -1751,8 +1730,7 @@ static hipError_t launch_phase_split(int N, int C, int H, int W, int pad, int s,
     a.m_s = magic_for(s);
     const size_t lds = (size_t)a.G * s * a.RI * pitch;
     const int grid = a.nblocks < 256 * 16 ? a.nblocks : 256 * 16;
-    hipLaunchKernelGGL(phase_split_kernel, dim3(grid), dim3(256), lds, st, a);
-    return hipGetLastError();
+    return launch(phase_split_kernel, dim3(grid), dim3(256), lds, st, a);
 }
 
 // ---- zero fill (a kernel, not a memset node, so that callers may capture it) --------------
@@ -1770,9 +1748,8 @@ hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t st)
     // dst is 16-byte aligned for every buffer the library clears (hipMalloc'd int32 tensors).
     const long long n16 = (long long)(bytes / 16);
     const int ntail = (int)(bytes % 16);
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(grid_for(n16, 256)), dim3(256), 0, st,
-                       reinterpret_cast<v4i *>(dst), n16, reinterpret_cast<int8_t *>(dst) + n16 * 16, ntail);
-    return hipGetLastError();
+    return launch(fill_zero_kernel, dim3(grid_for(n16, 256)), dim3(256), 0, st,
+                  reinterpret_cast<v4i *>(dst), n16, reinterpret_cast<int8_t *>(dst) + n16 * 16, ntail);
 }
 
 }  // namespace c2i8

@@ -18,6 +18,7 @@
 // Two more forms of the same layer follow it: one for grids too small to fill the chip (a workgroup of 32 pixels x 32
 // output channels whose waves share the depth) and one for large batches (a workgroup owns 224 pixels of an image).
 #include "kernels.h"
+#include "launch.h"
 #include "rewrite_bodies.h"
 
 namespace c2i8 {
@@ -443,32 +444,28 @@ static hipError_t launch_pointwise_image(const WindowProblem &g, hipStream_t st)
     a.m_W = magic_for(g.W);
     a.act = g.act;
     const dim3 grid((unsigned)(g.N * a.ptiles), (unsigned)((g.K + 127) / 128));
-    hipLaunchKernelGGL(conv_pointwise_image_kernel, grid, dim3(256), (size_t)2 * IMG_PX * IMG_PITCH, st, a);
-    return hipGetLastError();
+    return launch(conv_pointwise_image_kernel, grid, dim3(256), (size_t)2 * IMG_PX * IMG_PITCH, st, a);
 }
 
 template <int NKK>
 hipError_t launch_nkk(const PointArgs &a, dim3 grid, hipStream_t st)
 {
-    if (a.act.out) hipLaunchKernelGGL((conv_pointwise_kernel<NKK, true>), grid, dim3(256), (size_t)32 * (32 * NKK + 16), st, a);
-    else hipLaunchKernelGGL((conv_pointwise_kernel<NKK, false>), grid, dim3(256), (size_t)32 * (32 * NKK + 16), st, a);
-    return hipGetLastError();
+    if (a.act.out) return launch((conv_pointwise_kernel<NKK, true>), grid, dim3(256), (size_t)32 * (32 * NKK + 16), st, a);
+    else return launch((conv_pointwise_kernel<NKK, false>), grid, dim3(256), (size_t)32 * (32 * NKK + 16), st, a);
 }
 
 template <int NKK>
 hipError_t launch_split(const PointArgs &a, hipStream_t st)
 {
     const dim3 grid((unsigned)a.ntiles, (unsigned)((a.K + 31) / 32));
-    hipLaunchKernelGGL((conv_pointwise_split_kernel<NKK>), grid, dim3(256), (size_t)4 * 32 * (8 * NKK + 16) + 4 * 4 * 64 * 16, st, a);
-    return hipGetLastError();
+    return launch((conv_pointwise_split_kernel<NKK>), grid, dim3(256), (size_t)4 * 32 * (8 * NKK + 16) + 4 * 4 * 64 * 16, st, a);
 }
 
 template <int NKK>
 hipError_t launch_nhwc_split(const PointNhwcArgs &a, hipStream_t st)
 {
     const dim3 grid((unsigned)((a.M + 31) / 32), (unsigned)((a.K + 31) / 32));
-    hipLaunchKernelGGL((conv_pointwise_nhwc_split_kernel<NKK>), grid, dim3(256), (size_t)4 * 8 * NHWC_RED_PITCH * 16, st, a);
-    return hipGetLastError();
+    return launch((conv_pointwise_nhwc_split_kernel<NKK>), grid, dim3(256), (size_t)4 * 8 * NHWC_RED_PITCH * 16, st, a);
 }
 
 }  // namespace

@@ -28,6 +28,7 @@
 // is then (r, s, c); the KCRS weight rows are copied into LDS as they are and brought into that order there.
 // A lane's four results are four consecutive channels of a pixel, which is what an NHWC result stores.
 #include "kernels.h"
+#include "launch.h"
 #include "rewrite_bodies.h"
 
 namespace c2i8 {
@@ -519,18 +520,16 @@ static hipError_t launch_window_nkk(const WindowArgs &a, dim3 grid, size_t lds, 
 {
     if (a.nhwc) {
         if (a.act.out) {
-            if (a.K > 32) hipLaunchKernelGGL((conv_window_kernel<NKK, 2, true, true>), grid, dim3(256), lds, st, a);
-            else hipLaunchKernelGGL((conv_window_kernel<NKK, 1, true, true>), grid, dim3(256), lds, st, a);
-        } else if (a.K > 32) hipLaunchKernelGGL((conv_window_kernel<NKK, 2, false, true>), grid, dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((conv_window_kernel<NKK, 1, false, true>), grid, dim3(256), lds, st, a);
-        return hipGetLastError();
+            if (a.K > 32) return launch((conv_window_kernel<NKK, 2, true, true>), grid, dim3(256), lds, st, a);
+            else return launch((conv_window_kernel<NKK, 1, true, true>), grid, dim3(256), lds, st, a);
+        } else if (a.K > 32) return launch((conv_window_kernel<NKK, 2, false, true>), grid, dim3(256), lds, st, a);
+        else return launch((conv_window_kernel<NKK, 1, false, true>), grid, dim3(256), lds, st, a);
     }
     if (a.act.out) {
-        if (a.K > 32) hipLaunchKernelGGL((conv_window_kernel<NKK, 2, true, false>), grid, dim3(256), lds, st, a);
-        else hipLaunchKernelGGL((conv_window_kernel<NKK, 1, true, false>), grid, dim3(256), lds, st, a);
-    } else if (a.K > 32) hipLaunchKernelGGL((conv_window_kernel<NKK, 2, false, false>), grid, dim3(256), lds, st, a);
-    else hipLaunchKernelGGL((conv_window_kernel<NKK, 1, false, false>), grid, dim3(256), lds, st, a);
-    return hipGetLastError();
+        if (a.K > 32) return launch((conv_window_kernel<NKK, 2, true, false>), grid, dim3(256), lds, st, a);
+        else return launch((conv_window_kernel<NKK, 1, true, false>), grid, dim3(256), lds, st, a);
+    } else if (a.K > 32) return launch((conv_window_kernel<NKK, 2, false, false>), grid, dim3(256), lds, st, a);
+    else return launch((conv_window_kernel<NKK, 1, false, false>), grid, dim3(256), lds, st, a);
 }
 
 hipError_t launch_window_conv(const WindowProblem &g, hipStream_t st)
@@ -559,9 +558,8 @@ hipError_t launch_pack_weights_window(int K, int C, int R, int S, const int8_t *
     const int nd = (S + 3) / 4;
     const long long total = (long long)K * (depth / 4);
     const int blocks = (int)((total + 255) / 256 < 4096 ? (total + 255) / 256 : 4096);
-    hipLaunchKernelGGL(pack_weights_window_kernel, dim3(blocks), dim3(256), 0, st, src, dst, K, C * R, S, nd, depth,
-                       magic_for(nd));
-    return hipGetLastError();
+    return launch(pack_weights_window_kernel, dim3(blocks), dim3(256), 0, st, src, dst, K, C * R, S, nd, depth,
+                  magic_for(nd));
 }
 
 }  // namespace c2i8
