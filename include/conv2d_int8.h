@@ -85,7 +85,9 @@ typedef struct {
  * impossible while `stream` is being captured: a call that would have to grow the block then
  * returns CONV_ERR_WORKSPACE with nothing enqueued -- make the first call for a problem size
  * outside capture (or use conv2d_int8_ex with a workspace of your own).
- * Two launches: both rewrites, then the GEMM stage; one launch and no workspace when the choice
+ * Two launches: both rewrites, then the GEMM stage -- or, where its estimate is lower, a GEMM stage that takes the
+ * input as it is (channel blocking on its way into LDS; 3x3 weights too, else their rewrite goes first): one or two
+ * launches, same result and the same workspace rule; one launch and no workspace when the choice
  * is IMPLICIT -- except for large batches of a non-1x1 layer (2^21 output pixels and more), where the
  * weights are first rewritten into the cached workspace by a small kernel (if that block cannot be had,
  * e.g. under capture, the single launch runs instead: never an error from this). */
@@ -108,7 +110,8 @@ int conv2d_int8_static(int N, int C, int H, int W, int K, int R, int S, int stri
 
 /* The same for NHWC tensors (Sec. 5.2): in [N][H][W][C], wt KCRS, out [N][P][Q][K] int32.  Channel
  * blocking straight from the NHWC source (pack_layout_nhwc) and the weight rewrite in one launch, then a
- * GEMM stage whose epilogue writes NHWC itself: two launches.  (An `out` that does not start on 16 bytes goes
+ * GEMM stage whose epilogue writes NHWC itself: two launches, or the stage that takes the input as it is (see
+ * conv2d_int8).  (An `out` that does not start on 16 bytes goes
  * through an NKPQ staging tensor in the cached workspace and unpack_nhwc_int32: three.)  Same workspace rules as conv2d_int8.
  * When select_layout's choice for the shape is IMPLICIT (not the 1x1 form) and R * ceil(S*C, 4) <= 256, the
  * kernel that unrolls the stencil itself reads the NHWC source directly -- depth order (r, s, c), a kernel row's
@@ -125,7 +128,8 @@ int conv2d_int8_nhwc(int N, int C, int H, int W, int K, int R, int S, int stride
  * wt: KCRS weights, or -- if wt_is_packed != 0 -- the output of pack_weights for the
  * same layout/cb.  workspace: device memory of at least
  * conv2d_int8_workspace_bytes(desc, layout, cb, wt_is_packed) bytes, 256-byte aligned,
- * caller-owned, free to reuse once the stream has passed this call (may be NULL when that
+ * caller-owned, free to reuse once the stream has passed this call (PACKED and PAD_ONLY may leave it untouched: where the
+ * GEMM stage that blocks the channels on its way into LDS is estimated faster, nothing rewritten is stored; may be NULL when that
  * size is 0, as it is for IMPLICIT, which reads `in` and either form of `wt` directly). */
 int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb,
                    const int8_t *in, const int8_t *wt, int wt_is_packed, int32_t *out,
@@ -272,7 +276,8 @@ int image_pack_weights(const conv_desc_t *desc, const int8_t *src, int8_t *dst, 
  * conv_layout_t that applies to it, AUTO allowed); workspace as for conv2d_int8_ex, of at least
  * conv2d_int8_dilated_workspace_bytes(desc, dilation, layout, cb) bytes (sub-images and the dense problem's
  * own workspace; with PACKED, PAD_ONLY and IM2COL the GEMM stage's epilogue writes the interleaved positions
- * itself -- three launches -- and only IMPLICIT stores the sub-images' results and interleaves in a pass of its own).  Errors: a spread kernel larger than the padded image is
+ * itself -- three launches -- and only IMPLICIT stores the sub-images' results and interleaves in a pass of its own; with
+ * AUTO the library may also read the taps `dilation` pixels apart from the image as it is, without sub-images).  Errors: a spread kernel larger than the padded image is
  * CONV_ERR_INVALID_ARG; stride != 1, d < 2 or d > 64 are CONV_ERR_UNSUPPORTED; size queries return 0. */
 int dilated_desc(const conv_desc_t *desc, int dilation, conv_desc_t *inner);
 size_t dilation_pack_bytes(const conv_desc_t *desc, int dilation);

@@ -168,6 +168,20 @@ int dilated_problem(const conv_desc_t *d, int dilation, DilatedProblem *dp)
     return CONV_OK;
 }
 
+// Dilation as an address multiplier: the plan of the undilated problem with the dilated layer's output extents.
+int direct_dilated_plan(const conv_desc_t *desc, int dilation, int cb, Plan *pl)
+{
+    if (!desc || dilation <= 0) return CONV_ERR_INVALID_ARG;
+    int rc = make_plan(desc, CONV_LAYOUT_PACKED, cb, pl);
+    if (rc != CONV_OK) return rc;
+    const long long Re = (long long)dilation * (desc->R - 1) + 1, Se = (long long)dilation * (desc->S - 1) + 1;
+    if (Re > pl->Hp || Se > pl->Wp) return CONV_ERR_INVALID_ARG;
+    pl->P = (int)((pl->Hp - Re) / desc->stride + 1);
+    pl->Q = (int)((pl->Wp - Se) / desc->stride + 1);
+    pl->M = (long long)desc->N * pl->P * pl->Q;
+    return CONV_OK;
+}
+
 // AUTO -> the selector's choice (which may be IMAGE_PACK with its inner block in *cb).
 int resolve_layout(const conv_desc_t *d, int *layout, int *cb)
 {
@@ -219,13 +233,14 @@ int gemm_status(hipError_t e)
 // Which kernel runs the GEMM stage: a tile of the general kernel with a depth split, or the band kernel.
 struct GemmChoice {
     int tile, split_k;  // tile == CONV_TILE_BAND: the band kernel (split_k 1)
+    double cost;        // the models' estimate for the library's own choice (cycles)
 };
 
 int choose_gemm_now(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
 {
     if (tile == CONV_TILE_BAND) {
         if (split_k < 0 || split_k > 1 || !band_applies(g)) return split_k < 0 ? CONV_ERR_INVALID_ARG : CONV_ERR_UNSUPPORTED;
-        *c = GemmChoice{CONV_TILE_BAND, 1};
+        *c = GemmChoice{CONV_TILE_BAND, 1, 0};
         return CONV_OK;
     }
     if (tile < -1 || tile >= gemm_num_tiles()) return CONV_ERR_INVALID_ARG;
@@ -237,16 +252,16 @@ int choose_gemm_now(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
     double cost = 0;
     if (!gemm_pick(g, &t, &s, &cost)) {
         if (free_choice && band_applies(g)) {
-            *c = GemmChoice{CONV_TILE_BAND, 1};
+            *c = GemmChoice{CONV_TILE_BAND, 1, band_cost(g)};
             return CONV_OK;
         }
         return CONV_ERR_UNSUPPORTED;
     }
     if (free_choice && band_cost(g) < cost) {
-        *c = GemmChoice{CONV_TILE_BAND, 1};
+        *c = GemmChoice{CONV_TILE_BAND, 1, band_cost(g)};
         return CONV_OK;
     }
-    *c = GemmChoice{t, s};
+    *c = GemmChoice{t, s, cost};
     return CONV_OK;
 }
 
@@ -270,8 +285,8 @@ int choose_gemm_unsplit(const GemmProblem &g, GemmChoice *c)
         int t = -1, s = 1;
         double cost = 0;
         const bool tiled = gemm_pick(g, &t, &s, &cost);
-        if (band_applies(g) && (!tiled || band_cost(g) < cost)) *n = GemmChoice{CONV_TILE_BAND, 1};
-        else *n = GemmChoice{t, 1};
+        if (band_applies(g) && (!tiled || band_cost(g) < cost)) *n = GemmChoice{CONV_TILE_BAND, 1, 0};
+        else *n = GemmChoice{t, 1, cost};
         return tiled || n->tile == CONV_TILE_BAND;
     });
     if (!kept) return CONV_ERR_UNSUPPORTED;
@@ -290,6 +305,142 @@ int run_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t st)
     GemmChoice c;
     const int rc = choose_gemm(g, tile, split_k, &c);
     return rc == CONV_OK ? launch_choice(g, c, st) : rc;
+}
+
+// ---- two-stage path or the GEMM stage that blocks the channels itself (resident_mfma.hip) -----------------------------
+// Estimated times in microseconds.  Two-stage, fitted to 145 layers of 3 us to 300 us (mean error 11 %, the choice between
+// the two paths loses 2 % against the measured better one): the launches, the GEMM stage's model (the general kernel's
+// and the band kernel's cycles are different scales), the rewritten tensors written and read.  A second launch costs the stream about a microsecond more
+// than it costs a graph, in which both models were measured.
+constexpr double SECOND_LAUNCH_US = 1.0;
+double two_stage_us(const GemmProblem &g, double moved, double weights, bool wt_is_packed)
+{
+    GemmChoice c;
+    if (choose_gemm(g, -1, 0, &c) != CONV_OK) return 1e300;
+    const double us = c.tile == CONV_TILE_BAND
+                          ? wt_is_packed ? 3.8 + 0.71e-3 * c.cost + 0.075e-6 * moved + 0.5e-6 * weights
+                                         : 3.7 + 0.82e-3 * c.cost + 0.04e-6 * moved + 1.2e-6 * weights
+                          : wt_is_packed ? 5.3 + 0.251e-3 * c.cost + 0.298e-6 * moved + 1.5e-6 * weights
+                                         : 5.9 + 0.256e-3 * c.cost + 0.291e-6 * moved + 2.7e-6 * weights;
+    return us + SECOND_LAUNCH_US;
+}
+
+enum RouteHow : int { TWO_STAGE = 0, DIRECT_AS_IS = 1, DIRECT_RAW = 2, DIRECT_REWRITE = 3 };
+struct Route {
+    int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones
+    ResidentChoice pick;
+    int cb, depth;       // block and row bytes of the weights it reads (DIRECT_REWRITE: PAD_ONLY's, what is rewritten)
+};
+
+// A convolution with its activations in the network's own layout (NCHW, or NHWC).  pl: the plan whose output extents
+// apply (a dilated layer's own, if dil > 1); weights in blocks of cb with rows of `depth` bytes, or raw.
+ResidentProblem resident_problem(const conv_desc_t *d, const Plan &pl, int cb, int depth, bool raw, bool nhwc, int dil, const int8_t *in,
+                                 const int8_t *wt, int32_t *out, bool out_nhwc)
+{
+    ResidentProblem r{};
+    r.g = gemm_problem(d, pl, nullptr, wt, out);
+    r.g.mode = ACT_BLOCKED;
+    r.g.cb = cb;
+    r.g.Cb = (d->C + cb - 1) / cb;
+    r.g.depth = depth;
+    r.g.dil = dil;
+    r.g.out_nhwc = out_nhwc;
+    r.src = in;
+    r.N = d->N, r.C = d->C, r.H = d->H, r.W = d->W, r.pad = d->pad;
+    r.pixel_major = nhwc;
+    r.pixel_bytes = d->C;
+    r.block_bytes = raw ? (d->C + 15) / 16 * 16 : cb;   // a pixel's channels follow each other whatever the weights' block
+    r.img_bytes = (long long)d->C * d->H * d->W;
+    r.raw_weights = raw;
+    return r;
+}
+
+struct RouteKey {
+    conv_desc_t d;
+    int v[8];
+};
+
+// Which of them runs this call.  two_us: the estimate of the route there is without the resident kernel.
+template <typename TwoStage>
+Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool nhwc, int dil, const int8_t *wt, int32_t *out, bool out_nhwc,
+                 int tag, TwoStage &&two_us)
+{
+    static thread_local PlanTable<RouteKey, Route, 64> routes;
+    const RouteKey key{*d, {pl.layout, pl.cb, tag, (int)wt_is_packed, (int)nhwc * 2 + (int)out_nhwc, dil, (int)aligned16(wt),
+                            (int)(reinterpret_cast<uintptr_t>(out) & 63)}};
+    const Route *kept = routes.get(key, [&](Route *n) {
+        double best = two_us();
+        *n = Route{TWO_STAGE, {}, 0, 0};
+        auto consider = [&](int how, int cb, int depth, bool raw, double extra) {
+            ResidentChoice c;
+            const ResidentProblem r = resident_problem(d, pl, cb, depth, raw, nhwc, dil, nullptr, nullptr, out, out_nhwc);
+            if (!resident_pick(r, &c)) return;
+            // records of 128 channels and more leave one workgroup per compute unit; over many rounds the estimate, which
+            // was fitted to small and large layers alike, comes out 20 % low then (40 % from 256 channels on)
+            const double many = d->C > 112 && (double)pl.M * d->K > 256.0 * 64 * 128 ? d->C > 256 ? 1.4 : 1.25 : 1.0;
+            const double us = c.us * many + extra;
+            if (us < best) {
+                best = us;
+                *n = Route{how, c, cb, depth};
+            }
+        };
+        if (wt_is_packed) {
+            if (pl.layout == CONV_LAYOUT_PACKED || pl.layout == CONV_LAYOUT_PAD_ONLY) consider(DIRECT_AS_IS, pl.cb, pl.depth, false, 0);
+            return true;
+        }
+        const int C16 = round_up_i(d->C, 16);
+        const long long real = (long long)C16 * d->R * d->S;
+        if (real > (1LL << 20)) return true;
+        const int depth = round_up_i((int)real, CONV_DEPTH_ALIGN);
+        if (d->R == 1 && d->S == 1 && d->C % CONV_DEPTH_ALIGN == 0 && aligned16(wt)) consider(DIRECT_AS_IS, 64, d->C, false, 0);
+        else {
+            if (d->R == 3 && d->S == 3) consider(DIRECT_RAW, C16, depth, true, 0);
+            // the weights' own launch: 2.4-3.2 us up to a megabyte of them
+            if (C16 <= 1024) consider(DIRECT_REWRITE, C16, depth, false, 2.8 + 1.0e-6 * (double)d->K * depth + SECOND_LAUNCH_US);
+        }
+        return true;
+    });
+    return *kept;
+}
+
+// Runs a DIRECT_* route; ws: device memory for the rewritten weights (DIRECT_REWRITE), at least K * depth bytes.
+int run_direct(const Route &rt, const conv_desc_t *d, const Plan &pl, bool nhwc, int dil, const int8_t *in, const int8_t *wt, int32_t *out,
+               bool out_nhwc, void *ws, hipStream_t st)
+{
+    if (rt.how == DIRECT_REWRITE) {
+        if (launch_pack_weights_blocked(d->K, d->C, d->R, d->S, rt.cb, rt.depth, wt, static_cast<int8_t *>(ws), st) != hipSuccess)
+            return CONV_ERR_DEVICE;
+        wt = static_cast<const int8_t *>(ws);
+    }
+    return gemm_status(launch_resident(resident_problem(d, pl, rt.cb, rt.depth, rt.how == DIRECT_RAW, nhwc, dil, in, wt, out, out_nhwc), rt.pick, st));
+}
+size_t direct_bytes(const Route &rt, const conv_desc_t *d) { return rt.how == DIRECT_REWRITE ? (size_t)d->K * rt.depth : 0; }
+
+// The library's choice for a one-shot call whose selected layout is `layout` / `cb` (not IMPLICIT): pl gets the output
+// extents the resident kernel works from.
+int one_shot_route(const conv_desc_t *d, int layout, int cb, const int8_t *in, const int8_t *wt, int32_t *out, Plan *pl, Route *rt)
+{
+    const bool blocked = layout == CONV_LAYOUT_PACKED || layout == CONV_LAYOUT_PAD_ONLY;
+    int rc = make_plan(d, blocked ? layout : CONV_LAYOUT_PAD_ONLY, blocked ? cb : 0, pl);
+    if (rc != CONV_OK) {   // (an image too large for 32-bit offsets: only what the layout itself can do)
+        *rt = Route{TWO_STAGE, {}, 0, 0};
+        return CONV_OK;
+    }
+    const double in_bytes = (double)d->N * d->C * d->H * d->W;
+    *rt = pick_route(d, *pl, false, false, 1, wt, out, false, 4 + layout, [&] {
+        if (layout == CONV_LAYOUT_IMAGE_PACK) {   // two more launches and the packed image written and read once more
+            PackedProblem pp;
+            Plan inner;
+            if (image_pack_problem(d, cb, &pp) != CONV_OK || make_plan(&pp.d2, pp.inner_layout, pp.inner_cb, &inner) != CONV_OK) return 1e300;
+            const double pack = 5.0 + 0.25e-6 * (in_bytes + (double)pp.x2_bytes) + 2 * SECOND_LAUNCH_US;
+            if (inner.layout == CONV_LAYOUT_IMPLICIT) return pack + 4.0 + 0.25e-6 * ((double)pp.x2_bytes + 4.0 * pl->M * d->K);
+            return pack + two_stage_us(gemm_problem(&pp.d2, inner, nullptr, nullptr, out), (double)(pp.x2_bytes + inner.x_bytes), (double)inner.w_bytes, false);
+        }
+        Plan own;
+        if (make_plan(d, layout, cb, &own) != CONV_OK) return 1e300;
+        return two_stage_us(gemm_problem(d, own, nullptr, nullptr, out), in_bytes + (double)own.x_bytes, (double)own.w_bytes, false);
+    });
+    return CONV_OK;
 }
 
 int rewrite_weights(const conv_desc_t *d, const Plan &pl, const int8_t *wt, int8_t *dst, hipStream_t st)
@@ -642,6 +793,7 @@ int conv2d_int8_dilated(const conv_desc_t *desc, int dilation, int layout, int c
     DilatedProblem dp;
     int rc = dilated_problem(desc, dilation, &dp);
     if (rc != CONV_OK) return rc;
+    const bool library_chooses = layout == CONV_LAYOUT_AUTO;
     rc = resolve_layout(&dp.d2, &layout, &cb);
     if (rc != CONV_OK) return rc;
     if (!in || !wt || !out || !workspace || (reinterpret_cast<uintptr_t>(workspace) & (WS_ALIGN - 1)))
@@ -653,6 +805,16 @@ int conv2d_int8_dilated(const conv_desc_t *desc, int dilation, int layout, int c
     const bool stored = pl.layout == CONV_LAYOUT_IMPLICIT;  // else the GEMM stage's epilogue interleaves
     const size_t xb = align_up(dp.x2_bytes, WS_ALIGN), ob = stored ? align_up(dp.o2_bytes, WS_ALIGN) : 0;
     if (workspace_bytes < xb + ob + inner) return CONV_ERR_WORKSPACE;
+    Plan direct;
+    if (library_chooses && direct_dilated_plan(desc, dilation, 0, &direct) == CONV_OK) {
+        // the library's choice may also be the kernel that reads its taps `dilation` pixels apart from the image as it is
+        const Route rt = pick_route(desc, direct, false, false, dilation, wt, out, false, 3, [&] {
+            const double pack = 2.5 + 0.25e-6 * ((double)desc->N * desc->C * desc->H * desc->W + (double)dp.x2_bytes) + SECOND_LAUNCH_US;
+            return pack + two_stage_us(gemm_problem(&dp.d2, pl, nullptr, nullptr, nullptr), (double)dp.x2_bytes + (double)pl.x_bytes, (double)pl.w_bytes, false);
+        });
+        if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes)
+            return run_direct(rt, desc, direct, false, dilation, in, wt, out, false, workspace, (hipStream_t)stream);
+    }
     int8_t *x2 = static_cast<int8_t *>(workspace);
     void *ws = inner ? static_cast<void *>(x2 + xb + ob) : nullptr;
     rc = dilation_pack_int8(desc, dilation, in, x2, stream);
@@ -684,20 +846,6 @@ int conv2d_int8_dilated(const conv_desc_t *desc, int dilation, int layout, int c
     return rc == CONV_OK ? launch_choice(g, c, st) : rc;
 }
 
-// Dilation as an address multiplier: the plan of the undilated problem with the dilated layer's output extents.
-static int direct_dilated_plan(const conv_desc_t *desc, int dilation, int cb, Plan *pl)
-{
-    if (!desc || dilation <= 0) return CONV_ERR_INVALID_ARG;
-    int rc = make_plan(desc, CONV_LAYOUT_PACKED, cb, pl);
-    if (rc != CONV_OK) return rc;
-    const long long Re = (long long)dilation * (desc->R - 1) + 1, Se = (long long)dilation * (desc->S - 1) + 1;
-    if (Re > pl->Hp || Se > pl->Wp) return CONV_ERR_INVALID_ARG;
-    pl->P = (int)((pl->Hp - Re) / desc->stride + 1);
-    pl->Q = (int)((pl->Wp - Se) / desc->stride + 1);
-    pl->M = (long long)desc->N * pl->P * pl->Q;
-    return CONV_OK;
-}
-
 size_t conv2d_int8_dilated_direct_workspace_bytes(const conv_desc_t *desc, int dilation, int cb)
 {
     Plan pl;
@@ -716,6 +864,12 @@ int conv2d_int8_dilated_direct(const conv_desc_t *desc, int dilation, int cb, co
     const size_t xb = align_up(pl.x_bytes, WS_ALIGN);
     if (workspace_bytes < xb + align_up(pl.w_bytes, WS_ALIGN)) return CONV_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
+    const Route rt = pick_route(desc, pl, false, false, dilation, wt, out, false, 2, [&] {
+        GemmProblem g = gemm_problem(desc, pl, nullptr, nullptr, out);
+        g.dil = dilation;
+        return two_stage_us(g, (double)desc->N * desc->C * desc->H * desc->W + (double)pl.x_bytes, (double)pl.w_bytes, false);
+    });
+    if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, dilation, in, wt, out, false, workspace, st);
     int8_t *xq = static_cast<int8_t *>(workspace), *wq = xq + xb;
     const hipError_t e = launch_rewrite_fused(false, desc->N, desc->C, desc->H, desc->W, desc->K, desc->R, desc->S,
                                               desc->stride, desc->pad, pl.P, pl.Q, pl.cb, pl.depth, in, xq, wt, wq, st);
@@ -933,6 +1087,13 @@ int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb, const int8_t *in
     const size_t need = xb + (wt_is_packed ? 0 : align_up(pl.w_bytes, WS_ALIGN));
     if (workspace_bytes < need) return CONV_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
+    if (pl.layout != CONV_LAYOUT_IM2COL) {
+        const Route rt = pick_route(desc, pl, wt_is_packed != 0, false, 1, wt, out, false, 0, [&] {
+            return two_stage_us(gemm_problem(desc, pl, nullptr, nullptr, out), (double)desc->N * desc->C * desc->H * desc->W + (double)pl.x_bytes,
+                                (double)pl.w_bytes, wt_is_packed != 0);
+        });
+        if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, 1, in, wt, out, false, workspace, st);
+    }
     int8_t *xq = static_cast<int8_t *>(workspace);
     const int8_t *wq = wt;
     bool rewritten = false;
@@ -983,10 +1144,17 @@ int conv2d_int8(int N, int C, int H, int W, int K, int R, int S, int stride, int
         }
         return conv2d_int8_ex(&d, layout, 0, in, wt, 0, out, nullptr, 0, stream);
     }
+    // (the workspace rule is a property of the problem, whichever kernel the library then takes)
     void *ws = nullptr;
     size_t ws_bytes = 0;
     rc = cached_workspace(need, (hipStream_t)stream, &ws, &ws_bytes);
     if (rc != CONV_OK) return rc;
+    Route rt;
+    Plan pl;
+    rc = one_shot_route(&d, layout, cb, in, wt, out, &pl, &rt);
+    if (rc != CONV_OK) return rc;
+    if (rt.how != TWO_STAGE && direct_bytes(rt, &d) <= ws_bytes)
+        return run_direct(rt, &d, pl, false, 1, in, wt, out, false, ws, (hipStream_t)stream);
     return conv2d_int8_ex(&d, layout, cb, in, wt, 0, out, ws, ws_bytes, stream);
 }
 
@@ -1056,9 +1224,15 @@ int conv2d_int8_nhwc(int N, int C, int H, int W, int K, int R, int S, int stride
     const size_t need = xb + wb + ob;
     void *ws = nullptr;
     size_t ws_bytes = 0;
-    rc = cached_workspace(need, (hipStream_t)stream, &ws, &ws_bytes);
-    if (rc != CONV_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
+    const Route rt = pick_route(&d, pl, false, true, 1, wt, out, true, 1, [&] {
+        GemmProblem g = gemm_problem(&d, pl, nullptr, nullptr, out);
+        g.out_nhwc = 1;
+        return two_stage_us(g, (double)N * C * H * W + (double)pl.x_bytes, (double)pl.w_bytes, false) + (direct ? 0 : 10);
+    });
+    rc = cached_workspace(need, st, &ws, &ws_bytes);
+    if (rc != CONV_OK) return rc;
+    if (rt.how != TWO_STAGE && direct_bytes(rt, &d) <= ws_bytes) return run_direct(rt, &d, pl, true, 1, in, wt, out, true, ws, st);
     int8_t *xq = static_cast<int8_t *>(ws), *wq = xq + xb;
     int32_t *nkpq = reinterpret_cast<int32_t *>(wq + wb);
     const hipError_t e = launch_rewrite_fused_nhwc(N, C, H, W, K, R, S, pad, pl.cb, pl.depth, in, xq, wt, wq, st);

@@ -70,6 +70,24 @@ hipError_t launch_band_conv(const GemmProblem &g, hipStream_t st);
 // split_k > 1 clears `out` first and accumulates with atomics.
 hipError_t launch_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t st);
 
+// The GEMM stage that reads the network's own tensor (resident_mfma.hip): g as for the general kernel on a blocked
+// operand (weights in blocks of g.cb, taps g.dil apart), the activations from `src` instead of g.act.
+struct ResidentProblem {
+    GemmProblem g;
+    const int8_t *src;
+    int N, C, H, W, pad;
+    int pixel_major;     // a pixel's channels are contiguous (NHWC, or blocked): pixel_bytes apart, channel blocks block_bytes apart
+    int pixel_bytes, block_bytes;
+    long long img_bytes;
+    int raw_weights;     // g.wq is KCRS as it came (3 x 3 only), not in depth order
+};
+struct ResidentChoice {
+    int tile, mper;   // mper: output pixels of a workgroup
+    double us;        // estimated launch time
+};
+bool resident_pick(const ResidentProblem &r, ResidentChoice *c);   // false: outside the kernel's domain
+hipError_t launch_resident(const ResidentProblem &r, const ResidentChoice &c, hipStream_t st);
+
 // blocks x 4 waves x iters x 4 MFMA 32x32x32 i8 on register operands; out: blocks * 256 int32
 hipError_t launch_mfma_probe(int blocks, int iters, int32_t *out, hipStream_t st);
 

@@ -1222,3 +1222,41 @@ def test_im2col_from_nhwc(lib, cfg):
     onh = torch.empty((cfg.N, cfg.P, cfg.Q, cfg.K), dtype=torch.int32, device=DEV)
     lib.conv2d_int8_packed_nhwc(cfg.dims(), lib.LAYOUT_IM2COL, 0, A, B, onh)     # NHWC in, NHWC out
     assert np.array_equal(host(onh), layouts.unpack_nhwc(conv))
+
+
+# ---- the GEMM stage that blocks the channels on its way into LDS -------------------------------------------------
+# Shapes at its edges: channels that fill no quad, no 16-byte chunk and no 64-byte step; output channels around the tiles
+# of 32 and 64; tiles that span many small images; one pixel; pixels of no valid tap; strides; kernels of 1, 5 and 25 taps.
+RESIDENT_SHAPES = [
+    ConvShape("res-c17", 3, 17, 9, 11, 33, 3, 3, 1, 1), ConvShape("res-c66", 2, 66, 13, 10, 65, 3, 3, 2, 1),
+    ConvShape("res-c64-many", 70, 64, 3, 3, 64, 3, 3, 1, 1), ConvShape("res-c130", 2, 130, 8, 9, 96, 3, 3, 1, 1),
+    ConvShape("res-c35-5x5", 3, 35, 12, 7, 40, 5, 5, 1, 2), ConvShape("res-1x1-s2", 5, 64, 15, 15, 70, 1, 1, 2, 0),
+    ConvShape("res-one-pixel", 1, 40, 3, 3, 31, 3, 3, 1, 0), ConvShape("res-wide-border", 2, 24, 6, 6, 20, 3, 3, 3, 4),
+    ConvShape("res-5-taps", 2, 48, 9, 20, 32, 1, 5, 1, 2), ConvShape("res-plane-64b", 9, 64, 16, 16, 64, 3, 3, 1, 1),
+]
+
+
+@pytest.mark.parametrize("cfg", RESIDENT_SHAPES, ids=lambda c: c.name)
+@pytest.mark.parametrize("offset", [0, 3])
+def test_resident_stage(lib, cfg, offset):
+    x, w, want = oracle_conv(cfg)
+
+    def at(a):   # on the GPU, `offset` bytes behind an aligned address
+        t = torch.empty(a.size + offset, dtype=torch.int8, device=DEV)
+        t[offset:] = dev(a).view(-1)
+        return t[offset:].view(a.shape)
+
+    assert np.array_equal(host(lib.conv2d_int8(at(x), at(w), cfg.stride, cfg.pad)), want)
+    got = lib.conv2d_int8_nhwc(at(np.ascontiguousarray(x.transpose(0, 2, 3, 1))), at(w), cfg.stride, cfg.pad)
+    assert np.array_equal(host(got).transpose(0, 3, 1, 2), want)
+    for layout, cb in ((lib.LAYOUT_PACKED, 16), (lib.LAYOUT_PACKED, 64), (lib.LAYOUT_PAD_ONLY, 0)):
+        wq = lib.pack_weights(dev(w), layout, cb)
+        ws = torch.empty(max(256, lib.conv2d_int8_workspace_bytes(cfg.dims(), layout, cb, True)), dtype=torch.int8, device=DEV)
+        out = torch.full((cfg.N, cfg.K, cfg.P, cfg.Q), -7, dtype=torch.int32, device=DEV)
+        assert np.array_equal(host(lib.conv2d_int8_ex(cfg.dims(), layout, cb, at(x), wq, out, ws, wt_is_packed=True)), want), (layout, cb)
+    if cfg.stride == 1:
+        for d in (2, 3):
+            if cfg.H + 2 * cfg.pad >= d * (cfg.R - 1) + 1 and cfg.W + 2 * cfg.pad >= d * (cfg.S - 1) + 1:
+                want_d = direct.conv2d_int8_dilated(x, w, 1, cfg.pad, d)
+                assert np.array_equal(host(lib.conv2d_int8_dilated_direct(cfg.dims(), d, at(x), at(w))), want_d), d
+                assert np.array_equal(host(lib.conv2d_int8_dilated(cfg.dims(), d, at(x), at(w))), want_d), d
