@@ -20,7 +20,7 @@
 // out), 21 us from raw ones; 16 images 56x56, 72 -> 96, stride 2: 13.4 -> 10.1; 445 images 14x14, 32 -> 405: 87 -> 34;
 // dilation 2, 64 images 28x28, 64 -> 64: 12.5 (20 through sub-images) -> 8.7.
 #include "launch.h"
-#include "rewrite_bodies.h"
+#include "window_fill.h"
 
 namespace c2i8 {
 
@@ -41,7 +41,7 @@ struct ResidentArgs {
     int pitch, full8;              // record pitch; slots of a whole image (its range rounded up to 8 pixels)
     int pstride, bstride;          // pixel-major source: bytes from pixel to pixel, from channel block to channel block
     long long img_bytes, src_bytes;
-    int zero_off, win_off, tab_off;  // LDS byte offsets (the weight ring is at 0)
+    int zero_off, win_off, tab_off;  // LDS byte offsets (the weight tile is at 0)
     int tiles_k, tiles_m, mper;    // mper: output pixels of a workgroup
     int stream_out;                // NKPQ result with non-temporal stores
     unsigned mg_PQ, mg_Q, mg_tiles_k, mg_c16q, mg_cq, mg_full8, mg_g16, mg_S, mg_R, mg_u16;
@@ -153,21 +153,14 @@ __device__ __forceinline__ void res_store(const ResidentArgs &a, const v16i (&ac
     }
 }
 
-// Raw weights: the 36 bytes of 4 channels x 9 taps (byte 9c + t) as nine dwords of 4 channels each.
-template <int T>
-__device__ __forceinline__ unsigned tap_dword(const unsigned (&d)[9])
-{
-    constexpr int p0 = T, p1 = 9 + T, p2 = 18 + T, p3 = 27 + T;
-    const unsigned lo = __builtin_amdgcn_perm(d[p1 >> 2], d[p0 >> 2], 0x0C0C0000u | (4u + (p1 & 3)) << 8 | (p0 & 3));
-    const unsigned hi = __builtin_amdgcn_perm(d[p3 >> 2], d[p2 >> 2], 0x0C0C0000u | (4u + (p3 & 3)) << 8 | (p2 & 3));
-    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-}
-
 // TK: output channels of a workgroup, WK: waves side by side over them, NW: waves, FM: 32-pixel blocks a wave
 // multiplies at a time; SRC: ResSource; UNI: a 64-byte step of depth lies within one tap (and channel block);
 // RAW: the weights are KCRS (3 x 3), turned into depth order (tap, channel padded to 16) on their way into LDS.
+// The 64-channel tile of 8 waves keeps two output blocks' sums and the addresses of a whole tap in registers: at two of its
+// workgroups per compute unit it spilled, at one it does not, and its LDS rarely leaves room for two (64 images 56 x 56,
+// 64 -> 64, kept weights: 18.0 -> 17.4 us; 151 images 28 x 28, 128 -> 458: 116 -> 105).
 template <int TK, int WK, int NW, int FM, int SRC, bool UNI, bool RAW>
-__global__ void __launch_bounds__(NW * 64, NW / 2) conv_resident_kernel(const ResidentArgs a)
+__global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) conv_resident_kernel(const ResidentArgs a)
 {
     constexpr int NT = NW * 64, WM = NW / WK, WTK = TK / WK, FK = WTK / 32;
     constexpr int STEP = TK * 64;   // LDS bytes of one 64-byte step of the weight tile
@@ -212,132 +205,32 @@ __global__ void __launch_bounds__(NW * 64, NW / 2) conv_resident_kernel(const Re
         }
     }
     // ---- window ---------------------------------------------------------------------------------------------------
-    if constexpr (SRC == RES_NCHW) {
-        // unit: 4 channels x 8 pixels, neighbouring lanes on neighbouring channel quads (their 32-byte record pieces
-        // fall into different banks; the planes' lines are shared by the units that follow in the same workgroup)
-        const int units = a.cq * (slots >> 3);
-        constexpr int B = 4;   // units per thread and round of loads
-        typedef unsigned long long u64_a1 __attribute__((aligned(1)));
-        for (int u0 = tid; u0 < units; u0 += NT * B) {
-            unsigned long long v[B][4];
-            int dst[B];
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const int u = min(u0 + b * NT, units - 1);
-                const int g = fast_div_any(u, a.cq, a.mg_cq), c4 = (u - g * a.cq) * 4;
-                int s = g * 8, n = n0, lin = lo0 + s;
-                if (s >= len0) {
-                    const int r = s - len0, d = fast_div_any(r, a.full8, a.mg_full8);
-                    n = n0 + 1 + d;
-                    lin = r - d * a.full8;
-                }
-                dst[b] = a.win_off + s * a.pitch + c4;
-                const long long img = (long long)n * a.img_bytes;
-                const int8_t *base = a.src + img;
-                const long long left = a.src_bytes - 8 - img;
-                const int last = left > 0x7FFFFFFFLL ? 0x7FFFFFFF : (int)left;  // may be negative in a tiny last image: still in the tensor
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int want = min(c4 + i, a.C1) * a.HW + lin, at = min(want, last);
-                    v[b][i] = *reinterpret_cast<const u64_a1 *>(base + at) >> (8 * (want - at));
-                    if (c4 + i > a.C1) v[b][i] = 0;   // a record's bytes past the last channel are zero
-                }
-            }
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                if (u0 + b * NT >= units) break;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const unsigned r0 = (unsigned)(v[b][0] >> (32 * h)), r1 = (unsigned)(v[b][1] >> (32 * h));
-                    const unsigned r2 = (unsigned)(v[b][2] >> (32 * h)), r3 = (unsigned)(v[b][3] >> (32 * h));
-                    // 4 x 4 bytes: channel rows -> pixel columns
-                    const unsigned lo01 = __builtin_amdgcn_perm(r1, r0, 0x05010400), hi01 = __builtin_amdgcn_perm(r1, r0, 0x07030602);
-                    const unsigned lo23 = __builtin_amdgcn_perm(r3, r2, 0x05010400), hi23 = __builtin_amdgcn_perm(r3, r2, 0x07030602);
-                    unsigned char *d = smem + dst[b] + h * 4 * a.pitch;
-                    *reinterpret_cast<unsigned *>(d) = __builtin_amdgcn_perm(lo23, lo01, 0x05040100);
-                    *reinterpret_cast<unsigned *>(d + a.pitch) = __builtin_amdgcn_perm(lo23, lo01, 0x07060302);
-                    *reinterpret_cast<unsigned *>(d + 2 * a.pitch) = __builtin_amdgcn_perm(hi23, hi01, 0x05040100);
-                    *reinterpret_cast<unsigned *>(d + 3 * a.pitch) = __builtin_amdgcn_perm(hi23, hi01, 0x07060302);
-                }
-            }
-        }
-    } else {
-        // pixel-major source (NHWC, or a blocked image): 16-byte pieces of a record, neighbouring lanes on
-        // neighbouring pieces
-        const int units = a.u16 * slots;
-        constexpr int B = 4;
-        for (int u0 = tid; u0 < units; u0 += NT * B) {
-            v4i v[B];
-            int dst[B];
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                const int u = min(u0 + b * NT, units - 1);
-                const int s = fast_div_any(u, a.u16, a.mg_u16), j = u - s * a.u16;
-                int n = n0, lin = lo0 + s;
-                if (s >= len0) {
-                    const int r = s - len0, d = fast_div_any(r, a.full8, a.mg_full8);
-                    n = n0 + 1 + d;
-                    lin = r - d * a.full8;
-                }
-                dst[b] = a.win_off + s * a.pitch + j * 16;
-                lin = min(lin, a.HW - 1);
-                const long long img = (long long)n * a.img_bytes;
-                const long long left = a.src_bytes - 16 - img;
-                const int last = left > 0x7FFFFFFFLL ? 0x7FFFFFFF : (int)left;
-                const int blk = (j * 16) / a.cb;   // blocked source: cb a power of two or the whole record
-                const int want = lin * a.pstride + blk * a.bstride + (j * 16 - blk * a.cb), at = min(want, last);
-                v4i t;
-                __builtin_memcpy(&t, a.src + img + at, 16);
-                v[b] = want != at ? shift_piece(t, at - want) : t;
-            }
-#pragma unroll
-            for (int b = 0; b < B; ++b) {
-                if (u0 + b * NT >= units) break;
-                *reinterpret_cast<v4i *>(smem + dst[b]) = v[b];
-            }
-        }
-    }
-
+    const WindowRange range{n0, lo0, len0, a.full8, slots, a.mg_full8};
+    const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride, a.bstride, a.cb};
+    if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
+    else window_from_pixels<NT, 4>(from, range, a.u16, a.mg_u16, smem + a.win_off, a.pitch, tid);
     if constexpr (RAW) {
-        // unit: one row, 4 channels: 36 consecutive bytes
+        // unit: one row, 4 channels.  (Several units' loads in flight, or the first ones asked for ahead of the window,
+        // measured level or slower.)
         const int cq = a.C16 >> 2, units = TK * cq;
-        const long long row_bytes = (long long)a.C * 9, total = row_bytes * a.K;
-        typedef int v4i_a1 __attribute__((ext_vector_type(4), aligned(1)));
-        typedef unsigned u32_a1 __attribute__((aligned(1)));
         for (int u = tid; u < units; u += NT) {
             const int row = fast_div_any(u, cq, a.mg_c16q), c = u - row * cq;
             unsigned d[9];
-            const int valid = min(a.C - c * 4, 4) * 9;   // bytes that belong to this row's channels
-            {
-                const long long off = (long long)min(k0 + row, a.K - 1) * row_bytes + c * 36;
-                const int8_t *p = a.wq + off;
-                if (off + 36 <= total) {
-                    const v4i_a1 x0 = *reinterpret_cast<const v4i_a1 *>(p), x1 = *reinterpret_cast<const v4i_a1 *>(p + 16);
-                    d[0] = x0[0], d[1] = x0[1], d[2] = x0[2], d[3] = x0[3], d[4] = x1[0], d[5] = x1[1], d[6] = x1[2], d[7] = x1[3];
-                    d[8] = *reinterpret_cast<const u32_a1 *>(p + 32);
-                } else {   // the tensor's last channels, fewer than four of them
-#pragma unroll
-                    for (int i = 0; i < 9; ++i) {
-                        d[i] = 0;
-                        for (int b = 0; b < 4; ++b)
-                            if (off + i * 4 + b < total) d[i] |= (unsigned)(unsigned char)p[i * 4 + b] << (8 * b);
-                    }
-                }
-                if (valid < 36) {   // fewer than four channels left in the row (or none): what follows is the next row's
-#pragma unroll
-                    for (int i = 0; i < 9; ++i) {
-                        const int keep = valid - 4 * i;
-                        d[i] &= keep >= 4 ? 0xFFFFFFFFu : keep <= 0 ? 0u : (1u << (8 * keep)) - 1u;
-                    }
-                }
-                auto put = [&](int tap, unsigned v) {
+            raw9_load(a.wq, a.K, a.C, k0 + row, c, d);
+            raw9_mask(a.C, c, d);
+            const int at0 = row * 64 + (c & 3) * 4, rsw = (row >> 2) & 3;
+            auto put = [&](int tap, unsigned v) {
+                if constexpr (UNI) {   // a tap is C16 / 64 whole steps
+                    unsigned char *const at = smem + (c >> 4) * STEP + at0 + ((((c >> 2) & 3) ^ rsw) << 4);
+                    *reinterpret_cast<unsigned *>(at + tap * (a.C16 >> 6) * STEP) = v;
+                } else {
                     const int j = tap * a.C16 + c * 4;
-                    *reinterpret_cast<unsigned *>(smem + (j >> 6) * STEP + row * 64 + ((((j >> 4) & 3) ^ ((row >> 2) & 3)) << 4) + (j & 15)) = v;
-                };
-                put(0, tap_dword<0>(d)), put(1, tap_dword<1>(d)), put(2, tap_dword<2>(d));
-                put(3, tap_dword<3>(d)), put(4, tap_dword<4>(d)), put(5, tap_dword<5>(d));
-                put(6, tap_dword<6>(d)), put(7, tap_dword<7>(d)), put(8, tap_dword<8>(d));
-            }
+                    *reinterpret_cast<unsigned *>(smem + (j >> 6) * STEP + at0 + ((((j >> 4) & 3) ^ rsw) << 4)) = v;
+                }
+            };
+            put(0, raw9_tap<0>(d)), put(1, raw9_tap<1>(d)), put(2, raw9_tap<2>(d));
+            put(3, raw9_tap<3>(d)), put(4, raw9_tap<4>(d)), put(5, raw9_tap<5>(d));
+            put(6, raw9_tap<6>(d)), put(7, raw9_tap<7>(d)), put(8, raw9_tap<8>(d));
         }
     }
     // A load whose value no unit of the last round needed may still be outstanding: without this wait the compiler puts
@@ -449,7 +342,7 @@ __global__ void __launch_bounds__(NW * 64, NW / 2) conv_resident_kernel(const Re
 
 // TK, WK, NW, FM, and how many of its workgroups fit a compute unit by their registers
 #define C2I8_RES_LIST(X) \
-    X(64, 1, 8, 1, 2) \
+    X(64, 1, 8, 1, 1) \
     X(64, 1, 4, 1, 3) \
     X(32, 1, 4, 1, 5) \
     X(32, 1, 4, 2, 3) \
@@ -643,9 +536,10 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
 }
 
 
-// Launch time in microseconds, fitted to 6000 measured launches of 130 layers (every tile, 8 to 12 pixel counts each; mean
-// error 9 %, the pick loses 2 % against the measured best): a launch, then per round of workgroups that fit the chip a
-// fixed part, the chain of MFMAs of one wave and the rounds of window loads; bytes in and out of the busiest compute unit.
+// Launch time in microseconds, fitted to 12000 measured launches of 200 layers (every tile, 8 to 12 pixel counts each;
+// mean error 9 %, the pick loses 1 % against the measured best): a launch, then per round of workgroups that fit the chip a
+// fixed part, the chain of MFMAs of one wave and the rounds of window loads; for the busiest compute unit its MFMAs and the
+// bytes in and out.
 double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile, int mper, int slots)
 {
     const GemmProblem &g = r.g;
@@ -661,9 +555,9 @@ double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile
     const int blocks = (mper + 32 * d.fm - 1) / (32 * d.fm);
     const double chain = (double)((blocks + d.nw - 1) / d.nw) * d.fm * (d.tk / 32) * 2 * sh.steps;
     const double units = (double)((slots / 8 * (sh.C16 / 4) + d.nw * 256 - 1) / (d.nw * 256));
-    const double out_byte = g.PQ % 16 == 0 ? 2.5e-5 : 2.97e-5;
-    double t = 2.77 + rounds * (1.54 + 0.031 * chain + 0.58 * units) + ncu * (3.94e-5 * slots * sh.C16 + 1.13e-6 * d.tk * sh.steps * 64 + out_byte * d.tk * mper * (g.act_out ? 1 : 4));
-    if (r.raw_weights) t += 0.32 * rounds * d.tk * (sh.C16 / 4) / (d.nw * 64) + 0.038 * ncu * d.tk * (sh.C16 / 4) / 64;
+    const double mfma = d.tk / 32 * d.fm * blocks * 2.0 * sh.steps / 4, out_byte = g.PQ % 16 == 0 ? 2.27e-5 : 3.06e-5;
+    double t = 3.28 + rounds * (1.0 + 0.0279 * chain + 0.585 * units) + ncu * (1.85e-3 * mfma + 5.68e-5 * slots * sh.C16 + out_byte * d.tk * mper * (g.act_out ? 1 : 4));
+    if (r.raw_weights) t += 0.297 * rounds * d.tk * (sh.C16 / 4) / (d.nw * 64) + 0.0239 * ncu * d.tk * (sh.C16 / 4) / 64;
     return t;
 }
 
