@@ -325,9 +325,9 @@ double two_stage_us(const GemmProblem &g, double moved, double weights, bool wt_
     return us + SECOND_LAUNCH_US;
 }
 
-enum RouteHow : int { TWO_STAGE = 0, DIRECT_AS_IS = 1, DIRECT_RAW = 2, DIRECT_REWRITE = 3 };
+enum RouteHow : int { TWO_STAGE = 0, DIRECT_AS_IS = 1, DIRECT_RAW = 2, DIRECT_REWRITE = 3, DIRECT_BAND = 4 };
 struct Route {
-    int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones
+    int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones, band kernel on packed ones
     ResidentChoice pick;
     int cb, depth;       // block and row bytes of the weights it reads (DIRECT_REWRITE: PAD_ONLY's, what is rewritten)
 };
@@ -385,7 +385,12 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             }
         };
         if (wt_is_packed) {
-            if (pl.layout == CONV_LAYOUT_PACKED || pl.layout == CONV_LAYOUT_PAD_ONLY) consider(DIRECT_AS_IS, pl.cb, pl.depth, false, 0);
+            if (pl.layout == CONV_LAYOUT_PACKED || pl.layout == CONV_LAYOUT_PAD_ONLY) {
+                consider(DIRECT_AS_IS, pl.cb, pl.depth, false, 0);
+                double us;
+                if (!nhwc && dil == 1 && band_direct_us(resident_problem(d, pl, pl.cb, pl.depth, false, false, 1, nullptr, nullptr, out, out_nhwc), &us) && us < best)
+                    *n = Route{DIRECT_BAND, {}, pl.cb, pl.depth};
+            }
             return true;
         }
         const int C16 = round_up_i(d->C, 16);
@@ -412,7 +417,8 @@ int run_direct(const Route &rt, const conv_desc_t *d, const Plan &pl, bool nhwc,
             return CONV_ERR_DEVICE;
         wt = static_cast<const int8_t *>(ws);
     }
-    return gemm_status(launch_resident(resident_problem(d, pl, rt.cb, rt.depth, rt.how == DIRECT_RAW, nhwc, dil, in, wt, out, out_nhwc), rt.pick, st));
+    const ResidentProblem r = resident_problem(d, pl, rt.cb, rt.depth, rt.how == DIRECT_RAW, nhwc, dil, in, wt, out, out_nhwc);
+    return gemm_status(rt.how == DIRECT_BAND ? launch_band_direct(r, st) : launch_resident(r, rt.pick, st));
 }
 size_t direct_bytes(const Route &rt, const conv_desc_t *d) { return rt.how == DIRECT_REWRITE ? (size_t)d->K * rt.depth : 0; }
 

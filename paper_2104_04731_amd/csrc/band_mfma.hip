@@ -28,7 +28,7 @@
 // by the lanes' choice of source chunk, so the column-wise fragment reads spread over all banks.
 #include "kernels.h"
 #include "launch.h"
-#include "rewrite_bodies.h"
+#include "window_fill.h"
 
 #include <type_traits>
 
@@ -64,6 +64,11 @@ struct BandArgs {
     long long img_bytes;         // one image
     long long out_img;           // K*P*Q
     unsigned mg_Q, mg_bands, mg_tiles_k, mg_tiles_m, mg_CTN, mg_win_pieces;
+    // direct form: the activations are the network's own tensor (act: [N][C][H][W])
+    int C, H, W, HW, pad, R;
+    int pitch, zero_off, cq;     // record pitch, LDS offset of the record of zeros, channel quads of a record
+    unsigned mg_cq, mg_RS;
+    long long src_bytes;
     // window pixel offset of the wave's u-th group of depth steps (a group = the steps that share their
     // activation fragments: one step, or in the shifted-fragment form the taps of one kernel row):
     // its channel block's window + its kernel tap (row)
@@ -134,9 +139,16 @@ __device__ __forceinline__ void static_for(F &&f)
 // SROW: depth steps that share their activation fragments (1, or 3 = the taps of a kernel row in the
 // shifted-fragment form); GPW: such groups per wave; PB: pixel blocks per workgroup;
 // FULL: every wave multiplies exactly GPW groups (no test around a group).
-template <int SROW, int GPW, int PB, bool FULL>
+// DIRECT (shifted-fragment form): the window is filled from the network's own NCHW tensor -- the band's input rows as they
+// are, without border, as pixel-major records of all channels (window_fill.h); a lane whose input column or row lies
+// outside the image reads a record of zeros.  This wave's weights are asked for first, then the window; both latencies are
+// paid once, the rewrite's launch and its image not at all (packed weights, two launches in a graph -> one: 1 x 128 x 28 x
+// 28 -> 128 6.9 -> 5.7 us, 13 x 256 x 9 x 9 -> 124 8.7 -> 6.7, 32 x 256 x 8 x 8 -> 128 7.8 -> 6.6).  Measured and not taken:
+// the weights straight into registers (7.1 -> 8.3 us at 256 channels), eight window units in flight per thread (level).
+template <int SROW, int GPW, int PB, bool FULL, bool DIRECT>
 __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const BandArgs a)
 {
+    static_assert(!DIRECT || SROW == 3, "the direct form is a shifted-fragment form");
     constexpr int KPW = SROW * GPW;  // depth steps per wave
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
@@ -150,6 +162,10 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     asm volatile("" : : "s"(a.win_pieces), "s"(a.win_total), "s"(a.win_per_wave), "s"(a.wave_region), "s"(a.tiles_k),
                  "s"(a.tiles_m), "s"(a.m_fastest), "s"(a.xk), "s"(a.bk), "s"(a.bm), "s"(a.mg_bk), "s"(a.mg_per), "s"(a.blk_bytes), "s"(a.img_bytes), "s"(a.out_img), "s"(a.mg_Q),
                  "s"(a.mg_bands), "s"(a.mg_tiles_k), "s"(a.mg_tiles_m), "s"(a.mg_CTN), "s"(a.mg_win_pieces));
+
+    if constexpr (DIRECT)
+        asm volatile("" : : "s"(a.C), "s"(a.H), "s"(a.W), "s"(a.HW), "s"(a.pad), "s"(a.R), "s"(a.pitch), "s"(a.zero_off), "s"(a.cq),
+                     "s"(a.mg_cq), "s"(a.mg_RS), "s"(a.src_bytes));
 
     // workgroup -> (32 output channels, image, band)
     const int lid = band_xcd_id(blockIdx.x, gridDim.x);
@@ -175,7 +191,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     const int nks = max(0, min(a.kpw, a.ksteps - js));  // depth steps of this wave
     const int ng = nks / SROW;                          // groups of them (whole groups by construction)
 
-    const int wave_off = wave * a.wave_region, win_off = BAND_WAVES * a.wave_region;  // LDS byte offsets
+    const int wave_off = wave * a.wave_region, win_off = DIRECT ? a.zero_off + 64 : BAND_WAVES * a.wave_region;  // LDS byte offsets
 
     // A transfer moves 16 rows x 64 B; lane l lands at row l/4, position l%4 and fetches the chunk that
     // belongs there after the swizzle.
@@ -183,7 +199,25 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     const int lane_part = lrow * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4);
 
     // ---- window: every wave fetches a contiguous quarter of the pieces of all channel blocks' windows ----
-    {
+    int lo0 = 0;
+    if constexpr (DIRECT) {
+        const int y0 = max(p0 - a.pad, 0), y1 = min(p0 + a.PT - 1 - a.pad + a.R, a.H);   // input rows of the band
+        lo0 = (y0 * a.W) & ~7;
+        const int slots = max((y1 * a.W - lo0 + 7) & ~7, 0);
+        const WindowRange range{n, lo0, slots, 8, slots, 0};
+        const WindowSource from{a.act, (long long)a.C * a.HW, a.src_bytes, a.C - 1, a.HW, a.C, 16, 16};
+        const unsigned row_lo = (unsigned)(min(k0 + lrow, a.K - 1) * a.depth) + (unsigned)(lane_part & 63);
+        const unsigned row_hi = (unsigned)(min(k0 + 16 + lrow, a.K - 1) * a.depth) + (unsigned)(lane_part & 63);
+#pragma unroll
+        for (int t = 0; t < KPW; ++t)   // all waves' steps one after the other, 2 KB each
+            if (t < nks) {
+                const int8_t *step = a.wq + (size_t)(js + t) * 64;
+                band_dma16(step, row_lo, lds0 + (unsigned)((js + t) * 2) * 1024u);
+                band_dma16(step, row_hi, lds0 + (unsigned)((js + t) * 2 + 1) * 1024u);
+            }
+        window_from_nchw<BAND_WAVES * 64, 4>(from, range, a.cq, a.mg_cq, smem + win_off, a.pitch, threadIdx.x);
+        if (threadIdx.x < 16) *reinterpret_cast<unsigned *>(smem + a.zero_off + threadIdx.x * 4) = 0;
+    } else {
         const int last = a.blk_bytes - 16;  // rows past the padded image (a short last band) read this
         const int per = a.win_per_wave, g0 = wave * per, g1 = min(g0 + per, a.win_total);
         int b = bdiv_small(g0, a.mg_win_pieces), i = g0 - b * a.win_pieces;  // channel block, piece of its window
@@ -206,6 +240,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     // ---- where the lane's pixel of every block sits in a window (tap (0, 0)) ---------------------------
     const int col = lane & 15, grp = lane >> 4;  // pixel within a block / 16-byte chunk of a depth step
     int wbase[PB];
+    if constexpr (!DIRECT)
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb) {
         if (SROW > 1) {  // block = 16 consecutive input columns of one window row
@@ -221,7 +256,26 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     // ---- this wave's weights: exactly 2*KPW transfers (steps past the last repeat it), and in between
     // the LDS addresses of the main loop: one register per group and pixel block ---------------------------
     int baddr[GPW][PB];
-    {
+    if constexpr (DIRECT) {
+        int pr[PB], x[PB];
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+            pr[pb] = bdiv_small(pb, a.mg_CTN);
+            x[pb] = (pb - pr[pb] * a.CTN) * a.CT + col - a.pad;
+        }
+#pragma unroll
+        for (int u = 0; u < GPW; ++u) {
+            const int j = min(js + u * SROW, a.ksteps - 1);   // (uniform) first step of the group: channel block b, kernel row r
+            const int b = bdiv_small(j, a.mg_RS), r = (j - b * a.R * 3) / 3;
+#pragma unroll
+            for (int pb = 0; pb < PB; ++pb) {
+                const int y = p0 + pr[pb] - a.pad + r;
+                const bool inside = pr[pb] < a.PT && (unsigned)y < (unsigned)a.H && (unsigned)x[pb] < (unsigned)a.W;
+                baddr[u][pb] = inside ? win_off + (y * a.W + x[pb] - lo0) * a.pitch + b * 64 + grp * 16 : a.zero_off;
+                asm volatile("" : "+v"(baddr[u][pb]));
+            }
+        }
+    } else {
         const unsigned row_lo = (unsigned)(min(k0 + lrow, a.K - 1) * a.depth) + (unsigned)(lane_part & 63);
         const unsigned row_hi = (unsigned)(min(k0 + 16 + lrow, a.K - 1) * a.depth) + (unsigned)(lane_part & 63);
         const unsigned dst = lds0 + (unsigned)wave_off;
@@ -241,7 +295,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
             }
         }
     }
-    const int afrag = wave_off + col * 64 + ((grp ^ ((col >> 2) & 3)) << 4);  // weight fragment: row col, chunk grp
+    const int afrag = (DIRECT ? js * 2048 : wave_off) + col * 64 + ((grp ^ ((col >> 2) & 3)) << 4);  // weight fragment: row col, chunk grp
     // (every address is a multiple of 16: say so, or the reads are split into dword pairs)
     auto read_a = [&](int t, int rb) -> v4i {
         return *reinterpret_cast<const v4i *>(__builtin_assume_aligned(smem + afrag + (t * 2 + rb) * 1024, 16));
@@ -256,7 +310,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
 #pragma unroll
         for (int pb = 0; pb < PB; ++pb) acc[rb][pb] = v4i{0, 0, 0, 0};
 
-    band_wait_dma<2 * KPW>();  // every window piece this wave asked for has landed ...
+    band_wait_dma<DIRECT ? 0 : 2 * KPW>();  // every window piece this wave asked for has landed ...
     band_barrier();            // ... and everyone else's
 
     // ---- main loop: no barrier.  All activation fragments of group u+1 are requested before group u
@@ -264,7 +318,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     v4i af[2][2], bq[2][PB];
 #pragma unroll
     for (int pb = 0; pb < PB; ++pb) bq[0][pb] = read_b(0, pb);
-    band_wait_dma<2 * (KPW - 1)>();
+    if constexpr (!DIRECT) band_wait_dma<2 * (KPW - 1)>();
     af[0][0] = read_a(0, 0);
     af[0][1] = read_a(0, 1);
     static_for<0, GPW>([&](auto uc) {
@@ -292,7 +346,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
                     if constexpr (t + 1 < KPW) {
                         if (pb == PB / 2) {
                             __builtin_amdgcn_sched_barrier(0);  // the MFMAs above stay above the wait
-                            band_wait_dma<2 * (KPW - 2 - t)>();
+                            if constexpr (!DIRECT) band_wait_dma<2 * (KPW - 2 - t)>();
                             af[(t + 1) & 1][0] = read_a(t + 1, 0);
                             af[(t + 1) & 1][1] = read_a(t + 1, 1);
                             __builtin_amdgcn_sched_barrier(0);
@@ -307,6 +361,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     // spent weights); block i = rb*PB + pb is then summed and stored by wave i%4, which finds it by address --
     // no test on a register index anywhere. ------------------------------------------------------------------
     band_wait_dma<0>();  // transfers of steps this wave did not multiply must not land on partial sums
+    if constexpr (DIRECT) band_barrier();   // (the regions are not the waves' own there)
     {
         v4i *const mine = reinterpret_cast<v4i *>(__builtin_assume_aligned(smem + wave_off, 16));
 #pragma unroll
@@ -457,8 +512,8 @@ struct BandPlan {
 
 unsigned magic_of(long long d) { return d <= 1 ? 0u : (unsigned)((0x100000000ULL + (unsigned long long)d - 1) / (unsigned long long)d); }
 
-// Fills the plan; false where the kernel does not apply.
-bool band_plan(const GemmProblem &g, BandPlan *bp)
+// Fills the plan; false where the kernel does not apply.  direct: the activations are the network's own tensor (r->g is g).
+bool band_plan(const GemmProblem &g, BandPlan *bp, const ResidentProblem *r = nullptr)
 {
     if (g.mode != ACT_BLOCKED || g.cb != 64 || g.il_d) return false;
     if (g.act_out && (g.o_cb < 4 || (g.o_cb & (g.o_cb - 1)))) return false;
@@ -499,8 +554,22 @@ bool band_plan(const GemmProblem &g, BandPlan *bp)
     const long long WR = (long long)(PT - 1) * g.stride + (long long)(g.R - 1) * dil + 1;
     const long long win_pieces = (WR * g.Wp + 15) / 16;
     const long long red = (2LL * PB + BAND_WAVES - 1) / BAND_WAVES * BAND_WAVES * 1024, wbytes = (long long)KPW * 2048;  // whole slots
-    const long long wave_region = red > wbytes ? red : wbytes;
-    const long long lds = BAND_WAVES * wave_region + g.Cb * win_pieces * 1024;
+    long long wave_region = red > wbytes ? red : wbytes, wbytes_all = 0;
+    long long lds = BAND_WAVES * wave_region + g.Cb * win_pieces * 1024;
+    int pitch = 0;
+    if (r) {
+        if (!tiled || r->raw_weights || r->pixel_major) return false;
+        // 32-bit offsets inside an image; 8- and 16-byte loads clamped to the tensor
+        if (r->img_bytes > 0x7FFFFFFFLL || (long long)r->H * r->W > (1LL << 28) || (long long)r->N * r->img_bytes < 64) return false;
+        const int C16 = (r->C + 15) / 16 * 16;
+        pitch = (C16 / 16 | 1) * 16;
+        const long long rows = PT - 1 + g.R < r->H ? PT - 1 + g.R : r->H;
+        // the weights of all steps one after the other, later the waves' partial sums
+        wave_region = red;
+        wbytes_all = (ksteps + KPW) * 2048;   // (a wave reads KPW steps: past its last one they are not multiplied)
+        lds = wbytes_all + 64 + ((rows * r->W + 14) & ~7LL) * pitch + 64;   // zeros, window, a last block read past its channels
+        if (lds < BAND_WAVES * red) lds = BAND_WAVES * red;
+    }
     if (lds > (long long)BAND_LDS_LIMIT) return false;
     const long long bands = (P + PT - 1) / PT;
     const long long tiles_k = (g.K + BAND_TK - 1) / BAND_TK, tiles_m = (long long)N * bands;
@@ -510,10 +579,24 @@ bool band_plan(const GemmProblem &g, BandPlan *bp)
     if ((long long)g.K * g.depth > 0x7FFFFFFFLL || (long long)g.K * P * Q > 0x3FFFFFFFLL) return false;  // 32-bit offsets
 
     BandArgs &a = bp->a;
-    a.act = g.act;
+    a.act = r ? r->src : g.act;
     a.wq = g.wq;
     a.out = g.out;
     a.out_nhwc = g.out_nhwc;
+    if (r) {
+        a.C = r->C;
+        a.H = r->H;
+        a.W = r->W;
+        a.HW = r->H * r->W;
+        a.pad = r->pad;
+        a.R = g.R;
+        a.pitch = pitch;
+        a.zero_off = (int)wbytes_all;
+        a.cq = (r->C + 15) / 16 * 4;
+        a.mg_cq = magic_of(a.cq);
+        a.mg_RS = magic_of(g.R * g.S);
+        a.src_bytes = r->img_bytes * r->N;
+    }
     a.out_wide_k = g.K % 4 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 15) == 0;
     a.aout = ActOut{};
     if (g.act_out) {
@@ -614,10 +697,10 @@ bool band_plan(const GemmProblem &g, BandPlan *bp)
     return true;
 }
 
-template <int SROW, int GPW, int PB, bool FULL>
+template <int SROW, int GPW, int PB, bool FULL, bool DIRECT>
 hipError_t launch_band(const BandPlan &bp, hipStream_t st)
 {
-    auto kern = conv_band_kernel<SROW, GPW, PB, FULL>;
+    auto kern = conv_band_kernel<SROW, GPW, PB, FULL, DIRECT>;
     static bool raised = false;  // dynamic-LDS ceiling granted, per instantiation
     if (bp.lds > 64 * 1024 && !raised) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -664,6 +747,11 @@ double band_cost(const GemmProblem &g)
     return 1800.0 + (bytes / 40.0 > mfma ? bytes / 40.0 : mfma) + 1800.0;
 }
 
+#define C2I8_BAND_CASE(SROW, GPW, PB)                       \
+    if (bp.srow == SROW && bp.gpw == GPW && bp.pb == PB)    \
+        return bp.full ? launch_band<SROW, GPW, PB, true, DIRECT>(bp, st) : launch_band<SROW, GPW, PB, false, DIRECT>(bp, st);
+#define C2I8_BAND_PBS(SROW, GPW) C2I8_BAND_CASE(SROW, GPW, 4) C2I8_BAND_CASE(SROW, GPW, 7) C2I8_BAND_CASE(SROW, GPW, 8)
+
 hipError_t launch_band_conv(const GemmProblem &g, hipStream_t st)
 {
     // the plan (a table entry per workgroup among it) is kept per problem; the operands are this call's
@@ -675,15 +763,48 @@ hipError_t launch_band_conv(const GemmProblem &g, hipStream_t st)
     bp.a.wq = g.wq;
     bp.a.out = g.out;
     bp.a.aout.out = g.act_out;
-#define C2I8_BAND_CASE(SROW, GPW, PB)                       \
-    if (bp.srow == SROW && bp.gpw == GPW && bp.pb == PB)    \
-        return bp.full ? launch_band<SROW, GPW, PB, true>(bp, st) : launch_band<SROW, GPW, PB, false>(bp, st);
-#define C2I8_BAND_PBS(SROW, GPW) C2I8_BAND_CASE(SROW, GPW, 4) C2I8_BAND_CASE(SROW, GPW, 7) C2I8_BAND_CASE(SROW, GPW, 8)
+    constexpr bool DIRECT = false;
     C2I8_BAND_PBS(1, 3) C2I8_BAND_PBS(1, 6) C2I8_BAND_PBS(1, 9) C2I8_BAND_PBS(1, 12)
     C2I8_BAND_PBS(3, 1) C2I8_BAND_PBS(3, 2) C2I8_BAND_PBS(3, 3) C2I8_BAND_PBS(3, 4)
-#undef C2I8_BAND_PBS
-#undef C2I8_BAND_CASE
     return hipErrorInvalidValue;
 }
+
+// ---- the same on the network's own tensor ---------------------------------------------------------------------------
+// Launch time in microseconds, fitted to 60 launches of grids up to 512 workgroups (mean error 5 %): MFMAs, window bytes and
+// rounds of window loads of the busiest compute unit.  Larger grids pay the window of all channels again in every workgroup
+// (32 x 256 x 14 x 14 -> 512: 31 us against 20 in two launches): not taken.
+bool band_direct_us(const ResidentProblem &r, double *us)
+{
+    if (r.g.cb != 64) return false;
+    BandPlan bp;
+    if (!band_plan(r.g, &bp, &r) || bp.grid > 512) return false;
+    const BandArgs &a = bp.a;
+    const int rows = std::min(a.PT - 1 + a.R, a.H), slots = (rows * a.W + 14) & ~7;
+    const double ncu = (bp.grid + 255) / 256, units = (a.cq * (slots / 8) + 1023) / 1024;
+    *us = 4.1 + ncu * (0.0194 * bp.srow * bp.gpw * bp.pb * 2 + 5.24e-5 * a.cq * 4 * slots + 0.12 * units + (a.C % 16 ? 0.43 * units : 0));
+    return true;
+}
+
+hipError_t launch_band_direct(const ResidentProblem &r, hipStream_t st)
+{
+    struct Key {
+        GemmKey g;
+        int v[5];
+    };
+    static thread_local PlanTable<Key, BandPlan, 16> plans;
+    const Key key{gemm_key(r.g), {r.N, r.C, r.H, r.W, r.pad}};
+    const BandPlan *kept = plans.get(key, [&](BandPlan *p) { return band_plan(r.g, p, &r); });
+    if (!kept) return hipErrorInvalidValue;
+    BandPlan bp = *kept;
+    bp.a.act = r.src;
+    bp.a.wq = r.g.wq;
+    bp.a.out = r.g.out;
+    bp.a.aout.out = r.g.act_out;
+    constexpr bool DIRECT = true;
+    C2I8_BAND_PBS(3, 1) C2I8_BAND_PBS(3, 2) C2I8_BAND_PBS(3, 3) C2I8_BAND_PBS(3, 4)
+    return hipErrorInvalidValue;
+}
+#undef C2I8_BAND_PBS
+#undef C2I8_BAND_CASE
 
 }  // namespace c2i8

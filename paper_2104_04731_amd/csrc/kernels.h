@@ -87,6 +87,9 @@ struct ResidentChoice {
 };
 bool resident_pick(const ResidentProblem &r, ResidentChoice *c);   // false: outside the kernel's domain
 hipError_t launch_resident(const ResidentProblem &r, const ResidentChoice &c, hipStream_t st);
+// The band kernel on the same problem (NCHW, weights in blocks of 64): estimated launch time; false: not its domain.
+bool band_direct_us(const ResidentProblem &r, double *us);
+hipError_t launch_band_direct(const ResidentProblem &r, hipStream_t st);
 
 // blocks x 4 waves x iters x 4 MFMA 32x32x32 i8 on register operands; out: blocks * 256 int32
 hipError_t launch_mfma_probe(int blocks, int iters, int32_t *out, hipStream_t st);

@@ -1260,3 +1260,24 @@ def test_resident_stage(lib, cfg, offset):
                 want_d = direct.conv2d_int8_dilated(x, w, 1, cfg.pad, d)
                 assert np.array_equal(host(lib.conv2d_int8_dilated_direct(cfg.dims(), d, at(x), at(w))), want_d), d
                 assert np.array_equal(host(lib.conv2d_int8_dilated(cfg.dims(), d, at(x), at(w))), want_d), d
+
+
+# Kept weights in blocks of 64, 3-tap rows, small grids: the band kernel on the network's own tensor.
+BAND_DIRECT_SHAPES = [
+    ConvShape("band-c109", 2, 109, 10, 10, 61, 3, 3, 1, 1), ConvShape("band-c257", 7, 257, 8, 8, 70, 3, 3, 1, 1),
+    ConvShape("band-c256-wide", 1, 256, 3, 100, 33, 3, 3, 1, 1), ConvShape("band-no-border", 3, 256, 14, 14, 64, 3, 3, 1, 0),
+    ConvShape("band-border-3", 1, 260, 4, 4, 40, 3, 3, 1, 3), ConvShape("band-one-row", 1, 320, 20, 20, 32, 1, 3, 1, 1),
+    ConvShape("band-whole", 1, 128, 28, 28, 128, 3, 3, 1, 1), ConvShape("band-two-bands", 1, 192, 13, 9, 40, 3, 3, 1, 2),
+]
+
+
+@pytest.mark.parametrize("cfg", BAND_DIRECT_SHAPES, ids=lambda c: c.name)
+@pytest.mark.parametrize("offset", [0, 3])
+def test_band_direct(lib, cfg, offset):
+    x, w, want = oracle_conv(cfg)
+    t = torch.empty(x.size + offset, dtype=torch.int8, device=DEV)
+    t[offset:] = dev(x).view(-1)
+    wq = lib.pack_weights(dev(w), lib.LAYOUT_PACKED, 64)
+    ws = torch.empty(max(256, lib.conv2d_int8_workspace_bytes(cfg.dims(), lib.LAYOUT_PACKED, 64, True)), dtype=torch.int8, device=DEV)
+    out = torch.full((cfg.N, cfg.K, cfg.P, cfg.Q), -7, dtype=torch.int32, device=DEV)
+    assert np.array_equal(host(lib.conv2d_int8_ex(cfg.dims(), lib.LAYOUT_PACKED, 64, t[offset:].view(x.shape), wq, out, ws, wt_is_packed=True)), want)
