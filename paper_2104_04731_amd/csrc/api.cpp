@@ -285,7 +285,7 @@ int choose_gemm_unsplit(const GemmProblem &g, GemmChoice *c)
         int t = -1, s = 1;
         double cost = 0;
         const bool tiled = gemm_pick(g, &t, &s, &cost);
-        if (band_applies(g) && (!tiled || band_cost(g) < cost)) *n = GemmChoice{CONV_TILE_BAND, 1, 0};
+        if (band_applies(g) && (!tiled || band_cost(g) < cost)) *n = GemmChoice{CONV_TILE_BAND, 1, band_cost(g)};
         else *n = GemmChoice{t, 1, cost};
         return tiled || n->tile == CONV_TILE_BAND;
     });
@@ -308,20 +308,20 @@ int run_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t st)
 }
 
 // ---- two-stage path or the GEMM stage that blocks the channels itself (resident_mfma.hip) -----------------------------
-// Estimated times in microseconds.  Two-stage, fitted to 193 layers of 3 us to 300 us (mean error 11 %, the choice between
-// the two paths loses 1.3 % against the measured better one): the launches, the GEMM stage's model (the general kernel's
-// and the band kernel's cycles are different scales), the rewritten tensors written and read.  A second launch costs the
-// stream about a microsecond more than it costs a graph, in which both models were measured.
+// Estimated times in microseconds.  Two-stage, fitted to 188 layers of 5 us to 300 us (mean error 9 %, the choice between
+// the paths loses 1.3 % against the measured best one): the launches, the GEMM stage's own estimate, the rewritten tensors
+// written and read.  A second launch costs the stream about a microsecond more than it costs a graph, in which all of these
+// estimates were measured.
 constexpr double SECOND_LAUNCH_US = 1.0;
 double two_stage_us(const GemmProblem &g, double moved, double weights, bool wt_is_packed)
 {
     GemmChoice c;
     if (choose_gemm(g, -1, 0, &c) != CONV_OK) return 1e300;
     const double us = c.tile == CONV_TILE_BAND
-                          ? wt_is_packed ? 3.3 + 0.80e-3 * c.cost + 0.027e-6 * moved + 0.36e-6 * weights
-                                         : 2.2 + 1.08e-3 * c.cost + 1.18e-6 * weights
-                          : wt_is_packed ? 4.88 + 0.274e-3 * c.cost + 0.264e-6 * moved + 1.48e-6 * weights
-                                         : 5.68 + 0.277e-3 * c.cost + 0.247e-6 * moved + 2.48e-6 * weights;
+                          ? wt_is_packed ? 2.1 + 0.96 * c.cost + 0.157e-6 * moved + 0.44e-6 * weights
+                                         : 2.2 + 1.03 * c.cost + 0.117e-6 * moved + 1.27e-6 * weights
+                          : wt_is_packed ? 2.4 + 1.01 * c.cost + 0.187e-6 * moved + 0.29e-6 * weights
+                                         : 3.3 + 1.02 * c.cost + 0.166e-6 * moved + 1.1e-6 * weights;
     return us + SECOND_LAUNCH_US;
 }
 
@@ -376,8 +376,9 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             const ResidentProblem r = resident_problem(d, pl, cb, depth, raw, nhwc, dil, nullptr, nullptr, out, out_nhwc);
             if (!resident_pick(r, &c)) return;
             // records of 128 channels and more leave one workgroup per compute unit; over many rounds the estimate, which
-            // was fitted to small and large layers alike, comes out 15 % low then (and 5 % in any grid from 200 channels on)
-            const double many = (d->C > 112 && (double)pl.M * d->K > 256.0 * 64 * 128 ? 1.15 : 1.0) * (d->C >= 200 ? 1.05 : 1.0);
+            // was fitted to small and large layers alike, comes out 15 % low then (and 5 % in any grid from 200 channels on,
+            // 10 % with raw weights)
+            const double many = (d->C > 112 && (double)pl.M * d->K > 256.0 * 64 * 128 ? 1.15 : 1.0) * (d->C < 200 ? 1.0 : raw ? 1.1 : 1.05);
             const double us = c.us * many + extra;
             if (us < best) {
                 best = us;

@@ -30,6 +30,8 @@
 #include "launch.h"
 #include "window_fill.h"
 
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 namespace c2i8 {
@@ -732,19 +734,19 @@ TileInfo band_tile_info(const GemmProblem &g)
     return TileInfo{BAND_TK, bp.pb * 16, BAND_WAVES * 64, 1};
 }
 
-// The picker's estimate (core cycles, same scale as gemm_pick's).  Measured: the kernel wins where one round of
-// workgroups covers the problem and -- in the form without shifted fragments -- the reduction is deep enough to
-// pay for its fixed parts (address set-up, summing the waves' partial results); with more rounds the general
-// kernel's large tiles move fewer bytes per MAC.
+// The picker's estimate in microseconds, on gemm_pick's scale: fitted to 456 launches (mean error 6 %; the choice between
+// the two kernels loses 1.6 % against the measured better one): a launch, per round of workgroups a fixed part (address
+// set-up, summing the waves' partial results), the operands' bytes, the waves' MFMAs and the bytes stored.
 double band_cost(const GemmProblem &g)
 {
     BandPlan bp;
     if (!band_plan(g, &bp)) return 1e300;
     const BandArgs &a = bp.a;
-    if (bp.grid > 256 || (bp.srow == 1 && a.ksteps < 18)) return 1e300;
-    const double bytes = (double)a.win_total * 1024 + (double)BAND_TK * a.depth;
-    const double mfma = (double)a.kpw * bp.pb * 2 * 25.0;
-    return 1800.0 + (bytes / 40.0 > mfma ? bytes / 40.0 : mfma) + 1800.0;
+    const double bytes = (double)a.win_total * 1024 + (double)BAND_TK * a.depth, out = (double)a.PT * a.Q * BAND_TK * (g.act_out ? 1 : 4);
+    const long long fit = std::max<long long>(1, (long long)(BAND_LDS_LIMIT / bp.lds)), per = (bp.grid + 255) / 256;
+    const double res = (double)std::min(fit, per);   // workgroups sharing a compute unit
+    const double rounds = bp.grid <= 512 * fit ? std::ceil(bp.grid / (256.0 * res)) : bp.grid / (256.0 * res) + 0.3;
+    return 2.9 + rounds * (1.52 + (bp.srow == 1 ? 0.31 : 0) + res * (1.3e-6 * bytes + 0.0162 * bp.srow * bp.gpw * bp.pb * 2 + (g.PQ % 16 == 0 ? 4.83e-6 : 2.16e-5) * out));
 }
 
 #define C2I8_BAND_CASE(SROW, GPW, PB)                       \

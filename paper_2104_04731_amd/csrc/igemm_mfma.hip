@@ -21,6 +21,7 @@
 #include "kernels.h"
 #include "launch.h"
 
+#include <cmath>
 #include <type_traits>
 
 namespace c2i8 {
@@ -677,55 +678,58 @@ __global__ void __launch_bounds__((WK * WM * DS + HELP) * 64, (WK * WM * DS + HE
 // ---- tile table -----------------------------------------------------------------------
 struct TileDef {
     int tk, tm, wk, wm, ks, nstage, help, ds, wpc;
+    double start, alone, shared;   // gemm_pick's microseconds
 };
-// One row per kernel instantiation: TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC.  The table the picker reads and
-// the launch switch are both generated from this list, so a tile index means the same thing in both.
+// One row per kernel instantiation: TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, and what gemm_pick reckons with: a
+// workgroup's fixed part, the chain of its 64-byte depth step, and the work of a step where several workgroups share
+// a compute unit.  The table the picker reads and the launch switch are both generated from this list, so a tile index
+// means the same thing in both.
 #define C2I8_TILE_LIST(X) \
-    X(32, 32, 1, 1, 1, 8, 0, 1, 1) /* 0 */ \
-    X(64, 64, 2, 2, 1, 8, 0, 1, 1) /* 1 */ \
-    X(128, 128, 2, 2, 1, 6, 0, 1, 1) /* 2 */ \
-    X(32, 128, 1, 2, 1, 8, 0, 1, 1) /* 3 */ \
-    X(64, 128, 2, 2, 1, 8, 0, 1, 1) /* 4 */ \
-    X(64, 256, 1, 4, 1, 6, 0, 1, 1) /* 5 */ \
-    X(128, 64, 2, 2, 1, 8, 0, 1, 1) /* 6 */ \
-    X(256, 128, 2, 2, 1, 5, 0, 1, 1) /* 7 */ \
-    X(128, 256, 2, 2, 1, 5, 0, 1, 1) /* 8 */ \
-    X(256, 256, 2, 2, 1, 4, 0, 1, 1) /* 9 */ \
-    X(256, 128, 2, 2, 1, 3, 0, 1, 1) /* 10 */ \
-    X(128, 256, 2, 2, 1, 3, 0, 1, 1) /* 11 */ \
-    X(128, 128, 2, 2, 1, 4, 0, 1, 1) /* 12 */ \
-    X(256, 256, 2, 4, 2, 2, 0, 1, 1) /* 13 */ \
-    X(256, 256, 2, 2, 2, 2, 0, 1, 1) /* 14 */ \
-    X(256, 128, 2, 2, 2, 3, 0, 1, 1) /* 15 */ \
-    X(128, 128, 2, 2, 2, 4, 0, 1, 1) /* 16 */ \
-    X(64, 64, 2, 2, 2, 4, 0, 1, 1) /* 17 */ \
-    X(64, 64, 2, 2, 2, 6, 0, 1, 1) /* 18 */ \
-    X(32, 64, 1, 2, 2, 6, 0, 1, 1) /* 19 */ \
-    X(64, 128, 2, 2, 2, 4, 0, 1, 1) /* 20 */ \
-    X(64, 64, 2, 2, 2, 4, 4, 1, 1) /* 21 */ \
-    X(64, 64, 2, 2, 2, 8, 4, 1, 1) /* 22 */ \
-    X(128, 128, 2, 2, 2, 4, 4, 1, 1) /* 23 */ \
-    X(64, 128, 2, 2, 2, 4, 4, 1, 1) /* 24 */ \
-    X(128, 64, 2, 2, 2, 4, 4, 1, 1) /* 25 */ \
-    X(256, 128, 2, 2, 2, 3, 4, 1, 1) /* 26 */ \
-    X(128, 256, 2, 2, 2, 3, 4, 1, 1) /* 27 */ \
-    X(64, 64, 2, 2, 2, 4, 0, 2, 1) /* 28 */ \
-    X(64, 64, 2, 2, 2, 6, 0, 2, 1) /* 29 */ \
-    X(64, 128, 2, 2, 2, 4, 0, 2, 1) /* 30 */ \
-    X(128, 64, 2, 2, 2, 4, 0, 2, 1) /* 31 */ \
-    X(32, 64, 1, 2, 2, 6, 0, 2, 1) /* 32 */ \
-    X(32, 32, 1, 1, 2, 8, 0, 2, 1) /* 33 */ \
-    X(128, 256, 2, 4, 1, 3, 0, 1, 2) /* 34 */ \
-    X(256, 128, 4, 2, 1, 3, 0, 1, 2) /* 35 */ \
-    X(128, 128, 2, 2, 1, 4, 0, 1, 2) /* 36 */ \
-    X(128, 128, 2, 2, 2, 2, 0, 1, 2) /* 37 */ \
-    X(256, 256, 2, 4, 1, 4, 0, 1, 1) /* 38 */ \
-    X(256, 256, 4, 2, 1, 4, 0, 1, 1) /* 39 */ \
-    X(256, 256, 2, 4, 1, 3, 0, 1, 1) /* 40 */ \
-    X(64, 64, 2, 2, 4, 4, 4, 1, 1) /* 41 */ \
-    X(64, 64, 2, 2, 4, 4, 0, 2, 1) /* 42 */ \
-    X(64, 64, 2, 2, 4, 3, 4, 1, 1) /* 43 */ \
-    X(64, 64, 2, 2, 4, 4, 0, 1, 1) /* 44 */
+    X(32, 32, 1, 1, 1, 8, 0, 1, 1, 1.25, 0.059, 0.036) /* 0 */ \
+    X(64, 64, 2, 2, 1, 8, 0, 1, 1, 1.30, 0.073, 0.090) /* 1 */ \
+    X(128, 128, 2, 2, 1, 6, 0, 1, 1, 2.80, 0.245, 0.019) /* 2 */ \
+    X(32, 128, 1, 2, 1, 8, 0, 1, 1, 1.92, 0.124, 0.086) /* 3 */ \
+    X(64, 128, 2, 2, 1, 8, 0, 1, 1, 2.08, 0.135, 0.016) /* 4 */ \
+    X(64, 256, 1, 4, 1, 6, 0, 1, 1, 2.97, 0.256, 0.026) /* 5 */ \
+    X(128, 64, 2, 2, 1, 8, 0, 1, 1, 1.90, 0.145, 0.015) /* 6 */ \
+    X(256, 128, 2, 2, 1, 5, 0, 1, 1, 4.69, 0.403, 0.034) /* 7 */ \
+    X(128, 256, 2, 2, 1, 5, 0, 1, 1, 5.31, 0.354, 0.035) /* 8 */ \
+    X(256, 256, 2, 2, 1, 4, 0, 1, 1, 9.47, 0.615, 0.056) /* 9 */ \
+    X(256, 128, 2, 2, 1, 3, 0, 1, 1, 4.53, 0.067, 0.479) /* 10 */ \
+    X(128, 256, 2, 2, 1, 3, 0, 1, 1, 5.36, 0.083, 0.451) /* 11 */ \
+    X(128, 128, 2, 2, 1, 4, 0, 1, 1, 2.70, 0.213, 0.174) /* 12 */ \
+    X(256, 256, 2, 4, 2, 2, 0, 1, 1, 5.28, 0.503, 0.052) /* 13 */ \
+    X(256, 256, 2, 2, 2, 2, 0, 1, 1, 8.91, 0.593, 0.057) /* 14 */ \
+    X(256, 128, 2, 2, 2, 3, 0, 1, 1, 4.92, 0.326, 0.032) /* 15 */ \
+    X(128, 128, 2, 2, 2, 4, 0, 1, 1, 3.12, 0.156, 0.012) /* 16 */ \
+    X(64, 64, 2, 2, 2, 4, 0, 1, 1, 1.52, 0.042, 0.074) /* 17 */ \
+    X(64, 64, 2, 2, 2, 6, 0, 1, 1, 1.68, 0.053, 0.059) /* 18 */ \
+    X(32, 64, 1, 2, 2, 6, 0, 1, 1, 1.40, 0.052, 0.062) /* 19 */ \
+    X(64, 128, 2, 2, 2, 4, 0, 1, 1, 2.42, 0.091, 0.009) /* 20 */ \
+    X(64, 64, 2, 2, 2, 4, 4, 1, 1, 1.41, 0.034, 0.072) /* 21 */ \
+    X(64, 64, 2, 2, 2, 8, 4, 1, 1, 1.69, 0.040, 0.031) /* 22 */ \
+    X(128, 128, 2, 2, 2, 4, 4, 1, 1, 3.07, 0.149, 0.019) /* 23 */ \
+    X(64, 128, 2, 2, 2, 4, 4, 1, 1, 2.32, 0.076, 0.010) /* 24 */ \
+    X(128, 64, 2, 2, 2, 4, 4, 1, 1, 2.13, 0.083, 0.013) /* 25 */ \
+    X(256, 128, 2, 2, 2, 3, 4, 1, 1, 4.60, 0.325, 0.032) /* 26 */ \
+    X(128, 256, 2, 2, 2, 3, 4, 1, 1, 5.12, 0.309, 0.031) /* 27 */ \
+    X(64, 64, 2, 2, 2, 4, 0, 2, 1, 1.69, 0.020, 0.069) /* 28 */ \
+    X(64, 64, 2, 2, 2, 6, 0, 2, 1, 1.90, 0.029, 0.038) /* 29 */ \
+    X(64, 128, 2, 2, 2, 4, 0, 2, 1, 2.72, 0.067, 0.011) /* 30 */ \
+    X(128, 64, 2, 2, 2, 4, 0, 2, 1, 2.49, 0.073, 0.013) /* 31 */ \
+    X(32, 64, 1, 2, 2, 6, 0, 2, 1, 1.64, 0.015, 0.043) /* 32 */ \
+    X(32, 32, 1, 1, 2, 8, 0, 2, 1, 1.44, 0.001, 0.035) /* 33 */ \
+    X(128, 256, 2, 4, 1, 3, 0, 1, 2, 2.95, 0.255, 0.335) /* 34 */ \
+    X(256, 128, 4, 2, 1, 3, 0, 1, 2, 2.74, 0.288, 0.344) /* 35 */ \
+    X(128, 128, 2, 2, 1, 4, 0, 1, 2, 2.64, 0.206, 0.178) /* 36 */ \
+    X(128, 128, 2, 2, 2, 2, 0, 1, 2, 2.80, 0.145, 0.170) /* 37 */ \
+    X(256, 256, 2, 4, 1, 4, 0, 1, 1, 4.64, 0.566, 0.053) /* 38 */ \
+    X(256, 256, 4, 2, 1, 4, 0, 1, 1, 5.32, 0.575, 0.057) /* 39 */ \
+    X(256, 256, 2, 4, 1, 3, 0, 1, 1, 4.63, 0.554, 0.053) /* 40 */ \
+    X(64, 64, 2, 2, 4, 4, 4, 1, 1, 1.82, 0.021, 0.007) /* 41 */ \
+    X(64, 64, 2, 2, 4, 4, 0, 2, 1, 1.89, 0.020, 0.041) /* 42 */ \
+    X(64, 64, 2, 2, 4, 3, 4, 1, 1, 1.87, 0.032, 0.043) /* 43 */ \
+    X(64, 64, 2, 2, 4, 4, 0, 1, 1, 1.80, 0.041, 0.011) /* 44 */
 
 static const TileDef kTiles[] = {
 #define C2I8_ROW(...) {__VA_ARGS__},
@@ -753,7 +757,7 @@ template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, 
 static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
 {
     constexpr int NT = (WK * WM * DS + HELP) * 64;
-    const size_t lds = tile_lds_bytes(TileDef{TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC}, mode, a.ksteps_per_split);
+    const size_t lds = tile_lds_bytes(TileDef{TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, 0, 0, 0}, mode, a.ksteps_per_split);
     const int grid = a.tiles_k * a.tiles_m * a.split_k;
     auto kb = igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED>;
     auto km = igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX>;
@@ -780,13 +784,13 @@ static bool tile_fits(const TileDef &d, int ksteps, int per)
     return d.ks == 1 || (ksteps % d.ks == 0 && per % d.ks == 0);
 }
 
-// Per-launch time model (core cycles) used to pick a tile and a depth split.  Its constants
-// were fitted to a table of measured launch times (every tile on the five benchmark shapes
-// and on batch-scaled versions of them, both layouts) so that the tile it ranks first loses
-// as little as possible against the measured best; they are rates and latencies in spirit --
-// bytes per cycle a wave and a CU move global->LDS, the latency chain of a lone workgroup's
-// depth step, the sustained share of the MFMA issue rate, output bytes per cycle and CU,
-// the cost of starting a workgroup and each of its waves -- but only the ranking is used.
+// Launch time in microseconds, used to pick a tile and a depth split and to weigh the two-stage path against others.
+// Fitted to 80000 launches of 900 problems (every tile that applies, depth splits from 2 to 9; blocked and matrix operands,
+// NKPQ and NHWC results, 4 to 300 us): a launch, and per round of workgroups the tile's fixed part, its depth steps -- the
+// barrier-to-barrier chain of a lone workgroup or the work of all that share the compute unit -- and its stores, by how they
+// meet the 64-byte sectors; the tensors' bytes; for a depth split the clear before it and the additions in memory.  The tile
+// it ranks first loses 1.8 % against the measured best (a model of cycles per operand byte and per MFMA, with the same rates
+// for every tile, lost 9 %, and up to 2.7 times on wide images with few channels: 72 x 32 x 56 x 56 -> 71 picked 57 us of 29).
 bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost)
 {
     const int ksteps = g.depth / 64;
@@ -794,21 +798,18 @@ bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost)
     static const int splits[] = {1, 2, 3, 4, 6, 8, 9, 12, 16};
     double best = 1e300;
     int bt = *tile >= 0 ? *tile : 0, bs = *split_k > 0 ? *split_k : 1;
+    const double out_bytes = (double)g.M * g.K * (g.act_out ? 1 : 4);
+    const double act_bytes = g.mode == ACT_BLOCKED ? (double)g.M / g.PQ * g.Cb * g.cb * g.Hp * g.Wp : (double)g.M * g.depth;
+    const double stored = g.act_out || (!g.out_nhwc && g.PQ % 16 == 0) ? 1.2e-05 : !g.out_nhwc ? 1.67e-05 : g.K % 4 == 0 ? 3.99e-07 : 8.56e-05;
+    const double added = g.out_nhwc ? 0.000101 : 1.73e-05, summed = g.out_nhwc ? 5.1e-6 : 0.503e-6, setup = g.mode == ACT_BLOCKED ? 0.0788 : 0;
     for (int t = 0; t < kNumTiles; ++t) {
         if (*tile >= 0 && t != *tile) continue;
         const TileDef &d = kTiles[t];
         const int mwaves = d.wk * d.wm, waves = mwaves * d.ds + d.help;
         const double tiles = (double)ceil_div(g.K, d.tk) * ceil_div(g.M, d.tm);
-        const double lds = (double)d.nstage * (d.tk + d.tm) * 64 * d.ks + 2048;
         const int acc = d.tk * d.tm / (mwaves * 64);  // accumulator registers per lane
-        int cap = (int)(160.0 * 1024 / lds);
         const int reg_cap = acc > 128 ? 1 : acc > 64 ? 2 : 4;  // 512 registers per lane and SIMD
-        const int wave_cap = waves >= 8 ? reg_cap / 2 : reg_cap;
-        if (cap > wave_cap) cap = wave_cap;
-        if (cap < 1) cap = 1;
-        const double mfma = (double)d.tk * d.tm * 64 / 4096.0 / 0.6;
-        const double bytes = (double)(d.tk + d.tm) * 64;
-        const double lat = d.ks == 1 ? 350.0 : 360.0 / d.ks;  // barrier-to-barrier chain, per 64-deep step
+        const int wave_cap = waves >= 8 ? (reg_cap > 1 ? reg_cap / 2 : 1) : reg_cap;
         const int forced[] = {*split_k > ksteps ? ksteps : *split_k};
         const int *cand = *split_k > 0 ? forced : splits;
         const int ncand = *split_k > 0 ? 1 : (int)(sizeof(splits) / sizeof(splits[0]));
@@ -818,24 +819,18 @@ bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost)
             s = ceil_div(ksteps, ceil_div(ksteps, s));  // drop slices that would be empty
             const int per = ceil_div(ksteps, s);
             if (!tile_fits(d, ksteps, per)) continue;
-            if (tile_lds_bytes(d, g.mode, per) > kLdsLimit) continue;  // ring + offset table must fit one CU's LDS
-            const double wgs = tiles * s;
-            int res = (int)((wgs + 255) / 256);  // workgroups sharing a CU
-            if (res > cap) res = cap;
-            double dma = (d.ks >= 2 ? 5.5 : 6.5) * waves * res;
-            const double dma_max = d.ks >= 2 ? 44.0 : 38.0;
-            if (dma > dma_max) dma = dma_max;
-            double step = lat;
-            if (res * mfma > step) step = res * mfma;
-            if (res * bytes / dma > step) step = res * bytes / dma;
-            const double store = res * (double)d.tk * d.tm * 4 / (s > 1 ? 2.2 : 4.0);
-            const double start = 5000.0 + 5.0 * (d.tk + d.tm) / waves + (d.ds == 2 ? 1000.0 : 0.0) + 400.0 * waves * res;
-            const double wg = start + per * step + store;
+            const size_t lds = tile_lds_bytes(d, g.mode, per);
+            if (lds > kLdsLimit) continue;  // ring + offset table must fit one CU's LDS
+            int cap = (int)(kLdsLimit / lds);
+            if (cap > wave_cap) cap = wave_cap;
+            const double wgs = tiles * s, per_cu = (double)(long long)((wgs + 255) / 256);
+            const double res = per_cu < cap ? per_cu : cap;   // workgroups sharing a compute unit
             const double rounds = (double)(long long)((wgs + 256.0 * res - 1) / (256.0 * res));
-            double total = rounds * wg + (s > 1 ? 6000.0 : 0.0);
-            // measured on two machines at N = 2048: among the 256 x 256 tiles the eight-wave one with 128-byte
-            // stages is 5-15 % ahead of the four-wave one, which the cycle model above ranks level
-            if (d.tk * d.tm >= 65536 && waves >= 8 && d.ks >= 2) total *= 0.95;
+            const double chain = d.alone + setup, busy = res * d.shared;   // whichever is longer, joined smoothly
+            const double step = std::sqrt(std::sqrt(chain * chain * chain * chain + busy * busy * busy * busy));
+            const double cu_bytes = res * out_bytes / tiles / (s > 1 ? s : 1);
+            double total = 3.33 + rounds * (d.start + per * step + (s > 1 ? added : stored) * cu_bytes) + 1.21e-05 / 256 * act_bytes + 2.46e-05 / 256 * out_bytes;
+            if (s > 1) total += 1.86 + summed * out_bytes * s;
             if (total < best) {
                 best = total;
                 bt = t;
@@ -977,7 +972,7 @@ hipError_t launch_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t 
         if (e != hipSuccess) return e;
     }
     int index = 0;
-#define C2I8_CASE(tk, tm, wk, wm, ks, nstage, help, ds, wpc) \
+#define C2I8_CASE(tk, tm, wk, wm, ks, nstage, help, ds, wpc, ...) \
     if (tile == index++) return launch_tile<tk, tm, wk, wm, ks, nstage, help, ds, wpc>(a, g.mode, st);
     C2I8_TILE_LIST(C2I8_CASE)
 #undef C2I8_CASE

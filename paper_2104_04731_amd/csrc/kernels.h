@@ -60,7 +60,7 @@ size_t gemm_tile_lds_bytes(int tile, int mode, int steps_per_slice);
 // this problem (a tile with 128-byte stages needs an even number of depth steps per slice).
 bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost = nullptr);
 // The band kernel (band_mfma.hip): a GEMM stage for channel blocks of 64 that keeps a band of output rows'
-// input window resident in LDS and splits the depth over its waves.  band_cost: the same cycle scale as
+// input window resident in LDS and splits the depth over its waves.  band_cost: microseconds, as
 // the cost gemm_pick reports (1e300 where the kernel does not apply).
 bool band_applies(const GemmProblem &g);
 double band_cost(const GemmProblem &g);
