@@ -7,9 +7,9 @@
 // 64.  A dword of depth is then four horizontally adjacent input bytes of one (c, r) row, which
 // in NCHW are contiguous in memory -- no byte gathering anywhere.
 //
-// One workgroup (4 waves) computes PT x QT output pixels of one image for up to 64 output
+// One workgroup (4 waves) computes PT * G x QT output pixels of one image for up to 64 output
 // channels:
-//   1. window: the C * ((PT-1)*stride + R) input rows the tile touches, as wide as the tile's
+//   1. window: the C * ((PT*G-1)*stride + R) input rows the tile touches, as wide as the tile's
 //      pixels reach, are copied into LDS with the zero border filled in (dword loads from a
 //      column clamped into the image row, shifted so that what falls outside becomes zero);
 //   2. weights: the tile's rows of the weight operand -- KCRS itself, or the output of the weight
@@ -21,6 +21,7 @@
 //      and a byte-align each), its weight operand 16 bytes of weight row lane%32.
 //      v_mfma_i32_32x32x32_i8, channels x pixels;
 //   5. the D block (column = pixel = lane%32) goes straight to NKPQ: 128-byte runs per channel.
+// Steps 4 and 5 are repeated for the tile's row groups (window_groups says how many).
 //
 // NHWC source (Sec. 5.2).  A row of an NHWC image is W*C bytes in which the S*C bytes of a kernel row's taps
 // and channels are one run: the same kernel computes it as a one-channel image of W*C columns with a kernel
@@ -46,8 +47,11 @@ struct WindowArgs {
     int gC, gS, gRS;       // NHWC source: the real channel count, S and R*S of the KCRS weights
     int nhwc;              // NHWC source
     int out_nhwc, out_wide_k;  // result [N][P][Q][K]; K % 4 == 0 and out 16-byte aligned
-    int PT, qshift;        // output rows per tile; tile columns QT = 32 << qshift, PT << qshift = 4
-    int RW;                // window rows per channel: (PT-1)*stride + R
+    int PT, qshift;        // output rows the waves cover at a time; tile columns QT = 32 << qshift, PT << qshift = 4
+    int G;                 // how often they do: a tile has PT * G output rows
+    int RW;                // window rows per channel: (PT*G-1)*stride + R
+    int turn_off;          // LDS byte offset of the blocks turned around (0: over the window, G = 1)
+    int stream_out;        // result past the caches
     int pitch;             // bytes per window row, a multiple of 4
     int tiles_q, tiles_p;  // tiles per image
     int CR, nd;            // C*R; dwords per kernel row: ceil(S, 4) / 4
@@ -70,7 +74,7 @@ __device__ __forceinline__ unsigned load_u32(const void *p)  // any alignment
     return x;
 }
 
-template <int NKK, int NKB, bool ACT, bool NHWC>  // ACT: the activation epilogue, a kernel of its own; NHWC: the source
+template <int NKK, int NKB, bool ACT, bool NHWC, bool MULTI>  // ACT: the activation epilogue, a kernel of its own; NHWC: the source
 // (four workgroups per compute unit asked for, i.e. up to 128 registers: the deep instantiations use 86 -- five
 // fit -- and under a bound of 85 the compiler spilled their weight loads one by one, a wait behind each)
 __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
@@ -89,7 +93,7 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
     const int lid = xcd_contiguous(blockIdx.x, gridDim.x);
     const int t1 = fast_div_any(lid, a.tiles_q, a.m_tiles_q), tq = lid - t1 * a.tiles_q;
     const int n = fast_div_any(t1, a.tiles_p, a.m_tiles_p), tp = t1 - n * a.tiles_p;
-    const int p0 = tp * a.PT, q0 = tq << (5 + a.qshift), k0 = blockIdx.y * KB;
+    const int p0 = tp * a.PT * a.G, q0 = tq << (5 + a.qshift), k0 = blockIdx.y * KB;
     const int h_lo = p0 * a.stride - a.pad;
     const int w_first = q0 * a.stride_w - a.pad_w;
     const int w_lo = (w_first >> 2) << 2;  // rounded down, also when negative
@@ -278,148 +282,162 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
     // 4. MFMA.  A pixel's four bytes start at any byte of the window: two aligned dwords and a
     //    byte-align (unaligned LDS reads are served one lane at a time).
     const int pw = wave >> a.qshift, qw = wave & ((1 << a.qshift) - 1);
-    const int abyte = (pw * a.stride) * a.pitch + delta + (qw * 32 + l31) * a.stride_w;
-    const unsigned char *a4 = win + (abyte & ~3);  // table offsets are multiples of 4: the byte shift is the lane's own
-    const unsigned ash = (unsigned)abyte & 3u;
+    const int abyte0 = (pw * a.stride) * a.pitch + delta + (qw * 32 + l31) * a.stride_w;
+    const unsigned ash = (unsigned)abyte0 & 3u;   // (rows are a multiple of 4 apart)
     const unsigned char *wbase = wl + l31 * a.w_pitch + half * 16;
-    v16i acc[NKB];
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[kb][v] = 0;
     // Every step's table entries first, then the dword pairs one step ahead of their use: written step by step, each
     // step was two dependent LDS round trips (table, then pairs) in front of its MFMAs.
     v4i ta[NKK];
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) ta[kk] = *reinterpret_cast<const v4i *>(tab + kk * 8 + half * 4);
-    unsigned plo[2][4], phi[2][4];
-    auto fetch_pairs = [&](int kk) {
+    auto block = [&](int g) {   // the wave's block of output row group g
+        // (opaque: what follows from the extents is made anew for every block, and the weights are read anew -- kept across
+        // blocks, the addresses of 32 stores and the fragments do not fit the registers)
+        int aP = a.P, aQ = a.Q, aK = a.K, pitch = a.pitch;
+        if (MULTI) asm volatile("" : "+s"(aP), "+s"(aQ), "+s"(aK), "+s"(pitch) : : "memory");
+        const size_t PQ = (size_t)aP * aQ;
+        int32_t *outn = a.out + (size_t)n * aK * PQ;
+        const int pr = p0 + g * a.PT + pw;
+        const unsigned char *a4 = win + ((abyte0 + g * a.PT * a.stride * pitch) & ~3);  // table offsets are multiples of 4: the byte shift is the lane's own
+        v16i acc[NKB];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const unsigned *pp = reinterpret_cast<const unsigned *>(a4 + ta[kk][i]);
-            plo[kk & 1][i] = pp[0];
-            phi[kk & 1][i] = pp[1];
+        for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[kb][v] = 0;
+        unsigned plo[2][4], phi[2][4];
+        auto fetch_pairs = [&](int kk) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const unsigned *pp = reinterpret_cast<const unsigned *>(a4 + ta[kk][i]);
+                plo[kk & 1][i] = pp[0];
+                phi[kk & 1][i] = pp[1];
+            }
+        };
+        fetch_pairs(0);
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) {
+            if (kk + 1 < NKK) fetch_pairs(kk + 1);
+            v4i af;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) af[i] = (int)__builtin_amdgcn_alignbyte(phi[kk & 1][i], plo[kk & 1][i], ash);
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb) {
+                const v4i wf = *reinterpret_cast<const v4i *>(wbase + kb * 32 * a.w_pitch + kk * 32);
+                acc[kb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, af, acc[kb], 0, 0, 0);
+            }
         }
-    };
-    fetch_pairs(0);
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-        if (kk + 1 < NKK) fetch_pairs(kk + 1);
-        v4i af;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) af[i] = (int)__builtin_amdgcn_alignbyte(phi[kk & 1][i], plo[kk & 1][i], ash);
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-            const v4i wf = *reinterpret_cast<const v4i *>(wbase + kb * 32 * a.w_pitch + kk * 32);
-            acc[kb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf, af, acc[kb], 0, 0, 0);
-        }
-    }
 
-    // 5. D block: column = lane%32 = pixel, row = 8*(v/4) + 4*(lane/32) + v%4 = channel
-    if (ACT) {
-        const int p = p0 + pw, q = q0 + qw * 32 + l31;
-        if (p < a.P && q < a.Q) {
+        // 5. D block: column = lane%32 = pixel, row = 8*(v/4) + 4*(lane/32) + v%4 = channel
+        if (ACT) {
+            const int p = pr, q = q0 + qw * 32 + l31;
+            if (p < aP && q < aQ) {
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                    for (int vg = 0; vg < 4; ++vg)
+                        act_store4(a.act, n, p, q, k0 + kb * 32 + 8 * vg + 4 * half, aK, acc[kb][4 * vg], acc[kb][4 * vg + 1],
+                                   acc[kb][4 * vg + 2], acc[kb][4 * vg + 3]);
+            }
+            return;
+        }
+        if (a.out_nhwc && a.out_wide_k) {
+            // a lane's v%4 are channels k .. k+3 of its pixel: each wave lays its 32 pixels x KB channels out in LDS
+            // as the result has them ([pixel][channel], rows of KB + 4 dwords) and stores 16-byte pieces with the
+            // pieces of a pixel in consecutive lanes -- the channel runs of consecutive pixels follow each other in
+            // the result, so a store instruction writes whole runs instead of 32-byte pairs
+            if (!MULTI) __syncthreads();  // every wave is done with the window and the weights
+            constexpr int TPITCH = KB + 4, CPP = KB / 4;   // dwords per pixel row; 16-byte pieces per pixel
+            int *T = reinterpret_cast<int *>(smem + (MULTI ? a.turn_off : 0)) + wave * (32 * TPITCH);
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
                 for (int vg = 0; vg < 4; ++vg)
-                    act_store4(a.act, n, p, q, k0 + kb * 32 + 8 * vg + 4 * half, a.K, acc[kb][4 * vg], acc[kb][4 * vg + 1],
-                               acc[kb][4 * vg + 2], acc[kb][4 * vg + 3]);
-        }
-        return;
-    }
-    const size_t PQ = (size_t)a.P * a.Q;
-    int32_t *outn = a.out + (size_t)n * a.K * PQ;
-    if (a.out_nhwc && a.out_wide_k) {
-        // a lane's v%4 are channels k .. k+3 of its pixel: each wave lays its 32 pixels x KB channels out in LDS
-        // as the result has them ([pixel][channel], rows of KB + 4 dwords) and stores 16-byte pieces with the
-        // pieces of a pixel in consecutive lanes -- the channel runs of consecutive pixels follow each other in
-        // the result, so a store instruction writes whole runs instead of 32-byte pairs
-        __syncthreads();  // every wave is done with the window and the weights
-        constexpr int TPITCH = KB + 4, CPP = KB / 4;   // dwords per pixel row; 16-byte pieces per pixel
-        int *T = reinterpret_cast<int *>(smem) + wave * (32 * TPITCH);
+                    *reinterpret_cast<v4i *>(T + l31 * TPITCH + kb * 32 + 8 * vg + 4 * half) =
+                        v4i{acc[kb][4 * vg], acc[kb][4 * vg + 1], acc[kb][4 * vg + 2], acc[kb][4 * vg + 3]};
+            __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order
+            const int p = pr, pc = lane % CPP, px0 = lane / CPP;
+            if (p >= aP || k0 + 4 * pc >= aK) return;
+            int32_t *row = outn + ((size_t)p * aQ) * aK + k0 + 4 * pc;
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-            for (int vg = 0; vg < 4; ++vg)
-                *reinterpret_cast<v4i *>(T + l31 * TPITCH + kb * 32 + 8 * vg + 4 * half) =
-                    v4i{acc[kb][4 * vg], acc[kb][4 * vg + 1], acc[kb][4 * vg + 2], acc[kb][4 * vg + 3]};
-        __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order
-        const int p = p0 + pw, pc = lane % CPP, pr0 = lane / CPP;
-        if (p >= a.P || k0 + 4 * pc >= a.K) return;
-        int32_t *row = outn + ((size_t)p * a.Q) * a.K + k0 + 4 * pc;
-#pragma unroll
-        for (int j = 0; j < CPP / 2; ++j) {
-            const int pr = pr0 + j * (64 / CPP), q = q0 + qw * 32 + pr;
-            const v4i t = *reinterpret_cast<const v4i *>(T + pr * TPITCH + 4 * pc);
-            if (q < a.Q) *reinterpret_cast<v4i *>(row + (size_t)q * a.K) = t;
-        }
-        return;
-    }
-    if (a.out_nhwc) {   // results that do not start on 16 bytes, or K % 4 != 0: one by one
-        const int p = p0 + pw, q = q0 + qw * 32 + l31;
-        if (p >= a.P || q >= a.Q) return;
-        int32_t *px = outn + ((size_t)p * a.Q + q) * a.K;
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-            for (int vg = 0; vg < 4; ++vg) {
-                const int k = k0 + kb * 32 + 8 * vg + 4 * half;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (k + j < a.K) px[k + j] = acc[kb][4 * vg + j];
+            for (int j = 0; j < CPP / 2; ++j) {
+                const int px = px0 + j * (64 / CPP), q = q0 + qw * 32 + px;
+                const v4i t = *reinterpret_cast<const v4i *>(T + px * TPITCH + 4 * pc);
+                if (q < aQ) *reinterpret_cast<v4i *>(row + (size_t)q * aK) = t;
             }
-        return;
-    }
-    if (a.wide_out) {
-        // Q a multiple of 4 and `out` 16-byte aligned: each wave turns its 32x32 block around in LDS
-        // (rows of 36 dwords) so that a lane stores four consecutive pixels of one channel -- 16-byte
-        // stores, eight 128-byte runs per instruction instead of two
-        __syncthreads();  // every wave is done with the window and the weights
-        int *T = reinterpret_cast<int *>(smem) + wave * (32 * 36);
-        const int tr = lane >> 3, tg = lane & 7;
-        const int pp = p0 + pw, qq = q0 + qw * 32 + 4 * tg;
-#pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) T[(8 * (v >> 2) + 4 * half + (v & 3)) * 36 + l31] = acc[kb][v];
-            __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order: no wait beyond the compiler's own
-            int32_t *dst = outn + (size_t)(k0 + kb * 32 + tr) * PQ + (size_t)pp * a.Q + qq;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const v4i t = *reinterpret_cast<const v4i *>(T + (tr + 8 * j) * 36 + 4 * tg);
-                if (pp < a.P && qq < a.Q && k0 + kb * 32 + tr + 8 * j < a.K)
-                    *reinterpret_cast<v4i *>(dst + (size_t)(8 * j) * PQ) = t;
-            }
-            __builtin_amdgcn_wave_barrier();
+            return;
         }
-        return;
-    }
-    const int p = p0 + pw, q = q0 + qw * 32 + l31;
-    if (p >= a.P || q >= a.Q) return;
-    if (a.out_small) {  // byte offsets inside an image's planes fit 32 bits: one add per store
-        const unsigned PQ4 = (unsigned)PQ * 4u;
-        const unsigned o = (unsigned)(k0 + 4 * half) * PQ4 + ((unsigned)p * a.Q + q) * 4u;
-        char *ob = reinterpret_cast<char *>(outn);
-        const bool full = k0 + KB <= a.K;
+        if (a.out_nhwc) {   // results that do not start on 16 bytes, or K % 4 != 0: one by one
+            const int p = pr, q = q0 + qw * 32 + l31;
+            if (p >= aP || q >= aQ) return;
+            int32_t *px = outn + ((size_t)p * aQ + q) * aK;
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int vg = 0; vg < 4; ++vg) {
+                    const int k = k0 + kb * 32 + 8 * vg + 4 * half;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (k + j < aK) px[k + j] = acc[kb][4 * vg + j];
+                }
+            return;
+        }
+        if (a.wide_out) {
+            // Q a multiple of 4 and `out` 16-byte aligned: each wave turns its 32x32 block around in LDS
+            // (rows of 36 dwords) so that a lane stores four consecutive pixels of one channel -- 16-byte
+            // stores, eight 128-byte runs per instruction instead of two
+            if (!MULTI) __syncthreads();  // every wave is done with the window and the weights
+            int *T = reinterpret_cast<int *>(smem + (MULTI ? a.turn_off : 0)) + wave * (32 * 36);
+            const int tr = lane >> 3, tg = lane & 7;
+            const int pp = pr, qq = q0 + qw * 32 + 4 * tg;
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) T[(8 * (v >> 2) + 4 * half + (v & 3)) * 36 + l31] = acc[kb][v];
+                __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order: no wait beyond the compiler's own
+                int32_t *dst = outn + (size_t)(k0 + kb * 32 + tr) * PQ + (size_t)pp * aQ + qq;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const v4i t = *reinterpret_cast<const v4i *>(T + (tr + 8 * j) * 36 + 4 * tg);
+                    if (pp < aP && qq < aQ && k0 + kb * 32 + tr + 8 * j < aK) {
+                        v4i *const to = reinterpret_cast<v4i *>(dst + (size_t)(8 * j) * PQ);
+                        // (asm: of the two stores the compiler makes one, without the hint)
+                        if (a.stream_out) asm volatile("global_store_dwordx4 %0, %1, off nt" : : "v"(to), "v"(t) : "memory");
+                        else *to = t;
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            return;
+        }
+        const int p = pr, q = q0 + qw * 32 + l31;
+        if (p >= aP || q >= aQ) return;
+        if (a.out_small) {  // byte offsets inside an image's planes fit 32 bits: one add per store
+            const unsigned PQ4 = (unsigned)PQ * 4u;
+            const unsigned o = (unsigned)(k0 + 4 * half) * PQ4 + ((unsigned)p * aQ + q) * 4u;
+            char *ob = reinterpret_cast<char *>(outn);
+            const bool full = k0 + KB <= aK;
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int kr = kb * 32 + 8 * (v >> 2) + (v & 3);
+                    if (full || k0 + 4 * half + kr < aK)
+                        *reinterpret_cast<int32_t *>(ob + (o + (unsigned)kr * PQ4)) = acc[kb][v];
+                }
+            return;
+        }
+        int32_t *base = outn + (size_t)p * aQ + q;
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int kr = kb * 32 + 8 * (v >> 2) + (v & 3);
-                if (full || k0 + 4 * half + kr < a.K)
-                    *reinterpret_cast<int32_t *>(ob + (o + (unsigned)kr * PQ4)) = acc[kb][v];
+                const int k = k0 + kb * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
+                if (k < aK) base[(size_t)k * PQ] = acc[kb][v];
             }
-        return;
-    }
-    int32_t *base = outn + (size_t)p * a.Q + q;
-#pragma unroll
-    for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int k = k0 + kb * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-            if (k < a.K) base[(size_t)k * PQ] = acc[kb][v];
-        }
+    };
+    if (!MULTI) block(0);
+    else
+        for (int g = 0; g < a.G; ++g) block(g);
 }
 
 // dst[k][(cr*nd + d)*4 + b] = src[k][cr*S + 4*d + b] inside the kernel row, else 0; one thread per dword
@@ -450,6 +468,30 @@ int window_depth(int C, int R, int S)
 
 constexpr long long WINDOW_LIMIT = 40 * 1024;  // bytes of LDS the input window of a tile may take
 
+// A result this large goes past the last-level cache (256 MB) anyway.
+constexpr double STREAM_BYTES = 256e6;
+
+// How many row groups a tile takes (a kernel of its own from 2 on): its window's rows overlap, the weights and the table are
+// brought in once.  Measured over 110 stem and speech layers.  Up to 32 output channels the time goes into filling the LDS:
+// the most of 2, 4, 8 that leaves two workgroups for each place on the chip (353 images 3 x 212 x 166, 7 x 7 / 2 -> 16: 119
+// -> 85 us; 68 x 1 x 161 x 686, 20 x 5 / 2 -> 32: 50 -> 41; 100 x 3 x 131 x 151, 3 x 3 -> 32: 59 -> 48); three for a depth of
+// 64, which gains the least.  Above 32 channels it goes into the stores, which come in one burst per workgroup and
+// overlap less the longer it runs: two groups where the window is large (40 x 1 x 161 x 522, 20 x 5 / 2 -> 64: 46.5 -> 41) and
+// the stores do not bypass the caches, else one.
+static int window_groups(const WindowProblem &g, int PT, int QT, long long row_bytes, int depth, bool stream_out)
+{
+    if (g.nhwc_in || g.out_nhwc || g.act.out) return 1;
+    const long long cols = (long long)g.N * ((g.Q + QT - 1) / QT);
+    auto fits = [&](int G, long long least) {
+        const long long groups = (g.P + PT * G - 1) / (PT * G);
+        return cols * groups * ((g.K + 63) / 64) >= least && ((long long)(PT * G - 1) * g.stride + g.R) * row_bytes <= 16 * 1024;
+    };
+    if (g.K > 32) return !stream_out && ((PT - 1) * g.stride + g.R) * row_bytes >= 4000 && fits(2, 2048) ? 2 : 1;
+    int G = 1;
+    while (G < 8 && fits(2 * G, depth == 64 ? 3072 : 2048)) G *= 2;
+    return G;
+}
+
 // Tile shape by output width, window geometry and the LDS it needs.
 static bool window_plan(const WindowProblem &g, WindowArgs *a)
 {
@@ -477,8 +519,12 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     w.PT = 4 >> w.qshift;
     const int QT = 32 << w.qshift;
     const int S4 = (S + 3) / 4 * 4;
-    const long long RW = (long long)(w.PT - 1) * g.stride + g.R;
     const long long pitch = (((long long)(QT - 1) * stride_w + S4 + 3) + 3) / 4 * 4;
+    // whole 64-byte sectors per 16 pixels, and more than the caches keep: stored past them (300 images 3 x 224 x 224, 7 x 7 / 2
+    // -> 64, 963 MB: 294 -> 180 us; at 206 MB 42 -> 49, and partial sectors come out up to 2.5 times slower that way)
+    w.stream_out = g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && 4.0 * g.N * g.K * g.P * g.Q > STREAM_BYTES;
+    w.G = window_groups(g, w.PT, QT, C * pitch, depth, w.stream_out);
+    const long long RW = (long long)(w.PT * w.G - 1) * g.stride + g.R;
     if (RW > WINDOW_LIMIT || pitch > WINDOW_LIMIT || C * RW * pitch > WINDOW_LIMIT) return false;
     w.RW = (int)RW;
     const long long win = (C * RW * pitch + 4 + 15) / 16 * 16;  // + the dword after the last one (read, never used)
@@ -496,7 +542,7 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     w.win_bytes = (int)win;
     w.wl_bytes = (int)wlb;
     w.tiles_q = (g.Q + QT - 1) / QT;
-    w.tiles_p = (g.P + w.PT - 1) / w.PT;
+    w.tiles_p = (g.P + w.PT * w.G - 1) / (w.PT * w.G);
     if ((long long)g.N * w.tiles_p * w.tiles_q > 2147483647LL || (g.K + kb - 1) / kb > 65535) return false;
     w.m_wd = magic_for(pitch / 4);
     w.rpp = (pitch / 4 <= 256 && (long long)C * RW <= 8 * (256 / (pitch / 4))) ? (int)(256 / (pitch / 4)) : 0;
@@ -515,21 +561,22 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
 
 bool window_fits(const WindowProblem &g) { return window_plan(g, nullptr); }
 
+template <int NKK, bool ACT, bool NHWC, bool MULTI>
+static hipError_t launch_window_kb(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
+{
+    if (a.K > 32) return launch((conv_window_kernel<NKK, 2, ACT, NHWC, MULTI>), grid, dim3(256), lds, st, a);
+    return launch((conv_window_kernel<NKK, 1, ACT, NHWC, MULTI>), grid, dim3(256), lds, st, a);
+}
 template <int NKK>
 static hipError_t launch_window_nkk(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
 {
     if (a.nhwc) {
-        if (a.act.out) {
-            if (a.K > 32) return launch((conv_window_kernel<NKK, 2, true, true>), grid, dim3(256), lds, st, a);
-            else return launch((conv_window_kernel<NKK, 1, true, true>), grid, dim3(256), lds, st, a);
-        } else if (a.K > 32) return launch((conv_window_kernel<NKK, 2, false, true>), grid, dim3(256), lds, st, a);
-        else return launch((conv_window_kernel<NKK, 1, false, true>), grid, dim3(256), lds, st, a);
+        if (a.act.out) return launch_window_kb<NKK, true, true, false>(a, grid, lds, st);
+        return launch_window_kb<NKK, false, true, false>(a, grid, lds, st);
     }
-    if (a.act.out) {
-        if (a.K > 32) return launch((conv_window_kernel<NKK, 2, true, false>), grid, dim3(256), lds, st, a);
-        else return launch((conv_window_kernel<NKK, 1, true, false>), grid, dim3(256), lds, st, a);
-    } else if (a.K > 32) return launch((conv_window_kernel<NKK, 2, false, false>), grid, dim3(256), lds, st, a);
-    else return launch((conv_window_kernel<NKK, 1, false, false>), grid, dim3(256), lds, st, a);
+    if (a.act.out) return launch_window_kb<NKK, true, false, false>(a, grid, lds, st);
+    if (a.G > 1) return launch_window_kb<NKK, false, false, true>(a, grid, lds, st);
+    return launch_window_kb<NKK, false, false, false>(a, grid, lds, st);
 }
 
 hipError_t launch_window_conv(const WindowProblem &g, hipStream_t st)
@@ -540,8 +587,12 @@ hipError_t launch_window_conv(const WindowProblem &g, hipStream_t st)
     const int kb = g.K > 32 ? 64 : 32;
     const dim3 grid((unsigned)(g.N * a.tiles_p * a.tiles_q), (unsigned)((g.K + kb - 1) / kb));
     size_t lds = (size_t)a.win_bytes + a.wl_bytes + (size_t)depth + (g.nhwc_in ? ((size_t)kb * a.w_row + 3) / 4 * 4 : 0);
-    if (lds < 4 * 32 * 36 * 4) lds = 4 * 32 * 36 * 4;  // the output blocks of the four waves, turned around
-    if (g.out_nhwc && lds < (size_t)4 * 32 * (kb + 4) * 4) lds = (size_t)4 * 32 * (kb + 4) * 4;
+    // the output blocks of the four waves, turned around: over the window, or behind everything if the window is needed again
+    const size_t turned = g.act.out ? 0 : g.out_nhwc ? (size_t)4 * 32 * (kb + 4) * 4 : a.wide_out ? (size_t)4 * 32 * 36 * 4 : 0;
+    if (a.G > 1) {
+        a.turn_off = (int)((lds + 15) / 16 * 16);
+        lds = a.turn_off + turned;
+    } else if (lds < turned) lds = turned;
     switch (depth / 32) {
         case 2: return launch_window_nkk<2>(a, grid, lds, st);
         case 4: return launch_window_nkk<4>(a, grid, lds, st);

@@ -1281,3 +1281,29 @@ def test_band_direct(lib, cfg, offset):
     ws = torch.empty(max(256, lib.conv2d_int8_workspace_bytes(cfg.dims(), lib.LAYOUT_PACKED, 64, True)), dtype=torch.int8, device=DEV)
     out = torch.full((cfg.N, cfg.K, cfg.P, cfg.Q), -7, dtype=torch.int32, device=DEV)
     assert np.array_equal(host(lib.conv2d_int8_ex(cfg.dims(), lib.LAYOUT_PACKED, 64, t[offset:].view(x.shape), wq, out, ws, wt_is_packed=True)), want)
+
+
+# Tiles of several row groups (many small images), and a result larger than the last-level cache.
+WINDOW_GROUP_SHAPES = [
+    ConvShape("win-2-groups", 1100, 1, 20, 21, 5, 3, 3, 1, 1), ConvShape("win-8-groups", 1600, 1, 33, 12, 3, 3, 3, 1, 1),
+    ConvShape("win-4-groups-s2", 310, 3, 50, 71, 16, 5, 5, 2, 2), ConvShape("win-ragged", 260, 2, 35, 70, 33, 7, 3, 1, 0),
+    ConvShape("win-2-groups-64", 200, 3, 41, 131, 40, 7, 7, 2, 3),
+]
+
+
+@pytest.mark.parametrize("cfg", WINDOW_GROUP_SHAPES, ids=lambda c: c.name)
+def test_window_row_groups(lib, cfg):
+    x, w, want = oracle_conv(cfg)
+    assert np.array_equal(host(lib.conv2d_int8(dev(x), dev(w), cfg.stride, cfg.pad)), want)
+
+
+@pytest.mark.parametrize("K", [16, 64])
+def test_window_streamed(lib, K):
+    n = 256 * 10**6 // (4 * K * 32 * 32) + 2
+    gen = torch.Generator(device=DEV).manual_seed(K)
+    x = torch.randint(-128, 128, (n, 3, 32, 32), dtype=torch.int8, device=DEV, generator=gen)
+    w = torch.randint(-128, 128, (K, 3, 3, 3), dtype=torch.int8, device=DEV, generator=gen)
+    out = lib.conv2d_int8(x, w, 1, 1)
+    half = n // 2   # each half of the batch alone stays below the limit
+    assert torch.equal(out[:half], lib.conv2d_int8(x[:half], w, 1, 1)) and torch.equal(out[half:], lib.conv2d_int8(x[half:], w, 1, 1))
+    assert np.array_equal(host(out[-2:]), direct.conv2d_int8(host(x[-2:]), host(w), 1, 1))
