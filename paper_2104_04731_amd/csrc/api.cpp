@@ -233,7 +233,7 @@ int gemm_status(hipError_t e)
 // Which kernel runs the GEMM stage: a tile of the general kernel with a depth split, or the band kernel.
 struct GemmChoice {
     int tile, split_k;  // tile == CONV_TILE_BAND: the band kernel (split_k 1)
-    double cost;        // the models' estimate for the library's own choice (cycles)
+    double cost;        // the models' estimate for the library's own choice (microseconds)
 };
 
 int choose_gemm_now(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
