@@ -148,25 +148,27 @@ __device__ __forceinline__ void window_from_pixels(const WindowSource &t, const 
 // Raw 3x3 weights: 4 channels x 9 taps of one row are 36 consecutive bytes (byte 9c + t).  raw9_load fetches them (rows past
 // the last one and channels past the last one: zeros), raw9_tap<T> picks tap T's dword of four channels out of them: three
 // byte permutes.
-__device__ __forceinline__ void raw9_load(const int8_t *wt, int K, int C, int k, int quad, unsigned (&d)[9])
+__host__ __device__ __forceinline__ void raw9_load(const int8_t *wt, int K, int C, int k, int quad, unsigned (&d)[9])
 {
 #pragma unroll
     for (int i = 0; i < 9; ++i) d[i] = 0;
     const int valid = k < K ? min(C - quad * 4, 4) * 9 : 0;   // bytes that belong to this row's channels
     if (valid <= 0) return;
     const int8_t *p = wt + (long long)k * C * 9 + (long long)quad * 36;
-    if (valid == 36 || k < K - 1) {   // (behind a row's last channels comes the next row)
+    // 36 bytes are left in the tensor: behind a row's last channels come the next rows, and four of them (the shortest is
+    // nine bytes) always suffice.  One row is not enough where a row has a single channel.
+    if (min(K - k, 4) * C * 9 - quad * 36 >= 36) {
         const v4i_a1 x0 = *reinterpret_cast<const v4i_a1 *>(p), x1 = *reinterpret_cast<const v4i_a1 *>(p + 16);
         d[0] = x0[0], d[1] = x0[1], d[2] = x0[2], d[3] = x0[3], d[4] = x1[0], d[5] = x1[1], d[6] = x1[2], d[7] = x1[3];
         d[8] = *reinterpret_cast<const u32_a1 *>(p + 32);
-    } else {   // the tensor's last channels, fewer than four of them
+    } else {   // the tensor's last bytes
 #pragma unroll
         for (int i = 0; i < 9; ++i)
             for (int b = 0; b < 4; ++b)
                 if (i * 4 + b < valid) d[i] |= (unsigned)(unsigned char)p[i * 4 + b] << (8 * b);
     }
 }
-__device__ __forceinline__ void raw9_mask(int C, int quad, unsigned (&d)[9])
+__host__ __device__ __forceinline__ void raw9_mask(int C, int quad, unsigned (&d)[9])
 {
     const int valid = min(C - quad * 4, 4) * 9;
     if (valid < 36 && valid > 0) {

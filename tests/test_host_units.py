@@ -1,0 +1,23 @@
+"""Pieces of the library's code that can run on the host, compiled for the host and run there (no GPU)."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "host")
+
+
+@pytest.fixture
+def run_host(tmp_path):
+    def run(name):
+        exe = str(tmp_path / name)
+        subprocess.run(["hipcc", "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", os.path.join(HERE, name + ".cpp"), "-o", exe],
+                       check=True, timeout=300)
+        r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+        return r.returncode, r.stdout.strip()
+    return run
+
+
+def test_raw_weight_loads_stay_inside_the_tensor(run_host):
+    """1 to 70 channels against weights that end at a page without access: a load past them ends the program."""
+    assert run_host("raw_weights") == (0, "ok")
