@@ -168,6 +168,34 @@ int conv2d_int8_tile_applies(const conv_desc_t *desc, int layout, int cb, int ti
  * Never above 160 KB, one compute unit's LDS (host only). */
 size_t conv2d_int8_tile_lds_bytes(const conv_desc_t *desc, int layout, int cb, int tile, int split_k);
 
+/* ---- GEMM stage on the network's own tensor ---------------------------------------------
+ * The stage that blocks the channels on its way into LDS, called directly with a tile and a number of output pixels
+ * per workgroup (the calls above choose both themselves).  nhwc = 0: in [N][C][H][W], out [N][K][P][Q]; else in
+ * [N][H][W][C], out [N][P][Q][K].  wt_cb = 0: wt is KCRS as it is (3x3 kernels only); else the output of pack_weights
+ * (PACKED, wt_cb), 16-byte aligned.  dilation >= 1; P, Q as for conv2d_int8_dilated_direct.  pixels: a multiple of 32,
+ * 32 to 1024.  A pair whose weights and input window do not fit one compute unit's LDS: CONV_ERR_UNSUPPORTED, which is
+ * also what _applies says of it (host only). */
+int conv2d_int8_resident(const conv_desc_t *desc, int dilation, int nhwc, const int8_t *in, const int8_t *wt, int wt_cb,
+                         int32_t *out, int tile, int pixels, void *stream);
+int conv2d_int8_resident_applies(const conv_desc_t *desc, int dilation, int nhwc, int wt_cb, int tile, int pixels);
+/* rows = output channels of a workgroup, cols = pixels a wave multiplies at a time; past the last tile: CONV_ERR_INVALID_ARG */
+int conv2d_int8_resident_tile_info(int tile, int *rows, int *cols, int *threads);
+
+/* Which stage a call takes (host only), for tensors that start on 64 bytes. */
+typedef enum { CONV_ENTRY_ONE_SHOT = 0, CONV_ENTRY_EX = 1, CONV_ENTRY_NHWC = 2, CONV_ENTRY_DILATED = 3, CONV_ENTRY_DILATED_DIRECT = 4 } conv_entry_t;
+typedef enum {
+    CONV_STAGE_STORED = 0,           /* the rewritten operands are stored, then the GEMM stage of conv2d_int8_packed */
+    CONV_STAGE_RESIDENT = 1,         /* the stage above on the weights as they are given */
+    CONV_STAGE_RESIDENT_RAW = 2,     /* ... on KCRS weights, brought into depth order on their way into LDS */
+    CONV_STAGE_RESIDENT_REWRITE = 3, /* ... on weights that a launch of its own rewrites first */
+    CONV_STAGE_BAND = 4,             /* the band kernel (CONV_TILE_BAND) on the NCHW tensor as it is */
+    CONV_STAGE_AS_IS = 5             /* IMPLICIT's kernels; for NHWC also the 1x1 matrix product */
+} conv_stage_t;
+/* entry: which call (conv2d_int8, _ex, _nhwc, _dilated, _dilated_direct); layout, cb, wt_is_packed, dilation: its arguments,
+ * those it does not have are ignored.  tile, pixels: those of conv2d_int8_resident, -1 and 0 for the other stages. */
+int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int cb, int wt_is_packed, int dilation,
+                            int *stage, int *tile, int *pixels);
+
 /* ---- layout rewrites, individually callable (the "Transf." column of Table 3) ---------
  * pack_layout (Table 2 rows 2-4 on the input, plus the convolution's zero border):
  *   dst[n][c/cb][h+pad][w+pad][c%cb] = src[n][c][h][w]; zero where c >= C and on the border.

@@ -17,6 +17,8 @@ from . import build as _build
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_OVERFLOW_RISK, ERR_WORKSPACE, ERR_DEVICE = range(6)
 LAYOUT_AUTO, LAYOUT_PACKED, LAYOUT_IM2COL, LAYOUT_PAD_ONLY, LAYOUT_IMPLICIT, LAYOUT_IMAGE_PACK = range(6)
 TILE_BAND = -2   # CONV_TILE_BAND
+ENTRY_ONE_SHOT, ENTRY_EX, ENTRY_NHWC, ENTRY_DILATED, ENTRY_DILATED_DIRECT = range(5)
+STAGE_STORED, STAGE_RESIDENT, STAGE_RESIDENT_RAW, STAGE_RESIDENT_REWRITE, STAGE_BAND, STAGE_AS_IS = range(6)
 LAYOUT_NAMES = {LAYOUT_AUTO: "auto", LAYOUT_PACKED: "packed", LAYOUT_IM2COL: "im2col",
                 LAYOUT_PAD_ONLY: "pad_only", LAYOUT_IMPLICIT: "implicit",
                 LAYOUT_IMAGE_PACK: "image_pack"}
@@ -32,7 +34,8 @@ EXPORTS = [
     "conv2d_int8_dilated_workspace_bytes", "conv2d_int8_dilated",
     "conv2d_int8_dilated_direct_workspace_bytes", "conv2d_int8_dilated_direct",
     "gemm_int8_nt", "select_layout", "select_layout_weighted", "layout_overheads",
-    "conv_status_string",
+    "conv_status_string", "conv2d_int8_resident", "conv2d_int8_resident_applies", "conv2d_int8_resident_tile_info",
+    "conv2d_int8_query_stage",
 ]
 
 
@@ -122,6 +125,10 @@ def load(path: str | None = None):
         "select_layout_weighted": (i, [dp, dbl, dbl, ip, ip, ctypes.POINTER(dbl)]),
         "layout_overheads": (i, [dp, i, i] + [ctypes.POINTER(ctypes.c_int64)] * 3),
         "conv_status_string": (ctypes.c_char_p, [i]),
+        "conv2d_int8_resident": (i, [dp, i, i, vp, vp, i, vp, i, i, vp]),
+        "conv2d_int8_resident_applies": (i, [dp, i, i, i, i, i]),
+        "conv2d_int8_resident_tile_info": (i, [i, ip, ip, ip]),
+        "conv2d_int8_query_stage": (i, [dp, i, i, i, i, i, ip, ip, ip]),
     }
     for name, (res, args) in sig.items():
         fn = getattr(lib, name)
@@ -240,6 +247,36 @@ def tile_info(tile: int):
     _check(load().conv2d_int8_tile_info(tile, ctypes.byref(r), ctypes.byref(c), ctypes.byref(t),
                                         ctypes.byref(k)), "conv2d_int8_tile_info")
     return r.value, c.value, t.value, k.value
+
+
+# ---- GEMM stage on the network's own tensor ---------------------------------------------------
+def conv2d_int8_resident(dims, x: torch.Tensor, w: torch.Tensor, out: torch.Tensor, wt_cb: int, tile: int, pixels: int, dilation=1, nhwc=False,
+                         stream=None):
+    """The stage that blocks the channels on its way into LDS, with this tile and pixels per workgroup (wt_cb 0: KCRS weights)."""
+    _require(x, torch.int8, "input"); _require(w, torch.int8, "weights"); _require(out, torch.int32, "output")
+    _check(load().conv2d_int8_resident(ctypes.byref(_desc(*dims)), dilation, int(nhwc), _ptr(x), _ptr(w), wt_cb, _ptr(out), tile, pixels,
+                                       _stream(stream)), "conv2d_int8_resident")
+    return out
+
+
+def resident_applies(dims, wt_cb: int, tile: int, pixels: int, dilation=1, nhwc=False) -> bool:
+    return load().conv2d_int8_resident_applies(ctypes.byref(_desc(*dims)), dilation, int(nhwc), wt_cb, tile, pixels) == OK
+
+
+def resident_tiles():
+    """(output channels, pixels of a wave, threads) of every tile."""
+    out, v = [], [ctypes.c_int() for _ in range(3)]
+    while load().conv2d_int8_resident_tile_info(len(out), *map(ctypes.byref, v)) == OK:
+        out.append(tuple(x.value for x in v))
+    return out
+
+
+def query_stage(dims, entry, layout=LAYOUT_AUTO, cb=0, wt_is_packed=False, dilation=1):
+    """(stage, tile, pixels) of the call `entry` on tensors that start on 64 bytes."""
+    v = [ctypes.c_int() for _ in range(3)]
+    _check(load().conv2d_int8_query_stage(ctypes.byref(_desc(*dims)), entry, layout, cb, int(wt_is_packed), dilation, *map(ctypes.byref, v)),
+           "conv2d_int8_query_stage")
+    return tuple(x.value for x in v)
 
 
 # ---- layout rewrites ------------------------------------------------------------------------

@@ -325,7 +325,13 @@ double two_stage_us(const GemmProblem &g, double moved, double weights, bool wt_
     return us + SECOND_LAUNCH_US;
 }
 
-enum RouteHow : int { TWO_STAGE = 0, DIRECT_AS_IS = 1, DIRECT_RAW = 2, DIRECT_REWRITE = 3, DIRECT_BAND = 4 };
+enum RouteHow : int {
+    TWO_STAGE = CONV_STAGE_STORED,
+    DIRECT_AS_IS = CONV_STAGE_RESIDENT,
+    DIRECT_RAW = CONV_STAGE_RESIDENT_RAW,
+    DIRECT_REWRITE = CONV_STAGE_RESIDENT_REWRITE,
+    DIRECT_BAND = CONV_STAGE_BAND
+};
 struct Route {
     int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones, band kernel on packed ones
     ResidentChoice pick;
@@ -448,6 +454,56 @@ int one_shot_route(const conv_desc_t *d, int layout, int cb, const int8_t *in, c
         return two_stage_us(gemm_problem(d, own, nullptr, nullptr, out), in_bytes + (double)own.x_bytes, (double)own.w_bytes, false);
     });
     return CONV_OK;
+}
+
+// The same choice for the other entry points.
+Route ex_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, const int8_t *wt, int32_t *out)
+{
+    if (pl.layout == CONV_LAYOUT_IM2COL) return Route{TWO_STAGE, {}, 0, 0};
+    return pick_route(d, pl, wt_is_packed, false, 1, wt, out, false, 0, [&] {
+        return two_stage_us(gemm_problem(d, pl, nullptr, nullptr, out), (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, wt_is_packed);
+    });
+}
+
+Route nhwc_route(const conv_desc_t *d, const Plan &pl, const int8_t *wt, int32_t *out)
+{
+    return pick_route(d, pl, false, true, 1, wt, out, true, 1, [&] {
+        GemmProblem g = gemm_problem(d, pl, nullptr, nullptr, out);
+        g.out_nhwc = 1;
+        // (a result that does not start on 16 bytes goes through a staging tensor and one more pass)
+        return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false) + (aligned16(out) ? 0 : 10);
+    });
+}
+
+Route dilated_direct_route(const conv_desc_t *d, int dilation, const Plan &pl, const int8_t *wt, int32_t *out)
+{
+    return pick_route(d, pl, false, false, dilation, wt, out, false, 2, [&] {
+        GemmProblem g = gemm_problem(d, pl, nullptr, nullptr, out);
+        g.dil = dilation;
+        return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false);
+    });
+}
+
+// (dp, inner: the dense problem on the sub-images; direct: the plan of the image as it is)
+Route dilated_route(const conv_desc_t *d, int dilation, const DilatedProblem &dp, const Plan &inner, const Plan &direct, const int8_t *wt, int32_t *out)
+{
+    return pick_route(d, direct, false, false, dilation, wt, out, false, 3, [&] {
+        const double pack = 2.5 + 0.25e-6 * ((double)d->N * d->C * d->H * d->W + (double)dp.x2_bytes) + SECOND_LAUNCH_US;
+        return pack + two_stage_us(gemm_problem(&dp.d2, inner, nullptr, nullptr, nullptr), (double)dp.x2_bytes + (double)inner.x_bytes, (double)inner.w_bytes, false);
+    });
+}
+
+// conv2d_int8_nhwc's two forms that need no rewrite at all.
+bool nhwc_window(const conv_desc_t *d, const Plan &pl, const int8_t *in, const int8_t *wt, int32_t *out, WindowProblem *wp)
+{
+    int layout = CONV_LAYOUT_AUTO, cb = 0;
+    if (resolve_layout(d, &layout, &cb) != CONV_OK || layout != CONV_LAYOUT_IMPLICIT || pointwise_shape(d->C, d->R, d->S)) return false;
+    *wp = WindowProblem{in, wt, out, d->N, d->C, d->H, d->W, d->K, pl.P, pl.Q, d->R, d->S, d->stride, d->pad, 0, ActOut{}, 1, 1};
+    return window_fits(*wp);
+}
+bool nhwc_matrix(const conv_desc_t *d, const int8_t *in, const int8_t *wt, const int32_t *out)
+{
+    return d->R == 1 && d->S == 1 && d->stride == 1 && d->pad == 0 && d->C % CONV_DEPTH_ALIGN == 0 && aligned16(in) && aligned16(wt) && aligned16(out);
 }
 
 int rewrite_weights(const conv_desc_t *d, const Plan &pl, const int8_t *wt, int8_t *dst, hipStream_t st)
@@ -815,10 +871,7 @@ int conv2d_int8_dilated(const conv_desc_t *desc, int dilation, int layout, int c
     Plan direct;
     if (library_chooses && direct_dilated_plan(desc, dilation, 0, &direct) == CONV_OK) {
         // the library's choice may also be the kernel that reads its taps `dilation` pixels apart from the image as it is
-        const Route rt = pick_route(desc, direct, false, false, dilation, wt, out, false, 3, [&] {
-            const double pack = 2.5 + 0.25e-6 * ((double)desc->N * desc->C * desc->H * desc->W + (double)dp.x2_bytes) + SECOND_LAUNCH_US;
-            return pack + two_stage_us(gemm_problem(&dp.d2, pl, nullptr, nullptr, nullptr), (double)dp.x2_bytes + (double)pl.x_bytes, (double)pl.w_bytes, false);
-        });
+        const Route rt = dilated_route(desc, dilation, dp, pl, direct, wt, out);
         if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes)
             return run_direct(rt, desc, direct, false, dilation, in, wt, out, false, workspace, (hipStream_t)stream);
     }
@@ -871,11 +924,7 @@ int conv2d_int8_dilated_direct(const conv_desc_t *desc, int dilation, int cb, co
     const size_t xb = align_up(pl.x_bytes, WS_ALIGN);
     if (workspace_bytes < xb + align_up(pl.w_bytes, WS_ALIGN)) return CONV_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    const Route rt = pick_route(desc, pl, false, false, dilation, wt, out, false, 2, [&] {
-        GemmProblem g = gemm_problem(desc, pl, nullptr, nullptr, out);
-        g.dil = dilation;
-        return two_stage_us(g, (double)desc->N * desc->C * desc->H * desc->W + (double)pl.x_bytes, (double)pl.w_bytes, false);
-    });
+    const Route rt = dilated_direct_route(desc, dilation, pl, wt, out);
     if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, dilation, in, wt, out, false, workspace, st);
     int8_t *xq = static_cast<int8_t *>(workspace), *wq = xq + xb;
     const hipError_t e = launch_rewrite_fused(false, desc->N, desc->C, desc->H, desc->W, desc->K, desc->R, desc->S,
@@ -1018,6 +1067,87 @@ int conv2d_int8_query_tiling(const conv_desc_t *desc, int layout, int cb, int *t
     return CONV_OK;
 }
 
+int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int cb, int wt_is_packed, int dilation, int *stage, int *tile,
+                            int *pixels)
+{
+    if (!stage || !tile || !pixels) return CONV_ERR_INVALID_ARG;
+    Plan pl;
+    Route rt{TWO_STAGE, {}, 0, 0};
+    bool as_is = false;
+    int rc = CONV_OK;
+    if (entry == CONV_ENTRY_DILATED) {
+        DilatedProblem dp;
+        Plan inner;
+        const bool library_chooses = layout == CONV_LAYOUT_AUTO;
+        if ((rc = dilated_problem(desc, dilation, &dp)) != CONV_OK || (rc = resolve_layout(&dp.d2, &layout, &cb)) != CONV_OK ||
+            (rc = make_plan(&dp.d2, layout, cb, &inner)) != CONV_OK)
+            return rc;
+        if (library_chooses && direct_dilated_plan(desc, dilation, 0, &pl) == CONV_OK)
+            rt = dilated_route(desc, dilation, dp, inner, pl, nullptr, nullptr);
+    } else if (entry == CONV_ENTRY_DILATED_DIRECT) {
+        if ((rc = direct_dilated_plan(desc, dilation, cb, &pl)) != CONV_OK) return rc;
+        rt = dilated_direct_route(desc, dilation, pl, nullptr, nullptr);
+    } else if (entry == CONV_ENTRY_NHWC) {
+        if ((rc = make_plan(desc, CONV_LAYOUT_PACKED, 0, &pl)) != CONV_OK) return rc;
+        WindowProblem wp;
+        as_is = nhwc_window(desc, pl, nullptr, nullptr, nullptr, &wp) || nhwc_matrix(desc, nullptr, nullptr, nullptr);
+        if (!as_is) rt = nhwc_route(desc, pl, nullptr, nullptr);
+    } else if (entry == CONV_ENTRY_ONE_SHOT || entry == CONV_ENTRY_EX) {
+        if (entry == CONV_ENTRY_ONE_SHOT) layout = CONV_LAYOUT_AUTO, cb = 0, wt_is_packed = 0;
+        if ((rc = resolve_layout(desc, &layout, &cb)) != CONV_OK) return rc;
+        as_is = layout == CONV_LAYOUT_IMPLICIT;
+        if (layout != CONV_LAYOUT_IMAGE_PACK && (rc = make_plan(desc, layout, cb, &pl)) != CONV_OK) return rc;
+        if (entry == CONV_ENTRY_ONE_SHOT && !as_is) rc = one_shot_route(desc, layout, cb, nullptr, nullptr, nullptr, &pl, &rt);
+        if (rc == CONV_OK && rt.how == TWO_STAGE && !as_is && layout != CONV_LAYOUT_IMAGE_PACK) {   // (what conv2d_int8_ex makes of it)
+            if ((rc = make_plan(desc, layout, cb, &pl)) == CONV_OK) rt = ex_route(desc, pl, wt_is_packed != 0, nullptr, nullptr);
+        }
+        if (rc != CONV_OK) return rc;
+    } else return CONV_ERR_INVALID_ARG;
+    *stage = as_is ? CONV_STAGE_AS_IS : rt.how;
+    const bool resident = rt.how == DIRECT_AS_IS || rt.how == DIRECT_RAW || rt.how == DIRECT_REWRITE;
+    *tile = resident ? rt.pick.tile : -1;
+    *pixels = resident ? rt.pick.mper : 0;
+    return CONV_OK;
+}
+
+// ---- the resident kernel on its own --------------------------------------------------------------------------------
+static int resident_forced(const conv_desc_t *desc, int dilation, int nhwc, int wt_cb, int tile, int pixels, const int8_t *in, const int8_t *wt,
+                           int32_t *out, ResidentProblem *r)
+{
+    if (tile < 0 || tile >= resident_num_tiles() || pixels < 32 || pixels > 1024 || pixels % 32 || wt_cb < 0) return CONV_ERR_INVALID_ARG;
+    Plan pl;
+    const int rc = direct_dilated_plan(desc, dilation, wt_cb ? wt_cb : 16, &pl);
+    if (rc != CONV_OK) return rc;
+    *r = resident_problem(desc, pl, wt_cb ? pl.cb : round_up_i(desc->C, 16), pl.depth, wt_cb == 0, nhwc != 0, dilation, in, wt, out, nhwc != 0);
+    return resident_applies(*r, tile, pixels) ? CONV_OK : CONV_ERR_UNSUPPORTED;
+}
+
+int conv2d_int8_resident_tile_info(int tile, int *rows, int *cols, int *threads)
+{
+    if (tile < 0 || tile >= resident_num_tiles()) return CONV_ERR_INVALID_ARG;
+    const TileInfo t = resident_tile_info(tile);
+    if (rows) *rows = t.rows;
+    if (cols) *cols = t.cols;
+    if (threads) *threads = t.threads;
+    return CONV_OK;
+}
+
+int conv2d_int8_resident_applies(const conv_desc_t *desc, int dilation, int nhwc, int wt_cb, int tile, int pixels)
+{
+    ResidentProblem r;
+    return resident_forced(desc, dilation, nhwc, wt_cb, tile, pixels, nullptr, nullptr, nullptr, &r);
+}
+
+int conv2d_int8_resident(const conv_desc_t *desc, int dilation, int nhwc, const int8_t *in, const int8_t *wt, int wt_cb, int32_t *out, int tile,
+                         int pixels, void *stream)
+{
+    ResidentProblem r;
+    const int rc = resident_forced(desc, dilation, nhwc, wt_cb, tile, pixels, in, wt, out, &r);
+    if (rc != CONV_OK) return rc;
+    if (!in || !wt || !out || (wt_cb && !aligned16(wt))) return CONV_ERR_INVALID_ARG;
+    return gemm_status(launch_resident_forced(r, tile, pixels, (hipStream_t)stream));
+}
+
 int conv2d_int8_tile_applies(const conv_desc_t *desc, int layout, int cb, int tile, int split_k)
 {
     if (layout == CONV_LAYOUT_AUTO || (tile < 0 && tile != CONV_TILE_BAND) || tile >= gemm_num_tiles() || split_k < 1)
@@ -1094,13 +1224,8 @@ int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb, const int8_t *in
     const size_t need = xb + (wt_is_packed ? 0 : align_up(pl.w_bytes, WS_ALIGN));
     if (workspace_bytes < need) return CONV_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    if (pl.layout != CONV_LAYOUT_IM2COL) {
-        const Route rt = pick_route(desc, pl, wt_is_packed != 0, false, 1, wt, out, false, 0, [&] {
-            return two_stage_us(gemm_problem(desc, pl, nullptr, nullptr, out), (double)desc->N * desc->C * desc->H * desc->W + (double)pl.x_bytes,
-                                (double)pl.w_bytes, wt_is_packed != 0);
-        });
-        if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, 1, in, wt, out, false, workspace, st);
-    }
+    const Route rt = ex_route(desc, pl, wt_is_packed != 0, wt, out);
+    if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, 1, in, wt, out, false, workspace, st);
     int8_t *xq = static_cast<int8_t *>(workspace);
     const int8_t *wq = wt;
     bool rewritten = false;
@@ -1198,14 +1323,10 @@ int conv2d_int8_nhwc(int N, int C, int H, int W, int K, int R, int S, int stride
     if (rc != CONV_OK) return rc;
     if (!in || !wt || !out) return CONV_ERR_INVALID_ARG;
     {   // the selector's choice is the kernel that unrolls the stencil itself, and its NHWC form takes the shape: one launch
-        int layout = CONV_LAYOUT_AUTO, cb = 0;
-        if (resolve_layout(&d, &layout, &cb) == CONV_OK && layout == CONV_LAYOUT_IMPLICIT && !pointwise_shape(C, R, S)) {
-            WindowProblem wp{in, wt, out, N, C, H, W, K, pl.P, pl.Q, R, S, stride, pad, 0, ActOut{}, 1, 1};
-            if (window_fits(wp))
-                return launch_window_conv(wp, (hipStream_t)stream) == hipSuccess ? CONV_OK : CONV_ERR_DEVICE;
-        }
+        WindowProblem wp;
+        if (nhwc_window(&d, pl, in, wt, out, &wp)) return launch_window_conv(wp, (hipStream_t)stream) == hipSuccess ? CONV_OK : CONV_ERR_DEVICE;
     }
-    if (R == 1 && S == 1 && stride == 1 && pad == 0 && C % CONV_DEPTH_ALIGN == 0 && aligned16(in) && aligned16(wt) && aligned16(out)) {
+    if (nhwc_matrix(&d, in, wt, out)) {
         // A 1x1 layer on NHWC tensors is a plain matrix product of operands that are depth-contiguous as they are:
         // pixels x channels times the weight rows, into pixels x output channels.  No rewrite, one launch.
         if (pointwise_nhwc_split_fits(pl.M, C, K))   // a grid that leaves most of the chip idle: the depth split over a workgroup's waves
@@ -1232,11 +1353,7 @@ int conv2d_int8_nhwc(int N, int C, int H, int W, int K, int R, int S, int stride
     void *ws = nullptr;
     size_t ws_bytes = 0;
     hipStream_t st = (hipStream_t)stream;
-    const Route rt = pick_route(&d, pl, false, true, 1, wt, out, true, 1, [&] {
-        GemmProblem g = gemm_problem(&d, pl, nullptr, nullptr, out);
-        g.out_nhwc = 1;
-        return two_stage_us(g, (double)N * C * H * W + (double)pl.x_bytes, (double)pl.w_bytes, false) + (direct ? 0 : 10);
-    });
+    const Route rt = nhwc_route(&d, pl, wt, out);
     rc = cached_workspace(need, st, &ws, &ws_bytes);
     if (rc != CONV_OK) return rc;
     if (rt.how != TWO_STAGE && direct_bytes(rt, &d) <= ws_bytes) return run_direct(rt, &d, pl, true, 1, in, wt, out, true, ws, st);

@@ -87,6 +87,11 @@ struct ResidentChoice {
 };
 bool resident_pick(const ResidentProblem &r, ResidentChoice *c);   // false: outside the kernel's domain
 hipError_t launch_resident(const ResidentProblem &r, const ResidentChoice &c, hipStream_t st);
+// A tile and pixel count of the caller's choosing (0 <= tile < resident_num_tiles(), mper a positive multiple of 32).
+int resident_num_tiles();
+TileInfo resident_tile_info(int tile);   // rows: output channels of a workgroup, cols: pixels a wave multiplies at a time
+bool resident_applies(const ResidentProblem &r, int tile, int mper);
+hipError_t launch_resident_forced(const ResidentProblem &r, int tile, int mper, hipStream_t st);
 // The band kernel on the same problem (NCHW, weights in blocks of 64): estimated launch time; false: not its domain.
 bool band_direct_us(const ResidentProblem &r, double *us);
 hipError_t launch_band_direct(const ResidentProblem &r, hipStream_t st);

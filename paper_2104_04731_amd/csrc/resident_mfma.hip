@@ -612,22 +612,41 @@ bool resident_pick(const ResidentProblem &r, ResidentChoice *c)
     return false;
 }
 
-hipError_t launch_resident(const ResidentProblem &r, const ResidentChoice &c, hipStream_t st)
+static hipError_t launch_plan(const ResidentProblem &r, const ResidentPlan &p, hipStream_t st)
 {
-    static thread_local PlanTable<ResidentKey, ResidentPlan, 32> plans;
-    const ResidentPlan *kept = plans.get(resident_key(r), [&](ResidentPlan *p) { return resident_plan(r, c.tile, c.mper, p); });
-    if (!kept) return hipErrorInvalidValue;
-    ResidentArgs a = kept->a;
+    ResidentArgs a = p.a;
     a.src = r.src;
     a.wq = r.g.wq;
     a.out = r.g.out;
     a.act.out = r.g.act_out;
     int index = 0;
 #define C2I8_CASE(tk, wk, nw, fm, fit) \
-    if (kept->tile == index++) return launch_res_tile<tk, wk, nw, fm>(a, r.pixel_major, kept->uni, r.raw_weights, kept->lds, st);
+    if (p.tile == index++) return launch_res_tile<tk, wk, nw, fm>(a, r.pixel_major, p.uni, r.raw_weights, p.lds, st);
     C2I8_RES_LIST(C2I8_CASE)
 #undef C2I8_CASE
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_resident(const ResidentProblem &r, const ResidentChoice &c, hipStream_t st)
+{
+    static thread_local PlanTable<ResidentKey, ResidentPlan, 32> plans;
+    const ResidentPlan *kept = plans.get(resident_key(r), [&](ResidentPlan *p) { return resident_plan(r, c.tile, c.mper, p); });
+    return kept ? launch_plan(r, *kept, st) : hipErrorInvalidValue;
+}
+
+int resident_num_tiles() { return kNumResTiles; }
+TileInfo resident_tile_info(int tile) { return TileInfo{kResTiles[tile].tk, kResTiles[tile].fm * 32, kResTiles[tile].nw * 64, 0}; }
+
+bool resident_applies(const ResidentProblem &r, int tile, int mper)
+{
+    ResidentPlan p;
+    return resident_plan(r, tile, mper, &p);
+}
+
+hipError_t launch_resident_forced(const ResidentProblem &r, int tile, int mper, hipStream_t st)
+{
+    ResidentPlan p;   // (not kept: the table holds the library's own choices)
+    return resident_plan(r, tile, mper, &p) ? launch_plan(r, p, st) : hipErrorInvalidValue;
 }
 
 }  // namespace c2i8

@@ -391,3 +391,42 @@ def test_im2col_nhwc_validation(lib):
     assert raw.pack_weights_rsc(0, 3, 3, 3, p, p, None) == lib.ERR_INVALID_ARG
     assert raw.pack_weights_rsc(4, 3, 3, 3, None, p, None) == lib.ERR_INVALID_ARG
     assert raw.pack_weights_rsc(4, 65536, 3, 3, p, p, None) == lib.ERR_OVERFLOW_RISK
+
+
+def test_resident_stage_validation(lib):
+    raw = lib.load()
+    d = lib.ConvDesc(2, 20, 14, 14, 32, 3, 3, 1, 1)
+    p = ctypes.c_void_p(256)
+    call = lambda x=p, w=p, o=p, cb=32, tile=0, px=64, dil=1, desc=d: raw.conv2d_int8_resident(ctypes.byref(desc), dil, 0, x, w, cb, o, tile, px, None)
+    assert call(x=None) == lib.ERR_INVALID_ARG and call(w=None) == lib.ERR_INVALID_ARG and call(o=None) == lib.ERR_INVALID_ARG
+    assert call(w=ctypes.c_void_p(260)) == lib.ERR_INVALID_ARG            # rewritten weights are fetched in 16-byte pieces
+    assert call(tile=-1) == lib.ERR_INVALID_ARG and call(tile=len(lib.resident_tiles())) == lib.ERR_INVALID_ARG
+    assert call(px=0) == lib.ERR_INVALID_ARG and call(px=48) == lib.ERR_INVALID_ARG and call(px=1056) == lib.ERR_INVALID_ARG
+    assert call(cb=24) == lib.ERR_UNSUPPORTED and call(cb=-16) == lib.ERR_INVALID_ARG
+    assert call(dil=0) == lib.ERR_INVALID_ARG and call(dil=8) == lib.ERR_INVALID_ARG   # spread extent 17 > 16
+    assert call(cb=0, desc=lib.ConvDesc(2, 20, 14, 14, 32, 5, 5, 1, 2)) == lib.ERR_UNSUPPORTED   # raw weights: 3x3 only
+    assert call(desc=lib.ConvDesc(2, 1024, 14, 14, 32, 3, 3, 1, 1)) == lib.ERR_UNSUPPORTED       # more weights than LDS
+    assert raw.conv2d_int8_resident(None, 1, 0, p, p, 32, p, 0, 64, None) == lib.ERR_INVALID_ARG
+    assert lib.resident_applies((2, 20, 14, 14, 32, 3, 3, 1, 1), 32, 0, 64)
+
+
+def test_query_stage(lib):
+    raw = lib.load()
+    v = [ctypes.c_int() for _ in range(3)]
+    d = lib.ConvDesc(2, 20, 14, 14, 32, 3, 3, 1, 1)
+    assert raw.conv2d_int8_query_stage(ctypes.byref(d), 5, 0, 0, 0, 1, *map(ctypes.byref, v)) == lib.ERR_INVALID_ARG
+    assert raw.conv2d_int8_query_stage(ctypes.byref(d), 0, 0, 0, 0, 1, None, None, None) == lib.ERR_INVALID_ARG
+    assert raw.conv2d_int8_query_stage(None, 0, 0, 0, 0, 1, *map(ctypes.byref, v)) == lib.ERR_INVALID_ARG
+    for layout, cb in ((lib.LAYOUT_IM2COL, 0), (lib.LAYOUT_PACKED, 64), (lib.LAYOUT_PAD_ONLY, 0), (lib.LAYOUT_IMPLICIT, 0)):
+        for cfg in ALL_SHAPES:
+            if not lib.layout_applies(cfg.dims(), layout, cb):
+                continue
+            for packed in (False, True):
+                stage, tile, pixels = lib.query_stage(cfg.dims(), lib.ENTRY_EX, layout, cb, packed)
+                assert (stage == lib.STAGE_AS_IS) == (layout == lib.LAYOUT_IMPLICIT)
+                assert layout != lib.LAYOUT_IM2COL or stage == lib.STAGE_STORED
+                if stage in (lib.STAGE_RESIDENT, lib.STAGE_RESIDENT_RAW, lib.STAGE_RESIDENT_REWRITE):
+                    wt_cb = {lib.STAGE_RESIDENT_RAW: 0, lib.STAGE_RESIDENT_REWRITE: -(-cfg.C // 16) * 16}.get(stage, cb or -(-cfg.C // 16) * 16)
+                    assert lib.resident_applies(cfg.dims(), wt_cb, tile, pixels)
+                else:
+                    assert (tile, pixels) == (-1, 0)

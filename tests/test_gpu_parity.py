@@ -1307,3 +1307,57 @@ def test_window_streamed(lib, K):
     half = n // 2   # each half of the batch alone stays below the limit
     assert torch.equal(out[:half], lib.conv2d_int8(x[:half], w, 1, 1)) and torch.equal(out[half:], lib.conv2d_int8(x[half:], w, 1, 1))
     assert np.array_equal(host(out[-2:]), direct.conv2d_int8(host(x[-2:]), host(w), 1, 1))
+
+
+# The same stage with the tile and the pixels per workgroup given, so that every tile runs whatever the library would pick: a row
+# of one to three channels (the weights' last loads), channels that fill no quad, chunk or step, whole 64-channel rows on
+# planes of whole 64-byte sectors (streamed stores), tiles over many images, more blocks per workgroup than it has waves.
+RESIDENT_FORCED = [
+    ConvShape("rf-c1", 2, 1, 12, 11, 512, 3, 3, 1, 1), ConvShape("rf-c2", 2, 2, 9, 14, 65, 3, 3, 1, 1), ConvShape("rf-c3", 3, 3, 10, 10, 33, 3, 3, 2, 1),
+    ConvShape("rf-c17", 3, 17, 19, 23, 96, 3, 3, 1, 1), ConvShape("rf-c64-16x16", 5, 64, 16, 16, 128, 3, 3, 1, 1),
+    ConvShape("rf-c64-many", 90, 64, 3, 3, 64, 3, 3, 1, 1), ConvShape("rf-c72-s2", 2, 72, 29, 30, 70, 3, 3, 2, 1),
+    ConvShape("rf-c130", 1, 130, 40, 40, 64, 3, 3, 1, 1), ConvShape("rf-5x5", 2, 20, 21, 18, 64, 5, 5, 1, 2),
+    ConvShape("rf-1x1", 4, 128, 13, 14, 96, 1, 1, 1, 0), ConvShape("rf-dil3", 2, 48, 20, 17, 64, 3, 3, 1, 3),
+]
+
+
+@pytest.mark.parametrize("cfg", RESIDENT_FORCED, ids=lambda c: c.name)
+def test_resident_every_tile(lib, cfg):
+    x = uniform_int8(991, (cfg.N, cfg.C, cfg.H, cfg.W)); w = uniform_int8(992, (cfg.K, cfg.C, cfg.R, cfg.S))
+    dil = 3 if cfg.name == "rf-dil3" else 1
+    want = direct.conv2d_int8_dilated(x, w, cfg.stride, cfg.pad, dil)
+    want_h = layouts.unpack_nhwc(want)
+    dx, dxh = dev(x), dev(np.ascontiguousarray(x.transpose(0, 2, 3, 1)))
+    weights = [(cb, lib.pack_weights(dev(w), lib.LAYOUT_PACKED, cb)) for cb in (16, 64, layouts.ceil_to(cfg.C, 16))]
+    if (cfg.R, cfg.S) == (3, 3):   # raw weights, at an aligned address and behind one
+        odd = torch.empty(w.size + 3, dtype=torch.int8, device=DEV)
+        odd[3:] = dev(w).view(-1)
+        weights += [(0, dev(w)), (0, odd[3:].view(w.shape))]
+    ran = set()
+    for tile, (rows, cols, threads) in enumerate(lib.resident_tiles()):
+        for pixels in (32, 96, threads // 64 * cols + 64, 1024):
+            for cb, wq in weights:
+                for nhwc in (False, True):
+                    if not lib.resident_applies(cfg.dims(), cb, tile, pixels, dil, nhwc):
+                        with pytest.raises(lib.ConvError) as e:
+                            lib.conv2d_int8_resident(cfg.dims(), dxh if nhwc else dx, wq, torch.empty(1, dtype=torch.int32, device=DEV), cb, tile, pixels, dil, nhwc)
+                        assert e.value.status == lib.ERR_UNSUPPORTED
+                        continue
+                    buf = torch.full((want.size + 128,), -7, dtype=torch.int32, device=DEV)
+                    out = buf[64:64 + want.size].view(want_h.shape if nhwc else want.shape)
+                    lib.conv2d_int8_resident(cfg.dims(), dxh if nhwc else dx, wq, out, cb, tile, pixels, dil, nhwc)
+                    got = host(buf)
+                    assert np.array_equal(got[64:-64].reshape(out.shape), want_h if nhwc else want), (tile, pixels, cb, nhwc)
+                    assert (got[:64] == -7).all() and (got[-64:] == -7).all(), (tile, pixels, cb, nhwc)
+                    ran.add((tile, pixels > threads // 64 * cols, cb == 0, nhwc))
+    raw = (False, True) if (cfg.R, cfg.S) == (3, 3) else (False,)
+    small = cfg.C <= 72   # (deeper weights leave the 64-channel tiles no room for a large window)
+    assert not small or {(t, many, r, h) for t in range(len(lib.resident_tiles())) for many in (False, True) for r in raw for h in (False, True)} <= ran
+
+
+def test_band_direct_shapes_run_the_band_kernel(lib):
+    wide = ConvShape("band-c256-w71", 1, 256, 3, 71, 128, 3, 3, 1, 1)   # one output row per band, six blocks of columns
+    assert [c.name for c in BAND_DIRECT_SHAPES if lib.query_stage(c.dims(), lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True)[0] != lib.STAGE_BAND] == ["band-c256-wide"]
+    assert lib.query_stage(wide.dims(), lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True)[0] == lib.STAGE_BAND
+    for offset in (0, 3):
+        test_band_direct(lib, wide, offset)
