@@ -179,9 +179,11 @@ def main():
             wall, comb = timed(self.combined, steps, warmup)
             _, pre = timed(self.combined_prepacked, steps, warmup)
             o_mac = lib.layout_overheads(cfg.dims(), self.layout, self.cb)[0]   # multiply-accumulates on padding
-            # Every candidate layout the library has for this shape, through the explicit entry point with a
-            # caller workspace (input rewrite + weight rewrite + GEMM stage each call): what the selector's pick
+            # Every candidate layout the library has for this shape, taken at its word (input rewrite + weight rewrite
+            # stored in a caller workspace, then the GEMM stage; IMPLICIT stores nothing): what the selector's pick
             # costs against the fastest candidate (Sec. 4.4: the choice depends on operator, layout and metric).
+            # (conv2d_int8_ex would not tell them apart: where the stage that blocks the channels on its way into LDS
+            # is estimated faster, it runs that for every blocked layout.)
             cands = []
             for lay, cb in ((lib.LAYOUT_PACKED, 64), (lib.LAYOUT_PACKED, 32), (lib.LAYOUT_PACKED, 16), (lib.LAYOUT_IM2COL, 0),
                             (lib.LAYOUT_PAD_ONLY, 0), (lib.LAYOUT_IMPLICIT, 0), (lib.LAYOUT_IMAGE_PACK, 0),
@@ -191,7 +193,7 @@ def main():
                 nb = lib.conv2d_int8_workspace_bytes(cfg.dims(), lay, cb)
                 wsb = torch.empty(nb + 256, dtype=torch.int8, device=dev)
                 wsa = wsb[(-wsb.data_ptr()) % 256:] if nb else None
-                _, t = timed(lambda: lib.conv2d_int8_ex(cfg.dims(), lay, cb, self.x, self.w, self.out, wsa), min(steps, 100), 3)
+                _, t = timed(lambda: lib.conv2d_int8_stored(cfg.dims(), lay, cb, self.x, self.w, self.out, wsa), min(steps, 100), 3)
                 cands.append({"layout": lib.LAYOUT_NAMES[lay], "cb": cb, "combined_us": round(t * 1e3, 3),
                               "picked": (lay, cb) == (self.layout, self.cb if lay != lib.LAYOUT_PAD_ONLY else 0)})
                 del wsb
@@ -215,6 +217,8 @@ def main():
                 "tile": f"{rows}x{cols}", "split_k": self.split, "ops": cfg.ops,
                 "op_us": round(op * 1e3, 3), "transf_in_us": round(tr * 1e3, 3) if tr else None,
                 "transf_wt_us": round(trw * 1e3, 3), "combined_us": round(comb * 1e3, 3),
+                "combined_stage": lib.STAGE_NAMES[lib.query_stage(cfg.dims(), lib.ENTRY_ONE_SHOT)[0]],
+                "prepacked_stage": lib.STAGE_NAMES[lib.query_stage(cfg.dims(), lib.ENTRY_EX, self.layout, self.cb, True)[0]],
                 "combined_weights_prepacked_us": round(pre * 1e3, 3),
                 "tops_op": round(cfg.ops / (op * 1e-3) / 1e12, 3),
                 "issued_tops_op": round((cfg.ops + 2 * o_mac) / (op * 1e-3) / 1e12, 3),
@@ -334,7 +338,7 @@ def main():
 
         def step_two_stage():
             for c, w in zip(head, ws):
-                lib.conv2d_int8_ex(c.cfg.dims(), lib.LAYOUT_PACKED, 64, c.x, c.w, c.out, w)
+                lib.conv2d_int8_stored(c.cfg.dims(), lib.LAYOUT_PACKED, 64, c.x, c.w, c.out, w)
 
         ts_ms, _ = timed(step_two_stage, args.steps, args.warmup)
         two_stage = {"ms_per_step": round(ts_ms, 6), "value": round(head_ops / (ts_ms * 1e-3) / 1e12, 4),

@@ -136,6 +136,12 @@ int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb,
                    void *workspace, size_t workspace_bytes, void *stream);
 size_t conv2d_int8_workspace_bytes(const conv_desc_t *desc, int layout, int cb, int wt_is_packed);
 
+/* The same with `layout` and `cb` taken at their word: the operands are rewritten into the workspace in that layout and
+ * the GEMM stage of conv2d_int8_packed reads them from there (IMPLICIT, which rewrites nothing, as above). */
+int conv2d_int8_stored(const conv_desc_t *desc, int layout, int cb,
+                       const int8_t *in, const int8_t *wt, int wt_is_packed, int32_t *out,
+                       void *workspace, size_t workspace_bytes, void *stream);
+
 /* ---- GEMM stage alone (operands already rewritten; the "Op." column of Table 3) -------
  * in_packed: output of pack_layout (PACKED / PAD_ONLY) or im2col_int8 (IM2COL), or the NCHW
  * input itself (IMPLICIT); wt_packed: output of pack_weights.  layout must not be AUTO; cb as above (0 = 64 if

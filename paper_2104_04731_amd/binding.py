@@ -19,6 +19,7 @@ LAYOUT_AUTO, LAYOUT_PACKED, LAYOUT_IM2COL, LAYOUT_PAD_ONLY, LAYOUT_IMPLICIT, LAY
 TILE_BAND = -2   # CONV_TILE_BAND
 ENTRY_ONE_SHOT, ENTRY_EX, ENTRY_NHWC, ENTRY_DILATED, ENTRY_DILATED_DIRECT = range(5)
 STAGE_STORED, STAGE_RESIDENT, STAGE_RESIDENT_RAW, STAGE_RESIDENT_REWRITE, STAGE_BAND, STAGE_AS_IS = range(6)
+STAGE_NAMES = ("stored rewrites", "resident", "resident, raw weights", "resident, weights rewritten first", "band on NCHW", "as is")
 LAYOUT_NAMES = {LAYOUT_AUTO: "auto", LAYOUT_PACKED: "packed", LAYOUT_IM2COL: "im2col",
                 LAYOUT_PAD_ONLY: "pad_only", LAYOUT_IMPLICIT: "implicit",
                 LAYOUT_IMAGE_PACK: "image_pack"}
@@ -35,7 +36,7 @@ EXPORTS = [
     "conv2d_int8_dilated_direct_workspace_bytes", "conv2d_int8_dilated_direct",
     "gemm_int8_nt", "select_layout", "select_layout_weighted", "layout_overheads",
     "conv_status_string", "conv2d_int8_resident", "conv2d_int8_resident_applies", "conv2d_int8_resident_tile_info",
-    "conv2d_int8_query_stage",
+    "conv2d_int8_query_stage", "conv2d_int8_stored",
 ]
 
 
@@ -87,6 +88,7 @@ def load(path: str | None = None):
         "requant_int8": (i, [ctypes.c_longlong, vp, vp, i, i, vp]),
         "requant_pack_layout": (i, [i] * 8 + [vp, vp, vp]),
         "conv2d_int8_ex": (i, [dp, i, i, vp, vp, i, vp, vp, sz, vp]),
+        "conv2d_int8_stored": (i, [dp, i, i, vp, vp, i, vp, vp, sz, vp]),
         "conv2d_int8_workspace_bytes": (sz, [dp, i, i, i]),
         "conv2d_int8_packed": (i, [dp, i, i, vp, vp, vp, i, i, vp]),
         "conv2d_int8_query_tiling": (i, [dp, i, i, ip, ip]),
@@ -208,6 +210,15 @@ def conv2d_int8_workspace_bytes(dims, layout=LAYOUT_AUTO, cb=0, wt_is_packed=Fal
 
 def conv2d_int8_ex(dims, layout, cb, x, w, out, workspace, wt_is_packed=False, stream=None):
     return (_native or _calls()).conv2d_int8_ex(dims, layout, cb, x, w, out, workspace, wt_is_packed, stream)
+
+
+def conv2d_int8_stored(dims, layout, cb, x, w, out, workspace, wt_is_packed=False, stream=None):
+    """conv2d_int8_ex with the rewritten operands always stored in `layout`."""
+    _check(load().conv2d_int8_stored(ctypes.byref(_desc(*dims)), layout, cb, _ptr(x), _ptr(w), int(wt_is_packed), _ptr(out),
+                                     None if workspace is None else _ptr(workspace),
+                                     0 if workspace is None else workspace.numel() * workspace.element_size(), _stream(stream)),
+           "conv2d_int8_stored")
+    return out
 
 
 def conv2d_int8_packed(dims, layout, cb, x_packed, w_packed, out, tile=-1, split_k=0, stream=None):

@@ -1185,9 +1185,9 @@ size_t conv2d_int8_workspace_bytes(const conv_desc_t *desc, int layout, int cb, 
     return align_up(pl.x_bytes, WS_ALIGN) + (wt_is_packed ? 0 : align_up(pl.w_bytes, WS_ALIGN));
 }
 
-int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb, const int8_t *in, const int8_t *wt,
-                   int wt_is_packed, int32_t *out, void *workspace, size_t workspace_bytes,
-                   void *stream)
+// conv2d_int8_ex and conv2d_int8_stored.  stored: whatever a layout rewrites goes through the workspace.
+static int run_explicit(const conv_desc_t *desc, int layout, int cb, const int8_t *in, const int8_t *wt, int wt_is_packed, int32_t *out,
+                        void *workspace, size_t workspace_bytes, void *stream, bool stored)
 {
     int rc = resolve_layout(desc, &layout, &cb);
     if (rc != CONV_OK) return rc;
@@ -1208,8 +1208,7 @@ int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb, const int8_t *in
                               st) != hipSuccess ||
             launch_image_pack_weights(desc->K, desc->C, desc->R, desc->S, desc->stride, wt, w2, st) != hipSuccess)
             return CONV_ERR_DEVICE;
-        return conv2d_int8_ex(&pp.d2, pp.inner_layout, pp.inner_cb, x2, w2, 0, out, inner ? w2 + wb : nullptr, inner,
-                              stream);
+        return run_explicit(&pp.d2, pp.inner_layout, pp.inner_cb, x2, w2, 0, out, inner ? w2 + wb : nullptr, inner, stream, stored);
     }
     Plan pl;
     rc = make_plan(desc, layout, cb, &pl);
@@ -1224,7 +1223,7 @@ int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb, const int8_t *in
     const size_t need = xb + (wt_is_packed ? 0 : align_up(pl.w_bytes, WS_ALIGN));
     if (workspace_bytes < need) return CONV_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    const Route rt = ex_route(desc, pl, wt_is_packed != 0, wt, out);
+    const Route rt = stored ? Route{TWO_STAGE, {}, 0, 0} : ex_route(desc, pl, wt_is_packed != 0, wt, out);
     if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, 1, in, wt, out, false, workspace, st);
     int8_t *xq = static_cast<int8_t *>(workspace);
     const int8_t *wq = wt;
@@ -1248,6 +1247,20 @@ int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb, const int8_t *in
         if (rc != CONV_OK) return rc;
     }
     return run_gemm(gemm_problem(desc, pl, xq, wq, out), -1, 0, st);
+}
+
+int conv2d_int8_ex(const conv_desc_t *desc, int layout, int cb, const int8_t *in, const int8_t *wt,
+                   int wt_is_packed, int32_t *out, void *workspace, size_t workspace_bytes,
+                   void *stream)
+{
+    return run_explicit(desc, layout, cb, in, wt, wt_is_packed, out, workspace, workspace_bytes, stream, false);
+}
+
+int conv2d_int8_stored(const conv_desc_t *desc, int layout, int cb, const int8_t *in, const int8_t *wt,
+                       int wt_is_packed, int32_t *out, void *workspace, size_t workspace_bytes,
+                       void *stream)
+{
+    return run_explicit(desc, layout, cb, in, wt, wt_is_packed, out, workspace, workspace_bytes, stream, true);
 }
 
 int conv2d_int8(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,

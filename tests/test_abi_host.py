@@ -430,3 +430,18 @@ def test_query_stage(lib):
                     assert lib.resident_applies(cfg.dims(), wt_cb, tile, pixels)
                 else:
                     assert (tile, pixels) == (-1, 0)
+
+
+def test_stored_form_validates_as_the_explicit_one(lib):
+    raw = lib.load()
+    p = ctypes.c_void_p(256)
+    big = ctypes.c_size_t(1 << 40)
+    for dims, layout, cb, packed in (((1, 20, 9, 9, 8, 3, 3, 1, 1), 1, 24, 0), ((1, 20, 9, 9, 8, 3, 3, 1, 1), 9, 0, 0), ((0, 20, 9, 9, 8, 3, 3, 1, 1), 1, 16, 0),
+                                     ((1, 20, 9, 9, 8, 3, 3, 1, 1), 5, 16, 0), ((1, 20, 9, 9, 8, 3, 3, 2, 1), 5, 16, 1)):
+        d = lib.ConvDesc(*dims)
+        rc = raw.conv2d_int8_stored(ctypes.byref(d), layout, cb, p, p, packed, p, p, big, None)
+        assert rc == raw.conv2d_int8_ex(ctypes.byref(d), layout, cb, p, p, packed, p, p, big, None) != lib.OK
+    d = lib.ConvDesc(1, 20, 9, 9, 8, 3, 3, 1, 1)
+    need = lib.conv2d_int8_workspace_bytes((1, 20, 9, 9, 8, 3, 3, 1, 1), 1, 16)
+    assert raw.conv2d_int8_stored(ctypes.byref(d), 1, 16, p, p, 0, p, p, need - 1, None) == lib.ERR_WORKSPACE
+    assert raw.conv2d_int8_stored(ctypes.byref(d), 1, 16, p, p, 0, p, ctypes.c_void_p(264), need, None) == lib.ERR_INVALID_ARG

@@ -1361,3 +1361,22 @@ def test_band_direct_shapes_run_the_band_kernel(lib):
     assert lib.query_stage(wide.dims(), lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True)[0] == lib.STAGE_BAND
     for offset in (0, 3):
         test_band_direct(lib, wide, offset)
+
+
+# Layouts taken at their word, at the shapes whose conv2d_int8_ex goes to the stage above instead.
+@pytest.mark.parametrize("cfg", RESIDENT_SHAPES + [ConvShape("st-s2", 2, 20, 17, 14, 30, 3, 3, 2, 1)], ids=lambda c: c.name)
+def test_stored_layouts(lib, cfg):
+    x, w, want = oracle_conv(cfg)
+    dx, dw = dev(x), dev(w)
+    for layout, cb in ((lib.LAYOUT_PACKED, 16), (lib.LAYOUT_PACKED, 32), (lib.LAYOUT_PACKED, 64), (lib.LAYOUT_PAD_ONLY, 0), (lib.LAYOUT_IM2COL, 0),
+                       (lib.LAYOUT_IMAGE_PACK, 16), (lib.LAYOUT_IMAGE_PACK, 64)):
+        if not lib.layout_applies(cfg.dims(), layout, cb):
+            continue
+        for packed in (False, True) if layout != lib.LAYOUT_IMAGE_PACK else (False,):
+            need = lib.conv2d_int8_workspace_bytes(cfg.dims(), layout, cb, packed)
+            ws = torch.full((need + 256,), 85, dtype=torch.int8, device=DEV)
+            out = torch.full(want.shape, -7, dtype=torch.int32, device=DEV)
+            lib.conv2d_int8_stored(cfg.dims(), layout, cb, dx, lib.pack_weights(dw, layout, cb) if packed else dw, out, ws[:need], wt_is_packed=packed)
+            assert np.array_equal(host(out), want), (lib.LAYOUT_NAMES[layout], cb, packed)
+            assert not packed or layout == lib.LAYOUT_IMAGE_PACK or bool((ws[:need] != 85).any()), "nothing was stored"
+            assert bool((ws[need:] == 85).all())
