@@ -372,8 +372,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
                  int tag, TwoStage &&two_us)
 {
     static thread_local PlanTable<RouteKey, Route, 64> routes;
-    const RouteKey key{*d, {pl.layout, pl.cb, tag, (int)wt_is_packed, (int)nhwc * 2 + (int)out_nhwc, dil, (int)aligned16(wt),
-                            (int)(reinterpret_cast<uintptr_t>(out) & 63)}};
+    const RouteKey key{*d, {pl.layout, pl.cb, tag, (int)wt_is_packed, (int)nhwc * 2 + (int)out_nhwc, dil, (int)aligned16(wt), (int)aligned16(out)}};
     const Route *kept = routes.get(key, [&](Route *n) {
         double best = two_us();
         *n = Route{TWO_STAGE, {}, 0, 0};

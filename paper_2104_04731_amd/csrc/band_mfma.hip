@@ -757,7 +757,7 @@ double band_cost(const GemmProblem &g)
 hipError_t launch_band_conv(const GemmProblem &g, hipStream_t st)
 {
     // the plan (a table entry per workgroup among it) is kept per problem; the operands are this call's
-    static thread_local PlanTable<GemmKey, BandPlan, 16> plans;
+    static thread_local PlanTable<GemmKey, BandPlan, 32> plans;
     const BandPlan *kept = plans.get(gemm_key(g), [&](BandPlan *p) { return band_plan(g, p); });
     if (!kept) return hipErrorInvalidValue;
     BandPlan bp = *kept;
@@ -793,7 +793,7 @@ hipError_t launch_band_direct(const ResidentProblem &r, hipStream_t st)
         GemmKey g;
         int v[5];
     };
-    static thread_local PlanTable<Key, BandPlan, 16> plans;
+    static thread_local PlanTable<Key, BandPlan, 32> plans;
     const Key key{gemm_key(r.g), {r.N, r.C, r.H, r.W, r.pad}};
     const BandPlan *kept = plans.get(key, [&](BandPlan *p) { return band_plan(r.g, p, &r); });
     if (!kept) return hipErrorInvalidValue;

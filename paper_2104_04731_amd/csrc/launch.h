@@ -36,22 +36,26 @@ hipError_t launch(void (*kern)(P0, P1, P...), dim3 grid, dim3 block, size_t lds,
     return launch_values(kern, grid, block, lds, st, std::index_sequence_for<P0, P1, P...>{}, std::forward<A>(a)...);
 }
 
-// Direct-mapped table of N plans.  A network calls the same few layers over and over, and choosing how one runs
-// (candidate layouts, the tile model, the band kernel's block map) takes the host 0.5 to 4 us against the 2.4 us of
-// a launch.  Key: plain integers without padding, compared whole.  Meant to be thread_local: no locks, bounded, and
-// gone with the thread.
+// Table of up to N plans.  A network calls the same layers over and over, and choosing how one runs costs the host 0.5 to
+// 4 us (candidate layouts, the tile model, the band kernel's block map) and, where the resident kernel's window is walked
+// for every candidate, 9 to 18 (40 3x3 layers) -- against the 2.4 us of a launch.  A problem is looked for from its hash's slot on, up to
+// the first empty one, so N problems never displace one another (two of 20 would meet in a direct-mapped table of 64 with a
+// probability of 95 %, and evict each other on every call); in a full table a new one replaces the plan at its hash's
+// slot.  Key: plain integers without padding, compared whole.  Meant to be thread_local: no locks, bounded, and gone with
+// the thread.
 template <typename Key, typename Val, int N>
 class PlanTable {
     static_assert((N & (N - 1)) == 0, "a power of two");
     struct Entry {
         Key key;
         Val val;
-        bool used;
     };
+    unsigned hash_[N] = {};   // 0: empty
     Entry e_[N] = {};
 
 public:
-    // The plan of `key`, made by fill(&val) on a miss (fill returns false: nothing to keep, null comes back).
+    // The plan of `key`, made by fill(&val) on a miss (fill returns false: nothing to keep, null comes back).  It stays where
+    // it is until the next call.
     template <typename F>
     const Val *get(const Key &key, F &&fill)
     {
@@ -63,13 +67,17 @@ public:
             h = (h ^ w) * 2654435761u;
             h ^= h >> 15;
         }
-        Entry &e = e_[h & (N - 1)];
-        if (e.used && memcmp(&e.key, &key, sizeof(Key)) == 0) return &e.val;
-        e.used = false;
-        if (!fill(&e.val)) return nullptr;
-        e.key = key;
-        e.used = true;
-        return &e.val;
+        const unsigned first = h & (N - 1);
+        h |= 0x80000000u;
+        unsigned at = first;
+        for (int i = 0; i < N && hash_[at]; ++i, at = (at + 1) & (N - 1))
+            if (hash_[at] == h && memcmp(&e_[at].key, &key, sizeof(Key)) == 0) return &e_[at].val;
+        Val made{};
+        if (!fill(&made)) return nullptr;
+        e_[at].key = key;   // an empty slot, or, all N taken, the first one again
+        e_[at].val = made;
+        hash_[at] = h;
+        return &e_[at].val;
     }
 };
 

@@ -629,7 +629,7 @@ static hipError_t launch_plan(const ResidentProblem &r, const ResidentPlan &p, h
 
 hipError_t launch_resident(const ResidentProblem &r, const ResidentChoice &c, hipStream_t st)
 {
-    static thread_local PlanTable<ResidentKey, ResidentPlan, 32> plans;
+    static thread_local PlanTable<ResidentKey, ResidentPlan, 64> plans;
     const ResidentPlan *kept = plans.get(resident_key(r), [&](ResidentPlan *p) { return resident_plan(r, c.tile, c.mper, p); });
     return kept ? launch_plan(r, *kept, st) : hipErrorInvalidValue;
 }

@@ -21,3 +21,8 @@ def run_host(tmp_path):
 def test_raw_weight_loads_stay_inside_the_tensor(run_host):
     """1 to 70 channels against weights that end at a page without access: a load past them ends the program."""
     assert run_host("raw_weights") == (0, "ok")
+
+
+def test_plan_table_keeps_as_many_problems_as_it_holds(run_host):
+    """Plans are made once per problem while no more problems take turns than the table has places."""
+    assert run_host("plan_table") == (0, "ok")
