@@ -64,6 +64,7 @@ def _calls():
                                "(or __graft_entry__.build()) first")
         from . import _native as native
         native.set_error_class(ConvError)
+        native.set_library(_lib._handle)
         _native = native
     return _native
 

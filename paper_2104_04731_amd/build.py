@@ -33,7 +33,7 @@ def stale() -> bool:
 
 
 def native_commands():
-    """Compile and link lines of the extension module: torch's headers, the library beside it ($ORIGIN)."""
+    """Compile and link lines of the extension module: torch's headers and libraries (it is handed the loaded library)."""
     import sysconfig
 
     import torch
@@ -44,7 +44,7 @@ def native_commands():
                    "-isystem", os.path.join(root, "include"), "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
                    "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"],
                    "-c", os.path.join(CSRC, NATIVE_SOURCE), "-o", obj]
-    link_cmd = ["g++", "-shared", "-fPIC", "-o", NATIVE, obj, "-L" + PKG, "-lconv2d_int8", "-Wl,-rpath,$ORIGIN",
+    link_cmd = ["g++", "-shared", "-fPIC", "-o", NATIVE, obj, "-ldl",
                 "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-ltorch_hip", "-lc10", "-lc10_hip"]
     return compile_cmd, link_cmd
 

@@ -8,6 +8,8 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
+#include <dlfcn.h>
+
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
@@ -18,6 +20,20 @@
 namespace {
 
 PyObject *g_error = nullptr;  // binding.ConvError
+
+// The library's calls, looked up in the library that binding.load() loaded (which need not be the one beside this module).
+#define LIBRARY_CALLS(X)                                                                                                  \
+    X(conv2d_int8) X(conv2d_int8_static) X(conv2d_int8_nhwc) X(conv2d_int8_ex) X(conv2d_int8_packed) X(conv2d_int8_packed_nhwc) \
+    X(conv2d_int8_packed_requant) X(pack_layout) X(pack_layout_nhwc) X(pack_layout_bytes) X(pack_weights) X(pack_weights_depth) \
+    X(im2col_int8) X(im2col_nhwc_int8) X(unpack_nhwc_int32) X(requant_int8) X(requant_pack_layout) X(conv2d_int8_dilated)  \
+    X(conv2d_int8_dilated_workspace_bytes) X(conv2d_int8_dilated_direct) X(conv2d_int8_dilated_direct_workspace_bytes)     \
+    X(gemm_int8_nt)
+struct Library {
+#define CALL(name) decltype(&::name) name;
+    LIBRARY_CALLS(CALL)
+#undef CALL
+} lib;
+bool g_loaded = false;
 
 struct PyFail {};  // a Python error is set
 
@@ -159,6 +175,10 @@ PyObject *guarded(Py_ssize_t n, Py_ssize_t want, F &&f)
         PyErr_Format(PyExc_TypeError, "expected %zd arguments, got %zd", want, n);
         return nullptr;
     }
+    if (!g_loaded) {
+        PyErr_SetString(PyExc_RuntimeError, "no library has been loaded: use the functions of binding.py");
+        return nullptr;
+    }
     HANDLE_TH_ERRORS  // torch's own exceptions (out of memory among them) under their Python names
     try {
         return f();
@@ -211,9 +231,9 @@ PyObject *one_shot(PyObject *const *a, const char *name, bool nhwc, bool given_o
     return out.result();
 }
 
-NATIVE(conv2d_int8, 6, { return one_shot(a, "conv2d_int8", false, false, conv2d_int8); })
-NATIVE(conv2d_int8_static, 6, { return one_shot(a, "conv2d_int8_static", false, true, conv2d_int8_static); })
-NATIVE(conv2d_int8_nhwc, 6, { return one_shot(a, "conv2d_int8_nhwc", true, false, conv2d_int8_nhwc); })
+NATIVE(conv2d_int8, 6, { return one_shot(a, "conv2d_int8", false, false, lib.conv2d_int8); })
+NATIVE(conv2d_int8_static, 6, { return one_shot(a, "conv2d_int8_static", false, true, lib.conv2d_int8_static); })
+NATIVE(conv2d_int8_nhwc, 6, { return one_shot(a, "conv2d_int8_nhwc", true, false, lib.conv2d_int8_nhwc); })
 
 // (dims, layout, cb, x, w, out, workspace, wt_is_packed, stream)
 NATIVE(conv2d_int8_ex, 9, {
@@ -226,7 +246,7 @@ NATIVE(conv2d_int8_ex, 9, {
     int rc;
     {
         NoGil unlocked;
-        rc = conv2d_int8_ex(&d, layout, cb, (const int8_t *)x.data_ptr(), (const int8_t *)w.data_ptr(), packed, (int32_t *)o.data_ptr(),
+        rc = lib.conv2d_int8_ex(&d, layout, cb, (const int8_t *)x.data_ptr(), (const int8_t *)w.data_ptr(), packed, (int32_t *)o.data_ptr(),
                             ws ? ws->data_ptr() : nullptr, ws ? (size_t)ws->numel() * ws->element_size() : 0, st);
     }
     check(rc, "conv2d_int8_ex");
@@ -252,8 +272,8 @@ PyObject *gemm_stage(PyObject *const *a, const char *name, F &&call)
     return a[5];
 }
 
-NATIVE(conv2d_int8_packed, 9, { return gemm_stage(a, "conv2d_int8_packed", conv2d_int8_packed); })
-NATIVE(conv2d_int8_packed_nhwc, 9, { return gemm_stage(a, "conv2d_int8_packed_nhwc", conv2d_int8_packed_nhwc); })
+NATIVE(conv2d_int8_packed, 9, { return gemm_stage(a, "conv2d_int8_packed", lib.conv2d_int8_packed); })
+NATIVE(conv2d_int8_packed_nhwc, 9, { return gemm_stage(a, "conv2d_int8_packed_nhwc", lib.conv2d_int8_packed_nhwc); })
 
 // (dims, layout, cb, x_packed, w_packed, out_cb, out_pad, shift, relu, out, stream)
 NATIVE(conv2d_int8_packed_requant, 11, {
@@ -280,7 +300,7 @@ NATIVE(conv2d_int8_packed_requant, 11, {
             const int64_t shape[5] = {d.N, (d.K + (int64_t)out_cb - 1) / out_cb, P + 2LL * out_pad, Q + 2LL * out_pad, out_cb};
             out.made = empty_like_device(x, shape, at::kChar);
         }
-        rc = conv2d_int8_packed_requant(&d, layout, cb, (const int8_t *)x.data_ptr(), (const int8_t *)w.data_ptr(), (int8_t *)out.ptr(),
+        rc = lib.conv2d_int8_packed_requant(&d, layout, cb, (const int8_t *)x.data_ptr(), (const int8_t *)w.data_ptr(), (int8_t *)out.ptr(),
                                         out_cb, out_pad, shift, relu, st);
     }
     check(rc, "conv2d_int8_packed_requant");
@@ -299,7 +319,7 @@ PyObject *pack(PyObject *const *a, const char *name, bool nhwc, F &&call)
     if (out.given) tensor(a[3], "output");
     void *st = as_stream(a[4]);
     const int64_t N = x.size(0), C = x.size(nhwc ? 3 : 1), H = x.size(nhwc ? 1 : 2), W = x.size(nhwc ? 2 : 3);
-    if (!out.given && (pack_layout_bytes((int)N, (int)C, (int)H, (int)W, cb, pad) == 0 || (nhwc && cb % 16)))
+    if (!out.given && (lib.pack_layout_bytes((int)N, (int)C, (int)H, (int)W, cb, pad) == 0 || (nhwc && cb % 16)))
         fail(CONV_ERR_UNSUPPORTED, name);
     int rc;
     {
@@ -314,8 +334,8 @@ PyObject *pack(PyObject *const *a, const char *name, bool nhwc, F &&call)
     return out.result();
 }
 
-NATIVE(pack_layout, 5, { return pack(a, "pack_layout", false, pack_layout); })
-NATIVE(pack_layout_nhwc, 5, { return pack(a, "pack_layout_nhwc", true, pack_layout_nhwc); })
+NATIVE(pack_layout, 5, { return pack(a, "pack_layout", false, lib.pack_layout); })
+NATIVE(pack_layout_nhwc, 5, { return pack(a, "pack_layout_nhwc", true, lib.pack_layout_nhwc); })
 
 // (w, layout, cb, out, stream)
 NATIVE(pack_weights, 5, {
@@ -326,13 +346,13 @@ NATIVE(pack_weights, 5, {
     Out out(a[3]);
     if (out.given) tensor(a[3], "output");
     void *st = as_stream(a[4]);
-    const int depth = out.given ? 0 : pack_weights_depth(C, R, S, layout, cb);
+    const int depth = out.given ? 0 : lib.pack_weights_depth(C, R, S, layout, cb);
     if (!out.given && depth == 0) fail(CONV_ERR_UNSUPPORTED, "pack_weights");
     int rc;
     {
         NoGil unlocked;
         if (!out.given) out.made = empty_like_device(w, {(int64_t)K, (int64_t)depth}, at::kChar);
-        rc = pack_weights(K, C, R, S, layout, cb, (const int8_t *)w.data_ptr(), (int8_t *)out.ptr(), st);
+        rc = lib.pack_weights(K, C, R, S, layout, cb, (const int8_t *)w.data_ptr(), (int8_t *)out.ptr(), st);
     }
     check(rc, "pack_weights");
     return out.result();
@@ -365,8 +385,8 @@ PyObject *im2col(PyObject *const *a, const char *name, bool nhwc, F &&call)
     return out.result();
 }
 
-NATIVE(im2col_int8, 8, { return im2col(a, "im2col_int8", false, im2col_int8); })
-NATIVE(im2col_nhwc_int8, 8, { return im2col(a, "im2col_nhwc_int8", true, im2col_nhwc_int8); })
+NATIVE(im2col_int8, 8, { return im2col(a, "im2col_int8", false, lib.im2col_int8); })
+NATIVE(im2col_nhwc_int8, 8, { return im2col(a, "im2col_nhwc_int8", true, lib.im2col_nhwc_int8); })
 
 // ---- between layers -----------------------------------------------------------------------------------------
 // (x, out, stream)
@@ -381,7 +401,7 @@ NATIVE(unpack_nhwc_int32, 3, {
     {
         NoGil unlocked;
         if (!out.given) out.made = empty_like_device(x, {N, P, Q, K}, at::kInt);
-        rc = unpack_nhwc_int32((int)N, (int)K, (int)P, (int)Q, (const int32_t *)x.data_ptr(), (int32_t *)out.ptr(), st);
+        rc = lib.unpack_nhwc_int32((int)N, (int)K, (int)P, (int)Q, (const int32_t *)x.data_ptr(), (int32_t *)out.ptr(), st);
     }
     check(rc, "unpack_nhwc_int32");
     return out.result();
@@ -398,7 +418,7 @@ NATIVE(requant_int8, 5, {
     {
         NoGil unlocked;
         if (!out.given) out.made = empty_like_device(x, x.sizes(), at::kChar);
-        rc = requant_int8(x.numel(), (const int32_t *)x.data_ptr(), (int8_t *)out.ptr(), shift, relu, st);
+        rc = lib.requant_int8(x.numel(), (const int32_t *)x.data_ptr(), (int8_t *)out.ptr(), shift, relu, st);
     }
     check(rc, "requant_int8");
     return out.result();
@@ -421,7 +441,7 @@ NATIVE(requant_pack_layout, 7, {
             const int64_t shape[5] = {N, (K + cb - 1) / cb, P + 2LL * pad, Q + 2LL * pad, cb};
             out.made = empty_like_device(x, shape, at::kChar);
         }
-        rc = requant_pack_layout((int)N, (int)K, (int)P, (int)Q, cb, pad, shift, relu, (const int32_t *)x.data_ptr(), (int8_t *)out.ptr(), st);
+        rc = lib.requant_pack_layout((int)N, (int)K, (int)P, (int)Q, cb, pad, shift, relu, (const int32_t *)x.data_ptr(), (int8_t *)out.ptr(), st);
     }
     check(rc, "requant_pack_layout");
     return out.result();
@@ -456,11 +476,11 @@ PyObject *dilated(PyObject *const *a, bool direct)
         NoGil unlocked;
         if (!out.given) out.made = empty_like_device(x, {d.N, d.K, P, Q}, at::kInt);
         if (!ws.defined())
-            ws = aligned_workspace(x, direct ? conv2d_int8_dilated_direct_workspace_bytes(&d, dil, cb)
-                                             : conv2d_int8_dilated_workspace_bytes(&d, dil, layout, cb));
-        rc = direct ? conv2d_int8_dilated_direct(&d, dil, cb, (const int8_t *)x.data_ptr(), (const int8_t *)w.data_ptr(), (int32_t *)out.ptr(),
+            ws = aligned_workspace(x, direct ? lib.conv2d_int8_dilated_direct_workspace_bytes(&d, dil, cb)
+                                             : lib.conv2d_int8_dilated_workspace_bytes(&d, dil, layout, cb));
+        rc = direct ? lib.conv2d_int8_dilated_direct(&d, dil, cb, (const int8_t *)x.data_ptr(), (const int8_t *)w.data_ptr(), (int32_t *)out.ptr(),
                                                  ws.data_ptr(), ws.numel(), st)
-                    : conv2d_int8_dilated(&d, dil, layout, cb, (const int8_t *)x.data_ptr(), (const int8_t *)w.data_ptr(), (int32_t *)out.ptr(),
+                    : lib.conv2d_int8_dilated(&d, dil, layout, cb, (const int8_t *)x.data_ptr(), (const int8_t *)w.data_ptr(), (int32_t *)out.ptr(),
                                           ws.data_ptr(), ws.numel(), st);
     }
     check(rc, direct ? "conv2d_int8_dilated_direct" : "conv2d_int8_dilated");
@@ -486,7 +506,7 @@ NATIVE(gemm_int8_nt, 4, {
     {
         NoGil unlocked;
         if (!out.given) out.made = empty_like_device(A, {A.size(0), B.size(0)}, at::kInt);
-        rc = gemm_int8_nt((int)A.size(0), (int)B.size(0), (int)A.size(1), (const int8_t *)A.data_ptr(), (const int8_t *)B.data_ptr(),
+        rc = lib.gemm_int8_nt((int)A.size(0), (int)B.size(0), (int)A.size(1), (const int8_t *)A.data_ptr(), (const int8_t *)B.data_ptr(),
                           (int32_t *)out.ptr(), st);
     }
     check(rc, "gemm_int8_nt");
@@ -501,13 +521,34 @@ PyObject *set_error_class(PyObject *, PyObject *cls)
     Py_RETURN_NONE;
 }
 
+// The handle of the loaded library (an integer, as ctypes has it).
+PyObject *set_library(PyObject *, PyObject *handle)
+{
+    void *const h = PyLong_AsVoidPtr(handle);
+    if (!h) {
+        if (!PyErr_Occurred()) PyErr_SetString(PyExc_ValueError, "a library handle is not null");
+        return nullptr;
+    }
+    Library found;
+#define CALL(name)                                                                        \
+    if (!(found.name = reinterpret_cast<decltype(&::name)>(dlsym(h, #name)))) {          \
+        PyErr_SetString(PyExc_RuntimeError, "the loaded library has no symbol " #name);    \
+        return nullptr;                                                                    \
+    }
+    LIBRARY_CALLS(CALL)
+#undef CALL
+    lib = found;
+    g_loaded = true;
+    Py_RETURN_NONE;
+}
+
 #define ENTRY(name) {#name, (PyCFunction)(void (*)(void))py_##name, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
     ENTRY(conv2d_int8), ENTRY(conv2d_int8_static), ENTRY(conv2d_int8_nhwc), ENTRY(conv2d_int8_ex), ENTRY(conv2d_int8_packed),
     ENTRY(conv2d_int8_packed_nhwc), ENTRY(conv2d_int8_packed_requant), ENTRY(pack_layout), ENTRY(pack_layout_nhwc), ENTRY(pack_weights),
     ENTRY(im2col_int8), ENTRY(im2col_nhwc_int8), ENTRY(unpack_nhwc_int32), ENTRY(requant_int8), ENTRY(requant_pack_layout),
     ENTRY(conv2d_int8_dilated), ENTRY(conv2d_int8_dilated_direct), ENTRY(gemm_int8_nt),
-    {"set_error_class", set_error_class, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+    {"set_error_class", set_error_class, METH_O, nullptr}, {"set_library", set_library, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

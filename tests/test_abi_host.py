@@ -445,3 +445,26 @@ def test_stored_form_validates_as_the_explicit_one(lib):
     need = lib.conv2d_int8_workspace_bytes((1, 20, 9, 9, 8, 3, 3, 1, 1), 1, 16)
     assert raw.conv2d_int8_stored(ctypes.byref(d), 1, 16, p, p, 0, p, p, need - 1, None) == lib.ERR_WORKSPACE
     assert raw.conv2d_int8_stored(ctypes.byref(d), 1, 16, p, p, 0, p, ctypes.c_void_p(264), need, None) == lib.ERR_INVALID_ARG
+
+
+def test_tensor_calls_go_to_the_loaded_library(lib, tmp_path):
+    """load(path) decides which library every call goes to, the native module's among them: no other build is even mapped."""
+    import shutil, subprocess, sys
+    other = tmp_path / "libother.so"
+    shutil.copy(lib._build.LIB, other)
+    code = f"""
+import sys; sys.path.insert(0, {ROOT!r})
+import torch
+from paper_2104_04731_amd import binding as b
+b.load({str(other)!r})
+class S: cuda_stream = 0
+t = torch.zeros(64, dtype=torch.int32)
+try:
+    b.conv2d_int8_ex((1, 16384, 8, 8, 1, 3, 3, 1, 1), b.LAYOUT_PACKED, 16, t, t, t, None, stream=S())
+except b.ConvError as e:
+    print("status", e.status)
+maps = open("/proc/self/maps").read()
+print({str(other)!r} in maps, {lib._build.LIB!r} in maps)
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
+    assert r.stdout.split("\n")[:2] == [f"status {lib.ERR_OVERFLOW_RISK}", "True False"], r.stdout + r.stderr
