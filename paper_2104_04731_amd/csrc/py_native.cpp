@@ -76,6 +76,24 @@ int as_int(PyObject *o)
     return v;
 }
 
+// int(o): for the arguments that the binding has always passed through int() (whole-number floats among them).
+int as_int_cast(PyObject *o)
+{
+    if (PyLong_CheckExact(o)) return (int)PyLong_AsUnsignedLongMask(o);
+    PyObject *i = PyObject_CallFunctionObjArgs((PyObject *)&PyLong_Type, o, nullptr);
+    if (!i) throw PyFail{};
+    const int v = (int)PyLong_AsUnsignedLongMask(i);
+    Py_DECREF(i);
+    return v;
+}
+
+// int(o) as a flag: None and the like are refused
+bool as_flag(PyObject *o)
+{
+    if (PyBool_Check(o)) return o == Py_True;
+    return as_int_cast(o) != 0;
+}
+
 bool as_bool(PyObject *o)
 {
     const int v = PyObject_IsTrue(o);
@@ -241,7 +259,7 @@ NATIVE(conv2d_int8_ex, 9, {
     const int layout = as_int(a[1]), cb = as_int(a[2]);
     const at::Tensor &x = tensor(a[3], "input"), &w = tensor(a[4], "weights"), &o = tensor(a[5], "output");
     const at::Tensor *ws = a[6] == Py_None ? nullptr : &tensor(a[6], "workspace");
-    const int packed = as_bool(a[7]);
+    const int packed = as_flag(a[7]);
     void *st = as_stream(a[8]);
     int rc;
     {
@@ -278,11 +296,13 @@ NATIVE(conv2d_int8_packed_nhwc, 9, { return gemm_stage(a, "conv2d_int8_packed_nh
 // (dims, layout, cb, x_packed, w_packed, out_cb, out_pad, shift, relu, out, stream)
 NATIVE(conv2d_int8_packed_requant, 11, {
     const conv_desc_t d = as_desc(a[0]);
-    const int layout = as_int(a[1]), cb = as_int(a[2]), out_cb = as_int(a[5]), out_pad = as_int(a[6]), shift = as_int(a[7]);
+    const int layout = as_int_cast(a[1]), cb = as_int_cast(a[2]), shift = as_int_cast(a[7]);
     const at::Tensor &x = tensor(a[3], "input"), &w = tensor(a[4], "weights");
     const int relu = as_bool(a[8]);
     Out out(a[9]);
     if (out.given) tensor(a[9], "output");
+    // (a result to be made has its shape from these two: integers only)
+    const int out_cb = out.given ? as_int_cast(a[5]) : as_int(a[5]), out_pad = out.given ? as_int_cast(a[6]) : as_int(a[6]);
     void *st = as_stream(a[10]);
     int64_t P = 0, Q = 0;
     if (!out.given) {
@@ -410,7 +430,7 @@ NATIVE(unpack_nhwc_int32, 3, {
 // (x, shift, relu, out, stream)
 NATIVE(requant_int8, 5, {
     const at::Tensor &x = require(a[0], at::kInt, "accumulator tensor");
-    const int shift = as_int(a[1]), relu = as_bool(a[2]);
+    const int shift = as_int(a[1]), relu = as_flag(a[2]);
     Out out(a[3]);
     if (out.given) tensor(a[3], "output");
     void *st = as_stream(a[4]);
@@ -428,7 +448,7 @@ NATIVE(requant_int8, 5, {
 NATIVE(requant_pack_layout, 7, {
     const at::Tensor &x = require(a[0], at::kInt, "accumulator tensor");
     require_dims(x, 4, "accumulator tensor");
-    const int cb = as_int(a[1]), pad = as_int(a[2]), shift = as_int(a[3]), relu = as_bool(a[4]);
+    const int cb = as_int(a[1]), pad = as_int(a[2]), shift = as_int(a[3]), relu = as_flag(a[4]);
     const int64_t N = x.size(0), K = x.size(1), P = x.size(2), Q = x.size(3);
     Out out(a[5]);
     if (out.given) tensor(a[5], "output");
@@ -458,10 +478,11 @@ at::Tensor aligned_workspace(const at::Tensor &on, size_t need)
 PyObject *dilated(PyObject *const *a, bool direct)
 {
     const conv_desc_t d = as_desc(a[0]);
-    const int dil = as_int(a[1]), layout = as_int(a[4]), cb = as_int(a[5]);
+    const int layout = as_int_cast(a[4]), cb = as_int_cast(a[5]);
     const at::Tensor &x = require(a[2], at::kChar, "input"), &w = require(a[3], at::kChar, "weights");
     Out out(a[6]);
     if (out.given) tensor(a[6], "output");
+    const int dil = out.given ? as_int_cast(a[1]) : as_int(a[1]);   // (a result to be made has its shape from it: integers only)
     at::Tensor ws;
     if (a[7] != Py_None) ws = tensor(a[7], "workspace");
     void *st = as_stream(a[8]);

@@ -468,3 +468,44 @@ print({str(other)!r} in maps, {lib._build.LIB!r} in maps)
 """
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120)
     assert r.stdout.split("\n")[:2] == [f"status {lib.ERR_OVERFLOW_RISK}", "True False"], r.stdout + r.stderr
+
+
+def test_arguments_that_pass_through_int(lib):
+    """The calls whose block, layout, dilation and shift went through int() take whole-number floats and integer texts; the
+    other integer arguments, and what a new result's shape is made of, stay integers.  (A bad descriptor ends each call
+    before anything touches a device; a refused argument ends it before that.)"""
+    import torch
+
+    class Stream:
+        cuda_stream = 0
+    st = Stream()
+    t = torch.zeros(64, dtype=torch.int8)
+    deep = (1, 16384, 8, 8, 1, 3, 3, 1, 1)
+    requant = lambda layout=1, cb=16, ocb=16, opad=0, shift=3, relu=True, out=t: lib.conv2d_int8_packed_requant(
+        deep, layout, cb, t, t, ocb, opad, shift, relu, out=out, stream=st)
+    for kw in ({}, {"cb": 16.0}, {"ocb": 16.0}, {"opad": 0.0}, {"shift": 3.0}, {"shift": "3"}, {"layout": 1.0}, {"cb": np.int64(16)}, {"relu": None}):
+        with pytest.raises(lib.ConvError) as e:
+            requant(**kw)
+        assert e.value.status == lib.ERR_OVERFLOW_RISK, kw
+    for kw in ({"cb": "x"}, {"ocb": 16.0, "out": None}, {"opad": 0.0, "out": None}, {"shift": None}):
+        with pytest.raises((TypeError, ValueError)):
+            requant(**kw)
+    ex = lambda layout=1, cb=16, packed=False: lib.conv2d_int8_ex(deep, layout, cb, t, t, t, None, packed, stream=st)
+    with pytest.raises(lib.ConvError):
+        ex(packed=1)
+    for kw in ({"cb": 16.0}, {"layout": 1.0}, {"packed": None}):
+        with pytest.raises(TypeError):
+            ex(**kw)
+
+
+@pytest.mark.gpu
+def test_dilation_given_as_a_float(lib):
+    import torch
+    x = torch.ones((1, 16, 9, 9), dtype=torch.int8, device="cuda:0")
+    w = torch.ones((8, 16, 3, 3), dtype=torch.int8, device="cuda:0")
+    dims = (1, 16, 9, 9, 8, 3, 3, 1, 2)
+    for call in (lib.conv2d_int8_dilated, lib.conv2d_int8_dilated_direct):
+        want = call(dims, 2, x, w)
+        assert torch.equal(call(dims, 2.0, x, w, out=torch.zeros_like(want), cb=0.0), want)
+        with pytest.raises(TypeError):
+            call(dims, 2.0, x, w)
