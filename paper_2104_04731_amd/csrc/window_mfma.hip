@@ -74,7 +74,9 @@ __device__ __forceinline__ unsigned load_u32(const void *p)  // any alignment
     return x;
 }
 
-template <int NKK, int NKB, bool ACT, bool NHWC, bool MULTI>  // ACT: the activation epilogue, a kernel of its own; NHWC: the source
+// ACT: the activation epilogue, a kernel of its own; NHWC: the source; MULTI: tiles of several row groups; STREAM: 16-byte
+// stores of the NKPQ result past the caches (of two stores under a run-time flag the compiler makes one, without the hint)
+template <int NKK, int NKB, bool ACT, bool NHWC, bool MULTI, bool STREAM>
 // (four workgroups per compute unit asked for, i.e. up to 128 registers: the deep instantiations use 86 -- five
 // fit -- and under a bound of 85 the compiler spilled their weight loads one by one, a wait behind each)
 __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
@@ -381,7 +383,7 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
                 }
             return;
         }
-        if (a.wide_out) {
+        if (STREAM || a.wide_out) {
             // Q a multiple of 4 and `out` 16-byte aligned: each wave turns its 32x32 block around in LDS
             // (rows of 36 dwords) so that a lane stores four consecutive pixels of one channel -- 16-byte
             // stores, eight 128-byte runs per instruction instead of two
@@ -400,8 +402,7 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
                     const v4i t = *reinterpret_cast<const v4i *>(T + (tr + 8 * j) * 36 + 4 * tg);
                     if (pp < aP && qq < aQ && k0 + kb * 32 + tr + 8 * j < aK) {
                         v4i *const to = reinterpret_cast<v4i *>(dst + (size_t)(8 * j) * PQ);
-                        // (asm: of the two stores the compiler makes one, without the hint)
-                        if (a.stream_out) asm volatile("global_store_dwordx4 %0, %1, off nt" : : "v"(to), "v"(t) : "memory");
+                        if constexpr (STREAM) __builtin_nontemporal_store(t, to);
                         else *to = t;
                     }
                 }
@@ -522,7 +523,7 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     const long long pitch = (((long long)(QT - 1) * stride_w + S4 + 3) + 3) / 4 * 4;
     // whole 64-byte sectors per 16 pixels, and more than the caches keep: stored past them (300 images 3 x 224 x 224, 7 x 7 / 2
     // -> 64, 963 MB: 294 -> 180 us; at 206 MB 42 -> 49, and partial sectors come out up to 2.5 times slower that way)
-    w.stream_out = g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && 4.0 * g.N * g.K * g.P * g.Q > STREAM_BYTES;
+    w.stream_out = !g.nhwc_in && !g.out_nhwc && !g.act.out && g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && 4.0 * g.N * g.K * g.P * g.Q > STREAM_BYTES;
     w.G = window_groups(g, w.PT, QT, C * pitch, depth, w.stream_out);
     const long long RW = (long long)(w.PT * w.G - 1) * g.stride + g.R;
     if (RW > WINDOW_LIMIT || pitch > WINDOW_LIMIT || C * RW * pitch > WINDOW_LIMIT) return false;
@@ -561,11 +562,11 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
 
 bool window_fits(const WindowProblem &g) { return window_plan(g, nullptr); }
 
-template <int NKK, bool ACT, bool NHWC, bool MULTI>
+template <int NKK, bool ACT, bool NHWC, bool MULTI, bool STREAM = false>
 static hipError_t launch_window_kb(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (a.K > 32) return launch((conv_window_kernel<NKK, 2, ACT, NHWC, MULTI>), grid, dim3(256), lds, st, a);
-    return launch((conv_window_kernel<NKK, 1, ACT, NHWC, MULTI>), grid, dim3(256), lds, st, a);
+    if (a.K > 32) return launch((conv_window_kernel<NKK, 2, ACT, NHWC, MULTI, STREAM>), grid, dim3(256), lds, st, a);
+    return launch((conv_window_kernel<NKK, 1, ACT, NHWC, MULTI, STREAM>), grid, dim3(256), lds, st, a);
 }
 template <int NKK>
 static hipError_t launch_window_nkk(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
@@ -575,7 +576,10 @@ static hipError_t launch_window_nkk(const WindowArgs &a, dim3 grid, size_t lds, 
         return launch_window_kb<NKK, false, true, false>(a, grid, lds, st);
     }
     if (a.act.out) return launch_window_kb<NKK, true, false, false>(a, grid, lds, st);
-    if (a.G > 1) return launch_window_kb<NKK, false, false, true>(a, grid, lds, st);
+    if (a.G > 1)
+        return a.stream_out ? launch_window_kb<NKK, false, false, true, true>(a, grid, lds, st)
+                            : launch_window_kb<NKK, false, false, true>(a, grid, lds, st);
+    if (a.stream_out) return launch_window_kb<NKK, false, false, false, true>(a, grid, lds, st);
     return launch_window_kb<NKK, false, false, false>(a, grid, lds, st);
 }
 
