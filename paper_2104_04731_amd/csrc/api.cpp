@@ -35,7 +35,7 @@ WindowProblem window_problem(const conv_desc_t *d, const Plan &pl, const int8_t 
                              int32_t *out, int wt_rewritten)
 {
     return WindowProblem{x, w, out, d->N, d->C, d->H, d->W, d->K, pl.P, pl.Q, d->R, d->S, d->stride, d->pad,
-                         wt_rewritten, ActOut{}, 0, 0};
+                         wt_rewritten, ActOut{}, 0};
 }
 
 int run_implicit(const Plan &pl, const WindowProblem &g, hipStream_t st)
@@ -341,7 +341,7 @@ struct Route {
 // A convolution with its activations in the network's own layout (NCHW, or NHWC).  pl: the plan whose output extents
 // apply (a dilated layer's own, if dil > 1); weights in blocks of cb with rows of `depth` bytes, or raw.
 ResidentProblem resident_problem(const conv_desc_t *d, const Plan &pl, int cb, int depth, bool raw, bool nhwc, int dil, const int8_t *in,
-                                 const int8_t *wt, int32_t *out, bool out_nhwc)
+                                 const int8_t *wt, int32_t *out)
 {
     ResidentProblem r{};
     r.g = gemm_problem(d, pl, nullptr, wt, out);
@@ -350,12 +350,11 @@ ResidentProblem resident_problem(const conv_desc_t *d, const Plan &pl, int cb, i
     r.g.Cb = (d->C + cb - 1) / cb;
     r.g.depth = depth;
     r.g.dil = dil;
-    r.g.out_nhwc = out_nhwc;
+    r.g.out_nhwc = nhwc;
     r.src = in;
     r.N = d->N, r.C = d->C, r.H = d->H, r.W = d->W, r.pad = d->pad;
     r.pixel_major = nhwc;
     r.pixel_bytes = d->C;
-    r.block_bytes = raw ? (d->C + 15) / 16 * 16 : cb;   // a pixel's channels follow each other whatever the weights' block
     r.img_bytes = (long long)d->C * d->H * d->W;
     r.raw_weights = raw;
     return r;
@@ -368,17 +367,16 @@ struct RouteKey {
 
 // Which of them runs this call.  two_us: the estimate of the route there is without the resident kernel.
 template <typename TwoStage>
-Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool nhwc, int dil, const int8_t *wt, int32_t *out, bool out_nhwc,
-                 int tag, TwoStage &&two_us)
+Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool nhwc, int dil, const int8_t *wt, int32_t *out, int tag, TwoStage &&two_us)
 {
     static thread_local PlanTable<RouteKey, Route, 64> routes;
-    const RouteKey key{*d, {pl.layout, pl.cb, tag, (int)wt_is_packed, (int)nhwc * 2 + (int)out_nhwc, dil, (int)aligned16(wt), (int)aligned16(out)}};
+    const RouteKey key{*d, {pl.layout, pl.cb, tag, (int)wt_is_packed, (int)nhwc, dil, (int)aligned16(wt), (int)aligned16(out)}};
     const Route *kept = routes.get(key, [&](Route *n) {
         double best = two_us();
         *n = Route{TWO_STAGE, {}, 0, 0};
         auto consider = [&](int how, int cb, int depth, bool raw, double extra) {
             ResidentChoice c;
-            const ResidentProblem r = resident_problem(d, pl, cb, depth, raw, nhwc, dil, nullptr, nullptr, out, out_nhwc);
+            const ResidentProblem r = resident_problem(d, pl, cb, depth, raw, nhwc, dil, nullptr, nullptr, out);
             if (!resident_pick(r, &c)) return;
             // records of 128 channels and more leave one workgroup per compute unit; over many rounds the estimate, which
             // was fitted to small and large layers alike, comes out 15 % low then (and 5 % in any grid from 200 channels on,
@@ -394,7 +392,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             if (pl.layout == CONV_LAYOUT_PACKED || pl.layout == CONV_LAYOUT_PAD_ONLY) {
                 consider(DIRECT_AS_IS, pl.cb, pl.depth, false, 0);
                 double us;
-                if (!nhwc && dil == 1 && band_direct_us(resident_problem(d, pl, pl.cb, pl.depth, false, false, 1, nullptr, nullptr, out, out_nhwc), &us) && us < best)
+                if (!nhwc && dil == 1 && band_direct_us(resident_problem(d, pl, pl.cb, pl.depth, false, false, 1, nullptr, nullptr, out), &us) && us < best)
                     *n = Route{DIRECT_BAND, {}, pl.cb, pl.depth};
             }
             return true;
@@ -416,14 +414,14 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
 
 // Runs a DIRECT_* route; ws: device memory for the rewritten weights (DIRECT_REWRITE), at least K * depth bytes.
 int run_direct(const Route &rt, const conv_desc_t *d, const Plan &pl, bool nhwc, int dil, const int8_t *in, const int8_t *wt, int32_t *out,
-               bool out_nhwc, void *ws, hipStream_t st)
+               void *ws, hipStream_t st)
 {
     if (rt.how == DIRECT_REWRITE) {
         if (launch_pack_weights_blocked(d->K, d->C, d->R, d->S, rt.cb, rt.depth, wt, static_cast<int8_t *>(ws), st) != hipSuccess)
             return CONV_ERR_DEVICE;
         wt = static_cast<const int8_t *>(ws);
     }
-    const ResidentProblem r = resident_problem(d, pl, rt.cb, rt.depth, rt.how == DIRECT_RAW, nhwc, dil, in, wt, out, out_nhwc);
+    const ResidentProblem r = resident_problem(d, pl, rt.cb, rt.depth, rt.how == DIRECT_RAW, nhwc, dil, in, wt, out);
     return gemm_status(rt.how == DIRECT_BAND ? launch_band_direct(r, st) : launch_resident(r, rt.pick, st));
 }
 size_t direct_bytes(const Route &rt, const conv_desc_t *d) { return rt.how == DIRECT_REWRITE ? (size_t)d->K * rt.depth : 0; }
@@ -439,7 +437,7 @@ int one_shot_route(const conv_desc_t *d, int layout, int cb, const int8_t *in, c
         return CONV_OK;
     }
     const double in_bytes = (double)d->N * d->C * d->H * d->W;
-    *rt = pick_route(d, *pl, false, false, 1, wt, out, false, 4 + layout, [&] {
+    *rt = pick_route(d, *pl, false, false, 1, wt, out, 4 + layout, [&] {
         if (layout == CONV_LAYOUT_IMAGE_PACK) {   // two more launches and the packed image written and read once more
             PackedProblem pp;
             Plan inner;
@@ -459,14 +457,14 @@ int one_shot_route(const conv_desc_t *d, int layout, int cb, const int8_t *in, c
 Route ex_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, const int8_t *wt, int32_t *out)
 {
     if (pl.layout == CONV_LAYOUT_IM2COL) return Route{TWO_STAGE, {}, 0, 0};
-    return pick_route(d, pl, wt_is_packed, false, 1, wt, out, false, 0, [&] {
+    return pick_route(d, pl, wt_is_packed, false, 1, wt, out, 0, [&] {
         return two_stage_us(gemm_problem(d, pl, nullptr, nullptr, out), (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, wt_is_packed);
     });
 }
 
 Route nhwc_route(const conv_desc_t *d, const Plan &pl, const int8_t *wt, int32_t *out)
 {
-    return pick_route(d, pl, false, true, 1, wt, out, true, 1, [&] {
+    return pick_route(d, pl, false, true, 1, wt, out, 1, [&] {
         GemmProblem g = gemm_problem(d, pl, nullptr, nullptr, out);
         g.out_nhwc = 1;
         // (a result that does not start on 16 bytes goes through a staging tensor and one more pass)
@@ -476,7 +474,7 @@ Route nhwc_route(const conv_desc_t *d, const Plan &pl, const int8_t *wt, int32_t
 
 Route dilated_direct_route(const conv_desc_t *d, int dilation, const Plan &pl, const int8_t *wt, int32_t *out)
 {
-    return pick_route(d, pl, false, false, dilation, wt, out, false, 2, [&] {
+    return pick_route(d, pl, false, false, dilation, wt, out, 2, [&] {
         GemmProblem g = gemm_problem(d, pl, nullptr, nullptr, out);
         g.dil = dilation;
         return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false);
@@ -486,7 +484,7 @@ Route dilated_direct_route(const conv_desc_t *d, int dilation, const Plan &pl, c
 // (dp, inner: the dense problem on the sub-images; direct: the plan of the image as it is)
 Route dilated_route(const conv_desc_t *d, int dilation, const DilatedProblem &dp, const Plan &inner, const Plan &direct, const int8_t *wt, int32_t *out)
 {
-    return pick_route(d, direct, false, false, dilation, wt, out, false, 3, [&] {
+    return pick_route(d, direct, false, false, dilation, wt, out, 3, [&] {
         const double pack = 2.5 + 0.25e-6 * ((double)d->N * d->C * d->H * d->W + (double)dp.x2_bytes) + SECOND_LAUNCH_US;
         return pack + two_stage_us(gemm_problem(&dp.d2, inner, nullptr, nullptr, nullptr), (double)dp.x2_bytes + (double)inner.x_bytes, (double)inner.w_bytes, false);
     });
@@ -497,7 +495,7 @@ bool nhwc_window(const conv_desc_t *d, const Plan &pl, const int8_t *in, const i
 {
     int layout = CONV_LAYOUT_AUTO, cb = 0;
     if (resolve_layout(d, &layout, &cb) != CONV_OK || layout != CONV_LAYOUT_IMPLICIT || pointwise_shape(d->C, d->R, d->S)) return false;
-    *wp = WindowProblem{in, wt, out, d->N, d->C, d->H, d->W, d->K, pl.P, pl.Q, d->R, d->S, d->stride, d->pad, 0, ActOut{}, 1, 1};
+    *wp = WindowProblem{in, wt, out, d->N, d->C, d->H, d->W, d->K, pl.P, pl.Q, d->R, d->S, d->stride, d->pad, 0, ActOut{}, 1};
     return window_fits(*wp);
 }
 bool nhwc_matrix(const conv_desc_t *d, const int8_t *in, const int8_t *wt, const int32_t *out)
@@ -872,7 +870,7 @@ int conv2d_int8_dilated(const conv_desc_t *desc, int dilation, int layout, int c
         // the library's choice may also be the kernel that reads its taps `dilation` pixels apart from the image as it is
         const Route rt = dilated_route(desc, dilation, dp, pl, direct, wt, out);
         if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes)
-            return run_direct(rt, desc, direct, false, dilation, in, wt, out, false, workspace, (hipStream_t)stream);
+            return run_direct(rt, desc, direct, false, dilation, in, wt, out, workspace, (hipStream_t)stream);
     }
     int8_t *x2 = static_cast<int8_t *>(workspace);
     void *ws = inner ? static_cast<void *>(x2 + xb + ob) : nullptr;
@@ -924,7 +922,7 @@ int conv2d_int8_dilated_direct(const conv_desc_t *desc, int dilation, int cb, co
     if (workspace_bytes < xb + align_up(pl.w_bytes, WS_ALIGN)) return CONV_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     const Route rt = dilated_direct_route(desc, dilation, pl, wt, out);
-    if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, dilation, in, wt, out, false, workspace, st);
+    if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, dilation, in, wt, out, workspace, st);
     int8_t *xq = static_cast<int8_t *>(workspace), *wq = xq + xb;
     const hipError_t e = launch_rewrite_fused(false, desc->N, desc->C, desc->H, desc->W, desc->K, desc->R, desc->S,
                                               desc->stride, desc->pad, pl.P, pl.Q, pl.cb, pl.depth, in, xq, wt, wq, st);
@@ -1117,7 +1115,7 @@ static int resident_forced(const conv_desc_t *desc, int dilation, int nhwc, int 
     Plan pl;
     const int rc = direct_dilated_plan(desc, dilation, wt_cb ? wt_cb : 16, &pl);
     if (rc != CONV_OK) return rc;
-    *r = resident_problem(desc, pl, wt_cb ? pl.cb : round_up_i(desc->C, 16), pl.depth, wt_cb == 0, nhwc != 0, dilation, in, wt, out, nhwc != 0);
+    *r = resident_problem(desc, pl, wt_cb ? pl.cb : round_up_i(desc->C, 16), pl.depth, wt_cb == 0, nhwc != 0, dilation, in, wt, out);
     return resident_applies(*r, tile, pixels) ? CONV_OK : CONV_ERR_UNSUPPORTED;
 }
 
@@ -1223,7 +1221,7 @@ static int run_explicit(const conv_desc_t *desc, int layout, int cb, const int8_
     if (workspace_bytes < need) return CONV_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     const Route rt = stored ? Route{TWO_STAGE, {}, 0, 0} : ex_route(desc, pl, wt_is_packed != 0, wt, out);
-    if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, 1, in, wt, out, false, workspace, st);
+    if (rt.how != TWO_STAGE && direct_bytes(rt, desc) <= workspace_bytes) return run_direct(rt, desc, pl, false, 1, in, wt, out, workspace, st);
     int8_t *xq = static_cast<int8_t *>(workspace);
     const int8_t *wq = wt;
     bool rewritten = false;
@@ -1298,7 +1296,7 @@ int conv2d_int8(int N, int C, int H, int W, int K, int R, int S, int stride, int
     rc = one_shot_route(&d, layout, cb, in, wt, out, &pl, &rt);
     if (rc != CONV_OK) return rc;
     if (rt.how != TWO_STAGE && direct_bytes(rt, &d) <= ws_bytes)
-        return run_direct(rt, &d, pl, false, 1, in, wt, out, false, ws, (hipStream_t)stream);
+        return run_direct(rt, &d, pl, false, 1, in, wt, out, ws, (hipStream_t)stream);
     return conv2d_int8_ex(&d, layout, cb, in, wt, 0, out, ws, ws_bytes, stream);
 }
 
@@ -1368,7 +1366,7 @@ int conv2d_int8_nhwc(int N, int C, int H, int W, int K, int R, int S, int stride
     const Route rt = nhwc_route(&d, pl, wt, out);
     rc = cached_workspace(need, st, &ws, &ws_bytes);
     if (rc != CONV_OK) return rc;
-    if (rt.how != TWO_STAGE && direct_bytes(rt, &d) <= ws_bytes) return run_direct(rt, &d, pl, true, 1, in, wt, out, true, ws, st);
+    if (rt.how != TWO_STAGE && direct_bytes(rt, &d) <= ws_bytes) return run_direct(rt, &d, pl, true, 1, in, wt, out, ws, st);
     int8_t *xq = static_cast<int8_t *>(ws), *wq = xq + xb;
     int32_t *nkpq = reinterpret_cast<int32_t *>(wq + wb);
     const hipError_t e = launch_rewrite_fused_nhwc(N, C, H, W, K, R, S, pad, pl.cb, pl.depth, in, xq, wt, wq, st);

@@ -207,7 +207,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
         lo0 = (y0 * a.W) & ~7;
         const int slots = max((y1 * a.W - lo0 + 7) & ~7, 0);
         const WindowRange range{n, lo0, slots, 8, slots, 0};
-        const WindowSource from{a.act, (long long)a.C * a.HW, a.src_bytes, a.C - 1, a.HW, a.C, 16, 16};
+        const WindowSource from{a.act, (long long)a.C * a.HW, a.src_bytes, a.C - 1, a.HW, a.C};
         const unsigned row_lo = (unsigned)(min(k0 + lrow, a.K - 1) * a.depth) + (unsigned)(lane_part & 63);
         const unsigned row_hi = (unsigned)(min(k0 + 16 + lrow, a.K - 1) * a.depth) + (unsigned)(lane_part & 63);
 #pragma unroll
@@ -381,7 +381,9 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     const int kleft = a.K - k0 - 4 * grp;   // output channels from this lane's first one to the last
     const bool k_whole = k0 + BAND_TK <= a.K;  // wave-uniform: no channel of the tile lies past the last
     constexpr int SLOTS = (2 * PB + BAND_WAVES - 1) / BAND_WAVES;
-    if (SROW > 1 && k_whole && a.out_nhwc && a.out_wide_k && a.aout.out == nullptr) {
+    // (the direct form writes the NKPQ result only)
+    const bool out_nhwc = !DIRECT && a.out_nhwc, activate = !DIRECT && a.aout.out != nullptr;
+    if (SROW > 1 && k_whole && out_nhwc && a.out_wide_k && !activate) {
         // The same for an NHWC result whose pixels take 16-byte pieces: a lane's four sums are channels k .. k+3 of
         // one pixel; 32-bit byte offsets against the image's base.
         v4i sums[SLOTS];
@@ -405,7 +407,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
         }
         return;
     }
-    if (SROW > 1 && k_whole && !(a.out_nhwc | (a.aout.out != nullptr))) {
+    if (SROW > 1 && k_whole && !(out_nhwc | activate)) {
         // The common case -- int32 NKPQ result, whole channel tile, shifted-fragment form -- on a path of its own:
         // every sum is read before the first store (one LDS round trip for the wave, not one per slot), no test of
         // the result's form inside the loop, and 32-bit byte offsets against four scalar plane bases (the host
@@ -460,7 +462,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
         }
         // A lane's four values are channels k .. k+3 of one pixel: one piece of an NHWC result, one dword of the
         // next layer's blocked input after the activation.  (Wave-uniform tests: one of the three forms runs.)
-        if (a.out_nhwc | (a.aout.out != nullptr)) {
+        if (out_nhwc | activate) {
             int pp, qq;
             if (SROW > 1) {
                 const int pr = bdiv_small(pb, a.mg_CTN);
@@ -471,7 +473,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
             }
             const int k = k0 + rb * 16 + 4 * grp;
             if (valid && k < a.K) {
-                if (a.aout.out) {
+                if (activate) {
                     act_store4(a.aout, n, pp, qq, k, a.K, sum[0], sum[1], sum[2], sum[3]);
                 } else {
                     int32_t *px = a.out + (((size_t)n * a.P + pp) * a.Q + qq) * a.K + k;
@@ -560,7 +562,7 @@ bool band_plan(const GemmProblem &g, BandPlan *bp, const ResidentProblem *r = nu
     long long lds = BAND_WAVES * wave_region + g.Cb * win_pieces * 1024;
     int pitch = 0;
     if (r) {
-        if (!tiled || r->raw_weights || r->pixel_major) return false;
+        if (!tiled || r->raw_weights || r->pixel_major || g.act_out || g.out_nhwc) return false;
         // 32-bit offsets inside an image; 8- and 16-byte loads clamped to the tensor
         if (r->img_bytes > 0x7FFFFFFFLL || (long long)r->H * r->W > (1LL << 28) || (long long)r->N * r->img_bytes < 64) return false;
         const int C16 = (r->C + 15) / 16 * 16;
@@ -801,7 +803,6 @@ hipError_t launch_band_direct(const ResidentProblem &r, hipStream_t st)
     bp.a.act = r.src;
     bp.a.wq = r.g.wq;
     bp.a.out = r.g.out;
-    bp.a.aout.out = r.g.act_out;
     constexpr bool DIRECT = true;
     C2I8_BAND_PBS(3, 1) C2I8_BAND_PBS(3, 2) C2I8_BAND_PBS(3, 3) C2I8_BAND_PBS(3, 4)
     return hipErrorInvalidValue;

@@ -76,8 +76,8 @@ struct ResidentProblem {
     GemmProblem g;
     const int8_t *src;
     int N, C, H, W, pad;
-    int pixel_major;     // a pixel's channels are contiguous (NHWC, or blocked): pixel_bytes apart, channel blocks block_bytes apart
-    int pixel_bytes, block_bytes;
+    int pixel_major;     // a pixel's channels are contiguous (NHWC), pixel_bytes apart
+    int pixel_bytes;
     long long img_bytes;
     int raw_weights;     // g.wq is KCRS as it came (3 x 3 only), not in depth order
 };
@@ -153,10 +153,9 @@ struct WindowProblem {
     int N, C, H, W, K, P, Q, R, S, stride, pad;
     int wt_rewritten;
     ActOut act;
-    // NHWC source: in is [N][H][W][C] and the depth order is (r, s, c) -- a kernel row's S*C bytes are one run
-    // of an image row -- with the KCRS weights brought into that order on their way into LDS; not with wt_rewritten
-    int nhwc_in;
-    int out_nhwc;       // out is [N][P][Q][K]
+    // NHWC: in is [N][H][W][C], out [N][P][Q][K] and the depth order is (r, s, c) -- a kernel row's S*C bytes are one run
+    // of an image row -- with the KCRS weights brought into that order on their way into LDS; not with wt_rewritten or act
+    int nhwc;
 };
 int window_depth(int C, int R, int S);          // 0 if the padded depth exceeds what the kernel unrolls
 bool window_fits(const WindowProblem &g);       // depth, image width and LDS window within the kernel's limits

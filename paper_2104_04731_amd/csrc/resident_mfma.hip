@@ -32,14 +32,13 @@ struct ResidentArgs {
     const int8_t *src, *wq;
     int32_t *out;                  // [N][K][P][Q], or [N][P][Q][K] (out_nhwc)
     int out_nhwc;
-    ActOut act;                    // activation epilogue (act.out != null): `out` is not written
     int K, M, PQ, Q;
     int C, C1, H, W, HW;           // C1 = C - 1
     int stride, pad, dil, R, S;
     int depth, steps;              // bytes per weight row, 64-byte steps
     int cb, nreal, C16;            // weights' channel block; 16-byte chunks of depth that hold weights; bytes of a record
     int pitch, full8;              // record pitch; slots of a whole image (its range rounded up to 8 pixels)
-    int pstride, bstride;          // pixel-major source: bytes from pixel to pixel, from channel block to channel block
+    int pstride;                   // pixel-major source: bytes from pixel to pixel
     long long img_bytes, src_bytes;
     int zero_off, win_off, tab_off;  // LDS byte offsets (the weight tile is at 0)
     int tiles_k, tiles_m, mper;    // mper: output pixels of a workgroup
@@ -77,20 +76,7 @@ __device__ __forceinline__ void res_store(const ResidentArgs &a, const v16i (&ac
     int K = a.K, PQ = a.PQ;
     asm volatile("" : "+s"(K), "+s"(PQ));
     const int half4 = 4 * (lane >> 5);
-    if (a.act.out != nullptr) {
-#pragma unroll
-        for (int f = 0; f < FM; ++f) {
-            const int m = mw + f * 32 + (lane & 31);
-            const int n = fast_div_any(m, PQ, a.mg_PQ), pq = m - n * PQ;
-            const int p = fast_div_any(pq, a.Q, a.mg_Q), q = pq - p * a.Q;
-            if (m < m1)
-#pragma unroll
-                for (int i = 0; i < FK; ++i)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g)
-                        act_store4(a.act, n, p, q, kw + i * 32 + 8 * g + half4, K, acc[i][f][4 * g], acc[i][f][4 * g + 1], acc[i][f][4 * g + 2], acc[i][f][4 * g + 3]);
-        }
-    } else if (a.out_nhwc) {
+    if (a.out_nhwc) {
         const bool wide = (K & 3) == 0 && (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
 #pragma unroll
         for (int f = 0; f < FM; ++f) {
@@ -153,22 +139,21 @@ __device__ __forceinline__ void res_store(const ResidentArgs &a, const v16i (&ac
     }
 }
 
-// TK: output channels of a workgroup, WK: waves side by side over them, NW: waves, FM: 32-pixel blocks a wave
+// TK: output channels of a workgroup, NW: waves (each multiplies all of the channels), FM: 32-pixel blocks a wave
 // multiplies at a time; SRC: ResSource; UNI: a 64-byte step of depth lies within one tap (and channel block);
 // RAW: the weights are KCRS (3 x 3), turned into depth order (tap, channel padded to 16) on their way into LDS.
 // The 64-channel tile of 8 waves keeps two output blocks' sums and the addresses of a whole tap in registers: at two of its
 // workgroups per compute unit it spilled, at one it does not, and its LDS rarely leaves room for two (64 images 56 x 56,
 // 64 -> 64, kept weights: 18.0 -> 17.4 us; 151 images 28 x 28, 128 -> 458: 116 -> 105).
-template <int TK, int WK, int NW, int FM, int SRC, bool UNI, bool RAW>
+template <int TK, int NW, int FM, int SRC, bool UNI, bool RAW>
 __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) conv_resident_kernel(const ResidentArgs a)
 {
-    constexpr int NT = NW * 64, WM = NW / WK, WTK = TK / WK, FK = WTK / 32;
+    constexpr int NT = NW * 64, FK = TK / 32;
     constexpr int STEP = TK * 64;   // LDS bytes of one 64-byte step of the weight tile
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) unsigned char *)smem);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wk = wave % WK, wm = wave / WK;
 
     // channel tiles fastest: the workgroups of one pixel range share its input behind one L2
     const int lid = xcd_contiguous(blockIdx.x, gridDim.x);
@@ -206,7 +191,7 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
     }
     // ---- window ---------------------------------------------------------------------------------------------------
     const WindowRange range{n0, lo0, len0, a.full8, slots, a.mg_full8};
-    const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride, a.bstride, a.cb};
+    const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride};
     if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
     else window_from_pixels<NT, 4>(from, range, a.u16, a.mg_u16, smem + a.win_off, a.pitch, tid);
     if constexpr (RAW) {
@@ -264,10 +249,10 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
     // ---- every wave on its own from here: blocks of FM x 32 pixels, all of the depth, straight to the result -------
     // (no barrier: the stores of one wave run beside the MFMAs of the others)
     const int rswz = (lane >> 2) & 3, half = lane >> 5;
-    const int a0 = (wk * WTK + (lane & 31)) * 64 + ((half ^ rswz) << 4), a1 = (wk * WTK + (lane & 31)) * 64 + (((2 + half) ^ rswz) << 4);
+    const int a0 = (lane & 31) * 64 + ((half ^ rswz) << 4), a1 = (lane & 31) * 64 + (((2 + half) ^ rswz) << 4);
     constexpr int NE = UNI ? 1 : 2;          // table entries of a step that a lane looks at
     constexpr int NQ = 2 * FK * FM, NI = 2 * (FK + FM);
-    for (int blk = wm; m0 + blk * FM * 32 < m1; blk += WM) {
+    for (int blk = wave; m0 + blk * FM * 32 < m1; blk += NW) {
         const int mw = m0 + blk * FM * 32;
         // the lane's pixels: their records (tap (0, 0), first chunk) and which taps are in the image
         int base[FM];
@@ -336,20 +321,20 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
                 }
             }
         }
-        res_store<FK, FM>(a, acc, k0 + wk * WTK, mw, m1, n0, lane);
+        res_store<FK, FM>(a, acc, k0, mw, m1, n0, lane);
     }
 }
 
-// TK, WK, NW, FM, and how many of its workgroups fit a compute unit by their registers
+// TK, NW, FM, and how many of its workgroups fit a compute unit by their registers
 #define C2I8_RES_LIST(X) \
-    X(64, 1, 8, 1, 1) \
-    X(64, 1, 4, 1, 3) \
-    X(32, 1, 4, 1, 5) \
-    X(32, 1, 4, 2, 3) \
-    X(32, 1, 8, 1, 2)
+    X(64, 8, 1, 1) \
+    X(64, 4, 1, 3) \
+    X(32, 4, 1, 5) \
+    X(32, 4, 2, 3) \
+    X(32, 8, 1, 2)
 
 struct ResTile {
-    int tk, wk, nw, fm;
+    int tk, nw, fm;
     int fit;   // workgroups whose registers fit a compute unit
 };
 constexpr ResTile kResTiles[] = {
@@ -359,21 +344,21 @@ constexpr ResTile kResTiles[] = {
 };
 constexpr int kNumResTiles = sizeof(kResTiles) / sizeof(kResTiles[0]);
 
-template <int TK, int WK, int NW, int FM>
+template <int TK, int NW, int FM>
 hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool raw, size_t lds, hipStream_t st)
 {
     void (*kern)(ResidentArgs);
     static bool raised[8];
     const int which = pixels * 4 + uni * 2 + raw;
     switch (which) {
-        case 0: kern = conv_resident_kernel<TK, WK, NW, FM, RES_NCHW, false, false>; break;
-        case 1: kern = conv_resident_kernel<TK, WK, NW, FM, RES_NCHW, false, true>; break;
-        case 2: kern = conv_resident_kernel<TK, WK, NW, FM, RES_NCHW, true, false>; break;
-        case 3: kern = conv_resident_kernel<TK, WK, NW, FM, RES_NCHW, true, true>; break;
-        case 4: kern = conv_resident_kernel<TK, WK, NW, FM, RES_PIXELS, false, false>; break;
-        case 5: kern = conv_resident_kernel<TK, WK, NW, FM, RES_PIXELS, false, true>; break;
-        case 6: kern = conv_resident_kernel<TK, WK, NW, FM, RES_PIXELS, true, false>; break;
-        default: kern = conv_resident_kernel<TK, WK, NW, FM, RES_PIXELS, true, true>; break;
+        case 0: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, false>; break;
+        case 1: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, true>; break;
+        case 2: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, false>; break;
+        case 3: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, true>; break;
+        case 4: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, false>; break;
+        case 5: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, true>; break;
+        case 6: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, false>; break;
+        default: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, true>; break;
     }
     if (lds > 64 * 1024 && !raised[which]) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -436,12 +421,11 @@ struct ResidentShape {
 bool resident_shape(const ResidentProblem &r, ResidentShape *o)
 {
     const GemmProblem &g = r.g;
-    if (g.mode != ACT_BLOCKED || g.R * g.S > 31 || g.il_d || g.Q <= 0 || g.PQ % g.Q || g.M <= 0) return false;
+    if (g.mode != ACT_BLOCKED || g.R * g.S > 31 || g.il_d || g.act_out || g.Q <= 0 || g.PQ % g.Q || g.M <= 0) return false;
     if (r.raw_weights ? g.R != 3 || g.S != 3 : g.cb < 16 || g.cb % 16) return false;
     // 32-bit offsets inside an image and of its pixels; 8- and 16-byte loads clamped to the tensor
     if (r.img_bytes > 0x7FFFFFFFLL || (long long)r.H * r.W > (1LL << 28) || (long long)r.N * r.img_bytes < 64) return false;
     if ((long long)g.Q * g.stride > (1LL << 28) || (long long)(g.PQ / g.Q) * g.stride > (1LL << 28)) return false;
-    if (g.act_out && (g.o_cb < 4 || (g.o_cb & (g.o_cb - 1)))) return false;
     o->C16 = (r.C + 15) / 16 * 16;
     o->pitch = (o->C16 / 16 | 1) * 16;
     o->cb = r.raw_weights ? o->C16 : g.cb;
@@ -464,11 +448,6 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     auto magic = [](long long v) { return v <= 1 ? 0u : magic_for(v); };
     a.out = g.out;
     a.out_nhwc = g.out_nhwc;
-    if (g.act_out) {
-        int lg = 0;
-        while ((1 << lg) < g.o_cb) ++lg;
-        a.act = ActOut{g.act_out, g.act_shift, g.act_relu, lg, g.o_pad, g.PQ / g.Q + 2 * g.o_pad, g.Q + 2 * g.o_pad, (g.K + g.o_cb - 1) / g.o_cb};
-    }
     a.K = g.K;
     a.M = g.M;
     a.PQ = g.PQ;
@@ -494,7 +473,6 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     a.nreal = sh.nreal;
     a.pitch = sh.pitch;
     a.pstride = r.pixel_bytes;
-    a.bstride = r.block_bytes;
     a.img_bytes = img;
     a.src_bytes = img * r.N;
     a.cq = a.C16 / 4;
@@ -556,19 +534,19 @@ double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile
     const double chain = (double)((blocks + d.nw - 1) / d.nw) * d.fm * (d.tk / 32) * 2 * sh.steps;
     const double units = (double)((slots / 8 * (sh.C16 / 4) + d.nw * 256 - 1) / (d.nw * 256));
     const double mfma = d.tk / 32 * d.fm * blocks * 2.0 * sh.steps / 4, out_byte = g.PQ % 16 == 0 ? 2.27e-5 : 3.06e-5;
-    double t = 3.28 + rounds * (1.0 + 0.0279 * chain + 0.585 * units) + ncu * (1.85e-3 * mfma + 5.68e-5 * slots * sh.C16 + out_byte * d.tk * mper * (g.act_out ? 1 : 4));
+    double t = 3.28 + rounds * (1.0 + 0.0279 * chain + 0.585 * units) + ncu * (1.85e-3 * mfma + 5.68e-5 * slots * sh.C16 + out_byte * d.tk * mper * 4);
     if (r.raw_weights) t += 0.297 * rounds * d.tk * (sh.C16 / 4) / (d.nw * 64) + 0.0239 * ncu * d.tk * (sh.C16 / 4) / 64;
     return t;
 }
 
 struct ResidentKey {
     GemmKey g;
-    int v[10];
+    int v[9];
 };
 ResidentKey resident_key(const ResidentProblem &r)
 {
     const int out64 = (reinterpret_cast<uintptr_t>(r.g.out) & 63) == 0;
-    return ResidentKey{gemm_key(r.g), {r.N, r.C, r.H, r.W, r.pad, r.pixel_major, r.pixel_bytes, r.block_bytes, r.raw_weights, out64}};
+    return ResidentKey{gemm_key(r.g), {r.N, r.C, r.H, r.W, r.pad, r.pixel_major, r.pixel_bytes, r.raw_weights, out64}};
 }
 
 }  // namespace
@@ -618,10 +596,9 @@ static hipError_t launch_plan(const ResidentProblem &r, const ResidentPlan &p, h
     a.src = r.src;
     a.wq = r.g.wq;
     a.out = r.g.out;
-    a.act.out = r.g.act_out;
     int index = 0;
-#define C2I8_CASE(tk, wk, nw, fm, fit) \
-    if (p.tile == index++) return launch_res_tile<tk, wk, nw, fm>(a, r.pixel_major, p.uni, r.raw_weights, p.lds, st);
+#define C2I8_CASE(tk, nw, fm, fit) \
+    if (p.tile == index++) return launch_res_tile<tk, nw, fm>(a, r.pixel_major, p.uni, r.raw_weights, p.lds, st);
     C2I8_RES_LIST(C2I8_CASE)
 #undef C2I8_CASE
     return hipErrorInvalidValue;

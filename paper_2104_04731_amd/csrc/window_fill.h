@@ -27,7 +27,7 @@ struct WindowSource {
     const int8_t *src;
     long long img_bytes, src_bytes;   // of an image, of the tensor
     int C1, HW;                       // last channel, pixels of an image
-    int pstride, bstride, cb;         // pixel-major: bytes from pixel to pixel, from channel block (of cb) to block
+    int pstride;                      // pixel-major: bytes from pixel to pixel
 };
 
 typedef unsigned long long u64_a1 __attribute__((aligned(1)));
@@ -112,7 +112,7 @@ __device__ __forceinline__ void window_from_nchw(const WindowSource &t, const Wi
     }
 }
 
-// Pixel-major source (NHWC, or a blocked image) -> records: 16-byte pieces, neighbouring lanes on neighbouring pieces.
+// Pixel-major source (NHWC) -> records: 16-byte pieces, neighbouring lanes on neighbouring pieces.
 // u16: pieces of a record (what lies past the last channel is the next pixel's: its weights are zero).
 template <int NT, int B>
 __device__ __forceinline__ void window_from_pixels(const WindowSource &t, const WindowRange &w, int u16, unsigned mg_u16, unsigned char *win, int pitch, int tid)
@@ -131,8 +131,7 @@ __device__ __forceinline__ void window_from_pixels(const WindowSource &t, const 
             const long long img = (long long)n * t.img_bytes;
             const long long left = t.src_bytes - 16 - img;
             const int last = left > 0x7FFFFFFFLL ? 0x7FFFFFFF : (int)left;
-            const int blk = (j * 16) / t.cb;
-            const int want = lin * t.pstride + blk * t.bstride + (j * 16 - blk * t.cb), at = min(want, last);
+            const int want = lin * t.pstride + j * 16, at = min(want, last);
             v4i x;
             __builtin_memcpy(&x, t.src + img + at, 16);
             v[b] = want != at ? shift_piece(x, at - want) : x;

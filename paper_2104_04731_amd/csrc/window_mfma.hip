@@ -45,8 +45,8 @@ struct WindowArgs {
     int C, H, W, K, P, Q, R, stride, pad;   // (NHWC source: C = 1, W in bytes; stride and pad are the vertical ones)
     int stride_w, pad_w;   // horizontal stride and padding in bytes of an image row
     int gC, gS, gRS;       // NHWC source: the real channel count, S and R*S of the KCRS weights
-    int nhwc;              // NHWC source
-    int out_nhwc, out_wide_k;  // result [N][P][Q][K]; K % 4 == 0 and out 16-byte aligned
+    int nhwc;              // NHWC source and result ([N][P][Q][K])
+    int out_wide_k;        // K % 4 == 0 and out 16-byte aligned
     int PT, qshift;        // output rows the waves cover at a time; tile columns QT = 32 << qshift, PT << qshift = 4
     int G;                 // how often they do: a tile has PT * G output rows
     int RW;                // window rows per channel: (PT*G-1)*stride + R
@@ -59,7 +59,6 @@ struct WindowArgs {
     int w_pitch;           // bytes per channel in LDS: depth + 16 (the 32 rows a wave reads start in different banks)
     int win_bytes, wl_bytes;  // LDS bytes of the window and of the weight rows (multiples of 16)
     int out_small;         // 4*K*P*Q < 2^32
-    int in_small;          // C*H*W < 2^31
     int wt16;              // the weights are rewritten rows of `depth` bytes at a 16-byte aligned address: copied in 16-byte pieces
     int rpp;               // window fill by columns (0: not): window rows per pass of 256 threads, 256 / (pitch/4)
     int wide_out;          // Q % 4 == 0 and out 16-byte aligned: 16-byte stores
@@ -74,7 +73,7 @@ __device__ __forceinline__ unsigned load_u32(const void *p)  // any alignment
     return x;
 }
 
-// ACT: the activation epilogue, a kernel of its own; NHWC: the source; MULTI: tiles of several row groups; STREAM: 16-byte
+// ACT: the activation epilogue, a kernel of its own; NHWC: source and result; MULTI: tiles of several row groups; STREAM: 16-byte
 // stores of the NKPQ result past the caches (of two stores under a run-time flag the compiler makes one, without the hint)
 template <int NKK, int NKB, bool ACT, bool NHWC, bool MULTI, bool STREAM>
 // (four workgroups per compute unit asked for, i.e. up to 128 registers: the deep instantiations use 86 -- five
@@ -342,14 +341,14 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
             }
             return;
         }
-        if (a.out_nhwc && a.out_wide_k) {
+        if (NHWC && a.out_wide_k) {
             // a lane's v%4 are channels k .. k+3 of its pixel: each wave lays its 32 pixels x KB channels out in LDS
             // as the result has them ([pixel][channel], rows of KB + 4 dwords) and stores 16-byte pieces with the
             // pieces of a pixel in consecutive lanes -- the channel runs of consecutive pixels follow each other in
             // the result, so a store instruction writes whole runs instead of 32-byte pairs
-            if (!MULTI) __syncthreads();  // every wave is done with the window and the weights
+            __syncthreads();  // every wave is done with the window and the weights
             constexpr int TPITCH = KB + 4, CPP = KB / 4;   // dwords per pixel row; 16-byte pieces per pixel
-            int *T = reinterpret_cast<int *>(smem + (MULTI ? a.turn_off : 0)) + wave * (32 * TPITCH);
+            int *T = reinterpret_cast<int *>(smem) + wave * (32 * TPITCH);
 #pragma unroll
             for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
@@ -368,7 +367,7 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
             }
             return;
         }
-        if (a.out_nhwc) {   // results that do not start on 16 bytes, or K % 4 != 0: one by one
+        if (NHWC) {   // results that do not start on 16 bytes, or K % 4 != 0: one by one
             const int p = pr, q = q0 + qw * 32 + l31;
             if (p >= aP || q >= aQ) return;
             int32_t *px = outn + ((size_t)p * aQ + q) * aK;
@@ -481,7 +480,7 @@ constexpr double STREAM_BYTES = 256e6;
 // the stores do not bypass the caches, else one.
 static int window_groups(const WindowProblem &g, int PT, int QT, long long row_bytes, int depth, bool stream_out)
 {
-    if (g.nhwc_in || g.out_nhwc || g.act.out) return 1;
+    if (g.nhwc || g.act.out) return 1;
     const long long cols = (long long)g.N * ((g.Q + QT - 1) / QT);
     auto fits = [&](int G, long long least) {
         const long long groups = (g.P + PT * G - 1) / (PT * G);
@@ -496,12 +495,12 @@ static int window_groups(const WindowProblem &g, int PT, int QT, long long row_b
 // Tile shape by output width, window geometry and the LDS it needs.
 static bool window_plan(const WindowProblem &g, WindowArgs *a)
 {
-    if (g.nhwc_in && (g.wt_rewritten || (long long)g.S * g.C > 4096 || (long long)g.W * g.C > 2147483647LL ||
+    if (g.nhwc && (g.wt_rewritten || g.act.out || (long long)g.S * g.C > 4096 || (long long)g.W * g.C > 2147483647LL ||
                       (long long)g.stride * g.C > 65536 || (long long)g.pad * g.C > 2147483647LL))
         return false;
     // an NHWC source is computed as one channel of W*C columns under a kernel row of S*C bytes
-    const int C = g.nhwc_in ? 1 : g.C, W = g.nhwc_in ? g.W * g.C : g.W, S = g.nhwc_in ? g.S * g.C : g.S;
-    const long long stride_w = g.nhwc_in ? (long long)g.stride * g.C : g.stride;
+    const int C = g.nhwc ? 1 : g.C, W = g.nhwc ? g.W * g.C : g.W, S = g.nhwc ? g.S * g.C : g.S;
+    const long long stride_w = g.nhwc ? (long long)g.stride * g.C : g.stride;
     const int depth = window_depth(C, g.R, S);
     if (depth == 0 || W < 4 || (long long)C * g.H * W > 0x7FFFFFFFLL) return false;  // (32-bit offsets inside an image)
     WindowArgs w{};
@@ -510,11 +509,10 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     w.out = g.out;
     w.C = C; w.H = g.H; w.W = W; w.K = g.K; w.P = g.P; w.Q = g.Q; w.R = g.R;
     w.stride = g.stride; w.pad = g.pad;
-    w.stride_w = (int)stride_w; w.pad_w = g.nhwc_in ? g.pad * g.C : g.pad;
+    w.stride_w = (int)stride_w; w.pad_w = g.nhwc ? g.pad * g.C : g.pad;
     w.gC = g.C; w.gS = g.S; w.gRS = g.R * g.S;
     w.m_gC = magic_for(g.C);
-    w.nhwc = g.nhwc_in;
-    w.out_nhwc = g.out_nhwc;
+    w.nhwc = g.nhwc;
     w.out_wide_k = g.K % 4 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 15) == 0;
     w.qshift = g.Q > 64 ? 2 : g.Q > 32 ? 1 : 0;
     w.PT = 4 >> w.qshift;
@@ -526,7 +524,7 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     // 300 MB to 1.6 GB 2 to 27 % less, level in six cases of forty, and 7 % more for a 3 x 3 / 2 -> 32 from 960 MB on.  At 205 MB
     // it gains on a result that is written once (56 -> 48), but one that is written again is still in the last-level cache and takes 37
     // with plain stores.  (Partial sectors come out up to 2.5 times slower that way.)
-    w.stream_out = !g.nhwc_in && !g.out_nhwc && !g.act.out && g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && 4.0 * g.N * g.K * g.P * g.Q > STREAM_BYTES;
+    w.stream_out = !g.nhwc && !g.act.out && g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && 4.0 * g.N * g.K * g.P * g.Q > STREAM_BYTES;
     w.G = window_groups(g, w.PT, QT, C * pitch, depth, w.stream_out);
     const long long RW = (long long)(w.PT * w.G - 1) * g.stride + g.R;
     if (RW > WINDOW_LIMIT || pitch > WINDOW_LIMIT || C * RW * pitch > WINDOW_LIMIT) return false;
@@ -540,7 +538,7 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     w.w_pitch = depth + 16;
     const int kb = g.K > 32 ? 64 : 32;
     const long long wlb = (long long)kb * w.w_pitch;
-    const long long raw = g.nhwc_in ? ((long long)kb * w.w_row + 3) / 4 * 4 : 0;   // the weight rows as they came
+    const long long raw = g.nhwc ? ((long long)kb * w.w_row + 3) / 4 * 4 : 0;   // the weight rows as they came
     if (win + 8 + wlb + depth + raw > 64 * 1024) return false;  // cannot happen within the limits above
     w.pitch = (int)pitch;
     w.win_bytes = (int)win;
@@ -556,7 +554,6 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     w.m_tiles_q = magic_for(w.tiles_q);
     w.m_tiles_p = magic_for(w.tiles_p);
     w.out_small = 4LL * g.K * g.P * g.Q < (1LL << 32);
-    w.in_small = (long long)C * g.H * W < (1LL << 31);
     w.wide_out = g.Q % 4 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 15) == 0;
     w.act = g.act;
     if (a) *a = w;
@@ -574,10 +571,7 @@ static hipError_t launch_window_kb(const WindowArgs &a, dim3 grid, size_t lds, h
 template <int NKK>
 static hipError_t launch_window_nkk(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (a.nhwc) {
-        if (a.act.out) return launch_window_kb<NKK, true, true, false>(a, grid, lds, st);
-        return launch_window_kb<NKK, false, true, false>(a, grid, lds, st);
-    }
+    if (a.nhwc) return launch_window_kb<NKK, false, true, false>(a, grid, lds, st);
     if (a.act.out) return launch_window_kb<NKK, true, false, false>(a, grid, lds, st);
     if (a.G > 1)
         return a.stream_out ? launch_window_kb<NKK, false, false, true, true>(a, grid, lds, st)
@@ -593,9 +587,9 @@ hipError_t launch_window_conv(const WindowProblem &g, hipStream_t st)
     const int depth = a.w_pitch - 16;
     const int kb = g.K > 32 ? 64 : 32;
     const dim3 grid((unsigned)(g.N * a.tiles_p * a.tiles_q), (unsigned)((g.K + kb - 1) / kb));
-    size_t lds = (size_t)a.win_bytes + a.wl_bytes + (size_t)depth + (g.nhwc_in ? ((size_t)kb * a.w_row + 3) / 4 * 4 : 0);
+    size_t lds = (size_t)a.win_bytes + a.wl_bytes + (size_t)depth + (g.nhwc ? ((size_t)kb * a.w_row + 3) / 4 * 4 : 0);
     // the output blocks of the four waves, turned around: over the window, or behind everything if the window is needed again
-    const size_t turned = g.act.out ? 0 : g.out_nhwc ? (size_t)4 * 32 * (kb + 4) * 4 : a.wide_out ? (size_t)4 * 32 * 36 * 4 : 0;
+    const size_t turned = g.act.out ? 0 : g.nhwc ? (size_t)4 * 32 * (kb + 4) * 4 : a.wide_out ? (size_t)4 * 32 * 36 * 4 : 0;
     if (a.G > 1) {
         a.turn_off = (int)((lds + 15) / 16 * 16);
         lds = a.turn_off + turned;
