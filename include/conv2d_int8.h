@@ -179,7 +179,8 @@ size_t conv2d_int8_tile_lds_bytes(const conv_desc_t *desc, int layout, int cb, i
  * per workgroup (the calls above choose both themselves).  nhwc = 0: in [N][C][H][W], out [N][K][P][Q]; else in
  * [N][H][W][C], out [N][P][Q][K].  wt_cb = 0: wt is KCRS as it is (3x3 kernels only); else the output of pack_weights
  * (PACKED, wt_cb), 16-byte aligned.  dilation >= 1; P, Q as for conv2d_int8_dilated_direct.  pixels: a multiple of 32,
- * 32 to 1024.  A pair whose weights and input window do not fit one compute unit's LDS: CONV_ERR_UNSUPPORTED, which is
+ * 32 to 1024.  tile = CONV_TILE_BAND with pixels = 0 is the band kernel on the NCHW tensor (nhwc 0, wt_cb 64 -- or blocks
+ * of 64 in all -- dilation 1, stride 1, three taps per kernel row).  A pair whose weights and input window do not fit one compute unit's LDS: CONV_ERR_UNSUPPORTED, which is
  * also what _applies says of it (host only). */
 int conv2d_int8_resident(const conv_desc_t *desc, int dilation, int nhwc, const int8_t *in, const int8_t *wt, int wt_cb,
                          int32_t *out, int tile, int pixels, void *stream);

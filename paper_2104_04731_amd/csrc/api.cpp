@@ -308,22 +308,27 @@ int run_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t st)
 }
 
 // ---- two-stage path or the GEMM stage that blocks the channels itself (resident_mfma.hip) -----------------------------
-// Estimated times in microseconds.  Two-stage, fitted to 188 layers of 5 us to 300 us (mean error 9 %, the choice between
-// the paths loses 1.3 % against the measured best one): the launches, the GEMM stage's own estimate, the rewritten tensors
-// written and read.  A second launch costs the stream about a microsecond more than it costs a graph, in which all of these
-// estimates were measured.
+// Estimated times in microseconds.  Two-stage, fitted to 9800 calls of 4900 layers in graphs (a third held back; mean error 3 %
+// where the band kernel runs, 6 % else): the launches, the GEMM stage's own estimate, the rewritten tensors written and
+// read.  apart: image planes that are not whole dwords, for which the input's rewrite takes its general kernel and a
+// one-shot call launches the two rewrites one after the other (without this the estimate was 20 % low there and 6 to 11 %
+// high elsewhere).  A second launch costs the stream about a microsecond more than it costs a graph.
 constexpr double SECOND_LAUNCH_US = 1.0;
-double two_stage_us(const GemmProblem &g, double moved, double weights, bool wt_is_packed)
+double two_stage_us(const GemmProblem &g, double moved, double weights, bool wt_is_packed, bool apart)
 {
     GemmChoice c;
     if (choose_gemm(g, -1, 0, &c) != CONV_OK) return 1e300;
-    const double us = c.tile == CONV_TILE_BAND
-                          ? wt_is_packed ? 2.1 + 0.96 * c.cost + 0.157e-6 * moved + 0.44e-6 * weights
-                                         : 2.2 + 1.03 * c.cost + 0.117e-6 * moved + 1.27e-6 * weights
-                          : wt_is_packed ? 2.4 + 1.01 * c.cost + 0.187e-6 * moved + 0.29e-6 * weights
-                                         : 3.3 + 1.02 * c.cost + 0.166e-6 * moved + 1.1e-6 * weights;
-    return us + SECOND_LAUNCH_US;
+    const bool whole_slices = g.mode != ACT_BLOCKED || g.cb % 64 == 0;
+    double us;
+    if (c.tile == CONV_TILE_BAND)
+        us = wt_is_packed ? 1.0 + 1.08 * c.cost + 0.161e-6 * moved + 0.38e-6 * weights + (apart ? 0.8 : 0)
+                          : 1.24 + 1.09 * c.cost + 0.156e-6 * moved + 1.0e-6 * weights + (apart ? 2.9 : 0);
+    else
+        us = (wt_is_packed ? 1.87 + 0.95 * c.cost + 0.169e-6 * moved + 1.0e-6 * weights + (apart ? 0.84 : 0)
+                           : 2.29 + 0.927 * c.cost + 0.153e-6 * moved + 1.9e-6 * weights + (apart ? 3.0 : 0)) + (whole_slices ? 0 : 0.6);
+    return us + SECOND_LAUNCH_US * (apart && !wt_is_packed ? 2 : 1);
 }
+bool planes_apart(const conv_desc_t *d, int layout) { return layout != CONV_LAYOUT_IM2COL && (long long)d->H * d->W % 4 != 0; }
 
 enum RouteHow : int {
     TWO_STAGE = CONV_STAGE_STORED,
@@ -378,11 +383,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             ResidentChoice c;
             const ResidentProblem r = resident_problem(d, pl, cb, depth, raw, nhwc, dil, nullptr, nullptr, out);
             if (!resident_pick(r, &c)) return;
-            // records of 128 channels and more leave one workgroup per compute unit; over many rounds the estimate, which
-            // was fitted to small and large layers alike, comes out 15 % low then (and 5 % in any grid from 200 channels on,
-            // 10 % with raw weights)
-            const double many = (d->C > 112 && (double)pl.M * d->K > 256.0 * 64 * 128 ? 1.15 : 1.0) * (d->C < 200 ? 1.0 : raw ? 1.1 : 1.05);
-            const double us = c.us * many + extra;
+            const double us = c.us + extra;
             if (us < best) {
                 best = us;
                 *n = Route{how, c, cb, depth};
@@ -444,11 +445,12 @@ int one_shot_route(const conv_desc_t *d, int layout, int cb, const int8_t *in, c
             if (image_pack_problem(d, cb, &pp) != CONV_OK || make_plan(&pp.d2, pp.inner_layout, pp.inner_cb, &inner) != CONV_OK) return 1e300;
             const double pack = 5.0 + 0.25e-6 * (in_bytes + (double)pp.x2_bytes) + 2 * SECOND_LAUNCH_US;
             if (inner.layout == CONV_LAYOUT_IMPLICIT) return pack + 4.0 + 0.25e-6 * ((double)pp.x2_bytes + 4.0 * pl->M * d->K);
-            return pack + two_stage_us(gemm_problem(&pp.d2, inner, nullptr, nullptr, out), (double)(pp.x2_bytes + inner.x_bytes), (double)inner.w_bytes, false);
+            return pack + two_stage_us(gemm_problem(&pp.d2, inner, nullptr, nullptr, out), (double)(pp.x2_bytes + inner.x_bytes), (double)inner.w_bytes, false,
+                                       planes_apart(&pp.d2, inner.layout));
         }
         Plan own;
         if (make_plan(d, layout, cb, &own) != CONV_OK) return 1e300;
-        return two_stage_us(gemm_problem(d, own, nullptr, nullptr, out), in_bytes + (double)own.x_bytes, (double)own.w_bytes, false);
+        return two_stage_us(gemm_problem(d, own, nullptr, nullptr, out), in_bytes + (double)own.x_bytes, (double)own.w_bytes, false, planes_apart(d, layout));
     });
     return CONV_OK;
 }
@@ -458,7 +460,8 @@ Route ex_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, const in
 {
     if (pl.layout == CONV_LAYOUT_IM2COL) return Route{TWO_STAGE, {}, 0, 0};
     return pick_route(d, pl, wt_is_packed, false, 1, wt, out, 0, [&] {
-        return two_stage_us(gemm_problem(d, pl, nullptr, nullptr, out), (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, wt_is_packed);
+        return two_stage_us(gemm_problem(d, pl, nullptr, nullptr, out), (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, wt_is_packed,
+                            planes_apart(d, pl.layout));
     });
 }
 
@@ -468,7 +471,7 @@ Route nhwc_route(const conv_desc_t *d, const Plan &pl, const int8_t *wt, int32_t
         GemmProblem g = gemm_problem(d, pl, nullptr, nullptr, out);
         g.out_nhwc = 1;
         // (a result that does not start on 16 bytes goes through a staging tensor and one more pass)
-        return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false) + (aligned16(out) ? 0 : 10);
+        return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false, false) + (aligned16(out) ? 0 : 10);
     });
 }
 
@@ -477,7 +480,7 @@ Route dilated_direct_route(const conv_desc_t *d, int dilation, const Plan &pl, c
     return pick_route(d, pl, false, false, dilation, wt, out, 2, [&] {
         GemmProblem g = gemm_problem(d, pl, nullptr, nullptr, out);
         g.dil = dilation;
-        return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false);
+        return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false, planes_apart(d, pl.layout));
     });
 }
 
@@ -486,7 +489,8 @@ Route dilated_route(const conv_desc_t *d, int dilation, const DilatedProblem &dp
 {
     return pick_route(d, direct, false, false, dilation, wt, out, 3, [&] {
         const double pack = 2.5 + 0.25e-6 * ((double)d->N * d->C * d->H * d->W + (double)dp.x2_bytes) + SECOND_LAUNCH_US;
-        return pack + two_stage_us(gemm_problem(&dp.d2, inner, nullptr, nullptr, nullptr), (double)dp.x2_bytes + (double)inner.x_bytes, (double)inner.w_bytes, false);
+        return pack + two_stage_us(gemm_problem(&dp.d2, inner, nullptr, nullptr, nullptr), (double)dp.x2_bytes + (double)inner.x_bytes, (double)inner.w_bytes, false,
+                                   planes_apart(&dp.d2, inner.layout));
     });
 }
 
@@ -1111,12 +1115,13 @@ int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int 
 static int resident_forced(const conv_desc_t *desc, int dilation, int nhwc, int wt_cb, int tile, int pixels, const int8_t *in, const int8_t *wt,
                            int32_t *out, ResidentProblem *r)
 {
-    if (tile < 0 || tile >= resident_num_tiles() || pixels < 32 || pixels > 1024 || pixels % 32 || wt_cb < 0) return CONV_ERR_INVALID_ARG;
+    const bool band = tile == CONV_TILE_BAND;
+    if (wt_cb < 0 || (band ? pixels != 0 : tile < 0 || tile >= resident_num_tiles() || pixels < 32 || pixels > 1024 || pixels % 32)) return CONV_ERR_INVALID_ARG;
     Plan pl;
     const int rc = direct_dilated_plan(desc, dilation, wt_cb ? wt_cb : 16, &pl);
     if (rc != CONV_OK) return rc;
     *r = resident_problem(desc, pl, wt_cb ? pl.cb : round_up_i(desc->C, 16), pl.depth, wt_cb == 0, nhwc != 0, dilation, in, wt, out);
-    return resident_applies(*r, tile, pixels) ? CONV_OK : CONV_ERR_UNSUPPORTED;
+    return (band ? band_direct_applies(*r) : resident_applies(*r, tile, pixels)) ? CONV_OK : CONV_ERR_UNSUPPORTED;
 }
 
 int conv2d_int8_resident_tile_info(int tile, int *rows, int *cols, int *threads)
@@ -1142,7 +1147,7 @@ int conv2d_int8_resident(const conv_desc_t *desc, int dilation, int nhwc, const 
     const int rc = resident_forced(desc, dilation, nhwc, wt_cb, tile, pixels, in, wt, out, &r);
     if (rc != CONV_OK) return rc;
     if (!in || !wt || !out || (wt_cb && !aligned16(wt))) return CONV_ERR_INVALID_ARG;
-    return gemm_status(launch_resident_forced(r, tile, pixels, (hipStream_t)stream));
+    return gemm_status(tile == CONV_TILE_BAND ? launch_band_direct(r, (hipStream_t)stream) : launch_resident_forced(r, tile, pixels, (hipStream_t)stream));
 }
 
 int conv2d_int8_tile_applies(const conv_desc_t *desc, int layout, int cb, int tile, int split_k)

@@ -774,9 +774,16 @@ hipError_t launch_band_conv(const GemmProblem &g, hipStream_t st)
 }
 
 // ---- the same on the network's own tensor ---------------------------------------------------------------------------
-// Launch time in microseconds, fitted to 60 launches of grids up to 512 workgroups (mean error 5 %): MFMAs, window bytes and
-// rounds of window loads of the busiest compute unit.  Larger grids pay the window of all channels again in every workgroup
-// (32 x 256 x 14 x 14 -> 512: 31 us against 20 in two launches): not taken.
+// Launch time in microseconds, fitted to 267 launches of grids up to 512 workgroups (mean error 4 %, the same on a third of them held
+// back): MFMAs, window bytes and rounds of window loads of the busiest compute unit, and 2 us where its second workgroup
+// finds no room beside the first one and starts over behind it.  Larger grids pay the window of all channels again in every
+// workgroup (32 x 256 x 14 x 14 -> 512: 31 us against 20 in two launches): not taken.
+bool band_direct_applies(const ResidentProblem &r)
+{
+    BandPlan bp;
+    return band_plan(r.g, &bp, &r);
+}
+
 bool band_direct_us(const ResidentProblem &r, double *us)
 {
     if (r.g.cb != 64) return false;
@@ -785,7 +792,7 @@ bool band_direct_us(const ResidentProblem &r, double *us)
     const BandArgs &a = bp.a;
     const int rows = std::min(a.PT - 1 + a.R, a.H), slots = (rows * a.W + 14) & ~7;
     const double ncu = (bp.grid + 255) / 256, units = (a.cq * (slots / 8) + 1023) / 1024;
-    *us = 4.1 + ncu * (0.0194 * bp.srow * bp.gpw * bp.pb * 2 + 5.24e-5 * a.cq * 4 * slots + 0.12 * units + (a.C % 16 ? 0.43 * units : 0));
+    *us = 3.39 + ncu * (0.0186 * bp.srow * bp.gpw * bp.pb * 2 + 5.63e-5 * a.cq * 4 * slots + 0.204 * units) + (bp.lds > BAND_LDS_LIMIT / 2 ? 2.0 * (ncu - 1) : 0);
     return true;
 }
 

@@ -94,6 +94,7 @@ bool resident_applies(const ResidentProblem &r, int tile, int mper);
 hipError_t launch_resident_forced(const ResidentProblem &r, int tile, int mper, hipStream_t st);
 // The band kernel on the same problem (NCHW, weights in blocks of 64): estimated launch time; false: not its domain.
 bool band_direct_us(const ResidentProblem &r, double *us);
+bool band_direct_applies(const ResidentProblem &r);   // (also where the estimate is not made: large grids)
 hipError_t launch_band_direct(const ResidentProblem &r, hipStream_t st);
 
 // blocks x 4 waves x iters x 4 MFMA 32x32x32 i8 on register operands; out: blocks * 256 int32

@@ -514,10 +514,15 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
 }
 
 
-// Launch time in microseconds, fitted to 12000 measured launches of 200 layers (every tile, 8 to 12 pixel counts each;
-// mean error 9 %, the pick loses 1 % against the measured best): a launch, then per round of workgroups that fit the chip a
-// fixed part, the chain of MFMAs of one wave and the rounds of window loads; for the busiest compute unit its MFMAs and the
-// bytes in and out.
+// Launch time in microseconds, fitted to 37900 measured launches of 4900 layers (every tile, 2 to 5 pixel counts each; a third
+// of the layers held back).  A launch; per round of workgroups that fit the chip the chain of MFMAs of one wave and the
+// rounds of window loads; for the busiest compute unit its MFMAs and the bytes in and out; for the whole chip all
+// workgroups' bytes, which share the memory system (per: workgroups per compute unit -- without it a layer of 200 channels and
+// more came out right on half a chip and 8 % low on a full one); from the second round on window and weights once more, because a
+// round's loads queue behind the results that all workgroups of the round before store at its end; raw weights go through
+// the registers in rounds of loads of their own, more than twice as long where the rows of 9 C bytes do not start on dwords.
+// Near each layer's best launch, on the layers held back: mean error 5 %; by channels, weights and workgroups no group is off
+// by more than 4 %, but for kept weights of 200 channels and more in several rounds (9 % low).
 double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile, int mper, int slots)
 {
     const GemmProblem &g = r.g;
@@ -533,9 +538,15 @@ double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile
     const int blocks = (mper + 32 * d.fm - 1) / (32 * d.fm);
     const double chain = (double)((blocks + d.nw - 1) / d.nw) * d.fm * (d.tk / 32) * 2 * sh.steps;
     const double units = (double)((slots / 8 * (sh.C16 / 4) + d.nw * 256 - 1) / (d.nw * 256));
-    const double mfma = d.tk / 32 * d.fm * blocks * 2.0 * sh.steps / 4, out_byte = g.PQ % 16 == 0 ? 2.27e-5 : 3.06e-5;
-    double t = 3.28 + rounds * (1.0 + 0.0279 * chain + 0.585 * units) + ncu * (1.85e-3 * mfma + 5.68e-5 * slots * sh.C16 + out_byte * d.tk * mper * 4);
-    if (r.raw_weights) t += 0.297 * rounds * d.tk * (sh.C16 / 4) / (d.nw * 64) + 0.0239 * ncu * d.tk * (sh.C16 / 4) / 64;
+    const double mfma = d.tk / 32 * d.fm * blocks * 2.0 * sh.steps / 4, window = (double)slots * sh.C16, weights = (double)sh.steps * d.tk * 64;
+    const double result = 4.0 * d.tk * mper;
+    double t = 4.11 + rounds * (0.0258 * chain + 0.386 * units) + ncu * (8.14e-3 * mfma + 3.41e-5 * window + 1.43e-6 * weights + 5.66e-6 * result) +
+               per * (1.41e-5 * window + 6.7e-6 * weights + (g.PQ % 16 == 0 ? 1.55e-5 : 2.47e-5) * result) +
+               (rounds - 1) * (1.43e-5 * window + 8.08e-6 * weights);
+    if (r.raw_weights) {
+        const int loads = (d.tk * (sh.C16 / 4) + d.nw * 64 - 1) / (d.nw * 64);
+        t += rounds * (0.706 + (r.C % 4 ? 0.638 : 0.272) * loads);
+    }
     return t;
 }
 

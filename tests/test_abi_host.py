@@ -408,6 +408,10 @@ def test_resident_stage_validation(lib):
     assert call(desc=lib.ConvDesc(2, 1024, 14, 14, 32, 3, 3, 1, 1)) == lib.ERR_UNSUPPORTED       # more weights than LDS
     assert raw.conv2d_int8_resident(None, 1, 0, p, p, 32, p, 0, 64, None) == lib.ERR_INVALID_ARG
     assert lib.resident_applies((2, 20, 14, 14, 32, 3, 3, 1, 1), 32, 0, 64)
+    band = lambda dims, cb=64, dil=1, nhwc=0, px=0: raw.conv2d_int8_resident_applies(ctypes.byref(lib.ConvDesc(*dims)), dil, nhwc, cb, lib.TILE_BAND, px)
+    assert band((2, 20, 14, 14, 32, 3, 3, 1, 1)) == lib.OK and band((2, 20, 14, 14, 32, 3, 3, 1, 1), px=32) == lib.ERR_INVALID_ARG
+    for kw in ({"cb": 32}, {"cb": 0}, {"dil": 2}, {"nhwc": 1}, {"dims": (2, 20, 14, 14, 32, 3, 3, 2, 1)}, {"dims": (2, 20, 14, 14, 32, 5, 5, 1, 2)}):
+        assert band(**{"dims": (2, 20, 14, 14, 32, 3, 3, 1, 1), **kw}) == lib.ERR_UNSUPPORTED, kw
 
 
 def test_query_stage(lib):

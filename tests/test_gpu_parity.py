@@ -1355,12 +1355,26 @@ def test_resident_every_tile(lib, cfg):
     assert not small or {(t, many, r, h) for t in range(len(lib.resident_tiles())) for many in (False, True) for r in raw for h in (False, True)} <= ran
 
 
-def test_band_direct_shapes_run_the_band_kernel(lib):
-    wide = ConvShape("band-c256-w71", 1, 256, 3, 71, 128, 3, 3, 1, 1)   # one output row per band, six blocks of columns
-    assert [c.name for c in BAND_DIRECT_SHAPES if lib.query_stage(c.dims(), lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True)[0] != lib.STAGE_BAND] == ["band-c256-wide"]
-    assert lib.query_stage(wide.dims(), lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True)[0] == lib.STAGE_BAND
-    for offset in (0, 3):
-        test_band_direct(lib, wide, offset)
+# The band kernel on the network's own tensor, asked for: also one output row per band with six blocks of columns, and a grid
+# larger than the estimate's.
+BAND_FORCED = BAND_DIRECT_SHAPES + [ConvShape("band-c256-w71", 1, 256, 3, 71, 128, 3, 3, 1, 1), ConvShape("band-c217", 3, 217, 10, 10, 61, 3, 3, 1, 1),
+                                    ConvShape("band-c3", 2, 3, 9, 12, 33, 3, 3, 1, 1), ConvShape("band-many", 40, 70, 7, 7, 500, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("cfg", BAND_FORCED, ids=lambda c: c.name)
+@pytest.mark.parametrize("offset", [0, 3])
+def test_band_on_the_nchw_tensor(lib, cfg, offset):
+    assert lib.resident_applies(cfg.dims(), 64, lib.TILE_BAND, 0) == (cfg.name != "band-c256-wide")   # (its window does not fit)
+    if cfg.name == "band-c256-wide":
+        return
+    x, w, want = oracle_conv(cfg)
+    t = torch.empty(x.size + offset, dtype=torch.int8, device=DEV)
+    t[offset:] = dev(x).view(-1)
+    buf = torch.full((want.size + 128,), -7, dtype=torch.int32, device=DEV)
+    lib.conv2d_int8_resident(cfg.dims(), t[offset:].view(x.shape), lib.pack_weights(dev(w), lib.LAYOUT_PACKED, 64), buf[64:-64].view(want.shape), 64,
+                             lib.TILE_BAND, 0)
+    got = host(buf)
+    assert np.array_equal(got[64:-64].reshape(want.shape), want) and (got[:64] == -7).all() and (got[-64:] == -7).all()
 
 
 # Layouts taken at their word, at the shapes whose conv2d_int8_ex goes to the stage above instead.
