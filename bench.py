@@ -649,7 +649,7 @@ def n_scaled(lib, timed, CONFIGS, dev):
 
 
 def cpu_baseline(cfgs):
-    """The CPU checker, as it stands, timed on the host cores over the headline workload."""
+    """The oracle, as it stands, timed on the host cores over the headline workload."""
     from oracle import direct
     best = None
     ops = sum(c.ops for c in cfgs)

@@ -329,7 +329,8 @@ int conv2d_int8_dilated(const conv_desc_t *desc, int dilation, int layout, int c
  * (not the paper's route: there the intrinsic's operand must be a dense box, Sec. 4.2).  Any stride >= 1 and
  * dilation >= 1: out[n][k][p][q] = sum in0[n][c][p*stride + r*dilation - pad][q*stride + s*dilation - pad] * wt[k][c][r][s],
  * P = floor((H + 2 pad - dilation*(R-1) - 1)/stride) + 1.  Workspace as for conv2d_int8_ex, at least
- * conv2d_int8_dilated_direct_workspace_bytes(desc, dilation, cb) bytes.  Two launches. */
+ * conv2d_int8_dilated_direct_workspace_bytes(desc, dilation, cb) bytes.  Two launches, or the stage that takes the image
+ * as it is (see conv2d_int8). */
 size_t conv2d_int8_dilated_direct_workspace_bytes(const conv_desc_t *desc, int dilation, int cb);
 int conv2d_int8_dilated_direct(const conv_desc_t *desc, int dilation, int cb,
                                const int8_t *in, const int8_t *wt, int32_t *out,

@@ -2,7 +2,7 @@
 
 conv2d by its definition (Fig. 5 step 1 / Fig. 1b / Table 2 access [n, i+k];
 int8 operands, int32 accumulation, Sec. 5.1).  The shared object is compiled with
-gcc on first use if it has not been built yet (building the checker is not using it).
+gcc on first use if it has not been built yet (building it is not using it).
 """
 from __future__ import annotations
 

@@ -1330,8 +1330,8 @@ int conv2d_int8_static(int N, int C, int H, int W, int K, int R, int S, int stri
 int conv2d_int8_nhwc(int N, int C, int H, int W, int K, int R, int S, int stride, int pad,
                      const int8_t *in, const int8_t *wt, int32_t *out, void *stream)
 {
-    // channel blocking straight from the NHWC source, the usual GEMM stage into an NKPQ staging
-    // tensor in the workspace, then unpacking to NHWC
+    // The window kernel or a matrix product on the tensors as they are, the resident kernel, or channel blocking straight
+    // from the NHWC source and a GEMM stage that writes NHWC.
     conv_desc_t d{N, C, H, W, K, R, S, stride, pad};
     Plan pl;
     int rc = make_plan(&d, CONV_LAYOUT_PACKED, 0, &pl);

@@ -145,7 +145,7 @@ __device__ __forceinline__ void static_for(F &&f)
 // are, without border, as pixel-major records of all channels (window_fill.h); a lane whose input column or row lies
 // outside the image reads a record of zeros.  This wave's weights are asked for first, then the window; both latencies are
 // paid once, the rewrite's launch and its image not at all (packed weights, two launches in a graph -> one: 1 x 128 x 28 x
-// 28 -> 128 6.9 -> 5.7 us, 13 x 256 x 9 x 9 -> 124 8.7 -> 6.7, 32 x 256 x 8 x 8 -> 128 7.8 -> 6.6).  Measured and not taken:
+// 28 -> 128 6.7 -> 5.1 us, 13 x 256 x 9 x 9 -> 124 8.6 -> 6.1, 32 x 256 x 8 x 8 -> 128 7.6 -> 6.1).  Measured and not taken:
 // the weights straight into registers (7.1 -> 8.3 us at 256 channels), eight window units in flight per thread (level).
 template <int SROW, int GPW, int PB, bool FULL, bool DIRECT>
 __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const BandArgs a)

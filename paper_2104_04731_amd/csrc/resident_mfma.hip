@@ -16,9 +16,9 @@
 //     raw: 36 bytes of four channels x nine taps are nine dwords of the tile after 27 byte permutes.
 // Bound: the memory system (input once, result once) for the small and middle depths the kernel is for -- weights plus
 // window must fit one compute unit's LDS, which rules out 3x3 layers of more than about 300 channels.  Measured in a
-// graph, two-stage -> this kernel: 64 images 56x56, 64 -> 64, 3x3: 35 -> 18.8 us with rewritten weights (12.8 MB in, 51 MB
-// out), 21 us from raw ones; 16 images 56x56, 72 -> 96, stride 2: 13.4 -> 10.1; 445 images 14x14, 32 -> 405: 87 -> 34;
-// dilation 2, 64 images 28x28, 64 -> 64: 12.5 (20 through sub-images) -> 8.7.
+// graph, two-stage -> this kernel: 64 images 56x56, 64 -> 64, 3x3: 38 -> 19.6 us with rewritten weights (12.8 MB in, 51 MB
+// out), 38 -> 19.7 from raw ones; 16 images 56x56, 72 -> 96, stride 2: 12.2 -> 10.6; 445 images 14x14, 32 -> 405: 46 -> 36;
+// dilation 2, 64 images 28x28, 64 -> 64: 19.6 through sub-images -> 8.9.
 #include "launch.h"
 #include "window_fill.h"
 

@@ -1,6 +1,5 @@
-// Device bodies of the layout rewrites that more than one kernel uses (the stand-alone
-// rewrite kernels, the two-rewrites-in-one-launch kernel, and the whole-convolution kernel),
-// with the host helpers that fill their argument blocks.
+// Device bodies of the layout rewrites that more than one kernel uses (the stand-alone rewrite kernels and the
+// two-rewrites-in-one-launch kernel), with the host helpers that fill their argument blocks.
 #pragma once
 #include "act_requant.h"
 #include "kernels.h"

@@ -473,11 +473,11 @@ constexpr double STREAM_BYTES = 256e6;
 
 // How many row groups a tile takes (a kernel of its own from 2 on): its window's rows overlap, the weights and the table are
 // brought in once.  Measured over 110 stem and speech layers.  Up to 32 output channels the time goes into filling the LDS:
-// the most of 2, 4, 8 that leaves two workgroups for each place on the chip (353 images 3 x 212 x 166, 7 x 7 / 2 -> 16: 119
-// -> 85 us; 68 x 1 x 161 x 686, 20 x 5 / 2 -> 32: 50 -> 41; 100 x 3 x 131 x 151, 3 x 3 -> 32: 59 -> 48); three for a depth of
-// 64, which gains the least.  Above 32 channels it goes into the stores, which come in one burst per workgroup and
-// overlap less the longer it runs: two groups where the window is large (40 x 1 x 161 x 522, 20 x 5 / 2 -> 64: 46.5 -> 41) and
-// the stores do not bypass the caches, else one.
+// the most of 2, 4, 8 that leaves two workgroups for each place on the chip (kept weights, 353 images 3 x 212 x 166, 7 x 7 / 2
+// -> 16: 100 -> 88 us; 68 x 1 x 161 x 686, 20 x 5 / 2 -> 32: 49 -> 42; 100 x 3 x 131 x 151, 3 x 3 -> 32: 57 -> 52); three
+// times as many for a depth of 64, which gains the least.  Above 32 channels it goes into the stores, which come in one burst
+// per workgroup and overlap less the longer it runs: two groups where the window is large (40 x 1 x 161 x 522, 20 x 5 / 2 -> 64,
+// raw weights: 47.8 -> 41, kept ones 39.4 -> 37.2) and the stores do not bypass the caches, else one.
 static int window_groups(const WindowProblem &g, int PT, int QT, long long row_bytes, int depth, bool stream_out)
 {
     if (g.nhwc || g.act.out) return 1;

@@ -2,7 +2,7 @@
 
 This module only *generates inputs*: it holds none of the method's arithmetic
 (no convolution, no packing, no im2col, no cost model).  Both the GPU path and
-the CPU checker are fed from here so that they see identical bytes.
+the oracle are fed from here so that they see identical bytes.
 
 Shapes stand in for the DeepBench inference convolutions the paper measures on
 (Sec. 5.1): ordinary many-channel 3x3 layers, the 7x7 stride-2 three-channel
