@@ -308,27 +308,36 @@ int run_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t st)
 }
 
 // ---- two-stage path or the GEMM stage that blocks the channels itself (resident_mfma.hip) -----------------------------
-// Estimated times in microseconds.  Two-stage, fitted to 9800 calls of 4900 layers in graphs (a third held back; mean error 3 %
-// where the band kernel runs, 6 % else): the launches, the GEMM stage's own estimate, the rewritten tensors written and
-// read.  apart: image planes that are not whole dwords, for which the input's rewrite takes its general kernel and a
-// one-shot call launches the two rewrites one after the other (without this the estimate was 20 % low there and 6 to 11 %
-// high elsewhere).  A second launch costs the stream about a microsecond more than it costs a graph.
+// Estimated times in microseconds.  Two-stage, fitted per kind of call to 19000 calls of 5800 layers in graphs (a third held
+// back; mean error 3 % where the band kernel runs, 5 to 6 % for the general one, 7 to 9 % unrolled and from NHWC): the launches, the
+// GEMM stage's own estimate, the rewritten tensors written and read.  apart: image planes that are not whole dwords, for which
+// the rewrite of 64-channel slices takes its general kernel and a one-shot call launches the two rewrites one after the other.
+// A second launch costs the stream about a microsecond more than it costs a graph.
 constexpr double SECOND_LAUNCH_US = 1.0;
-double two_stage_us(const GemmProblem &g, double moved, double weights, bool wt_is_packed, bool apart)
+struct TwoStageFit {
+    double launch, gemm, moved, weights, apart;
+};
+constexpr TwoStageFit FIT_BAND[] = {{1.24, 1.09, 0.148e-6, 1.01e-6, 2.9}, {1.01, 1.09, 0.153e-6, 0.37e-6, 0.79}};      // raw, kept weights
+constexpr TwoStageFit FIT_SLICES[] = {{2.21, 0.929, 0.142e-6, 1.89e-6, 3.33}, {1.82, 0.949, 0.154e-6, 1.03e-6, 1.11}};  // blocks of whole 64 channels
+constexpr TwoStageFit FIT_BLOCKS[] = {{3.36, 0.927, 0.218e-6, 1.81e-6, 1.63}, {2.85, 0.936, 0.221e-6, 1.04e-6, 0}};      // other blocks
+constexpr TwoStageFit FIT_UNROLLED[] = {{3.23, 1.0, 0.340e-6, 5.25e-6, 0}, {3.06, 1.01, 0.347e-6, 4.11e-6, 0}};
+constexpr TwoStageFit FIT_NHWC_BAND = {0.28, 1.19, 0.304e-6, 0.735e-6, 0}, FIT_NHWC = {0.22, 1.27, 0.251e-6, 0, 0};
+
+// d, pl: what is rewritten and how; g: the GEMM stage on it (a dilated layer's own extents, an NHWC result).
+double two_stage_us(const conv_desc_t *d, const Plan &pl, const GemmProblem &g, bool wt_is_packed, bool nhwc)
 {
     GemmChoice c;
     if (choose_gemm(g, -1, 0, &c) != CONV_OK) return 1e300;
-    const bool whole_slices = g.mode != ACT_BLOCKED || g.cb % 64 == 0;
-    double us;
-    if (c.tile == CONV_TILE_BAND)
-        us = wt_is_packed ? 1.0 + 1.08 * c.cost + 0.161e-6 * moved + 0.38e-6 * weights + (apart ? 0.8 : 0)
-                          : 1.24 + 1.09 * c.cost + 0.156e-6 * moved + 1.0e-6 * weights + (apart ? 2.9 : 0);
-    else
-        us = (wt_is_packed ? 1.87 + 0.95 * c.cost + 0.169e-6 * moved + 1.0e-6 * weights + (apart ? 0.84 : 0)
-                           : 2.29 + 0.927 * c.cost + 0.153e-6 * moved + 1.9e-6 * weights + (apart ? 3.0 : 0)) + (whole_slices ? 0 : 0.6);
+    const bool band = c.tile == CONV_TILE_BAND;
+    const TwoStageFit &f = nhwc ? band ? FIT_NHWC_BAND : FIT_NHWC
+                                : (band ? FIT_BAND : pl.layout == CONV_LAYOUT_IM2COL ? FIT_UNROLLED : pl.cb % 64 == 0 ? FIT_SLICES : FIT_BLOCKS)[wt_is_packed];
+    const bool apart = !nhwc && pl.layout != CONV_LAYOUT_IM2COL && (long long)d->H * d->W % 4 != 0;
+    const double moved = (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes;
+    double us = f.launch + f.gemm * c.cost + f.moved * moved + f.weights * (double)pl.w_bytes + (apart ? f.apart : 0);
+    if (nhwc && d->C % 16) us += 1.4 + 0.12e-6 * moved;                                      // (pixels' ends go byte by byte)
+    if (nhwc && d->K % 4) us += (band ? 0.19e-6 : 0.054e-6) * 4.0 * (double)pl.M * d->K;     // (results value by value)
     return us + SECOND_LAUNCH_US * (apart && !wt_is_packed ? 2 : 1);
 }
-bool planes_apart(const conv_desc_t *d, int layout) { return layout != CONV_LAYOUT_IM2COL && (long long)d->H * d->W % 4 != 0; }
 
 enum RouteHow : int {
     TWO_STAGE = CONV_STAGE_STORED,
@@ -445,12 +454,11 @@ int one_shot_route(const conv_desc_t *d, int layout, int cb, const int8_t *in, c
             if (image_pack_problem(d, cb, &pp) != CONV_OK || make_plan(&pp.d2, pp.inner_layout, pp.inner_cb, &inner) != CONV_OK) return 1e300;
             const double pack = 5.0 + 0.25e-6 * (in_bytes + (double)pp.x2_bytes) + 2 * SECOND_LAUNCH_US;
             if (inner.layout == CONV_LAYOUT_IMPLICIT) return pack + 4.0 + 0.25e-6 * ((double)pp.x2_bytes + 4.0 * pl->M * d->K);
-            return pack + two_stage_us(gemm_problem(&pp.d2, inner, nullptr, nullptr, out), (double)(pp.x2_bytes + inner.x_bytes), (double)inner.w_bytes, false,
-                                       planes_apart(&pp.d2, inner.layout));
+            return pack + two_stage_us(&pp.d2, inner, gemm_problem(&pp.d2, inner, nullptr, nullptr, out), false, false);
         }
         Plan own;
         if (make_plan(d, layout, cb, &own) != CONV_OK) return 1e300;
-        return two_stage_us(gemm_problem(d, own, nullptr, nullptr, out), in_bytes + (double)own.x_bytes, (double)own.w_bytes, false, planes_apart(d, layout));
+        return two_stage_us(d, own, gemm_problem(d, own, nullptr, nullptr, out), false, false);
     });
     return CONV_OK;
 }
@@ -460,8 +468,7 @@ Route ex_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, const in
 {
     if (pl.layout == CONV_LAYOUT_IM2COL) return Route{TWO_STAGE, {}, 0, 0};
     return pick_route(d, pl, wt_is_packed, false, 1, wt, out, 0, [&] {
-        return two_stage_us(gemm_problem(d, pl, nullptr, nullptr, out), (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, wt_is_packed,
-                            planes_apart(d, pl.layout));
+        return two_stage_us(d, pl, gemm_problem(d, pl, nullptr, nullptr, out), wt_is_packed, false);
     });
 }
 
@@ -471,7 +478,7 @@ Route nhwc_route(const conv_desc_t *d, const Plan &pl, const int8_t *wt, int32_t
         GemmProblem g = gemm_problem(d, pl, nullptr, nullptr, out);
         g.out_nhwc = 1;
         // (a result that does not start on 16 bytes goes through a staging tensor and one more pass)
-        return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false, false) + (aligned16(out) ? 0 : 10);
+        return two_stage_us(d, pl, g, false, true) + (aligned16(out) ? 0 : 10);
     });
 }
 
@@ -480,7 +487,7 @@ Route dilated_direct_route(const conv_desc_t *d, int dilation, const Plan &pl, c
     return pick_route(d, pl, false, false, dilation, wt, out, 2, [&] {
         GemmProblem g = gemm_problem(d, pl, nullptr, nullptr, out);
         g.dil = dilation;
-        return two_stage_us(g, (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes, (double)pl.w_bytes, false, planes_apart(d, pl.layout));
+        return two_stage_us(d, pl, g, false, false);
     });
 }
 
@@ -489,8 +496,7 @@ Route dilated_route(const conv_desc_t *d, int dilation, const DilatedProblem &dp
 {
     return pick_route(d, direct, false, false, dilation, wt, out, 3, [&] {
         const double pack = 2.5 + 0.25e-6 * ((double)d->N * d->C * d->H * d->W + (double)dp.x2_bytes) + SECOND_LAUNCH_US;
-        return pack + two_stage_us(gemm_problem(&dp.d2, inner, nullptr, nullptr, nullptr), (double)dp.x2_bytes + (double)inner.x_bytes, (double)inner.w_bytes, false,
-                                   planes_apart(&dp.d2, inner.layout));
+        return pack + two_stage_us(&dp.d2, inner, gemm_problem(&dp.d2, inner, nullptr, nullptr, nullptr), false, false);
     });
 }
 
