@@ -1394,3 +1394,21 @@ def test_stored_layouts(lib, cfg):
             assert np.array_equal(host(out), want), (lib.LAYOUT_NAMES[layout], cb, packed)
             assert not packed or layout == lib.LAYOUT_IMAGE_PACK or bool((ws[:need] != 85).any()), "nothing was stored"
             assert bool((ws[need:] == 85).all())
+
+
+# The weight half of the fused rewrite launch on the shapes of test_fused_rewrite_weight_range, through the call that takes the
+# layout at its word (conv2d_int8_ex runs them without a rewrite).
+@pytest.mark.parametrize(*test_fused_rewrite_weight_range.pytestmark[0].args, ids=str)
+def test_fused_rewrite_weight_range_stored(lib, dims, cb):
+    cfg = ConvShape("fused-w", *dims)
+    x = uniform_int8(971, (cfg.N, cfg.C, cfg.H, cfg.W)); w = uniform_int8(972, (cfg.K, cfg.C, cfg.R, cfg.S))
+    want = direct.conv2d_int8(x, w, cfg.stride, cfg.pad)
+    need = lib.conv2d_int8_workspace_bytes(dims, lib.LAYOUT_PACKED, cb)
+    ws = torch.full((need + 256,), 85, dtype=torch.int8, device=DEV)
+    out = torch.full(want.shape, -5, dtype=torch.int32, device=DEV)
+    lib.conv2d_int8_stored(dims, lib.LAYOUT_PACKED, cb, dev(x), dev(w), out, ws[:need])
+    assert np.array_equal(host(out), want)
+    xq, wq = layouts.pack_layout(x, cb, cfg.pad), layouts.pack_weights_blocked(w, cb)
+    at = layouts.ceil_to(xq.size, 256)
+    got = host(ws)
+    assert np.array_equal(got[:xq.size], xq.ravel()) and np.array_equal(got[at:at + wq.size], wq.ravel()) and (got[need:] == 85).all()

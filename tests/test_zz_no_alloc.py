@@ -53,3 +53,18 @@ def test_static_workspace_refuses_what_does_not_fit(lib):
     assert e.value.status == lib.ERR_WORKSPACE
     torch.cuda.synchronize()
     assert int((out != -7).sum()) == 0      # nothing was enqueued
+
+
+def test_static_workspace_with_layers_that_store_their_rewrites(lib):
+    """The first test above with layers whose rewritten operands do go to the array: 1.7 MB of it, then a little less of the
+    same bytes, then a depth split behind stored rewrites, then the first again."""
+    big, small, split = CONFIGS["C4a"], CONFIGS["C4a"].scaled(6), ConvShape("split-stored", 4, 256, 3, 3, 64, 5, 5, 1, 2)
+    for cfg in (big, small, split, big):
+        layout, cb, _ = lib.select_layout(cfg.dims())
+        assert lib.query_stage(cfg.dims(), lib.ENTRY_EX, layout, cb)[0] == lib.STAGE_STORED, cfg.name
+        assert cfg is not split or lib.query_tiling(cfg.dims(), layout, cb)[1] > 1
+        x, w = cfg.make()
+        dx, dw = torch.from_numpy(x).to(DEV), torch.from_numpy(w).to(DEV)
+        got, ref = _run_both(lib, cfg, dx, dw)
+        assert np.array_equal(got, ref), cfg.name
+        assert np.array_equal(got, direct.conv2d_int8(x, w, cfg.stride, cfg.pad)), cfg.name
