@@ -1412,3 +1412,37 @@ def test_fused_rewrite_weight_range_stored(lib, dims, cb):
     at = layouts.ceil_to(xq.size, 256)
     got = host(ws)
     assert np.array_equal(got[:xq.size], xq.ravel()) and np.array_equal(got[at:at + wq.size], wq.ravel()) and (got[need:] == 85).all()
+
+
+# NHWC and dilated calls on layers deep enough for the stored rewrites (most shapes of the tests above go to the resident kernel):
+# band kernel and general kernel with depth splits, strides, kernel taps `dilation` pixels apart, a result off its 16 bytes.
+STORED_NHWC = [CONFIGS["C4a"], ConvShape("sn-c256-k30", 1, 256, 9, 9, 30, 3, 3, 1, 1), ConvShape("sn-5x5-s2", 3, 320, 10, 7, 70, 5, 5, 2, 2),
+               ConvShape("sn-c600-s2", 2, 600, 8, 7, 66, 3, 3, 2, 1), ConvShape("sn-c1000", 2, 1000, 5, 5, 37, 3, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("cfg", STORED_NHWC, ids=lambda c: c.name)
+def test_nhwc_through_stored_rewrites(lib, cfg):
+    assert lib.query_stage(cfg.dims(), lib.ENTRY_NHWC)[0] == lib.STAGE_STORED
+    x, w, want = oracle_conv(cfg)
+    want = layouts.unpack_nhwc(want)
+    xh = dev(np.ascontiguousarray(x.transpose(0, 2, 3, 1)))
+    for offset in (0, 1):   # (1: staging tensor and a pass of its own, where the call stays on this route)
+        buf = torch.full((want.size + 8,), -7, dtype=torch.int32, device=DEV)
+        lib.conv2d_int8_nhwc(xh, dev(w), cfg.stride, cfg.pad, out=buf[offset:offset + want.size].view(want.shape))
+        got = host(buf)
+        assert np.array_equal(got[offset:offset + want.size].reshape(want.shape), want) and (got[:offset] == -7).all() and (got[offset + want.size:] == -7).all()
+
+
+STORED_DILATED = [((8, 256, 6, 6, 64, 3, 3, 1, 2), 2, 0), ((1, 512, 9, 9, 40, 3, 3, 1, 2), 2, 16), ((2, 200, 12, 15, 70, 5, 5, 1, 4), 2, 32),
+                  ((2, 400, 17, 13, 96, 3, 3, 3, 4), 4, 0), ((1, 600, 11, 10, 30, 3, 2, 2, 2), 2, 48), ((3, 1000, 9, 9, 50, 1, 1, 2, 0), 5, 0)]
+
+
+@pytest.mark.parametrize("case", STORED_DILATED, ids=str)
+def test_dilated_direct_through_stored_rewrites(lib, case):
+    dims, d, cb = case
+    assert lib.query_stage(dims, lib.ENTRY_DILATED_DIRECT, cb=cb, dilation=d)[0] == lib.STAGE_STORED
+    x = uniform_int8(943, dims[:4]); w = uniform_int8(944, (dims[4], dims[1], dims[5], dims[6]))
+    want = direct.conv2d_int8_dilated(x, w, dims[7], dims[8], d)
+    out = torch.full(want.shape, -3, dtype=torch.int32, device=DEV)
+    lib.conv2d_int8_dilated_direct(dims, d, dev(x), dev(w), cb, out=out)
+    assert np.array_equal(host(out), want)
