@@ -160,22 +160,9 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
     const int tm = fast_div_any(lid, a.tiles_k, a.mg_tiles_k), tk = lid - tm * a.tiles_k;
     const int k0 = tk * TK, m0 = tm * a.mper, m1 = min(m0 + a.mper, a.M);
 
-    // ---- input ranges: per image from the first pixel any valid tap reads to the last, starts a multiple of 8 ----
-    const int n0 = fast_div_any(m0, a.PQ, a.mg_PQ), n1 = fast_div_any(m1 - 1, a.PQ, a.mg_PQ);
-    auto first_of = [&](int pq) {
-        const int p = fast_div_any(pq, a.Q, a.mg_Q), q = pq - p * a.Q;
-        const int row = p * a.stride - a.pad, col = q * a.stride - a.pad;
-        return (row < 0 ? 0 : row * a.W + min(max(col, 0), a.W - 1)) & ~7;
-    };
-    auto end_of = [&](int pq) {
-        const int p = fast_div_any(pq, a.Q, a.mg_Q), q = pq - p * a.Q;
-        const int row = p * a.stride - a.pad + (a.R - 1) * a.dil, col = q * a.stride - a.pad + (a.S - 1) * a.dil;
-        return row >= a.H ? a.HW : row * a.W + max(min(a.W - 1, col), -1) + 1;
-    };
-    const int lo0 = first_of(m0 - n0 * a.PQ);
-    const int len0 = max(((n1 > n0 ? end_of(a.PQ - 1) : end_of(m1 - 1 - n0 * a.PQ)) - lo0 + 7) & ~7, 0);
-    const int len_last = n1 > n0 ? max((end_of(m1 - 1 - n1 * a.PQ) + 7) & ~7, 0) : 0;
-    const int slots = len0 + (n1 > n0 ? (n1 - n0 - 1) * a.full8 + len_last : 0);
+    int n1;
+    const WindowRange range = tile_window(a, m0, m1, &n1);
+    const int n0 = range.n0, lo0 = range.lo0, len0 = range.len0;
 
     // ---- weights ------------------------------------------------------------------------------------------------
     if constexpr (!RAW) {
@@ -190,7 +177,6 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
         }
     }
     // ---- window ---------------------------------------------------------------------------------------------------
-    const WindowRange range{n0, lo0, len0, a.full8, slots, a.mg_full8};
     const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride};
     if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
     else window_from_pixels<NT, 4>(from, range, a.u16, a.mg_u16, smem + a.win_off, a.pitch, tid);
@@ -368,36 +354,6 @@ hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool ra
     return launch(kern, dim3((unsigned)(a.tiles_k * a.tiles_m)), dim3(NW * 64), lds, st, a);
 }
 
-// Slots (pixel records) of the windows of `mper` output pixels: the most over the first `tiles` tiles of the problem
-// (0: all of them; tile starts repeat within an image after PQ / gcd(mper, PQ) tiles).
-int max_slots(const ResidentProblem &r, int mper, int tiles)
-{
-    const GemmProblem &g = r.g;
-    const int PQ = g.PQ, Q = g.Q, W = r.W, HW = r.H * r.W, st = g.stride, pad = r.pad, dil = g.dil > 0 ? g.dil : 1;
-    auto first = [&](int pq) {
-        const int p = pq / Q, row = p * st - pad, col = (pq - p * Q) * st - pad;
-        return row < 0 ? 0 : (row * W + (col < 0 ? 0 : col > W - 1 ? W - 1 : col)) & ~7;
-    };
-    auto end = [&](int pq) {
-        const int p = pq / Q, row = p * st - pad + (g.R - 1) * dil, col = (pq - p * Q) * st - pad + (g.S - 1) * dil;
-        return row >= r.H ? HW : row * W + (col > W - 1 ? W - 1 : col < -1 ? -1 : col) + 1;
-    };
-    const int full8 = (end(PQ - 1) + 7) & ~7;
-    int most = 0, a = 0, count = 0;
-    for (long long m0 = 0; m0 < g.M && (m0 == 0 || a != 0) && (tiles == 0 || count < tiles); m0 += mper, a = (a + mper) % PQ, ++count) {
-        const int m1 = m0 + mper < g.M ? a + mper : a + (int)(g.M - m0);   // local end (may pass the image)
-        const int n1 = (m1 - 1) / PQ;
-        int s = ((n1 > 0 ? end(PQ - 1) : end(m1 - 1)) - first(a) + 7) & ~7;
-        if (s < 0) s = 0;
-        if (n1 > 0) {
-            const int t = (end(m1 - 1 - n1 * PQ) + 7) & ~7;
-            s += (n1 - 1) * full8 + (t > 0 ? t : 0);
-        }
-        if (s > most) most = s;
-    }
-    return most;
-}
-
 struct ResidentPlan {
     ResidentArgs a;
     int tile;
@@ -561,6 +517,34 @@ ResidentKey resident_key(const ResidentProblem &r)
 }
 
 }  // namespace
+
+int max_slots(const ResidentProblem &r, int mper, int tiles)
+{
+    const GemmProblem &g = r.g;
+    const int PQ = g.PQ, Q = g.Q, W = r.W, HW = r.H * r.W, st = g.stride, pad = r.pad, dil = g.dil > 0 ? g.dil : 1;
+    auto first = [&](int pq) {
+        const int p = pq / Q, row = p * st - pad, col = (pq - p * Q) * st - pad;
+        return row < 0 ? 0 : (row * W + (col < 0 ? 0 : col > W - 1 ? W - 1 : col)) & ~7;
+    };
+    auto end = [&](int pq) {
+        const int p = pq / Q, row = p * st - pad + (g.R - 1) * dil, col = (pq - p * Q) * st - pad + (g.S - 1) * dil;
+        return row >= r.H ? HW : row * W + (col > W - 1 ? W - 1 : col < -1 ? -1 : col) + 1;
+    };
+    const int full8 = (end(PQ - 1) + 7) & ~7;
+    int most = 0, a = 0, count = 0;
+    for (long long m0 = 0; m0 < g.M && (m0 == 0 || a != 0) && (tiles == 0 || count < tiles); m0 += mper, a = (a + mper) % PQ, ++count) {
+        const int m1 = m0 + mper < g.M ? a + mper : a + (int)(g.M - m0);   // local end (may pass the image)
+        const int n1 = (m1 - 1) / PQ;
+        int s = ((n1 > 0 ? end(PQ - 1) : end(m1 - 1)) - first(a) + 7) & ~7;
+        if (s < 0) s = 0;
+        if (n1 > 0) {
+            const int t = (end(m1 - 1 - n1 * PQ) + 7) & ~7;
+            s += (n1 - 1) * full8 + (t > 0 ? t : 0);
+        }
+        if (s > most) most = s;
+    }
+    return most;
+}
 
 bool resident_pick(const ResidentProblem &r, ResidentChoice *c)
 {

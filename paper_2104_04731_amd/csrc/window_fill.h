@@ -22,6 +22,32 @@ __device__ __forceinline__ void window_slot(const WindowRange &w, int s, int *n,
     }
 }
 
+// The ranges of a workgroup's pixels [m0, m1): per image from the first pixel any valid tap reads to the last, starts a
+// multiple of 8.  n1: its last image.
+template <typename A>
+__device__ __forceinline__ WindowRange tile_window(const A &a, int m0, int m1, int *n1_out)
+{
+    const int n0 = fast_div_any(m0, a.PQ, a.mg_PQ), n1 = fast_div_any(m1 - 1, a.PQ, a.mg_PQ);
+    auto first_of = [&](int pq) {
+        const int p = fast_div_any(pq, a.Q, a.mg_Q), q = pq - p * a.Q;
+        const int row = p * a.stride - a.pad, col = q * a.stride - a.pad;
+        return (row < 0 ? 0 : row * a.W + min(max(col, 0), a.W - 1)) & ~7;
+    };
+    auto end_of = [&](int pq) {
+        const int p = fast_div_any(pq, a.Q, a.mg_Q), q = pq - p * a.Q;
+        const int row = p * a.stride - a.pad + (a.R - 1) * a.dil, col = q * a.stride - a.pad + (a.S - 1) * a.dil;
+        return row >= a.H ? a.HW : row * a.W + max(min(a.W - 1, col), -1) + 1;
+    };
+    const int lo0 = first_of(m0 - n0 * a.PQ);
+    const int len0 = max(((n1 > n0 ? end_of(a.PQ - 1) : end_of(m1 - 1 - n0 * a.PQ)) - lo0 + 7) & ~7, 0);
+    const int len_last = n1 > n0 ? max((end_of(m1 - 1 - n1 * a.PQ) + 7) & ~7, 0) : 0;
+    *n1_out = n1;
+    return WindowRange{n0, lo0, len0, a.full8, len0 + (n1 > n0 ? (n1 - n0 - 1) * a.full8 + len_last : 0), a.mg_full8};
+}
+// Slots of the windows of `mper` output pixels: the most over the first `tiles` tiles of the problem (0: all of them; tile
+// starts repeat within an image after PQ / gcd(mper, PQ) tiles).
+int max_slots(const ResidentProblem &r, int mper, int tiles);
+
 // The tensor a window is filled from.
 struct WindowSource {
     const int8_t *src;
@@ -33,31 +59,100 @@ struct WindowSource {
 typedef unsigned long long u64_a1 __attribute__((aligned(1)));
 typedef unsigned u32_a1 __attribute__((aligned(1)));
 
-// Eight pixels of four channels (a channel per 64-bit value) -> eight records' dwords, `pitch` bytes apart.
-__device__ __forceinline__ void put_4x8(const unsigned long long (&v)[4], unsigned char *d, int pitch)
+// Four pixels of four channels (a channel per dword) -> four records' dwords, `pitch` bytes apart.
+__device__ __forceinline__ void put_4x4(unsigned r0, unsigned r1, unsigned r2, unsigned r3, unsigned char *d, int pitch)
 {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const unsigned r0 = (unsigned)(v[0] >> (32 * h)), r1 = (unsigned)(v[1] >> (32 * h));
-        const unsigned r2 = (unsigned)(v[2] >> (32 * h)), r3 = (unsigned)(v[3] >> (32 * h));
-        const unsigned lo01 = __builtin_amdgcn_perm(r1, r0, 0x05010400), hi01 = __builtin_amdgcn_perm(r1, r0, 0x07030602);
-        const unsigned lo23 = __builtin_amdgcn_perm(r3, r2, 0x05010400), hi23 = __builtin_amdgcn_perm(r3, r2, 0x07030602);
-        *reinterpret_cast<unsigned *>(d) = __builtin_amdgcn_perm(lo23, lo01, 0x05040100);
-        *reinterpret_cast<unsigned *>(d + pitch) = __builtin_amdgcn_perm(lo23, lo01, 0x07060302);
-        *reinterpret_cast<unsigned *>(d + 2 * pitch) = __builtin_amdgcn_perm(hi23, hi01, 0x05040100);
-        *reinterpret_cast<unsigned *>(d + 3 * pitch) = __builtin_amdgcn_perm(hi23, hi01, 0x07060302);
-        d += 4 * pitch;
-    }
+    const unsigned lo01 = __builtin_amdgcn_perm(r1, r0, 0x05010400), hi01 = __builtin_amdgcn_perm(r1, r0, 0x07030602);
+    const unsigned lo23 = __builtin_amdgcn_perm(r3, r2, 0x05010400), hi23 = __builtin_amdgcn_perm(r3, r2, 0x07030602);
+    *reinterpret_cast<unsigned *>(d) = __builtin_amdgcn_perm(lo23, lo01, 0x05040100);
+    *reinterpret_cast<unsigned *>(d + pitch) = __builtin_amdgcn_perm(lo23, lo01, 0x07060302);
+    *reinterpret_cast<unsigned *>(d + 2 * pitch) = __builtin_amdgcn_perm(hi23, hi01, 0x05040100);
+    *reinterpret_cast<unsigned *>(d + 3 * pitch) = __builtin_amdgcn_perm(hi23, hi01, 0x07060302);
 }
 
-// NCHW -> records.  Unit: 4 channels x 8 pixels, neighbouring lanes on neighbouring channel quads (a record's pieces fall
-// into different banks; the planes' lines are shared by the units that follow in the same workgroup).  cq: channel quads
-// of a record; bytes past the last channel are zero.  (Bound by the loads where several waves share a SIMD -- without its
-// LDS writes it takes as long -- and by the instruction count of a lone wave, hence the short path: one image, nothing
-// past the tensor's end, whole quads only: scalar bases and one 32-bit offset per unit.)
+// Eight pixels of four channels (a channel per 64-bit value).
+__device__ __forceinline__ void put_4x8(const unsigned long long (&v)[4], unsigned char *d, int pitch)
+{
+    put_4x4((unsigned)v[0], (unsigned)v[1], (unsigned)v[2], (unsigned)v[3], d, pitch);
+    put_4x4((unsigned)(v[0] >> 32), (unsigned)(v[1] >> 32), (unsigned)(v[2] >> 32), (unsigned)(v[3] >> 32), d + 4 * pitch, pitch);
+}
+
+// The form for windows of many pixels: a unit is 4 channels x 16 pixels, four lanes take 64 bytes of a channel row in 16-byte
+// loads, the next four the next quad's.  What decides there is how many cache lines a load instruction names: one whose lanes
+// are a channel plane apart each (the form below) takes 20 to 65 cycles, one of these 14 (64 images 56 x 56, 64 -> 64: 18.0 -> 15.9 us;
+// 16 images 72 x 56 x 56 -> 96, stride 2: 9.7 -> 8.1).  The LDS stores of four lanes meet in the same banks, which costs
+// about what the loads do.  false, nothing done: a load could pass the tensor's end.
+template <int NT, int B>
+__device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, unsigned char *win, int pitch, int tid)
+{
+    const int8_t *const src = t.src + (long long)w.n0 * t.img_bytes;
+    const long long left = t.src_bytes - (long long)w.n0 * t.img_bytes;
+    const bool padded = t.C1 + 1 != 4 * cq;
+    // (the last image's rows of the last channels, rounded up to 16 pixels, are the last bytes any unit asks for)
+    const int over = w.slots - w.len0, images = over > 0 ? fast_div_any(over - 1, w.full8, w.mg_full8) + 1 : 0;
+    const int last_end = images ? over - (images - 1) * w.full8 : w.lo0 + w.len0;
+    const bool inside = (long long)images * t.img_bytes + (long long)t.C1 * t.HW + last_end + 8 <= left;
+    if (!inside) return false;
+    constexpr int U = B / 2;   // units per thread and round of loads
+    const int units = ((w.slots + 63) >> 6) * 4 * cq;
+    for (int u0 = tid; u0 < units; u0 += NT * U) {
+        v4i v[U][4];
+        int at[U], c4[U];
+#pragma unroll
+        for (int b = 0; b < U; ++b) {
+            const int u = u0 + b * NT, rest = u >> 2, run = fast_div_any(rest, cq, mg_cq);
+            c4[b] = (rest - run * cq) * 4;
+            at[b] = u < units ? (run * 4 + (u & 3)) * 16 : w.slots;
+            if (at[b] < w.slots) {
+                int n, lin;
+                window_slot(w, at[b], &n, &lin);
+                const int8_t *const p = src + (long long)(n - w.n0) * t.img_bytes + lin;
+                const int ahead = at[b] < w.len0 ? w.len0 - at[b] : w.full8 - lin;   // slots of this image's range from here on
+                if (ahead >= 16 || at[b] + 8 >= w.slots) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) __builtin_memcpy(&v[b][i], p + (long long)min(c4[b] + i, t.C1) * t.HW, 16);
+                } else {   // the other eight pixels begin the next image
+                    const int8_t *const p2 = src + (long long)(n + 1 - w.n0) * t.img_bytes;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const long long c = (long long)min(c4[b] + i, t.C1) * t.HW;
+                        unsigned long long x[2];
+                        x[0] = *reinterpret_cast<const u64_a1 *>(p + c);
+                        x[1] = *reinterpret_cast<const u64_a1 *>(p2 + c);
+                        __builtin_memcpy(&v[b][i], x, 16);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < U; ++b)
+            if (at[b] < w.slots) {
+                if (padded)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c4[b] + i > t.C1) v[b][i] = v4i{0, 0, 0, 0};
+                unsigned char *const d = win + at[b] * pitch + c4[b];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < 2 || at[b] + 8 < w.slots)
+                        put_4x4((unsigned)v[b][0][e], (unsigned)v[b][1][e], (unsigned)v[b][2][e], (unsigned)v[b][3][e], d + 4 * e * pitch, pitch);
+            }
+    }
+    return true;
+}
+
+// NCHW -> records; bytes past the last channel are zero.  cq: channel quads of a record.  The form for few pixels: a unit is 4
+// channels x 8 pixels, neighbouring lanes on neighbouring channel quads (a record's pieces fall into different banks), no
+// lane without work.  (Bound by the instruction count of a lone wave, hence the short path: one image, nothing past the
+// tensor's end, whole quads only: scalar bases and one 32-bit offset per unit.)  The other form from 128 pixels on, or where
+// its runs of 64 are four fifths full, if it has work for every thread: below, its idle lanes cost more than its loads save
+// (2 images 292 x 20 x 20 -> 66, 88 pixels: 8.2 us, 9.4 with it; 15 images 256 x 7 x 7 -> 26: 9.4 and 9.0; 8 images 64 x 7 x 7 ->
+// 130: 4.7 and 4.9).
 template <int NT, int B>
 __device__ __forceinline__ void window_from_nchw(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, unsigned char *win, int pitch, int tid)
 {
+    const int runs = (w.slots + 63) >> 6;
+    if ((w.slots >= 128 || w.slots * 5 >= runs * 256) && runs * 4 * cq >= NT && window_wide_nchw<NT, B>(t, w, cq, mg_cq, win, pitch, tid)) return;
     const int units = cq * (w.slots >> 3);
     const long long img0 = (long long)w.n0 * t.img_bytes;
     if (w.slots == w.len0 && t.C1 + 1 == 4 * cq && img0 + (long long)t.C1 * t.HW + w.lo0 + w.slots <= t.src_bytes) {
