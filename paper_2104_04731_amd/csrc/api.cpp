@@ -390,7 +390,8 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
         *n = Route{TWO_STAGE, {}, 0, 0};
         auto consider = [&](int how, int cb, int depth, bool raw, double extra) {
             ResidentChoice c;
-            const ResidentProblem r = resident_problem(d, pl, cb, depth, raw, nhwc, dil, nullptr, nullptr, out);
+            ResidentProblem r = resident_problem(d, pl, cb, depth, raw, nhwc, dil, nullptr, nullptr, out);
+            r.kept = wt_is_packed;
             if (!resident_pick(r, &c)) return;
             const double us = c.us + extra;
             if (us < best) {

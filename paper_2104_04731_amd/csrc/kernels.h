@@ -80,6 +80,7 @@ struct ResidentProblem {
     int pixel_bytes;
     long long img_bytes;
     int raw_weights;     // g.wq is KCRS as it came (3 x 3 only), not in depth order
+    int kept;            // the weights were rewritten before this call (which estimates apply)
 };
 struct ResidentChoice {
     int tile, mper;   // mper: output pixels of a workgroup

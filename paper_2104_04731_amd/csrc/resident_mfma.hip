@@ -42,8 +42,9 @@ struct ResidentArgs {
     long long img_bytes, src_bytes;
     int zero_off, win_off, tab_off;  // LDS byte offsets (the weight tile is at 0)
     int tiles_k, tiles_m, mper;    // mper: output pixels of a workgroup
+    int nblk, parts;               // blocks of pixels that a wave multiplies at a time; waves that share the depth of each (1: none do)
     int stream_out;                // NKPQ result with non-temporal stores
-    unsigned mg_PQ, mg_Q, mg_tiles_k, mg_c16q, mg_cq, mg_full8, mg_g16, mg_S, mg_R, mg_u16;
+    unsigned mg_nblk, mg_parts, mg_PQ, mg_Q, mg_tiles_k, mg_c16q, mg_cq, mg_full8, mg_g16, mg_S, mg_R, mg_u16;
     int cq, u16;                   // channel quads / 16-byte units of a record that are loaded
 };
 
@@ -139,13 +140,35 @@ __device__ __forceinline__ void res_store(const ResidentArgs &a, const v16i (&ac
     }
 }
 
+// One piece of a block (rows 8g + 4*(lane/32) + 0..3), summed up from the depth parts: row k of the result onwards, pixel m.
+__device__ __forceinline__ void res_store_piece(const ResidentArgs &a, const v4i &t, int k, int m, int m1, int n0)
+{
+    const int left = a.K - k;
+    if (m >= m1 || left <= 0) return;
+    if (a.out_nhwc) {
+        int32_t *px = a.out + (size_t)m * a.K + k;
+        if ((a.K & 3) == 0 && (reinterpret_cast<uintptr_t>(a.out) & 15) == 0) *reinterpret_cast<v4i *>(px) = t;
+        else
+            for (int v = 0; v < 4; ++v)
+                if (v < left) px[v] = t[v];
+    } else {
+        const int n = fast_div_any(m, a.PQ, a.mg_PQ), pq = m - n * a.PQ;
+        int32_t *px = a.out + ((size_t)n * a.K + k) * a.PQ + pq;
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (v < left) px[(size_t)v * a.PQ] = t[v];
+    }
+}
+
 // TK: output channels of a workgroup, NW: waves (each multiplies all of the channels), FM: 32-pixel blocks a wave
 // multiplies at a time; SRC: ResSource; UNI: a 64-byte step of depth lies within one tap (and channel block);
+// SPLIT: a workgroup has fewer blocks of pixels than waves, and several waves share the depth of each (a form of its own: in the
+// other one's code the smallest launches took half a microsecond longer).
 // RAW: the weights are KCRS (3 x 3), turned into depth order (tap, channel padded to 16) on their way into LDS.
 // The 64-channel tile of 8 waves keeps two output blocks' sums and the addresses of a whole tap in registers: at two of its
 // workgroups per compute unit it spilled, at one it does not, and its LDS rarely leaves room for two (64 images 56 x 56,
 // 64 -> 64, kept weights: 18.0 -> 17.4 us; 151 images 28 x 28, 128 -> 458: 116 -> 105).
-template <int TK, int NW, int FM, int SRC, bool UNI, bool RAW>
+template <int TK, int NW, int FM, int SRC, bool UNI, bool RAW, bool SPLIT>
 __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) conv_resident_kernel(const ResidentArgs a)
 {
     constexpr int NT = NW * 64, FK = TK / 32;
@@ -238,7 +261,24 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
     const int a0 = (lane & 31) * 64 + ((half ^ rswz) << 4), a1 = (lane & 31) * 64 + (((2 + half) ^ rswz) << 4);
     constexpr int NE = UNI ? 1 : 2;          // table entries of a step that a lane looks at
     constexpr int NQ = 2 * FK * FM, NI = 2 * (FK + FM);
-    for (int blk = wave; m0 + blk * FM * 32 < m1; blk += NW) {
+    int blk = wave, j0 = 0, j1 = a.steps, part = 0;
+    if constexpr (SPLIT) {
+        part = fast_div(wave, a.mg_nblk);
+        blk = part < a.parts ? wave - part * a.nblk : 1 << 20;
+        const int per = fast_div(a.steps + a.parts - 1, a.mg_parts);
+        j0 = min(part * per, a.steps), j1 = min(j0 + per, a.steps);
+    }
+    v16i acc[FK][FM];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < FK; ++i)
+#pragma unroll
+            for (int j = 0; j < FM; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+    };
+    if constexpr (SPLIT) clear();
+    for (; m0 + blk * FM * 32 < m1; blk += NW) {
         const int mw = m0 + blk * FM * 32;
         // the lane's pixels: their records (tap (0, 0), first chunk) and which taps are in the image
         int base[FM];
@@ -256,13 +296,7 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
             for (int r = 0; r < a.R; ++r) mk |= ((unsigned)(row + r * a.dil) < (unsigned)a.H ? cm : 0u) << (r * a.S);
             mask[f] = mk;
         }
-        v16i acc[FK][FM];
-#pragma unroll
-        for (int i = 0; i < FK; ++i)
-#pragma unroll
-            for (int j = 0; j < FM; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+        if constexpr (!SPLIT) clear();
         // The fragments of step j+1 are read into a second register set while step j multiplies, a few behind every
         // MFMA: a wave issues in order, so a block of reads and addresses would stand between the MFMAs of two steps.
         v4i af[2][2][FK], bf[2][2][FM];
@@ -283,15 +317,15 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
 #pragma unroll
             for (int h = 0; h < NE; ++h) te[h] = e[2 * h];
         };
-        read_table(0);
+        read_table(j0);
 #pragma unroll
-        for (int t = 0; t < NI; ++t) read_item(t, smem, af[0], bf[0]);
-        read_table(1);
-        const unsigned char *nxt = smem + STEP;
-        for (int j = 0; j < a.steps; j += 2) {
+        for (int t = 0; t < NI; ++t) read_item(t, smem + j0 * STEP, af[0], bf[0]);
+        read_table(j0 + 1);
+        const unsigned char *nxt = smem + (j0 + 1) * STEP;
+        for (int j = j0; j < j1; j += 2) {
 #pragma unroll
             for (int par = 0; par < 2; ++par) {
-                if (j + par < a.steps) {
+                if (j + par < j1) {
 #pragma unroll
                     for (int q = 0; q < NQ; ++q) {
                         const int h = q / (FK * FM), i = q / FM % FK, f = q % FM;
@@ -307,7 +341,30 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
                 }
             }
         }
-        res_store<FK, FM>(a, acc, k0, mw, m1, n0, lane);
+        if constexpr (SPLIT) break;
+        else res_store<FK, FM>(a, acc, k0, mw, m1, n0, lane);
+    }
+    if constexpr (!SPLIT) return;
+
+    // ---- the parts of a block meet in LDS (nothing there is read any more): part p adds up and stores every parts-th piece ----
+    constexpr int NP = FK * FM * 4;
+    res_barrier();
+    v4i *const xch = reinterpret_cast<v4i *>(smem) + lane;
+    const int b = wave - part * a.nblk, mw = m0 + b * FM * 32;
+    if (part < a.parts)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int i = p / (4 * FM), f = p / 4 % FM, g = p % 4;
+            xch[((b * NP + p) * a.parts + part) * 64] = v4i{acc[i][f][4 * g], acc[i][f][4 * g + 1], acc[i][f][4 * g + 2], acc[i][f][4 * g + 3]};
+        }
+    res_barrier();
+    if (part >= a.parts || mw >= m1) return;
+    for (int p = part; p < NP; p += a.parts) {
+        const v4i *at = xch + (b * NP + p) * a.parts * 64;
+        v4i t = at[0];
+        for (int d = 1; d < a.parts; ++d) t += at[d * 64];
+        const int i = p / (4 * FM), f = p / 4 % FM, g = p % 4;
+        res_store_piece(a, t, k0 + i * 32 + g * 8 + 4 * half, mw + f * 32 + (lane & 31), m1, n0);
     }
 }
 
@@ -334,17 +391,26 @@ template <int TK, int NW, int FM>
 hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool raw, size_t lds, hipStream_t st)
 {
     void (*kern)(ResidentArgs);
-    static bool raised[8];
-    const int which = pixels * 4 + uni * 2 + raw;
+    constexpr bool CAN_SPLIT = TK == 32 && FM == 1;
+    static bool raised[16];
+    const int which = (a.parts > 1) * 8 + pixels * 4 + uni * 2 + raw;
     switch (which) {
-        case 0: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, false>; break;
-        case 1: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, true>; break;
-        case 2: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, false>; break;
-        case 3: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, true>; break;
-        case 4: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, false>; break;
-        case 5: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, true>; break;
-        case 6: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, false>; break;
-        default: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, true>; break;
+        case 0: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, false, false>; break;
+        case 1: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, true, false>; break;
+        case 2: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, false, false>; break;
+        case 3: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, true, false>; break;
+        case 4: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, false, false>; break;
+        case 5: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, true, false>; break;
+        case 6: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, false, false>; break;
+        case 7: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, true, false>; break;
+        case 8: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, false, CAN_SPLIT>; break;
+        case 9: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, true, CAN_SPLIT>; break;
+        case 10: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, false, CAN_SPLIT>; break;
+        case 11: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, true, CAN_SPLIT>; break;
+        case 12: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, false, CAN_SPLIT>; break;
+        case 13: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, true, CAN_SPLIT>; break;
+        case 14: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, false, CAN_SPLIT>; break;
+        default: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, true, CAN_SPLIT>; break;
     }
     if (lds > 64 * 1024 && !raised[which]) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -363,9 +429,22 @@ struct ResidentPlan {
 
 // LDS of a workgroup: the weight tile and one step more (read behind the last step, never used), a record of zeros, the
 // window and a chunk more, the depth table.
-long long resident_lds(const ResTile &d, int steps, bool uni, long long slots, int pitch)
+long long resident_lds(const ResTile &d, int steps, bool uni, long long slots, int pitch, int parts)
 {
-    return ((long long)steps + 1) * d.tk * 64 + 64 + slots * pitch + 64 + ((long long)steps * (uni ? 8 : 32) + 15) / 16 * 16;
+    const long long all = ((long long)steps + 1) * d.tk * 64 + 64 + slots * pitch + 64 + ((long long)steps * (uni ? 8 : 32) + 15) / 16 * 16;
+    const long long meeting = parts > 1 ? (long long)d.nw * d.tk * d.fm * 128 : 0;   // (the parts' sums, in place of all that)
+    return all > meeting ? all : meeting;
+}
+// Waves that share the depth of a block where a workgroup has fewer blocks than waves: from 16 steps of depth on (at 9 the
+// meeting costs what the shorter chains save: 64 images 49 x 9 x 9 -> 256, stride 2: 5.4 -> 6.0 us; at 36, 3 images 256 x 14 x
+// 14 -> 147: 7.4 -> 6.3).
+int resident_parts(const ResTile &d, int mper, int steps)
+{
+    const int nblk = (mper + 32 * d.fm - 1) / (32 * d.fm);
+    int parts = 1;
+    if (d.tk == 32 && d.fm == 1 && steps >= 16)
+        while (parts * 2 * nblk <= d.nw) parts *= 2;
+    return parts;
 }
 constexpr long long RES_LDS_LIMIT = 160 * 1024;
 
@@ -443,8 +522,12 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     }
     out->uni = sh.uni;
     if ((mper / PQ + 2) * PQ * g.K * 4 >= (1LL << 32)) return false;   // 32-bit byte offsets from the workgroup's first image
+    a.nblk = (mper + 32 * d.fm - 1) / (32 * d.fm);
+    a.parts = resident_parts(d, mper, a.steps);
+    a.mg_nblk = magic(a.nblk);
+    a.mg_parts = magic(a.parts);
     const long long slots = max_slots(r, mper, 0);
-    const long long wts = ((long long)a.steps + 1) * d.tk * 64, lds = resident_lds(d, a.steps, sh.uni, slots, a.pitch);
+    const long long wts = ((long long)a.steps + 1) * d.tk * 64, lds = resident_lds(d, a.steps, sh.uni, slots, a.pitch, a.parts);
     if (lds > RES_LDS_LIMIT || (long long)((g.R - 1) * r.W + g.S - 1) * dil * a.pitch + a.C16 > (1LL << 30)) return false;
     // whole 64-byte sectors per store instruction: kept out of the caches on the way (64 images 56 x 56, 64 -> 64: 20.3 ->
     // 18.8 us; planes that start anywhere else come out up to twice as slow that way)
@@ -470,7 +553,8 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
 }
 
 
-// Launch time in microseconds, fitted to 37900 measured launches of 4900 layers (every tile, 2 to 5 pixel counts each; a third
+// Launch time in microseconds where the call brings raw weights: what the choice between stored rewrites and this kernel was
+// fitted with, from 37900 measured launches of 4900 layers (every tile, 2 to 5 pixel counts each; a third
 // of the layers held back).  A launch; per round of workgroups that fit the chip the chain of MFMAs of one wave and the
 // rounds of window loads; for the busiest compute unit its MFMAs and the bytes in and out; for the whole chip all
 // workgroups' bytes, which share the memory system (per: workgroups per compute unit -- without it a layer of 200 channels and
@@ -479,11 +563,11 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
 // the registers in rounds of loads of their own, more than twice as long where the rows of 9 C bytes do not start on dwords.
 // Near each layer's best launch, on the layers held back: mean error 5 %; by channels, weights and workgroups no group is off
 // by more than 4 %, but for kept weights of 200 channels and more in several rounds (9 % low).
-double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile, int mper, int slots)
+double resident_cost_given(const ResidentProblem &r, const ResidentShape &sh, int tile, int mper, int slots)
 {
     const GemmProblem &g = r.g;
     const ResTile &d = kResTiles[tile];
-    const long long lds = resident_lds(d, sh.steps, sh.uni, slots, sh.pitch);
+    const long long lds = resident_lds(d, sh.steps, sh.uni, slots, sh.pitch, 1);
     if (lds > RES_LDS_LIMIT) return 1e300;
     const long long wgs = (long long)((g.K + d.tk - 1) / d.tk) * ((g.M + mper - 1) / mper);
     long long fit = RES_LDS_LIMIT / lds;              // workgroups sharing a compute unit
@@ -504,6 +588,47 @@ double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile
         t += rounds * (0.706 + (r.C % 4 ? 0.638 : 0.272) * loads);
     }
     return t;
+}
+
+// The same for kept weights, fitted per tile to 60000 measured launches of 13400 layers (two pixel counts each; a third of the
+// layers held back: mean error 5 to 6 %, 8 with the formula above, which knows neither depth parts nor the wide fill).  A launch; per round of workgroups that
+// fit the chip its fixed part, the chain of MFMAs of one wave and the trips of window loads, in either form of the fill; for the
+// busiest compute unit its MFMAs; for the whole chip the bytes of all windows, weight tiles and results (planes of whole 64-byte
+// sectors, others), which share the memory system; the meeting of depth parts; from the second round on window and weights once
+// more, because a round's loads queue behind the results of the round before. 
+struct ResidentFit {
+    double launch, round, chain, narrow, wide, mfma, window, weights, aligned, other, parts, window2, weights2;
+};
+constexpr ResidentFit kResFit[] = {
+    {4.48, 0, 0.0237, 0, 0.379, 0.0139, 2.95e-05, 1.8e-06, 1.93e-05, 2.8e-05, 0, 7.09e-06, 1.41e-05},
+    {3.64, 0.459, 0.0254, 0.47, 0.829, 0.00978, 1.94e-05, 4.04e-06, 2.46e-05, 3.65e-05, 0, 0, 1.05e-05},
+    {3.42, 0.26, 0.0364, 0.682, 1.02, 0.0118, 1.3e-05, 9.74e-06, 2.79e-05, 4.16e-05, 0.78, 0, 8.3e-06},
+    {4.39, 0, 0.0268, 0.299, 0.8, 0.0111, 1.77e-05, 5.95e-06, 2.72e-05, 3.91e-05, 0, 9.25e-06, 1.52e-05},
+    {3.26, 0.891, 0.0197, 0.502, 0.756, 0.021, 1.9e-05, 9.3e-06, 1.82e-05, 3.14e-05, 0.699, 0, 7.95e-06},
+};
+double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile, int mper, int slots)
+{
+    const GemmProblem &g = r.g;
+    const ResTile &d = kResTiles[tile];
+    const ResidentFit &f = kResFit[tile];
+    const int parts = resident_parts(d, mper, sh.steps);
+    const long long lds = resident_lds(d, sh.steps, sh.uni, slots, sh.pitch, parts);
+    if (lds > RES_LDS_LIMIT) return 1e300;
+    const long long wgs = (long long)((g.K + d.tk - 1) / d.tk) * ((g.M + mper - 1) / mper);
+    long long fit = RES_LDS_LIMIT / lds;              // workgroups sharing a compute unit
+    if (fit > d.fit) fit = d.fit;
+    const double per = wgs / 256.0;
+    const double ncu = per <= (double)fit ? (double)((wgs + 255) / 256) : per + 0.4;
+    const double rounds = (double)((wgs + 256 * fit - 1) / (256 * fit));
+    const int blocks = (mper + 32 * d.fm - 1) / (32 * d.fm), runs = (slots + 63) / 64;
+    const double chain = (double)((blocks + d.nw - 1) / d.nw) * d.fm * (d.tk / 32) * 2 * sh.steps / parts;
+    const bool wide = (slots >= 128 || slots * 5 >= runs * 256) && runs * sh.C16 >= d.nw * 64;   // (window_from_nchw)
+    const double trips = wide ? (double)((runs * sh.C16 + d.nw * 128 - 1) / (d.nw * 128)) : (double)((slots / 8 * (sh.C16 / 4) + d.nw * 256 - 1) / (d.nw * 256));
+    const double mfma = d.tk / 32 * d.fm * blocks * 2.0 * sh.steps / 4, window = (double)slots * sh.C16, weights = (double)sh.steps * d.tk * 64;
+    const double result = 4.0 * d.tk * mper;
+    return f.launch + rounds * (f.round + f.chain * chain + (wide ? f.wide : f.narrow) * trips + (parts > 1 ? f.parts : 0)) + f.mfma * ncu * mfma +
+           per * (f.window * window + f.weights * weights + (g.PQ % 16 == 0 ? f.aligned : f.other) * result) +
+           (rounds - 1) * (f.window2 * window + f.weights2 * weights);
 }
 
 struct ResidentKey {
@@ -567,7 +692,7 @@ bool resident_pick(const ResidentProblem &r, ResidentChoice *c)
     for (int m : sizes) add(m);
     for (int t = 0; t < kNumResTiles; ++t)
         for (int i = 0; i < n; ++i) {
-            const Cand x{resident_cost(r, sh, t, mpers[i], slots_of[i]), t, mpers[i]};
+            const Cand x{(r.kept ? resident_cost : resident_cost_given)(r, sh, t, mpers[i], slots_of[i]), t, mpers[i]};
             for (int k = 0; k < 3; ++k)
                 if (x.cost < best[k].cost) {
                     for (int j = 2; j > k; --j) best[j] = best[j - 1];

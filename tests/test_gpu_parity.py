@@ -1355,6 +1355,39 @@ def test_resident_every_tile(lib, cfg):
     assert not small or {(t, many, r, h) for t in range(len(lib.resident_tiles())) for many in (False, True) for r in raw for h in (False, True)} <= ran
 
 
+# Workgroups with fewer blocks of pixels than waves, deep enough (16 steps of depth) for several waves to share a block: parts of
+# unequal depth, a last tile with fewer blocks than the others, channels that fill no piece, both results, every weight form.
+RESIDENT_PARTS = [
+    ConvShape("rp-c256", 2, 256, 7, 9, 33, 3, 3, 1, 1), ConvShape("rp-c113-s2", 3, 113, 14, 11, 30, 3, 3, 2, 1), ConvShape("rp-1x1", 3, 1024, 5, 7, 40, 1, 1, 1, 0),
+    ConvShape("rp-5x5", 1, 41, 9, 12, 64, 5, 5, 1, 2), ConvShape("rp-one-pixel", 1, 300, 3, 3, 5, 3, 3, 1, 0), ConvShape("rp-dil2", 1, 130, 11, 10, 34, 3, 3, 1, 2),
+]
+
+
+@pytest.mark.parametrize("cfg", RESIDENT_PARTS, ids=lambda c: c.name)
+def test_resident_depth_parts(lib, cfg):
+    dil = 2 if cfg.name == "rp-dil2" else 1
+    x = uniform_int8(993, (cfg.N, cfg.C, cfg.H, cfg.W)); w = uniform_int8(994, (cfg.K, cfg.C, cfg.R, cfg.S))
+    want = direct.conv2d_int8_dilated(x, w, cfg.stride, cfg.pad, dil)
+    want_h = layouts.unpack_nhwc(want)
+    dx, dxh = dev(x), dev(np.ascontiguousarray(x.transpose(0, 2, 3, 1)))
+    weights = [(cb, lib.pack_weights(dev(w), lib.LAYOUT_PACKED, cb)) for cb in (16, 64)] + [(0, dev(w))]
+    ran = 0
+    for tile, (rows, cols, threads) in enumerate(lib.resident_tiles()):
+        for pixels in (32, 64, 96, 128):
+            for cb, wq in weights:
+                for nhwc in (False, True):
+                    if not lib.resident_applies(cfg.dims(), cb, tile, pixels, dil, nhwc):
+                        continue
+                    buf = torch.full((want.size + 128,), -7, dtype=torch.int32, device=DEV)
+                    out = buf[64:64 + want.size].view(want_h.shape if nhwc else want.shape)
+                    lib.conv2d_int8_resident(cfg.dims(), dxh if nhwc else dx, wq, out, cb, tile, pixels, dil, nhwc)
+                    got = host(buf)
+                    assert np.array_equal(got[64:-64].reshape(out.shape), want_h if nhwc else want), (tile, pixels, cb, nhwc)
+                    assert (got[:64] == -7).all() and (got[-64:] == -7).all(), (tile, pixels, cb, nhwc)
+                    ran += 1
+    assert ran > 20
+
+
 # The band kernel on the network's own tensor, asked for: also one output row per band with six blocks of columns, and a grid
 # larger than the estimate's.
 BAND_FORCED = BAND_DIRECT_SHAPES + [ConvShape("band-c256-w71", 1, 256, 3, 71, 128, 3, 3, 1, 1), ConvShape("band-c217", 3, 217, 10, 10, 61, 3, 3, 1, 1),
