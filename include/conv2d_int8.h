@@ -180,12 +180,16 @@ size_t conv2d_int8_tile_lds_bytes(const conv_desc_t *desc, int layout, int cb, i
  * [N][H][W][C], out [N][P][Q][K].  wt_cb = 0: wt is KCRS as it is (3x3 kernels only); else the output of pack_weights
  * (PACKED, wt_cb), 16-byte aligned.  dilation >= 1; P, Q as for conv2d_int8_dilated_direct.  pixels: a multiple of 32,
  * 32 to 1024.  tile = CONV_TILE_BAND with pixels = 0 is the band kernel on the NCHW tensor (nhwc 0, wt_cb 64 -- or blocks
- * of 64 in all -- dilation 1, stride 1, three taps per kernel row).  A pair whose weights and input window do not fit one compute unit's LDS: CONV_ERR_UNSUPPORTED, which is
+ * of 64 in all -- dilation 1, stride 1, three taps per kernel row).
+ * tile = CONV_TILE_STREAM + t: the stage that keeps the input window of `pixels` pixels in LDS, 64 channels at a time, and
+ * streams the weights past it (wt_cb 16, 32 or a multiple of 64; pixels from 1 to the tile's cols).  A pair whose weights and input window do not fit one compute unit's LDS: CONV_ERR_UNSUPPORTED, which is
  * also what _applies says of it (host only). */
 int conv2d_int8_resident(const conv_desc_t *desc, int dilation, int nhwc, const int8_t *in, const int8_t *wt, int wt_cb,
                          int32_t *out, int tile, int pixels, void *stream);
 int conv2d_int8_resident_applies(const conv_desc_t *desc, int dilation, int nhwc, int wt_cb, int tile, int pixels);
-/* rows = output channels of a workgroup, cols = pixels a wave multiplies at a time; past the last tile: CONV_ERR_INVALID_ARG */
+/* rows = output channels of a workgroup, cols = pixels a wave multiplies at a time (from CONV_TILE_STREAM on: pixels of a
+ * workgroup at most); past the last tile: CONV_ERR_INVALID_ARG */
+#define CONV_TILE_STREAM 256
 int conv2d_int8_resident_tile_info(int tile, int *rows, int *cols, int *threads);
 
 /* Which stage a call takes (host only), for tensors that start on 64 bytes. */
@@ -196,7 +200,9 @@ typedef enum {
     CONV_STAGE_RESIDENT_RAW = 2,     /* ... on KCRS weights, brought into depth order on their way into LDS */
     CONV_STAGE_RESIDENT_REWRITE = 3, /* ... on weights that a launch of its own rewrites first */
     CONV_STAGE_BAND = 4,             /* the band kernel (CONV_TILE_BAND) on the NCHW tensor as it is */
-    CONV_STAGE_AS_IS = 5             /* IMPLICIT's kernels; for NHWC also the 1x1 matrix product */
+    CONV_STAGE_AS_IS = 5,            /* IMPLICIT's kernels; for NHWC also the 1x1 matrix product */
+    CONV_STAGE_STREAM = 6,           /* CONV_TILE_STREAM's stage on weights as they are given */
+    CONV_STAGE_STREAM_REWRITE = 7    /* ... on weights that a launch of its own rewrites first */
 } conv_stage_t;
 /* entry: which call (conv2d_int8, _ex, _nhwc, _dilated, _dilated_direct); layout, cb, wt_is_packed, dilation: its arguments,
  * those it does not have are ignored.  tile, pixels: those of conv2d_int8_resident, -1 and 0 for the other stages. */

@@ -17,9 +17,11 @@ from . import build as _build
 OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_OVERFLOW_RISK, ERR_WORKSPACE, ERR_DEVICE = range(6)
 LAYOUT_AUTO, LAYOUT_PACKED, LAYOUT_IM2COL, LAYOUT_PAD_ONLY, LAYOUT_IMPLICIT, LAYOUT_IMAGE_PACK = range(6)
 TILE_BAND = -2   # CONV_TILE_BAND
+TILE_STREAM = 256   # CONV_TILE_STREAM: the first of these tiles
 ENTRY_ONE_SHOT, ENTRY_EX, ENTRY_NHWC, ENTRY_DILATED, ENTRY_DILATED_DIRECT = range(5)
-STAGE_STORED, STAGE_RESIDENT, STAGE_RESIDENT_RAW, STAGE_RESIDENT_REWRITE, STAGE_BAND, STAGE_AS_IS = range(6)
-STAGE_NAMES = ("stored rewrites", "resident", "resident, raw weights", "resident, weights rewritten first", "band on NCHW", "as is")
+STAGE_STORED, STAGE_RESIDENT, STAGE_RESIDENT_RAW, STAGE_RESIDENT_REWRITE, STAGE_BAND, STAGE_AS_IS, STAGE_STREAM, STAGE_STREAM_REWRITE = range(8)
+STAGE_NAMES = ("stored rewrites", "resident", "resident, raw weights", "resident, weights rewritten first", "band on NCHW", "as is", "streamed weights",
+               "streamed weights, rewritten first")
 LAYOUT_NAMES = {LAYOUT_AUTO: "auto", LAYOUT_PACKED: "packed", LAYOUT_IM2COL: "im2col",
                 LAYOUT_PAD_ONLY: "pad_only", LAYOUT_IMPLICIT: "implicit",
                 LAYOUT_IMAGE_PACK: "image_pack"}
@@ -280,6 +282,14 @@ def resident_tiles():
     out, v = [], [ctypes.c_int() for _ in range(3)]
     while load().conv2d_int8_resident_tile_info(len(out), *map(ctypes.byref, v)) == OK:
         out.append(tuple(x.value for x in v))
+    return out
+
+
+def stream_tiles():
+    """{tile: (output channels, most pixels, threads)} of the tiles from TILE_STREAM on."""
+    out, v = {}, [ctypes.c_int() for _ in range(3)]
+    while load().conv2d_int8_resident_tile_info(TILE_STREAM + len(out), *map(ctypes.byref, v)) == OK:
+        out[TILE_STREAM + len(out)] = tuple(x.value for x in v)
     return out
 
 

@@ -307,6 +307,8 @@ int run_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t st)
     return rc == CONV_OK ? launch_choice(g, c, st) : rc;
 }
 
+bool is_stream_tile(int tile) { return tile >= CONV_TILE_STREAM && tile < CONV_TILE_STREAM + stream_num_tiles(); }
+
 // ---- two-stage path or the GEMM stage that blocks the channels itself (resident_mfma.hip) -----------------------------
 // Estimated times in microseconds.  Two-stage, fitted per kind of call to 19000 calls of 5800 layers in graphs (a third held
 // back; mean error 3 % where the band kernel runs, 5 to 6 % for the general one, 7 to 9 % unrolled and from NHWC): the launches, the
@@ -344,12 +346,14 @@ enum RouteHow : int {
     DIRECT_AS_IS = CONV_STAGE_RESIDENT,
     DIRECT_RAW = CONV_STAGE_RESIDENT_RAW,
     DIRECT_REWRITE = CONV_STAGE_RESIDENT_REWRITE,
-    DIRECT_BAND = CONV_STAGE_BAND
+    DIRECT_BAND = CONV_STAGE_BAND,
+    DIRECT_STREAM = CONV_STAGE_STREAM,
+    DIRECT_STREAM_REWRITE = CONV_STAGE_STREAM_REWRITE
 };
 struct Route {
-    int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones, band kernel on packed ones
+    int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones, band kernel on packed ones, stream kernel on packed / rewritten ones
     ResidentChoice pick;
-    int cb, depth;       // block and row bytes of the weights it reads (DIRECT_REWRITE: PAD_ONLY's, what is rewritten)
+    int cb, depth;       // block and row bytes of the weights it reads (the two REWRITEs: what is rewritten; PAD_ONLY's, PACKED's)
 };
 
 // A convolution with its activations in the network's own layout (NCHW, or NHWC).  pl: the plan whose output extents
@@ -403,8 +407,13 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             if (pl.layout == CONV_LAYOUT_PACKED || pl.layout == CONV_LAYOUT_PAD_ONLY) {
                 consider(DIRECT_AS_IS, pl.cb, pl.depth, false, 0);
                 double us;
-                if (!nhwc && dil == 1 && band_direct_us(resident_problem(d, pl, pl.cb, pl.depth, false, false, 1, nullptr, nullptr, out), &us) && us < best)
+                if (!nhwc && dil == 1 && band_direct_us(resident_problem(d, pl, pl.cb, pl.depth, false, false, 1, nullptr, nullptr, out), &us) && us < best) {
+                    best = us;
                     *n = Route{DIRECT_BAND, {}, pl.cb, pl.depth};
+                }
+                ResidentChoice c;
+                if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), &c) && c.us < best)
+                    *n = Route{DIRECT_STREAM, c, pl.cb, pl.depth};
             }
             return true;
         }
@@ -417,6 +426,13 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             if (d->R == 3 && d->S == 3) consider(DIRECT_RAW, C16, depth, true, 0);
             // the weights' own launch: 2.4-3.2 us up to a megabyte of them
             if (C16 <= 1024) consider(DIRECT_REWRITE, C16, depth, false, 2.8 + 1.0e-6 * (double)d->K * depth + SECOND_LAUNCH_US);
+            // weights streamed from blocks of 64 channels: where the two estimates' errors (5 % each) do not decide
+            const int depth64 = (d->C + 63) / 64 * 64 * d->R * d->S;
+            ResidentChoice c;
+            if (stream_pick(resident_problem(d, pl, 64, depth64, false, nhwc, dil, nullptr, nullptr, out), &c)) {
+                const double us = c.us + 2.8 + 1.0e-6 * (double)d->K * depth64 + SECOND_LAUNCH_US;
+                if (us < 0.95 * best) *n = Route{DIRECT_STREAM_REWRITE, c, 64, depth64};
+            }
         }
         return true;
     });
@@ -427,15 +443,19 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
 int run_direct(const Route &rt, const conv_desc_t *d, const Plan &pl, bool nhwc, int dil, const int8_t *in, const int8_t *wt, int32_t *out,
                void *ws, hipStream_t st)
 {
-    if (rt.how == DIRECT_REWRITE) {
+    if (rt.how == DIRECT_REWRITE || rt.how == DIRECT_STREAM_REWRITE) {
         if (launch_pack_weights_blocked(d->K, d->C, d->R, d->S, rt.cb, rt.depth, wt, static_cast<int8_t *>(ws), st) != hipSuccess)
             return CONV_ERR_DEVICE;
         wt = static_cast<const int8_t *>(ws);
     }
     const ResidentProblem r = resident_problem(d, pl, rt.cb, rt.depth, rt.how == DIRECT_RAW, nhwc, dil, in, wt, out);
+    if (rt.how == DIRECT_STREAM || rt.how == DIRECT_STREAM_REWRITE) return gemm_status(launch_stream(r, rt.pick.tile, rt.pick.mper, st));
     return gemm_status(rt.how == DIRECT_BAND ? launch_band_direct(r, st) : launch_resident(r, rt.pick, st));
 }
-size_t direct_bytes(const Route &rt, const conv_desc_t *d) { return rt.how == DIRECT_REWRITE ? (size_t)d->K * rt.depth : 0; }
+size_t direct_bytes(const Route &rt, const conv_desc_t *d)
+{
+    return rt.how == DIRECT_REWRITE || rt.how == DIRECT_STREAM_REWRITE ? (size_t)d->K * rt.depth : 0;
+}
 
 // The library's choice for a one-shot call whose selected layout is `layout` / `cb` (not IMPLICIT): pl gets the output
 // extents the resident kernel works from.
@@ -1122,19 +1142,20 @@ int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int 
 static int resident_forced(const conv_desc_t *desc, int dilation, int nhwc, int wt_cb, int tile, int pixels, const int8_t *in, const int8_t *wt,
                            int32_t *out, ResidentProblem *r)
 {
-    const bool band = tile == CONV_TILE_BAND;
-    if (wt_cb < 0 || (band ? pixels != 0 : tile < 0 || tile >= resident_num_tiles() || pixels < 32 || pixels > 1024 || pixels % 32)) return CONV_ERR_INVALID_ARG;
+    const bool band = tile == CONV_TILE_BAND, stream = is_stream_tile(tile);
+    if (stream && (wt_cb <= 0 || pixels < 1 || pixels > stream_tile_info(tile - CONV_TILE_STREAM).cols)) return CONV_ERR_INVALID_ARG;
+    if (wt_cb < 0 || (stream ? false : band ? pixels != 0 : tile < 0 || tile >= resident_num_tiles() || pixels < 32 || pixels > 1024 || pixels % 32)) return CONV_ERR_INVALID_ARG;
     Plan pl;
     const int rc = direct_dilated_plan(desc, dilation, wt_cb ? wt_cb : 16, &pl);
     if (rc != CONV_OK) return rc;
     *r = resident_problem(desc, pl, wt_cb ? pl.cb : round_up_i(desc->C, 16), pl.depth, wt_cb == 0, nhwc != 0, dilation, in, wt, out);
-    return (band ? band_direct_applies(*r) : resident_applies(*r, tile, pixels)) ? CONV_OK : CONV_ERR_UNSUPPORTED;
+    return (stream ? stream_applies(*r, tile - CONV_TILE_STREAM, pixels) : band ? band_direct_applies(*r) : resident_applies(*r, tile, pixels)) ? CONV_OK : CONV_ERR_UNSUPPORTED;
 }
 
 int conv2d_int8_resident_tile_info(int tile, int *rows, int *cols, int *threads)
 {
-    if (tile < 0 || tile >= resident_num_tiles()) return CONV_ERR_INVALID_ARG;
-    const TileInfo t = resident_tile_info(tile);
+    if ((tile < 0 || tile >= resident_num_tiles()) && !is_stream_tile(tile)) return CONV_ERR_INVALID_ARG;
+    const TileInfo t = is_stream_tile(tile) ? stream_tile_info(tile - CONV_TILE_STREAM) : resident_tile_info(tile);
     if (rows) *rows = t.rows;
     if (cols) *cols = t.cols;
     if (threads) *threads = t.threads;
@@ -1154,6 +1175,7 @@ int conv2d_int8_resident(const conv_desc_t *desc, int dilation, int nhwc, const 
     const int rc = resident_forced(desc, dilation, nhwc, wt_cb, tile, pixels, in, wt, out, &r);
     if (rc != CONV_OK) return rc;
     if (!in || !wt || !out || (wt_cb && !aligned16(wt))) return CONV_ERR_INVALID_ARG;
+    if (is_stream_tile(tile)) return gemm_status(launch_stream_forced(r, tile - CONV_TILE_STREAM, pixels, (hipStream_t)stream));
     return gemm_status(tile == CONV_TILE_BAND ? launch_band_direct(r, (hipStream_t)stream) : launch_resident_forced(r, tile, pixels, (hipStream_t)stream));
 }
 

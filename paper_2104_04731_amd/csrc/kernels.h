@@ -80,7 +80,7 @@ struct ResidentProblem {
     int pixel_bytes;
     long long img_bytes;
     int raw_weights;     // g.wq is KCRS as it came (3 x 3 only), not in depth order
-    int kept;            // the weights were rewritten before this call (which estimates apply)
+    int kept;            // the weights were rewritten before this call (what the estimates are for)
 };
 struct ResidentChoice {
     int tile, mper;   // mper: output pixels of a workgroup
@@ -93,6 +93,13 @@ int resident_num_tiles();
 TileInfo resident_tile_info(int tile);   // rows: output channels of a workgroup, cols: pixels a wave multiplies at a time
 bool resident_applies(const ResidentProblem &r, int tile, int mper);
 hipError_t launch_resident_forced(const ResidentProblem &r, int tile, int mper, hipStream_t st);
+// The stream kernel (stream_mfma.hip) on the same problem: window chunk by chunk, weights through a ring.
+int stream_num_tiles();
+TileInfo stream_tile_info(int tile);     // rows, cols: output channels and (at most) pixels of a workgroup
+bool stream_applies(const ResidentProblem &r, int tile, int mper);
+bool stream_pick(const ResidentProblem &r, ResidentChoice *c);   // false: outside the kernel's domain
+hipError_t launch_stream(const ResidentProblem &r, int tile, int mper, hipStream_t st);
+hipError_t launch_stream_forced(const ResidentProblem &r, int tile, int mper, hipStream_t st);
 // The band kernel on the same problem (NCHW, weights in blocks of 64): estimated launch time; false: not its domain.
 bool band_direct_us(const ResidentProblem &r, double *us);
 bool band_direct_applies(const ResidentProblem &r);   // (also where the estimate is not made: large grids)

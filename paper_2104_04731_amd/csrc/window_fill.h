@@ -82,8 +82,8 @@ __device__ __forceinline__ void put_4x8(const unsigned long long (&v)[4], unsign
 // are a channel plane apart each (the form below) takes 20 to 65 cycles, one of these 14 (64 images 56 x 56, 64 -> 64: 18.0 -> 15.9 us;
 // 16 images 72 x 56 x 56 -> 96, stride 2: 9.7 -> 8.1).  The LDS stores of four lanes meet in the same banks, which costs
 // about what the loads do.  false, nothing done: a load could pass the tensor's end.
-template <int NT, int B>
-__device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, unsigned char *win, int pitch, int tid)
+template <int NT, int B, typename Place>
+__device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, Place &&place, int pitch, int tid)
 {
     const int8_t *const src = t.src + (long long)w.n0 * t.img_bytes;
     const long long left = t.src_bytes - (long long)w.n0 * t.img_bytes;
@@ -131,7 +131,7 @@ __device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const Wi
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         if (c4[b] + i > t.C1) v[b][i] = v4i{0, 0, 0, 0};
-                unsigned char *const d = win + at[b] * pitch + c4[b];
+                unsigned char *const d = place(at[b], c4[b]);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
                     if (e < 2 || at[b] + 8 < w.slots)
@@ -148,25 +148,26 @@ __device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const Wi
 // its runs of 64 are four fifths full, if it has work for every thread: below, its idle lanes cost more than its loads save
 // (2 images 292 x 20 x 20 -> 66, 88 pixels: 8.2 us, 9.4 with it; 15 images 256 x 7 x 7 -> 26: 9.4 and 9.0; 8 images 64 x 7 x 7 ->
 // 130: 4.7 and 4.9).
-template <int NT, int B>
-__device__ __forceinline__ void window_from_nchw(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, unsigned char *win, int pitch, int tid)
+// place(slot, channel): where a record's dword of four channels goes.
+template <int NT, int B, typename Place>
+__device__ __forceinline__ void window_from_nchw_to(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, Place &&place, int pitch, int tid)
 {
     const int runs = (w.slots + 63) >> 6;
-    if ((w.slots >= 128 || w.slots * 5 >= runs * 256) && runs * 4 * cq >= NT && window_wide_nchw<NT, B>(t, w, cq, mg_cq, win, pitch, tid)) return;
+    if ((w.slots >= 128 || w.slots * 5 >= runs * 256) && runs * 4 * cq >= NT && window_wide_nchw<NT, B>(t, w, cq, mg_cq, place, pitch, tid)) return;
     const int units = cq * (w.slots >> 3);
     const long long img0 = (long long)w.n0 * t.img_bytes;
     if (w.slots == w.len0 && t.C1 + 1 == 4 * cq && img0 + (long long)t.C1 * t.HW + w.lo0 + w.slots <= t.src_bytes) {
         const int8_t *const b0 = t.src + img0 + w.lo0, *const b1 = b0 + t.HW, *const b2 = b1 + t.HW, *const b3 = b2 + t.HW;
         for (int u0 = tid; u0 < units; u0 += NT * B) {   // B: units per thread and round of loads
             unsigned long long v[B][4];
-            int dst[B];
+            unsigned char *dst[B];
 #pragma unroll
             for (int b = 0; b < B; ++b) {
                 const int u = u0 + b * NT;
                 if (u < units) {
                     const int g = fast_div_any(u, cq, mg_cq), c4 = (u - g * cq) * 4;
                     const unsigned off = (unsigned)(c4 * t.HW + g * 8);
-                    dst[b] = g * 8 * pitch + c4;
+                    dst[b] = place(g * 8, c4);
                     v[b][0] = *reinterpret_cast<const u64_a1 *>(b0 + off);
                     v[b][1] = *reinterpret_cast<const u64_a1 *>(b1 + off);
                     v[b][2] = *reinterpret_cast<const u64_a1 *>(b2 + off);
@@ -175,19 +176,19 @@ __device__ __forceinline__ void window_from_nchw(const WindowSource &t, const Wi
             }
 #pragma unroll
             for (int b = 0; b < B; ++b)
-                if (u0 + b * NT < units) put_4x8(v[b], win + dst[b], pitch);
+                if (u0 + b * NT < units) put_4x8(v[b], dst[b], pitch);
         }
         return;
     }
     for (int u0 = tid; u0 < units; u0 += NT * B) {
         unsigned long long v[B][4];
-        int dst[B];
+        unsigned char *dst[B];
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             const int u = min(u0 + b * NT, units - 1), g = fast_div_any(u, cq, mg_cq), c4 = (u - g * cq) * 4;
             int n, lin;
             window_slot(w, g * 8, &n, &lin);
-            dst[b] = g * 8 * pitch + c4;
+            dst[b] = place(g * 8, c4);
             const long long img = (long long)n * t.img_bytes;
             const int8_t *base = t.src + img;
             const long long left = t.src_bytes - 8 - img;
@@ -202,9 +203,14 @@ __device__ __forceinline__ void window_from_nchw(const WindowSource &t, const Wi
 #pragma unroll
         for (int b = 0; b < B; ++b) {
             if (u0 + b * NT >= units) break;
-            put_4x8(v[b], win + dst[b], pitch);
+            put_4x8(v[b], dst[b], pitch);
         }
     }
+}
+template <int NT, int B>
+__device__ __forceinline__ void window_from_nchw(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, unsigned char *win, int pitch, int tid)
+{
+    window_from_nchw_to<NT, B>(t, w, cq, mg_cq, [&](int slot, int c4) { return win + slot * pitch + c4; }, pitch, tid);
 }
 
 // Pixel-major source (NHWC) -> records: 16-byte pieces, neighbouring lanes on neighbouring pieces.

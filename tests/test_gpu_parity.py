@@ -1388,6 +1388,72 @@ def test_resident_depth_parts(lib, cfg):
     assert ran > 20
 
 
+# The stage that streams the weights, tile and pixels given: every tile on NCHW and NHWC, channels that end in every part of a
+# 64-channel chunk, blocks of 16, 32, 64 and more, fewer steps than a ring has stages, 1x1 (a chunk per step), strides,
+# dilation, tiles over many small images, a tile that sees the border only, windows of more chunks than fit (refilled beside the MFMAs).
+STREAM_SHAPES = [
+    ConvShape("sm-c64", 2, 64, 14, 14, 64, 3, 3, 1, 1), ConvShape("sm-c100", 3, 100, 10, 11, 70, 3, 3, 1, 1), ConvShape("sm-k300", 2, 256, 14, 14, 300, 3, 3, 1, 1),
+    ConvShape("sm-wide", 1, 130, 40, 37, 64, 3, 3, 1, 1), ConvShape("sm-s2", 5, 200, 7, 7, 130, 3, 3, 2, 1), ConvShape("sm-5x5", 2, 20, 21, 18, 64, 5, 5, 1, 2),
+    ConvShape("sm-3x3-images", 9, 65, 3, 3, 33, 3, 3, 1, 1), ConvShape("sm-dil3", 2, 48, 20, 17, 64, 3, 3, 1, 3), ConvShape("sm-refilled", 1, 512, 27, 30, 257, 3, 3, 1, 1),
+    ConvShape("sm-1x1", 2, 128, 9, 13, 64, 1, 1, 1, 0), ConvShape("sm-c17", 3, 17, 19, 23, 96, 3, 3, 1, 1), ConvShape("sm-2x3-border", 2, 320, 6, 6, 40, 2, 3, 1, 3),
+]
+
+
+@pytest.mark.parametrize("cfg", STREAM_SHAPES, ids=lambda c: c.name)
+def test_stream_every_tile(lib, cfg):
+    dil = 3 if cfg.name == "sm-dil3" else 1
+    x = uniform_int8(995, (cfg.N, cfg.C, cfg.H, cfg.W)); w = uniform_int8(996, (cfg.K, cfg.C, cfg.R, cfg.S))
+    want = direct.conv2d_int8_dilated(x, w, cfg.stride, cfg.pad, dil)
+    want_h = layouts.unpack_nhwc(want)
+    t = torch.empty(x.size + 3, dtype=torch.int8, device=DEV)   # (behind an odd address)
+    t[3:] = dev(x).view(-1)
+    dx, dxh = t[3:].view(x.shape), dev(np.ascontiguousarray(x.transpose(0, 2, 3, 1)))
+    ran = set()
+    for cb in (16, 32, 64, 256):
+        wq = lib.pack_weights(dev(w), lib.LAYOUT_PACKED, cb)
+        for tile, (rows, cols, threads) in lib.stream_tiles().items():
+            for pixels in (cols, 33):
+                for nhwc in (False, True):
+                    if not lib.resident_applies(cfg.dims(), cb, tile, pixels, dil, nhwc):
+                        continue
+                    buf = torch.full((want.size + 128,), -7, dtype=torch.int32, device=DEV)
+                    out = buf[64:64 + want.size].view(want_h.shape if nhwc else want.shape)
+                    lib.conv2d_int8_resident(cfg.dims(), dxh if nhwc else dx, wq, out, cb, tile, pixels, dil, nhwc)
+                    got = host(buf)
+                    assert np.array_equal(got[64:-64].reshape(out.shape), want_h if nhwc else want), (tile, pixels, cb, nhwc)
+                    assert (got[:64] == -7).all() and (got[-64:] == -7).all(), (tile, pixels, cb, nhwc)
+                    ran.add((tile, nhwc))
+    assert {(t, h) for t in lib.stream_tiles() for h in (False, True)} <= ran
+
+
+# Calls that the library sends there: kept weights, and raw ones rewritten first (NCHW, NHWC, dilated).
+STREAM_CALLS = [ConvShape("sc-s2", 60, 400, 14, 14, 64, 3, 3, 2, 1), ConvShape("sc-k40", 100, 512, 7, 7, 40, 3, 3, 1, 1), ConvShape("sc-5x5", 100, 300, 14, 14, 20, 5, 5, 1, 2)]
+
+
+@pytest.mark.parametrize("cfg", STREAM_CALLS, ids=lambda c: c.name)
+def test_calls_that_stream_their_weights(lib, cfg):
+    x, w, want = oracle_conv(cfg)
+    dx, dw = dev(x), dev(w)
+    assert lib.query_stage(cfg.dims(), lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True)[0] == lib.STAGE_STREAM
+    assert lib.query_stage(cfg.dims(), lib.ENTRY_ONE_SHOT)[0] == lib.query_stage(cfg.dims(), lib.ENTRY_NHWC)[0] == lib.STAGE_STREAM_REWRITE
+    wq = lib.pack_weights(dw, lib.LAYOUT_PACKED, 64)
+    ws = torch.empty(max(256, lib.conv2d_int8_workspace_bytes(cfg.dims(), lib.LAYOUT_PACKED, 64)), dtype=torch.int8, device=DEV)
+    for weights, packed in ((wq, True), (dw, False)):
+        out = torch.full(want.shape, -7, dtype=torch.int32, device=DEV)
+        assert np.array_equal(host(lib.conv2d_int8_ex(cfg.dims(), lib.LAYOUT_PACKED, 64, dx, weights, out, ws, wt_is_packed=packed)), want), packed
+    assert np.array_equal(host(lib.conv2d_int8(dx, dw, cfg.stride, cfg.pad)), want)
+    got = lib.conv2d_int8_nhwc(dev(np.ascontiguousarray(x.transpose(0, 2, 3, 1))), dw, cfg.stride, cfg.pad)
+    assert np.array_equal(host(got).transpose(0, 3, 1, 2), want)
+    g, out = torch.cuda.CUDAGraph(), torch.empty(want.shape, dtype=torch.int32, device=DEV)
+    with torch.cuda.graph(g):
+        lib.conv2d_int8_ex(cfg.dims(), lib.LAYOUT_PACKED, 64, dx, wq, out, ws, wt_is_packed=True)
+    for _ in range(3):
+        out.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(host(out), want)
+
+
 # The band kernel on the network's own tensor, asked for: also one output row per band with six blocks of columns, and a grid
 # larger than the estimate's.
 BAND_FORCED = BAND_DIRECT_SHAPES + [ConvShape("band-c256-w71", 1, 256, 3, 71, 128, 3, 3, 1, 1), ConvShape("band-c217", 3, 217, 10, 10, 61, 3, 3, 1, 1),
