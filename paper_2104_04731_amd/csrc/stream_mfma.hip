@@ -494,7 +494,7 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
                 if (k >= a.K) continue;
                 char *const to = reinterpret_cast<char *>(a.out) + ((size_t)w.n0 * a.K + (size_t)k) * row;
                 if (whole) {
-                    if (a.stream_out) __builtin_nontemporal_store(t, reinterpret_cast<v4i *>(to + off));
+                    if (a.stream_out) __builtin_nontemporal_store(t, reinterpret_cast<v4i_a4 *>(to + off));
                     else *reinterpret_cast<v4i_a4 *>(to + off) = t;
                 } else if (ok) {   // (two images meet in the four pixels -- or more, of fewer than four -- or the tile ends)
                     unsigned o = off;
