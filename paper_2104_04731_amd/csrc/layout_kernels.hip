@@ -266,8 +266,8 @@ hipError_t launch_pack_weights_blocked(int K, int C, int R, int S, int cb, int d
 {
     const long long items = (long long)K * (depth / 16);
     if (items >= (1LL << 31)) return hipErrorInvalidValue;
-    return launch(pack_weights_blocked_kernel, dim3(grid_for(items, 256)), dim3(256), 0, st,
-                  weight_args_blocked(K, C, R, S, cb, depth, src, dst));
+    const WeightArgs w = weight_args_blocked(K, C, R, S, cb, depth, src, dst);
+    return launch(pack_weights_blocked_kernel, dim3(grid_for(weight_items(w), 256)), dim3(256), 0, st, w);
 }
 
 // Row-padded copy: dst[k][j] = j < CRS ? src[k][j] : 0 (the (c,r,s) order is KCRS itself).
@@ -765,7 +765,7 @@ hipError_t launch_rewrite_fused(bool im2col, int N, int C, int H, int W, int K, 
     const long long w_items = (long long)K * (depth / 16);
     if (w_items >= (1LL << 31)) return hipErrorNotSupported;
     a.in_blocks = (int)blocks;
-    a.w_blocks = grid_for(w_items, 256);
+    a.w_blocks = grid_for(im2col ? w_items : weight_items(a.wt), 256);
     a.in_is_im2col = im2col;
     a.w_is_blocked = !im2col;
     if (blocks + a.w_blocks >= (1LL << 31)) return hipErrorNotSupported;
@@ -862,7 +862,7 @@ hipError_t launch_rewrite_fused_nhwc(int N, int C, int H, int W, int K, int R, i
     const long long w_items = (long long)K * (depth / 16);
     if (w_items >= (1LL << 31)) return hipErrorNotSupported;
     const WeightArgs w = weight_args_blocked(K, C, R, S, cb, depth, wt, wq);
-    const int in_blocks = grid_for(a.total, 256), w_blocks = grid_for(w_items, 256);
+    const int in_blocks = grid_for(a.total, 256), w_blocks = grid_for(weight_items(w), 256);
     return launch(rewrite_fused_nhwc_kernel, dim3(in_blocks + w_blocks), dim3(256), 0, st, a, w, in_blocks, w_blocks);
 }
 

@@ -354,6 +354,51 @@ static inline bool plan_pack_src(int N, int C, int H, int W, int cb, int pad, co
     return true;
 }
 
+typedef unsigned u32_a1 __attribute__((aligned(1)));
+
+// Raw 3x3 weights: 4 channels x 9 taps of one row are 36 consecutive bytes (byte 9c + t).  raw9_load fetches them (rows past
+// the last one and channels past the last one: zeros), raw9_tap<T> picks tap T's dword of four channels out of them: three
+// byte permutes.
+__host__ __device__ __forceinline__ void raw9_load(const int8_t *wt, int K, int C, int k, int quad, unsigned (&d)[9])
+{
+#pragma unroll
+    for (int i = 0; i < 9; ++i) d[i] = 0;
+    const int valid = k < K ? min(C - quad * 4, 4) * 9 : 0;   // bytes that belong to this row's channels
+    if (valid <= 0) return;
+    const int8_t *p = wt + (long long)k * C * 9 + (long long)quad * 36;
+    // 36 bytes are left in the tensor: behind a row's last channels come the next rows, and four of them (the shortest is
+    // nine bytes) always suffice.  One row is not enough where a row has a single channel.
+    if (min(K - k, 4) * C * 9 - quad * 36 >= 36) {
+        const v4i_a1 x0 = *reinterpret_cast<const v4i_a1 *>(p), x1 = *reinterpret_cast<const v4i_a1 *>(p + 16);
+        d[0] = x0[0], d[1] = x0[1], d[2] = x0[2], d[3] = x0[3], d[4] = x1[0], d[5] = x1[1], d[6] = x1[2], d[7] = x1[3];
+        d[8] = *reinterpret_cast<const u32_a1 *>(p + 32);
+    } else {   // the tensor's last bytes
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            for (int b = 0; b < 4; ++b)
+                if (i * 4 + b < valid) d[i] |= (unsigned)(unsigned char)p[i * 4 + b] << (8 * b);
+    }
+}
+__host__ __device__ __forceinline__ void raw9_mask(int C, int quad, unsigned (&d)[9])
+{
+    const int valid = min(C - quad * 4, 4) * 9;
+    if (valid < 36 && valid > 0) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const int keep = valid - 4 * i;
+            d[i] &= keep >= 4 ? 0xFFFFFFFFu : keep <= 0 ? 0u : (1u << (8 * keep)) - 1u;
+        }
+    }
+}
+template <int T>
+__device__ __forceinline__ unsigned raw9_tap(const unsigned (&d)[9])
+{
+    constexpr int p0 = T, p1 = 9 + T, p2 = 18 + T, p3 = 27 + T;
+    const unsigned lo = __builtin_amdgcn_perm(d[p1 >> 2], d[p0 >> 2], 0x0C0C0000u | (4u + (p1 & 3)) << 8 | (p0 & 3));
+    const unsigned hi = __builtin_amdgcn_perm(d[p3 >> 2], d[p2 >> 2], 0x0C0C0000u | (4u + (p3 & 3)) << 8 | (p2 & 3));
+    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+
 // ---- pack_weights -----------------------------------------------------------------------
 // Blocked: dst[k][((b*R + r)*S + s)*cb + ci] = src[k][b*cb+ci][r][s]; one thread per 16 B.
 struct WeightArgs {
@@ -361,6 +406,8 @@ struct WeightArgs {
     int8_t *dst;
     int K, C, R, S, cb, depth, nreal;  // cb == 0: row-padded copy (depth order of KCRS itself)
     unsigned m_chunks, m_g16, m_RS;    // ceil(2^32 / d) for depth/16, cb/16, R*S
+    int cq;                            // 3x3 in quads: channel quads of a row, the blocks' padding included; else 0
+    unsigned m_cq;
 };
 
 // One thread per 16 destination bytes, `nthreads` threads per (virtual) workgroup; K*depth/16 < 2^31.
@@ -372,6 +419,25 @@ __device__ __forceinline__ void pack_weights_blocked_body(const WeightArgs &a, i
     const int chunks = depth / 16;
     const int total = K * chunks;
     const int g16 = cb / 16, RS = a.R * a.S;
+    if (a.cq) {
+        // 3x3: a thread takes four channels' nine taps, 36 bytes in a row, and stores nine dwords (neighbouring threads'
+        // stores are neighbours).  Sixteen single bytes per piece, the general form below, are sixteen load instructions that
+        // each name 64 cache lines (alone, in blocks of 64: 512 x 256 channels 3.3-3.5 -> 2.5-2.7 us, 512 x 512 3.9 -> 2.65,
+        // in blocks of 16 3.8 -> 3.1, 37 x 100 2.63 -> 2.37).
+        const int cq = a.cq, tail = (chunks - nreal) * 4;   // dwords of a row past its last block
+        for (int t = vbid * nthreads + (int)threadIdx.x; t < K * cq; t += vgrid * nthreads) {
+            const int k = fast_div_any(t, cq, a.m_cq), q = t - k * cq, b = fast_div_any(q >> 2, g16, a.m_g16);
+            unsigned d[9];
+            raw9_load(src, K, C, k, q, d);
+            unsigned *const row = reinterpret_cast<unsigned *>(dst + (long long)k * depth), *const o = row + b * 9 * (cb / 4) + q - b * (cb / 4);
+            const int tap = cb / 4;
+            o[0] = raw9_tap<0>(d), o[tap] = raw9_tap<1>(d), o[2 * tap] = raw9_tap<2>(d);
+            o[3 * tap] = raw9_tap<3>(d), o[4 * tap] = raw9_tap<4>(d), o[5 * tap] = raw9_tap<5>(d);
+            o[6 * tap] = raw9_tap<6>(d), o[7 * tap] = raw9_tap<7>(d), o[8 * tap] = raw9_tap<8>(d);
+            for (int z = q; z < tail; z += cq) row[nreal * 4 + z] = 0;
+        }
+        return;
+    }
     for (int t = vbid * nthreads + (int)threadIdx.x; t < total; t += vgrid * nthreads) {
         const int k = fast_div_any(t, chunks, a.m_chunks), ch = t - k * chunks;
         // sixteen loads issued back to back, none under a condition: a piece past the real depth and the
@@ -400,8 +466,13 @@ static inline WeightArgs weight_args_blocked(int K, int C, int R, int S, int cb,
                                              const int8_t *src, int8_t *dst)
 {
     const int Cb = (C + cb - 1) / cb;
+    // Whole quads only: a quad cut by the row's end goes byte by byte, which is slower than the general form (70 x 298 channels
+    // 2.7 -> 3.9 us, 256 x 17 2.6 -> 3.4); up to 16 channels there is nothing to gain (16 x 16 2.2 either way).
+    const int cq = R == 3 && S == 3 && C % 4 == 0 && C > 16 && C < 1 << 24 ? Cb * (cb / 4) : 0;
     return WeightArgs{src, dst, K, C, R, S, cb, depth, Cb * R * S * (cb / 16),
-                      magic_for(depth / 16), magic_for(cb / 16), magic_for((long long)R * S)};
+                      magic_for(depth / 16), magic_for(cb / 16), magic_for((long long)R * S), cq, cq > 1 ? magic_for(cq) : 0u};
 }
+// Work items of the blocked body.
+static inline long long weight_items(const WeightArgs &w) { return (long long)w.K * (w.cq ? w.cq : w.depth / 16); }
 
 }  // namespace c2i8

@@ -1,5 +1,5 @@
 // Device pieces of the GEMM stages that read the network's own tensors: input pixels turned around into pixel-major LDS
-// records, and raw 3x3 weights brought into depth order.  Used by resident_mfma.hip and band_mfma.hip.
+// records (the raw 3x3 weights' pieces are in rewrite_bodies.h).
 #pragma once
 #include "rewrite_bodies.h"
 
@@ -57,7 +57,6 @@ struct WindowSource {
 };
 
 typedef unsigned long long u64_a1 __attribute__((aligned(1)));
-typedef unsigned u32_a1 __attribute__((aligned(1)));
 
 // Four pixels of four channels (a channel per dword) -> four records' dwords, `pitch` bytes apart.
 __device__ __forceinline__ void put_4x4(unsigned r0, unsigned r1, unsigned r2, unsigned r3, unsigned char *d, int pitch)
@@ -243,49 +242,6 @@ __device__ __forceinline__ void window_from_pixels(const WindowSource &t, const 
             *reinterpret_cast<v4i *>(win + dst[b]) = v[b];
         }
     }
-}
-
-// Raw 3x3 weights: 4 channels x 9 taps of one row are 36 consecutive bytes (byte 9c + t).  raw9_load fetches them (rows past
-// the last one and channels past the last one: zeros), raw9_tap<T> picks tap T's dword of four channels out of them: three
-// byte permutes.
-__host__ __device__ __forceinline__ void raw9_load(const int8_t *wt, int K, int C, int k, int quad, unsigned (&d)[9])
-{
-#pragma unroll
-    for (int i = 0; i < 9; ++i) d[i] = 0;
-    const int valid = k < K ? min(C - quad * 4, 4) * 9 : 0;   // bytes that belong to this row's channels
-    if (valid <= 0) return;
-    const int8_t *p = wt + (long long)k * C * 9 + (long long)quad * 36;
-    // 36 bytes are left in the tensor: behind a row's last channels come the next rows, and four of them (the shortest is
-    // nine bytes) always suffice.  One row is not enough where a row has a single channel.
-    if (min(K - k, 4) * C * 9 - quad * 36 >= 36) {
-        const v4i_a1 x0 = *reinterpret_cast<const v4i_a1 *>(p), x1 = *reinterpret_cast<const v4i_a1 *>(p + 16);
-        d[0] = x0[0], d[1] = x0[1], d[2] = x0[2], d[3] = x0[3], d[4] = x1[0], d[5] = x1[1], d[6] = x1[2], d[7] = x1[3];
-        d[8] = *reinterpret_cast<const u32_a1 *>(p + 32);
-    } else {   // the tensor's last bytes
-#pragma unroll
-        for (int i = 0; i < 9; ++i)
-            for (int b = 0; b < 4; ++b)
-                if (i * 4 + b < valid) d[i] |= (unsigned)(unsigned char)p[i * 4 + b] << (8 * b);
-    }
-}
-__host__ __device__ __forceinline__ void raw9_mask(int C, int quad, unsigned (&d)[9])
-{
-    const int valid = min(C - quad * 4, 4) * 9;
-    if (valid < 36 && valid > 0) {
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const int keep = valid - 4 * i;
-            d[i] &= keep >= 4 ? 0xFFFFFFFFu : keep <= 0 ? 0u : (1u << (8 * keep)) - 1u;
-        }
-    }
-}
-template <int T>
-__device__ __forceinline__ unsigned raw9_tap(const unsigned (&d)[9])
-{
-    constexpr int p0 = T, p1 = 9 + T, p2 = 18 + T, p3 = 27 + T;
-    const unsigned lo = __builtin_amdgcn_perm(d[p1 >> 2], d[p0 >> 2], 0x0C0C0000u | (4u + (p1 & 3)) << 8 | (p0 & 3));
-    const unsigned hi = __builtin_amdgcn_perm(d[p3 >> 2], d[p2 >> 2], 0x0C0C0000u | (4u + (p3 & 3)) << 8 | (p2 & 3));
-    return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
 }  // namespace c2i8

@@ -115,6 +115,18 @@ def test_pack_weights(lib, wshape, cb):
     np.testing.assert_array_equal(got, layouts.pack_weights_blocked(w, cbp))
 
 
+@pytest.mark.parametrize("K,C", [(1, 20), (33, 32), (7, 100), (65, 64), (3, 16), (5, 18), (130, 256)])
+@pytest.mark.parametrize("cb", [16, 48, 64, 128])
+def test_pack_weights_3x3_in_quads(lib, K, C, cb):
+    """Whole quads of a row's channels and their neighbours on the general form, from an aligned and an odd source address."""
+    w = uniform_int8(K * 1000 + C + cb, (K, C, 3, 3))
+    raw = torch.empty(w.size + 1, dtype=torch.int8, device="cuda")
+    off = raw[1:].view(w.shape)
+    off.copy_(dev(w))
+    for src in (dev(w), off):
+        np.testing.assert_array_equal(host(lib.pack_weights(src, lib.LAYOUT_PACKED, cb)), layouts.pack_weights_blocked(w, cb))
+
+
 @pytest.mark.parametrize("dims", [(2, 3, 6, 7, 3, 2, 2, 1), (1, 3, 31, 29, 7, 7, 2, 3), (1, 16, 14, 14, 3, 3, 1, 1),
                                   (2, 1, 41, 50, 20, 5, 2, 0), (1, 5, 9, 9, 1, 1, 1, 0), (1, 2, 5, 5, 7, 7, 1, 1),
                                   (1, 70, 6, 6, 3, 3, 3, 2)])
