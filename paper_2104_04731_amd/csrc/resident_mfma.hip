@@ -641,14 +641,15 @@ double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile
            (rounds - 1) * (f.window2 * window + f.weights2 * weights);
 }
 
+// With the choice: one layer on the same depth order may come with kept weights and with raw ones, whose estimates differ.
 struct ResidentKey {
     GemmKey g;
-    int v[9];
+    int v[11];
 };
-ResidentKey resident_key(const ResidentProblem &r)
+ResidentKey resident_key(const ResidentProblem &r, const ResidentChoice &c)
 {
     const int out64 = (reinterpret_cast<uintptr_t>(r.g.out) & 63) == 0;
-    return ResidentKey{gemm_key(r.g), {r.N, r.C, r.H, r.W, r.pad, r.pixel_major, r.pixel_bytes, r.raw_weights, out64}};
+    return ResidentKey{gemm_key(r.g), {r.N, r.C, r.H, r.W, r.pad, r.pixel_major, r.pixel_bytes, r.raw_weights, out64, c.tile, c.mper}};
 }
 
 }  // namespace
@@ -737,7 +738,7 @@ static hipError_t launch_plan(const ResidentProblem &r, const ResidentPlan &p, h
 hipError_t launch_resident(const ResidentProblem &r, const ResidentChoice &c, hipStream_t st)
 {
     static thread_local PlanTable<ResidentKey, ResidentPlan, 64> plans;
-    const ResidentPlan *kept = plans.get(resident_key(r), [&](ResidentPlan *p) { return resident_plan(r, c.tile, c.mper, p); });
+    const ResidentPlan *kept = plans.get(resident_key(r, c), [&](ResidentPlan *p) { return resident_plan(r, c.tile, c.mper, p); });
     return kept ? launch_plan(r, *kept, st) : hipErrorInvalidValue;
 }
 

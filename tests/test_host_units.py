@@ -1,6 +1,8 @@
 """Pieces of the library's code that can run on the host, compiled for the host and run there (no GPU)."""
+import json
 import os
 import subprocess
+import sys
 
 import pytest
 
@@ -30,3 +32,37 @@ def test_plan_table_keeps_as_many_problems_as_it_holds(run_host):
 def test_window_fills_stay_inside_tensor_and_window(run_host):
     """6000 random layers' input ranges, from NCHW and NHWC tensors that touch a page without access on either side."""
     assert run_host("window_fill", ("-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include")) == (0, "ok")
+
+
+# (dims, layout, block): layers whose one-shot and kept-weights calls both take the resident kernel, with different tiles or pixels
+SHARED_LAYERS = [((266, 64, 56, 56, 64, 5, 5, 1, 2), 3, 0), ((2, 128, 48, 48, 64, 1, 1, 1, 0), 1, 64), ((132, 32, 14, 14, 512, 5, 5, 1, 2), 3, 0),
+                 ((12, 32, 56, 56, 281, 1, 1, 1, 0), 3, 0), ((2, 70, 37, 37, 163, 5, 5, 1, 2), 3, 0), ((350, 32, 56, 56, 51, 3, 3, 1, 1), 3, 0)]
+
+
+@pytest.fixture
+def launches(tmp_path):
+    """What calls of conv2d_int8_ex would launch, made one after the other in a process of their own."""
+    from paper_2104_04731_amd import build
+    recorder = str(tmp_path / "launch_recorder.so")
+    subprocess.run(["g++", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include", os.path.join(HERE, "launch_recorder.cpp"), "-o", recorder],
+                   check=True, timeout=120)
+
+    def run(calls):
+        r = subprocess.run([sys.executable, os.path.join(HERE, "launches.py"), recorder, build.LIB, json.dumps(calls)], capture_output=True, text=True, check=True, timeout=120)
+        return json.loads(r.stdout)
+    return run
+
+
+@pytest.mark.parametrize("dims,layout,cb", SHARED_LAYERS)
+def test_a_layer_called_both_ways_keeps_a_plan_for_each(lib, launches, dims, layout, cb):
+    """Raw and kept weights of one layer, in both orders: each call launches what the query says of it, whichever came first."""
+    kept, raw = (dims, layout, cb, 1), (dims, layout, cb, 0)
+    first, second = launches([kept, raw]), launches([raw, kept])[::-1]
+    assert first == second
+    (N, C, H, W, K, R, S, stride, pad), tiles = dims, lib.resident_tiles()
+    M = N * ((H + 2 * pad - R) // stride + 1) * ((W + 2 * pad - S) // stride + 1)
+    for call in first:
+        stage, tile, pixels = call["stage"]
+        assert call["rc"] == 0 and stage in (lib.STAGE_RESIDENT, lib.STAGE_RESIDENT_RAW, lib.STAGE_RESIDENT_REWRITE)
+        rows, _, threads = tiles[tile]
+        assert (call["workgroups"], call["threads"]) == (-(-K // rows) * -(-M // pixels), threads)
