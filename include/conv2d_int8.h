@@ -205,7 +205,8 @@ typedef enum {
     CONV_STAGE_STREAM_REWRITE = 7    /* ... on weights that a launch of its own rewrites first */
 } conv_stage_t;
 /* entry: which call (conv2d_int8, _ex, _nhwc, _dilated, _dilated_direct); layout, cb, wt_is_packed, dilation: its arguments,
- * those it does not have are ignored.  tile, pixels: those of conv2d_int8_resident, -1 and 0 for the other stages. */
+ * those it does not have are ignored.  tile, pixels: what conv2d_int8_resident takes for the same launch (RESIDENT*: a tile
+ * index, STREAM*: CONV_TILE_STREAM + t); -1 and 0 for the other stages. */
 int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int cb, int wt_is_packed, int dilation,
                             int *stage, int *tile, int *pixels);
 

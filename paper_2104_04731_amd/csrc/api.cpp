@@ -1132,9 +1132,9 @@ int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int 
         if (rc != CONV_OK) return rc;
     } else return CONV_ERR_INVALID_ARG;
     *stage = as_is ? CONV_STAGE_AS_IS : rt.how;
-    const bool resident = rt.how == DIRECT_AS_IS || rt.how == DIRECT_RAW || rt.how == DIRECT_REWRITE;
-    *tile = resident ? rt.pick.tile : -1;
-    *pixels = resident ? rt.pick.mper : 0;
+    const bool stream = rt.how == DIRECT_STREAM || rt.how == DIRECT_STREAM_REWRITE, given = rt.how == DIRECT_BAND || rt.how == TWO_STAGE;
+    *tile = given ? -1 : rt.pick.tile + (stream ? CONV_TILE_STREAM : 0);
+    *pixels = given ? 0 : rt.pick.mper;
     return CONV_OK;
 }
 

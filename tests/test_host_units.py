@@ -66,3 +66,16 @@ def test_a_layer_called_both_ways_keeps_a_plan_for_each(lib, launches, dims, lay
         assert call["rc"] == 0 and stage in (lib.STAGE_RESIDENT, lib.STAGE_RESIDENT_RAW, lib.STAGE_RESIDENT_REWRITE)
         rows, _, threads = tiles[tile]
         assert (call["workgroups"], call["threads"]) == (-(-K // rows) * -(-M // pixels), threads)
+
+
+@pytest.mark.parametrize("dims", [(144, 128, 28, 28, 128, 3, 3, 2, 1), (451, 450, 7, 8, 64, 3, 3, 1, 1), (100, 300, 14, 14, 20, 5, 5, 1, 2)])
+def test_query_names_the_streaming_tile(lib, launches, dims):
+    """Kept weights and raw ones: the tile and pixels that the query reports are launched, and the forced call takes them."""
+    (N, C, H, W, K, R, S, stride, pad), tiles = dims, lib.stream_tiles()
+    M = N * ((H + 2 * pad - R) // stride + 1) * ((W + 2 * pad - S) // stride + 1)
+    for call, stage in zip(launches([(dims, 1, 64, 1), (dims, 1, 64, 0)]), (lib.STAGE_STREAM, lib.STAGE_STREAM_REWRITE)):
+        got, tile, pixels = call["stage"]
+        assert call["rc"] == 0 and got == stage
+        rows, most, threads = tiles[tile]
+        assert pixels <= most and (call["workgroups"], call["threads"]) == (-(-K // rows) * -(-M // pixels), threads)
+        assert lib.resident_applies(dims, 64, tile, pixels)
