@@ -696,8 +696,8 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
     a.zero_off = d.ring();
     a.win_off = a.zero_off + 64;
     a.tab_off = a.win_off + nbuf * a.buf_bytes;
-    // whole 64-byte sectors per store instruction go past the caches (resident_mfma.hip)
-    a.stream_out = PQ % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0;
+    // whole 64-byte sectors per store instruction, of planes and tiles that hold whole ones, go past the caches (resident_mfma.hip)
+    a.stream_out = PQ % 16 == 0 && mper % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0;
     const long long tk = (g.K + d.tk() - 1) / d.tk(), tm = ((long long)g.M + mper - 1) / mper;
     if (tk * tm > 0x7FFFFFFFLL) return false;
     a.tiles_k = (int)tk;
@@ -808,9 +808,17 @@ bool stream_pick(const ResidentProblem &r, ResidentChoice *c)
         consider(r.g.PQ);
     }
     for (const ResidentChoice &x : best) {   // (the window was sampled: the plan knows whether it fits)
-        StreamPlan p;
+        StreamPlan p, whole;
         if (x.us < 1e300 && stream_plan(r, x.tile, x.mper, &p)) {
             *c = x;
+            // Tiles that begin inside a 64-byte sector write it in two parts: on planes of whole sectors the count goes up to whole ones,
+            // where that is at most an eighth more, cuts no image that was divided evenly, and leaves the window as many buffers.  41
+            // layers, mean 1.033 (72 images 500 x 55 x 55 -> 64 stride 2: 111 -> 112 pixels, 63.8 -> 55.5 us), the worst 0.974; up to
+            // 0.89 without the conditions.  (The store's kind does not matter there: 30 layers, past the caches or not, 0.998.)
+            const int up = (x.mper + 15) / 16 * 16;
+            if (r.g.PQ % 16 == 0 && !r.pixel_major && up != x.mper && r.g.PQ % x.mper && up * 8 <= x.mper * 9 && up <= kStreamTiles[x.tile].tm() &&
+                stream_plan(r, x.tile, up, &whole) && whole.a.nbuf == p.a.nbuf)
+                c->mper = up;
             return true;
         }
     }

@@ -1438,6 +1438,26 @@ def test_stream_every_tile(lib, cfg):
     assert {(t, h) for t in lib.stream_tiles() for h in (False, True)} <= ran
 
 
+@pytest.mark.parametrize("pixels", [32, 33, 40, 48])
+def test_stream_results_at_every_alignment(lib, pixels):
+    """Planes of whole 64-byte sectors, cut at whole sectors (stores past the caches) and inside them, and results at every address of
+    an int32: NCHW behind 64 bytes and not, NHWC behind 16 bytes and not."""
+    N, C, H, W, K = 3, 100, 8, 16, 68
+    x = uniform_int8(997, (N, C, H, W)); w = uniform_int8(998, (K, C, 3, 3))
+    want = direct.conv2d_int8(x, w, 1, 1)
+    want_h = layouts.unpack_nhwc(want)
+    dx, dxh, wq = dev(x), dev(np.ascontiguousarray(x.transpose(0, 2, 3, 1))), lib.pack_weights(dev(w), lib.LAYOUT_PACKED, 64)
+    for tile in lib.stream_tiles():
+        for nhwc in (False, True):
+            for behind in (64, 65, 66, 68, 72):
+                buf = torch.full((want.size + 192,), -7, dtype=torch.int32, device=DEV)
+                out = buf[behind:behind + want.size].view(want_h.shape if nhwc else want.shape)
+                lib.conv2d_int8_resident((N, C, H, W, K, 3, 3, 1, 1), dxh if nhwc else dx, wq, out, 64, tile, pixels, 1, nhwc)
+                got = host(buf)
+                assert np.array_equal(got[behind:behind + want.size].reshape(out.shape), want_h if nhwc else want), (tile, nhwc, behind)
+                assert (got[:behind] == -7).all() and (got[behind + want.size:] == -7).all(), (tile, nhwc, behind)
+
+
 # Calls that the library sends there: kept weights, and raw ones rewritten first (NCHW, NHWC, dilated).
 STREAM_CALLS = [ConvShape("sc-s2", 60, 400, 14, 14, 64, 3, 3, 2, 1), ConvShape("sc-k40", 100, 512, 7, 7, 40, 3, 3, 1, 1), ConvShape("sc-5x5", 100, 300, 14, 14, 20, 5, 5, 1, 2)]
 

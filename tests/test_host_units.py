@@ -79,3 +79,10 @@ def test_query_names_the_streaming_tile(lib, launches, dims):
         rows, most, threads = tiles[tile]
         assert pixels <= most and (call["workgroups"], call["threads"]) == (-(-K // rows) * -(-M // pixels), threads)
         assert lib.resident_applies(dims, 64, tile, pixels)
+
+
+@pytest.mark.parametrize("dims", [(72, 500, 55, 55, 64, 3, 3, 2, 1), (575, 256, 7, 7, 357, 3, 3, 2, 1), (22, 512, 28, 28, 420, 3, 3, 1, 1)])
+def test_streaming_tiles_begin_on_whole_sectors(lib, dims):
+    """Planes of whole 64-byte sectors: the library's own pixel counts cut none."""
+    stage, tile, pixels = lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True)
+    assert stage == lib.STAGE_STREAM and pixels % 16 == 0
