@@ -265,7 +265,7 @@ int choose_gemm_now(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
     return CONV_OK;
 }
 
-// The library's own choice is kept per problem (the tile model looks at 45 tiles x 9 splits: 3-4 us of host time).
+// The library's own choice is kept per problem (the tile model looks at 45 tiles x up to 9 splits: 2.7 us of host time).
 int choose_gemm(const GemmProblem &g, int tile, int split_k, GemmChoice *c)
 {
     if (tile != -1 || split_k != 0) return choose_gemm_now(g, tile, split_k, c);
@@ -392,11 +392,13 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
     const Route *kept = routes.get(key, [&](Route *n) {
         double best = two_us();
         *n = Route{TWO_STAGE, {}, 0, 0};
+        // (one for all: which pixels a window holds does not depend on the weights' form)
+        WindowWalk walk = window_walk(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out));
         auto consider = [&](int how, int cb, int depth, bool raw, double extra) {
             ResidentChoice c;
             ResidentProblem r = resident_problem(d, pl, cb, depth, raw, nhwc, dil, nullptr, nullptr, out);
             r.kept = wt_is_packed;
-            if (!resident_pick(r, &c)) return;
+            if (!resident_pick(r, walk, &c)) return;
             const double us = c.us + extra;
             if (us < best) {
                 best = us;
@@ -412,7 +414,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
                     *n = Route{DIRECT_BAND, {}, pl.cb, pl.depth};
                 }
                 ResidentChoice c;
-                if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), &c) && c.us < best)
+                if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), walk, best, &c))
                     *n = Route{DIRECT_STREAM, c, pl.cb, pl.depth};
             }
             return true;
@@ -429,10 +431,9 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             // weights streamed from blocks of 64 channels: where the two estimates' errors (5 % each) do not decide
             const int depth64 = (d->C + 63) / 64 * 64 * d->R * d->S;
             ResidentChoice c;
-            if (stream_pick(resident_problem(d, pl, 64, depth64, false, nhwc, dil, nullptr, nullptr, out), &c)) {
-                const double us = c.us + 2.8 + 1.0e-6 * (double)d->K * depth64 + SECOND_LAUNCH_US;
-                if (us < 0.95 * best) *n = Route{DIRECT_STREAM_REWRITE, c, 64, depth64};
-            }
+            const double rewrite = 2.8 + 1.0e-6 * (double)d->K * depth64 + SECOND_LAUNCH_US;
+            if (stream_pick(resident_problem(d, pl, 64, depth64, false, nhwc, dil, nullptr, nullptr, out), walk, 0.95 * best - rewrite, &c))
+                *n = Route{DIRECT_STREAM_REWRITE, c, 64, depth64};
         }
         return true;
     });

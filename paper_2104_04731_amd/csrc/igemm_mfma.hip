@@ -802,6 +802,16 @@ bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost)
     const double act_bytes = g.mode == ACT_BLOCKED ? (double)g.M / g.PQ * g.Cb * g.cb * g.Hp * g.Wp : (double)g.M * g.depth;
     const double stored = g.act_out || (!g.out_nhwc && g.PQ % 16 == 0) ? 1.2e-05 : !g.out_nhwc ? 1.67e-05 : g.K % 4 == 0 ? 3.99e-07 : 8.56e-05;
     const double added = g.out_nhwc ? 0.000101 : 1.73e-05, summed = g.out_nhwc ? 5.1e-6 : 0.503e-6, setup = g.mode == ACT_BLOCKED ? 0.0788 : 0;
+    // slices of the depth and their steps, the same for every tile: empty slices dropped, each number of them once
+    int slices[9], pers[9], ncand = 0;
+    for (int i = 0; i < (*split_k > 0 ? 1 : (int)(sizeof(splits) / sizeof(splits[0]))); ++i) {
+        int s = *split_k <= 0 ? splits[i] : *split_k > ksteps ? ksteps : *split_k;
+        if (s > ksteps) continue;
+        s = ceil_div(ksteps, ceil_div(ksteps, s));
+        if (ncand && s == slices[ncand - 1]) continue;
+        slices[ncand] = s;
+        pers[ncand++] = ceil_div(ksteps, s);
+    }
     for (int t = 0; t < kNumTiles; ++t) {
         if (*tile >= 0 && t != *tile) continue;
         const TileDef &d = kTiles[t];
@@ -810,18 +820,12 @@ bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost)
         const int acc = d.tk * d.tm / (mwaves * 64);  // accumulator registers per lane
         const int reg_cap = acc > 128 ? 1 : acc > 64 ? 2 : 4;  // 512 registers per lane and SIMD
         const int wave_cap = waves >= 8 ? (reg_cap > 1 ? reg_cap / 2 : 1) : reg_cap;
-        const int forced[] = {*split_k > ksteps ? ksteps : *split_k};
-        const int *cand = *split_k > 0 ? forced : splits;
-        const int ncand = *split_k > 0 ? 1 : (int)(sizeof(splits) / sizeof(splits[0]));
         for (int ci = 0; ci < ncand; ++ci) {
-            int s = cand[ci];
-            if (s > ksteps) continue;
-            s = ceil_div(ksteps, ceil_div(ksteps, s));  // drop slices that would be empty
-            const int per = ceil_div(ksteps, s);
+            const int s = slices[ci], per = pers[ci];
             if (!tile_fits(d, ksteps, per)) continue;
             const size_t lds = tile_lds_bytes(d, g.mode, per);
             if (lds > kLdsLimit) continue;  // ring + offset table must fit one CU's LDS
-            int cap = (int)(kLdsLimit / lds);
+            int cap = (int)kLdsLimit / (int)lds;
             if (cap > wave_cap) cap = wave_cap;
             const double wgs = tiles * s, per_cu = (double)(long long)((wgs + 255) / 256);
             const double res = per_cu < cap ? per_cu : cap;   // workgroups sharing a compute unit

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "window_walk.h"
+
 namespace c2i8 {
 
 // How the GEMM stage finds the depth-contiguous activation row of output pixel m.
@@ -86,7 +88,12 @@ struct ResidentChoice {
     int tile, mper;   // mper: output pixels of a workgroup
     double us;        // estimated launch time
 };
-bool resident_pick(const ResidentProblem &r, ResidentChoice *c);   // false: outside the kernel's domain
+inline WindowWalk window_walk(const ResidentProblem &r)
+{
+    const int dil = r.g.dil > 0 ? r.g.dil : 1;
+    return WindowWalk(r.g.M, r.g.PQ, r.g.Q, r.H, r.W, r.g.stride, r.pad, (r.g.R - 1) * dil, (r.g.S - 1) * dil);
+}
+bool resident_pick(const ResidentProblem &r, WindowWalk &walk, ResidentChoice *c);   // false: outside the kernel's domain
 hipError_t launch_resident(const ResidentProblem &r, const ResidentChoice &c, hipStream_t st);
 // A tile and pixel count of the caller's choosing (0 <= tile < resident_num_tiles(), mper a positive multiple of 32).
 int resident_num_tiles();
@@ -97,7 +104,7 @@ hipError_t launch_resident_forced(const ResidentProblem &r, int tile, int mper, 
 int stream_num_tiles();
 TileInfo stream_tile_info(int tile);     // rows, cols: output channels and (at most) pixels of a workgroup
 bool stream_applies(const ResidentProblem &r, int tile, int mper);
-bool stream_pick(const ResidentProblem &r, ResidentChoice *c);   // false: outside the kernel's domain
+bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, ResidentChoice *c);   // false: outside the kernel's domain, or nothing below `limit` microseconds
 hipError_t launch_stream(const ResidentProblem &r, int tile, int mper, hipStream_t st);
 hipError_t launch_stream_forced(const ResidentProblem &r, int tile, int mper, hipStream_t st);
 // The band kernel on the same problem (NCHW, weights in blocks of 64): estimated launch time; false: not its domain.

@@ -536,7 +536,7 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     a.parts = resident_parts(d, mper, a.steps);
     a.mg_nblk = magic(a.nblk);
     a.mg_parts = magic(a.parts);
-    const long long slots = max_slots(r, mper, 0);
+    const long long slots = window_walk(r).most(mper);
     const long long wts = ((long long)a.steps + 1) * d.tk * 64, lds = resident_lds(d, a.steps, sh.uni, slots, a.pitch, a.parts);
     if (lds > RES_LDS_LIMIT || (long long)((g.R - 1) * r.W + g.S - 1) * dil * a.pitch + a.C16 > (1LL << 30)) return false;
     // whole 64-byte sectors per store instruction: kept out of the caches on the way (64 images 56 x 56, 64 -> 64: 20.3 ->
@@ -573,14 +573,13 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
 // the registers in rounds of loads of their own, more than twice as long where the rows of 9 C bytes do not start on dwords.
 // Near each layer's best launch, on the layers held back: mean error 5 %; by channels, weights and workgroups no group is off
 // by more than 4 %, but for kept weights of 200 channels and more in several rounds (9 % low).
-double resident_cost_given(const ResidentProblem &r, const ResidentShape &sh, int tile, int mper, int slots)
+__attribute__((always_inline)) inline double resident_cost_given(const ResidentProblem &r, const ResidentShape &sh, const ResTile &d, int mper, int tiles_m, int slots)
 {
     const GemmProblem &g = r.g;
-    const ResTile &d = kResTiles[tile];
     const long long lds = resident_lds(d, sh.steps, sh.uni, slots, sh.pitch, 1);
     if (lds > RES_LDS_LIMIT) return 1e300;
-    const long long wgs = (long long)((g.K + d.tk - 1) / d.tk) * ((g.M + mper - 1) / mper);
-    long long fit = RES_LDS_LIMIT / lds;              // workgroups sharing a compute unit
+    const long long wgs = (long long)((g.K + d.tk - 1) / d.tk) * tiles_m;
+    int fit = (int)RES_LDS_LIMIT / (int)lds;              // workgroups sharing a compute unit
     if (fit > d.fit) fit = d.fit;
     const double per = wgs / 256.0;
     const double ncu = per <= (double)fit ? (double)((wgs + 255) / 256) : per + 0.4;
@@ -616,16 +615,14 @@ constexpr ResidentFit kResFit[] = {
     {4.39, 0, 0.0268, 0.299, 0.8, 0.0111, 1.77e-05, 5.95e-06, 2.72e-05, 3.91e-05, 0, 9.25e-06, 1.52e-05},
     {3.26, 0.891, 0.0197, 0.502, 0.756, 0.021, 1.9e-05, 9.3e-06, 1.82e-05, 3.14e-05, 0.699, 0, 7.95e-06},
 };
-double resident_cost(const ResidentProblem &r, const ResidentShape &sh, int tile, int mper, int slots)
+__attribute__((always_inline)) inline double resident_cost(const ResidentProblem &r, const ResidentShape &sh, const ResTile &d, const ResidentFit &f, int mper, int tiles_m, int slots)
 {
     const GemmProblem &g = r.g;
-    const ResTile &d = kResTiles[tile];
-    const ResidentFit &f = kResFit[tile];
     const int parts = resident_parts(d, mper, sh.steps);
     const long long lds = resident_lds(d, sh.steps, sh.uni, slots, sh.pitch, parts);
     if (lds > RES_LDS_LIMIT) return 1e300;
-    const long long wgs = (long long)((g.K + d.tk - 1) / d.tk) * ((g.M + mper - 1) / mper);
-    long long fit = RES_LDS_LIMIT / lds;              // workgroups sharing a compute unit
+    const long long wgs = (long long)((g.K + d.tk - 1) / d.tk) * tiles_m;
+    int fit = (int)RES_LDS_LIMIT / (int)lds;              // workgroups sharing a compute unit
     if (fit > d.fit) fit = d.fit;
     const double per = wgs / 256.0;
     const double ncu = per <= (double)fit ? (double)((wgs + 255) / 256) : per + 0.4;
@@ -654,35 +651,7 @@ ResidentKey resident_key(const ResidentProblem &r, const ResidentChoice &c)
 
 }  // namespace
 
-int max_slots(const ResidentProblem &r, int mper, int tiles)
-{
-    const GemmProblem &g = r.g;
-    const int PQ = g.PQ, Q = g.Q, W = r.W, HW = r.H * r.W, st = g.stride, pad = r.pad, dil = g.dil > 0 ? g.dil : 1;
-    auto first = [&](int pq) {
-        const int p = pq / Q, row = p * st - pad, col = (pq - p * Q) * st - pad;
-        return row < 0 ? 0 : (row * W + (col < 0 ? 0 : col > W - 1 ? W - 1 : col)) & ~7;
-    };
-    auto end = [&](int pq) {
-        const int p = pq / Q, row = p * st - pad + (g.R - 1) * dil, col = (pq - p * Q) * st - pad + (g.S - 1) * dil;
-        return row >= r.H ? HW : row * W + (col > W - 1 ? W - 1 : col < -1 ? -1 : col) + 1;
-    };
-    const int full8 = (end(PQ - 1) + 7) & ~7;
-    int most = 0, a = 0, count = 0;
-    for (long long m0 = 0; m0 < g.M && (m0 == 0 || a != 0) && (tiles == 0 || count < tiles); m0 += mper, a = (a + mper) % PQ, ++count) {
-        const int m1 = m0 + mper < g.M ? a + mper : a + (int)(g.M - m0);   // local end (may pass the image)
-        const int n1 = (m1 - 1) / PQ;
-        int s = ((n1 > 0 ? end(PQ - 1) : end(m1 - 1)) - first(a) + 7) & ~7;
-        if (s < 0) s = 0;
-        if (n1 > 0) {
-            const int t = (end(m1 - 1 - n1 * PQ) + 7) & ~7;
-            s += (n1 - 1) * full8 + (t > 0 ? t : 0);
-        }
-        if (s > most) most = s;
-    }
-    return most;
-}
-
-bool resident_pick(const ResidentProblem &r, ResidentChoice *c)
+bool resident_pick(const ResidentProblem &r, WindowWalk &walk, ResidentChoice *c)
 {
     ResidentShape sh;
     if (!resident_shape(r, &sh)) return false;
@@ -697,13 +666,15 @@ bool resident_pick(const ResidentProblem &r, ResidentChoice *c)
         for (int i = 0; i < n; ++i)
             if (mpers[i] == (int)mper) return;
         mpers[n] = (int)mper;
-        slots_of[n++] = max_slots(r, (int)mper, 8);
+        slots_of[n++] = walk.sampled((int)mper);
     };
     for (int w = 1; w <= 4; ++w) add((((long long)r.g.M + 256 * w - 1) / (256 * w) + 31) / 32 * 32);
     for (int m : sizes) add(m);
-    for (int t = 0; t < kNumResTiles; ++t)
+    int tiles_m[12];
+    for (int i = 0; i < n; ++i) tiles_m[i] = (int)(((long long)r.g.M + mpers[i] - 1) / mpers[i]);
+    auto consider = [&](const ResTile &d, int t) __attribute__((always_inline)) {   // (a tile known to the compiler: its divisions are shifts)
         for (int i = 0; i < n; ++i) {
-            const Cand x{(r.kept ? resident_cost : resident_cost_given)(r, sh, t, mpers[i], slots_of[i]), t, mpers[i]};
+            const Cand x{r.kept ? resident_cost(r, sh, d, kResFit[t], mpers[i], tiles_m[i], slots_of[i]) : resident_cost_given(r, sh, d, mpers[i], tiles_m[i], slots_of[i]), t, mpers[i]};
             for (int k = 0; k < 3; ++k)
                 if (x.cost < best[k].cost) {
                     for (int j = 2; j > k; --j) best[j] = best[j - 1];
@@ -711,6 +682,11 @@ bool resident_pick(const ResidentProblem &r, ResidentChoice *c)
                     break;
                 }
         }
+    };
+    int index = 0;
+#define C2I8_CASE(tk, nw, fm, fit) consider(ResTile{tk, nw, fm, fit}, index++);
+    C2I8_RES_LIST(C2I8_CASE)
+#undef C2I8_CASE
     for (const Cand &x : best) {   // (the window was sampled: the plan knows whether it fits)
         ResidentPlan p;
         if (x.cost < 1e300 && resident_plan(r, x.tile, x.mper, &p)) {

@@ -685,7 +685,7 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
     }
     const long long images = mper / PQ + 2;
     if (images * PQ * g.K * 4 >= (1LL << 32) || images * r.img_bytes > 0x7FFFFFFFLL) return false;   // 32-bit offsets from the tile's first image
-    const long long slots = max_slots(r, mper, 0);
+    const long long slots = window_walk(r).most(mper);
     const int least = least_buffers(sh, d.sps());
     int nbuf = sh.chunks;
     while (nbuf > least && stream_lds(d, sh, nbuf, slots) > ST_LDS_LIMIT) --nbuf;
@@ -736,19 +736,21 @@ constexpr StreamFit kStreamFit[] = {
     {2.12, 3.62, 0.647, 1.92e-05, 3.89e-05, 3.85e-06, 3.46e-05, 0.107},
     {2.15, 3.53, 0.475, 2.25e-05, 4.82e-05, 2.29e-05, 5.84e-05, 0.0652},
 };
-double stream_cost(const ResidentProblem &r, const StreamShape &sh, int tile, int mper, int slots)
+// The estimate without its window, which only adds to it.
+__attribute__((always_inline)) inline double stream_cost_bare(const ResidentProblem &r, const StreamTile &d, const StreamFit &f, long long wgs, int stages, int mper)
 {
-    const StreamTile &d = kStreamTiles[tile];
-    const StreamFit &f = kStreamFit[tile];
+    const double rounds = (double)((wgs + 255) / 256), per = wgs / 256.0, channels = r.g.K < d.tk() ? r.g.K : d.tk();
+    const double result = 4.0 * channels * mper;
+    return f.launch + rounds * (f.round + f.stage * stages) + per * ((r.g.PQ % 16 == 0 ? f.aligned : f.other) * result + f.shared * stages);
+}
+// What the window adds: chunks there are buffers for, and the others.  (1e300: too few buffers fit.)
+__attribute__((always_inline)) inline double stream_cost_window(const ResidentProblem &r, const StreamShape &sh, const StreamTile &d, const StreamFit &f, long long wgs, int slots)
+{
     int nbuf = sh.chunks;
     while (nbuf > 1 && stream_lds(d, sh, nbuf, slots) > ST_LDS_LIMIT) --nbuf;
     if (nbuf < least_buffers(sh, d.sps()) || stream_lds(d, sh, nbuf, slots) > ST_LDS_LIMIT) return 1e300;
-    const long long wgs = (long long)((r.g.K + d.tk() - 1) / d.tk()) * (((long long)r.g.M + mper - 1) / mper);
-    const double rounds = (double)((wgs + 255) / 256), per = wgs / 256.0, stages = (double)((sh.steps + d.sps() - 1) / d.sps());
-    const double first = 64.0 * slots * nbuf, rest = 64.0 * slots * (sh.chunks - nbuf), channels = r.g.K < d.tk() ? r.g.K : d.tk();
-    const double result = 4.0 * channels * mper;
-    return f.launch + rounds * (f.round + f.stage * stages + f.first * first + f.rest * rest) +
-           per * ((r.g.PQ % 16 == 0 ? f.aligned : f.other) * result + f.shared * stages);
+    const double first = 64.0 * slots * nbuf, rest = 64.0 * slots * (sh.chunks - nbuf);
+    return (double)((wgs + 255) / 256) * (f.first * first + f.rest * rest);
 }
 
 hipError_t launch_plan(const ResidentProblem &r, const StreamPlan &p, hipStream_t st)
@@ -767,16 +769,15 @@ hipError_t launch_plan(const ResidentProblem &r, const StreamPlan &p, hipStream_
 
 }  // namespace
 
-bool stream_pick(const ResidentProblem &r, ResidentChoice *c)
+bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, ResidentChoice *c)
 {
     StreamShape sh;
     // (fewer taps: a chunk of the window serves too few stages, and the estimate was fitted on 3x3 and 5x5 kernels)
     if (!stream_shape(r, &sh) || sh.RS < 9) return false;
-    ResidentChoice best[3] = {{0, 0, 1e300}, {0, 0, 1e300}, {0, 0, 1e300}};
-    int seen = 0, mpers[64], slots[64];   // windows are walked once per pixel count
-    for (int t = 0; t < kNumStreamTiles; ++t) {
-        const StreamTile &d = kStreamTiles[t];
-        const long long tk = (r.g.K + d.tk() - 1) / d.tk(), M = r.g.M;
+    ResidentChoice best[3] = {{0, 0, limit}, {0, 0, limit}, {0, 0, limit}};
+    auto pick_in = [&](const StreamTile &d, const StreamFit &f, int t) __attribute__((always_inline)) {   // (a tile known to the compiler: its divisions are shifts)
+        const long long M = r.g.M;
+        const int tk = (r.g.K + d.tk() - 1) / d.tk(), stages = (sh.steps + d.sps() - 1) / d.sps();
         int tried[10], n = 0;
         auto consider = [&](long long mper) {   // whole rounds of workgroups, whole images, the tile
             if (mper > d.tm()) mper = d.tm();
@@ -784,14 +785,10 @@ bool stream_pick(const ResidentProblem &r, ResidentChoice *c)
             for (int i = 0; i < n; ++i)
                 if (tried[i] == (int)mper) return;
             tried[n++] = (int)mper;
-            int at = 0;
-            while (at < seen && mpers[at] != (int)mper) ++at;
-            if (at == seen) {
-                if (seen == 64) return;
-                mpers[seen] = (int)mper;
-                slots[seen++] = max_slots(r, (int)mper, 8);
-            }
-            const ResidentChoice x{t, (int)mper, stream_cost(r, sh, t, (int)mper, slots[at])};
+            const long long wgs = (long long)tk * (((unsigned)M + (unsigned)mper - 1) / (unsigned)mper);
+            ResidentChoice x{t, (int)mper, stream_cost_bare(r, d, f, wgs, stages, (int)mper)};
+            if (x.us >= best[2].us) return;   // (most counts end here, before their windows are walked)
+            x.us += stream_cost_window(r, sh, d, f, wgs, walk.sampled(x.mper));
             for (int k = 0; k < 3; ++k)
                 if (x.us < best[k].us) {
                     for (int j = 2; j > k; --j) best[j] = best[j - 1];
@@ -800,16 +797,21 @@ bool stream_pick(const ResidentProblem &r, ResidentChoice *c)
                 }
         };
         for (int rounds = 1; rounds <= 3; ++rounds) {
-            const long long wide = 256LL * rounds / tk, m = wide > 0 ? (M + wide - 1) / wide : d.tm();
+            const int wide = 256 * rounds / tk;
+            const long long m = wide > 0 ? ((unsigned)M + (unsigned)wide - 1) / (unsigned)wide : d.tm();
             consider(m);
             consider((m + 31) / 32 * 32);
         }
         consider(d.tm());
         consider(r.g.PQ);
-    }
+    };
+    int index = 0;
+#define C2I8_CASE(fk, fm, wk, wm, ds, nst) pick_in(StreamTile{fk, fm, wk, wm, ds, nst}, kStreamFit[index], index), ++index;
+    C2I8_STREAM_LIST(C2I8_CASE)
+#undef C2I8_CASE
     for (const ResidentChoice &x : best) {   // (the window was sampled: the plan knows whether it fits)
         StreamPlan p, whole;
-        if (x.us < 1e300 && stream_plan(r, x.tile, x.mper, &p)) {
+        if (x.mper > 0 && stream_plan(r, x.tile, x.mper, &p)) {
             *c = x;
             // Tiles that begin inside a 64-byte sector write it in two parts: on planes of whole sectors the count goes up to whole ones,
             // where that is at most an eighth more, cuts no image that was divided evenly, and leaves the window as many buffers.  41

@@ -44,9 +44,6 @@ __device__ __forceinline__ WindowRange tile_window(const A &a, int m0, int m1, i
     *n1_out = n1;
     return WindowRange{n0, lo0, len0, a.full8, len0 + (n1 > n0 ? (n1 - n0 - 1) * a.full8 + len_last : 0), a.mg_full8};
 }
-// Slots of the windows of `mper` output pixels: the most over the first `tiles` tiles of the problem (0: all of them; tile
-// starts repeat within an image after PQ / gcd(mper, PQ) tiles).
-int max_slots(const ResidentProblem &r, int mper, int tiles);
 
 // The tensor a window is filled from.
 struct WindowSource {

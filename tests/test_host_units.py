@@ -34,6 +34,11 @@ def test_window_fills_stay_inside_tensor_and_window(run_host):
     assert run_host("window_fill", ("-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include")) == (0, "ok")
 
 
+def test_window_walk_against_its_definition(run_host):
+    """The estimates' window sizes: 20000 random problems, up to images of 2^28 pixels, against integer divisions."""
+    assert run_host("window_walk", ("-x", "c++")) == (0, "ok")
+
+
 # (dims, layout, block): layers whose one-shot and kept-weights calls both take the resident kernel, with different tiles or pixels
 SHARED_LAYERS = [((266, 64, 56, 56, 64, 5, 5, 1, 2), 3, 0), ((2, 128, 48, 48, 64, 1, 1, 1, 0), 1, 64), ((132, 32, 14, 14, 512, 5, 5, 1, 2), 3, 0),
                  ((12, 32, 56, 56, 281, 1, 1, 1, 0), 3, 0), ((2, 70, 37, 37, 163, 5, 5, 1, 2), 3, 0), ((350, 32, 56, 56, 51, 3, 3, 1, 1), 3, 0)]
