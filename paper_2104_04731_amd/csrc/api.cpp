@@ -413,8 +413,12 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
                     best = us;
                     *n = Route{DIRECT_BAND, {}, pl.cb, pl.depth};
                 }
+                // The smallest streaming tile is for calls of 8 to 14 us, most of them the band kernel's behind a rewrite: there the estimates'
+                // errors decide, and its own is the best of many.  Of 2571 layers 353 went to it or a larger tile wherever an estimate was lower, 1.119
+                // of the other launch's speed in the mean, 17 % of them more than 5 % slower (1 image 512 x 23 x 23 -> 512 stride 2: 10.8 -> 14.5 us);
+                // taken at 0.86 and below 258 do, 1.183, 8 %.
                 ResidentChoice c;
-                if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), walk, best, &c))
+                if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), walk, best, 0.86, &c))
                     *n = Route{DIRECT_STREAM, c, pl.cb, pl.depth};
             }
             return true;
@@ -432,7 +436,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             const int depth64 = (d->C + 63) / 64 * 64 * d->R * d->S;
             ResidentChoice c;
             const double rewrite = 2.8 + 1.0e-6 * (double)d->K * depth64 + SECOND_LAUNCH_US;
-            if (stream_pick(resident_problem(d, pl, 64, depth64, false, nhwc, dil, nullptr, nullptr, out), walk, 0.95 * best - rewrite, &c))
+            if (stream_pick(resident_problem(d, pl, 64, depth64, false, nhwc, dil, nullptr, nullptr, out), walk, 0.95 * best - rewrite, 1, &c))
                 *n = Route{DIRECT_STREAM_REWRITE, c, 64, depth64};
         }
         return true;

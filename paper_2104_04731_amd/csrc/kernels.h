@@ -82,7 +82,7 @@ struct ResidentProblem {
     int pixel_bytes;
     long long img_bytes;
     int raw_weights;     // g.wq is KCRS as it came (3 x 3 only), not in depth order
-    int kept;            // the weights were rewritten before this call (what the estimates are for)
+    int kept;            // the weights were rewritten before this call (which of the two estimates applies)
 };
 struct ResidentChoice {
     int tile, mper;   // mper: output pixels of a workgroup
@@ -104,7 +104,9 @@ hipError_t launch_resident_forced(const ResidentProblem &r, int tile, int mper, 
 int stream_num_tiles();
 TileInfo stream_tile_info(int tile);     // rows, cols: output channels and (at most) pixels of a workgroup
 bool stream_applies(const ResidentProblem &r, int tile, int mper);
-bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, ResidentChoice *c);   // false: outside the kernel's domain, or nothing below `limit` microseconds
+// False where no estimate is below `limit` microseconds, and outside the kernel's domain.  smallest: the smallest tile alone has to be
+// below that much of it.
+bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, double smallest, ResidentChoice *c);
 hipError_t launch_stream(const ResidentProblem &r, int tile, int mper, hipStream_t st);
 hipError_t launch_stream_forced(const ResidentProblem &r, int tile, int mper, hipStream_t st);
 // The band kernel on the same problem (NCHW, weights in blocks of 64): estimated launch time; false: not its domain.

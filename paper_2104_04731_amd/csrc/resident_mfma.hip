@@ -563,16 +563,19 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
 }
 
 
-// Launch time in microseconds where the call brings raw weights: what the choice between stored rewrites and this kernel was
-// fitted with, from 37900 measured launches of 4900 layers (every tile, 2 to 5 pixel counts each; a third
+// Launch time in microseconds where the call brings its weights raw, turned around here or rewritten within the call: what the choice
+// between stored rewrites and this kernel was fitted with, from 37900 measured launches of 4900 layers (every tile, 2 to 5 pixel counts each; a third
 // of the layers held back).  A launch; per round of workgroups that fit the chip the chain of MFMAs of one wave and the
 // rounds of window loads; for the busiest compute unit its MFMAs and the bytes in and out; for the whole chip all
 // workgroups' bytes, which share the memory system (per: workgroups per compute unit -- without it a layer of 200 channels and
 // more came out right on half a chip and 8 % low on a full one); from the second round on window and weights once more, because a
 // round's loads queue behind the results that all workgroups of the round before store at its end; raw weights go through
 // the registers in rounds of loads of their own, more than twice as long where the rows of 9 C bytes do not start on dwords.
-// Near each layer's best launch, on the layers held back: mean error 5 %; by channels, weights and workgroups no group is off
-// by more than 4 %, but for kept weights of 200 channels and more in several rounds (9 % low).
+// It was fitted before the wide fill, the depth parts and the raw weights' units in flight, and knows none of them.  What that means now, over 10000
+// one-shot, NHWC and dilated calls: near each layer's best launch 12 % mean error on raw weights (11 % high in the median), 9 % on
+// rewritten ones (6 % high), 18 % from NHWC (value-by-value stores of odd K are not in it) -- but what it chooses, tile, pixels and this
+// kernel or the stored path, loses 1.0 % against the best of what was measured, and 0.9 % if the chosen launch's time were known
+// exactly.  Fits per tile with an error of 6 % chose worse (1.4 %: 1x1 layers, and candidates unlike the fitted ones), as did scaling this one's level (1.0 %).
 __attribute__((always_inline)) inline double resident_cost_given(const ResidentProblem &r, const ResidentShape &sh, const ResTile &d, int mper, int tiles_m, int slots)
 {
     const GemmProblem &g = r.g;
@@ -600,7 +603,7 @@ __attribute__((always_inline)) inline double resident_cost_given(const ResidentP
 }
 
 // The same for kept weights, fitted per tile to 60000 measured launches of 13400 layers (two pixel counts each; a third of the
-// layers held back: mean error 5 to 6 %, 8 with the formula above, which knows neither depth parts nor the wide fill).  A launch; per round of workgroups that
+// layers held back: mean error 5 to 6 %, 8 with the formula above).  A launch; per round of workgroups that
 // fit the chip its fixed part, the chain of MFMAs of one wave and the trips of window loads, in either form of the fill; for the
 // busiest compute unit its MFMAs; for the whole chip the bytes of all windows, weight tiles and results (planes of whole 64-byte
 // sectors, others), which share the memory system; the meeting of depth parts; from the second round on window and weights once

@@ -721,7 +721,10 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
 }
 
 // Launch time in microseconds, fitted per tile to 128000 measured launches of 13400 layers (kept weights, NCHW; a third of the
-// layers held back: mean error 4 %, 7 % for the largest tile, whose clock falls with what it reads).  A launch; per
+// layers held back: mean error 4 %, 7 % for the largest tile, which leaves 208 images 256 x 28 x 28 -> 219 on the stored path: 134 us, here 118).
+// It serves NHWC and dilated calls too, from which nothing was fitted: 606 of them that it sends here take 0.64 (dilated) and 0.86
+// (NHWC) of the best other launch in the mean, 0.94 where K is not a multiple of four (results value by value, in no term; one in six loses
+// more than 5 % there, of the others one in fifty).  A launch; per
 // round of workgroups (one per compute unit) its fixed part, its ring stages, the window bytes it begins with and those that come
 // later; the result's bytes on planes of whole 64-byte sectors and on others; what the stages of all workgroups share.
 struct StreamFit {
@@ -769,12 +772,13 @@ hipError_t launch_plan(const ResidentProblem &r, const StreamPlan &p, hipStream_
 
 }  // namespace
 
-bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, ResidentChoice *c)
+bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, double smallest, ResidentChoice *c)
 {
     StreamShape sh;
     // (fewer taps: a chunk of the window serves too few stages, and the estimate was fitted on 3x3 and 5x5 kernels)
     if (!stream_shape(r, &sh) || sh.RS < 9) return false;
     ResidentChoice best[3] = {{0, 0, limit}, {0, 0, limit}, {0, 0, limit}};
+    bool larger = false;   // a larger tile is below the limit
     auto pick_in = [&](const StreamTile &d, const StreamFit &f, int t) __attribute__((always_inline)) {   // (a tile known to the compiler: its divisions are shifts)
         const long long M = r.g.M;
         const int tk = (r.g.K + d.tk() - 1) / d.tk(), stages = (sh.steps + d.sps() - 1) / d.sps();
@@ -789,6 +793,7 @@ bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, Resid
             ResidentChoice x{t, (int)mper, stream_cost_bare(r, d, f, wgs, stages, (int)mper)};
             if (x.us >= best[2].us) return;   // (most counts end here, before their windows are walked)
             x.us += stream_cost_window(r, sh, d, f, wgs, walk.sampled(x.mper));
+            larger = larger || (t != kNumStreamTiles - 1 && x.us < limit);
             for (int k = 0; k < 3; ++k)
                 if (x.us < best[k].us) {
                     for (int j = 2; j > k; --j) best[j] = best[j - 1];
@@ -809,6 +814,7 @@ bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, Resid
 #define C2I8_CASE(fk, fm, wk, wm, ds, nst) pick_in(StreamTile{fk, fm, wk, wm, ds, nst}, kStreamFit[index], index), ++index;
     C2I8_STREAM_LIST(C2I8_CASE)
 #undef C2I8_CASE
+    if (!larger && best[0].us >= smallest * limit) return false;
     for (const ResidentChoice &x : best) {   // (the window was sampled: the plan knows whether it fits)
         StreamPlan p, whole;
         if (x.mper > 0 && stream_plan(r, x.tile, x.mper, &p)) {
