@@ -632,7 +632,7 @@ __attribute__((always_inline)) inline double resident_cost(const ResidentProblem
     const double rounds = (double)((wgs + 256 * fit - 1) / (256 * fit));
     const int blocks = (mper + 32 * d.fm - 1) / (32 * d.fm), runs = (slots + 63) / 64;
     const double chain = (double)((blocks + d.nw - 1) / d.nw) * d.fm * (d.tk / 32) * 2 * sh.steps / parts;
-    const bool wide = (slots >= 128 || slots * 5 >= runs * 256) && runs * sh.C16 >= d.nw * 64;   // (window_from_nchw)
+    const bool wide = r.H * r.W >= 64 && (slots >= 128 || slots * 5 >= runs * 256) && runs * sh.C16 >= d.nw * 64;   // (window_from_nchw)
     const double trips = wide ? (double)((runs * sh.C16 + d.nw * 128 - 1) / (d.nw * 128)) : (double)((slots / 8 * (sh.C16 / 4) + d.nw * 256 - 1) / (d.nw * 256));
     const double mfma = d.tk / 32 * d.fm * blocks * 2.0 * sh.steps / 4, window = (double)slots * sh.C16, weights = (double)sh.steps * d.tk * 64;
     const double result = 4.0 * d.tk * mper;

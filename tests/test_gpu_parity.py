@@ -1367,6 +1367,22 @@ def test_resident_every_tile(lib, cfg):
     assert not small or {(t, many, r, h) for t in range(len(lib.resident_tiles())) for many in (False, True) for r in raw for h in (False, True)} <= ran
 
 
+@pytest.mark.parametrize("H,W", [(7, 9), (8, 8), (5, 13), (1, 64), (3, 3)])
+@pytest.mark.parametrize("C", [64, 70])
+def test_resident_window_over_small_planes(lib, H, W, C):
+    """Windows of many images on both sides of the plane size from which they are filled in 64-byte runs, at an odd address."""
+    cfg = ConvShape(f"small-planes-{C}-{H}x{W}", 40, C, H, W, 33, 3, 3, 1, 1)
+    x, w, want = oracle_conv(cfg)
+    t = torch.empty(x.size + 1, dtype=torch.int8, device=DEV)
+    t[1:] = dev(x).view(-1)
+    wq = lib.pack_weights(dev(w), lib.LAYOUT_PACKED, 64)
+    tiles = [(tile, 192) for tile in range(len(lib.resident_tiles()))] + [(tile, cols) for tile, (_, cols, _) in lib.stream_tiles().items()]
+    for tile, pixels in tiles:
+        if lib.resident_applies(cfg.dims(), 64, tile, pixels):
+            out = torch.full(want.shape, -7, dtype=torch.int32, device=DEV)
+            assert np.array_equal(host(lib.conv2d_int8_resident(cfg.dims(), t[1:].view(x.shape), wq, out, 64, tile, pixels)), want), (tile, pixels)
+
+
 # Workgroups with fewer blocks of pixels than waves, deep enough (16 steps of depth) for several waves to share a block: parts of
 # unequal depth, a last tile with fewer blocks than the others, channels that fill no piece, both results, every weight form.
 RESIDENT_PARTS = [
