@@ -45,7 +45,7 @@ struct StreamArgs {
     long long img_bytes, src_bytes;
     int zero_off, win_off, tab_off;
     int tiles_k, tiles_m, tiles_fast, m_fastest, mper;
-    unsigned mg_PQ, mg_Q, mg_tiles_fast, mg_full8, mg_g16, mg_S, mg_R, mg_RS, mg_sub;
+    unsigned mg_PQ, mg_Q, mg_tiles_fast, mg_full8, mg_g16, mg_S, mg_R, mg_RS;
     int sub;                       // 64-channel chunks of a weight block (blocks of 64 and more), else 0
 };
 
@@ -712,7 +712,7 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
         a.tiles_fast = a.m_fastest ? a.tiles_m : a.tiles_k;
     }
     a.mg_PQ = magic(g.PQ), a.mg_Q = magic(g.Q), a.mg_tiles_fast = magic(a.tiles_fast), a.mg_full8 = magic(a.full8);
-    a.mg_g16 = magic(a.g16), a.mg_S = magic(g.S), a.mg_R = magic(g.R), a.mg_RS = magic(sh.RS), a.mg_sub = magic(sh.sub);
+    a.mg_g16 = magic(a.g16), a.mg_S = magic(g.S), a.mg_R = magic(g.R), a.mg_RS = magic(sh.RS);
     out->tile = tile;
     out->source = sh.source;
     out->uni = sh.uni;
