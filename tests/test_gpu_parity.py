@@ -1474,6 +1474,34 @@ def test_stream_results_at_every_alignment(lib, pixels):
                 assert (got[:behind] == -7).all() and (got[behind + want.size:] == -7).all(), (tile, nhwc, behind)
 
 
+def test_direct_stages_past_32_bits(lib):
+    """Input and result larger than 2^31 bytes: the window fills (64-byte runs, 8-byte units, NHWC pieces), depth parts and the streaming
+    stage, at the first image, the ones around 2^31 bytes of input and of result, and the last."""
+    N, C, H, W, K = 5500, 128, 56, 56, 32
+    gen = torch.Generator(device=DEV).manual_seed(31)
+    w = torch.randint(-128, 128, (K, C, 3, 3), dtype=torch.int8, device=DEV, generator=gen)
+    wq = lib.pack_weights(w, lib.LAYOUT_PACKED, 64)
+    flat = torch.randint(-128, 128, (N * C * H * W,), dtype=torch.int8, device=DEV, generator=gen)
+    assert flat.numel() > 2**31 and 4 * N * K * H * W > 2**31
+    look = sorted({0, 2**31 // (C * H * W), 2**31 // (C * H * W) + 1, 2**31 // (4 * K * H * W), 2**31 // (4 * K * H * W) + 1, N - 1})
+    ran = set()
+    for nhwc in (False, True):
+        x = flat.view((N, H, W, C) if nhwc else (N, C, H, W))
+        some = host(x[look].permute(0, 3, 1, 2).contiguous() if nhwc else x[look].contiguous())
+        want = direct.conv2d_int8(some, host(w), 1, 1)
+        tiles = [(tile, pixels, weights) for tile in range(len(lib.resident_tiles())) for pixels in (32, 128) for weights in (0, 64)]
+        tiles += [(tile, min(cols, 112), 64) for tile, (_, cols, _) in lib.stream_tiles().items()]
+        for tile, pixels, weights in tiles:
+            if not lib.resident_applies((N, C, H, W, K, 3, 3, 1, 1), weights, tile, pixels, 1, nhwc):
+                continue
+            out = torch.full((N, H, W, K) if nhwc else (N, K, H, W), -7, dtype=torch.int32, device=DEV)
+            lib.conv2d_int8_resident((N, C, H, W, K, 3, 3, 1, 1), x, wq if weights else w, out, weights, tile, pixels, 1, nhwc)
+            got = host(out[look])
+            assert np.array_equal(got.transpose(0, 3, 1, 2) if nhwc else got, want), (tile, pixels, weights, nhwc)
+            ran.add((tile >= lib.TILE_STREAM, pixels, weights, nhwc))
+    assert {(s, p, cb, h) for s, p, cb in ((False, 32, 0), (False, 32, 64), (False, 128, 0), (False, 128, 64), (True, 112, 64)) for h in (False, True)} <= ran
+
+
 # Calls that the library sends there: kept weights, and raw ones rewritten first (NCHW, NHWC, dilated).
 STREAM_CALLS = [ConvShape("sc-s2", 60, 400, 14, 14, 64, 3, 3, 2, 1), ConvShape("sc-k40", 100, 512, 7, 7, 40, 3, 3, 1, 1), ConvShape("sc-5x5", 100, 300, 14, 14, 20, 5, 5, 1, 2)]
 
