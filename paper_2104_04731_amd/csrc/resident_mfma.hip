@@ -46,6 +46,7 @@ struct ResidentArgs {
     int stream_out;                // NKPQ result with non-temporal stores
     unsigned mg_nblk, mg_parts, mg_PQ, mg_Q, mg_tiles_k, mg_c16q, mg_cq, mg_full8, mg_g16, mg_S, mg_R, mg_u16;
     int cq, u16;                   // channel quads / 16-byte units of a record that are loaded
+    int wide;                      // WindowSource::wide
 };
 
 __device__ __forceinline__ void res_dma16(const int8_t *src, unsigned lds_base)
@@ -200,7 +201,7 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
         }
     }
     // ---- window ---------------------------------------------------------------------------------------------------
-    const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride};
+    const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride, a.wide};
     if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
     else window_from_pixels<NT, 4>(from, range, a.u16, a.mg_u16, smem + a.win_off, a.pitch, tid);
     if constexpr (RAW) {
@@ -537,6 +538,7 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     a.mg_nblk = magic(a.nblk);
     a.mg_parts = magic(a.parts);
     const long long slots = window_walk(r).most(mper);
+    a.wide = window_wide_units(HW, slots, r.C);
     const long long wts = ((long long)a.steps + 1) * d.tk * 64, lds = resident_lds(d, a.steps, sh.uni, slots, a.pitch, a.parts);
     if (lds > RES_LDS_LIMIT || (long long)((g.R - 1) * r.W + g.S - 1) * dil * a.pitch + a.C16 > (1LL << 30)) return false;
     // whole 64-byte sectors per store instruction: kept out of the caches on the way (64 images 56 x 56, 64 -> 64: 20.3 ->
@@ -632,7 +634,7 @@ __attribute__((always_inline)) inline double resident_cost(const ResidentProblem
     const double rounds = (double)((wgs + 256 * fit - 1) / (256 * fit));
     const int blocks = (mper + 32 * d.fm - 1) / (32 * d.fm), runs = (slots + 63) / 64;
     const double chain = (double)((blocks + d.nw - 1) / d.nw) * d.fm * (d.tk / 32) * 2 * sh.steps / parts;
-    const bool wide = r.H * r.W >= 64 && (slots >= 128 || slots * 5 >= runs * 256) && runs * sh.C16 >= d.nw * 64;   // (window_from_nchw)
+    const bool wide = (slots >= 128 || slots * 5 >= runs * 256) && runs * sh.C16 >= d.nw * 64;   // (window_from_nchw)
     const double trips = wide ? (double)((runs * sh.C16 + d.nw * 128 - 1) / (d.nw * 128)) : (double)((slots / 8 * (sh.C16 / 4) + d.nw * 256 - 1) / (d.nw * 256));
     const double mfma = d.tk / 32 * d.fm * blocks * 2.0 * sh.steps / 4, window = (double)slots * sh.C16, weights = (double)sh.steps * d.tk * 64;
     const double result = 4.0 * d.tk * mper;

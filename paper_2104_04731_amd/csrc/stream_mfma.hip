@@ -42,6 +42,7 @@ struct StreamArgs {
     int chunks, nbuf, buf_bytes;   // 64-channel chunks, window buffers, bytes of one
     int full8;                     // slots of a whole image (its range rounded up to 8 pixels)
     int pstride;                   // bytes from pixel to pixel (NHWC)
+    int wide;                      // WindowSource::wide
     long long img_bytes, src_bytes;
     int zero_off, win_off, tab_off;
     int tiles_k, tiles_m, tiles_fast, m_fastest, mper;
@@ -263,7 +264,7 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
     // (every buffer there is: the loads of many rounds share one trip to memory)
     const int first_chunks = min(a.nbuf, a.chunks);
     if constexpr (SRC == ST_NCHW) {
-        const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, 0};
+        const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, 0, a.wide};
         const int cq = min(first_chunks * 16, (a.C1 + 4) >> 2);
         window_from_nchw_to<NT, 4>(from, w, cq, magic_for_device(cq), [&](int slot, int c4) { return smem + a.win_off + (c4 >> 6) * a.buf_bytes + slot * ST_PITCH + (c4 & 63); },
                                    ST_PITCH, tid);
@@ -686,6 +687,7 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
     const long long images = mper / PQ + 2;
     if (images * PQ * g.K * 4 >= (1LL << 32) || images * r.img_bytes > 0x7FFFFFFFLL) return false;   // 32-bit offsets from the tile's first image
     const long long slots = window_walk(r).most(mper);
+    a.wide = window_wide_units(HW, slots, r.C);
     const int least = least_buffers(sh, d.sps());
     int nbuf = sh.chunks;
     while (nbuf > least && stream_lds(d, sh, nbuf, slots) > ST_LDS_LIMIT) --nbuf;

@@ -51,7 +51,14 @@ struct WindowSource {
     long long img_bytes, src_bytes;   // of an image, of the tensor
     int C1, HW;                       // last channel, pixels of an image
     int pstride;                      // pixel-major: bytes from pixel to pixel
+    int wide = 4;                     // 64-byte runs: units of a run and channel quad, or 0: not taken
 };
+
+// WindowSource::wide for C channels of HW pixels in windows of up to `slots`: no runs on planes of less than 64 pixels, where one holds the
+// ends of several images' rows, but for two such images (under 128 slots) of whole quads.  Layers on 7 x 7 and 7 x 8, with runs -> without: 65
+// whose channels fill no quad 1.05 in the mean (503 images 114 x 7 x 7 -> 32 1x1 8.1 -> 7.2 us), 100 with whole quads 1.02, the 60 small windows of whole quads
+// 0.99.  Made on the host: a test of the plane's size in the kernel cost it 360 bytes of code and calls of 8 us 3 %.
+static inline int window_wide_units(long long HW, long long slots, int C) { return HW >= 64 || (slots < 128 && C % 4 == 0) ? 4 : 0; }
 
 typedef unsigned long long u64_a1 __attribute__((aligned(1)));
 
@@ -143,15 +150,13 @@ __device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const Wi
 // tensor's end, whole quads only: scalar bases and one 32-bit offset per unit.)  The other form from 128 pixels on, or where
 // its runs of 64 are four fifths full, if it has work for every thread: below, its idle lanes cost more than its loads save
 // (2 images 292 x 20 x 20 -> 66, 88 pixels: 8.2 us, 9.4 with it; 15 images 256 x 7 x 7 -> 26: 9.4 and 9.0; 8 images 64 x 7 x 7 ->
-// 130: 4.7 and 4.9).  Nor on planes of less than 64 pixels, where a run
-// holds the ends of several images' rows (1200 layers on 7 x 7 and 7 x 8: 1.012 of its speed without it, 503 images 114 x 7 x 7 -> 32 1x1 8.1 -> 7.2 us;
-// two images 256 x 7 x 7 at stride 2 in 512 threads lose 1 % in the mean, 8 at most).
+// 130: 4.7 and 4.9).
 // place(slot, channel): where a record's dword of four channels goes.
 template <int NT, int B, typename Place>
 __device__ __forceinline__ void window_from_nchw_to(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, Place &&place, int pitch, int tid)
 {
     const int runs = (w.slots + 63) >> 6;
-    if (t.HW >= 64 && (w.slots >= 128 || w.slots * 5 >= runs * 256) && runs * 4 * cq >= NT && window_wide_nchw<NT, B>(t, w, cq, mg_cq, place, pitch, tid)) return;
+    if ((w.slots >= 128 || w.slots * 5 >= runs * 256) && runs * cq * t.wide >= NT && window_wide_nchw<NT, B>(t, w, cq, mg_cq, place, pitch, tid)) return;
     const int units = cq * (w.slots >> 3);
     const long long img0 = (long long)w.n0 * t.img_bytes;
     if (w.slots == w.len0 && t.C1 + 1 == 4 * cq && img0 + (long long)t.C1 * t.HW + w.lo0 + w.slots <= t.src_bytes) {
