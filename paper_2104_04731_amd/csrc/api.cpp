@@ -413,12 +413,12 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
                     best = us;
                     *n = Route{DIRECT_BAND, {}, pl.cb, pl.depth};
                 }
-                // The smallest streaming tile is for calls of 8 to 14 us, most of them the band kernel's behind a rewrite: there the estimates'
-                // errors decide, and its own is the best of many.  Of 2571 layers 353 went to it or a larger tile wherever an estimate was lower, 1.119
-                // of the other launch's speed in the mean, 17 % of them more than 5 % slower (1 image 512 x 23 x 23 -> 512 stride 2: 10.8 -> 14.5 us);
-                // taken at 0.86 and below 258 do, 1.183, 8 %.
+                // The smallest streaming tile is for calls of 8 to 14 us.  Against the stored path the estimates' errors decide there, and its own is
+                // the best of many: of 2571 layers 353 went to streaming wherever an estimate was lower, at 1.119 of the other launch's speed in
+                // the mean, 17 % of them more than 5 % slower (1 image 512 x 23 x 23 -> 512 stride 2: 10.8 -> 14.5 us); with the smallest tile at 0.86 of
+                // the stored path's estimate and below 262 do, 1.185, 8 %.
                 ResidentChoice c;
-                if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), walk, best, 0.86, &c))
+                if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), walk, best, n->how == TWO_STAGE ? 0.86 : 1, &c))
                     *n = Route{DIRECT_STREAM, c, pl.cb, pl.depth};
             }
             return true;
