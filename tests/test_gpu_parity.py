@@ -1502,7 +1502,7 @@ def test_direct_stages_past_32_bits(lib):
     assert {(s, p, cb, h) for s, p, cb in ((False, 32, 0), (False, 32, 64), (False, 128, 0), (False, 128, 64), (True, 112, 64)) for h in (False, True)} <= ran
 
 
-# Calls that the library sends there: kept weights, and raw ones rewritten first (NCHW, NHWC, dilated).
+# Calls that the library sends there: kept weights, and raw ones rewritten first (NCHW, NHWC).
 STREAM_CALLS = [ConvShape("sc-s2", 60, 400, 14, 14, 64, 3, 3, 2, 1), ConvShape("sc-k40", 100, 512, 7, 7, 40, 3, 3, 1, 1), ConvShape("sc-5x5", 100, 300, 14, 14, 20, 5, 5, 1, 2)]
 
 
@@ -1528,6 +1528,24 @@ def test_calls_that_stream_their_weights(lib, cfg):
         g.replay()
         torch.cuda.synchronize()
         assert np.array_equal(host(out), want)
+
+
+@pytest.mark.parametrize("dims,d", [((60, 400, 14, 14, 64, 3, 3, 1, 2), 2), ((60, 400, 17, 15, 61, 3, 3, 1, 3), 3)])
+def test_dilated_calls_that_stream_their_weights(lib, dims, d):
+    """Both routes' calls, in a workspace of exactly the size the library asks for."""
+    N, C, H, W, K, R, S, stride, pad = dims
+    x = uniform_int8(983, (N, C, H, W)); w = uniform_int8(984, (K, C, R, S))
+    want = direct.conv2d_int8_dilated(x, w, stride, pad, d)
+    dx, dw = dev(x), dev(w)
+    desc, of = lib._desc(*dims), lib.load()
+    for entry, call, need in ((lib.ENTRY_DILATED, lib.conv2d_int8_dilated, of.conv2d_int8_dilated_workspace_bytes(desc, d, lib.LAYOUT_AUTO, 0)),
+                              (lib.ENTRY_DILATED_DIRECT, lib.conv2d_int8_dilated_direct, of.conv2d_int8_dilated_direct_workspace_bytes(desc, d, 0))):
+        assert lib.query_stage(dims, entry, dilation=d)[0] == lib.STAGE_STREAM_REWRITE
+        ws = torch.full((need + 256,), 85, dtype=torch.int8, device=DEV)
+        out = torch.full(want.shape, -7, dtype=torch.int32, device=DEV)
+        call(dims, d, dx, dw, out=out, workspace=ws[:need])
+        assert np.array_equal(host(out), want)
+        assert bool((ws[need:] == 85).all())
 
 
 # The band kernel on the network's own tensor, asked for: also one output row per band with six blocks of columns, and a grid
