@@ -538,7 +538,7 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     a.mg_nblk = magic(a.nblk);
     a.mg_parts = magic(a.parts);
     const long long slots = window_walk(r).most(mper);
-    a.wide = window_wide_units(HW, slots, r.C);
+    a.wide = window_wide_units(HW);
     const long long wts = ((long long)a.steps + 1) * d.tk * 64, lds = resident_lds(d, a.steps, sh.uni, slots, a.pitch, a.parts);
     if (lds > RES_LDS_LIMIT || (long long)((g.R - 1) * r.W + g.S - 1) * dil * a.pitch + a.C16 > (1LL << 30)) return false;
     // whole 64-byte sectors per store instruction: kept out of the caches on the way (64 images 56 x 56, 64 -> 64: 20.3 ->

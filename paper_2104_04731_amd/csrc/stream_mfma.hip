@@ -687,7 +687,7 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
     const long long images = mper / PQ + 2;
     if (images * PQ * g.K * 4 >= (1LL << 32) || images * r.img_bytes > 0x7FFFFFFFLL) return false;   // 32-bit offsets from the tile's first image
     const long long slots = window_walk(r).most(mper);
-    a.wide = window_wide_units(HW, slots, r.C);
+    a.wide = window_wide_units(HW);
     const int least = least_buffers(sh, d.sps());
     int nbuf = sh.chunks;
     while (nbuf > least && stream_lds(d, sh, nbuf, slots) > ST_LDS_LIMIT) --nbuf;
