@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
                 band_dma16(step, row_lo, lds0 + (unsigned)((js + t) * 2) * 1024u);
                 band_dma16(step, row_hi, lds0 + (unsigned)((js + t) * 2 + 1) * 1024u);
             }
-        window_from_nchw<BAND_WAVES * 64, 4>(from, range, a.cq, a.mg_cq, smem + win_off, a.pitch, threadIdx.x);
+        window_from_nchw<BAND_WAVES * 64, 4, true>(from, range, a.cq, a.mg_cq, smem + win_off, a.pitch, threadIdx.x);
         if (threadIdx.x < 16) *reinterpret_cast<unsigned *>(smem + a.zero_off + threadIdx.x * 4) = 0;
     } else {
         const int last = a.blk_bytes - 16;  // rows past the padded image (a short last band) read this

@@ -166,10 +166,12 @@ __device__ __forceinline__ void res_store_piece(const ResidentArgs &a, const v4i
 // SPLIT: a workgroup has fewer blocks of pixels than waves, and several waves share the depth of each (a form of its own: in the
 // other one's code the smallest launches took half a microsecond longer).
 // RAW: the weights are KCRS (3 x 3), turned into depth order (tap, channel padded to 16) on their way into LDS.
+// RUNS: NCHW windows may be filled in 64-byte runs (a form of its own: that code, jumped over, cost calls of 4 to 6 us 1.0 to 1.6 % on given weights;
+// on raw ones it is always there: 33 layers that jump over it took 1.5 % longer without it).
 // The 64-channel tile of 8 waves keeps two output blocks' sums and the addresses of a whole tap in registers: at two of its
 // workgroups per compute unit it spilled, at one it does not, and its LDS rarely leaves room for two (64 images 56 x 56,
 // 64 -> 64, kept weights: 18.0 -> 17.4 us; 151 images 28 x 28, 128 -> 458: 116 -> 105).
-template <int TK, int NW, int FM, int SRC, bool UNI, bool RAW, bool SPLIT>
+template <int TK, int NW, int FM, int SRC, bool UNI, bool RAW, bool SPLIT, bool RUNS>
 __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) conv_resident_kernel(const ResidentArgs a)
 {
     constexpr int NT = NW * 64, FK = TK / 32;
@@ -202,7 +204,7 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
     }
     // ---- window ---------------------------------------------------------------------------------------------------
     const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride, a.wide};
-    if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
+    if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4, RUNS>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
     else window_from_pixels<NT, 4>(from, range, a.u16, a.mg_u16, smem + a.win_off, a.pitch, tid);
     if constexpr (RAW) {
         // unit: one row, 4 channels; four units' loads in flight (15 images 256 x 7 x 7 -> 26, 4 units per thread: 7.9 us one by
@@ -399,30 +401,21 @@ constexpr ResTile kResTiles[] = {
 constexpr int kNumResTiles = sizeof(kResTiles) / sizeof(kResTiles[0]);
 
 template <int TK, int NW, int FM>
-hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool raw, size_t lds, hipStream_t st)
+hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool raw, bool runs, size_t lds, hipStream_t st)
 {
-    void (*kern)(ResidentArgs);
+    typedef void (*Kernel)(ResidentArgs);
     constexpr bool CAN_SPLIT = TK == 32 && FM == 1;
-    static bool raised[16];
-    const int which = (a.parts > 1) * 8 + pixels * 4 + uni * 2 + raw;
-    switch (which) {
-        case 0: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, false, false>; break;
-        case 1: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, true, false>; break;
-        case 2: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, false, false>; break;
-        case 3: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, true, false>; break;
-        case 4: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, false, false>; break;
-        case 5: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, true, false>; break;
-        case 6: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, false, false>; break;
-        case 7: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, true, false>; break;
-        case 8: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, false, CAN_SPLIT>; break;
-        case 9: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, false, true, CAN_SPLIT>; break;
-        case 10: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, false, CAN_SPLIT>; break;
-        case 11: kern = conv_resident_kernel<TK, NW, FM, RES_NCHW, true, true, CAN_SPLIT>; break;
-        case 12: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, false, CAN_SPLIT>; break;
-        case 13: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, false, true, CAN_SPLIT>; break;
-        case 14: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, false, CAN_SPLIT>; break;
-        default: kern = conv_resident_kernel<TK, NW, FM, RES_PIXELS, true, true, CAN_SPLIT>; break;
-    }
+#define C2I8_FORMS(SRC, RAW, SPLIT, RUNS) \
+    conv_resident_kernel<TK, NW, FM, SRC, false, RAW, SPLIT, RUNS>, conv_resident_kernel<TK, NW, FM, SRC, true, RAW, SPLIT, RUNS>
+    static constexpr Kernel kernels[] = {
+        C2I8_FORMS(RES_NCHW, false, false, false), C2I8_FORMS(RES_NCHW, false, false, true), C2I8_FORMS(RES_NCHW, true, false, true),
+        C2I8_FORMS(RES_PIXELS, false, false, false), C2I8_FORMS(RES_PIXELS, true, false, false),
+        C2I8_FORMS(RES_NCHW, false, CAN_SPLIT, false), C2I8_FORMS(RES_NCHW, false, CAN_SPLIT, true), C2I8_FORMS(RES_NCHW, true, CAN_SPLIT, true),
+        C2I8_FORMS(RES_PIXELS, false, CAN_SPLIT, false), C2I8_FORMS(RES_PIXELS, true, CAN_SPLIT, false)};
+#undef C2I8_FORMS
+    static bool raised[sizeof(kernels) / sizeof(kernels[0])];
+    const int form = pixels ? 3 + raw : raw ? 2 : runs, which = (a.parts > 1) * 10 + form * 2 + uni;
+    const Kernel kern = kernels[which];
     if (lds > 64 * 1024 && !raised[which]) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
@@ -434,7 +427,7 @@ hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool ra
 struct ResidentPlan {
     ResidentArgs a;
     int tile;
-    bool uni;
+    bool uni, runs;
     size_t lds;
 };
 
@@ -539,6 +532,7 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     a.mg_parts = magic(a.parts);
     const long long slots = window_walk(r).most(mper);
     a.wide = window_wide_units(HW);
+    out->runs = slots < (1 << 20) && window_takes_runs((int)slots, a.cq, a.wide, d.nw * 64);   // (what the largest window takes; more do not fit LDS)
     const long long wts = ((long long)a.steps + 1) * d.tk * 64, lds = resident_lds(d, a.steps, sh.uni, slots, a.pitch, a.parts);
     if (lds > RES_LDS_LIMIT || (long long)((g.R - 1) * r.W + g.S - 1) * dil * a.pitch + a.C16 > (1LL << 30)) return false;
     // whole 64-byte sectors per store instruction: kept out of the caches on the way (64 images 56 x 56, 64 -> 64: 20.3 ->
@@ -710,7 +704,7 @@ static hipError_t launch_plan(const ResidentProblem &r, const ResidentPlan &p, h
     a.out = r.g.out;
     int index = 0;
 #define C2I8_CASE(tk, nw, fm, fit) \
-    if (p.tile == index++) return launch_res_tile<tk, nw, fm>(a, r.pixel_major, p.uni, r.raw_weights, p.lds, st);
+    if (p.tile == index++) return launch_res_tile<tk, nw, fm>(a, r.pixel_major, p.uni, r.raw_weights, p.runs, p.lds, st);
     C2I8_RES_LIST(C2I8_CASE)
 #undef C2I8_CASE
     return hipErrorInvalidValue;

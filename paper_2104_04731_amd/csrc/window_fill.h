@@ -145,6 +145,12 @@ __device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const Wi
     return true;
 }
 
+__host__ __device__ static inline bool window_takes_runs(int slots, int cq, int wide, int threads)
+{
+    const int runs = (slots + 63) >> 6;
+    return (slots >= 128 || slots * 5 >= runs * 256) && runs * cq * wide >= threads;
+}
+
 // NCHW -> records; bytes past the last channel are zero.  cq: channel quads of a record.  The form for few pixels: a unit is 4
 // channels x 8 pixels, neighbouring lanes on neighbouring channel quads (a record's pieces fall into different banks), no
 // lane without work.  (Bound by the instruction count of a lone wave, hence the short path: one image, nothing past the
@@ -152,12 +158,11 @@ __device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const Wi
 // its runs of 64 are four fifths full, if it has work for every thread: below, its idle lanes cost more than its loads save
 // (2 images 292 x 20 x 20 -> 66, 88 pixels: 8.2 us, 9.4 with it; 15 images 256 x 7 x 7 -> 26: 9.4 and 9.0; 8 images 64 x 7 x 7 ->
 // 130: 4.7 and 4.9).
-// place(slot, channel): where a record's dword of four channels goes.
-template <int NT, int B, typename Place>
+// place(slot, channel): where a record's dword of four channels goes.  RUNS: the other form is compiled in.
+template <int NT, int B, bool RUNS, typename Place>
 __device__ __forceinline__ void window_from_nchw_to(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, Place &&place, int pitch, int tid)
 {
-    const int runs = (w.slots + 63) >> 6;
-    if ((w.slots >= 128 || w.slots * 5 >= runs * 256) && runs * cq * t.wide >= NT && window_wide_nchw<NT, B>(t, w, cq, mg_cq, place, pitch, tid)) return;
+    if (RUNS && window_takes_runs(w.slots, cq, t.wide, NT) && window_wide_nchw<NT, B>(t, w, cq, mg_cq, place, pitch, tid)) return;
     const int units = cq * (w.slots >> 3);
     const long long img0 = (long long)w.n0 * t.img_bytes;
     if (w.slots == w.len0 && t.C1 + 1 == 4 * cq && img0 + (long long)t.C1 * t.HW + w.lo0 + w.slots <= t.src_bytes) {
@@ -211,10 +216,10 @@ __device__ __forceinline__ void window_from_nchw_to(const WindowSource &t, const
         }
     }
 }
-template <int NT, int B>
+template <int NT, int B, bool RUNS>
 __device__ __forceinline__ void window_from_nchw(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, unsigned char *win, int pitch, int tid)
 {
-    window_from_nchw_to<NT, B>(t, w, cq, mg_cq, [&](int slot, int c4) { return win + slot * pitch + c4; }, pitch, tid);
+    window_from_nchw_to<NT, B, RUNS>(t, w, cq, mg_cq, [&](int slot, int c4) { return win + slot * pitch + c4; }, pitch, tid);
 }
 
 // Pixel-major source (NHWC) -> records: 16-byte pieces, neighbouring lanes on neighbouring pieces.

@@ -70,11 +70,13 @@ int main()
             const int last = n1 > n0 ? max((end(m1 - 1 - n1 * PQ) + 7) & ~7, 0) : 0, slots = len0 + (n1 > n0 ? (n1 - n0 - 1) * full8 + last : 0);
             const WindowRange range{n0, lo0, len0, full8, slots, magic(full8)};
             const WindowSource from{(const int8_t *)src, (long long)C * HW, bytes, C - 1, HW, C};
-            for (int nhwc = 0; nhwc < 2; ++nhwc) {
+            for (int form = 0; form < 3; ++form) {
+                const int nhwc = form == 2;
                 win.assign((size_t)slots * pitch + 256, 0xEE);
                 for (int tid = 0; tid < 256; ++tid) {
                     if (nhwc) window_from_pixels<256, 4>(from, range, C16 / 16, magic(C16 / 16), win.data(), pitch, tid);
-                    else window_from_nchw<256, 4>(from, range, C16 / 4, magic(C16 / 4), win.data(), pitch, tid);
+                    else if (form) window_from_nchw<256, 4, true>(from, range, C16 / 4, magic(C16 / 4), win.data(), pitch, tid);
+                    else window_from_nchw<256, 4, false>(from, range, C16 / 4, magic(C16 / 4), win.data(), pitch, tid);
                 }
                 for (size_t i = (size_t)slots * pitch; i < win.size(); ++i)
                     if (win[i] != 0xEE) return printf("written past the window: C %d H %d W %d\n", C, H, W), 1;
