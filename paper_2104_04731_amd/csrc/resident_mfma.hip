@@ -671,9 +671,14 @@ bool resident_pick(const ResidentProblem &r, WindowWalk &walk, ResidentChoice *c
     for (int m : sizes) add(m);
     int tiles_m[12];
     for (int i = 0; i < n; ++i) tiles_m[i] = (int)(((long long)r.g.M + mpers[i] - 1) / mpers[i]);
+    // Kept weights: the middle of the two estimates, a twelfth lower (the first one's level is too high).  Their errors differ: of 700 drawn 3x3 and 5x5
+    // layers 17 % were more than 2 % slower with the second one alone than with the first, 7 % with both, 0.987 of the time in the mean.  Kernels
+    // of fewer taps than the second one was fitted on: the first alone (260 1x1 layers 0.956 in the mean; with the second up to 1.6 of it).
+    const bool both = r.kept && r.g.R * r.g.S >= 9;
     auto consider = [&](const ResTile &d, int t) __attribute__((always_inline)) {   // (a tile known to the compiler: its divisions are shifts)
         for (int i = 0; i < n; ++i) {
-            const Cand x{r.kept ? resident_cost(r, sh, d, kResFit[t], mpers[i], tiles_m[i], slots_of[i]) : resident_cost_given(r, sh, d, mpers[i], tiles_m[i], slots_of[i]), t, mpers[i]};
+            Cand x{resident_cost_given(r, sh, d, mpers[i], tiles_m[i], slots_of[i]), t, mpers[i]};
+            if (both) x.cost = 0.46 * (x.cost + resident_cost(r, sh, d, kResFit[t], mpers[i], tiles_m[i], slots_of[i]));
             for (int k = 0; k < 3; ++k)
                 if (x.cost < best[k].cost) {
                     for (int j = 2; j > k; --j) best[j] = best[j - 1];

@@ -40,8 +40,8 @@ def test_window_walk_against_its_definition(run_host):
 
 
 # (dims, layout, block): layers whose one-shot and kept-weights calls both take the resident kernel, with different tiles or pixels
-SHARED_LAYERS = [((266, 64, 56, 56, 64, 5, 5, 1, 2), 3, 0), ((2, 128, 48, 48, 64, 1, 1, 1, 0), 1, 64), ((132, 32, 14, 14, 512, 5, 5, 1, 2), 3, 0),
-                 ((12, 32, 56, 56, 281, 1, 1, 1, 0), 3, 0), ((2, 70, 37, 37, 163, 5, 5, 1, 2), 3, 0), ((350, 32, 56, 56, 51, 3, 3, 1, 1), 3, 0)]
+SHARED_LAYERS = [((266, 64, 56, 56, 64, 5, 5, 1, 2), 3, 0), ((233, 32, 9, 9, 275, 5, 5, 1, 2), 3, 0), ((161, 64, 32, 32, 59, 5, 5, 1, 2), 3, 0),
+                 ((87, 32, 15, 15, 172, 5, 5, 1, 2), 3, 0), ((2, 70, 37, 37, 163, 5, 5, 1, 2), 3, 0), ((215, 64, 7, 7, 432, 5, 5, 1, 2), 3, 0)]
 
 
 @pytest.fixture
@@ -91,3 +91,11 @@ def test_streaming_tiles_begin_on_whole_sectors(lib, dims):
     """Planes of whole 64-byte sectors: the library's own pixel counts cut none."""
     stage, tile, pixels = lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True)
     assert stage == lib.STAGE_STREAM and pixels % 16 == 0
+
+
+@pytest.mark.parametrize("dims", [(66, 64, 19, 19, 34, 1, 1, 2, 0), (14, 192, 23, 23, 182, 1, 1, 2, 0), (1, 256, 31, 31, 424, 1, 1, 1, 0), (66, 64, 17, 17, 328, 1, 1, 1, 0),
+                                  (197, 384, 9, 9, 56, 1, 1, 1, 0), (109, 448, 17, 17, 47, 1, 1, 1, 0)])
+def test_given_and_kept_1x1_weights_take_the_same_launch(lib, dims):
+    """A 1x1 layer of whole 64 channels: its raw weights are in depth order as they are, so the two calls read the same bytes."""
+    raw = lib.query_stage(dims, lib.ENTRY_ONE_SHOT)
+    assert raw[0] == lib.STAGE_RESIDENT and lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True) == raw
