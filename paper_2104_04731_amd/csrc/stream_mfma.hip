@@ -266,7 +266,7 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
     if constexpr (SRC == ST_NCHW) {
         const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, 0, a.wide};
         const int cq = min(first_chunks * 16, (a.C1 + 4) >> 2);
-        window_from_nchw_to<NT, 4, true>(from, w, cq, magic_for_device(cq), [&](int slot, int c4) { return smem + a.win_off + (c4 >> 6) * a.buf_bytes + slot * ST_PITCH + (c4 & 63); },
+        window_from_nchw_to<NT, 4, true, true>(from, w, cq, magic_for_device(cq), [&](int slot, int c4) { return smem + a.win_off + (c4 >> 6) * a.buf_bytes + slot * ST_PITCH + (c4 & 63); },
                                    ST_PITCH, tid);
     } else
         for (int i0 = tid / FT; i0 < first_chunks * rounds; i0 += 2 * BATCH) {

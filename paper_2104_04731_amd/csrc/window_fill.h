@@ -145,10 +145,10 @@ __device__ __forceinline__ bool window_wide_nchw(const WindowSource &t, const Wi
     return true;
 }
 
-__host__ __device__ static inline bool window_takes_runs(int slots, int cq, int wide, int threads)
+__host__ __device__ static inline bool window_takes_runs(int slots, int cq, int wide, int threads, bool deep = false)
 {
     const int runs = (slots + 63) >> 6;
-    return (slots >= 128 || slots * 5 >= runs * 256) && runs * cq * wide >= threads;
+    return (slots >= 128 || slots * 5 >= runs * 256 || (deep && cq > 64 && slots > 32)) && runs * cq * wide >= threads;
 }
 
 // NCHW -> records; bytes past the last channel are zero.  cq: channel quads of a record.  The form for few pixels: a unit is 4
@@ -158,11 +158,14 @@ __host__ __device__ static inline bool window_takes_runs(int slots, int cq, int 
 // its runs of 64 are four fifths full, if it has work for every thread: below, its idle lanes cost more than its loads save
 // (2 images 292 x 20 x 20 -> 66, 88 pixels: 8.2 us, 9.4 with it; 15 images 256 x 7 x 7 -> 26: 9.4 and 9.0; 8 images 64 x 7 x 7 ->
 // 130: 4.7 and 4.9).
+// DEEP (the stream kernel): above 256 channels whatever the idle lanes.  A window's channel rows are then more cache lines than the L1 holds, and the
+// form for few pixels comes back to each of them once per eight pixels: 450 launches on 72 to 96 pixels of 512 channels 0.915 of the time in the
+// mean, at best 0.77 (134 on 40 and 48 pixels 0.947; 5 to 7 chunks of 64 channels 0.96 to 0.98).  Planes of less than 64 pixels: 1.02, at worst 1.4.
 // place(slot, channel): where a record's dword of four channels goes.  RUNS: the other form is compiled in.
-template <int NT, int B, bool RUNS, typename Place>
+template <int NT, int B, bool RUNS, bool DEEP, typename Place>
 __device__ __forceinline__ void window_from_nchw_to(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, Place &&place, int pitch, int tid)
 {
-    if (RUNS && window_takes_runs(w.slots, cq, t.wide, NT) && window_wide_nchw<NT, B>(t, w, cq, mg_cq, place, pitch, tid)) return;
+    if (RUNS && window_takes_runs(w.slots, cq, t.wide, NT, DEEP) && window_wide_nchw<NT, B>(t, w, cq, mg_cq, place, pitch, tid)) return;
     const int units = cq * (w.slots >> 3);
     const long long img0 = (long long)w.n0 * t.img_bytes;
     if (w.slots == w.len0 && t.C1 + 1 == 4 * cq && img0 + (long long)t.C1 * t.HW + w.lo0 + w.slots <= t.src_bytes) {
@@ -219,7 +222,7 @@ __device__ __forceinline__ void window_from_nchw_to(const WindowSource &t, const
 template <int NT, int B, bool RUNS>
 __device__ __forceinline__ void window_from_nchw(const WindowSource &t, const WindowRange &w, int cq, unsigned mg_cq, unsigned char *win, int pitch, int tid)
 {
-    window_from_nchw_to<NT, B, RUNS>(t, w, cq, mg_cq, [&](int slot, int c4) { return win + slot * pitch + c4; }, pitch, tid);
+    window_from_nchw_to<NT, B, RUNS, false>(t, w, cq, mg_cq, [&](int slot, int c4) { return win + slot * pitch + c4; }, pitch, tid);
 }
 
 // Pixel-major source (NHWC) -> records: 16-byte pieces, neighbouring lanes on neighbouring pieces.

@@ -1418,12 +1418,14 @@ def test_resident_depth_parts(lib, cfg):
 
 # The stage that streams the weights, tile and pixels given: every tile on NCHW and NHWC, channels that end in every part of a
 # 64-channel chunk, blocks of 16, 32, 64 and more, fewer steps than a ring has stages, 1x1 (a chunk per step), strides,
-# dilation, tiles over many small images, a tile that sees the border only, windows of more chunks than fit (refilled beside the MFMAs).
+# dilation, tiles over many small images, a tile that sees the border only, windows of more chunks than fit (refilled beside the MFMAs), small windows
+# of more than 256 channels (filled in 64-byte runs whatever the idle lanes).
 STREAM_SHAPES = [
     ConvShape("sm-c64", 2, 64, 14, 14, 64, 3, 3, 1, 1), ConvShape("sm-c100", 3, 100, 10, 11, 70, 3, 3, 1, 1), ConvShape("sm-k300", 2, 256, 14, 14, 300, 3, 3, 1, 1),
     ConvShape("sm-wide", 1, 130, 40, 37, 64, 3, 3, 1, 1), ConvShape("sm-s2", 5, 200, 7, 7, 130, 3, 3, 2, 1), ConvShape("sm-5x5", 2, 20, 21, 18, 64, 5, 5, 1, 2),
     ConvShape("sm-3x3-images", 9, 65, 3, 3, 33, 3, 3, 1, 1), ConvShape("sm-dil3", 2, 48, 20, 17, 64, 3, 3, 1, 3), ConvShape("sm-refilled", 1, 512, 27, 30, 257, 3, 3, 1, 1),
     ConvShape("sm-1x1", 2, 128, 9, 13, 64, 1, 1, 1, 0), ConvShape("sm-c17", 3, 17, 19, 23, 96, 3, 3, 1, 1), ConvShape("sm-2x3-border", 2, 320, 6, 6, 40, 2, 3, 1, 3),
+    ConvShape("sm-c300", 2, 300, 9, 11, 40, 3, 3, 1, 1), ConvShape("sm-c449-two-runs", 1, 449, 20, 23, 33, 3, 3, 1, 1),
 ]
 
 
