@@ -46,7 +46,6 @@ struct ResidentArgs {
     int stream_out;                // NKPQ result with non-temporal stores
     unsigned mg_nblk, mg_parts, mg_PQ, mg_Q, mg_tiles_k, mg_c16q, mg_cq, mg_full8, mg_g16, mg_S, mg_R, mg_u16;
     int cq, u16;                   // channel quads / 16-byte units of a record that are loaded
-    int wide;                      // WindowSource::wide
 };
 
 __device__ __forceinline__ void res_dma16(const int8_t *src, unsigned lds_base)
@@ -167,7 +166,7 @@ __device__ __forceinline__ void res_store_piece(const ResidentArgs &a, const v4i
 // other one's code the smallest launches took half a microsecond longer).
 // RAW: the weights are KCRS (3 x 3), turned into depth order (tap, channel padded to 16) on their way into LDS.
 // RUNS: NCHW windows may be filled in 64-byte runs (a form of its own: that code, jumped over, cost calls of 4 to 6 us 1.0 to 1.6 % on given weights;
-// on raw ones it is always there: 33 layers that jump over it took 1.5 % longer without it).
+// on raw ones it is there for every plane of 64 pixels and more: 33 layers that jump over it took 1.5 % longer without it).
 // The 64-channel tile of 8 waves keeps two output blocks' sums and the addresses of a whole tap in registers: at two of its
 // workgroups per compute unit it spilled, at one it does not, and its LDS rarely leaves room for two (64 images 56 x 56,
 // 64 -> 64, kept weights: 18.0 -> 17.4 us; 151 images 28 x 28, 128 -> 458: 116 -> 105).
@@ -203,7 +202,7 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
         }
     }
     // ---- window ---------------------------------------------------------------------------------------------------
-    const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride, a.wide};
+    const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride};
     if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4, RUNS>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
     else window_from_pixels<NT, 4>(from, range, a.u16, a.mg_u16, smem + a.win_off, a.pitch, tid);
     if constexpr (RAW) {
@@ -408,13 +407,13 @@ hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool ra
 #define C2I8_FORMS(SRC, RAW, SPLIT, RUNS) \
     conv_resident_kernel<TK, NW, FM, SRC, false, RAW, SPLIT, RUNS>, conv_resident_kernel<TK, NW, FM, SRC, true, RAW, SPLIT, RUNS>
     static constexpr Kernel kernels[] = {
-        C2I8_FORMS(RES_NCHW, false, false, false), C2I8_FORMS(RES_NCHW, false, false, true), C2I8_FORMS(RES_NCHW, true, false, true),
+        C2I8_FORMS(RES_NCHW, false, false, false), C2I8_FORMS(RES_NCHW, false, false, true), C2I8_FORMS(RES_NCHW, true, false, false), C2I8_FORMS(RES_NCHW, true, false, true),
         C2I8_FORMS(RES_PIXELS, false, false, false), C2I8_FORMS(RES_PIXELS, true, false, false),
-        C2I8_FORMS(RES_NCHW, false, CAN_SPLIT, false), C2I8_FORMS(RES_NCHW, false, CAN_SPLIT, true), C2I8_FORMS(RES_NCHW, true, CAN_SPLIT, true),
+        C2I8_FORMS(RES_NCHW, false, CAN_SPLIT, false), C2I8_FORMS(RES_NCHW, false, CAN_SPLIT, true), C2I8_FORMS(RES_NCHW, true, CAN_SPLIT, false), C2I8_FORMS(RES_NCHW, true, CAN_SPLIT, true),
         C2I8_FORMS(RES_PIXELS, false, CAN_SPLIT, false), C2I8_FORMS(RES_PIXELS, true, CAN_SPLIT, false)};
 #undef C2I8_FORMS
     static bool raised[sizeof(kernels) / sizeof(kernels[0])];
-    const int form = pixels ? 3 + raw : raw ? 2 : runs, which = (a.parts > 1) * 10 + form * 2 + uni;
+    const int form = pixels ? 4 + raw : raw * 2 + runs, which = (a.parts > 1) * 12 + form * 2 + uni;
     const Kernel kern = kernels[which];
     if (lds > 64 * 1024 && !raised[which]) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -531,8 +530,8 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     a.mg_nblk = magic(a.nblk);
     a.mg_parts = magic(a.parts);
     const long long slots = window_walk(r).most(mper);
-    a.wide = window_wide_units(HW);
-    out->runs = slots < (1 << 20) && window_takes_runs((int)slots, a.cq, a.wide, d.nw * 64);   // (what the largest window takes; more do not fit LDS)
+    // (what the largest window takes, on planes that take runs at all; raw weights: see the kernel's RUNS)
+    out->runs = window_wide_units(HW) && (r.raw_weights || (slots < (1 << 20) && window_takes_runs((int)slots, a.cq, window_wide_units(HW), d.nw * 64)));
     const long long wts = ((long long)a.steps + 1) * d.tk * 64, lds = resident_lds(d, a.steps, sh.uni, slots, a.pitch, a.parts);
     if (lds > RES_LDS_LIMIT || (long long)((g.R - 1) * r.W + g.S - 1) * dil * a.pitch + a.C16 > (1LL << 30)) return false;
     // whole 64-byte sectors per store instruction: kept out of the caches on the way (64 images 56 x 56, 64 -> 64: 20.3 ->

@@ -1378,9 +1378,10 @@ def test_resident_window_over_small_planes(lib, H, W, C):
     wq = lib.pack_weights(dev(w), lib.LAYOUT_PACKED, 64)
     tiles = [(tile, 192) for tile in range(len(lib.resident_tiles()))] + [(tile, cols) for tile, (_, cols, _) in lib.stream_tiles().items()]
     for tile, pixels in tiles:
-        if lib.resident_applies(cfg.dims(), 64, tile, pixels):
-            out = torch.full(want.shape, -7, dtype=torch.int32, device=DEV)
-            assert np.array_equal(host(lib.conv2d_int8_resident(cfg.dims(), t[1:].view(x.shape), wq, out, 64, tile, pixels)), want), (tile, pixels)
+        for weights, cb in ((wq, 64), (dev(w), 0)):
+            if (cb or tile < lib.TILE_STREAM) and lib.resident_applies(cfg.dims(), cb, tile, pixels):
+                out = torch.full(want.shape, -7, dtype=torch.int32, device=DEV)
+                assert np.array_equal(host(lib.conv2d_int8_resident(cfg.dims(), t[1:].view(x.shape), weights, out, cb, tile, pixels)), want), (tile, pixels, cb)
 
 
 # Workgroups with fewer blocks of pixels than waves, deep enough (16 steps of depth) for several waves to share a block: parts of
