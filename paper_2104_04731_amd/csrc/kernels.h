@@ -178,6 +178,8 @@ struct WindowProblem {
 int window_depth(int C, int R, int S);          // 0 if the padded depth exceeds what the kernel unrolls
 bool window_fits(const WindowProblem &g);       // depth, image width and LDS window within the kernel's limits
 hipError_t launch_window_conv(const WindowProblem &g, hipStream_t st);
+// The same on large results (stencil_mfma.hip); false: the window kernel's.
+bool launch_stencil_conv(const WindowProblem &g, hipStream_t st, hipError_t *e);
 hipError_t launch_pack_weights_window(int K, int C, int R, int S, const int8_t *src, int8_t *dst, hipStream_t st);
 // The same for 1x1 convolutions over whole 64-channel multiples: a workgroup turns its pixels
 // around in LDS; the weights are used as they are ([K][C]).

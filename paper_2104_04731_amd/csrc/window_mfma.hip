@@ -521,7 +521,8 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     const long long pitch = (((long long)(QT - 1) * stride_w + S4 + 3) + 3) / 4 * 4;
     // whole 64-byte sectors per 16 pixels, and more than the caches keep: stored past them.  3 x 224 x 224, 7 x 7 / 2 -> 64, plain ->
     // streamed: 87 images (279 MB) 76 -> 64 us, 300 (963 MB) 239 -> 207, 512 396 -> 350: 4.6 to 4.9 TB/s all along.  Over ten layers of
-    // 300 MB to 1.6 GB 2 to 27 % less, level in six cases of forty, and 7 % more for a 3 x 3 / 2 -> 32 from 960 MB on.  At 205 MB
+    // 300 MB to 1.6 GB 2 to 27 % less, level in six cases of forty, and 7 % more for a 3 x 3 / 2 -> 32 from 960 MB on.  
+    // (most results of this size are the stencil kernel's, in stencil_mfma.hip; what it leaves comes here.)  At 205 MB
     // it gains on a result that is written once (56 -> 48), but one that is written again is still in the last-level cache and takes 37
     // with plain stores.  (Partial sectors come out up to 2.5 times slower that way.)
     w.stream_out = !g.nhwc && !g.act.out && g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && 4.0 * g.N * g.K * g.P * g.Q > STREAM_BYTES;
@@ -584,6 +585,8 @@ hipError_t launch_window_conv(const WindowProblem &g, hipStream_t st)
 {
     WindowArgs a;
     if (!window_plan(g, &a)) return hipErrorInvalidValue;
+    hipError_t e;
+    if (launch_stencil_conv(g, st, &e)) return e;
     const int depth = a.w_pitch - 16;
     const int kb = g.K > 32 ? 64 : 32;
     const dim3 grid((unsigned)(g.N * a.tiles_p * a.tiles_q), (unsigned)((g.K + kb - 1) / kb));

@@ -1321,6 +1321,50 @@ def test_window_streamed(lib, K):
     assert np.array_equal(host(out[-2:]), direct.conv2d_int8(host(x[-2:]), host(w), 1, 1))
 
 
+# Large results of the stencil-unrolling layers: tiles of consecutive pixels (few output channels keep the problems small).  Rows that are no whole
+# 16-byte pieces and rows of fewer than 16 bytes; rows as wide as the kernel takes and past that; images of less than a tile, of many tiles and of a ragged
+# last one; channels that fill no group of eight, and more than 32 and 64 of them; every depth; strides and margins; a result past the last-level
+# cache on planes of whole lines and on others.
+STENCIL = [
+    ConvShape("st-c1-odd", 1, 1, 700, 701, 5, 3, 3, 1, 1), ConvShape("st-narrow", 3000, 2, 30, 9, 7, 3, 3, 1, 1), ConvShape("st-16-wide", 1100, 1, 17, 16, 8, 3, 3, 1, 1),
+    ConvShape("st-row-4096", 1, 1, 90, 4096, 3, 3, 3, 1, 1), ConvShape("st-row-4112", 1, 1, 90, 4112, 3, 3, 3, 1, 1), ConvShape("st-pad9-s3", 12, 3, 500, 463, 16, 5, 5, 3, 9),
+    ConvShape("st-20x5", 30, 1, 161, 333, 32, 20, 5, 2, 0), ConvShape("st-depth256", 14, 4, 137, 138, 24, 7, 7, 1, 3), ConvShape("st-k33", 24, 3, 224, 224, 33, 7, 7, 2, 3),
+    ConvShape("st-1x4-k1", 2, 4, 400, 403, 1, 1, 4, 1, 0),
+]
+
+
+@pytest.mark.parametrize("cfg", STENCIL, ids=lambda c: c.name)
+@pytest.mark.parametrize("offset", [0, 1])
+def test_stencil_tiles(lib, cfg, offset):
+    """Both weight forms, an input at any byte and a result at any dword, nothing stored past the result."""
+    x = uniform_int8(71, (cfg.N, cfg.C, cfg.H, cfg.W)); w = uniform_int8(72, (cfg.K, cfg.C, cfg.R, cfg.S))
+    want = _ORACLE_CACHE.setdefault("st-" + cfg.name, direct.conv2d_int8(x, w, cfg.stride, cfg.pad))
+    buf = torch.zeros(x.size + 16, dtype=torch.int8, device=DEV)
+    dx = buf[offset:offset + x.size].view(x.shape); dx.copy_(dev(x))
+    out = torch.full((want.size + 8,), -77, dtype=torch.int32, device=DEV)
+    for packed in (False, True):
+        dw = lib.pack_weights(dev(w), lib.LAYOUT_IMPLICIT, 0) if packed else dev(w)
+        out.fill_(-77)
+        lib.conv2d_int8_ex(cfg.dims(), lib.LAYOUT_IMPLICIT, 0, dx, dw, out[offset:offset + want.size].view(want.shape), None, wt_is_packed=packed)
+        got = host(out)
+        assert np.array_equal(got[offset:offset + want.size].reshape(want.shape), want)
+        assert (got[:offset] == -77).all() and (got[offset + want.size:] == -77).all()
+
+
+@pytest.mark.parametrize("dims", [(1, 75, 92, 32, 5, 5, 2, 0), (3, 64, 64, 64, 3, 3, 1, 1), (1, 100, 102, 64, 3, 3, 1, 1), (5, 57, 60, 130, 3, 3, 1, 1)])
+def test_stencil_tiles_past_the_last_level_cache(lib, dims):
+    C, H, W, K, R, S, stride, pad = dims
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
+    n = 240 * 10**6 // (4 * K * P * Q) + 2
+    gen = torch.Generator(device=DEV).manual_seed(K + W)
+    x = torch.randint(-128, 128, (n, C, H, W), dtype=torch.int8, device=DEV, generator=gen)
+    w = torch.randint(-128, 128, (K, C, R, S), dtype=torch.int8, device=DEV, generator=gen)
+    out = lib.conv2d_int8(x, w, stride, pad)
+    for i in range(0, n, n // 8):   # a slice alone stays below the limits
+        assert torch.equal(out[i:i + n // 8], lib.conv2d_int8(x[i:i + n // 8], w, stride, pad))
+    assert np.array_equal(host(out[-2:]), direct.conv2d_int8(host(x[-2:]), host(w), stride, pad))
+
+
 # The same stage with the tile and the pixels per workgroup given, so that every tile runs whatever the library would pick: a row
 # of one to three channels (the weights' last loads), channels that fill no quad, chunk or step, whole 64-channel rows on
 # planes of whole 64-byte sectors (streamed stores), tiles over many images, more blocks per workgroup than it has waves.
