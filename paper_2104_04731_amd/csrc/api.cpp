@@ -354,6 +354,7 @@ struct Route {
     int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones, band kernel on packed ones, stream kernel on packed / rewritten ones
     ResidentChoice pick;
     int cb, depth;       // block and row bytes of the weights it reads (the two REWRITEs: what is rewritten; PAD_ONLY's, PACKED's)
+    bool raw;            // KCRS as it came, not in depth order
 };
 
 // A convolution with its activations in the network's own layout (NCHW, or NHWC).  pl: the plan whose output extents
@@ -391,7 +392,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
     const RouteKey key{*d, {pl.layout, pl.cb, tag, (int)wt_is_packed, (int)nhwc, dil, (int)aligned16(wt), (int)aligned16(out)}};
     const Route *kept = routes.get(key, [&](Route *n) {
         double best = two_us();
-        *n = Route{TWO_STAGE, {}, 0, 0};
+        *n = Route{TWO_STAGE, {}, 0, 0, false};
         // (one for all: which pixels a window holds does not depend on the weights' form)
         WindowWalk walk = window_walk(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out));
         auto consider = [&](int how, int cb, int depth, bool raw, double extra) {
@@ -402,7 +403,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             const double us = c.us + extra;
             if (us < best) {
                 best = us;
-                *n = Route{how, c, cb, depth};
+                *n = Route{how, c, cb, depth, raw};
             }
         };
         if (wt_is_packed) {
@@ -411,7 +412,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
                 double us;
                 if (!nhwc && dil == 1 && band_direct_us(resident_problem(d, pl, pl.cb, pl.depth, false, false, 1, nullptr, nullptr, out), &us) && us < best) {
                     best = us;
-                    *n = Route{DIRECT_BAND, {}, pl.cb, pl.depth};
+                    *n = Route{DIRECT_BAND, {}, pl.cb, pl.depth, false};
                 }
                 // The smallest streaming tile is for calls of 8 to 14 us.  Against the stored path the estimates' errors decide there, and its own is
                 // the best of many: of 2571 layers 353 went to streaming wherever an estimate was lower, at 1.119 of the other launch's speed in
@@ -419,7 +420,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
                 // the stored path's estimate and below 262 do, 1.185, 8 %.
                 ResidentChoice c;
                 if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), walk, best, n->how == TWO_STAGE ? 0.86 : 1, &c))
-                    *n = Route{DIRECT_STREAM, c, pl.cb, pl.depth};
+                    *n = Route{DIRECT_STREAM, c, pl.cb, pl.depth, false};
             }
             return true;
         }
@@ -430,6 +431,8 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
         if (d->R == 1 && d->S == 1 && d->C % CONV_DEPTH_ALIGN == 0 && aligned16(wt)) consider(DIRECT_AS_IS, 64, d->C, false, 0);
         else {
             if (d->R == 3 && d->S == 3) consider(DIRECT_RAW, C16, depth, true, 0);
+            // rows of C bytes as they are: no second launch (105 pointwise, pair and NHWC calls 0.88 of the time, the small ones 0.6 to 0.8)
+            if (d->R == 1 && d->S == 1) consider(DIRECT_AS_IS, C16, depth, true, 0);
             // the weights' own launch: 2.4-3.2 us up to a megabyte of them
             if (C16 <= 1024) consider(DIRECT_REWRITE, C16, depth, false, 2.8 + 1.0e-6 * (double)d->K * depth + SECOND_LAUNCH_US);
             // weights streamed from blocks of 64 channels, where their estimate is well below: 320 drawn calls that come here against what ran them before
@@ -438,7 +441,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             ResidentChoice c;
             const double rewrite = 2.8 + 1.0e-6 * (double)d->K * depth64 + SECOND_LAUNCH_US;
             if (stream_pick(resident_problem(d, pl, 64, depth64, false, nhwc, dil, nullptr, nullptr, out), walk, 0.95 * best - rewrite, 1, &c))
-                *n = Route{DIRECT_STREAM_REWRITE, c, 64, depth64};
+                *n = Route{DIRECT_STREAM_REWRITE, c, 64, depth64, false};
         }
         return true;
     });
@@ -454,7 +457,7 @@ int run_direct(const Route &rt, const conv_desc_t *d, const Plan &pl, bool nhwc,
             return CONV_ERR_DEVICE;
         wt = static_cast<const int8_t *>(ws);
     }
-    const ResidentProblem r = resident_problem(d, pl, rt.cb, rt.depth, rt.how == DIRECT_RAW, nhwc, dil, in, wt, out);
+    const ResidentProblem r = resident_problem(d, pl, rt.cb, rt.depth, rt.raw, nhwc, dil, in, wt, out);
     if (rt.how == DIRECT_STREAM || rt.how == DIRECT_STREAM_REWRITE) return gemm_status(launch_stream(r, rt.pick.tile, rt.pick.mper, st));
     return gemm_status(rt.how == DIRECT_BAND ? launch_band_direct(r, st) : launch_resident(r, rt.pick, st));
 }
@@ -470,7 +473,7 @@ int one_shot_route(const conv_desc_t *d, int layout, int cb, const int8_t *in, c
     const bool blocked = layout == CONV_LAYOUT_PACKED || layout == CONV_LAYOUT_PAD_ONLY;
     int rc = make_plan(d, blocked ? layout : CONV_LAYOUT_PAD_ONLY, blocked ? cb : 0, pl);
     if (rc != CONV_OK) {   // (an image too large for 32-bit offsets: only what the layout itself can do)
-        *rt = Route{TWO_STAGE, {}, 0, 0};
+        *rt = Route{TWO_STAGE, {}, 0, 0, false};
         return CONV_OK;
     }
     const double in_bytes = (double)d->N * d->C * d->H * d->W;
@@ -493,7 +496,7 @@ int one_shot_route(const conv_desc_t *d, int layout, int cb, const int8_t *in, c
 // The same choice for the other entry points.
 Route ex_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, const int8_t *wt, int32_t *out)
 {
-    if (pl.layout == CONV_LAYOUT_IM2COL) return Route{TWO_STAGE, {}, 0, 0};
+    if (pl.layout == CONV_LAYOUT_IM2COL) return Route{TWO_STAGE, {}, 0, 0, false};
     return pick_route(d, pl, wt_is_packed, false, 1, wt, out, 0, [&] {
         return two_stage_us(d, pl, gemm_problem(d, pl, nullptr, nullptr, out), wt_is_packed, false);
     });
@@ -1154,6 +1157,7 @@ static int resident_forced(const conv_desc_t *desc, int dilation, int nhwc, int 
     Plan pl;
     const int rc = direct_dilated_plan(desc, dilation, wt_cb ? wt_cb : 16, &pl);
     if (rc != CONV_OK) return rc;
+    if (!wt_cb && desc->R != 3) return CONV_ERR_UNSUPPORTED;   // (raw 1x1 weights: only the library's own choice)
     *r = resident_problem(desc, pl, wt_cb ? pl.cb : round_up_i(desc->C, 16), pl.depth, wt_cb == 0, nhwc != 0, dilation, in, wt, out);
     return (stream ? stream_applies(*r, tile - CONV_TILE_STREAM, pixels) : band ? band_direct_applies(*r) : resident_applies(*r, tile, pixels)) ? CONV_OK : CONV_ERR_UNSUPPORTED;
 }

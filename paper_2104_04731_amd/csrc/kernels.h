@@ -81,7 +81,7 @@ struct ResidentProblem {
     int pixel_major;     // a pixel's channels are contiguous (NHWC), pixel_bytes apart
     int pixel_bytes;
     long long img_bytes;
-    int raw_weights;     // g.wq is KCRS as it came (3 x 3 only), not in depth order
+    int raw_weights;     // g.wq is KCRS as it came (3 x 3 and 1 x 1 only), not in depth order
     int kept;            // the weights were rewritten before this call (which of the two estimates applies)
 };
 struct ResidentChoice {

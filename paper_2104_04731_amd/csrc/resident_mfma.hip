@@ -14,6 +14,8 @@
 //     start in 16 different bank groups and a tap's offset is a plain addition.
 //   * depth order: that of pack_weights (PACKED with any block, PAD_ONLY), or (tap, channel) for 3x3 weights that come
 //     raw: 36 bytes of four channels x nine taps are nine dwords of the tile after 27 byte permutes.
+//   * 1x1 weights that come raw are in that order already, in rows of C bytes: fetched in pieces of 16, zeros behind the
+//     last channel, so that a step of depth may read past a record (whatever lies there is multiplied by zero).
 // Bound: the memory system (input once, result once) for the small and middle depths the kernel is for -- weights plus
 // window must fit one compute unit's LDS, which rules out 3x3 layers of more than about 300 channels.  Measured in a
 // graph, two-stage -> this kernel: 64 images 56x56, 64 -> 64, 3x3: 38 -> 19.6 us with rewritten weights (12.8 MB in, 51 MB
@@ -66,6 +68,7 @@ __device__ __forceinline__ void res_barrier()
 }
 
 enum ResSource : int { RES_NCHW = 0, RES_PIXELS = 1 };
+enum ResWeights : int { RES_PACKED = 0, RES_RAW9 = 1, RES_RAW1 = 2 };   // in depth order; KCRS of 3 x 3 and of 1 x 1 kernels
 
 
 // D block (i, f): column = lane%32 (pixel), row = 8*(v/4) + 4*(lane/32) + v%4 (channel).  kw, mw: the wave's first channel
@@ -170,7 +173,7 @@ __device__ __forceinline__ void res_store_piece(const ResidentArgs &a, const v4i
 // The 64-channel tile of 8 waves keeps two output blocks' sums and the addresses of a whole tap in registers: at two of its
 // workgroups per compute unit it spilled, at one it does not, and its LDS rarely leaves room for two (64 images 56 x 56,
 // 64 -> 64, kept weights: 18.0 -> 17.4 us; 151 images 28 x 28, 128 -> 458: 116 -> 105).
-template <int TK, int NW, int FM, int SRC, bool UNI, bool RAW, bool SPLIT, bool RUNS>
+template <int TK, int NW, int FM, int SRC, bool UNI, int WTS, bool SPLIT, bool RUNS>
 __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) conv_resident_kernel(const ResidentArgs a)
 {
     constexpr int NT = NW * 64, FK = TK / 32;
@@ -190,11 +193,24 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
     const int n0 = range.n0, lo0 = range.lo0, len0 = range.len0;
 
     // ---- weights ------------------------------------------------------------------------------------------------
-    if constexpr (!RAW) {
+    // RES_RAW1: the same pieces through registers, at any alignment.  The first two per thread are on their way while the window is asked for; four
+    // were no faster in the deepest layers and 0.3 to 0.6 us slower in all others: a lone wave's instructions decide (2 images 120 x 56 x 56 -> 143,
+    // the weights rewritten by a launch of their own: 8.5 us; four pieces per thread: 5.9, two: 5.3, what a whole piece does not need jumped over: 5.0).
+    constexpr int G = TK / 16;
+    const int lrow = lane >> 2, x = (lane & 3) ^ ((lane >> 4) & 3);
+    constexpr int U1 = 2;
+    v4i raw1[U1];
+    auto raw1_batch = [&](int t0) {
+#pragma unroll
+        for (int b = 0; b < U1; ++b) {
+            const int t = t0 + b * NW, st = t / G, g = t - st * G;
+            if (t < a.steps * G) raw1[b] = raw1_load(a.wq, a.K, a.C, k0 + g * 16 + lrow, st * 64 + x * 16);
+        }
+    };
+    if constexpr (WTS == RES_RAW1) raw1_batch(wave);
+    if constexpr (WTS == RES_PACKED) {
         // a transfer moves 16 rows x 64 bytes of one step; a lane fetches the 16-byte chunk that belongs at its place
         // after the swizzle (chunk position XOR (row / 4) % 4)
-        constexpr int G = TK / 16;
-        const int lrow = lane >> 2, x = (lane & 3) ^ ((lane >> 4) & 3);
         for (int t = wave; t < a.steps * G; t += NW) {
             const int st = t / G, g = t - st * G;
             const int8_t *src = a.wq + (size_t)min(k0 + g * 16 + lrow, a.K - 1) * a.depth + st * 64 + x * 16;
@@ -205,7 +221,15 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
     const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride};
     if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4, RUNS>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
     else window_from_pixels<NT, 4>(from, range, a.u16, a.mg_u16, smem + a.win_off, a.pitch, tid);
-    if constexpr (RAW) {
+    if constexpr (WTS == RES_RAW1) {
+        for (int t0 = wave; t0 < a.steps * G; t0 += NW * U1) {
+            if (t0 != wave) raw1_batch(t0);
+#pragma unroll
+            for (int b = 0; b < U1; ++b)
+                if (t0 + b * NW < a.steps * G) *reinterpret_cast<v4i *>(smem + (t0 + b * NW) * 1024 + lane * 16) = raw1[b];
+        }
+    }
+    if constexpr (WTS == RES_RAW9) {
         // unit: one row, 4 channels; four units' loads in flight (15 images 256 x 7 x 7 -> 26, 4 units per thread: 7.9 us one by
         // one, 7.5 four at a time)
         constexpr int U = 4;
@@ -400,20 +424,19 @@ constexpr ResTile kResTiles[] = {
 constexpr int kNumResTiles = sizeof(kResTiles) / sizeof(kResTiles[0]);
 
 template <int TK, int NW, int FM>
-hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool raw, bool runs, size_t lds, hipStream_t st)
+hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, int wts, bool runs, size_t lds, hipStream_t st)
 {
     typedef void (*Kernel)(ResidentArgs);
     constexpr bool CAN_SPLIT = TK == 32 && FM == 1;
-#define C2I8_FORMS(SRC, RAW, SPLIT, RUNS) \
-    conv_resident_kernel<TK, NW, FM, SRC, false, RAW, SPLIT, RUNS>, conv_resident_kernel<TK, NW, FM, SRC, true, RAW, SPLIT, RUNS>
-    static constexpr Kernel kernels[] = {
-        C2I8_FORMS(RES_NCHW, false, false, false), C2I8_FORMS(RES_NCHW, false, false, true), C2I8_FORMS(RES_NCHW, true, false, false), C2I8_FORMS(RES_NCHW, true, false, true),
-        C2I8_FORMS(RES_PIXELS, false, false, false), C2I8_FORMS(RES_PIXELS, true, false, false),
-        C2I8_FORMS(RES_NCHW, false, CAN_SPLIT, false), C2I8_FORMS(RES_NCHW, false, CAN_SPLIT, true), C2I8_FORMS(RES_NCHW, true, CAN_SPLIT, false), C2I8_FORMS(RES_NCHW, true, CAN_SPLIT, true),
-        C2I8_FORMS(RES_PIXELS, false, CAN_SPLIT, false), C2I8_FORMS(RES_PIXELS, true, CAN_SPLIT, false)};
+#define C2I8_FORMS(WTS, SPLIT, SRC, RUNS) \
+    conv_resident_kernel<TK, NW, FM, SRC, WTS == RES_RAW1, WTS, SPLIT, RUNS>, conv_resident_kernel<TK, NW, FM, SRC, true, WTS, SPLIT, RUNS>
+#define C2I8_SOURCES(WTS, SPLIT) C2I8_FORMS(WTS, SPLIT, RES_NCHW, false), C2I8_FORMS(WTS, SPLIT, RES_NCHW, true), C2I8_FORMS(WTS, SPLIT, RES_PIXELS, false)
+    static constexpr Kernel kernels[] = {C2I8_SOURCES(RES_PACKED, false), C2I8_SOURCES(RES_RAW9, false), C2I8_SOURCES(RES_RAW1, false),
+                                         C2I8_SOURCES(RES_PACKED, CAN_SPLIT), C2I8_SOURCES(RES_RAW9, CAN_SPLIT), C2I8_SOURCES(RES_RAW1, CAN_SPLIT)};
+#undef C2I8_SOURCES
 #undef C2I8_FORMS
     static bool raised[sizeof(kernels) / sizeof(kernels[0])];
-    const int form = pixels ? 4 + raw : raw * 2 + runs, which = (a.parts > 1) * 12 + form * 2 + uni;
+    const int which = (((a.parts > 1) * 3 + wts) * 3 + (pixels ? 2 : runs)) * 2 + uni;
     const Kernel kern = kernels[which];
     if (lds > 64 * 1024 && !raised[which]) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -425,7 +448,7 @@ hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, bool ra
 
 struct ResidentPlan {
     ResidentArgs a;
-    int tile;
+    int tile, wts;   // wts: ResWeights
     bool uni, runs;
     size_t lds;
 };
@@ -460,7 +483,7 @@ bool resident_shape(const ResidentProblem &r, ResidentShape *o)
 {
     const GemmProblem &g = r.g;
     if (g.mode != ACT_BLOCKED || g.R * g.S > 31 || g.il_d || g.act_out || g.Q <= 0 || g.PQ % g.Q || g.M <= 0) return false;
-    if (r.raw_weights ? g.R != 3 || g.S != 3 : g.cb < 16 || g.cb % 16) return false;
+    if (r.raw_weights ? g.R != g.S || (g.R == 1 ? (long long)g.K * r.C < 16 : g.R != 3) : g.cb < 16 || g.cb % 16) return false;
     // 32-bit offsets inside an image and of its pixels; 8- and 16-byte loads clamped to the tensor
     if (r.img_bytes > 0x7FFFFFFFLL || (long long)r.H * r.W > (1LL << 28) || (long long)r.N * r.img_bytes < 64) return false;
     if ((long long)g.Q * g.stride > (1LL << 28) || (long long)(g.PQ / g.Q) * g.stride > (1LL << 28)) return false;
@@ -524,6 +547,7 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
         a.full8 = (int)((end + 7) & ~7LL);
     }
     out->uni = sh.uni;
+    out->wts = !r.raw_weights ? RES_PACKED : g.R == 1 ? RES_RAW1 : RES_RAW9;
     if ((mper / PQ + 2) * PQ * g.K * 4 >= (1LL << 32)) return false;   // 32-bit byte offsets from the workgroup's first image
     a.nblk = (mper + 32 * d.fm - 1) / (32 * d.fm);
     a.parts = resident_parts(d, mper, a.steps);
@@ -590,10 +614,13 @@ __attribute__((always_inline)) inline double resident_cost_given(const ResidentP
     double t = 4.11 + rounds * (0.0258 * chain + 0.386 * units) + ncu * (8.14e-3 * mfma + 3.41e-5 * window + 1.43e-6 * weights + 5.66e-6 * result) +
                per * (1.41e-5 * window + 6.7e-6 * weights + (g.PQ % 16 == 0 ? 1.55e-5 : 2.47e-5) * result) +
                (rounds - 1) * (1.43e-5 * window + 8.08e-6 * weights);
-    if (r.raw_weights) {
+    if (r.raw_weights && g.R == 3) {
         const int loads = (d.tk * (sh.C16 / 4) + d.nw * 64 - 1) / (d.nw * 64);
         t += rounds * (0.706 + (r.C % 4 ? 0.638 : 0.272) * loads);
     }
+    // (raw 1x1 weights: batches of two pieces per thread.  Between 0.2 and 0.3 of a microsecond for each: at 0 the workgroups of 33 images 388 x 24 x 24
+    // -> 256 fetch them twice as often as they have to, 21.7 us instead of 16.4, and 22 images 373 x 44 x 44 -> 128 stride 2 leave the stored path, 15.8 -> 16.6)
+    else if (r.raw_weights) t += rounds * 0.25 * ((d.tk / 16 * sh.steps + 2 * d.nw - 1) / (2 * d.nw));
     return t;
 }
 
@@ -708,7 +735,7 @@ static hipError_t launch_plan(const ResidentProblem &r, const ResidentPlan &p, h
     a.out = r.g.out;
     int index = 0;
 #define C2I8_CASE(tk, nw, fm, fit) \
-    if (p.tile == index++) return launch_res_tile<tk, nw, fm>(a, r.pixel_major, p.uni, r.raw_weights, p.runs, p.lds, st);
+    if (p.tile == index++) return launch_res_tile<tk, nw, fm>(a, r.pixel_major, p.uni, p.wts, p.runs, p.lds, st);
     C2I8_RES_LIST(C2I8_CASE)
 #undef C2I8_CASE
     return hipErrorInvalidValue;

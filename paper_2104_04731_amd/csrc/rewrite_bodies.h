@@ -399,6 +399,26 @@ __device__ __forceinline__ unsigned raw9_tap(const unsigned (&d)[9])
     return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
+// Raw 1x1 weights: 16 channels of row k from channel c0 on, at any address (channels past the last one: zeros; a row past the last
+// one: that one's; bytes >= 16, the tensor's).  A piece that would end behind the tensor is fetched with its last 16 bytes and moved down.
+__host__ __device__ __forceinline__ v4i raw1_load(const int8_t *wt, int K, int C, int k, int c0)
+{
+    const long long last = (long long)K * C - 16, at = (long long)min(k, K - 1) * C + c0, from = min(at, last);
+    const v4i_a1 x = *reinterpret_cast<const v4i_a1 *>(wt + from);
+    v4i d = x;
+    const int keep = (C - c0) * 8;   // bits
+    if (keep < 128 || at > last) {
+        unsigned long long lo = (unsigned)x[0] | (unsigned long long)(unsigned)x[1] << 32, hi = (unsigned)x[2] | (unsigned long long)(unsigned)x[3] << 32;
+        const int down = (int)(at - from) * 8;
+        if (down >= 64) lo = down >= 128 ? 0 : hi >> (down - 64), hi = 0;
+        else if (down > 0) lo = lo >> down | hi << (64 - down), hi >>= down;
+        if (keep <= 64) lo = keep <= 0 ? 0 : lo & ~0ull >> (64 - keep), hi = 0;
+        else if (keep < 128) hi &= ~0ull >> (128 - keep);
+        d = v4i{(int)lo, (int)(lo >> 32), (int)hi, (int)(hi >> 32)};
+    }
+    return d;
+}
+
 // ---- pack_weights -----------------------------------------------------------------------
 // Blocked: dst[k][((b*R + r)*S + s)*cb + ci] = src[k][b*cb+ci][r][s]; one thread per 16 B.
 struct WeightArgs {

@@ -1365,6 +1365,31 @@ def test_stencil_tiles_past_the_last_level_cache(lib, dims):
     assert np.array_equal(host(out[-2:]), direct.conv2d_int8(host(x[-2:]), host(w), stride, pad))
 
 
+# 1x1 weights as they come, rows of C bytes at any address: rows shorter than a 16-byte piece and than 64 bytes, one channel more and less, the
+# tensor's end within a piece, the first batch of pieces and the ones after it (more than 512 channels), strides and a margin.
+ROWS_1X1 = [(2, c, 14, 14, k, s, p) for c, k, s, p in ((17, 33, 1, 0), (24, 64, 2, 0), (33, 47, 1, 1), (63, 32, 1, 0), (65, 95, 2, 1), (100, 130, 1, 0), (200, 64, 1, 0), (319, 31, 2, 0),
+                                                       (541, 70, 1, 0), (1030, 40, 1, 0))] + [(1, 40, 4, 4, 1, 1, 0), (40, 130, 28, 28, 66, 1, 0), (3, 128, 9, 9, 36, 1, 0)]
+
+
+@pytest.mark.parametrize("dims", ROWS_1X1, ids=str)
+@pytest.mark.parametrize("offset", [0, 5])
+def test_1x1_weights_as_they_come(lib, dims, offset):
+    """One-shot, blocked and NHWC calls; weights at any byte, next to bytes that are none of theirs."""
+    N, C, H, W, K, stride, pad = dims
+    x = uniform_int8(73, (N, C, H, W)); w = uniform_int8(74, (K, C, 1, 1))
+    want = direct.conv2d_int8(x, w, stride, pad)
+    buf = torch.full((w.size + 32,), 85, dtype=torch.int8, device=DEV)
+    dw = buf[offset:offset + w.size].view(w.shape); dw.copy_(dev(w))
+    assert np.array_equal(host(lib.conv2d_int8(dev(x), dw, stride, pad)), want)
+    dims9 = (N, C, H, W, K, 1, 1, stride, pad)
+    out = torch.full(want.shape, -77, dtype=torch.int32, device=DEV)
+    ws = torch.empty(max(lib.conv2d_int8_workspace_bytes(dims9, lib.LAYOUT_PACKED, 64, False), 256), dtype=torch.int8, device=DEV)
+    lib.conv2d_int8_ex(dims9, lib.LAYOUT_PACKED, 64, dev(x), dw, out, ws, wt_is_packed=False)
+    assert np.array_equal(host(out), want)
+    got = host(lib.conv2d_int8_nhwc(dev(np.ascontiguousarray(x.transpose(0, 2, 3, 1))), dw, stride, pad))
+    assert np.array_equal(got.transpose(0, 3, 1, 2), want)
+
+
 # The same stage with the tile and the pixels per workgroup given, so that every tile runs whatever the library would pick: a row
 # of one to three channels (the weights' last loads), channels that fill no quad, chunk or step, whole 64-channel rows on
 # planes of whole 64-byte sectors (streamed stores), tiles over many images, more blocks per workgroup than it has waves.

@@ -24,6 +24,11 @@ def test_raw_weight_loads_stay_inside_the_tensor(run_host):
     assert run_host("raw_weights") == (0, "ok")
 
 
+def test_raw_1x1_weight_loads_stay_inside_the_tensor(run_host):
+    """1 to 130 channels, the same way; every 16-byte piece a tile asks for is compared with the bytes, zeros past the row."""
+    assert run_host("raw_rows") == (0, "ok")
+
+
 def test_plan_table_keeps_as_many_problems_as_it_holds(run_host):
     """Plans are made once per problem while no more problems take turns than the table has places."""
     assert run_host("plan_table") == (0, "ok")
