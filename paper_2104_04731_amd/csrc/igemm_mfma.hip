@@ -20,6 +20,7 @@
 #include "act_requant.h"
 #include "kernels.h"
 #include "launch.h"
+#include "store_past.h"
 
 #include <cmath>
 #include <type_traits>
@@ -28,6 +29,7 @@ namespace c2i8 {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v4i_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 struct GemmArgs {
     const int8_t *act;
@@ -54,6 +56,7 @@ struct GemmArgs {
     int out_nhwc;  // `out` is [N][P][Q][K] instead of [N][K][P][Q]
     int grp_m;     // > 0: tile order in groups of grp_m pixel tiles (below); 0: one of the two row-major orders
     unsigned mg_grp_sz, mg_grp_m, mg_tiles_km;  // ceil(2^32 / d) for grp_m * tiles_k, grp_m, tiles_k * tiles_m
+    int rows;      // large wave tiles: NKPQ result through LDS in whole rows of the tile, 1: stored through the caches, 2: past them
     int stagger;   // start offsets of the first round of workgroups: this many 64-cycle units per phase step (0: none)
 };
 
@@ -106,6 +109,15 @@ constexpr int slots_before(int l, int nq, int off, int qb)
     return n;
 }
 
+// The result of a large wave tile on its way through LDS: rows of TM pixels (four rows on are 32 banks on), 32 of each row of waves
+// per pass, in two buffers where they fit beside as many workgroups as the operand ring does.
+constexpr int row_pitch(int tm) { return tm * 4 + 32; }
+constexpr int row_buffers(int tk, int tm, int wk, int row_bytes)
+{
+    const int ring = (tk + tm) * row_bytes, two = 2 * wk * 32 * row_pitch(tm);
+    return two <= ring || 160 * 1024 / two == 160 * 1024 / ring ? 2 : 1;
+}
+
 // HELP extra waves per workgroup only move operands (they issue their share of the transfers
 // and keep the barriers, no MFMA): a wave moves about 1 KB per 140-180 cycles through the
 // global->LDS path whatever the queue depth, so small tiles, whose four MFMA waves would be
@@ -120,8 +132,11 @@ constexpr int slots_before(int l, int nq, int off, int qb)
 // WPC > 1 caps the registers so that WPC workgroups fit one CU: while one of them waits at a
 // barrier or drains its output tile, the matrix pipe works for the other.
 //
+// ROWS: the NKPQ result leaves through LDS in whole rows of the tile (large wave tiles; kernels of their own, since the code beside
+// the other results made a fused activation's launch of 17 us 0.5 longer).
+//
 // The body is a device function of (logical workgroup id, workgroup count, LDS base).
-template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int MODE>
+template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int MODE, bool ROWS>
 __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int nblocks, unsigned char *smem)
 {
     constexpr int NWM = WK * WM;           // waves of one multiplying group
@@ -519,6 +534,60 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
 
     }
 
+    if constexpr (ROWS) {
+        // Through LDS, a pass per row block of every wave, so that a store instruction writes 16 bytes per lane of whole rows of
+        // the tile: straight from the blocks it is FK * FM * 16 dword stores per lane, and a compute unit takes twelve clocks for a
+        // store instruction whatever its width.  A 256 x 256 tile leaves in 3.6 us of its 36 where it took 7.5.  Every address but
+        // one 32-bit offset per lane is scalar and a whole tile's rows are tested nowhere: with the row's place worked out per lane
+        // and a branch per row the way through LDS took 7.5 us as well.
+        constexpr int PITCH = row_pitch(TM), PR = WK * 32, BUF = PR * PITCH;
+        constexpr int NBUF = row_buffers(TK, TM, WK, RP * NSTAGE);
+        constexpr int LPR4 = TM / 4, RPS = 64 / LPR4;      // lanes of a row, rows of a store instruction
+        constexpr int NST = PR / (NWM * RPS);            // stores of a wave in a pass of PR rows
+        static_assert(LPR4 <= 64 && PR % (NWM * RPS) == 0 && 32 % (NST * RPS) == 0, "a wave's rows belong to one row of waves");
+        const int mq = m0 + (lane % LPR4) * 4, n0 = div_magic(m0, a.PQ, a.mg_PQ);
+        const int n = div_magic(min(mq, a.M - 1), a.PQ, a.mg_PQ), pq = mq - n * a.PQ;
+        const unsigned row = (unsigned)a.PQ * 4u;
+        const unsigned off = ((unsigned)(n - n0) * (unsigned)a.K * (unsigned)a.PQ + (unsigned)pq) * 4u + (unsigned)(lane / LPR4) * row;
+        const bool there = mq < a.M;   // (planes are whole quads, and so is M)
+        const int r0 = wave * NST * RPS, kw = k0 + (r0 >> 5) * WTK + (r0 & 31);
+        char *const to0 = reinterpret_cast<char *>(a.out) + ((size_t)n0 * a.K + (size_t)kw) * row;
+        const unsigned char *const from = smem + (r0 + lane / LPR4) * PITCH + lane % LPR4 * 16;
+        unsigned char *const mine = smem + (wk * 32 + 4 * (lane >> 5)) * PITCH + (wm * WTM + (lane & 31)) * 4;
+        lds_barrier();   // (the ring is idle: every transfer has landed)
+        auto pass = [&](int i, auto inside, auto past) {
+            const int b = NBUF == 2 ? (i & 1) * BUF : 0;
+            if (NBUF == 1 && i > 0) lds_barrier();
+#pragma unroll
+            for (int f = 0; f < FM; ++f)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) *reinterpret_cast<int *>(mine + b + (8 * (v >> 2) + (v & 3)) * PITCH + f * 128) = acc[i][f][v];
+            lds_barrier();
+            v4i t[NST];
+#pragma unroll
+            for (int r = 0; r < NST; ++r) t[r] = *reinterpret_cast<const v4i *>(__builtin_assume_aligned(from + b + r * RPS * PITCH, 16));
+#pragma unroll
+            for (int r = 0; r < NST; ++r) {
+                char *const to = to0 + (size_t)(i * 32 + r * RPS) * row;
+                if constexpr (decltype(inside)::value) {
+                    if constexpr (decltype(past)::value) store_past16(to, off, t[r]);
+                    else *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                    continue;
+                }
+                if (there && kw + i * 32 + r * RPS + lane / LPR4 < a.K) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+            }
+        };
+        auto passes = [&](auto inside, auto past) {
+#pragma unroll
+            for (int i = 0; i < FK; ++i) pass(i, inside, past);
+        };
+        const bool inside = k0 + TK <= a.K && m0 + TM <= a.M;   // no test per row
+        if (!inside) passes(std::false_type{}, std::false_type{});
+        else if (a.rows == 2) passes(std::true_type{}, std::true_type{});
+        else passes(std::true_type{}, std::false_type{});
+        return;
+    }
+
     // Epilogue: D block (i, jm): column = lane%32 (pixel), row = 8*(v/4) + 4*(lane/32) + v%4.
     // Consecutive lanes write consecutive pixels of one output plane: 128-byte runs in NKPQ.
     if (a.act_out) {
@@ -667,18 +736,19 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
     }
 }
 
-template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int WPC, int MODE>
+template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int WPC, int MODE, bool ROWS>
 __global__ void __launch_bounds__((WK * WM * DS + HELP) * 64, (WK * WM * DS + HELP + 3) / 4 * WPC)
     igemm_i8_kernel(const GemmArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    igemm_body<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, MODE>(a, blockIdx.x, gridDim.x, smem);
+    igemm_body<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, MODE, ROWS>(a, blockIdx.x, gridDim.x, smem);
 }
 
 // ---- tile table -----------------------------------------------------------------------
 struct TileDef {
     int tk, tm, wk, wm, ks, nstage, help, ds, wpc;
     double start, alone, shared;   // gemm_pick's microseconds
+    constexpr bool large() const { return (tk / wk / 32) * (tm / wm / 32) > 2; }   // its result leaves through LDS where it can
 };
 // One row per kernel instantiation: TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, and what gemm_pick reckons with: a
 // workgroup's fixed part, the chain of its 64-byte depth step, and the work of a step where several workgroups share
@@ -746,36 +816,43 @@ TileInfo gemm_tile_info(int t)
 }
 
 // LDS a launch of tile `d` asks for: the operand ring plus, for the blocked layout, one offset per 16-byte
-// depth chunk of a slice (`per` 64-byte steps).  The picker and the launcher use the same figure.
+// depth chunk of a slice (`per` 64-byte steps); or the rows of a result on their way out, where that is more.  The picker and the launcher use the same figure.
 constexpr size_t kLdsLimit = 160 * 1024;
-static size_t tile_lds_bytes(const TileDef &d, int mode, int per)
+static size_t tile_lds_bytes(const TileDef &d, int mode, int per, bool by_rows)
 {
-    return (size_t)d.nstage * (d.tk + d.tm) * 64 * d.ks + (mode == ACT_BLOCKED ? (size_t)per * 16 : 0);
+    const size_t ring = (size_t)d.nstage * (d.tk + d.tm) * 64 * d.ks + (mode == ACT_BLOCKED ? (size_t)per * 16 : 0);
+    const size_t rows = by_rows && d.large() ? (size_t)row_buffers(d.tk, d.tm, d.wk, 64 * d.ks * d.nstage) * d.wk * 32 * row_pitch(d.tm) : 0;
+    return ring > rows ? ring : rows;
 }
 
 template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int WPC = 1>
 static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
 {
     constexpr int NT = (WK * WM * DS + HELP) * 64;
-    const size_t lds = tile_lds_bytes(TileDef{TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, 0, 0, 0}, mode, a.ksteps_per_split);
+    constexpr TileDef tile{TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, 0, 0, 0};
+    const size_t lds = tile_lds_bytes(tile, mode, a.ksteps_per_split, a.rows != 0);
     const int grid = a.tiles_k * a.tiles_m * a.split_k;
-    auto kb = igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED>;
-    auto km = igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX>;
-    auto kern = mode == ACT_BLOCKED ? kb : km;
+    void (*kern)(GemmArgs) = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, false>
+                                                 : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, false>;
+    if constexpr (tile.large())
+        if (a.rows)
+            kern = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, true>
+                                       : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, true>;
     if (lds > kLdsLimit) return hipErrorInvalidValue;  // the picker never offers such a pair
-    static size_t raised[2] = {0, 0};  // dynamic-LDS ceiling already granted, per kernel
-    if (lds > 64 * 1024 && lds > raised[mode]) {
+    static size_t raised[2][2] = {};  // dynamic-LDS ceiling already granted, per kernel
+    size_t &granted = raised[mode][a.rows != 0];
+    if (lds > 64 * 1024 && lds > granted) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
-        raised[mode] = 160 * 1024;
+        granted = 160 * 1024;
     }
     return launch(kern, dim3(grid), dim3(NT), lds, st, a);
 }
 
 static int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-size_t gemm_tile_lds_bytes(int t, int mode, int steps_per_slice) { return tile_lds_bytes(kTiles[t], mode, steps_per_slice); }
+size_t gemm_tile_lds_bytes(int t, int mode, int steps_per_slice) { return tile_lds_bytes(kTiles[t], mode, steps_per_slice, true); }
 
 // A tile with 128- or 256-byte stages walks the depth two or four steps at a time: every slice
 // must be a whole number of stages.
@@ -823,7 +900,7 @@ bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost)
         for (int ci = 0; ci < ncand; ++ci) {
             const int s = slices[ci], per = pers[ci];
             if (!tile_fits(d, ksteps, per)) continue;
-            const size_t lds = tile_lds_bytes(d, g.mode, per);
+            const size_t lds = tile_lds_bytes(d, g.mode, per, true);
             if (lds > kLdsLimit) continue;  // ring + offset table must fit one CU's LDS
             int cap = (int)kLdsLimit / (int)lds;
             if (cap > wave_cap) cap = wave_cap;
@@ -896,6 +973,18 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
     if (!tile_fits(d, a.ksteps_total, a.ksteps_per_split)) return false;
     a.out_fits_32bit = (unsigned long long)g.M * g.K * sizeof(int32_t) < (1ULL << 32);
     {
+        // NKPQ results of large wave tiles through LDS (see the kernel), on planes of whole 16-byte pieces, and past the caches.  A result
+        // above 256 MB does not fit the last-level cache, and as plain stores it pushes the operands out of the L2s (2048 images
+        // 256 x 14 x 14 -> 512: 550 us, with an input that fits the L2s 485; past the caches that makes no difference): 5 drawn layers
+        // take 0.85 of the time.  One that fits the L2s is otherwise written back when the kernel ends: 41 drawn layers of up to 32 MB
+        // take 0.90, the worst 1.00.  Between the two a result that is written again is still in the last-level cache, and past it takes
+        // up to 1.08; there the eight-wave 256 x 256 tiles alone go through LDS into the caches (0.91 to 0.98 on planes of 14 x 14, the
+        // smaller tiles 0.98 to 1.03).
+        const double bytes = 4.0 * g.M * g.K;
+        const bool can = d.large() && !a.act_out && !a.out_nhwc && !a.il_d && a.split_k == 1 && g.PQ % 4 == 0 && (d.tm / (long long)g.PQ + 2) * g.PQ * g.K < (1LL << 30);
+        a.rows = !can ? 0 : past_caches(bytes) ? 2 : d.tk == 256 && d.tm == 256 && d.wk * d.wm == 8 ? 1 : 0;
+    }
+    {
         // Start offsets of the first round (see the kernel): worth their idle time where the launch runs several
         // rounds and a large output tile is a sizeable part of a workgroup's life (small tiles drift apart by
         // themselves: measured level or slightly worse with offsets).  Estimates in core cycles: 60 per
@@ -907,7 +996,7 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
         const long long grid = (long long)a.tiles_k * a.tiles_m * a.split_k;
         a.stagger = 0;
         if (grid >= 2 * 256 && a.split_k == 1 && epi_clk >= 16000 && epi_clk >= 0.15 * (main_clk + epi_clk)) {
-            a.stagger = (int)(2.0 * epi_clk / (32 * 64) + 0.5);
+            a.stagger = (int)((a.rows == 2 ? 1.25 : 2.0) * epi_clk / (32 * 64) + 0.5);
         }
     }
     {

@@ -1,0 +1,20 @@
+// Stores past the caches, and from what size of a result they pay.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace c2i8 {
+
+// A result larger than the last-level cache (256 MB) leaves it anyway, one that fits the L2s (8 x 4 MB) is written back when the kernel
+// ends if it was not before; between the two a smaller one that is written again is still in the last-level cache.
+inline bool past_caches(double bytes) { return bytes > 256e6 || bytes <= 32e6; }
+
+// 16 bytes per lane to base + off (at any dword) past the caches.  Written out: of two stores to one address in two branches, one
+// of them __builtin_nontemporal_store, the compiler makes a single plain one.  The wait state behind it is the one that a vector
+// instruction needs before it may write the registers of a store of more than eight bytes: the compiler does not know that this is one.
+typedef int past_v4i __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store_past16(char *base, unsigned off, past_v4i x)
+{
+    asm volatile("global_store_dwordx4 %0, %1, %2 nt\n\ts_nop 0" : : "v"(off), "v"(x), "s"(base) : "memory");
+}
+
+}  // namespace c2i8

@@ -16,6 +16,7 @@
 #include "window_fill.h"
 #include "kernels.h"
 #include "launch.h"
+#include "store_past.h"
 
 #include <type_traits>
 
@@ -468,47 +469,65 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
         constexpr int LPR = FM * WM * 8;                           // lanes of a row, four pixels each
         constexpr int RPI = 64 / LPR < 1 ? 1 : 64 / LPR;           // rows of a store instruction
         static_assert(LPR <= 64, "a wave stores a row of the tile");
+        constexpr int NS = ROWS / (NW * RPI);                      // store instructions of a wave in a pass
+        static_assert(ROWS % (NW * RPI) == 0 && 32 % (NS * RPI) == 0, "a wave's rows belong to one row of waves");
         const int quad = lane % LPR, mq = m0 + quad * 4;
         const int n = fast_div_any(min(mq, a.M - 1), a.PQ, a.mg_PQ), pq = mq - n * a.PQ;
-        const size_t row = (size_t)a.PQ * sizeof(int32_t);
-        const unsigned off = ((unsigned)(n - w.n0) * (unsigned)a.K * (unsigned)a.PQ + (unsigned)pq) * 4u;
+        const unsigned row = (unsigned)a.PQ * 4u;
+        const unsigned off = ((unsigned)(n - w.n0) * (unsigned)a.K * (unsigned)a.PQ + (unsigned)pq) * 4u + (unsigned)(lane / LPR) * row;
         const int ok = min(max(m1 - mq, 0), 4);
         const bool whole = ok == 4 && pq + 3 < a.PQ;
+        // a wave's rows follow one another: their places are scalar, and which of them exist is asked for the tile as a whole
+        const int r0 = wave * NS * RPI, kw = k0 + (r0 >> 5) * FK * 32 + (r0 & 31);
+        char *const to0 = reinterpret_cast<char *>(a.out) + ((size_t)w.n0 * a.K + (size_t)kw) * row;
+        const unsigned char *const from = smem + (r0 + lane / LPR) * PITCH + quad * 16;
         st_barrier();
+        auto passes = [&](auto inside, auto past) {
 #pragma unroll
-        for (int i = 0; i < FK; ++i) {
-            unsigned char *const buf = smem + (i & 1) * BUF;
-            unsigned char *const mine = buf + grp * GROUP + (wk * 32 + 4 * half) * PITCH + (wm * FM * 32 + (lane & 31)) * 4;
+            for (int i = 0; i < FK; ++i) {
+                unsigned char *const mine = smem + (i & 1) * BUF + grp * GROUP + (wk * 32 + 4 * half) * PITCH + (wm * FM * 32 + (lane & 31)) * 4;
 #pragma unroll
-            for (int f = 0; f < FM; ++f)
+                for (int f = 0; f < FM; ++f)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) *reinterpret_cast<int *>(mine + (8 * (v >> 2) + (v & 3)) * PITCH + f * 128) = acc[i][f][v];
-            st_barrier();
+                    for (int v = 0; v < 16; ++v) *reinterpret_cast<int *>(mine + (8 * (v >> 2) + (v & 3)) * PITCH + f * 128) = acc[i][f][v];
+                st_barrier();
+                v4i t[NS];
 #pragma unroll
-            for (int r0 = 0; r0 < ROWS; r0 += NW * RPI) {
-                const int r = r0 + wave * RPI + lane / LPR;        // (wave-uniform where a row takes the whole wave)
-                const int k = k0 + (r >> 5) * FK * 32 + i * 32 + (r & 31);
-                const unsigned char *const at = buf + r * PITCH + quad * 16;
-                v4i t = *reinterpret_cast<const v4i *>(__builtin_assume_aligned(at, 16));
+                for (int r = 0; r < NS; ++r) {
+                    const unsigned char *const at = from + (i & 1) * BUF + r * RPI * PITCH;
+                    t[r] = *reinterpret_cast<const v4i *>(__builtin_assume_aligned(at, 16));
 #pragma unroll
-                for (int d = 1; d < DS; ++d) t += *reinterpret_cast<const v4i *>(__builtin_assume_aligned(at + d * GROUP, 16));
-                if (k >= a.K) continue;
-                char *const to = reinterpret_cast<char *>(a.out) + ((size_t)w.n0 * a.K + (size_t)k) * row;
+                    for (int d = 1; d < DS; ++d) t[r] += *reinterpret_cast<const v4i *>(__builtin_assume_aligned(at + d * GROUP, 16));
+                }
+                auto there = [&](int r) { return decltype(inside)::value || kw + i * 32 + r * RPI + lane / LPR < a.K; };
                 if (whole) {
-                    if (a.stream_out) __builtin_nontemporal_store(t, reinterpret_cast<v4i_a4 *>(to + off));
-                    else *reinterpret_cast<v4i_a4 *>(to + off) = t;
-                } else if (ok) {   // (two images meet in the four pixels -- or more, of fewer than four -- or the tile ends)
-                    unsigned o = off;
-                    int q = pq;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (e < ok) *reinterpret_cast<int32_t *>(to + o) = t[e];
-                        o += 4;
-                        if (++q == a.PQ) q = 0, o += (unsigned)(a.K - 1) * (unsigned)a.PQ * 4u;
+                    for (int r = 0; r < NS; ++r) {
+                        char *const to = to0 + (size_t)(i * 32 + r * RPI) * row;
+                        if (!there(r)) continue;
+                        if constexpr (decltype(past)::value) store_past16(to, off, t[r]);
+                        else *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                    }
+                } else if (ok) {   // (two images meet in the four pixels -- or more, of fewer than four -- or the tile ends)
+#pragma unroll
+                    for (int r = 0; r < NS; ++r) {
+                        char *const to = to0 + (size_t)(i * 32 + r * RPI) * row;
+                        if (!there(r)) continue;
+                        unsigned o = off;
+                        int q = pq;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (e < ok) *reinterpret_cast<int32_t *>(to + o) = t[r][e];
+                            o += 4;
+                            if (++q == a.PQ) q = 0, o += (unsigned)(a.K - 1) * row;
+                        }
                     }
                 }
             }
-        }
+        };
+        if (k0 + TK > a.K) passes(std::false_type{}, std::false_type{});
+        else if (a.stream_out) passes(std::true_type{}, std::true_type{});
+        else passes(std::true_type{}, std::false_type{});
         return;
     }
 
@@ -698,8 +717,12 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
     a.zero_off = d.ring();
     a.win_off = a.zero_off + 64;
     a.tab_off = a.win_off + nbuf * a.buf_bytes;
-    // whole 64-byte sectors per store instruction, of planes and tiles that hold whole ones, go past the caches (resident_mfma.hip)
-    a.stream_out = PQ % 16 == 0 && mper % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0;
+    // Past the caches: whole 64-byte sectors per store instruction, of planes and tiles that hold whole ones (37 drawn layers 0.97 of the
+    // time, the worst 1.03); other planes of whole 16-byte pieces from 8 to 32 MB (0.98, 1.03) and above 256 (0.95, 0.97).  (From 32 to
+    // 256 MB they take up to 1.28, below 8 up to 1.04, planes of other sizes up to 1.13.)
+    const double bytes = 4.0 * g.M * g.K;
+    const bool sectors = PQ % 16 == 0 && mper % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0;
+    a.stream_out = sectors || (PQ % 4 == 0 && mper % 4 == 0 && bytes > 8e6 && past_caches(bytes));
     const long long tk = (g.K + d.tk() - 1) / d.tk(), tm = ((long long)g.M + mper - 1) / mper;
     if (tk * tm > 0x7FFFFFFFLL) return false;
     a.tiles_k = (int)tk;
@@ -824,7 +847,7 @@ bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, doubl
             // Tiles that begin inside a 64-byte sector write it in two parts: on planes of whole sectors the count goes up to whole ones,
             // where that is at most an eighth more, cuts no image that was divided evenly, and leaves the window as many buffers.  41
             // layers, mean 1.033 (72 images 500 x 55 x 55 -> 64 stride 2: 111 -> 112 pixels, 63.8 -> 55.5 us), the worst 0.974; up to
-            // 0.89 without the conditions.  (The store's kind does not matter there: 30 layers, past the caches or not, 0.998.)
+            // 0.89 without the conditions.
             const int up = (x.mper + 15) / 16 * 16;
             if (r.g.PQ % 16 == 0 && !r.pixel_major && up != x.mper && r.g.PQ % x.mper && up * 8 <= x.mper * 9 && up <= kStreamTiles[x.tile].tm() &&
                 stream_plan(r, x.tile, up, &whole) && whole.a.nbuf == p.a.nbuf)

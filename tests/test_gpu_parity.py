@@ -256,6 +256,48 @@ def test_conv_every_tile_and_split(lib, name):
             assert np.array_equal(got, want), f"tile {tile} split {split}"
 
 
+@pytest.mark.parametrize("cfg", [
+    ConvShape("three-images-per-row", 5, 64, 14, 14, 260, 3, 3, 1, 1), ConvShape("many-images-per-tile", 70, 64, 2, 2, 520, 3, 3, 1, 1),
+    ConvShape("one-tile", 4, 128, 8, 8, 256, 3, 3, 1, 1), ConvShape("stride", 3, 64, 25, 31, 90, 3, 3, 2, 1),
+], ids=lambda c: c.name)
+def test_large_tiles_write_whole_rows(lib, cfg):
+    """Planes of whole 16-byte pieces: every tile of more than two blocks per wave writes rows that pass through LDS; channels and
+    pixels that end inside a tile, images that end inside a row, a result at any dword, and nothing written beside it."""
+    x = uniform_int8(351, (cfg.N, cfg.C, cfg.H, cfg.W)); w = uniform_int8(352, (cfg.K, cfg.C, cfg.R, cfg.S))
+    want = direct.conv2d_int8(x, w, cfg.stride, cfg.pad)
+    assert want.shape[2] * want.shape[3] % 4 == 0
+    xp = lib.pack_layout(dev(x), 64, cfg.pad)
+    wp = lib.pack_weights(dev(w), lib.LAYOUT_PACKED, 64)
+    for tile in range(lib.num_tiles()):
+        if not lib.tile_applies(cfg.dims(), lib.LAYOUT_PACKED, 64, tile, 1):
+            continue
+        buf = torch.full((want.size + 131,), -7, dtype=torch.int32, device=DEV)
+        out = buf[65:65 + want.size].view(want.shape)
+        lib.conv2d_int8_packed(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, out, tile=tile, split_k=1)
+        got = host(buf)
+        assert np.array_equal(got[65:-66].reshape(want.shape), want), tile
+        assert (got[:65] == -7).all() and (got[-66:] == -7).all(), tile
+
+
+@pytest.mark.parametrize("N", [48, 230], ids=["77MB", "369MB"])
+def test_large_results_of_large_tiles(lib, N):
+    """Results that go through LDS into the caches (between what the L2s and the last-level cache hold) and past them: the same words
+    as the smallest tile's, which stores dwords straight from its blocks."""
+    cfg = ConvShape("large", N, 64, 28, 28, 512, 3, 3, 1, 1)
+    x = torch.randint(-128, 128, (cfg.N, cfg.C, cfg.H, cfg.W), dtype=torch.int8, device=DEV)
+    w = torch.randint(-128, 128, (cfg.K, cfg.C, cfg.R, cfg.S), dtype=torch.int8, device=DEV)
+    xp = lib.pack_layout(x, 64, cfg.pad)
+    wp = lib.pack_weights(w, lib.LAYOUT_PACKED, 64)
+    want = torch.empty((cfg.N, cfg.K, 28, 28), dtype=torch.int32, device=DEV)
+    lib.conv2d_int8_packed(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, want, tile=0, split_k=1)
+    for tile in range(lib.num_tiles()):
+        if lib.tile_info(tile)[0] * lib.tile_info(tile)[1] < 128 * 256 or not lib.tile_applies(cfg.dims(), lib.LAYOUT_PACKED, 64, tile, 1):
+            continue
+        out = torch.full_like(want, -7)
+        lib.conv2d_int8_packed(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, out, tile=tile, split_k=1)
+        assert torch.equal(out, want), tile
+
+
 BLOCK64 = [
     ConvShape("k-tail", 3, 128, 9, 9, 70, 3, 3, 1, 1), ConvShape("5x5-stride2", 1, 128, 13, 11, 64, 5, 5, 2, 2),
     ConvShape("1x5", 2, 128, 6, 20, 33, 1, 5, 1, 0), ConvShape("3x3-odd-blocks", 2, 192, 7, 7, 64, 3, 3, 1, 1),
