@@ -977,7 +977,7 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
         // above 256 MB does not fit the last-level cache, and as plain stores it pushes the operands out of the L2s (2048 images
         // 256 x 14 x 14 -> 512: 550 us, with an input that fits the L2s 485; past the caches that makes no difference): 5 drawn layers
         // take 0.85 of the time.  One that fits the L2s is otherwise written back when the kernel ends: 41 drawn layers of up to 32 MB
-        // take 0.90, the worst 1.00.  Between the two a result that is written again is still in the last-level cache, and past it takes
+        // take 0.90, the worst 1.00 (the line is drawn lower, by the window kernel's).  Between the two a result that is written again is still in the last-level cache, and past it takes
         // up to 1.08; there the eight-wave 256 x 256 tiles alone go through LDS into the caches (0.91 to 0.98 on planes of 14 x 14, the
         // smaller tiles 0.98 to 1.03).
         const double bytes = 4.0 * g.M * g.K;

@@ -4,9 +4,10 @@
 
 namespace c2i8 {
 
-// A result larger than the last-level cache (256 MB) leaves it anyway, one that fits the L2s (8 x 4 MB) is written back when the kernel
-// ends if it was not before; between the two a smaller one that is written again is still in the last-level cache.
-inline bool past_caches(double bytes) { return bytes > 256e6 || bytes <= 32e6; }
+// A result larger than the last-level cache (256 MB) leaves it anyway, one that fits the L2s (8 x 4 MB) beside the operands is written
+// back when the kernel ends if it was not before; between the two a smaller one that is written again is still in the last-level cache.
+constexpr double END_FLUSH_BYTES = 28e6;
+inline bool past_caches(double bytes) { return bytes > 256e6 || bytes <= END_FLUSH_BYTES; }
 
 // 16 bytes per lane to base + off (at any dword) past the caches.  Written out: of two stores to one address in two branches, one
 // of them __builtin_nontemporal_store, the compiler makes a single plain one.  The wait state behind it is the one that a vector

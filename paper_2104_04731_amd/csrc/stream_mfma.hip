@@ -718,7 +718,7 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
     a.win_off = a.zero_off + 64;
     a.tab_off = a.win_off + nbuf * a.buf_bytes;
     // Past the caches: whole 64-byte sectors per store instruction, of planes and tiles that hold whole ones (37 drawn layers 0.97 of the
-    // time, the worst 1.03); other planes of whole 16-byte pieces from 8 to 32 MB (0.98, 1.03) and above 256 (0.95, 0.97).  (From 32 to
+    // time, the worst 1.03); other planes of whole 16-byte pieces from 8 to 28 MB (0.98, 1.03) and above 256 (0.95, 0.97).  (From there to
     // 256 MB they take up to 1.28, below 8 up to 1.04, planes of other sizes up to 1.13.)
     const double bytes = 4.0 * g.M * g.K;
     const bool sectors = PQ % 16 == 0 && mper % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0;

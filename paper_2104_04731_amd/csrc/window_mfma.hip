@@ -30,6 +30,7 @@
 // A lane's four results are four consecutive channels of a pixel, which is what an NHWC result stores.
 #include "kernels.h"
 #include "launch.h"
+#include "store_past.h"
 #include "rewrite_bodies.h"
 
 namespace c2i8 {
@@ -468,9 +469,6 @@ int window_depth(int C, int R, int S)
 
 constexpr long long WINDOW_LIMIT = 40 * 1024;  // bytes of LDS the input window of a tile may take
 
-// A result this large goes past the last-level cache (256 MB) anyway.
-constexpr double STREAM_BYTES = 256e6;
-
 // How many row groups a tile takes (a kernel of its own from 2 on): its window's rows overlap, the weights and the table are
 // brought in once.  Measured over 110 stem and speech layers.  Up to 32 output channels the time goes into filling the LDS:
 // the most of 2, 4, 8 that leaves two workgroups for each place on the chip (kept weights, 353 images 3 x 212 x 166, 7 x 7 / 2
@@ -519,13 +517,13 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     const int QT = 32 << w.qshift;
     const int S4 = (S + 3) / 4 * 4;
     const long long pitch = (((long long)(QT - 1) * stride_w + S4 + 3) + 3) / 4 * 4;
-    // whole 64-byte sectors per 16 pixels, and more than the caches keep: stored past them.  3 x 224 x 224, 7 x 7 / 2 -> 64, plain ->
-    // streamed: 87 images (279 MB) 76 -> 64 us, 300 (963 MB) 239 -> 207, 512 396 -> 350: 4.6 to 4.9 TB/s all along.  Over ten layers of
-    // 300 MB to 1.6 GB 2 to 27 % less, level in six cases of forty, and 7 % more for a 3 x 3 / 2 -> 32 from 960 MB on.  
-    // (most results of this size are the stencil kernel's, in stencil_mfma.hip; what it leaves comes here.)  At 205 MB
-    // it gains on a result that is written once (56 -> 48), but one that is written again is still in the last-level cache and takes 37
-    // with plain stores.  (Partial sectors come out up to 2.5 times slower that way.)
-    w.stream_out = !g.nhwc && !g.act.out && g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && 4.0 * g.N * g.K * g.P * g.Q > STREAM_BYTES;
+    // Whole 64-byte sectors per 16 pixels, and more than the caches keep or so little that the L2s write it back when the kernel ends:
+    // stored past them.  3 x 224 x 224, 7 x 7 / 2 -> 64, plain -> past: 87 images (279 MB) 76 -> 64 us, 300 (963 MB) 239 -> 207, 512
+    // 396 -> 350 (most results of this size are the stencil kernel's, in stencil_mfma.hip; what it leaves comes here); 4 images (13 MB)
+    // 7.06 -> 6.62, 8 (26 MB) 9.57 -> 8.53; 3 x 192 x 160, 3 x 3 / 2 -> 64, 8 images (16 MB) 6.61 -> 6.06, 12 (24 MB) 7.79 -> 6.95.  Between
+    // the two a result that is written again is still in the last-level cache: 16 of the latter (31 MB) 8.82 -> 9.17, 24 (47 MB)
+    // 11.4 -> 13.1.  Partial sectors come out slower that way (4 x 1 x 161 x 500, 20 x 5 / 2 -> 32: 6.11 -> 6.46).
+    w.stream_out = !g.nhwc && !g.act.out && g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && past_caches(4.0 * g.N * g.K * g.P * g.Q);
     w.G = window_groups(g, w.PT, QT, C * pitch, depth, w.stream_out);
     const long long RW = (long long)(w.PT * w.G - 1) * g.stride + g.R;
     if (RW > WINDOW_LIMIT || pitch > WINDOW_LIMIT || C * RW * pitch > WINDOW_LIMIT) return false;

@@ -772,6 +772,23 @@ def test_implicit_configs(lib, name):
         assert np.array_equal(got, want), f"{name} rewritten={rewritten}: {np.count_nonzero(got != want)} mismatches"
 
 
+@pytest.mark.parametrize("K", [7, 64, 90])
+@pytest.mark.parametrize("Q", [16, 48, 160])
+def test_implicit_rows_of_whole_sectors(lib, Q, K):
+    """Rows of whole 64-byte sectors leave past the caches where the result starts on 64 bytes, and through them where it does not:
+    one, two and four rows to a tile, the last ones outside the image, channels that end inside a block; nothing is written beside it."""
+    cfg = ConvShape("sectors", 3, 3, 7, Q, K, 3, 3, 1, 1)
+    x = uniform_int8(353, (cfg.N, cfg.C, cfg.H, cfg.W)); w = uniform_int8(354, (cfg.K, cfg.C, cfg.R, cfg.S))
+    want = direct.conv2d_int8(x, w, 1, 1)
+    for start in (64, 68, 65):
+        buf = torch.full((want.size + 132,), -7, dtype=torch.int32, device=DEV)
+        out = buf[start:start + want.size].view(want.shape)
+        lib.conv2d_int8_ex(cfg.dims(), lib.LAYOUT_IMPLICIT, 0, dev(x), dev(w), out, None)
+        got = host(buf)
+        assert np.array_equal(got[start:start + want.size].reshape(want.shape), want), start
+        assert (got[:start] == -7).all() and (got[start + want.size:] == -7).all(), start
+
+
 IMPLICIT_SHAPES = [
     ConvShape("row-tile-tail", 2, 3, 20, 150, 64, 7, 7, 2, 3), ConvShape("two-row-tile", 2, 3, 11, 90, 33, 3, 3, 2, 1),
     ConvShape("four-row-tile", 3, 4, 10, 30, 70, 3, 3, 1, 1), ConvShape("odd-width", 1, 2, 9, 13, 5, 3, 5, 1, 2),
