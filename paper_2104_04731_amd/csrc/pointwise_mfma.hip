@@ -20,6 +20,7 @@
 #include "kernels.h"
 #include "launch.h"
 #include "rewrite_bodies.h"
+#include "store_past.h"
 
 namespace c2i8 {
 
@@ -52,7 +53,7 @@ __device__ __forceinline__ v4i ld_v4(const void *p)  // any alignment
     return x;
 }
 
-template <int NKK, bool ACT>  // C = 32 * NKK; ACT: the activation epilogue (a kernel of its own: the plain one stays as lean as it was)
+template <int NKK, bool ACT, bool PAST>  // C = 32 * NKK; ACT: the activation epilogue (a kernel of its own: the plain one stays as lean as it was)
 __global__ void __launch_bounds__(256) conv_pointwise_kernel(const PointArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -139,7 +140,9 @@ __global__ void __launch_bounds__(256) conv_pointwise_kernel(const PointArgs a)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int kr = 8 * (v >> 2) + (v & 3);
-            if (k0 + 4 * half + kr < a.K) base[(size_t)kr * a.HW] = acc[v];
+            if (k0 + 4 * half + kr >= a.K) continue;
+            if constexpr (PAST) __builtin_nontemporal_store(acc[v], base + (size_t)kr * a.HW);
+            else base[(size_t)kr * a.HW] = acc[v];
         }
     }
     if (lid + (int)gridDim.x >= a.ntiles) break;
@@ -448,10 +451,12 @@ static hipError_t launch_pointwise_image(const WindowProblem &g, hipStream_t st)
 }
 
 template <int NKK>
-hipError_t launch_nkk(const PointArgs &a, dim3 grid, hipStream_t st)
+hipError_t launch_nkk(const PointArgs &a, dim3 grid, bool past, hipStream_t st)
 {
-    if (a.act.out) return launch((conv_pointwise_kernel<NKK, true>), grid, dim3(256), (size_t)32 * (32 * NKK + 16), st, a);
-    else return launch((conv_pointwise_kernel<NKK, false>), grid, dim3(256), (size_t)32 * (32 * NKK + 16), st, a);
+    const size_t lds = (size_t)32 * (32 * NKK + 16);
+    if (a.act.out) return launch((conv_pointwise_kernel<NKK, true, false>), grid, dim3(256), lds, st, a);
+    if (past) return launch((conv_pointwise_kernel<NKK, false, true>), grid, dim3(256), lds, st, a);
+    return launch((conv_pointwise_kernel<NKK, false, false>), grid, dim3(256), lds, st, a);
 }
 
 template <int NKK>
@@ -535,15 +540,19 @@ hipError_t launch_pointwise_conv(const WindowProblem &g, hipStream_t st)
     int wgs = 256 * 4 / kgroups;  // about four workgroups fit a CU
     if (wgs < 256) wgs = 256;
     const dim3 grid((unsigned)(a.ntiles < wgs ? a.ntiles : wgs), (unsigned)kgroups);
+    // Whole 64-byte sectors of a result that the L2s would write back when the kernel ends go past them (16 images 256 x 28 x 28 -> 256:
+    // 8.0 -> 7.2 us, 8 images 128 x 56 x 56 -> 256 8.8 -> 8.3; level below 10 MB, and above what the last-level cache holds).
+    const double bytes = 4.0 * g.N * g.K * g.H * g.W;
+    const bool past = a.HW % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && bytes >= 8e6 && bytes <= END_FLUSH_BYTES;
     switch (g.C / 32) {
-        case 2: return launch_nkk<2>(a, grid, st);
-        case 4: return launch_nkk<4>(a, grid, st);
-        case 6: return launch_nkk<6>(a, grid, st);
-        case 8: return launch_nkk<8>(a, grid, st);
-        case 10: return launch_nkk<10>(a, grid, st);
-        case 12: return launch_nkk<12>(a, grid, st);
-        case 14: return launch_nkk<14>(a, grid, st);
-        case 16: return launch_nkk<16>(a, grid, st);
+        case 2: return launch_nkk<2>(a, grid, past, st);
+        case 4: return launch_nkk<4>(a, grid, past, st);
+        case 6: return launch_nkk<6>(a, grid, past, st);
+        case 8: return launch_nkk<8>(a, grid, past, st);
+        case 10: return launch_nkk<10>(a, grid, past, st);
+        case 12: return launch_nkk<12>(a, grid, past, st);
+        case 14: return launch_nkk<14>(a, grid, past, st);
+        case 16: return launch_nkk<16>(a, grid, past, st);
     }
     return hipErrorInvalidValue;
 }
