@@ -109,14 +109,19 @@ constexpr int slots_before(int l, int nq, int off, int qb)
     return n;
 }
 
-// The result of a large wave tile on its way through LDS: rows of TM pixels (four rows on are 32 banks on), 32 of each row of waves
-// per pass, in two buffers where they fit beside as many workgroups as the operand ring does.
+enum RowsOf : int { ROWS_NONE = 0, ROWS_NKPQ = 1, ROWS_NHWC = 2 };
+
+// The NKPQ result of a large wave tile on its way through LDS: rows of TM pixels (four rows on are 32 banks on), 32 of each row of waves
+// per pass, in two buffers where they fit beside as many workgroups as the operand ring does.  An NHWC result: a pixel's TK channels
+// to a row, 32 of each column of waves per pass, one buffer.
 constexpr int row_pitch(int tm) { return tm * 4 + 32; }
 constexpr int row_buffers(int tk, int tm, int wk, int row_bytes)
 {
     const int ring = (tk + tm) * row_bytes, two = 2 * wk * 32 * row_pitch(tm);
     return two <= ring || 160 * 1024 / two == 160 * 1024 / ring ? 2 : 1;
 }
+
+constexpr int pixel_pitch(int tk) { return tk * 4 + 16; }   // (eight pixels on are 32 banks on)
 
 // HELP extra waves per workgroup only move operands (they issue their share of the transfers
 // and keep the barriers, no MFMA): a wave moves about 1 KB per 140-180 cycles through the
@@ -132,11 +137,11 @@ constexpr int row_buffers(int tk, int tm, int wk, int row_bytes)
 // WPC > 1 caps the registers so that WPC workgroups fit one CU: while one of them waits at a
 // barrier or drains its output tile, the matrix pipe works for the other.
 //
-// ROWS: the NKPQ result leaves through LDS in whole rows of the tile (large wave tiles; kernels of their own, since the code beside
-// the other results made a fused activation's launch of 17 us 0.5 longer).
+// ROWS: the result leaves through LDS in whole rows of the tile, ROWS_NKPQ or ROWS_NHWC (large wave tiles; kernels of their own, since
+// the code beside the other results made a fused activation's launch of 17 us 0.5 longer).
 //
 // The body is a device function of (logical workgroup id, workgroup count, LDS base).
-template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int MODE, bool ROWS>
+template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int MODE, int ROWS>
 __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int nblocks, unsigned char *smem)
 {
     constexpr int NWM = WK * WM;           // waves of one multiplying group
@@ -534,7 +539,7 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
 
     }
 
-    if constexpr (ROWS) {
+    if constexpr (ROWS == ROWS_NKPQ) {
         // Through LDS, a pass per row block of every wave, so that a store instruction writes 16 bytes per lane of whole rows of
         // the tile: straight from the blocks it is FK * FM * 16 dword stores per lane, and a compute unit takes twelve clocks for a
         // store instruction whatever its width.  A 256 x 256 tile leaves in 3.6 us of its 36 where it took 7.5.  Every address but
@@ -580,6 +585,52 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
         auto passes = [&](auto inside, auto past) {
 #pragma unroll
             for (int i = 0; i < FK; ++i) pass(i, inside, past);
+        };
+        const bool inside = k0 + TK <= a.K && m0 + TM <= a.M;   // no test per row
+        if (!inside) passes(std::false_type{}, std::false_type{});
+        else if (a.rows == 2) passes(std::true_type{}, std::true_type{});
+        else passes(std::true_type{}, std::false_type{});
+        return;
+    }
+
+    if constexpr (ROWS == ROWS_NHWC) {
+        // The same for [N][P][Q][K]: a lane's four values v%4 are four channels of a pixel, a row is a pixel's TK channels, and a store
+        // instruction writes 1 KB of rows where it wrote 32 bytes of each of 32 pixels.
+        constexpr int PITCH = pixel_pitch(TK), PR = WM * 32;
+        constexpr int LPR4 = TK / 4, RPS = 64 / LPR4, NST = PR / (NWM * RPS);
+        static_assert(LPR4 <= 64 && PR % (NWM * RPS) == 0 && 32 % (NST * RPS) == 0, "a wave's rows belong to one column of waves");
+        const int r0 = wave * NST * RPS, mw = m0 + (r0 >> 5) * WTM + (r0 & 31);
+        const int kq = k0 + lane % LPR4 * 4;
+        const bool there = kq < a.K;   // (K is a multiple of four)
+        char *const to0 = reinterpret_cast<char *>(a.out) + ((size_t)mw * a.K + k0) * 4;
+        const unsigned row = (unsigned)a.K * 4u, off = (unsigned)(lane / LPR4) * row + (unsigned)(lane % LPR4) * 16u;
+        const unsigned char *const from = smem + (r0 + lane / LPR4) * PITCH + lane % LPR4 * 16;
+        unsigned char *const mine = smem + (wm * 32 + (lane & 31)) * PITCH + (wk * WTK + 4 * (lane >> 5)) * 4;
+        auto passes = [&](auto inside, auto past) {
+#pragma unroll
+            for (int f = 0; f < FM; ++f) {
+                lds_barrier();   // (the ring is idle: every transfer has landed)
+#pragma unroll
+                for (int i = 0; i < FK; ++i)
+#pragma unroll
+                    for (int vg = 0; vg < 4; ++vg)
+                        *reinterpret_cast<v4i *>(__builtin_assume_aligned(mine + (i * 32 + 8 * vg) * 4, 16)) =
+                            v4i{acc[i][f][4 * vg], acc[i][f][4 * vg + 1], acc[i][f][4 * vg + 2], acc[i][f][4 * vg + 3]};
+                lds_barrier();
+                v4i t[NST];
+#pragma unroll
+                for (int r = 0; r < NST; ++r) t[r] = *reinterpret_cast<const v4i *>(__builtin_assume_aligned(from + r * RPS * PITCH, 16));
+#pragma unroll
+                for (int r = 0; r < NST; ++r) {
+                    char *const to = to0 + (size_t)(f * 32 + r * RPS) * row;
+                    if constexpr (decltype(inside)::value) {
+                        if constexpr (decltype(past)::value) store_past16(to, off, t[r]);
+                        else *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                        continue;
+                    }
+                    if (there && mw + f * 32 + r * RPS + lane / LPR4 < a.M) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                }
+            }
         };
         const bool inside = k0 + TK <= a.K && m0 + TM <= a.M;   // no test per row
         if (!inside) passes(std::false_type{}, std::false_type{});
@@ -736,7 +787,7 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
     }
 }
 
-template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int WPC, int MODE, bool ROWS>
+template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int WPC, int MODE, int ROWS>
 __global__ void __launch_bounds__((WK * WM * DS + HELP) * 64, (WK * WM * DS + HELP + 3) / 4 * WPC)
     igemm_i8_kernel(const GemmArgs a)
 {
@@ -818,10 +869,12 @@ TileInfo gemm_tile_info(int t)
 // LDS a launch of tile `d` asks for: the operand ring plus, for the blocked layout, one offset per 16-byte
 // depth chunk of a slice (`per` 64-byte steps); or the rows of a result on their way out, where that is more.  The picker and the launcher use the same figure.
 constexpr size_t kLdsLimit = 160 * 1024;
-static size_t tile_lds_bytes(const TileDef &d, int mode, int per, bool by_rows)
+static size_t tile_lds_bytes(const TileDef &d, int mode, int per, int rows_of)
 {
     const size_t ring = (size_t)d.nstage * (d.tk + d.tm) * 64 * d.ks + (mode == ACT_BLOCKED ? (size_t)per * 16 : 0);
-    const size_t rows = by_rows && d.large() ? (size_t)row_buffers(d.tk, d.tm, d.wk, 64 * d.ks * d.nstage) * d.wk * 32 * row_pitch(d.tm) : 0;
+    size_t rows = 0;
+    if (d.large() && rows_of == ROWS_NKPQ) rows = (size_t)row_buffers(d.tk, d.tm, d.wk, 64 * d.ks * d.nstage) * d.wk * 32 * row_pitch(d.tm);
+    if (d.large() && rows_of == ROWS_NHWC) rows = (size_t)d.wm * 32 * pixel_pitch(d.tk);
     return ring > rows ? ring : rows;
 }
 
@@ -830,17 +883,22 @@ static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
 {
     constexpr int NT = (WK * WM * DS + HELP) * 64;
     constexpr TileDef tile{TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, 0, 0, 0};
-    const size_t lds = tile_lds_bytes(tile, mode, a.ksteps_per_split, a.rows != 0);
     const int grid = a.tiles_k * a.tiles_m * a.split_k;
-    void (*kern)(GemmArgs) = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, false>
-                                                 : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, false>;
-    if constexpr (tile.large())
-        if (a.rows)
-            kern = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, true>
-                                       : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, true>;
+    const int rows = !a.rows ? ROWS_NONE : a.out_nhwc ? ROWS_NHWC : ROWS_NKPQ;
+    void (*kern)(GemmArgs) = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, ROWS_NONE>
+                                                 : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, ROWS_NONE>;
+    if constexpr (tile.large()) {
+        if (rows == ROWS_NKPQ)
+            kern = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, ROWS_NKPQ>
+                                       : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, ROWS_NKPQ>;
+        if (rows == ROWS_NHWC)
+            kern = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, ROWS_NHWC>
+                                       : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, ROWS_NHWC>;
+    }
+    const size_t lds = tile_lds_bytes(tile, mode, a.ksteps_per_split, rows);
     if (lds > kLdsLimit) return hipErrorInvalidValue;  // the picker never offers such a pair
-    static size_t raised[2][2] = {};  // dynamic-LDS ceiling already granted, per kernel
-    size_t &granted = raised[mode][a.rows != 0];
+    static size_t raised[2][3] = {};  // dynamic-LDS ceiling already granted, per kernel
+    size_t &granted = raised[mode][rows];
     if (lds > 64 * 1024 && lds > granted) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -852,7 +910,7 @@ static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
 
 static int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
-size_t gemm_tile_lds_bytes(int t, int mode, int steps_per_slice) { return tile_lds_bytes(kTiles[t], mode, steps_per_slice, true); }
+size_t gemm_tile_lds_bytes(int t, int mode, int steps_per_slice) { return tile_lds_bytes(kTiles[t], mode, steps_per_slice, ROWS_NKPQ); }
 
 // A tile with 128- or 256-byte stages walks the depth two or four steps at a time: every slice
 // must be a whole number of stages.
@@ -900,7 +958,7 @@ bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost)
         for (int ci = 0; ci < ncand; ++ci) {
             const int s = slices[ci], per = pers[ci];
             if (!tile_fits(d, ksteps, per)) continue;
-            const size_t lds = tile_lds_bytes(d, g.mode, per, true);
+            const size_t lds = tile_lds_bytes(d, g.mode, per, ROWS_NKPQ);
             if (lds > kLdsLimit) continue;  // ring + offset table must fit one CU's LDS
             int cap = (int)kLdsLimit / (int)lds;
             if (cap > wave_cap) cap = wave_cap;
@@ -979,10 +1037,13 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
         // take 0.85 of the time.  One that fits the L2s is otherwise written back when the kernel ends: 41 drawn layers of up to 32 MB
         // take 0.90, the worst 1.00 (the line is drawn lower, by the window kernel's).  Between the two a result that is written again is still in the last-level cache, and past it takes
         // up to 1.08; there the eight-wave 256 x 256 tiles alone go through LDS into the caches (0.91 to 0.98 on planes of 14 x 14, the
-        // smaller tiles 0.98 to 1.03).
+        // smaller tiles 0.98 to 1.03).  NHWC results of whole 16-byte pieces always: 42 drawn 3 x 3 and 1 x 1 layers, up to 28 MB 0.79 and
+        // 0.90 of the time, 28 to 256 MB 1.00 and 0.97 (through the caches), above 0.81; the worst 1.007.
         const double bytes = 4.0 * g.M * g.K;
-        const bool can = d.large() && !a.act_out && !a.out_nhwc && !a.il_d && a.split_k == 1 && g.PQ % 4 == 0 && (d.tm / (long long)g.PQ + 2) * g.PQ * g.K < (1LL << 30);
-        a.rows = !can ? 0 : past_caches(bytes) ? 2 : d.tk == 256 && d.tm == 256 && d.wk * d.wm == 8 ? 1 : 0;
+        const bool can = d.large() && !a.act_out && !a.il_d && a.split_k == 1 &&
+                         (a.out_nhwc ? g.K % 4 == 0 && tile_lds_bytes(d, g.mode, a.ksteps_per_split, ROWS_NHWC) <= kLdsLimit
+                                     : g.PQ % 4 == 0 && (d.tm / (long long)g.PQ + 2) * g.PQ * g.K < (1LL << 30));
+        a.rows = !can ? 0 : past_caches(bytes) ? 2 : a.out_nhwc || (d.tk == 256 && d.tm == 256 && d.wk * d.wm == 8) ? 1 : 0;
     }
     {
         // Start offsets of the first round (see the kernel): worth their idle time where the launch runs several

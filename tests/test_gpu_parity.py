@@ -258,11 +258,11 @@ def test_conv_every_tile_and_split(lib, name):
 
 @pytest.mark.parametrize("cfg", [
     ConvShape("three-images-per-row", 5, 64, 14, 14, 260, 3, 3, 1, 1), ConvShape("many-images-per-tile", 70, 64, 2, 2, 520, 3, 3, 1, 1),
-    ConvShape("one-tile", 4, 128, 8, 8, 256, 3, 3, 1, 1), ConvShape("stride", 3, 64, 25, 31, 90, 3, 3, 2, 1),
+    ConvShape("one-tile", 4, 128, 8, 8, 256, 3, 3, 1, 1), ConvShape("stride", 3, 64, 25, 31, 92, 3, 3, 2, 1),
 ], ids=lambda c: c.name)
 def test_large_tiles_write_whole_rows(lib, cfg):
-    """Planes of whole 16-byte pieces: every tile of more than two blocks per wave writes rows that pass through LDS; channels and
-    pixels that end inside a tile, images that end inside a row, a result at any dword, and nothing written beside it."""
+    """Planes (NHWC: pixels) of whole 16-byte pieces: every tile of more than two blocks per wave writes rows that pass through LDS;
+    channels and pixels that end inside a tile, images that end inside a row, an NKPQ result at any dword, and nothing written beside it."""
     x = uniform_int8(351, (cfg.N, cfg.C, cfg.H, cfg.W)); w = uniform_int8(352, (cfg.K, cfg.C, cfg.R, cfg.S))
     want = direct.conv2d_int8(x, w, cfg.stride, cfg.pad)
     assert want.shape[2] * want.shape[3] % 4 == 0
@@ -271,12 +271,13 @@ def test_large_tiles_write_whole_rows(lib, cfg):
     for tile in range(lib.num_tiles()):
         if not lib.tile_applies(cfg.dims(), lib.LAYOUT_PACKED, 64, tile, 1):
             continue
-        buf = torch.full((want.size + 131,), -7, dtype=torch.int32, device=DEV)
-        out = buf[65:65 + want.size].view(want.shape)
-        lib.conv2d_int8_packed(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, out, tile=tile, split_k=1)
-        got = host(buf)
-        assert np.array_equal(got[65:-66].reshape(want.shape), want), tile
-        assert (got[:65] == -7).all() and (got[-66:] == -7).all(), tile
+        for run, shaped, at in ((lib.conv2d_int8_packed, want, 65), (lib.conv2d_int8_packed_nhwc, layouts.unpack_nhwc(want), 64)):
+            buf = torch.full((want.size + 131,), -7, dtype=torch.int32, device=DEV)
+            out = buf[at:at + want.size].view(shaped.shape)
+            run(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, out, tile=tile, split_k=1)
+            got = host(buf)
+            assert np.array_equal(got[at:at + want.size].reshape(shaped.shape), shaped), (tile, run.__name__)
+            assert (got[:at] == -7).all() and (got[at + want.size:] == -7).all(), (tile, run.__name__)
 
 
 @pytest.mark.parametrize("N", [48, 230], ids=["77MB", "369MB"])
