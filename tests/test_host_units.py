@@ -104,3 +104,23 @@ def test_given_and_kept_1x1_weights_take_the_same_launch(lib, dims):
     """A 1x1 layer of whole 64 channels: its raw weights are in depth order as they are, so the two calls read the same bytes."""
     raw = lib.query_stage(dims, lib.ENTRY_ONE_SHOT)
     assert raw[0] == lib.STAGE_RESIDENT and lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True) == raw
+
+
+def test_stores_past_the_caches_keep_their_wait_states(tmp_path):
+    """A vector instruction that writes a 16-byte store's registers stands as far behind the store written out as behind one of the compiler's."""
+    listing = tmp_path / "store_past.s"
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-S", "--cuda-device-only", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    os.path.join(HERE, "store_past.hip"), "-o", str(listing)], check=True, capture_output=True, timeout=120)
+
+    def states(kernel):
+        lines = listing.read_text().split(f"\n{kernel}:")[1].split("\n", 1)[1].split("s_endpgm")[0].splitlines()
+        code = [s for s in (line.split(";")[0].split() for line in lines) if s and not s[0].endswith(":")]
+        at = next(i for i, s in enumerate(code) if s[0] == "global_store_dwordx4")
+        n = 0
+        for s in code[at + 1:]:
+            if s[0].startswith("v_"):
+                return n
+            n += int(s[1]) + 1 if s[0] == "s_nop" else 1
+        raise AssertionError("no vector instruction behind the store")
+
+    assert states("store_written_out") >= states("store_compiled") >= 1
