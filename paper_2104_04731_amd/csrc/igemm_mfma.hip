@@ -109,7 +109,7 @@ constexpr int slots_before(int l, int nq, int off, int qb)
     return n;
 }
 
-enum RowsOf : int { ROWS_NONE = 0, ROWS_NKPQ = 1, ROWS_NHWC = 2 };
+enum RowsOf : int { ROWS_NONE = 0, ROWS_NKPQ = 1, ROWS_NHWC = 2, ROWS_ACT = 3 };
 
 // The NKPQ result of a large wave tile on its way through LDS: rows of TM pixels (four rows on are 32 banks on), 32 of each row of waves
 // per pass, in two buffers where they fit beside as many workgroups as the operand ring does.  An NHWC result: a pixel's TK channels
@@ -138,7 +138,8 @@ constexpr int pixel_pitch(int tk) { return tk * 4 + 16; }   // (eight pixels on 
 // barrier or drains its output tile, the matrix pipe works for the other.
 //
 // ROWS: the result leaves through LDS in whole rows of the tile, ROWS_NKPQ or ROWS_NHWC (large wave tiles; kernels of their own, since
-// the code beside the other results made a fused activation's launch of 17 us 0.5 longer).
+// the code beside the other results made a fused activation's launch of 17 us 0.5 longer).  ROWS_ACT: a fused activation and no other
+// result, 12 KB of code where both were 30 (32 images 256 x 14 x 14 -> 512, blocked chain of three launches: 23.6 -> 23.4 us).
 //
 // The body is a device function of (logical workgroup id, workgroup count, LDS base).
 template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int MODE, int ROWS>
@@ -641,7 +642,7 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
 
     // Epilogue: D block (i, jm): column = lane%32 (pixel), row = 8*(v/4) + 4*(lane/32) + v%4.
     // Consecutive lanes write consecutive pixels of one output plane: 128-byte runs in NKPQ.
-    if (a.act_out) {
+    if constexpr (ROWS == ROWS_ACT) {
         // Fused activation: the four values v%4 of a lane are four consecutive output channels of one
         // pixel -- one dword of that pixel's channel-contiguous run in the next layer's blocked input.
         const int o_cb = 1 << a.o_cb_log2;
@@ -884,9 +885,12 @@ static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
     constexpr int NT = (WK * WM * DS + HELP) * 64;
     constexpr TileDef tile{TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, 0, 0, 0};
     const int grid = a.tiles_k * a.tiles_m * a.split_k;
-    const int rows = !a.rows ? ROWS_NONE : a.out_nhwc ? ROWS_NHWC : ROWS_NKPQ;
+    const int rows = a.act_out ? ROWS_ACT : !a.rows ? ROWS_NONE : a.out_nhwc ? ROWS_NHWC : ROWS_NKPQ;
     void (*kern)(GemmArgs) = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, ROWS_NONE>
                                                  : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, ROWS_NONE>;
+    if (rows == ROWS_ACT)
+        kern = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, ROWS_ACT>
+                                   : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, ROWS_ACT>;
     if constexpr (tile.large()) {
         if (rows == ROWS_NKPQ)
             kern = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, ROWS_NKPQ>
@@ -897,7 +901,7 @@ static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
     }
     const size_t lds = tile_lds_bytes(tile, mode, a.ksteps_per_split, rows);
     if (lds > kLdsLimit) return hipErrorInvalidValue;  // the picker never offers such a pair
-    static size_t raised[2][3] = {};  // dynamic-LDS ceiling already granted, per kernel
+    static size_t raised[2][4] = {};  // dynamic-LDS ceiling already granted, per kernel
     size_t &granted = raised[mode][rows];
     if (lds > 64 * 1024 && lds > granted) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
