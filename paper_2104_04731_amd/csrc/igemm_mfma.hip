@@ -558,6 +558,7 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
         const bool there = mq < a.M;   // (planes are whole quads, and so is M)
         const int r0 = wave * NST * RPS, kw = k0 + (r0 >> 5) * WTK + (r0 & 31);
         char *const to0 = reinterpret_cast<char *>(a.out) + ((size_t)n0 * a.K + (size_t)kw) * row;
+        const auto base = past_base(to0);
         const unsigned char *const from = smem + (r0 + lane / LPR4) * PITCH + lane % LPR4 * 16;
         unsigned char *const mine = smem + (wk * 32 + 4 * (lane >> 5)) * PITCH + (wm * WTM + (lane & 31)) * 4;
         lds_barrier();   // (the ring is idle: every transfer has landed)
@@ -574,13 +575,13 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
             for (int r = 0; r < NST; ++r) t[r] = *reinterpret_cast<const v4i *>(__builtin_assume_aligned(from + b + r * RPS * PITCH, 16));
 #pragma unroll
             for (int r = 0; r < NST; ++r) {
-                char *const to = to0 + (size_t)(i * 32 + r * RPS) * row;
-                if constexpr (decltype(inside)::value) {
-                    if constexpr (decltype(past)::value) store_past16(to, off, t[r]);
-                    else *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                if constexpr (decltype(past)::value) {
+                    store_past16(base, off, (unsigned)(i * 32 + r * RPS) * row, t[r]);
                     continue;
                 }
-                if (there && kw + i * 32 + r * RPS + lane / LPR4 < a.K) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                char *const to = to0 + (size_t)(i * 32 + r * RPS) * row;
+                if (decltype(inside)::value) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                else if (there && kw + i * 32 + r * RPS + lane / LPR4 < a.K) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
             }
         };
         auto passes = [&](auto inside, auto past) {
@@ -604,6 +605,7 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
         const int kq = k0 + lane % LPR4 * 4;
         const bool there = kq < a.K;   // (K is a multiple of four)
         char *const to0 = reinterpret_cast<char *>(a.out) + ((size_t)mw * a.K + k0) * 4;
+        const auto base = past_base(to0);
         const unsigned row = (unsigned)a.K * 4u, off = (unsigned)(lane / LPR4) * row + (unsigned)(lane % LPR4) * 16u;
         const unsigned char *const from = smem + (r0 + lane / LPR4) * PITCH + lane % LPR4 * 16;
         unsigned char *const mine = smem + (wm * 32 + (lane & 31)) * PITCH + (wk * WTK + 4 * (lane >> 5)) * 4;
@@ -623,13 +625,13 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
                 for (int r = 0; r < NST; ++r) t[r] = *reinterpret_cast<const v4i *>(__builtin_assume_aligned(from + r * RPS * PITCH, 16));
 #pragma unroll
                 for (int r = 0; r < NST; ++r) {
-                    char *const to = to0 + (size_t)(f * 32 + r * RPS) * row;
-                    if constexpr (decltype(inside)::value) {
-                        if constexpr (decltype(past)::value) store_past16(to, off, t[r]);
-                        else *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                    if constexpr (decltype(past)::value) {
+                        store_past16(base, off, (unsigned)(f * 32 + r * RPS) * row, t[r]);
                         continue;
                     }
-                    if (there && mw + f * 32 + r * RPS + lane / LPR4 < a.M) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                    char *const to = to0 + (size_t)(f * 32 + r * RPS) * row;
+                    if (decltype(inside)::value) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                    else if (there && mw + f * 32 + r * RPS + lane / LPR4 < a.M) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
                 }
             }
         };
@@ -1045,7 +1047,7 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
         // 0.90 of the time, 28 to 256 MB 1.00 and 0.97 (through the caches), above 0.81; the worst 1.007.
         const double bytes = 4.0 * g.M * g.K;
         const bool can = d.large() && !a.act_out && !a.il_d && a.split_k == 1 &&
-                         (a.out_nhwc ? g.K % 4 == 0 && tile_lds_bytes(d, g.mode, a.ksteps_per_split, ROWS_NHWC) <= kLdsLimit
+                         (a.out_nhwc ? g.K % 4 == 0 && (long long)d.tm * g.K < (1LL << 30) && tile_lds_bytes(d, g.mode, a.ksteps_per_split, ROWS_NHWC) <= kLdsLimit
                                      : g.PQ % 4 == 0 && (d.tm / (long long)g.PQ + 2) * g.PQ * g.K < (1LL << 30));
         a.rows = !can ? 0 : past_caches(bytes) ? 2 : a.out_nhwc || (d.tk == 256 && d.tm == 256 && d.wk * d.wm == 8) ? 1 : 0;
     }

@@ -480,6 +480,7 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
         // a wave's rows follow one another: their places are scalar, and which of them exist is asked for the tile as a whole
         const int r0 = wave * NS * RPI, kw = k0 + (r0 >> 5) * FK * 32 + (r0 & 31);
         char *const to0 = reinterpret_cast<char *>(a.out) + ((size_t)w.n0 * a.K + (size_t)kw) * row;
+        const auto base = past_base(to0);
         const unsigned char *const from = smem + (r0 + lane / LPR) * PITCH + quad * 16;
         st_barrier();
         auto passes = [&](auto inside, auto past) {
@@ -503,10 +504,9 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
                 if (whole) {
 #pragma unroll
                     for (int r = 0; r < NS; ++r) {
-                        char *const to = to0 + (size_t)(i * 32 + r * RPI) * row;
                         if (!there(r)) continue;
-                        if constexpr (decltype(past)::value) store_past16(to, off, t[r]);
-                        else *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                        if constexpr (decltype(past)::value) store_past16(base, off, (unsigned)(i * 32 + r * RPI) * row, t[r]);
+                        else *reinterpret_cast<v4i_a4 *>(to0 + (size_t)(i * 32 + r * RPI) * row + off) = t[r];
                     }
                 } else if (ok) {   // (two images meet in the four pixels -- or more, of fewer than four -- or the tile ends)
 #pragma unroll

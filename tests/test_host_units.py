@@ -106,21 +106,45 @@ def test_given_and_kept_1x1_weights_take_the_same_launch(lib, dims):
     assert raw[0] == lib.STAGE_RESIDENT and lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True) == raw
 
 
-def test_stores_past_the_caches_keep_their_wait_states(tmp_path):
-    """A vector instruction that writes a 16-byte store's registers stands as far behind the store written out as behind one of the compiler's."""
-    listing = tmp_path / "store_past.s"
+@pytest.fixture(scope="module")
+def store_listing(tmp_path_factory):
+    """kernel -> its instructions, as lists of words"""
+    listing = tmp_path_factory.mktemp("listing") / "store_past.s"
     subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-S", "--cuda-device-only", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                     os.path.join(HERE, "store_past.hip"), "-o", str(listing)], check=True, capture_output=True, timeout=120)
 
-    def states(kernel):
+    def code(kernel):
         lines = listing.read_text().split(f"\n{kernel}:")[1].split("\n", 1)[1].split("s_endpgm")[0].splitlines()
-        code = [s for s in (line.split(";")[0].split() for line in lines) if s and not s[0].endswith(":")]
-        at = next(i for i, s in enumerate(code) if s[0] == "global_store_dwordx4")
-        n = 0
-        for s in code[at + 1:]:
-            if s[0].startswith("v_"):
-                return n
-            n += int(s[1]) + 1 if s[0] == "s_nop" else 1
-        raise AssertionError("no vector instruction behind the store")
+        return [s for s in (line.split(";")[0].replace(",", " ").split() for line in lines) if s and not s[0].endswith(":")]
+    return code
 
-    assert states("store_written_out") >= states("store_compiled") >= 1
+
+def wait_states(code):
+    return sum(int(s[1]) + 1 if s[0] == "s_nop" else 1 for s in code)
+
+
+def is_store(s):
+    return s[0] in ("global_store_dwordx4", "buffer_store_dwordx4")
+
+
+def test_stores_past_the_caches_keep_their_wait_states(store_listing):
+    """A vector instruction that writes a 16-byte store's registers stands as far behind the store past the caches as behind one of the compiler's."""
+    def states(kernel):
+        code = store_listing(kernel)
+        at = next(i for i, s in enumerate(code) if is_store(s))
+        return wait_states(code[at + 1:next(i for i, s in enumerate(code) if i > at and s[0].startswith("v_"))])
+
+    assert states("rewritten_behind_past") >= states("rewritten_behind_compiled") >= 1
+
+
+def test_stores_past_the_caches_wait_for_their_base(store_listing):
+    """A base that a vector instruction writes is five wait states old when the store reads it."""
+    code = store_listing("base_written_past")
+    at = next(i for i, s in enumerate(code) if is_store(s))
+    wrote = [i for i in range(at) if code[i][0] == "v_readfirstlane_b32"]
+    assert len(wrote) == 2 and wait_states(code[wrote[-1] + 1:at]) >= 5
+
+
+def test_stores_past_the_caches_are_not_merged_with_plain_ones(store_listing):
+    stores = [s for s in store_listing("two_branches") if is_store(s)]
+    assert len(stores) == 2 and sum("nt" in s for s in stores) == 1
