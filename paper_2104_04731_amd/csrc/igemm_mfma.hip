@@ -56,7 +56,7 @@ struct GemmArgs {
     int out_nhwc;  // `out` is [N][P][Q][K] instead of [N][K][P][Q]
     int grp_m;     // > 0: tile order in groups of grp_m pixel tiles (below); 0: one of the two row-major orders
     unsigned mg_grp_sz, mg_grp_m, mg_tiles_km;  // ceil(2^32 / d) for grp_m * tiles_k, grp_m, tiles_k * tiles_m
-    int rows;      // large wave tiles: NKPQ result through LDS in whole rows of the tile, 1: stored through the caches, 2: past them
+    int rows;      // large wave tiles: NKPQ result through LDS in whole rows of the tile, RowsHow
     int stagger;   // start offsets of the first round of workgroups: this many 64-cycle units per phase step (0: none)
 };
 
@@ -109,6 +109,7 @@ constexpr int slots_before(int l, int nq, int off, int qb)
     return n;
 }
 
+enum RowsHow : int { ROWS_CACHED = 1, ROWS_STREAM, ROWS_THROUGH };   // into the caches, or past them (store_past.h)
 enum RowsOf : int { ROWS_NONE = 0, ROWS_NKPQ = 1, ROWS_NHWC = 2, ROWS_ACT = 3 };
 
 // The NKPQ result of a large wave tile on its way through LDS: rows of TM pixels (four rows on are 32 banks on), 32 of each row of waves
@@ -575,8 +576,8 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
             for (int r = 0; r < NST; ++r) t[r] = *reinterpret_cast<const v4i *>(__builtin_assume_aligned(from + b + r * RPS * PITCH, 16));
 #pragma unroll
             for (int r = 0; r < NST; ++r) {
-                if constexpr (decltype(past)::value) {
-                    store_past16(base, off, (unsigned)(i * 32 + r * RPS) * row, t[r]);
+                if constexpr (decltype(past)::value != PAST_NONE) {
+                    store_past16<decltype(past)::value>(base, off, (unsigned)(i * 32 + r * RPS) * row, t[r]);
                     continue;
                 }
                 char *const to = to0 + (size_t)(i * 32 + r * RPS) * row;
@@ -589,9 +590,10 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
             for (int i = 0; i < FK; ++i) pass(i, inside, past);
         };
         const bool inside = k0 + TK <= a.K && m0 + TM <= a.M;   // no test per row
-        if (!inside) passes(std::false_type{}, std::false_type{});
-        else if (a.rows == 2) passes(std::true_type{}, std::true_type{});
-        else passes(std::true_type{}, std::false_type{});
+        if (!inside) passes(std::false_type{}, PastHow<PAST_NONE>{});
+        else if (a.rows == ROWS_THROUGH) passes(std::true_type{}, PastHow<PAST_THROUGH>{});
+        else if (a.rows == ROWS_STREAM) passes(std::true_type{}, PastHow<PAST_STREAM>{});
+        else passes(std::true_type{}, PastHow<PAST_NONE>{});
         return;
     }
 
@@ -625,8 +627,8 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
                 for (int r = 0; r < NST; ++r) t[r] = *reinterpret_cast<const v4i *>(__builtin_assume_aligned(from + r * RPS * PITCH, 16));
 #pragma unroll
                 for (int r = 0; r < NST; ++r) {
-                    if constexpr (decltype(past)::value) {
-                        store_past16(base, off, (unsigned)(f * 32 + r * RPS) * row, t[r]);
+                    if constexpr (decltype(past)::value != PAST_NONE) {
+                        store_past16<decltype(past)::value>(base, off, (unsigned)(f * 32 + r * RPS) * row, t[r]);
                         continue;
                     }
                     char *const to = to0 + (size_t)(f * 32 + r * RPS) * row;
@@ -636,9 +638,10 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
             }
         };
         const bool inside = k0 + TK <= a.K && m0 + TM <= a.M;   // no test per row
-        if (!inside) passes(std::false_type{}, std::false_type{});
-        else if (a.rows == 2) passes(std::true_type{}, std::true_type{});
-        else passes(std::true_type{}, std::false_type{});
+        if (!inside) passes(std::false_type{}, PastHow<PAST_NONE>{});
+        else if (a.rows == ROWS_THROUGH) passes(std::true_type{}, PastHow<PAST_THROUGH>{});
+        else if (a.rows == ROWS_STREAM) passes(std::true_type{}, PastHow<PAST_STREAM>{});
+        else passes(std::true_type{}, PastHow<PAST_NONE>{});
         return;
     }
 
@@ -1040,8 +1043,9 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
         // NKPQ results of large wave tiles through LDS (see the kernel), on planes of whole 16-byte pieces, and past the caches.  A result
         // above 256 MB does not fit the last-level cache, and as plain stores it pushes the operands out of the L2s (2048 images
         // 256 x 14 x 14 -> 512: 550 us, with an input that fits the L2s 485; past the caches that makes no difference): 5 drawn layers
-        // take 0.85 of the time.  One that fits the L2s is otherwise written back when the kernel ends: 41 drawn layers of up to 32 MB
-        // take 0.90, the worst 1.00 (the line is drawn lower, by the window kernel's).  Between the two a result that is written again is still in the last-level cache, and past it takes
+        // take 0.85 of the time.  One that fits the L2s is otherwise written back when the kernel ends: 41 drawn layers of up to 32 MB take
+        // 0.90, the worst 1.00, non-temporal (the line is drawn lower, by the window kernel's), and 7 of 6 to 26 MB another 0.98 written
+        // through.  Between the two a result that is written again is still in the last-level cache, and past it takes
         // up to 1.08; there the eight-wave 256 x 256 tiles alone go through LDS into the caches (0.91 to 0.98 on planes of 14 x 14, the
         // smaller tiles 0.98 to 1.03).  NHWC results of whole 16-byte pieces always: 42 drawn 3 x 3 and 1 x 1 layers, up to 28 MB 0.79 and
         // 0.90 of the time, 28 to 256 MB 1.00 and 0.97 (through the caches), above 0.81; the worst 1.007.
@@ -1049,7 +1053,9 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
         const bool can = d.large() && !a.act_out && !a.il_d && a.split_k == 1 &&
                          (a.out_nhwc ? g.K % 4 == 0 && (long long)d.tm * g.K < (1LL << 30) && tile_lds_bytes(d, g.mode, a.ksteps_per_split, ROWS_NHWC) <= kLdsLimit
                                      : g.PQ % 4 == 0 && (d.tm / (long long)g.PQ + 2) * g.PQ * g.K < (1LL << 30));
-        a.rows = !can ? 0 : past_caches(bytes) ? 2 : a.out_nhwc || (d.tk == 256 && d.tm == 256 && d.wk * d.wm == 8) ? 1 : 0;
+        const Past past = past_caches(bytes);
+        a.rows = !can ? 0 : past == PAST_THROUGH ? ROWS_THROUGH : past == PAST_STREAM ? ROWS_STREAM
+                          : a.out_nhwc || (d.tk == 256 && d.tm == 256 && d.wk * d.wm == 8) ? ROWS_CACHED : 0;
     }
     {
         // Start offsets of the first round (see the kernel): worth their idle time where the launch runs several
@@ -1063,7 +1069,7 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
         const long long grid = (long long)a.tiles_k * a.tiles_m * a.split_k;
         a.stagger = 0;
         if (grid >= 2 * 256 && a.split_k == 1 && epi_clk >= 16000 && epi_clk >= 0.15 * (main_clk + epi_clk)) {
-            a.stagger = (int)((a.rows == 2 ? 1.25 : 2.0) * epi_clk / (32 * 64) + 0.5);
+            a.stagger = (int)((a.rows > ROWS_CACHED ? 1.25 : 2.0) * epi_clk / (32 * 64) + 0.5);
         }
     }
     {

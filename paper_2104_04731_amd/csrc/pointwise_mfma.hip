@@ -137,11 +137,12 @@ __global__ void __launch_bounds__(256) conv_pointwise_kernel(const PointArgs a)
         }
     } else if (p < a.HW) {
         int32_t *base = a.out + ((size_t)n * a.K + k0 + 4 * half) * a.HW + p;
+        const auto past = past_base(a.out + ((size_t)n * a.K + k0) * a.HW);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int kr = 8 * (v >> 2) + (v & 3);
             if (k0 + 4 * half + kr >= a.K) continue;
-            if constexpr (PAST) __builtin_nontemporal_store(acc[v], base + (size_t)kr * a.HW);
+            if constexpr (PAST) store_past4<PAST_THROUGH>(past, ((unsigned)(4 * half) * a.HW + p) * 4u, (unsigned)(kr * a.HW) * 4u, acc[v]);
             else base[(size_t)kr * a.HW] = acc[v];
         }
     }
@@ -540,10 +541,10 @@ hipError_t launch_pointwise_conv(const WindowProblem &g, hipStream_t st)
     int wgs = 256 * 4 / kgroups;  // about four workgroups fit a CU
     if (wgs < 256) wgs = 256;
     const dim3 grid((unsigned)(a.ntiles < wgs ? a.ntiles : wgs), (unsigned)kgroups);
-    // Whole 64-byte sectors of a result that the L2s would write back when the kernel ends go past them (16 images 256 x 28 x 28 -> 256:
-    // 8.0 -> 7.2 us, 8 images 128 x 56 x 56 -> 256 8.8 -> 8.3; level below 10 MB, and above what the last-level cache holds).
+    // Whole 64-byte sectors of a result that the L2s would write back when the kernel ends go through them as they come (16 images
+    // 256 x 28 x 28 -> 256: 8.1 -> 7.2 us, 8 images 128 x 56 x 56 -> 256 9.3 -> 7.9, 64 images 512 x 8 x 8 -> 512 7.5 -> 6.5; level below 8 MB).
     const double bytes = 4.0 * g.N * g.K * g.H * g.W;
-    const bool past = a.HW % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && bytes >= 8e6 && bytes <= END_FLUSH_BYTES;
+    const bool past = a.HW % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && bytes >= 8e6 && past_caches(bytes) == PAST_THROUGH;
     switch (g.C / 32) {
         case 2: return launch_nkk<2>(a, grid, past, st);
         case 4: return launch_nkk<4>(a, grid, past, st);

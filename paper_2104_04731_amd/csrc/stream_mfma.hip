@@ -34,7 +34,7 @@ enum StreamSource : int { ST_NCHW = 0, ST_NHWC = 1 };
 struct StreamArgs {
     const int8_t *src, *wq;
     int32_t *out;                  // [N][K][P][Q], or from an NHWC source [N][P][Q][K]
-    int stream_out;                // NKPQ result past the caches
+    int past;                      // NKPQ result past the caches: Past
     int K, M, PQ, Q;
     int C1, H, W, HW;              // C1: last channel
     int stride, pad, dil, R, S, RS;
@@ -505,7 +505,7 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
 #pragma unroll
                     for (int r = 0; r < NS; ++r) {
                         if (!there(r)) continue;
-                        if constexpr (decltype(past)::value) store_past16(base, off, (unsigned)(i * 32 + r * RPI) * row, t[r]);
+                        if constexpr (decltype(past)::value != PAST_NONE) store_past16<decltype(past)::value>(base, off, (unsigned)(i * 32 + r * RPI) * row, t[r]);
                         else *reinterpret_cast<v4i_a4 *>(to0 + (size_t)(i * 32 + r * RPI) * row + off) = t[r];
                     }
                 } else if (ok) {   // (two images meet in the four pixels -- or more, of fewer than four -- or the tile ends)
@@ -525,9 +525,10 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
                 }
             }
         };
-        if (k0 + TK > a.K) passes(std::false_type{}, std::false_type{});
-        else if (a.stream_out) passes(std::true_type{}, std::true_type{});
-        else passes(std::true_type{}, std::false_type{});
+        if (k0 + TK > a.K) passes(std::false_type{}, PastHow<PAST_NONE>{});
+        else if (a.past == PAST_THROUGH) passes(std::true_type{}, PastHow<PAST_THROUGH>{});
+        else if (a.past == PAST_STREAM) passes(std::true_type{}, PastHow<PAST_STREAM>{});
+        else passes(std::true_type{}, PastHow<PAST_NONE>{});
         return;
     }
 
@@ -719,10 +720,13 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
     a.tab_off = a.win_off + nbuf * a.buf_bytes;
     // Past the caches: whole 64-byte sectors per store instruction, of planes and tiles that hold whole ones (37 drawn layers 0.97 of the
     // time, the worst 1.03); other planes of whole 16-byte pieces from 8 to 28 MB (0.98, 1.03) and above 256 (0.95, 0.97).  (From there to
-    // 256 MB they take up to 1.28, below 8 up to 1.04, planes of other sizes up to 1.13.)
+    // 256 MB they take up to 1.28, below 8 up to 1.04, planes of other sizes up to 1.13.)  All that non-temporal; up to 28 MB they are
+    // written through, which is level or faster (5 layers of whole sectors 0.99 - 1.00, 4 of quads 0.99 - 1.00) and better for their reader.
     const double bytes = 4.0 * g.M * g.K;
     const bool sectors = PQ % 16 == 0 && mper % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0;
-    a.stream_out = sectors || (PQ % 4 == 0 && mper % 4 == 0 && bytes > 8e6 && past_caches(bytes));
+    const bool quads = PQ % 4 == 0 && mper % 4 == 0 && bytes > 8e6;
+    a.past = sectors || quads ? past_caches(bytes) : PAST_NONE;
+    if (sectors && a.past == PAST_NONE) a.past = PAST_STREAM;
     const long long tk = (g.K + d.tk() - 1) / d.tk(), tm = ((long long)g.M + mper - 1) / mper;
     if (tk * tm > 0x7FFFFFFFLL) return false;
     a.tiles_k = (int)tk;

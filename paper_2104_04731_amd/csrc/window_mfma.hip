@@ -52,7 +52,7 @@ struct WindowArgs {
     int G;                 // how often they do: a tile has PT * G output rows
     int RW;                // window rows per channel: (PT*G-1)*stride + R
     int turn_off;          // LDS byte offset of the blocks turned around (0: over the window, G = 1)
-    int stream_out;        // result past the caches
+    Past past;             // result past the caches
     int pitch;             // bytes per window row, a multiple of 4
     int tiles_q, tiles_p;  // tiles per image
     int CR, nd;            // C*R; dwords per kernel row: ceil(S, 4) / 4
@@ -74,9 +74,9 @@ __device__ __forceinline__ unsigned load_u32(const void *p)  // any alignment
     return x;
 }
 
-// ACT: the activation epilogue, a kernel of its own; NHWC: source and result; MULTI: tiles of several row groups; STREAM: 16-byte
-// stores of the NKPQ result past the caches (of two stores under a run-time flag the compiler makes one, without the hint)
-template <int NKK, int NKB, bool ACT, bool NHWC, bool MULTI, bool STREAM>
+// ACT: the activation epilogue, a kernel of its own; NHWC: source and result; MULTI: tiles of several row groups; PAST: 16-byte
+// stores of the NKPQ result past the caches
+template <int NKK, int NKB, bool ACT, bool NHWC, bool MULTI, Past PAST>
 // (four workgroups per compute unit asked for, i.e. up to 128 registers: the deep instantiations use 86 -- five
 // fit -- and under a bound of 85 the compiler spilled their weight loads one by one, a wait behind each)
 __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
                 }
             return;
         }
-        if (STREAM || a.wide_out) {
+        if (PAST != PAST_NONE || a.wide_out) {
             // Q a multiple of 4 and `out` 16-byte aligned: each wave turns its 32x32 block around in LDS
             // (rows of 36 dwords) so that a lane stores four consecutive pixels of one channel -- 16-byte
             // stores, eight 128-byte runs per instruction instead of two
@@ -397,12 +397,14 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
                 for (int v = 0; v < 16; ++v) T[(8 * (v >> 2) + 4 * half + (v & 3)) * 36 + l31] = acc[kb][v];
                 __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order: no wait beyond the compiler's own
                 int32_t *dst = outn + (size_t)(k0 + kb * 32 + tr) * PQ + (size_t)pp * aQ + qq;
+                const unsigned off = ((unsigned)(k0 + kb * 32 + tr) * (unsigned)PQ + (unsigned)(pp * aQ + qq)) * 4u;   // (an image below 28 MB)
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const v4i t = *reinterpret_cast<const v4i *>(T + (tr + 8 * j) * 36 + 4 * tg);
                     if (pp < aP && qq < aQ && k0 + kb * 32 + tr + 8 * j < aK) {
                         v4i *const to = reinterpret_cast<v4i *>(dst + (size_t)(8 * j) * PQ);
-                        if constexpr (STREAM) __builtin_nontemporal_store(t, to);
+                        if constexpr (PAST == PAST_THROUGH) store_past16<PAST>(past_base(outn), off, (unsigned)(8 * j) * (unsigned)PQ * 4u, t);
+                        else if constexpr (PAST == PAST_STREAM) __builtin_nontemporal_store(t, to);
                         else *to = t;
                     }
                 }
@@ -476,7 +478,7 @@ constexpr long long WINDOW_LIMIT = 40 * 1024;  // bytes of LDS the input window 
 // times as many for a depth of 64, which gains the least.  Above 32 channels it goes into the stores, which come in one burst
 // per workgroup and overlap less the longer it runs: two groups where the window is large (40 x 1 x 161 x 522, 20 x 5 / 2 -> 64,
 // raw weights: 47.8 -> 41, kept ones 39.4 -> 37.2) and the stores do not bypass the caches, else one.
-static int window_groups(const WindowProblem &g, int PT, int QT, long long row_bytes, int depth, bool stream_out)
+static int window_groups(const WindowProblem &g, int PT, int QT, long long row_bytes, int depth, bool past)
 {
     if (g.nhwc || g.act.out) return 1;
     const long long cols = (long long)g.N * ((g.Q + QT - 1) / QT);
@@ -484,7 +486,7 @@ static int window_groups(const WindowProblem &g, int PT, int QT, long long row_b
         const long long groups = (g.P + PT * G - 1) / (PT * G);
         return cols * groups * ((g.K + 63) / 64) >= least && ((long long)(PT * G - 1) * g.stride + g.R) * row_bytes <= 16 * 1024;
     };
-    if (g.K > 32) return !stream_out && ((PT - 1) * g.stride + g.R) * row_bytes >= 4000 && fits(2, 2048) ? 2 : 1;
+    if (g.K > 32) return !past && ((PT - 1) * g.stride + g.R) * row_bytes >= 4000 && fits(2, 2048) ? 2 : 1;
     int G = 1;
     while (G < 8 && fits(2 * G, depth == 64 ? 3072 : 2048)) G *= 2;
     return G;
@@ -520,11 +522,12 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     // Whole 64-byte sectors per 16 pixels, and more than the caches keep or so little that the L2s write it back when the kernel ends:
     // stored past them.  3 x 224 x 224, 7 x 7 / 2 -> 64, plain -> past: 87 images (279 MB) 76 -> 64 us, 300 (963 MB) 239 -> 207, 512
     // 396 -> 350 (most results of this size are the stencil kernel's, in stencil_mfma.hip; what it leaves comes here); 4 images (13 MB)
-    // 7.06 -> 6.62, 8 (26 MB) 9.57 -> 8.53; 3 x 192 x 160, 3 x 3 / 2 -> 64, 8 images (16 MB) 6.61 -> 6.06, 12 (24 MB) 7.79 -> 6.95.  Between
-    // the two a result that is written again is still in the last-level cache: 16 of the latter (31 MB) 8.82 -> 9.17, 24 (47 MB)
-    // 11.4 -> 13.1.  Partial sectors come out slower that way (4 x 1 x 161 x 500, 20 x 5 / 2 -> 32: 6.11 -> 6.46).
-    w.stream_out = !g.nhwc && !g.act.out && g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0 && past_caches(4.0 * g.N * g.K * g.P * g.Q);
-    w.G = window_groups(g, w.PT, QT, C * pitch, depth, w.stream_out);
+    // 7.05 -> 6.01, 8 (26 MB) 9.70 -> 7.89; 3 x 192 x 160, 3 x 3 / 2 -> 64, 8 images (16 MB) 6.61 -> 5.44.  Between the two a result that is
+    // written again is still in the last-level cache: non-temporal, 16 of the latter (31 MB) 8.82 -> 9.17, 24 (47 MB) 11.4 -> 13.1.  Partial
+    // sectors come out slower that way (4 x 1 x 161 x 500, 20 x 5 / 2 -> 32: 6.11 -> 6.46).
+    const bool sectors = !g.nhwc && !g.act.out && g.Q % 16 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 63) == 0;
+    w.past = sectors ? past_caches(4.0 * g.N * g.K * g.P * g.Q) : PAST_NONE;
+    w.G = window_groups(g, w.PT, QT, C * pitch, depth, w.past != PAST_NONE);
     const long long RW = (long long)(w.PT * w.G - 1) * g.stride + g.R;
     if (RW > WINDOW_LIMIT || pitch > WINDOW_LIMIT || C * RW * pitch > WINDOW_LIMIT) return false;
     w.RW = (int)RW;
@@ -561,21 +564,24 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
 
 bool window_fits(const WindowProblem &g) { return window_plan(g, nullptr); }
 
-template <int NKK, bool ACT, bool NHWC, bool MULTI, bool STREAM = false>
+template <int NKK, bool ACT, bool NHWC, bool MULTI, Past PAST = PAST_NONE>
 static hipError_t launch_window_kb(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (a.K > 32) return launch((conv_window_kernel<NKK, 2, ACT, NHWC, MULTI, STREAM>), grid, dim3(256), lds, st, a);
-    return launch((conv_window_kernel<NKK, 1, ACT, NHWC, MULTI, STREAM>), grid, dim3(256), lds, st, a);
+    if (a.K > 32) return launch((conv_window_kernel<NKK, 2, ACT, NHWC, MULTI, PAST>), grid, dim3(256), lds, st, a);
+    return launch((conv_window_kernel<NKK, 1, ACT, NHWC, MULTI, PAST>), grid, dim3(256), lds, st, a);
 }
 template <int NKK>
 static hipError_t launch_window_nkk(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
 {
     if (a.nhwc) return launch_window_kb<NKK, false, true, false>(a, grid, lds, st);
     if (a.act.out) return launch_window_kb<NKK, true, false, false>(a, grid, lds, st);
-    if (a.G > 1)
-        return a.stream_out ? launch_window_kb<NKK, false, false, true, true>(a, grid, lds, st)
-                            : launch_window_kb<NKK, false, false, true>(a, grid, lds, st);
-    if (a.stream_out) return launch_window_kb<NKK, false, false, false, true>(a, grid, lds, st);
+    if (a.G > 1) {
+        if (a.past == PAST_THROUGH) return launch_window_kb<NKK, false, false, true, PAST_THROUGH>(a, grid, lds, st);
+        return a.past == PAST_STREAM ? launch_window_kb<NKK, false, false, true, PAST_STREAM>(a, grid, lds, st)
+                                     : launch_window_kb<NKK, false, false, true>(a, grid, lds, st);
+    }
+    if (a.past == PAST_THROUGH) return launch_window_kb<NKK, false, false, false, PAST_THROUGH>(a, grid, lds, st);
+    if (a.past == PAST_STREAM) return launch_window_kb<NKK, false, false, false, PAST_STREAM>(a, grid, lds, st);
     return launch_window_kb<NKK, false, false, false>(a, grid, lds, st);
 }
 

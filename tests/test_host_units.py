@@ -114,7 +114,7 @@ def store_listing(tmp_path_factory):
                     os.path.join(HERE, "store_past.hip"), "-o", str(listing)], check=True, capture_output=True, timeout=120)
 
     def code(kernel):
-        lines = listing.read_text().split(f"\n{kernel}:")[1].split("\n", 1)[1].split("s_endpgm")[0].splitlines()
+        lines = listing.read_text().split(f"\n{kernel}:")[1].split("\n", 1)[1].split("\n\t.section")[0].splitlines()
         return [s for s in (line.split(";")[0].replace(",", " ").split() for line in lines) if s and not s[0].endswith(":")]
     return code
 
@@ -146,5 +146,6 @@ def test_stores_past_the_caches_wait_for_their_base(store_listing):
 
 
 def test_stores_past_the_caches_are_not_merged_with_plain_ones(store_listing):
-    stores = [s for s in store_listing("two_branches") if is_store(s)]
-    assert len(stores) == 2 and sum("nt" in s for s in stores) == 1
+    """One that streams a result past every cache, one that writes it through to the last-level cache, where its reader finds it, a plain one."""
+    stores = [s for s in store_listing("three_branches") if is_store(s)]
+    assert sorted(("nt" in s, "sc1" in s, "sc0" in s) for s in stores) == [(False, False, False), (False, True, False), (True, False, False)]
