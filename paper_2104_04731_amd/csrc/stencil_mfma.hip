@@ -286,15 +286,40 @@ __global__ void __launch_bounds__(STENCIL_THREADS, NKK * NKB > 12 ? 3 : 4) conv_
 }  // namespace
 
 // Pixels of a tile, 0 where the window kernel stays; `few`: three workgroups per compute unit at most.  From 190 stem, speech and small 3 x 3
-// layers, each timed with tiles of 128 to 1024 pixels on three sets of buffers in turn (figures: of the window kernel's time).
+// layers, each timed with tiles of 128 to 1024 pixels on three sets of buffers in turn, and from another 900 with results of 30 to 560 MB, this
+// kernel and the window kernel on two sets, the best of three processes (figures: of the window kernel's time).
 //   Results past the last-level cache (240 MB here: less than its 256 MB is free for a result that is written again).  Planes of whole lines:
-//   512 pixels (0.51 - 0.9).  Others: 64 KB of result per workgroup, three per compute unit (128 images 5 x 5 / 2 -> 32, 326 MB: 0.64, and 0.72 with
-//   as many workgroups as fit; 64 channels, 256 pixels 0.65 - 1.04, 512 pixels 0.76 - 1.2).
+//   512 pixels, up to 16 channels 1024 (4 - 16 channels, 320 MB: 0.82 of 512's time).  Others, from 190 MB on: what the workgroups of an XCD hold
+//   written in parts must be less than its L2.  Where one writes 36 KB and more, three per compute unit (128 images 5 x 5 / 2 -> 32, 326 MB:
+//   0.64, and 0.72 with as many as fit), 512 pixels, 256 above 32 channels (512: up to 1.2 of that).  Of less as many as fit, with 1024
+//   pixels up to 8 channels: three were up to 1.95 (15352 images 3 x 62 x 62, 3 x 3 -> 2: 725 us, the window kernel 371, as many as fit 352).
 //   Smaller results, up to 32 channels: the most pixels of 256, 512, 1024 that leave 640 workgroups: the window's rows overlap and the weights come in
 //   once per tile (112 images 20 x 5 / 2 -> 32, 140 MB: 256 pixels 0.89, 512 0.70, 1024 0.64).  Below 160 000 pixels, 240 000 for depths up to 128,
 //   the window kernel's many small workgroups win (1.0 - 1.2), and so they do up to 125 MB for a depth of 64 and 25 - 32 channels (1.0 - 1.1).
 //   Smaller results, more channels: from 120 MB on (0.65 - 0.95; 3 x 3 kernels in one depth of 64 from 200 MB, 1.0 - 1.2 below), deep stems from 36 MB
-//   (0.76 - 1.0).  Many channels on narrow images make windows of many short rows: the window kernel's (up to 1.3).
+//   (0.61 - 1.0).  Many channels on narrow images make windows of many short rows: the window kernel's (up to 1.3).
+//   And where the window kernel's blocks of 32 pixels suit the rows (stencil_pays).  600 layers drawn once that was settled: up to 32 channels 0.68
+//   in the mean and 1.07 at worst on planes of partial lines (0.93 and 2.06 without these two rules), 0.80 and 1.12 on others; above 32
+//   channels 0.92 and 1.15 (0.97 and 1.8), 0.95 and 1.13.
+static bool stencil_pays(const WindowProblem &g, int depth, double out, bool lines)
+{
+    // how full its tiles of 128 pixels are
+    const int QT = g.Q > 64 ? 128 : g.Q > 32 ? 64 : 32, PT = 128 / QT;
+    const long long tiles = (long long)((g.Q + QT - 1) / QT) * ((g.P + PT - 1) / PT);
+    const double fill = (double)g.P * g.Q / (128.0 * tiles);
+    if (lines) {
+        // its blocks are whole lines as well, and few channels' depth of 64 is multiplied in no time: 1.0 - 1.36, else 0.38 - 1.06
+        return g.Q % 32 != 0 || g.K <= 8 || out < 150e6 || fill <= 0.65 || (g.K <= 16 && depth >= 128 && fill < 0.95);
+    }
+    if (g.K <= 32) return true;
+    if (tiles == 1) return false;                                                         // (an image to a workgroup on both sides: 0.8 - 1.5)
+    if (out < 190e6) return depth != 128 || fill <= 0.62;                                 // (0.72 - 1.0; better filled 0.93 - 1.11)
+    // up to 290 MB the last-level cache takes in what it writes in parts
+    if (out < 290e6) return fill <= (g.K <= 64 && depth >= 192 ? 0.65 : 0.45);             // (0.47 - 1.09; up to 0.6 0.84 - 1.47, beyond 0.9 - 1.33)
+    if (g.K > 64) return fill <= 0.45;                                                    // (0.5 - 1.0; beyond 0.76 - 1.21)
+    return depth >= 128 || fill <= (g.Q % 4 == 0 ? 0.45 : 0.80);                           // (0.54 - 1.07; beyond, and 16-byte stores, 0.9 - 1.17)
+}
+
 static int stencil_tile(const WindowProblem &g, int depth, bool *few)
 {
     const double out = 4.0 * g.N * g.K * g.P * g.Q;
@@ -302,17 +327,20 @@ static int stencil_tile(const WindowProblem &g, int depth, bool *few)
     const bool lines = (long long)g.P * g.Q % 32 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 127) == 0;
     *few = false;
     if (g.C > 4 && g.K > 32 && g.stride > 1 && g.W <= 64) return 0;
+    if (!stencil_pays(g, depth, out, lines)) return 0;
+    const int partial = g.K <= 8 ? 1024 : g.K <= 32 ? 512 : 256;
+    const double written = 4.0 * std::min<long long>(partial, (long long)g.P * g.Q) * std::min(g.K, 64);   // by a workgroup
     if (out >= 240e6) {
-        if (lines) return 512;
-        *few = true;
-        return g.K > 32 ? 256 : 512;
+        if (lines) return g.K <= 16 ? 1024 : 512;
+        *few = written >= 36e3;
+        return partial;
     }
     if (out < 120e6 ? g.C > 4 : g.C > 4 && g.W < 56) return 0;
     if (g.K > 32) return out >= (depth == 64 && g.R == 3 ? 200e6 : depth >= 128 && g.C <= 4 && g.W >= 56 ? 36e6 : 120e6) ? 512 : 0;
     if (depth == 64 && g.K > 24 && out < 125e6) return 0;
     if (out >= 190e6 && !lines) {
-        *few = true;
-        return 512;
+        *few = written >= 36e3;
+        return partial;
     }
     if (pixels < (depth <= 128 ? 240000 : 160000)) return 0;
     return pixels >= 640 * 1024 ? 1024 : pixels >= 640 * 512 ? 512 : 256;

@@ -9,7 +9,7 @@ import sys
 
 recorder = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
 lib = ctypes.CDLL(sys.argv[2])
-recorded = (ctypes.c_int * 4).in_dll(recorder, "recorded")
+recorded, name = (ctypes.c_int * 4).in_dll(recorder, "recorded"), (ctypes.c_char * 512).in_dll(recorder, "recorded_name")
 p, big = ctypes.c_void_p(1 << 20), ctypes.c_size_t(1 << 40)
 out = []
 for dims, layout, cb, packed in json.loads(sys.argv[3]):
@@ -18,5 +18,5 @@ for dims, layout, cb, packed in json.loads(sys.argv[3]):
     rc = lib.conv2d_int8_ex(d, layout, cb, p, p, packed, p, p, big, None)
     v = [ctypes.c_int() for _ in range(3)]
     lib.conv2d_int8_query_stage(d, 1, layout, cb, packed, 1, *map(ctypes.byref, v))
-    out.append(dict(rc=rc, launches=recorded[0] - before, workgroups=recorded[1], threads=recorded[2], lds=recorded[3], stage=[x.value for x in v]))
+    out.append(dict(rc=rc, launches=recorded[0] - before, workgroups=recorded[1], threads=recorded[2], lds=recorded[3], kernel=name.value.decode(), stage=[x.value for x in v]))
 print(json.dumps(out))

@@ -106,6 +106,30 @@ def test_given_and_kept_1x1_weights_take_the_same_launch(lib, dims):
     assert raw[0] == lib.STAGE_RESIDENT and lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True) == raw
 
 
+# (dims, pixels of a tile, three workgroups per compute unit at most), or window: large results of stencil-unrolling layers
+STENCIL_RULE = [
+    ((15352, 3, 62, 62, 2, 3, 3, 1, 1), 1024, False), ((1198, 1, 89, 109, 6, 3, 3, 1, 0), 1024, False), ((690, 4, 81, 84, 12, 3, 3, 1, 0), 512, False),
+    ((678, 1, 76, 79, 32, 3, 3, 1, 1), 512, True), ((92118, 3, 13, 14, 24, 3, 3, 2, 0), 512, False), ((1440, 3, 37, 37, 64, 3, 3, 1, 0), 256, True),
+    ((11381, 3, 13, 14, 64, 3, 3, 1, 0), 256, False), ((512, 3, 224, 224, 64, 7, 7, 2, 3), 512, False), ((4340, 3, 48, 48, 8, 3, 3, 1, 1), 1024, False),
+    ((495, 2, 40, 41, 64, 3, 3, 1, 1), 0, False), ((73, 3, 86, 87, 96, 3, 3, 1, 1), 0, False), ((60, 4, 95, 115, 128, 3, 3, 1, 1), 0, False),
+    ((60064, 2, 6, 26, 48, 5, 5, 1, 0), 0, False), ((1302, 3, 32, 32, 64, 3, 3, 1, 1), 0, False), ((557, 4, 240, 384, 24, 3, 3, 2, 1), 0, False),
+]
+
+
+@pytest.mark.parametrize("dims,pixels,few", STENCIL_RULE, ids=str)
+def test_large_results_take_the_kernel_that_suits_them(lib, launches, dims, pixels, few):
+    """Tiles of consecutive pixels as large as what a workgroup writes allows, three per compute unit only where that is much; rows that fill the
+    window kernel's tiles stay there."""
+    N, C, H, W, K, R, S, stride, pad = dims
+    (call,) = launches([(dims, lib.LAYOUT_IMPLICIT, 0, 0)])
+    assert call["rc"] == 0 and call["launches"] == 1
+    assert ("conv_stencil_kernel" if pixels else "conv_window_kernel") in call["kernel"]
+    if pixels:
+        P, Q = lib.out_hw(H, W, R, S, stride, pad)
+        assert call["workgroups"] == N * -(-(-(-P * Q // 32)) // (pixels // 32)) * -(-K // 64)
+        assert (call["lds"] > 160 * 1024 // 4) == few
+
+
 @pytest.fixture(scope="module")
 def store_listing(tmp_path_factory):
     """kernel -> its instructions, as lists of words"""
