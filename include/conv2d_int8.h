@@ -170,8 +170,8 @@ int conv2d_int8_tile_info(int tile, int *rows, int *cols, int *threads, int *ste
  * problem?  CONV_OK or CONV_ERR_UNSUPPORTED (host only). */
 int conv2d_int8_tile_applies(const conv_desc_t *desc, int layout, int cb, int tile, int split_k);
 /* LDS bytes per workgroup that this tile and split would ask for on this problem (operand ring plus, for
- * the blocked layouts, one offset per 16-byte depth chunk of a slice); 0 where the pair does not apply.
- * Never above 160 KB, one compute unit's LDS (host only). */
+ * the blocked layouts, one offset per 16-byte depth chunk of a slice; or the rows in which conv2d_int8_packed's result
+ * leaves through LDS, where that is more); 0 where the pair does not apply.  Never above 160 KB, one compute unit's LDS (host only). */
 size_t conv2d_int8_tile_lds_bytes(const conv_desc_t *desc, int layout, int cb, int tile, int split_k);
 
 /* ---- GEMM stage on the network's own tensor ---------------------------------------------

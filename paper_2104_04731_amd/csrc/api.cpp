@@ -1207,10 +1207,8 @@ size_t conv2d_int8_tile_lds_bytes(const conv_desc_t *desc, int layout, int cb, i
     if (conv2d_int8_tile_applies(desc, layout, cb, tile, split_k) != CONV_OK) return 0;
     Plan pl;
     if (make_plan(desc, layout, cb, &pl) != CONV_OK) return 0;
-    if (tile == CONV_TILE_BAND) return band_lds_bytes(gemm_problem(desc, pl, nullptr, nullptr, nullptr));
-    const int steps = pl.depth / 64, slices = split_k > steps ? steps : split_k;
-    const int per = (steps + slices - 1) / slices;
-    return gemm_tile_lds_bytes(tile, pl.layout == CONV_LAYOUT_IM2COL ? ACT_MATRIX : ACT_BLOCKED, per);
+    const GemmProblem g = gemm_problem(desc, pl, nullptr, nullptr, nullptr);
+    return tile == CONV_TILE_BAND ? band_lds_bytes(g) : gemm_tile_lds_bytes(g, tile, split_k);
 }
 
 size_t conv2d_int8_workspace_bytes(const conv_desc_t *desc, int layout, int cb, int wt_is_packed)

@@ -866,7 +866,6 @@ static const TileDef kTiles[] = {
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 int gemm_num_tiles() { return kNumTiles; }
-size_t gemm_tile_lds_bytes(int t, int mode, int steps_per_slice);
 TileInfo gemm_tile_info(int t)
 {
     return TileInfo{kTiles[t].tk, kTiles[t].tm, (kTiles[t].wk * kTiles[t].wm * kTiles[t].ds + kTiles[t].help) * 64, kTiles[t].ks};
@@ -884,13 +883,15 @@ static size_t tile_lds_bytes(const TileDef &d, int mode, int per, int rows_of)
     return ring > rows ? ring : rows;
 }
 
+static RowsOf rows_of(const GemmArgs &a) { return a.act_out ? ROWS_ACT : !a.rows ? ROWS_NONE : a.out_nhwc ? ROWS_NHWC : ROWS_NKPQ; }
+
 template <int TK, int TM, int WK, int WM, int KS, int NSTAGE, int HELP, int DS, int WPC = 1>
 static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
 {
     constexpr int NT = (WK * WM * DS + HELP) * 64;
     constexpr TileDef tile{TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, 0, 0, 0};
     const int grid = a.tiles_k * a.tiles_m * a.split_k;
-    const int rows = a.act_out ? ROWS_ACT : !a.rows ? ROWS_NONE : a.out_nhwc ? ROWS_NHWC : ROWS_NKPQ;
+    const int rows = rows_of(a);
     void (*kern)(GemmArgs) = mode == ACT_BLOCKED ? igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_BLOCKED, ROWS_NONE>
                                                  : igemm_i8_kernel<TK, TM, WK, WM, KS, NSTAGE, HELP, DS, WPC, ACT_MATRIX, ROWS_NONE>;
     if (rows == ROWS_ACT)
@@ -918,8 +919,6 @@ static hipError_t launch_tile(const GemmArgs &a, int mode, hipStream_t st)
 }
 
 static int ceil_div(int a, int b) { return (a + b - 1) / b; }
-
-size_t gemm_tile_lds_bytes(int t, int mode, int steps_per_slice) { return tile_lds_bytes(kTiles[t], mode, steps_per_slice, ROWS_NKPQ); }
 
 // A tile with 128- or 256-byte stages walks the depth two or four steps at a time: every slice
 // must be a whole number of stages.
@@ -1125,6 +1124,12 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
     a.mg_tiles_km = magic((long long)a.tiles_k * a.tiles_m);
     *out = a;
     return true;
+}
+
+size_t gemm_tile_lds_bytes(const GemmProblem &g, int tile, int split_k)
+{
+    GemmArgs a;
+    return make_gemm_args(g, tile, split_k, &a) ? tile_lds_bytes(kTiles[tile], g.mode, a.ksteps_per_split, rows_of(a)) : 0;
 }
 
 hipError_t launch_gemm(const GemmProblem &g, int tile, int split_k, hipStream_t st)

@@ -106,6 +106,16 @@ def test_given_and_kept_1x1_weights_take_the_same_launch(lib, dims):
     assert raw[0] == lib.STAGE_RESIDENT and lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, True) == raw
 
 
+@pytest.mark.parametrize("dims,layout,cb", [((8, 256, 14, 14, 512, 3, 3, 1, 1), 1, 64), ((9, 256, 13, 13, 512, 3, 3, 1, 1), 1, 64), ((60, 96, 28, 28, 520, 3, 3, 1, 1), 1, 32),
+                                            ((300, 64, 28, 28, 512, 3, 3, 1, 1), 1, 64), ((16, 64, 14, 14, 512, 3, 3, 1, 1), 2, 0)], ids=str)
+def test_tile_lds_is_what_the_launch_asks_for(lib, launches, dims, layout, cb):
+    """Every tile, the depth whole and split: the ring with its offsets, or the rows of a result that leaves through LDS."""
+    pairs = [(t, split) for t in range(lib.num_tiles()) for split in (1, 2, 3) if lib.tile_applies(dims, layout, cb, t, split)]
+    calls = launches([(dims, layout, cb, 1, t, split) for t, split in pairs])
+    assert pairs and all(c["rc"] == 0 for c in calls)
+    assert [c["lds"] for c in calls] == [lib.tile_lds_bytes(dims, layout, cb, t, split) for t, split in pairs]
+
+
 # (dims, pixels of a tile, three workgroups per compute unit at most), or window: large results of stencil-unrolling layers
 STENCIL_RULE = [
     ((15352, 3, 62, 62, 2, 3, 3, 1, 1), 1024, False), ((1198, 1, 89, 109, 6, 3, 3, 1, 0), 1024, False), ((690, 4, 81, 84, 12, 3, 3, 1, 0), 512, False),
