@@ -564,24 +564,28 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
 
 bool window_fits(const WindowProblem &g) { return window_plan(g, nullptr); }
 
-template <int NKK, bool ACT, bool NHWC, bool MULTI, Past PAST = PAST_NONE>
+template <int NKK, bool ACT, bool NHWC, bool MULTI>
 static hipError_t launch_window_kb(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
 {
-    if (a.K > 32) return launch((conv_window_kernel<NKK, 2, ACT, NHWC, MULTI, PAST>), grid, dim3(256), lds, st, a);
-    return launch((conv_window_kernel<NKK, 1, ACT, NHWC, MULTI, PAST>), grid, dim3(256), lds, st, a);
+    if (a.K > 32) return launch((conv_window_kernel<NKK, 2, ACT, NHWC, MULTI, PAST_NONE>), grid, dim3(256), lds, st, a);
+    return launch((conv_window_kernel<NKK, 1, ACT, NHWC, MULTI, PAST_NONE>), grid, dim3(256), lds, st, a);
+}
+// (past the caches above 32 channels a tile has one row group: window_groups)
+template <int NKK, Past PAST>
+static hipError_t launch_window_past(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
+{
+    if (a.K > 32) return launch((conv_window_kernel<NKK, 2, false, false, false, PAST>), grid, dim3(256), lds, st, a);
+    if (a.G > 1) return launch((conv_window_kernel<NKK, 1, false, false, true, PAST>), grid, dim3(256), lds, st, a);
+    return launch((conv_window_kernel<NKK, 1, false, false, false, PAST>), grid, dim3(256), lds, st, a);
 }
 template <int NKK>
 static hipError_t launch_window_nkk(const WindowArgs &a, dim3 grid, size_t lds, hipStream_t st)
 {
     if (a.nhwc) return launch_window_kb<NKK, false, true, false>(a, grid, lds, st);
     if (a.act.out) return launch_window_kb<NKK, true, false, false>(a, grid, lds, st);
-    if (a.G > 1) {
-        if (a.past == PAST_THROUGH) return launch_window_kb<NKK, false, false, true, PAST_THROUGH>(a, grid, lds, st);
-        return a.past == PAST_STREAM ? launch_window_kb<NKK, false, false, true, PAST_STREAM>(a, grid, lds, st)
-                                     : launch_window_kb<NKK, false, false, true>(a, grid, lds, st);
-    }
-    if (a.past == PAST_THROUGH) return launch_window_kb<NKK, false, false, false, PAST_THROUGH>(a, grid, lds, st);
-    if (a.past == PAST_STREAM) return launch_window_kb<NKK, false, false, false, PAST_STREAM>(a, grid, lds, st);
+    if (a.past == PAST_THROUGH) return launch_window_past<NKK, PAST_THROUGH>(a, grid, lds, st);
+    if (a.past == PAST_STREAM) return launch_window_past<NKK, PAST_STREAM>(a, grid, lds, st);
+    if (a.G > 1) return launch_window_kb<NKK, false, false, true>(a, grid, lds, st);
     return launch_window_kb<NKK, false, false, false>(a, grid, lds, st);
 }
 
