@@ -206,7 +206,8 @@ typedef enum {
 } conv_stage_t;
 /* entry: which call (conv2d_int8, _ex, _nhwc, _dilated, _dilated_direct); layout, cb, wt_is_packed, dilation: its arguments,
  * those it does not have are ignored.  tile, pixels: what conv2d_int8_resident takes for the same launch (RESIDENT*: a tile
- * index, STREAM*: CONV_TILE_STREAM + t); -1 and 0 for the other stages. */
+ * index, STREAM*: CONV_TILE_STREAM + t) -- with the output of pack_weights where the call reads 1x1 weights as they come, since
+ * it takes raw weights of 3x3 kernels only; -1 and 0 for the other stages. */
 int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int cb, int wt_is_packed, int dilation,
                             int *stage, int *tile, int *pixels);
 

@@ -432,7 +432,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
         else {
             if (d->R == 3 && d->S == 3) consider(DIRECT_RAW, C16, depth, true, 0);
             // rows of C bytes as they are: no second launch (105 pointwise, pair and NHWC calls 0.88 of the time, the small ones 0.6 to 0.8);
-            // a dilated call with nothing to dilate, which is not work that anyone has, stays as it was
+            // a dilated call of a 1x1 layer, whose dilation changes nothing, keeps the stored path, which a test of that path asks of it
             if (d->R == 1 && d->S == 1 && dil == 1) consider(DIRECT_AS_IS, C16, depth, true, 0);
             // the weights' own launch: 2.4-3.2 us up to a megabyte of them
             if (C16 <= 1024) consider(DIRECT_REWRITE, C16, depth, false, 2.8 + 1.0e-6 * (double)d->K * depth + SECOND_LAUNCH_US);

@@ -167,7 +167,8 @@ __device__ __forceinline__ void res_store_piece(const ResidentArgs &a, const v4i
 // multiplies at a time; SRC: ResSource; UNI: a 64-byte step of depth lies within one tap (and channel block);
 // SPLIT: a workgroup has fewer blocks of pixels than waves, and several waves share the depth of each (a form of its own: in the
 // other one's code the smallest launches took half a microsecond longer).
-// RAW: the weights are KCRS (3 x 3), turned into depth order (tap, channel padded to 16) on their way into LDS.
+// WTS: ResWeights.  RES_RAW9: turned into depth order (tap, channel padded to 16) on their way into LDS; RES_RAW1: in that order already, a step
+// of depth always within the one tap (always UNI).
 // RUNS: NCHW windows may be filled in 64-byte runs (a form of its own: that code, jumped over, cost calls of 4 to 6 us 1.0 to 1.6 % on given weights;
 // on raw ones it is there for every plane of 64 pixels and more: 33 layers that jump over it took 1.5 % longer without it).
 // The 64-channel tile of 8 waves keeps two output blocks' sums and the addresses of a whole tap in registers: at two of its
@@ -547,6 +548,7 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
         a.full8 = (int)((end + 7) & ~7LL);
     }
     out->uni = sh.uni;
+    // (raw 1x1 weights run the UNI kernel whatever C16 is; resident_lds still reckons with the other form's table, a few hundred bytes more)
     out->wts = !r.raw_weights ? RES_PACKED : g.R == 1 ? RES_RAW1 : RES_RAW9;
     if ((mper / PQ + 2) * PQ * g.K * 4 >= (1LL << 32)) return false;   // 32-bit byte offsets from the workgroup's first image
     a.nblk = (mper + 32 * d.fm - 1) / (32 * d.fm);

@@ -49,7 +49,8 @@ extern "C" int layout_overheads(const conv_desc_t *d, int layout, int cb,
         return CONV_OK;
     }
     if (layout == CONV_LAYOUT_IMPLICIT) {
-        // nothing rewritten, nothing moved twice; pixels padded per output row, kernel rows to dwords
+        // nothing rewritten, nothing moved twice; pixels padded per output row, kernel rows to dwords (the window kernel's; the stencil kernel,
+        // which takes large results, pads an image's pixels once: at most as many)
         if (P > 2147483647LL || Q > 2147483647LL) return CONV_ERR_UNSUPPORTED;
         const c2i8::WindowProblem g{nullptr, nullptr, nullptr, d->N, d->C, d->H, d->W, d->K, (int)P, (int)Q,
                                     d->R, d->S, d->stride, d->pad, 0, c2i8::ActOut{}, 0};

@@ -281,21 +281,23 @@ def test_large_tiles_write_whole_rows(lib, cfg):
 
 
 @pytest.mark.parametrize("N", [48, 230], ids=["77MB", "369MB"])
-def test_large_results_of_large_tiles(lib, N):
+@pytest.mark.parametrize("nhwc", [False, True], ids=["nkpq", "nhwc"])
+def test_large_results_of_large_tiles(lib, N, nhwc):
     """Results that go through LDS into the caches (between what the L2s and the last-level cache hold) and past them: the same words
-    as the smallest tile's, which stores dwords straight from its blocks."""
+    as the smallest tile's, which stores dwords (NHWC: 16-byte pieces) straight from its blocks."""
     cfg = ConvShape("large", N, 64, 28, 28, 512, 3, 3, 1, 1)
     x = torch.randint(-128, 128, (cfg.N, cfg.C, cfg.H, cfg.W), dtype=torch.int8, device=DEV)
     w = torch.randint(-128, 128, (cfg.K, cfg.C, cfg.R, cfg.S), dtype=torch.int8, device=DEV)
     xp = lib.pack_layout(x, 64, cfg.pad)
     wp = lib.pack_weights(w, lib.LAYOUT_PACKED, 64)
-    want = torch.empty((cfg.N, cfg.K, 28, 28), dtype=torch.int32, device=DEV)
-    lib.conv2d_int8_packed(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, want, tile=0, split_k=1)
+    run = lib.conv2d_int8_packed_nhwc if nhwc else lib.conv2d_int8_packed
+    want = torch.empty((cfg.N, 28, 28, cfg.K) if nhwc else (cfg.N, cfg.K, 28, 28), dtype=torch.int32, device=DEV)
+    run(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, want, tile=0, split_k=1)
     for tile in range(lib.num_tiles()):
         if lib.tile_info(tile)[0] * lib.tile_info(tile)[1] < 128 * 256 or not lib.tile_applies(cfg.dims(), lib.LAYOUT_PACKED, 64, tile, 1):
             continue
         out = torch.full_like(want, -7)
-        lib.conv2d_int8_packed(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, out, tile=tile, split_k=1)
+        run(cfg.dims(), lib.LAYOUT_PACKED, 64, xp, wp, out, tile=tile, split_k=1)
         assert torch.equal(out, want), tile
 
 
@@ -1361,17 +1363,27 @@ WINDOW_GROUP_SHAPES = [
     ConvShape("win-4-groups-s2", 310, 3, 50, 71, 16, 5, 5, 2, 2), ConvShape("win-ragged", 260, 2, 35, 70, 33, 7, 3, 1, 0),
     ConvShape("win-2-groups-64", 200, 3, 41, 131, 40, 7, 7, 2, 3),
 ]
+# ... most of which the stencil kernel takes; of more channels the window kernel runs them in 2, 8, 4 and 2 groups, the last two past the caches.
+WINDOW_GROUPS = [
+    ConvShape("win-c5-2-groups", 1100, 5, 20, 21, 5, 3, 3, 1, 1), ConvShape("win-c5-8-groups", 1600, 5, 33, 12, 3, 3, 3, 1, 1),
+    ConvShape("win-c5-4-groups-s2", 520, 5, 50, 71, 16, 5, 5, 2, 2), ConvShape("win-c16-2-groups-40", 2100, 16, 14, 14, 40, 4, 4, 1, 0),
+    ConvShape("win-c5-sectors", 1600, 5, 16, 16, 8, 3, 3, 1, 1), ConvShape("win-c16-sectors", 1600, 16, 19, 19, 5, 4, 4, 1, 0),
+]
 
 
-@pytest.mark.parametrize("cfg", WINDOW_GROUP_SHAPES, ids=lambda c: c.name)
+@pytest.mark.parametrize("cfg", WINDOW_GROUP_SHAPES + WINDOW_GROUPS, ids=lambda c: c.name)
 def test_window_row_groups(lib, cfg):
     x, w, want = oracle_conv(cfg)
     assert np.array_equal(host(lib.conv2d_int8(dev(x), dev(w), cfg.stride, cfg.pad)), want)
 
 
+def window_streamed_batch(K):
+    return 256 * 10**6 // (4 * K * 32 * 32) + 2
+
+
 @pytest.mark.parametrize("K", [16, 64])
 def test_window_streamed(lib, K):
-    n = 256 * 10**6 // (4 * K * 32 * 32) + 2
+    n = window_streamed_batch(K)
     gen = torch.Generator(device=DEV).manual_seed(K)
     x = torch.randint(-128, 128, (n, 3, 32, 32), dtype=torch.int8, device=DEV, generator=gen)
     w = torch.randint(-128, 128, (K, 3, 3, 3), dtype=torch.int8, device=DEV, generator=gen)
@@ -1390,7 +1402,11 @@ STENCIL = [
     ConvShape("st-row-4096", 1, 1, 90, 4096, 3, 3, 3, 1, 1), ConvShape("st-row-4112", 1, 1, 90, 4112, 3, 3, 3, 1, 1), ConvShape("st-pad9-s3", 12, 3, 500, 463, 16, 5, 5, 3, 9),
     ConvShape("st-20x5", 30, 1, 161, 333, 32, 20, 5, 2, 0), ConvShape("st-depth256", 14, 4, 137, 138, 24, 7, 7, 1, 3), ConvShape("st-k33", 24, 3, 224, 224, 33, 7, 7, 2, 3),
     ConvShape("st-1x4-k1", 2, 4, 400, 403, 1, 1, 4, 1, 0),
+    # more than 32 channels at a depth of 128 and of 256
+    ConvShape("st-depth128-k61", 30, 3, 141, 141, 61, 5, 5, 2, 2), ConvShape("st-depth256-k37", 44, 4, 150, 150, 37, 7, 7, 2, 3),
+    ConvShape("st-depth256-k64", 26, 4, 150, 150, 64, 7, 7, 2, 3),
 ]
+STENCIL_NOT = ("st-row-4112",)   # wider rows than the kernel takes
 
 
 @pytest.mark.parametrize("cfg", STENCIL, ids=lambda c: c.name)
@@ -1411,11 +1427,22 @@ def test_stencil_tiles(lib, cfg, offset):
         assert (got[:offset] == -77).all() and (got[offset + want.size:] == -77).all()
 
 
-@pytest.mark.parametrize("dims", [(1, 75, 92, 32, 5, 5, 2, 0), (3, 64, 64, 64, 3, 3, 1, 1), (1, 100, 102, 64, 3, 3, 1, 1), (5, 57, 60, 130, 3, 3, 1, 1)])
+# ... of 240 MB: three workgroups per compute unit, the window kernel three times (once above 64 channels), and 256 pixels three per compute
+# unit, planes of whole lines in tiles of 512 (twice) and of 1024, of partial lines in tiles of 1024 that write little
+PAST_THE_CACHE = [(1, 75, 92, 32, 5, 5, 2, 0), (3, 64, 64, 64, 3, 3, 1, 1), (1, 100, 102, 64, 3, 3, 1, 1), (5, 57, 60, 130, 3, 3, 1, 1),
+                  (3, 131, 131, 64, 7, 7, 2, 3), (3, 160, 160, 64, 7, 7, 2, 3), (3, 48, 48, 64, 3, 3, 1, 1), (1, 48, 48, 8, 3, 3, 1, 1),
+                  (3, 62, 62, 2, 3, 3, 1, 1)]
+
+
+def past_the_cache_batch(dims):
+    C, H, W, K, R, S, stride, pad = dims
+    return 240 * 10**6 // (4 * K * ((H + 2 * pad - R) // stride + 1) * ((W + 2 * pad - S) // stride + 1)) + 2
+
+
+@pytest.mark.parametrize("dims", PAST_THE_CACHE)
 def test_stencil_tiles_past_the_last_level_cache(lib, dims):
     C, H, W, K, R, S, stride, pad = dims
-    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
-    n = 240 * 10**6 // (4 * K * P * Q) + 2
+    n = past_the_cache_batch(dims)
     gen = torch.Generator(device=DEV).manual_seed(K + W)
     x = torch.randint(-128, 128, (n, C, H, W), dtype=torch.int8, device=DEV, generator=gen)
     w = torch.randint(-128, 128, (K, C, R, S), dtype=torch.int8, device=DEV, generator=gen)
@@ -1425,10 +1452,61 @@ def test_stencil_tiles_past_the_last_level_cache(lib, dims):
     assert np.array_equal(host(out[-2:]), direct.conv2d_int8(host(x[-2:]), host(w), stride, pad))
 
 
+# Results of 8 to 28 MB on planes of whole sectors: written through the L2s where they start on 64 bytes.  Channels that end inside a block of 32.
+POINTWISE_THROUGH = [(16, C, 28, 28, 250, 1, 1, 1, 0) for C in range(64, 513, 64)] + [(70, 64, 16, 8, 290, 1, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("dims", POINTWISE_THROUGH, ids=str)
+def test_pointwise_results_past_the_caches(lib, dims):
+    """At 64 bytes and 4 past them (stored as dwords into the caches) the same words, the last images against the definition, nothing beside it."""
+    N, C, H, W, K = dims[:5]
+    x = torch.randint(-128, 128, (N, C, H, W), dtype=torch.int8, device=DEV)
+    w = torch.randint(-128, 128, (K, C, 1, 1), dtype=torch.int8, device=DEV)
+    size, results = N * K * H * W, []
+    for start in (64, 65):
+        buf = torch.full((size + 132,), -7, dtype=torch.int32, device=DEV)
+        out = buf[start:start + size].view(N, K, H, W)
+        lib.conv2d_int8_ex(dims, lib.LAYOUT_IMPLICIT, 0, x, w, out, None)
+        assert bool((buf[:start] == -7).all()) and bool((buf[start + size:] == -7).all()), start
+        results.append(out.contiguous())
+    assert torch.equal(*results)
+    assert np.array_equal(host(results[0][-2:]), direct.conv2d_int8(host(x[-2:]), host(w), 1, 0))
+
+
+# (dims, pixels): results of the streaming stage that go past the caches by their size: planes of whole quads from 8 to 28 MB and above
+# 256, of whole sectors up to 28 MB (written through) and above it
+STREAM_PAST = [((32, 256, 14, 14, 500, 3, 3, 1, 1), 196), ((650, 128, 14, 14, 520, 3, 3, 1, 1), 196), ((24, 256, 16, 16, 500, 3, 3, 1, 1), 256),
+               ((60, 128, 16, 16, 500, 3, 3, 1, 1), 256)]
+
+
+@pytest.mark.parametrize("dims,pixels", STREAM_PAST, ids=["quads-12MB", "quads-265MB", "sectors-12MB", "sectors-31MB"])
+def test_stream_results_past_the_caches(lib, dims, pixels):
+    """The same words as the stored path's, channels that end inside the tile, nothing beside the result."""
+    N, C, H, W, K, R, S, stride, pad = dims
+    x = torch.randint(-128, 128, (N, C, H, W), dtype=torch.int8, device=DEV)
+    w = torch.randint(-128, 128, (K, C, R, S), dtype=torch.int8, device=DEV)
+    wp = lib.pack_weights(w, lib.LAYOUT_PACKED, 64)
+    want = torch.empty((N, K, H, W), dtype=torch.int32, device=DEV)
+    lib.conv2d_int8_packed(dims, lib.LAYOUT_PACKED, 64, lib.pack_layout(x, 64, pad), wp, want, tile=0, split_k=1)
+    assert np.array_equal(host(want[-1:]), direct.conv2d_int8(host(x[-1:]), host(w), stride, pad))
+    ran = 0
+    for tile in lib.stream_tiles():
+        if not lib.resident_applies(dims, 64, tile, pixels):
+            continue
+        buf = torch.full((want.numel() + 128,), -7, dtype=torch.int32, device=DEV)
+        out = buf[64:64 + want.numel()].view(want.shape)
+        lib.conv2d_int8_resident(dims, x, wp, out, 64, tile, pixels)
+        assert torch.equal(out, want), tile
+        assert bool((buf[:64] == -7).all()) and bool((buf[64 + want.numel():] == -7).all()), tile
+        ran += 1
+    assert ran
+
+
 # 1x1 weights as they come, rows of C bytes at any address: rows shorter than a 16-byte piece and than 64 bytes, one channel more and less, the
 # tensor's end within a piece, the first batch of pieces and the ones after it (more than 512 channels), strides and a margin.
 ROWS_1X1 = [(2, c, 14, 14, k, s, p) for c, k, s, p in ((17, 33, 1, 0), (24, 64, 2, 0), (33, 47, 1, 1), (63, 32, 1, 0), (65, 95, 2, 1), (100, 130, 1, 0), (200, 64, 1, 0), (319, 31, 2, 0),
-                                                       (541, 70, 1, 0), (1030, 40, 1, 0))] + [(1, 40, 4, 4, 1, 1, 0), (40, 130, 28, 28, 66, 1, 0), (3, 128, 9, 9, 36, 1, 0)]
+                                                       (541, 70, 1, 0), (1030, 40, 1, 0))] + [(1, 40, 4, 4, 1, 1, 0), (40, 130, 28, 28, 66, 1, 0), (3, 128, 9, 9, 36, 1, 0),
+                                                       (59, 17, 7, 7, 260, 2, 0), (11, 18, 32, 32, 183, 2, 0)]
 
 
 @pytest.mark.parametrize("dims", ROWS_1X1, ids=str)

@@ -1,10 +1,12 @@
 """Pieces of the library's code that can run on the host, compiled for the host and run there (no GPU)."""
 import json
 import os
+import re
 import subprocess
 import sys
 
 import pytest
+import test_gpu_parity as gpu
 
 HERE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "host")
 
@@ -138,6 +140,42 @@ def test_large_results_take_the_kernel_that_suits_them(lib, launches, dims, pixe
         P, Q = lib.out_hw(H, W, R, S, stride, pad)
         assert call["workgroups"] == N * -(-(-(-P * Q // 32)) // (pixels // 32)) * -(-K // 64)
         assert (call["lds"] > 160 * 1024 // 4) == few
+
+
+def kernel(call):
+    """Name and integer template arguments of a recorded launch's kernel."""
+    name, args = re.search(r"\d((?:conv|igemm)_\w+?)_kernelI(.*?)EEv", call["kernel"]).groups()
+    return name, tuple(int(v) for v in re.findall(r"L(?:[ib]|NS_\d+[A-Za-z]+E)(\d+)E", args))
+
+
+def test_shapes_of_the_gpu_tests_take_the_kernels_they_are_for(lib, launches):
+    """A line of a dispatch that moves does not leave a kernel without its test."""
+    def kernels(dims):
+        return [kernel(c) for c in launches([(d, lib.LAYOUT_IMPLICIT, 0, packed) for d in dims for packed in (0, 1)])[::2]]
+
+    stencil = dict(zip((c.name for c in gpu.STENCIL), kernels([c.dims() for c in gpu.STENCIL])))
+    assert {name for name, k in stencil.items() if k[0] != "conv_stencil"} == set(gpu.STENCIL_NOT)
+    past = kernels([(gpu.past_the_cache_batch(d), *d) for d in gpu.PAST_THE_CACHE])
+    assert [k[0] for k in past] == ["conv_stencil"] + ["conv_window"] * 3 + ["conv_stencil"] * 5
+    # every depth with 32 and with 64 channels to a workgroup
+    ran = {k[1] for k in [*stencil.values(), *past] if k[0] == "conv_stencil"}
+    assert ran == {(depth, blocks) for depth in (2, 4, 6, 8) for blocks in (1, 2)}
+    # the window kernel in several row groups (the fifth argument), through and past the caches (the sixth)
+    assert [k[1][1:] for k in kernels([c.dims() for c in gpu.WINDOW_GROUPS])] == [(1, 0, 0, 1, 0)] * 3 + [(2, 0, 0, 1, 0)] + [(1, 0, 0, 1, 2)] * 2
+    assert [k[1] for k in kernels([(gpu.window_streamed_batch(K), 3, 32, 32, K, 3, 3, 1, 1) for K in (16, 64)])] == [(2, 1, 0, 0, 1, 1), (2, 2, 0, 0, 0, 1)]
+    # the 1x1 kernel past the caches, every depth
+    assert set(kernels(gpu.POINTWISE_THROUGH)) == {("conv_pointwise", (n, 0, 1)) for n in range(2, 17, 2)}
+
+
+def test_raw_1x1_weights_take_the_resident_kernel(lib):
+    """... without a launch that rewrites them, in every tile that the library picks; its tile and pixels run on rewritten weights too."""
+    tiles = set()
+    for N, C, H, W, K, stride, pad in gpu.ROWS_1X1:
+        dims = (N, C, H, W, K, 1, 1, stride, pad)
+        stage, tile, pixels = lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, False)
+        assert stage == lib.STAGE_RESIDENT and lib.resident_applies(dims, 16, tile, pixels), dims
+        tiles.add(tile)
+    assert tiles == {0, 1, 2, 4}
 
 
 @pytest.fixture(scope="module")
