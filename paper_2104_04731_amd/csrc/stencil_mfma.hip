@@ -293,14 +293,16 @@ __global__ void __launch_bounds__(STENCIL_THREADS, NKK * NKB > 12 ? 3 : 4) conv_
 //   written in parts must be less than its L2.  Where one writes 36 KB and more, three per compute unit (128 images 5 x 5 / 2 -> 32, 326 MB:
 //   0.64, and 0.72 with as many as fit), 512 pixels, 256 above 32 channels (512: up to 1.2 of that).  Of less as many as fit, with 1024
 //   pixels up to 8 channels: three were up to 1.95 (15352 images 3 x 62 x 62, 3 x 3 -> 2: 725 us, the window kernel 371, as many as fit 352).
+//   (240 layers of 190 to 245 MB and more than 32 channels: 0.965 of the time of 512 pixels and as many as fit.)  1024 pixels whose window is too
+//   large: 512 (2087 images 8 x 91 x 260, 3 x 3 / 2 -> 6, 300 MB: 177 us, the window kernel 535).
 //   Smaller results, up to 32 channels: the most pixels of 256, 512, 1024 that leave 640 workgroups: the window's rows overlap and the weights come in
 //   once per tile (112 images 20 x 5 / 2 -> 32, 140 MB: 256 pixels 0.89, 512 0.70, 1024 0.64).  Below 160 000 pixels, 240 000 for depths up to 128,
 //   the window kernel's many small workgroups win (1.0 - 1.2), and so they do up to 125 MB for a depth of 64 and 25 - 32 channels (1.0 - 1.1).
 //   Smaller results, more channels: from 120 MB on (0.65 - 0.95; 3 x 3 kernels in one depth of 64 from 200 MB, 1.0 - 1.2 below), deep stems from 36 MB
 //   (0.61 - 1.0).  Many channels on narrow images make windows of many short rows: the window kernel's (up to 1.3).
-//   And where the window kernel's blocks of 32 pixels suit the rows (stencil_pays).  600 layers drawn once that was settled: up to 32 channels 0.68
-//   in the mean and 1.07 at worst on planes of partial lines (0.93 and 2.06 without these two rules), 0.80 and 1.12 on others; above 32
-//   channels 0.92 and 1.15 (0.97 and 1.8), 0.95 and 1.13.
+//   And where the window kernel's blocks of 32 pixels suit the rows (stencil_pays).  906 layers drawn once that was settled, three inputs and two
+//   results in turn, mean and worst, results from 190 MB on: up to 32 channels 0.75 and 1.17 on planes of partial lines, 0.72 and 1.03 on others; above
+//   0.90 and 1.16, 0.84 and 1.03.  Smaller ones: 0.86 and 1.08, 0.90 and 1.05; above 32 channels 0.96 and 1.17, 0.96 and 1.05.
 static bool stencil_pays(const WindowProblem &g, int depth, double out, bool lines)
 {
     // how full its tiles of 128 pixels are
@@ -312,12 +314,10 @@ static bool stencil_pays(const WindowProblem &g, int depth, double out, bool lin
         return g.Q % 32 != 0 || g.K <= 8 || out < 150e6 || fill <= 0.65 || (g.K <= 16 && depth >= 128 && fill < 0.95);
     }
     if (g.K <= 32) return true;
-    if (tiles == 1) return false;                                                         // (an image to a workgroup on both sides: 0.8 - 1.5)
-    if (out < 190e6) return depth != 128 || fill <= 0.62;                                 // (0.72 - 1.0; better filled 0.93 - 1.11)
-    // up to 290 MB the last-level cache takes in what it writes in parts
-    if (out < 290e6) return fill <= (g.K <= 64 && depth >= 192 ? 0.65 : 0.45);             // (0.47 - 1.09; up to 0.6 0.84 - 1.47, beyond 0.9 - 1.33)
-    if (g.K > 64) return fill <= 0.45;                                                    // (0.5 - 1.0; beyond 0.76 - 1.21)
-    return depth >= 128 || fill <= (g.Q % 4 == 0 ? 0.45 : 0.80);                           // (0.54 - 1.07; beyond, and 16-byte stores, 0.9 - 1.17)
+    if (tiles == 1) return false;   // (an image to a workgroup on both sides: 0.8 - 1.5)
+    if (out < 45e6) return fill <= 0.70;   // (deep stems of 36 MB and more: 0.85 - 0.91; better filled 0.91 - 1.17, 1.04 in the mean)
+    // more than 64 channels: 0.57 - 1.23 and 0.98 in the mean, better filled 0.95 - 1.38 and 1.08
+    return out < 190e6 || g.K <= 64 || fill < 0.80;
 }
 
 static int stencil_tile(const WindowProblem &g, int depth, bool *few)
@@ -330,7 +330,7 @@ static int stencil_tile(const WindowProblem &g, int depth, bool *few)
     if (!stencil_pays(g, depth, out, lines)) return 0;
     const int partial = g.K <= 8 ? 1024 : g.K <= 32 ? 512 : 256;
     const double written = 4.0 * std::min<long long>(partial, (long long)g.P * g.Q) * std::min(g.K, 64);   // by a workgroup
-    if (out >= 240e6) {
+    if (out >= (lines || g.K <= 32 ? 240e6 : 190e6)) {
         if (lines) return g.K <= 16 ? 1024 : 512;
         *few = written >= 36e3;
         return partial;
@@ -368,12 +368,16 @@ static bool stencil_plan(const WindowProblem &g, StencilArgs *out, dim3 *grid, s
     // a row holds the whole image row and what the last pixel's last dword pair reaches
     const long long reach = margin - g.pad + (long long)(g.Q - 1) * g.stride + S4 + 4;
     const long long pitch = (std::max(margin + ((long long)g.W + 15) / 16 * 16, reach) + 15) / 16 * 16;
-    // the image's blocks of 32 pixels spread evenly over its tiles
+    // the image's blocks of 32 pixels spread evenly over its tiles; 512 pixels where the window of 1024 is too large
     const int blocks = (int)((PQ + 31) / 32);
-    a.tiles = (blocks + target / 32 - 1) / (target / 32);
-    a.mper = (blocks + a.tiles - 1) / a.tiles * 32;
-    const long long rows_out = a.tiles == 1 ? g.P : std::min<long long>((a.mper + g.Q - 2) / g.Q + 1, g.P);   // that consecutive pixels touch at most
-    const long long RW = (rows_out - 1) * g.stride + g.R, win = g.C * RW * pitch;
+    long long RW, win;
+    for (int pixels = target;; pixels = 512) {
+        a.tiles = (blocks + pixels / 32 - 1) / (pixels / 32);
+        a.mper = (blocks + a.tiles - 1) / a.tiles * 32;
+        const long long rows_out = a.tiles == 1 ? g.P : std::min<long long>((a.mper + g.Q - 2) / g.Q + 1, g.P);   // that consecutive pixels touch at most
+        RW = (rows_out - 1) * g.stride + g.R, win = g.C * RW * pitch;
+        if (win <= STENCIL_WINDOW || pixels <= 512) break;
+    }
     if (pitch > STENCIL_WINDOW || RW > STENCIL_WINDOW || win > STENCIL_WINDOW || (long long)g.N * a.tiles > 0x7FFFFFFFLL || (g.K + 63) / 64 > 65535) return false;
     a.RW = (int)RW;
     a.pitch = (int)pitch;

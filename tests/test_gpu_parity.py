@@ -1427,8 +1427,8 @@ def test_stencil_tiles(lib, cfg, offset):
         assert (got[:offset] == -77).all() and (got[offset + want.size:] == -77).all()
 
 
-# ... of 240 MB: three workgroups per compute unit, the window kernel three times (once above 64 channels), and 256 pixels three per compute
-# unit, planes of whole lines in tiles of 512 (twice) and of 1024, of partial lines in tiles of 1024 that write little
+# ... of 240 MB: three workgroups per compute unit, the window kernel on whole lines, 256 pixels three per compute unit, the window kernel above
+# 64 channels, 256 pixels again, planes of whole lines in tiles of 512 (twice) and of 1024, of partial lines in tiles of 1024 that write little
 PAST_THE_CACHE = [(1, 75, 92, 32, 5, 5, 2, 0), (3, 64, 64, 64, 3, 3, 1, 1), (1, 100, 102, 64, 3, 3, 1, 1), (5, 57, 60, 130, 3, 3, 1, 1),
                   (3, 131, 131, 64, 7, 7, 2, 3), (3, 160, 160, 64, 7, 7, 2, 3), (3, 48, 48, 64, 3, 3, 1, 1), (1, 48, 48, 8, 3, 3, 1, 1),
                   (3, 62, 62, 2, 3, 3, 1, 1)]
