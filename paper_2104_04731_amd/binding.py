@@ -18,6 +18,7 @@ OK, ERR_INVALID_ARG, ERR_UNSUPPORTED, ERR_OVERFLOW_RISK, ERR_WORKSPACE, ERR_DEVI
 LAYOUT_AUTO, LAYOUT_PACKED, LAYOUT_IM2COL, LAYOUT_PAD_ONLY, LAYOUT_IMPLICIT, LAYOUT_IMAGE_PACK = range(6)
 TILE_BAND = -2   # CONV_TILE_BAND
 TILE_STREAM = 256   # CONV_TILE_STREAM: the first of these tiles
+TILE_PANEL = 512    # CONV_TILE_PANEL: query_stage's first one of conv2d_int8_panel
 ENTRY_ONE_SHOT, ENTRY_EX, ENTRY_NHWC, ENTRY_DILATED, ENTRY_DILATED_DIRECT = range(5)
 STAGE_STORED, STAGE_RESIDENT, STAGE_RESIDENT_RAW, STAGE_RESIDENT_REWRITE, STAGE_BAND, STAGE_AS_IS, STAGE_STREAM, STAGE_STREAM_REWRITE = range(8)
 STAGE_NAMES = ("stored rewrites", "resident", "resident, raw weights", "resident, weights rewritten first", "band on NCHW", "as is", "streamed weights",
@@ -38,7 +39,7 @@ EXPORTS = [
     "conv2d_int8_dilated_direct_workspace_bytes", "conv2d_int8_dilated_direct",
     "gemm_int8_nt", "select_layout", "select_layout_weighted", "layout_overheads",
     "conv_status_string", "conv2d_int8_resident", "conv2d_int8_resident_applies", "conv2d_int8_resident_tile_info",
-    "conv2d_int8_query_stage", "conv2d_int8_stored",
+    "conv2d_int8_query_stage", "conv2d_int8_stored", "conv2d_int8_panel", "conv2d_int8_panel_workspace_bytes", "conv2d_int8_panel_tile_info",
 ]
 
 
@@ -133,6 +134,9 @@ def load(path: str | None = None):
         "conv2d_int8_resident": (i, [dp, i, i, vp, vp, i, vp, i, i, vp]),
         "conv2d_int8_resident_applies": (i, [dp, i, i, i, i, i]),
         "conv2d_int8_resident_tile_info": (i, [i, ip, ip, ip]),
+        "conv2d_int8_panel": (i, [dp, i, i, vp, vp, i, vp, i, i, vp, sz, vp]),
+        "conv2d_int8_panel_workspace_bytes": (sz, [dp, i, i, i, i, i]),
+        "conv2d_int8_panel_tile_info": (i, [i, ip, ip]),
         "conv2d_int8_query_stage": (i, [dp, i, i, i, i, i, ip, ip, ip]),
     }
     for name, (res, args) in sig.items():
@@ -290,6 +294,28 @@ def stream_tiles():
     out, v = {}, [ctypes.c_int() for _ in range(3)]
     while load().conv2d_int8_resident_tile_info(TILE_STREAM + len(out), *map(ctypes.byref, v)) == OK:
         out[TILE_STREAM + len(out)] = tuple(x.value for x in v)
+    return out
+
+
+def conv2d_int8_panel(dims, x: torch.Tensor, w: torch.Tensor, out: torch.Tensor, wt_cb: int, tile: int, pixels: int, workspace: torch.Tensor,
+                      dilation=1, nhwc=False, stream=None):
+    """The stage that reads its weights in panels, with this tile and pixels per workgroup (wt_cb 0: KCRS weights)."""
+    _require(x, torch.int8, "input"); _require(w, torch.int8, "weights"); _require(out, torch.int32, "output")
+    _check(load().conv2d_int8_panel(ctypes.byref(_desc(*dims)), dilation, int(nhwc), _ptr(x), _ptr(w), wt_cb, _ptr(out), tile, pixels,
+                                    _ptr(workspace), workspace.numel(), _stream(stream)), "conv2d_int8_panel")
+    return out
+
+
+def panel_workspace_bytes(dims, wt_cb: int, tile: int, pixels: int, dilation=1, nhwc=False) -> int:
+    """0: the stage does not take this call."""
+    return load().conv2d_int8_panel_workspace_bytes(ctypes.byref(_desc(*dims)), dilation, int(nhwc), wt_cb, tile, pixels)
+
+
+def panel_tiles():
+    """(output channels, most pixels) of every tile."""
+    out, v = [], [ctypes.c_int() for _ in range(2)]
+    while load().conv2d_int8_panel_tile_info(len(out), *map(ctypes.byref, v)) == OK:
+        out.append(tuple(x.value for x in v))
     return out
 
 

@@ -348,10 +348,11 @@ enum RouteHow : int {
     DIRECT_REWRITE = CONV_STAGE_RESIDENT_REWRITE,
     DIRECT_BAND = CONV_STAGE_BAND,
     DIRECT_STREAM = CONV_STAGE_STREAM,
-    DIRECT_STREAM_REWRITE = CONV_STAGE_STREAM_REWRITE
+    DIRECT_STREAM_REWRITE = CONV_STAGE_STREAM_REWRITE,
+    DIRECT_PANEL = CONV_TILE_PANEL   // (reported as CONV_STAGE_STORED, with its tile)
 };
 struct Route {
-    int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones, band kernel on packed ones, stream kernel on packed / rewritten ones
+    int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones, band kernel on packed ones, stream kernel on packed / rewritten ones, panel kernel
     ResidentChoice pick;
     int cb, depth;       // block and row bytes of the weights it reads (the two REWRITEs: what is rewritten; PAD_ONLY's, PACKED's)
     bool raw;            // KCRS as it came, not in depth order
@@ -406,6 +407,19 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
                 *n = Route{how, c, cb, depth, raw};
             }
         };
+        // Last: the panel kernel, two launches, where its estimate is below 0.9 of the best other one's and its panels fit the workspace that the
+        // other routes ask for: 2150 of 9400 calls of 6 to 600 us, 0.81 of the time in the mean, 3 % of them more than 2 %
+        // longer (at 0.95 of it 2540, 0.83, 5 %).  Not for NCHW tensors of
+        // up to 64 channels, whose window and weights the resident kernel holds in LDS whole: 330 calls that the estimates would send here take 0.92, 12 %
+        // of them more than 5 % longer (at worst 1.5).
+        auto panels = [&](double before) {
+            if (!nhwc && d->C <= 64) return;
+            const size_t room = align_up(pl.x_bytes, WS_ALIGN) + (wt_is_packed ? 0 : align_up(pl.w_bytes, WS_ALIGN));
+            ResidentChoice c;
+            if (panel_weight_bytes(d->K, d->C, d->R * d->S) <= room &&
+                panel_pick(resident_problem(d, pl, pl.cb, pl.depth, !wt_is_packed, nhwc, dil, nullptr, nullptr, out), 0.9 * before - SECOND_LAUNCH_US, &c))
+                *n = Route{DIRECT_PANEL, c, pl.cb, pl.depth, !wt_is_packed};
+        };
         if (wt_is_packed) {
             if (pl.layout == CONV_LAYOUT_PACKED || pl.layout == CONV_LAYOUT_PAD_ONLY) {
                 consider(DIRECT_AS_IS, pl.cb, pl.depth, false, 0);
@@ -420,7 +434,8 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
                 // the stored path's estimate and below 262 do, 1.185, 8 %.
                 ResidentChoice c;
                 if (stream_pick(resident_problem(d, pl, pl.cb, pl.depth, false, nhwc, dil, nullptr, nullptr, out), walk, best, n->how == TWO_STAGE ? 0.86 : 1, &c))
-                    *n = Route{DIRECT_STREAM, c, pl.cb, pl.depth, false};
+                    *n = Route{DIRECT_STREAM, c, pl.cb, pl.depth, false}, best = c.us;
+                panels(best);
             }
             return true;
         }
@@ -442,8 +457,9 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             ResidentChoice c;
             const double rewrite = 2.8 + 1.0e-6 * (double)d->K * depth64 + SECOND_LAUNCH_US;
             if (stream_pick(resident_problem(d, pl, 64, depth64, false, nhwc, dil, nullptr, nullptr, out), walk, 0.95 * best - rewrite, 1, &c))
-                *n = Route{DIRECT_STREAM_REWRITE, c, 64, depth64, false};
+                *n = Route{DIRECT_STREAM_REWRITE, c, 64, depth64, false}, best = c.us + rewrite;
         }
+        panels(best);
         return true;
     });
     return *kept;
@@ -459,11 +475,17 @@ int run_direct(const Route &rt, const conv_desc_t *d, const Plan &pl, bool nhwc,
         wt = static_cast<const int8_t *>(ws);
     }
     const ResidentProblem r = resident_problem(d, pl, rt.cb, rt.depth, rt.raw, nhwc, dil, in, wt, out);
+    if (rt.how == DIRECT_PANEL) {
+        int8_t *const panels = static_cast<int8_t *>(ws);
+        const hipError_t e = launch_panel_weights(r, panels, st);
+        return gemm_status(e == hipSuccess ? launch_panel(r, panels, rt.pick.tile, rt.pick.mper, st) : e);
+    }
     if (rt.how == DIRECT_STREAM || rt.how == DIRECT_STREAM_REWRITE) return gemm_status(launch_stream(r, rt.pick.tile, rt.pick.mper, st));
     return gemm_status(rt.how == DIRECT_BAND ? launch_band_direct(r, st) : launch_resident(r, rt.pick, st));
 }
 size_t direct_bytes(const Route &rt, const conv_desc_t *d)
 {
+    if (rt.how == DIRECT_PANEL) return panel_weight_bytes(d->K, d->C, d->R * d->S);
     return rt.how == DIRECT_REWRITE || rt.how == DIRECT_STREAM_REWRITE ? (size_t)d->K * rt.depth : 0;
 }
 
@@ -1141,9 +1163,10 @@ int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int 
         }
         if (rc != CONV_OK) return rc;
     } else return CONV_ERR_INVALID_ARG;
-    *stage = as_is ? CONV_STAGE_AS_IS : rt.how;
+    const bool panel = !as_is && rt.how == DIRECT_PANEL;
+    *stage = as_is ? CONV_STAGE_AS_IS : panel ? CONV_STAGE_STORED : rt.how;
     const bool stream = rt.how == DIRECT_STREAM || rt.how == DIRECT_STREAM_REWRITE, given = rt.how == DIRECT_BAND || rt.how == TWO_STAGE;
-    *tile = given ? -1 : rt.pick.tile + (stream ? CONV_TILE_STREAM : 0);
+    *tile = given ? -1 : rt.pick.tile + (stream ? CONV_TILE_STREAM : panel ? CONV_TILE_PANEL : 0);
     *pixels = given ? 0 : rt.pick.mper;
     return CONV_OK;
 }
@@ -1188,6 +1211,48 @@ int conv2d_int8_resident(const conv_desc_t *desc, int dilation, int nhwc, const 
     if (!in || !wt || !out || (wt_cb && !aligned16(wt))) return CONV_ERR_INVALID_ARG;
     if (is_stream_tile(tile)) return gemm_status(launch_stream_forced(r, tile - CONV_TILE_STREAM, pixels, (hipStream_t)stream));
     return gemm_status(tile == CONV_TILE_BAND ? launch_band_direct(r, (hipStream_t)stream) : launch_resident_forced(r, tile, pixels, (hipStream_t)stream));
+}
+
+// ---- the panel kernel on its own -------------------------------------------------------------------------------------
+static int panel_forced(const conv_desc_t *desc, int dilation, int nhwc, int wt_cb, int tile, int pixels, const int8_t *in, const int8_t *wt, int32_t *out,
+                        ResidentProblem *r)
+{
+    if (wt_cb < 0 || tile < 0 || tile >= panel_num_tiles() || pixels < 1 || pixels > panel_tile_info(tile).cols) return CONV_ERR_INVALID_ARG;
+    Plan pl;
+    const int rc = direct_dilated_plan(desc, dilation, wt_cb ? wt_cb : 16, &pl);
+    if (rc != CONV_OK) return rc;
+    *r = resident_problem(desc, pl, pl.cb, pl.depth, wt_cb == 0, nhwc != 0, dilation, in, wt, out);
+    return panel_applies(*r, tile, pixels) ? CONV_OK : CONV_ERR_UNSUPPORTED;
+}
+
+int conv2d_int8_panel_tile_info(int tile, int *rows, int *cols)
+{
+    if (tile < 0 || tile >= panel_num_tiles()) return CONV_ERR_INVALID_ARG;
+    const TileInfo t = panel_tile_info(tile);
+    if (rows) *rows = t.rows;
+    if (cols) *cols = t.cols;
+    return CONV_OK;
+}
+
+size_t conv2d_int8_panel_workspace_bytes(const conv_desc_t *desc, int dilation, int nhwc, int wt_cb, int tile, int pixels)
+{
+    ResidentProblem r;
+    return panel_forced(desc, dilation, nhwc, wt_cb, tile, pixels, nullptr, nullptr, nullptr, &r) == CONV_OK
+               ? panel_weight_bytes(desc->K, desc->C, desc->R * desc->S)
+               : 0;
+}
+
+int conv2d_int8_panel(const conv_desc_t *desc, int dilation, int nhwc, const int8_t *in, const int8_t *wt, int wt_cb, int32_t *out, int tile,
+                      int pixels, void *workspace, size_t workspace_bytes, void *stream)
+{
+    ResidentProblem r;
+    const int rc = panel_forced(desc, dilation, nhwc, wt_cb, tile, pixels, in, wt, out, &r);
+    if (rc != CONV_OK) return rc;
+    if (!in || !wt || !out || !workspace || (wt_cb && !aligned16(wt)) || !aligned16(workspace)) return CONV_ERR_INVALID_ARG;
+    if (workspace_bytes < panel_weight_bytes(desc->K, desc->C, desc->R * desc->S)) return CONV_ERR_WORKSPACE;
+    int8_t *const panels = static_cast<int8_t *>(workspace);
+    const hipError_t e = launch_panel_weights(r, panels, (hipStream_t)stream);
+    return gemm_status(e == hipSuccess ? launch_panel(r, panels, tile, pixels, (hipStream_t)stream) : e);
 }
 
 int conv2d_int8_tile_applies(const conv_desc_t *desc, int layout, int cb, int tile, int split_k)

@@ -108,6 +108,14 @@ bool stream_applies(const ResidentProblem &r, int tile, int mper);
 bool stream_pick(const ResidentProblem &r, WindowWalk &walk, double limit, double smallest, ResidentChoice *c);
 hipError_t launch_stream(const ResidentProblem &r, int tile, int mper, hipStream_t st);
 hipError_t launch_stream_forced(const ResidentProblem &r, int tile, int mper, hipStream_t st);
+// The panel kernel (panel_mfma.hip) on the same problem: weights (raw, or in any blocks) rewritten into panels by a launch of their own.
+int panel_num_tiles();
+TileInfo panel_tile_info(int tile);      // rows, cols: output channels and (at most) pixels of a workgroup
+size_t panel_weight_bytes(int K, int C, int RS);
+hipError_t launch_panel_weights(const ResidentProblem &r, int8_t *dst, hipStream_t st);   // dst: panel_weight_bytes, 16-byte aligned
+bool panel_applies(const ResidentProblem &r, int tile, int mper);
+bool panel_pick(const ResidentProblem &r, double limit, ResidentChoice *c);   // false: no estimate (both launches) below `limit`, or not its domain
+hipError_t launch_panel(const ResidentProblem &r, const int8_t *panels, int tile, int mper, hipStream_t st);
 // The band kernel on the same problem (NCHW, weights in blocks of 64): estimated launch time; false: not its domain.
 bool band_direct_us(const ResidentProblem &r, double *us);
 bool band_direct_applies(const ResidentProblem &r);   // (also where the estimate is not made: large grids)

@@ -37,6 +37,12 @@ __device__ __forceinline__ void store_past16(__amdgpu_buffer_rsrc_t base, unsign
 {
     __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(past_v4u, x), base, off, row, past_bits(HOW));
 }
+// The same with plain stores among the kinds.
+template <Past HOW>
+__device__ __forceinline__ void store_row16(__amdgpu_buffer_rsrc_t base, unsigned off, unsigned row, past_v4i x)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(past_v4u, x), base, off, row, HOW == PAST_NONE ? 0 : past_bits(HOW));
+}
 template <Past HOW>
 __device__ __forceinline__ void store_past4(__amdgpu_buffer_rsrc_t base, unsigned off, unsigned row, int x)
 {

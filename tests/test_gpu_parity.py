@@ -1849,3 +1849,85 @@ def test_dilated_direct_through_stored_rewrites(lib, case):
     out = torch.full(want.shape, -3, dtype=torch.int32, device=DEV)
     lib.conv2d_int8_dilated_direct(dims, d, dev(x), dev(w), cb, out=out)
     assert np.array_equal(host(out), want)
+
+
+# ---- the panel kernel (window in LDS, weights from panels into registers) ----------------------------------------------------
+# Remainders of every kind: channels of the last 64, output channels of the last 32, 64 and tile, planes of no whole 16 bytes, images that end
+# inside a tile and inside eight slots, no border, taps a row or a column apart only, several parts of the depth, the tensor's end.
+PANEL_DIMS = [((2, 64, 14, 14, 64, 3, 3, 1, 1), 1), ((1, 70, 9, 11, 100, 3, 3, 1, 1), 1), ((3, 130, 7, 7, 300, 3, 3, 1, 1), 1), ((2, 64, 14, 15, 65, 3, 3, 2, 1), 1),
+              ((5, 40, 8, 8, 70, 5, 5, 1, 2), 1), ((2, 96, 13, 13, 130, 3, 3, 1, 0), 1), ((2, 65, 14, 14, 33, 3, 3, 1, 2), 2), ((3, 200, 17, 9, 65, 3, 2, 1, 1), 1),
+              ((1, 192, 20, 20, 31, 3, 3, 1, 3), 3), ((9, 67, 3, 3, 64, 3, 3, 1, 0), 1), ((3, 101, 5, 9, 70, 1, 1, 1, 0), 1), ((2, 700, 8, 8, 64, 3, 3, 1, 1), 1),
+              ((1, 130, 30, 56, 64, 3, 3, 1, 1), 1), ((4, 16, 1, 8, 32, 1, 5, 1, 0), 1)]
+
+
+@pytest.mark.parametrize("dims,d", PANEL_DIMS, ids=str)
+def test_panel_stage(lib, dims, d):
+    """Every tile, with as many pixels as it takes, with counts that fill no block and with one, on weights of every form."""
+    N, C, H, W, K, R, S, stride, pad = dims
+    x = uniform_int8(991, (N, C, H, W)); w = uniform_int8(992, (K, C, R, S))
+    want = direct.conv2d_int8_dilated(x, w, stride, pad, d)
+    dw, ran = dev(w), set()
+    forms = {0: dw, 16: lib.pack_weights(dw, lib.LAYOUT_PACKED, 16), 64: lib.pack_weights(dw, lib.LAYOUT_PACKED, 64)}
+    for nhwc in (False, True):
+        dx = dev(np.ascontiguousarray(x.transpose(0, 2, 3, 1))) if nhwc else dev(x)
+        expect = np.ascontiguousarray(want.transpose(0, 2, 3, 1)) if nhwc else want
+        for tile, (rows, cols) in enumerate(lib.panel_tiles()):
+            for pixels in (1, 49, cols - 16, cols):
+                for cb, weights in forms.items():
+                    need = lib.panel_workspace_bytes(dims, cb, tile, pixels, d, nhwc)
+                    if not need or (pixels == 1 and cb):
+                        continue
+                    ws = torch.full((need + 64,), 77, dtype=torch.int8, device=DEV)
+                    buf = torch.full((want.size + 128,), -7, dtype=torch.int32, device=DEV)
+                    lib.conv2d_int8_panel(dims, dx, weights, buf[64:-64].view(expect.shape), cb, tile, pixels, ws[:need], d, nhwc)
+                    got = host(buf)
+                    assert np.array_equal(got[64:-64].reshape(expect.shape), expect), (nhwc, tile, pixels, cb)
+                    assert (got[:64] == -7).all() and (got[-64:] == -7).all() and bool((ws[need:] == 77).all())
+                    ran.add((nhwc, tile))
+    assert len(ran) == 2 * len(lib.panel_tiles())
+
+
+@pytest.mark.parametrize("dims,kept", [((200, 128, 28, 28, 100, 3, 3, 2, 1), True), ((300, 96, 14, 15, 200, 3, 3, 2, 1), False)], ids=["kept weights", "raw weights"])
+@pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "off by a byte and a value"])
+def test_calls_that_take_the_panel_stage(lib, dims, kept, offset):
+    """Kept weights; one-shot and NHWC; eager and replayed, in a workspace of the size the library asks for."""
+    N, C, H, W, K, R, S, stride, pad = dims
+    x = uniform_int8(993, (N, C, H, W)); w = uniform_int8(994, (K, C, R, S))
+    want = direct.conv2d_int8(x, w, stride, pad)
+    dx = torch.empty(x.size + 1, dtype=torch.int8, device=DEV)[offset:offset + x.size].view(x.shape)
+    dx.copy_(torch.from_numpy(x))
+    dw = dev(w)
+    wq = lib.pack_weights(dw, lib.LAYOUT_PACKED, 64) if kept else dw
+    assert lib.query_stage(dims, lib.ENTRY_EX, lib.LAYOUT_PACKED, 64, kept)[1] >= lib.TILE_PANEL
+    need = lib.conv2d_int8_workspace_bytes(dims, lib.LAYOUT_PACKED, 64, kept)
+    ws = torch.full((need + 256,), 85, dtype=torch.int8, device=DEV)
+    out = torch.full((want.size + 1,), -7, dtype=torch.int32, device=DEV)[offset:offset + want.size].view(want.shape)
+    call = lambda: lib.conv2d_int8_ex(dims, lib.LAYOUT_PACKED, 64, dx, wq, out, ws[:need], wt_is_packed=kept)
+    assert np.array_equal(host(call()), want) and bool((ws[need:] == 85).all())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for _ in range(3):
+        out.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(host(out), want)
+    if not kept:
+        assert lib.query_stage(dims, lib.ENTRY_ONE_SHOT)[1] >= lib.TILE_PANEL and lib.query_stage(dims, lib.ENTRY_NHWC)[1] >= lib.TILE_PANEL
+        assert np.array_equal(host(lib.conv2d_int8(dx, dw, stride, pad)), want)
+        got = lib.conv2d_int8_nhwc(dx.permute(0, 2, 3, 1).contiguous(), dw, stride, pad)
+        assert np.array_equal(host(got).transpose(0, 3, 1, 2), want)
+
+
+def test_dilated_calls_that_take_the_panel_stage(lib):
+    dims, d = (300, 192, 15, 15, 33, 3, 3, 1, 2), 2
+    x = uniform_int8(995, dims[:4]); w = uniform_int8(996, (dims[4], dims[1], 3, 3))
+    want = direct.conv2d_int8_dilated(x, w, 1, 2, d)
+    desc, of = lib._desc(*dims), lib.load()
+    for entry, call, need in ((lib.ENTRY_DILATED, lib.conv2d_int8_dilated, of.conv2d_int8_dilated_workspace_bytes(desc, d, lib.LAYOUT_AUTO, 0)),
+                              (lib.ENTRY_DILATED_DIRECT, lib.conv2d_int8_dilated_direct, of.conv2d_int8_dilated_direct_workspace_bytes(desc, d, 0))):
+        assert lib.query_stage(dims, entry, dilation=d)[1] >= lib.TILE_PANEL
+        ws = torch.full((need + 256,), 85, dtype=torch.int8, device=DEV)
+        out = torch.full(want.shape, -7, dtype=torch.int32, device=DEV)
+        call(dims, d, dev(x), dev(w), out=out, workspace=ws[:need])
+        assert np.array_equal(host(out), want) and bool((ws[need:] == 85).all())

@@ -46,6 +46,26 @@ def test_window_walk_against_its_definition(run_host):
     assert run_host("window_walk", ("-x", "c++")) == (0, "ok")
 
 
+def test_panel_windows_stay_inside_tensor_and_window(run_host):
+    """The panel kernel's windows over random problems: guard pages around the tensor, and every tap's input at its distance."""
+    assert run_host("panel_fill", ("-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include")) == (0, "ok")
+
+
+def test_panel_stage_validation(lib):
+    """What the stage refuses, before any device call; no tile asks for more LDS than lets two workgroups share a compute unit."""
+    import ctypes
+    raw, d, p = lib.load(), lib.ConvDesc(2, 64, 14, 14, 64, 3, 3, 1, 1), 256
+    call = lambda x=p, w=p, o=p, cb=64, tile=0, px=64, ws=p, n=1 << 30, dil=1, desc=d: raw.conv2d_int8_panel(ctypes.byref(desc), dil, 0, x, w, cb, o, tile, px, ws, n, None)
+    tiles = lib.panel_tiles()
+    for bad in (dict(tile=-1), dict(tile=len(tiles)), dict(px=0), dict(px=tiles[0][1] + 1), dict(cb=-1), dict(x=0), dict(w=0), dict(o=0), dict(ws=0), dict(w=264), dict(ws=264), dict(dil=0)):
+        assert call(**bad) == lib.ERR_INVALID_ARG, bad
+    assert call(n=lib.panel_workspace_bytes((2, 64, 14, 14, 64, 3, 3, 1, 1), 64, 0, 64) - 1) == lib.ERR_WORKSPACE
+    assert call(cb=24) == lib.ERR_UNSUPPORTED
+    # a border wider than the kernel, rows of fewer than eight slots, a window that fits no compute unit
+    for dims in ((2, 64, 14, 14, 64, 3, 3, 1, 3), (2, 64, 14, 5, 64, 3, 3, 1, 1), (1, 64, 700, 700, 64, 3, 3, 1, 1)):
+        assert call(desc=lib.ConvDesc(*dims)) == lib.ERR_UNSUPPORTED and lib.panel_workspace_bytes(dims, 64, 0, 64) == 0, dims
+
+
 # (dims, layout, block): layers whose one-shot and kept-weights calls both take the resident kernel, with different tiles or pixels
 SHARED_LAYERS = [((266, 64, 56, 56, 64, 5, 5, 1, 2), 3, 0), ((233, 32, 9, 9, 275, 5, 5, 1, 2), 3, 0), ((161, 64, 32, 32, 59, 5, 5, 1, 2), 3, 0),
                  ((87, 32, 15, 15, 172, 5, 5, 1, 2), 3, 0), ((2, 70, 37, 37, 163, 5, 5, 1, 2), 3, 0), ((215, 64, 7, 7, 432, 5, 5, 1, 2), 3, 0)]
