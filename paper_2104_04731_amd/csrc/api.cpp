@@ -337,7 +337,6 @@ double two_stage_us(const conv_desc_t *d, const Plan &pl, const GemmProblem &g, 
     const double moved = (double)d->N * d->C * d->H * d->W + (double)pl.x_bytes;
     double us = f.launch + f.gemm * c.cost + f.moved * moved + f.weights * (double)pl.w_bytes + (apart ? f.apart : 0);
     if (nhwc && d->C % 16) us += 1.4 + 0.12e-6 * moved;                                      // (pixels' ends go byte by byte)
-    if (nhwc && d->K % 4) us += (band ? 0.19e-6 : 0.054e-6) * 4.0 * (double)pl.M * d->K;     // (results value by value)
     return us + SECOND_LAUNCH_US * (apart && !wt_is_packed ? 2 : 1);
 }
 

@@ -48,7 +48,7 @@ struct BandArgs {
     const int8_t *act;  // [N][Cb][Hp][Wp][64]
     const int8_t *wq;   // [K][depth], depth index ((b*R + r)*S + s)*64 + c
     int32_t *out;       // [N][K][P][Q], or [N][P][Q][K] (out_nhwc)
-    int out_nhwc, out_wide_k;    // NHWC result; K % 4 == 0 and out on 16 bytes: a lane's four channels go out as one piece
+    int out_nhwc;                // NHWC result
     ActOut aout;                 // activation epilogue (aout.out != null): `out` is not written
     int K, P, Q, Wp, stride;
     int depth, ksteps, kpw;      // bytes per weight row; 64-byte steps in all and per wave
@@ -383,8 +383,8 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
     constexpr int SLOTS = (2 * PB + BAND_WAVES - 1) / BAND_WAVES;
     // (the direct form writes the NKPQ result only)
     const bool out_nhwc = !DIRECT && a.out_nhwc, activate = !DIRECT && a.aout.out != nullptr;
-    if (SROW > 1 && k_whole && out_nhwc && a.out_wide_k && !activate) {
-        // The same for an NHWC result whose pixels take 16-byte pieces: a lane's four sums are channels k .. k+3 of
+    if (SROW > 1 && k_whole && out_nhwc && !activate) {
+        // The same for an NHWC result, whose pixels' rows begin on any dword: a lane's four sums are channels k .. k+3 of
         // one pixel; 32-bit byte offsets against the image's base.
         v4i sums[SLOTS];
 #pragma unroll
@@ -403,7 +403,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
             const int pr = bdiv_small(pb, a.mg_CTN), q0 = (pb - pr * a.CTN) * a.CT;  // wave-uniform
             const int cols = (i < 2 * PB && pr < a.PT && p0 + pr < a.P) ? min(a.CT, a.Q - q0) : 0;
             const unsigned offb = (unsigned)(((p0 + pr) * a.Q + q0 + col) * a.K + k0 + rb * 16 + 4 * grp) * 4u;
-            if (col < cols) *reinterpret_cast<v4i *>(const_cast<char *>(img) + offb) = sums[m];
+            if (col < cols) *reinterpret_cast<v4i_a4 *>(const_cast<char *>(img) + offb) = sums[m];
         }
         return;
     }
@@ -477,10 +477,10 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
                     act_store4(a.aout, n, pp, qq, k, a.K, sum[0], sum[1], sum[2], sum[3]);
                 } else {
                     int32_t *px = a.out + (((size_t)n * a.P + pp) * a.Q + qq) * a.K + k;
-                    if (a.out_wide_k) *reinterpret_cast<v4i *>(px) = sum;
+                    if (k + 3 < a.K) *reinterpret_cast<v4i_a4 *>(px) = sum;
                     else {
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
+                        for (int v = 0; v < 3; ++v)
                             if (k + v < a.K) px[v] = sum[v];
                     }
                 }
@@ -601,7 +601,6 @@ bool band_plan(const GemmProblem &g, BandPlan *bp, const ResidentProblem *r = nu
         a.mg_RS = magic_of(g.R * g.S);
         a.src_bytes = r->img_bytes * r->N;
     }
-    a.out_wide_k = g.K % 4 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 15) == 0;
     a.aout = ActOut{};
     if (g.act_out) {
         int lg = 0;

@@ -605,13 +605,13 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
         static_assert(LPR4 <= 64 && PR % (NWM * RPS) == 0 && 32 % (NST * RPS) == 0, "a wave's rows belong to one column of waves");
         const int r0 = wave * NST * RPS, mw = m0 + (r0 >> 5) * WTM + (r0 & 31);
         const int kq = k0 + lane % LPR4 * 4;
-        const bool there = kq < a.K;   // (K is a multiple of four)
+        const int left = a.K - kq;   // (rows of K values begin on any dword; PARTS: the last piece may be part of one)
         char *const to0 = reinterpret_cast<char *>(a.out) + ((size_t)mw * a.K + k0) * 4;
         const auto base = past_base(to0);
         const unsigned row = (unsigned)a.K * 4u, off = (unsigned)(lane / LPR4) * row + (unsigned)(lane % LPR4) * 16u;
         const unsigned char *const from = smem + (r0 + lane / LPR4) * PITCH + lane % LPR4 * 16;
         unsigned char *const mine = smem + (wm * 32 + (lane & 31)) * PITCH + (wk * WTK + 4 * (lane >> 5)) * 4;
-        auto passes = [&](auto inside, auto past) {
+        auto passes = [&](auto inside, auto past, auto parts) {
 #pragma unroll
             for (int f = 0; f < FM; ++f) {
                 lds_barrier();   // (the ring is idle: every transfer has landed)
@@ -633,15 +633,23 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
                     }
                     char *const to = to0 + (size_t)(f * 32 + r * RPS) * row;
                     if (decltype(inside)::value) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
-                    else if (there && mw + f * 32 + r * RPS + lane / LPR4 < a.M) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                    else if (mw + f * 32 + r * RPS + lane / LPR4 < a.M) {
+                        if (decltype(parts)::value ? left >= 4 : left > 0) *reinterpret_cast<v4i_a4 *>(to + off) = t[r];
+                        else if constexpr (decltype(parts)::value)
+#pragma unroll
+                            for (int e = 0; e < 3; ++e)
+                                if (e < left) reinterpret_cast<int32_t *>(to + off)[e] = t[r][e];
+                    }
                 }
             }
         };
         const bool inside = k0 + TK <= a.K && m0 + TM <= a.M;   // no test per row
-        if (!inside) passes(std::false_type{}, PastHow<PAST_NONE>{});
-        else if (a.rows == ROWS_THROUGH) passes(std::true_type{}, PastHow<PAST_THROUGH>{});
-        else if (a.rows == ROWS_STREAM) passes(std::true_type{}, PastHow<PAST_STREAM>{});
-        else passes(std::true_type{}, PastHow<PAST_NONE>{});
+        if (!inside) {
+            if (a.K & 3) passes(std::false_type{}, PastHow<PAST_NONE>{}, std::true_type{});
+            else passes(std::false_type{}, PastHow<PAST_NONE>{}, std::false_type{});
+        } else if (a.rows == ROWS_THROUGH) passes(std::true_type{}, PastHow<PAST_THROUGH>{}, std::false_type{});
+        else if (a.rows == ROWS_STREAM) passes(std::true_type{}, PastHow<PAST_STREAM>{}, std::false_type{});
+        else passes(std::true_type{}, PastHow<PAST_NONE>{}, std::false_type{});
         return;
     }
 
@@ -683,7 +691,7 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
     }
     if (a.out_nhwc) {
         // NHWC result: the four values v%4 of a lane are four consecutive channels of one pixel, 16 bytes of
-        // that pixel's channel run (aligned when K % 4 == 0; a depth split adds them one by one)
+        // that pixel's channel run, from any dword on (a depth split adds them one by one)
 #pragma unroll
         for (int jm = 0; jm < FM; ++jm) {
             const int m = m0 + wm * WTM + jm * 32 + (lane & 31);
@@ -700,8 +708,8 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
                             if (k + t < a.K)
                                 __hip_atomic_fetch_add(pix + k + t, acc[i][jm][4 * vg + t], __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT);
-                    } else if (k + 3 < a.K && (a.K & 3) == 0) {
-                        *reinterpret_cast<v4i *>(pix + k) =
+                    } else if (k + 3 < a.K) {
+                        *reinterpret_cast<v4i_a4 *>(pix + k) =
                             v4i{acc[i][jm][4 * vg], acc[i][jm][4 * vg + 1], acc[i][jm][4 * vg + 2], acc[i][jm][4 * vg + 3]};
                     } else {
                         for (int t = 0; t < 4; ++t)
@@ -943,7 +951,7 @@ bool gemm_pick(const GemmProblem &g, int *tile, int *split_k, double *cost)
     int bt = *tile >= 0 ? *tile : 0, bs = *split_k > 0 ? *split_k : 1;
     const double out_bytes = (double)g.M * g.K * (g.act_out ? 1 : 4);
     const double act_bytes = g.mode == ACT_BLOCKED ? (double)g.M / g.PQ * g.Cb * g.cb * g.Hp * g.Wp : (double)g.M * g.depth;
-    const double stored = g.act_out || (!g.out_nhwc && g.PQ % 16 == 0) ? 1.2e-05 : !g.out_nhwc ? 1.67e-05 : g.K % 4 == 0 ? 3.99e-07 : 8.56e-05;
+    const double stored = g.act_out || (!g.out_nhwc && g.PQ % 16 == 0) ? 1.2e-05 : !g.out_nhwc ? 1.67e-05 : 3.99e-07;
     const double added = g.out_nhwc ? 0.000101 : 1.73e-05, summed = g.out_nhwc ? 5.1e-6 : 0.503e-6, setup = g.mode == ACT_BLOCKED ? 0.0788 : 0;
     // slices of the depth and their steps, the same for every tile: empty slices dropped, each number of them once
     int slices[9], pers[9], ncand = 0;
@@ -1046,11 +1054,12 @@ static bool make_gemm_args(const GemmProblem &g, int tile, int split_k, GemmArgs
         // 0.90, the worst 1.00, non-temporal (the line is drawn lower, by the window kernel's), and 7 of 6 to 26 MB another 0.98 written
         // through.  Between the two a result that is written again is still in the last-level cache, and past it takes
         // up to 1.08; there the eight-wave 256 x 256 tiles alone go through LDS into the caches (0.91 to 0.98 on planes of 14 x 14, the
-        // smaller tiles 0.98 to 1.03).  NHWC results of whole 16-byte pieces always: 42 drawn 3 x 3 and 1 x 1 layers, up to 28 MB 0.79 and
+        // smaller tiles 0.98 to 1.03).  NHWC results always, also those whose rows are no whole 16-byte pieces: value by value 256 NHWC layers with K no
+        // multiple of four, of all kernels, took 1.5 times as long (770 images 64 x 11 x 11 -> 349 1x1 110 -> 25 us).  Of whole pieces: 42 drawn 3 x 3 and 1 x 1 layers, up to 28 MB 0.79 and
         // 0.90 of the time, 28 to 256 MB 1.00 and 0.97 (through the caches), above 0.81; the worst 1.007.
         const double bytes = 4.0 * g.M * g.K;
         const bool can = d.large() && !a.act_out && !a.il_d && a.split_k == 1 &&
-                         (a.out_nhwc ? g.K % 4 == 0 && (long long)d.tm * g.K < (1LL << 30) && tile_lds_bytes(d, g.mode, a.ksteps_per_split, ROWS_NHWC) <= kLdsLimit
+                         (a.out_nhwc ? (long long)d.tm * g.K < (1LL << 30) && tile_lds_bytes(d, g.mode, a.ksteps_per_split, ROWS_NHWC) <= kLdsLimit
                                      : g.PQ % 4 == 0 && (d.tm / (long long)g.PQ + 2) * g.PQ * g.K < (1LL << 30));
         const Past past = past_caches(bytes);
         a.rows = !can ? 0 : past == PAST_THROUGH ? ROWS_THROUGH : past == PAST_STREAM ? ROWS_STREAM

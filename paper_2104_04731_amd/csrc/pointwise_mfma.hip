@@ -296,7 +296,12 @@ __global__ void __launch_bounds__(256) conv_pointwise_nhwc_split_kernel(const Po
         sum[3] += t[3];
     }
     const int p = p0 + pix, k = k0 + 4 * cg;
-    if (p < a.M && k < a.K) *reinterpret_cast<v4i *>(a.out + (size_t)p * a.K + k) = sum;   // K % 4 == 0: k + 3 < K
+    if (p >= a.M) return;
+    int32_t *const px = a.out + (size_t)p * a.K + k;   // (any dword)
+    if (k + 3 < a.K) *reinterpret_cast<v4i_a4 *>(px) = sum;
+    else
+        for (int e = 0; e < 3; ++e)
+            if (k + e < a.K) px[e] = sum[e];
 }
 
 // ---- the same layer for large batches: a workgroup owns up to 224 pixels of one image ---------------
@@ -476,13 +481,13 @@ hipError_t launch_nhwc_split(const PointNhwcArgs &a, hipStream_t st)
 
 }  // namespace
 
-// The NHWC split form: whole 128-channel quarters, a result in 16-byte pieces, and a grid of at most two workgroups
+// The NHWC split form: whole 128-channel quarters, and a grid of at most two workgroups
 // per compute unit -- it has no pixels to turn around, so it stays ahead of the general GEMM stage for twice as long
 // as the NCHW split form (14x14 images: C = 512, K = 1024, two images 3.5 against 3.8 us, four 5.4 against 4.3;
 // C = K = 256, eight images 2.6 against 3.2, sixteen level).  Pointers 16-byte aligned (the caller checks).
 bool pointwise_nhwc_split_fits(long long M, int C, int K)
 {
-    return C % 128 == 0 && C <= 512 && K % 4 == 0 && M >= 1 && ((M + 31) / 32) * ((K + 31) / 32) <= 512;
+    return C % 128 == 0 && C <= 512 && M >= 1 && ((M + 31) / 32) * ((K + 31) / 32) <= 512;
 }
 
 hipError_t launch_pointwise_nhwc_split(const int8_t *in, const int8_t *wt, int32_t *out, long long M, int C, int K,

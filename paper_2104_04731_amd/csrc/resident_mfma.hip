@@ -95,10 +95,10 @@ __device__ __forceinline__ void res_store(const ResidentArgs &a, const v16i (&ac
                         const v4i t = {acc[i][f][4 * g], acc[i][f][4 * g + 1], acc[i][f][4 * g + 2], acc[i][f][4 * g + 3]};
                         if (wide) {
                             if (left > 0) *reinterpret_cast<v4i *>(px + i * 32 + 8 * g) = t;
-                        } else {
-                            for (int v = 0; v < 4; ++v)
+                        } else if (left >= 4) *reinterpret_cast<v4i_a4 *>(px + i * 32 + 8 * g) = t;   // (rows of K values begin on any dword)
+                        else
+                            for (int v = 0; v < 3; ++v)
                                 if (v < left) px[i * 32 + 8 * g + v] = t[v];
-                        }
                     }
         }
     } else {
@@ -151,8 +151,9 @@ __device__ __forceinline__ void res_store_piece(const ResidentArgs &a, const v4i
     if (a.out_nhwc) {
         int32_t *px = a.out + (size_t)m * a.K + k;
         if ((a.K & 3) == 0 && (reinterpret_cast<uintptr_t>(a.out) & 15) == 0) *reinterpret_cast<v4i *>(px) = t;
+        else if (left >= 4) *reinterpret_cast<v4i_a4 *>(px) = t;
         else
-            for (int v = 0; v < 4; ++v)
+            for (int v = 0; v < 3; ++v)
                 if (v < left) px[v] = t[v];
     } else {
         const int n = fast_div_any(m, a.PQ, a.mg_PQ), pq = m - n * a.PQ;

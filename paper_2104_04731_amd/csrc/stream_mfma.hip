@@ -536,14 +536,13 @@ __global__ void __launch_bounds__(WK * WM * DS * 64, 2) conv_stream_kernel(const
     // D block (i, f): column = lane%32 (pixel), row = 8*(v/4) + 4*(lane/32) + v%4 (channel); piece = four rows of a block
     constexpr int NP = NM * 4, OWN = NP / DS;
     static_assert(NP % DS == 0, "every depth group finishes the same number of pieces");
-    const bool wide = (a.K & 3) == 0 && (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
     auto store_piece = [&](int x, const v4i &t) {
         const int m = mw + x / 4 % FM * 32 + (lane & 31), k = k0 + wk * FK * 32 + x / (4 * FM) * 32 + x % 4 * 8 + 4 * half, left = a.K - k;
         if (m >= m1 || left <= 0) return;
         int32_t *px = a.out + (size_t)m * a.K + k;
-        if (wide) *reinterpret_cast<v4i *>(px) = t;
+        if ((a.K & 3) == 0 || left >= 4) *reinterpret_cast<v4i_a4 *>(px) = t;   // (rows of K values begin on any dword)
         else
-            for (int v = 0; v < 4; ++v)
+            for (int v = 0; v < 3; ++v)
                 if (v < left) px[v] = t[v];
     };
     auto piece = [&](int x) {

@@ -47,7 +47,6 @@ struct WindowArgs {
     int stride_w, pad_w;   // horizontal stride and padding in bytes of an image row
     int gC, gS, gRS;       // NHWC source: the real channel count, S and R*S of the KCRS weights
     int nhwc;              // NHWC source and result ([N][P][Q][K])
-    int out_wide_k;        // K % 4 == 0 and out 16-byte aligned
     int PT, qshift;        // output rows the waves cover at a time; tile columns QT = 32 << qshift, PT << qshift = 4
     int G;                 // how often they do: a tile has PT * G output rows
     int RW;                // window rows per channel: (PT*G-1)*stride + R
@@ -342,7 +341,7 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
             }
             return;
         }
-        if (NHWC && a.out_wide_k) {
+        if (NHWC) {
             // a lane's v%4 are channels k .. k+3 of its pixel: each wave lays its 32 pixels x KB channels out in LDS
             // as the result has them ([pixel][channel], rows of KB + 4 dwords) and stores 16-byte pieces with the
             // pieces of a pixel in consecutive lanes -- the channel runs of consecutive pixels follow each other in
@@ -358,29 +357,19 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
                         v4i{acc[kb][4 * vg], acc[kb][4 * vg + 1], acc[kb][4 * vg + 2], acc[kb][4 * vg + 3]};
             __builtin_amdgcn_wave_barrier();  // LDS serves a wave's accesses in order
             const int p = pr, pc = lane % CPP, px0 = lane / CPP;
-            if (p >= aP || k0 + 4 * pc >= aK) return;
+            const int left = aK - (k0 + 4 * pc);
+            if (p >= aP || left <= 0) return;
             int32_t *row = outn + ((size_t)p * aQ) * aK + k0 + 4 * pc;
 #pragma unroll
             for (int j = 0; j < CPP / 2; ++j) {
                 const int px = px0 + j * (64 / CPP), q = q0 + qw * 32 + px;
                 const v4i t = *reinterpret_cast<const v4i *>(T + px * TPITCH + 4 * pc);
-                if (q < aQ) *reinterpret_cast<v4i *>(row + (size_t)q * aK) = t;
+                if (q >= aQ) continue;
+                if ((aK & 3) == 0 || left >= 4) *reinterpret_cast<v4i_a4 *>(row + (size_t)q * aK) = t;   // (rows of K values begin on any dword)
+                else
+                    for (int e = 0; e < 3; ++e)
+                        if (e < left) row[(size_t)q * aK + e] = t[e];
             }
-            return;
-        }
-        if (NHWC) {   // results that do not start on 16 bytes, or K % 4 != 0: one by one
-            const int p = pr, q = q0 + qw * 32 + l31;
-            if (p >= aP || q >= aQ) return;
-            int32_t *px = outn + ((size_t)p * aQ + q) * aK;
-#pragma unroll
-            for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                for (int vg = 0; vg < 4; ++vg) {
-                    const int k = k0 + kb * 32 + 8 * vg + 4 * half;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (k + j < aK) px[k + j] = acc[kb][4 * vg + j];
-                }
             return;
         }
         if (PAST != PAST_NONE || a.wide_out) {
@@ -513,7 +502,6 @@ static bool window_plan(const WindowProblem &g, WindowArgs *a)
     w.gC = g.C; w.gS = g.S; w.gRS = g.R * g.S;
     w.m_gC = magic_for(g.C);
     w.nhwc = g.nhwc;
-    w.out_wide_k = g.K % 4 == 0 && (reinterpret_cast<uintptr_t>(g.out) & 15) == 0;
     w.qshift = g.Q > 64 ? 2 : g.Q > 32 ? 1 : 0;
     w.PT = 4 >> w.qshift;
     const int QT = 32 << w.qshift;

