@@ -472,7 +472,7 @@ __global__ void __launch_bounds__(BAND_WAVES * 64, 1) conv_band_kernel(const Ban
                 pp = p0 + pr, qq = px - pr * a.Q;
             }
             const int k = k0 + rb * 16 + 4 * grp;
-            if (valid && k < a.K) {
+            if (valid && (activate || k < a.K)) {
                 if (activate) {
                     act_store4(a.aout, n, pp, qq, k, a.K, sum[0], sum[1], sum[2], sum[3]);
                 } else {

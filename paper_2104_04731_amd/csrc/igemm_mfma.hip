@@ -672,18 +672,14 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
 #pragma unroll
                 for (int vg = 0; vg < 4; ++vg) {
                     const int k = k0 + wk * WTK + i * 32 + 8 * vg + 4 * (lane >> 5);
-                    if (k >= a.K) continue;
-                    int y[4];
+                    if (k >= a.o_Cb << a.o_cb_log2) continue;
+                    int y[4];   // (channels from K on are zeros, up to the last block's end)
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) y[t] = act_requant(acc[i][jm][4 * vg + t], a.act_shift, a.act_relu);
+                    for (int t = 0; t < 4; ++t) y[t] = k + t < a.K ? act_requant(acc[i][jm][4 * vg + t], a.act_shift, a.act_relu) : 0;
                     int8_t *dst = a.act_out + ((((size_t)n * a.o_Cb + (k >> a.o_cb_log2)) * plane + pix) << a.o_cb_log2) +
                                   (k & (o_cb - 1));
-                    if (k + 3 < a.K)
-                        *reinterpret_cast<unsigned *>(dst) = (unsigned)(y[0] & 0xFF) | (unsigned)(y[1] & 0xFF) << 8 |
-                                                             (unsigned)(y[2] & 0xFF) << 16 | (unsigned)(y[3] & 0xFF) << 24;
-                    else
-                        for (int t = 0; t < 4; ++t)
-                            if (k + t < a.K) dst[t] = (int8_t)y[t];
+                    *reinterpret_cast<unsigned *>(dst) = (unsigned)(y[0] & 0xFF) | (unsigned)(y[1] & 0xFF) << 8 |
+                                                         (unsigned)(y[2] & 0xFF) << 16 | (unsigned)(y[3] & 0xFF) << 24;
                 }
             }
         }

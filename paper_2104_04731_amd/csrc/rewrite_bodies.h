@@ -51,18 +51,15 @@ __device__ __forceinline__ int fast_div_any(int n, int d, unsigned magic)
     return q;
 }
 // Four consecutive output channels k .. k+3 of pixel (n, p, q) -- what one lane holds in v%4 of an MFMA
-// result block -- activated and stored as one dword of the blocked tensor (bytes past channel K-1 are not written).
+// result block -- activated and stored as one dword of the blocked tensor; channels from K on are zeros, up to the last block's end.
 __device__ __forceinline__ void act_store4(const ActOut &e, int n, int p, int q, int k, int K, int x0, int x1, int x2, int x3)
 {
-    if (k >= K) return;
+    if (k >= e.Cb << e.cb_log2) return;
     const size_t pix = ((size_t)n * e.Cb + (k >> e.cb_log2)) * e.Hp * e.Wp + (size_t)(p + e.pad) * e.Wp + (q + e.pad);
     int8_t *dst = e.out + (pix << e.cb_log2) + (k & ((1 << e.cb_log2) - 1));
     const int y[4] = {act_requant(x0, e.shift, e.relu), act_requant(x1, e.shift, e.relu), act_requant(x2, e.shift, e.relu),
                       act_requant(x3, e.shift, e.relu)};
-    if (k + 3 < K) *reinterpret_cast<unsigned *>(dst) = pack4(y[0], y[1], y[2], y[3]);
-    else
-        for (int t = 0; t < 4; ++t)
-            if (k + t < K) dst[t] = (int8_t)y[t];
+    *reinterpret_cast<unsigned *>(dst) = pack4(k < K ? y[0] : 0, k + 1 < K ? y[1] : 0, k + 2 < K ? y[2] : 0, k + 3 < K ? y[3] : 0);
 }
 
 __device__ __forceinline__ unsigned magic_for_device(int d)  // the same constant, made on the device

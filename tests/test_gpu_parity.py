@@ -1955,3 +1955,25 @@ def test_nhwc_rows_that_begin_on_any_dword(lib, K):
     x1 = uniform_int8(999, (2, 128, 9, 5)); w1 = uniform_int8(1000, (K, 128, 1, 1))   # a 1x1 layer on a small grid: the depth split over the waves
     got = lib.conv2d_int8_nhwc(dev(np.ascontiguousarray(x1.transpose(0, 2, 3, 1))), dev(w1), 1, 0)
     assert np.array_equal(host(got), layouts.unpack_nhwc(direct.conv2d_int8(x1, w1, 1, 0)))
+
+
+@pytest.mark.parametrize("K", [1, 17, 33, 50, 70, 130])
+def test_fused_activation_fills_its_last_block(lib, K):
+    """Channels that the last block lacks come out zero, whichever kernel writes it, over whatever the output held; nothing beside it."""
+    shapes = [((2, 256, 7, 7, K, 3, 3, 1, 1), "PACKED"), ((40, 64, 14, 14, K, 3, 3, 1, 1), "PACKED"), ((3, 48, 9, 9, K, 1, 1, 1, 0), "PACKED"),
+              ((2, 3, 20, 20, K, 5, 5, 2, 2), "IMPLICIT"), ((2, 64, 8, 8, K, 1, 1, 1, 0), "IMPLICIT")]
+    for dims, layout in shapes:
+        N, C, H, W, _, R, S, stride, pad = dims
+        x = uniform_int8(1001, (N, C, H, W)); w = uniform_int8(1002, (K, C, R, S))
+        act = layouts.requant(direct.conv2d_int8(x, w, stride, pad), 9, False)
+        lay, cb = (lib.LAYOUT_IMPLICIT, 0) if layout == "IMPLICIT" else (lib.LAYOUT_PACKED, 64 if C > 32 else 16)
+        wq = lib.pack_weights(dev(w), lay, cb)
+        xq = dev(x) if layout == "IMPLICIT" else lib.pack_layout(dev(x), cb, pad)
+        for out_cb in (16, 32, 64):
+            for out_pad in (0, 1):
+                want = layouts.pack_layout(act, out_cb, out_pad)
+                buf = torch.full((want.size + 128,), 85, dtype=torch.int8, device=DEV)
+                lib.conv2d_int8_packed_requant(dims, lay, cb, xq, wq, out_cb, out_pad, 9, False, out=buf[64:64 + want.size].view(want.shape))
+                got = host(buf)
+                assert np.array_equal(got[64:-64].reshape(want.shape), want), (dims, layout, out_cb, out_pad)
+                assert (got[:64] == 85).all() and (got[-64:] == 85).all()
