@@ -656,8 +656,7 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
     // Epilogue: D block (i, jm): column = lane%32 (pixel), row = 8*(v/4) + 4*(lane/32) + v%4.
     // Consecutive lanes write consecutive pixels of one output plane: 128-byte runs in NKPQ.
     if constexpr (ROWS == ROWS_ACT) {
-        // Fused activation: the four values v%4 of a lane are four consecutive output channels of one
-        // pixel -- one dword of that pixel's channel-contiguous run in the next layer's blocked input.
+        // Fused activation: the two lanes of a pixel store 16 channels of its run in the next layer's blocked input each.
         const int o_cb = 1 << a.o_cb_log2;
 #pragma unroll
         for (int jm = 0; jm < FM; ++jm) {
@@ -669,18 +668,10 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
             const size_t plane = (size_t)a.o_Hp * a.o_Wp;
 #pragma unroll
             for (int i = 0; i < FK; ++i) {
-#pragma unroll
-                for (int vg = 0; vg < 4; ++vg) {
-                    const int k = k0 + wk * WTK + i * 32 + 8 * vg + 4 * (lane >> 5);
-                    if (k >= a.o_Cb << a.o_cb_log2) continue;
-                    int y[4];   // (channels from K on are zeros, up to the last block's end)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) y[t] = k + t < a.K ? act_requant(acc[i][jm][4 * vg + t], a.act_shift, a.act_relu) : 0;
-                    int8_t *dst = a.act_out + ((((size_t)n * a.o_Cb + (k >> a.o_cb_log2)) * plane + pix) << a.o_cb_log2) +
-                                  (k & (o_cb - 1));
-                    *reinterpret_cast<unsigned *>(dst) = (unsigned)(y[0] & 0xFF) | (unsigned)(y[1] & 0xFF) << 8 |
-                                                         (unsigned)(y[2] & 0xFF) << 16 | (unsigned)(y[3] & 0xFF) << 24;
-                }
+                const int kb = k0 + wk * WTK + i * 32, k = kb + 16 * (lane >> 5);
+                const v4i y = act_block16(acc[i][jm], a.K - kb, lane, a.act_shift, a.act_relu);   // (channels from K on are zeros, up to the last block's end)
+                if (k < a.o_Cb << a.o_cb_log2)
+                    *reinterpret_cast<v4i *>(a.act_out + ((((size_t)n * a.o_Cb + (k >> a.o_cb_log2)) * plane + pix) << a.o_cb_log2) + (k & (o_cb - 1))) = y;
             }
         }
         return;

@@ -1024,8 +1024,7 @@ __global__ void __launch_bounds__(256) requant_kernel(const int32_t *src, int8_t
             for (int j = 0; j < 4; ++j) {
                 v4i x;
                 __builtin_memcpy(&x, src + e0 + 4 * j, 16);
-                o[j] = (int)pack4(act_requant(x[0], shift, relu), act_requant(x[1], shift, relu), act_requant(x[2], shift, relu),
-                                  act_requant(x[3], shift, relu));
+                o[j] = (int)act_requant4(x[0], x[1], x[2], x[3], shift, relu);
             }
             __builtin_memcpy(dst + e0, &o, 16);
         } else {
@@ -1069,14 +1068,13 @@ __global__ void __launch_bounds__(256) requant_pack_kernel(const RequantPackArgs
         v4i o = {0, 0, 0, 0};
         if (p >= 0 && p < a.P && q >= 0 && q < a.Q && k0 < a.K) {
             const int32_t *s = a.src + ((size_t)n * a.K + k0) * PQ + (size_t)p * a.Q + q;
-            int x[16], v[16];
+            int x[16];
             // all sixteen loads first (channels past K re-read the last one: no branch between the loads)
 #pragma unroll
             for (int i = 0; i < 16; ++i) x[i] = s[(size_t)min(i, a.K - 1 - k0) * PQ];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = k0 + i < a.K ? act_requant(x[i], a.shift, a.relu) : 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) o[j] = (int)pack4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
+            for (int j = 0; j < 4; ++j)
+                o[j] = (int)act_keep(act_requant4(x[4 * j], x[4 * j + 1], x[4 * j + 2], x[4 * j + 3], a.shift, a.relu), a.K - k0 - 4 * j);
         }
         reinterpret_cast<v4i *>(a.dst)[t] = o;
     }

@@ -130,10 +130,7 @@ __global__ void __launch_bounds__(256) conv_pointwise_kernel(const PointArgs a)
     if (ACT) {
         if (p < a.HW) {
             const int py = fast_div_any(p, a.W, a.m_W), qx = p - py * a.W;
-#pragma unroll
-            for (int vg = 0; vg < 4; ++vg)
-                act_store4(a.act, n, py, qx, k0 + 8 * vg + 4 * half, a.K, acc[4 * vg], acc[4 * vg + 1], acc[4 * vg + 2],
-                           acc[4 * vg + 3]);
+            act_store32(a.act, n, py, qx, k0, a.K, lane, acc);
         }
     } else if (p < a.HW) {
         int32_t *base = a.out + ((size_t)n * a.K + k0 + 4 * half) * a.HW + p;
@@ -408,10 +405,7 @@ __global__ void __launch_bounds__(256) conv_pointwise_image_kernel(const PointIm
         for (int b = 0; b < IMG_PXB; ++b) {
             if (32 * b + l31 < npx) {
                 const int p = px0 + 32 * b + l31, py = fast_div_any(p, a.W, a.m_W), qx = p - py * a.W;
-#pragma unroll
-                for (int vg = 0; vg < 4; ++vg)
-                    act_store4(a.act, n, py, qx, k0 + 8 * vg + 4 * half, a.K, acc[b][4 * vg], acc[b][4 * vg + 1],
-                               acc[b][4 * vg + 2], acc[b][4 * vg + 3]);
+                act_store32(a.act, n, py, qx, k0, a.K, lane, acc[b]);
             }
         }
         return;

@@ -57,9 +57,16 @@ __device__ __forceinline__ void act_store4(const ActOut &e, int n, int p, int q,
     if (k >= e.Cb << e.cb_log2) return;
     const size_t pix = ((size_t)n * e.Cb + (k >> e.cb_log2)) * e.Hp * e.Wp + (size_t)(p + e.pad) * e.Wp + (q + e.pad);
     int8_t *dst = e.out + (pix << e.cb_log2) + (k & ((1 << e.cb_log2) - 1));
-    const int y[4] = {act_requant(x0, e.shift, e.relu), act_requant(x1, e.shift, e.relu), act_requant(x2, e.shift, e.relu),
-                      act_requant(x3, e.shift, e.relu)};
-    *reinterpret_cast<unsigned *>(dst) = pack4(k < K ? y[0] : 0, k + 1 < K ? y[1] : 0, k + 2 < K ? y[2] : 0, k + 3 < K ? y[3] : 0);
+    *reinterpret_cast<unsigned *>(dst) = act_keep(act_requant4(x0, x1, x2, x3, e.shift, e.relu), K - k);
+}
+// The 32 channels from k on of a 32 x 32 result, two pieces of 16 bytes (act_block16).
+__device__ __forceinline__ void act_store32(const ActOut &e, int n, int p, int q, int k, int K, int lane, const int __attribute__((ext_vector_type(16))) &d)
+{
+    const auto y = act_block16(d, K - k, lane, e.shift, e.relu);
+    k += 16 * (lane >> 5);
+    if (k >= e.Cb << e.cb_log2) return;
+    const size_t pix = ((size_t)n * e.Cb + (k >> e.cb_log2)) * e.Hp * e.Wp + (size_t)(p + e.pad) * e.Wp + (q + e.pad);
+    *reinterpret_cast<v4i *>(e.out + (pix << e.cb_log2) + (k & ((1 << e.cb_log2) - 1))) = y;
 }
 
 __device__ __forceinline__ unsigned magic_for_device(int d)  // the same constant, made on the device

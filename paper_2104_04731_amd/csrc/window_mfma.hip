@@ -333,11 +333,7 @@ __global__ void __launch_bounds__(256, 4) conv_window_kernel(const WindowArgs a)
             const int p = pr, q = q0 + qw * 32 + l31;
             if (p < aP && q < aQ) {
 #pragma unroll
-                for (int kb = 0; kb < NKB; ++kb)
-#pragma unroll
-                    for (int vg = 0; vg < 4; ++vg)
-                        act_store4(a.act, n, p, q, k0 + kb * 32 + 8 * vg + 4 * half, aK, acc[kb][4 * vg], acc[kb][4 * vg + 1],
-                                   acc[kb][4 * vg + 2], acc[kb][4 * vg + 3]);
+                for (int kb = 0; kb < NKB; ++kb) act_store32(a.act, n, p, q, k0 + kb * 32, aK, lane, acc[kb]);
             }
             return;
         }

@@ -1977,3 +1977,21 @@ def test_fused_activation_fills_its_last_block(lib, K):
                 got = host(buf)
                 assert np.array_equal(got[64:-64].reshape(want.shape), want), (dims, layout, out_cb, out_pad)
                 assert (got[:64] == 85).all() and (got[-64:] == 85).all()
+
+
+@pytest.mark.parametrize("relu", [False, True])
+def test_requant_at_the_ends_of_int32(lib, relu):
+    """Every shift, where rounding, the clip to int8 and the sum's range meet (a sum that left 32 bits would come out on the other side)."""
+    edges = {0, 1, 2, -1, -2, 2**31 - 1, 2**31 - 2, -2**31, -2**31 + 1}
+    for e in range(31):
+        for d in (-1, 0, 1):
+            edges |= {2**e + d, -2**e + d, 127 * 2**e + d, -128 * 2**e + d, 2**31 - 2**e + d, 255 * 2**e // 2 + d, -257 * 2**e // 2 + d}
+    x = np.array(sorted(v for v in edges if -2**31 <= v < 2**31), dtype=np.int64)
+    x = np.concatenate([x, x[:-x.size % 16 + 5]])   # (a ragged end: that many go one by one)
+    for shift in range(32):
+        v = (x + (1 << shift >> 1)) >> shift
+        want = np.clip(np.maximum(v, 0) if relu else v, -128, 127).astype(np.int8)
+        np.testing.assert_array_equal(host(lib.requant_int8(dev(x.astype(np.int32)), shift, relu)), want, err_msg=f"shift {shift}")
+        nkpq = np.ascontiguousarray(x[:x.size // 21 * 21].reshape(1, 21, -1, 1))
+        got = host(lib.requant_pack_layout(dev(nkpq.astype(np.int32)), 16, 1, shift, relu))
+        np.testing.assert_array_equal(got, layouts.pack_layout(want[:nkpq.size].reshape(nkpq.shape), 16, 1), err_msg=f"blocked, shift {shift}")
