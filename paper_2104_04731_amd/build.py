@@ -10,7 +10,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libconv2d_int8.so")
 SOURCES = ["api.cpp", "selector.cpp", "igemm_mfma.hip", "band_mfma.hip", "resident_mfma.hip", "stream_mfma.hip", "layout_kernels.hip", "window_mfma.hip", "stencil_mfma.hip",
            "panel_mfma.hip", "pointwise_mfma.hip"]
-HEADERS = [os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "rewrite_bodies.h"), os.path.join(CSRC, "act_requant.h"), os.path.join(CSRC, "desc_check.h"), os.path.join(CSRC, "launch.h"), os.path.join(CSRC, "store_past.h"), os.path.join(CSRC, "panel_fill.h"), os.path.join(CSRC, "window_fill.h"), os.path.join(CSRC, "window_walk.h"),
+HEADERS = [os.path.join(CSRC, "kernels.h"), os.path.join(CSRC, "rewrite_bodies.h"), os.path.join(CSRC, "act_requant.h"), os.path.join(CSRC, "act_store.h"), os.path.join(CSRC, "desc_check.h"), os.path.join(CSRC, "launch.h"), os.path.join(CSRC, "store_past.h"), os.path.join(CSRC, "panel_fill.h"), os.path.join(CSRC, "window_fill.h"), os.path.join(CSRC, "window_walk.h"),
            os.path.join(os.path.dirname(PKG), "include", "conv2d_int8.h")]
 
 NATIVE_SOURCE = "py_native.cpp"                    # the Python side of the tensor-taking calls: host code, no kernels

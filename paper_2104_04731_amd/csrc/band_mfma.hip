@@ -26,6 +26,7 @@
 //     wave w adds up and stores every fourth 16 x 16 block, straight to NKPQ.
 // Both LDS operands are XOR-swizzled per 64-byte row ((row/4)%4 on the 16-byte chunk index), done
 // by the lanes' choice of source chunk, so the column-wise fragment reads spread over all banks.
+#include "act_store.h"
 #include "kernels.h"
 #include "launch.h"
 #include "window_fill.h"

@@ -17,7 +17,7 @@
 // The activation row of pixel m is addressed as rowbase(m) + koff[chunk]: for the blocked
 // layout koff walks (channel block, r, s) over the zero-padded image (implicit GEMM, no
 // unrolled matrix in memory); for a row-major matrix (im2col output) it is 16*chunk.
-#include "act_requant.h"
+#include "act_store.h"
 #include "kernels.h"
 #include "launch.h"
 #include "store_past.h"

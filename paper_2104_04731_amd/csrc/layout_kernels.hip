@@ -1,6 +1,7 @@
 // Layout rewrites of Table 2 as bandwidth-bound copy kernels: every destination byte
 // (zero padding included) is written exactly once, in 16-byte pieces, and source reads run
 // along the contiguous W axis across the lanes of a wave.
+#include "act_store.h"
 #include "kernels.h"
 #include "launch.h"
 #include "rewrite_bodies.h"

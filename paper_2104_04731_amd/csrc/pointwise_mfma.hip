@@ -17,6 +17,7 @@
 // than one tile keeps its weight operands and fetches the next tile's pixels during the current one.
 // Two more forms of the same layer follow it: one for grids too small to fill the chip (a workgroup of 32 pixels x 32
 // output channels whose waves share the depth) and one for large batches (a workgroup owns 224 pixels of an image).
+#include "act_store.h"
 #include "kernels.h"
 #include "launch.h"
 #include "rewrite_bodies.h"

@@ -1,7 +1,6 @@
 // Device bodies of the layout rewrites that more than one kernel uses (the stand-alone rewrite kernels and the
 // two-rewrites-in-one-launch kernel), with the host helpers that fill their argument blocks.
 #pragma once
-#include "act_requant.h"
 #include "kernels.h"
 
 namespace c2i8 {
@@ -50,25 +49,6 @@ __device__ __forceinline__ int fast_div_any(int n, int d, unsigned magic)
     if ((long long)q * d > n) --q;
     return q;
 }
-// Four consecutive output channels k .. k+3 of pixel (n, p, q) -- what one lane holds in v%4 of an MFMA
-// result block -- activated and stored as one dword of the blocked tensor; channels from K on are zeros, up to the last block's end.
-__device__ __forceinline__ void act_store4(const ActOut &e, int n, int p, int q, int k, int K, int x0, int x1, int x2, int x3)
-{
-    if (k >= e.Cb << e.cb_log2) return;
-    const size_t pix = ((size_t)n * e.Cb + (k >> e.cb_log2)) * e.Hp * e.Wp + (size_t)(p + e.pad) * e.Wp + (q + e.pad);
-    int8_t *dst = e.out + (pix << e.cb_log2) + (k & ((1 << e.cb_log2) - 1));
-    *reinterpret_cast<unsigned *>(dst) = act_keep(act_requant4(x0, x1, x2, x3, e.shift, e.relu), K - k);
-}
-// The 32 channels from k on of a 32 x 32 result, two pieces of 16 bytes (act_block16).
-__device__ __forceinline__ void act_store32(const ActOut &e, int n, int p, int q, int k, int K, int lane, const int __attribute__((ext_vector_type(16))) &d)
-{
-    const auto y = act_block16(d, K - k, lane, e.shift, e.relu);
-    k += 16 * (lane >> 5);
-    if (k >= e.Cb << e.cb_log2) return;
-    const size_t pix = ((size_t)n * e.Cb + (k >> e.cb_log2)) * e.Hp * e.Wp + (size_t)(p + e.pad) * e.Wp + (q + e.pad);
-    *reinterpret_cast<v4i *>(e.out + (pix << e.cb_log2) + (k & ((1 << e.cb_log2) - 1))) = y;
-}
-
 __device__ __forceinline__ unsigned magic_for_device(int d)  // the same constant, made on the device
 {
     return d == 1 ? 0u : (unsigned)(0xFFFFFFFFu / (unsigned)d) + 1u;

@@ -28,6 +28,7 @@
 // row of S*C bytes, a horizontal stride of stride*C and pad*C bytes of horizontal padding.  The depth order
 // is then (r, s, c); the KCRS weight rows are copied into LDS as they are and brought into that order there.
 // A lane's four results are four consecutive channels of a pixel, which is what an NHWC result stores.
+#include "act_store.h"
 #include "kernels.h"
 #include "launch.h"
 #include "store_past.h"
