@@ -280,6 +280,11 @@ int conv2d_int8_packed_requant(const conv_desc_t *desc, int layout, int cb,
                                const int8_t *in_packed, const int8_t *wt_packed, int8_t *out_blocked,
                                int out_cb, int out_pad, int shift, int relu, void *stream);
 
+/* The same with the stage named: tile, pixels as for conv2d_int8_resident, whose stage then reads in_packed (cb a power of two;
+ * CONV_ERR_UNSUPPORTED where it does not apply), or -1 and 0 for conv2d_int8_packed's. */
+int conv2d_int8_resident_requant(const conv_desc_t *desc, int layout, int cb, const int8_t *in_packed, const int8_t *wt_packed,
+                                 int8_t *out_blocked, int out_cb, int out_pad, int shift, int relu, int tile, int pixels, void *stream);
+
 /* Tensor unpacking for an NHWC consumer (the last step of the benchmark of Sec. 5.1 in the layout
  * of Sec. 5.2): dst[n][p][q][k] = src[n][k][p][q], int32. */
 int unpack_nhwc_int32(int N, int K, int P, int Q, const int32_t *src, int32_t *dst, void *stream);

@@ -39,7 +39,7 @@ EXPORTS = [
     "conv2d_int8_dilated_direct_workspace_bytes", "conv2d_int8_dilated_direct",
     "gemm_int8_nt", "select_layout", "select_layout_weighted", "layout_overheads",
     "conv_status_string", "conv2d_int8_resident", "conv2d_int8_resident_applies", "conv2d_int8_resident_tile_info",
-    "conv2d_int8_query_stage", "conv2d_int8_stored", "conv2d_int8_panel", "conv2d_int8_panel_workspace_bytes", "conv2d_int8_panel_tile_info",
+    "conv2d_int8_query_stage", "conv2d_int8_stored", "conv2d_int8_resident_requant", "conv2d_int8_panel", "conv2d_int8_panel_workspace_bytes", "conv2d_int8_panel_tile_info",
 ]
 
 
@@ -116,6 +116,7 @@ def load(path: str | None = None):
         "image_pack_int8": (i, [dp, vp, vp, vp]),
         "image_pack_weights": (i, [dp, vp, vp, vp]),
         "conv2d_int8_packed_requant": (i, [dp, i, i, vp, vp, vp, i, i, i, i, vp]),
+        "conv2d_int8_resident_requant": (i, [dp, i, i, vp, vp, vp, i, i, i, i, i, i, vp]),
         "conv2d_int8_packed_nhwc": (i, [dp, i, i, vp, vp, vp, i, i, vp]),
         "dilated_desc": (i, [dp, i, dp]),
         "dilation_pack_bytes": (sz, [dp, i]),
@@ -274,6 +275,16 @@ def conv2d_int8_resident(dims, x: torch.Tensor, w: torch.Tensor, out: torch.Tens
     _require(x, torch.int8, "input"); _require(w, torch.int8, "weights"); _require(out, torch.int32, "output")
     _check(load().conv2d_int8_resident(ctypes.byref(_desc(*dims)), dilation, int(nhwc), _ptr(x), _ptr(w), wt_cb, _ptr(out), tile, pixels,
                                        _stream(stream)), "conv2d_int8_resident")
+    return out
+
+
+def conv2d_int8_resident_requant(dims, layout, cb, x_packed: torch.Tensor, w_packed: torch.Tensor, out_cb, out_pad, shift, relu, out: torch.Tensor,
+                                 tile: int, pixels: int, stream=None):
+    """conv2d_int8_packed_requant through that stage, with this tile and pixels per workgroup (-1, 0: conv2d_int8_packed's stages)."""
+    for t, what in ((x_packed, "input"), (w_packed, "weights"), (out, "output")):
+        _require(t, torch.int8, what)
+    _check(load().conv2d_int8_resident_requant(ctypes.byref(_desc(*dims)), layout, cb, _ptr(x_packed), _ptr(w_packed), _ptr(out), out_cb, out_pad, shift,
+                                               int(relu), tile, pixels, _stream(stream)), "conv2d_int8_resident_requant")
     return out
 
 

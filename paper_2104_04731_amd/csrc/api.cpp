@@ -379,6 +379,52 @@ ResidentProblem resident_problem(const conv_desc_t *d, const Plan &pl, int cb, i
     return r;
 }
 
+// The layer of g, a GEMM stage with its activation, on the blocked image that g reads.
+ResidentProblem blocked_problem(const conv_desc_t *d, const GemmProblem &g)
+{
+    ResidentProblem r{};
+    r.g = g;
+    r.src = g.act;
+    r.N = d->N, r.C = d->C, r.H = g.Hp, r.W = g.Wp, r.pad = 0;
+    r.pixel_major = r.blocked = r.kept = 1;
+    r.pixel_bytes = g.cb;
+    r.img_bytes = (long long)g.Cb * g.Hp * g.Wp * g.cb;
+    return r;
+}
+
+// Whether the resident kernel takes it.  The estimates of the other stages know the int32 result only: refitted to two thirds of 2540 fused activations
+// (mean error 9.5 % band, 7 % general).  Of the 847 others the 92 where this kernel's own estimate is below 0.85 of that take all of them
+// to 0.964 of the time (0.80 where the channels are 64 at most and the launch above 10 us; the best of both would be 0.94), none more than 3 % slower; below 0.95 of it:
+// 0.959, 12 slower, one of them by half.  What it saves is the R S fetches of every activation: 64 images 64 x 56 x 56 -> 64, 3x3: 24.0 -> 14.7 us;
+// 192 images 128 x 35 x 35 -> 17: 37 -> 22.  Not 1x1 layers with a stride: the window holds the pixels in between, and no fetch is saved (877 images
+// 32 x 56 x 56 -> 46, stride 2: 33.4 -> 41.5); nor those of more than 64 channels out, whose windows are filled once per tile of channels (218 layers that
+// differ 0.976 in the mean, 22 slower, up to 1.15; up to 64 channels 225 layers 0.80).
+bool choose_blocked(const ResidentProblem &r, ResidentChoice *pick)
+{
+    struct Kept {
+        ResidentChoice pick;
+        bool takes;
+    };
+    struct Key {
+        GemmKey g;
+        int C;
+    };
+    static thread_local PlanTable<Key, Kept, 64> chosen;
+    const Kept *kept = chosen.get(Key{gemm_key(r.g), r.C}, [&](Kept *n) {
+        GemmChoice c;
+        WindowWalk walk = window_walk(r);
+        *n = Kept{};
+        n->takes = r.g.mode == ACT_BLOCKED && !(r.g.R * r.g.S == 1 && (r.g.stride > 1 || r.g.K > 64)) && resident_pick(r, walk, &n->pick);
+        if (n->takes && choose_gemm_unsplit(r.g, &c) == CONV_OK) {
+            const double results = (double)r.g.M * r.g.K;
+            n->takes = n->pick.us < 0.85 * (c.tile == CONV_TILE_BAND ? 1.17 * c.cost - 1.75 : 1.089 * c.cost - 1.86 - 1.92e-8 * results);
+        }
+        return true;
+    });
+    if (kept && kept->takes) *pick = kept->pick;
+    return kept && kept->takes;
+}
+
 struct RouteKey {
     conv_desc_t d;
     int v[8];
@@ -1070,9 +1116,10 @@ int conv2d_int8_packed_nhwc(const conv_desc_t *desc, int layout, int cb, const i
     return run_gemm(g, tile, split_k, (hipStream_t)stream);
 }
 
-int conv2d_int8_packed_requant(const conv_desc_t *desc, int layout, int cb, const int8_t *in_packed,
-                               const int8_t *wt_packed, int8_t *out_blocked, int out_cb, int out_pad, int shift, int relu,
-                               void *stream)
+// how: REQUANT_CHOOSE, REQUANT_STORED (the GEMM stages of conv2d_int8_packed), or a tile of the resident kernel with its pixels.
+enum : int { REQUANT_STORED = -1, REQUANT_CHOOSE = -2 };
+static int packed_requant(const conv_desc_t *desc, int layout, int cb, const int8_t *in_packed, const int8_t *wt_packed, int8_t *out_blocked, int out_cb,
+                          int out_pad, int shift, int relu, int how, int pixels, void *stream)
 {
     if (layout == CONV_LAYOUT_AUTO) return CONV_ERR_INVALID_ARG;
     Plan pl;
@@ -1093,6 +1140,7 @@ int conv2d_int8_packed_requant(const conv_desc_t *desc, int layout, int cb, cons
         return launch_fill_zero(out_blocked, (size_t)desc->N * (size_t)Cbq * (size_t)Hq * (size_t)Wq * (size_t)out_cb, st);
     };
     if (implicit) {
+        if (how >= 0) return CONV_ERR_UNSUPPORTED;
         if (clear(pl.pointwise || desc->K <= 32 ? 32 : 64) != hipSuccess) return CONV_ERR_DEVICE;
         WindowProblem wp = window_problem(desc, pl, in_packed, wt_packed, nullptr, 1);
         int lg = 0;
@@ -1106,11 +1154,33 @@ int conv2d_int8_packed_requant(const conv_desc_t *desc, int layout, int cb, cons
     g.act_relu = relu != 0;
     g.o_cb = out_cb;
     g.o_pad = out_pad;
+    if (how != REQUANT_STORED) {
+        const ResidentProblem r = blocked_problem(desc, g);
+        ResidentChoice pick{how, pixels, 0};
+        if (how >= 0 && !resident_applies(r, how, pixels)) return CONV_ERR_UNSUPPORTED;
+        if (how >= 0 || choose_blocked(r, &pick)) {
+            if (clear(resident_tile_info(pick.tile).rows) != hipSuccess) return CONV_ERR_DEVICE;
+            return gemm_status(how >= 0 ? launch_resident_forced(r, pick.tile, pick.mper, st) : launch_resident(r, pick, st));
+        }
+    }
     GemmChoice c;
     rc = choose_gemm_unsplit(g, &c);
     if (rc != CONV_OK) return rc;
     if (clear((c.tile == CONV_TILE_BAND ? band_tile_info(g) : gemm_tile_info(c.tile)).rows) != hipSuccess) return CONV_ERR_DEVICE;
     return launch_choice(g, c, st);
+}
+
+int conv2d_int8_packed_requant(const conv_desc_t *desc, int layout, int cb, const int8_t *in_packed, const int8_t *wt_packed, int8_t *out_blocked,
+                               int out_cb, int out_pad, int shift, int relu, void *stream)
+{
+    return packed_requant(desc, layout, cb, in_packed, wt_packed, out_blocked, out_cb, out_pad, shift, relu, REQUANT_CHOOSE, 0, stream);
+}
+
+int conv2d_int8_resident_requant(const conv_desc_t *desc, int layout, int cb, const int8_t *in_packed, const int8_t *wt_packed, int8_t *out_blocked,
+                                 int out_cb, int out_pad, int shift, int relu, int tile, int pixels, void *stream)
+{
+    if (tile == -1 ? pixels != 0 : tile < 0 || tile >= resident_num_tiles() || pixels < 32 || pixels > 1024 || pixels % 32) return CONV_ERR_INVALID_ARG;
+    return packed_requant(desc, layout, cb, in_packed, wt_packed, out_blocked, out_cb, out_pad, shift, relu, tile, pixels, stream);
 }
 
 int conv2d_int8_query_tiling(const conv_desc_t *desc, int layout, int cb, int *tile, int *split_k)

@@ -82,6 +82,7 @@ struct ResidentProblem {
     int pixel_bytes;
     long long img_bytes;
     int raw_weights;     // g.wq is KCRS as it came (3 x 3 and 1 x 1 only), not in depth order
+    int blocked;         // src is the blocked, bordered image that g describes (H, W with the border, pad 0, pixel_bytes g.cb) and the result g.act_out's
     int kept;            // the weights were rewritten before this call (which of the two estimates applies)
 };
 struct ResidentChoice {

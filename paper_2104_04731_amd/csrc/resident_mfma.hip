@@ -16,11 +16,15 @@
 //     raw: 36 bytes of four channels x nine taps are nine dwords of the tile after 27 byte permutes.
 //   * 1x1 weights that come raw are in that order already, in rows of C bytes: fetched in pieces of 16, zeros behind the
 //     last channel, so that a step of depth may read past a record (whatever lies there is multiplied by zero).
+//   * the blocked image of the layer before (a chain's): records come whole, the border is in the image, and the result leaves as the next layer's
+//     blocked input.  The general kernel fetches every activation once per tap.
 // Bound: the memory system (input once, result once) for the small and middle depths the kernel is for -- weights plus
 // window must fit one compute unit's LDS, which rules out 3x3 layers of more than about 300 channels.  Measured in a
 // graph, two-stage -> this kernel: 64 images 56x56, 64 -> 64, 3x3: 38 -> 19.6 us with rewritten weights (12.8 MB in, 51 MB
 // out), 38 -> 19.7 from raw ones; 16 images 56x56, 72 -> 96, stride 2: 12.2 -> 10.6; 445 images 14x14, 32 -> 405: 46 -> 36;
-// dilation 2, 64 images 28x28, 64 -> 64: 19.6 through sub-images -> 8.9.
+// dilation 2, 64 images 28x28, 64 -> 64: 19.6 through sub-images -> 8.9.  From and to blocked images: 64 images 56x56, 64 -> 64: 24.0 -> 14.7 (12.8 MB
+// in, 12.8 MB out: a fill, a chain of MFMAs and a store that follow one another in the one workgroup that a compute unit has).
+#include "act_store.h"
 #include "launch.h"
 #include "window_fill.h"
 
@@ -49,6 +53,10 @@ struct ResidentArgs {
     unsigned mg_nblk, mg_parts, mg_PQ, mg_Q, mg_tiles_k, mg_c16q, mg_cq, mg_full8, mg_g16, mg_S, mg_R, mg_u16;
     int cq, u16;                   // channel quads / 16-byte units of a record that are loaded
 };
+struct ResidentBlockedArgs : ResidentArgs {
+    ActOut act;
+    int g16_log2;                  // 16-byte pieces of a block of the source
+};
 
 __device__ __forceinline__ void res_dma16(const int8_t *src, unsigned lds_base)
 {
@@ -67,7 +75,8 @@ __device__ __forceinline__ void res_barrier()
     asm volatile("" : : : "memory");
 }
 
-enum ResSource : int { RES_NCHW = 0, RES_PIXELS = 1 };
+// RES_BLOCKED: the blocked image of the layer before, its border there already; the result goes on as the next one's (ActOut).
+enum ResSource : int { RES_NCHW = 0, RES_PIXELS = 1, RES_BLOCKED = 2 };
 enum ResWeights : int { RES_PACKED = 0, RES_RAW9 = 1, RES_RAW1 = 2 };   // in depth order; KCRS of 3 x 3 and of 1 x 1 kernels
 
 
@@ -143,6 +152,29 @@ __device__ __forceinline__ void res_store(const ResidentArgs &a, const v16i (&ac
     }
 }
 
+// The same activated, into the next layer's blocked input.
+template <int FK, int FM>
+__device__ __forceinline__ void res_store_act(const ResidentBlockedArgs &a, const v16i (&acc)[FK][FM], int kw, int mw, int m1, int lane)
+{
+    int K = a.K, PQ = a.PQ, cbl = a.act.cb_log2;
+    asm volatile("" : "+s"(K), "+s"(PQ), "+s"(cbl));
+    const int half = lane >> 5;
+#pragma unroll
+    for (int f = 0; f < FM; ++f) {
+        const int m = mw + f * 32 + (lane & 31);
+        const int n = fast_div_any(m, PQ, a.mg_PQ), pq = m - n * PQ;
+        const int p = fast_div_any(pq, a.Q, a.mg_Q), q = pq - p * a.Q;
+        const long long plane = (long long)a.act.Hp * a.act.Wp, pix = (long long)n * a.act.Cb * plane + (long long)(p + a.act.pad) * a.act.Wp + (q + a.act.pad);
+#pragma unroll
+        for (int i = 0; i < FK; ++i) {
+            const int kb = kw + i * 32, k = kb + 16 * half;
+            const v4i y = act_block16(acc[i][f], K - kb, lane, a.act.shift, a.act.relu);
+            if (m < m1 && k < a.act.Cb << cbl)
+                *reinterpret_cast<v4i *>(a.act.out + (((pix + (k >> cbl) * plane) << cbl) + (k & ((1 << cbl) - 1)))) = y;
+        }
+    }
+}
+
 // One piece of a block (rows 8g + 4*(lane/32) + 0..3), summed up from the depth parts: row k of the result onwards, pixel m.
 __device__ __forceinline__ void res_store_piece(const ResidentArgs &a, const v4i &t, int k, int m, int m1, int n0)
 {
@@ -176,7 +208,8 @@ __device__ __forceinline__ void res_store_piece(const ResidentArgs &a, const v4i
 // workgroups per compute unit it spilled, at one it does not, and its LDS rarely leaves room for two (64 images 56 x 56,
 // 64 -> 64, kept weights: 18.0 -> 17.4 us; 151 images 28 x 28, 128 -> 458: 116 -> 105).
 template <int TK, int NW, int FM, int SRC, bool UNI, int WTS, bool SPLIT, bool RUNS>
-__global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) conv_resident_kernel(const ResidentArgs a)
+__global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2)
+    conv_resident_kernel(const std::conditional_t<SRC == RES_BLOCKED, ResidentBlockedArgs, ResidentArgs> a)
 {
     constexpr int NT = NW * 64, FK = TK / 32;
     constexpr int STEP = TK * 64;   // LDS bytes of one 64-byte step of the weight tile
@@ -222,6 +255,7 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
     // ---- window ---------------------------------------------------------------------------------------------------
     const WindowSource from{a.src, a.img_bytes, a.src_bytes, a.C1, a.HW, a.pstride};
     if constexpr (SRC == RES_NCHW) window_from_nchw<NT, 4, RUNS>(from, range, a.cq, a.mg_cq, smem + a.win_off, a.pitch, tid);
+    else if constexpr (SRC == RES_BLOCKED) window_from_blocks<NT, 4>(from, range, a.u16, a.g16_log2, smem + a.win_off, a.pitch, tid);
     else window_from_pixels<NT, 4>(from, range, a.u16, a.mg_u16, smem + a.win_off, a.pitch, tid);
     if constexpr (WTS == RES_RAW1) {
         for (int t0 = wave; t0 < a.steps * G; t0 += NW * U1) {
@@ -380,6 +414,7 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
             }
         }
         if constexpr (SPLIT) break;
+        else if constexpr (SRC == RES_BLOCKED) res_store_act<FK, FM>(a, acc, k0, mw, m1, lane);
         else res_store<FK, FM>(a, acc, k0, mw, m1, n0, lane);
     }
     if constexpr (!SPLIT) return;
@@ -402,7 +437,11 @@ __global__ void __launch_bounds__(NW * 64, TK == 64 && NW == 8 ? 2 : NW / 2) con
         v4i t = at[0];
         for (int d = 1; d < a.parts; ++d) t += at[d * 64];
         const int i = p / (4 * FM), f = p / 4 % FM, g = p % 4;
-        res_store_piece(a, t, k0 + i * 32 + g * 8 + 4 * half, mw + f * 32 + (lane & 31), m1, n0);
+        const int k = k0 + i * 32 + g * 8 + 4 * half, m = mw + f * 32 + (lane & 31);
+        if constexpr (SRC == RES_BLOCKED) {
+            const int n = fast_div_any(m, a.PQ, a.mg_PQ), pq = m - n * a.PQ, row = fast_div_any(pq, a.Q, a.mg_Q);
+            if (m < m1) act_store4(a.act, n, row, pq - row * a.Q, k, a.K, t[0], t[1], t[2], t[3]);
+        } else res_store_piece(a, t, k, m, m1, n0);
     }
 }
 
@@ -448,8 +487,27 @@ hipError_t launch_res_tile(const ResidentArgs &a, bool pixels, bool uni, int wts
     return launch(kern, dim3((unsigned)(a.tiles_k * a.tiles_m)), dim3(NW * 64), lds, st, a);
 }
 
+template <int TK, int NW, int FM>
+hipError_t launch_res_blocked(const ResidentBlockedArgs &a, bool uni, size_t lds, hipStream_t st)
+{
+    typedef void (*Kernel)(ResidentBlockedArgs);
+    constexpr bool CAN_SPLIT = TK == 32 && FM == 1;
+#define C2I8_FORMS(SPLIT) \
+    conv_resident_kernel<TK, NW, FM, RES_BLOCKED, false, RES_PACKED, SPLIT, false>, conv_resident_kernel<TK, NW, FM, RES_BLOCKED, true, RES_PACKED, SPLIT, false>
+    static constexpr Kernel kernels[] = {C2I8_FORMS(false), C2I8_FORMS(CAN_SPLIT)};
+#undef C2I8_FORMS
+    static bool raised[sizeof(kernels) / sizeof(kernels[0])];
+    const int which = (a.parts > 1) * 2 + uni;
+    if (lds > 64 * 1024 && !raised[which]) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernels[which]), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        if (e != hipSuccess) return e;
+        raised[which] = true;
+    }
+    return launch(kernels[which], dim3((unsigned)(a.tiles_k * a.tiles_m)), dim3(NW * 64), lds, st, a);
+}
+
 struct ResidentPlan {
-    ResidentArgs a;
+    ResidentBlockedArgs a;   // (what is behind its base: a blocked source's)
     int tile, wts;   // wts: ResWeights
     bool uni, runs;
     size_t lds;
@@ -484,11 +542,14 @@ struct ResidentShape {
 bool resident_shape(const ResidentProblem &r, ResidentShape *o)
 {
     const GemmProblem &g = r.g;
-    if (g.mode != ACT_BLOCKED || g.R * g.S > 31 || g.il_d || g.act_out || g.Q <= 0 || g.PQ % g.Q || g.M <= 0) return false;
+    if (g.mode != ACT_BLOCKED || g.R * g.S > 31 || g.il_d || (g.act_out != nullptr) != (r.blocked != 0) || g.Q <= 0 || g.PQ % g.Q || g.M <= 0) return false;
     if (r.raw_weights ? g.R != g.S || (g.R == 1 ? (long long)g.K * r.C < 16 : g.R != 3) : g.cb < 16 || g.cb % 16) return false;
     // 32-bit offsets inside an image and of its pixels; 8- and 16-byte loads clamped to the tensor
     if (r.img_bytes > 0x7FFFFFFFLL || (long long)r.H * r.W > (1LL << 28) || (long long)r.N * r.img_bytes < 64) return false;
     if ((long long)g.Q * g.stride > (1LL << 28) || (long long)(g.PQ / g.Q) * g.stride > (1LL << 28)) return false;
+    // (whole aligned pieces, none across two blocks; 32-bit offsets in a window's pieces)
+    if (r.blocked && ((g.cb & (g.cb - 1)) || r.raw_weights || (reinterpret_cast<uintptr_t>(r.src) & 15) || (reinterpret_cast<uintptr_t>(g.act_out) & 15)))
+        return false;
     o->C16 = (r.C + 15) / 16 * 16;
     o->pitch = (o->C16 / 16 | 1) * 16;
     o->cb = r.raw_weights ? o->C16 : g.cb;
@@ -506,8 +567,8 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     ResidentShape sh;
     if (!resident_shape(r, &sh)) return false;
     const long long HW = (long long)r.H * r.W, img = r.img_bytes;
-    ResidentArgs &a = out->a;
-    a = ResidentArgs{};
+    ResidentBlockedArgs &a = out->a;
+    a = ResidentBlockedArgs{};
     auto magic = [](long long v) { return v <= 1 ? 0u : magic_for(v); };
     a.out = g.out;
     a.out_nhwc = g.out_nhwc;
@@ -541,6 +602,16 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     a.cq = a.C16 / 4;
     a.mper = mper;
     a.u16 = a.C16 / 16;
+    if (r.blocked) {
+        auto log2_of = [](int v) {
+            int l = 0;
+            while ((1 << l) < v) ++l;
+            return l;
+        };
+        a.g16_log2 = log2_of(g.cb / 16);
+        a.act = ActOut{g.act_out, g.act_shift, g.act_relu, log2_of(g.o_cb), g.o_pad, (int)(g.PQ / g.Q) + 2 * g.o_pad, g.Q + 2 * g.o_pad,
+                       (g.K + g.o_cb - 1) / g.o_cb};
+    }
     const long long Q = g.Q, PQ = g.PQ;
     {
         const long long row = (PQ / Q - 1) * g.stride - r.pad + (g.R - 1) * dil, col = (Q - 1) * g.stride - r.pad + (g.S - 1) * dil;
@@ -551,7 +622,7 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
     out->uni = sh.uni;
     // (raw 1x1 weights run the UNI kernel whatever C16 is; resident_lds still reckons with the other form's table, a few hundred bytes more)
     out->wts = !r.raw_weights ? RES_PACKED : g.R == 1 ? RES_RAW1 : RES_RAW9;
-    if ((mper / PQ + 2) * PQ * g.K * 4 >= (1LL << 32)) return false;   // 32-bit byte offsets from the workgroup's first image
+    if (!r.blocked && (mper / PQ + 2) * PQ * g.K * 4 >= (1LL << 32)) return false;   // 32-bit byte offsets from the workgroup's first image
     a.nblk = (mper + 32 * d.fm - 1) / (32 * d.fm);
     a.parts = resident_parts(d, mper, a.steps);
     a.mg_nblk = magic(a.nblk);
@@ -666,15 +737,47 @@ __attribute__((always_inline)) inline double resident_cost(const ResidentProblem
            (rounds - 1) * (f.window2 * window + f.weights2 * weights);
 }
 
+// From blocked images into the next layer's: the same kind of fit, to two thirds of 70000 launches of 2540 layers (mean error on the rest 7.5 to 9 % per
+// tile).  Trips of 16-byte pieces; result bytes are a quarter; in the 64-channel tile of 8 waves the rounds of weight transfers, which nothing hides there.
+struct ResidentActFit {
+    double launch, round, chain, trips, mfma, window, weights, result, parts, window2, weights2, transfers;
+};
+constexpr ResidentActFit kResActFit[] = {
+    {3.48, 0, 0.0158, 0.727, 0.0152, 7.69e-06, 0, 4.8e-05, 0, 2.82e-06, 9.05e-06, 0.274},
+    {3.38, 0.32, 0.0252, 0.778, 0.0103, 0, 4.23e-06, 7.76e-05, 0, 3.69e-06, 9.73e-06, 0},
+    {3.12, 0.516, 0.039, 0.763, 0.0124, 2.15e-06, 1.06e-05, 0.000111, 0.654, 0, 0, 0},
+    {3.88, 0.213, 0.0239, 0.712, 0.0156, 4.36e-06, 8.02e-06, 9.71e-05, 0, 9.31e-06, 8.89e-06, 0},
+    {3.25, 0.572, 0.0128, 0.764, 0.0239, 6.22e-06, 8.33e-06, 7.93e-05, 0.84, 4.51e-06, 2.72e-06, 0},
+};
+inline double resident_cost_act(const ResidentProblem &r, const ResidentShape &sh, const ResTile &d, const ResidentActFit &f, int mper, int tiles_m, int slots)
+{
+    const int parts = resident_parts(d, mper, sh.steps);
+    const long long lds = resident_lds(d, sh.steps, sh.uni, slots, sh.pitch, parts);
+    if (lds > RES_LDS_LIMIT) return 1e300;
+    const long long wgs = (long long)((r.g.K + d.tk - 1) / d.tk) * tiles_m;
+    int fit = (int)RES_LDS_LIMIT / (int)lds;
+    if (fit > d.fit) fit = d.fit;
+    const double per = wgs / 256.0;
+    const double ncu = per <= (double)fit ? (double)((wgs + 255) / 256) : per + 0.4;
+    const double rounds = (double)((wgs + 256 * fit - 1) / (256 * fit));
+    const int blocks = (mper + 32 * d.fm - 1) / (32 * d.fm);
+    const double chain = (double)((blocks + d.nw - 1) / d.nw) * d.fm * (d.tk / 32) * 2 * sh.steps / parts;
+    const double trips = (double)((slots * (sh.C16 / 16) + d.nw * 256 - 1) / (d.nw * 256));
+    const double mfma = d.tk / 32 * d.fm * blocks * 2.0 * sh.steps / 4, window = (double)slots * sh.C16, weights = (double)sh.steps * d.tk * 64;
+    const double transfers = (double)((sh.steps * d.tk * 64 + d.nw * 8192 - 1) / (d.nw * 8192));
+    return f.launch + rounds * (f.round + f.chain * chain + f.trips * trips + f.transfers * transfers + (parts > 1 ? f.parts : 0)) + f.mfma * ncu * mfma +
+           per * (f.window * window + f.weights * weights + f.result * d.tk * mper) + (rounds - 1) * (f.window2 * window + f.weights2 * weights);
+}
+
 // With the choice: one layer on the same depth order may come with kept weights and with raw ones, whose estimates differ.
 struct ResidentKey {
     GemmKey g;
-    int v[11];
+    int v[12];
 };
 ResidentKey resident_key(const ResidentProblem &r, const ResidentChoice &c)
 {
     const int out64 = (reinterpret_cast<uintptr_t>(r.g.out) & 63) == 0;
-    return ResidentKey{gemm_key(r.g), {r.N, r.C, r.H, r.W, r.pad, r.pixel_major, r.pixel_bytes, r.raw_weights, out64, c.tile, c.mper}};
+    return ResidentKey{gemm_key(r.g), {r.N, r.C, r.H, r.W, r.pad, r.pixel_major, r.pixel_bytes, r.raw_weights, r.blocked, out64, c.tile, c.mper}};
 }
 
 }  // namespace
@@ -703,10 +806,11 @@ bool resident_pick(const ResidentProblem &r, WindowWalk &walk, ResidentChoice *c
     // Kept weights: the middle of the two estimates, a twelfth lower (the first one's level is too high).  Their errors differ: of 700 drawn 3x3 and 5x5
     // layers 17 % were more than 2 % slower with the second one alone than with the first, 7 % with both, 0.987 of the time in the mean.  Kernels
     // of fewer taps than the second one was fitted on: the first alone (260 1x1 layers 0.956 in the mean; with the second up to 1.6 of it).
-    const bool both = r.kept && r.g.R * r.g.S >= 9;
+    const bool both = r.kept && !r.blocked && r.g.R * r.g.S >= 9;
     auto consider = [&](const ResTile &d, int t) __attribute__((always_inline)) {   // (a tile known to the compiler: its divisions are shifts)
         for (int i = 0; i < n; ++i) {
-            Cand x{resident_cost_given(r, sh, d, mpers[i], tiles_m[i], slots_of[i]), t, mpers[i]};
+            Cand x{r.blocked ? resident_cost_act(r, sh, d, kResActFit[t], mpers[i], tiles_m[i], slots_of[i])
+                             : resident_cost_given(r, sh, d, mpers[i], tiles_m[i], slots_of[i]), t, mpers[i]};
             if (both) x.cost = 0.46 * (x.cost + resident_cost(r, sh, d, kResFit[t], mpers[i], tiles_m[i], slots_of[i]));
             for (int k = 0; k < 3; ++k)
                 if (x.cost < best[k].cost) {
@@ -732,13 +836,15 @@ bool resident_pick(const ResidentProblem &r, WindowWalk &walk, ResidentChoice *c
 
 static hipError_t launch_plan(const ResidentProblem &r, const ResidentPlan &p, hipStream_t st)
 {
-    ResidentArgs a = p.a;
+    ResidentBlockedArgs a = p.a;
     a.src = r.src;
     a.wq = r.g.wq;
     a.out = r.g.out;
+    a.act.out = r.g.act_out;
     int index = 0;
 #define C2I8_CASE(tk, nw, fm, fit) \
-    if (p.tile == index++) return launch_res_tile<tk, nw, fm>(a, r.pixel_major, p.uni, p.wts, p.runs, p.lds, st);
+    if (p.tile == index++) \
+        return r.blocked ? launch_res_blocked<tk, nw, fm>(a, p.uni, p.lds, st) : launch_res_tile<tk, nw, fm>(a, r.pixel_major, p.uni, p.wts, p.runs, p.lds, st);
     C2I8_RES_LIST(C2I8_CASE)
 #undef C2I8_CASE
     return hipErrorInvalidValue;

@@ -257,4 +257,31 @@ __device__ __forceinline__ void window_from_pixels(const WindowSource &t, const 
     }
 }
 
+// Blocked source [n][block][pixel][16 << g16_log2 channels] -> records: 16-byte pieces in the order they lie in, so that a wave's loads are whole
+// lines.  u16: pieces of a record.
+template <int NT, int B>
+__device__ __forceinline__ void window_from_blocks(const WindowSource &t, const WindowRange &w, int u16, int g16_log2, unsigned char *win, int pitch, int tid)
+{
+    const int per = w.slots << g16_log2, blocks = (u16 + (1 << g16_log2) - 1) >> g16_log2, units = per * blocks;
+    const unsigned mg_per = magic_for_device(max(per, 1));
+    const int8_t *const src = t.src + (long long)w.n0 * t.img_bytes;
+    const int block_bytes = t.HW * t.pstride;
+    for (int u0 = tid; u0 < units; u0 += NT * B) {
+        v4i v[B];
+        int dst[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int u = min(u0 + b * NT, units - 1), blk = fast_div_any(u, per, mg_per), rest = u - blk * per;
+            const int s = rest >> g16_log2, j = rest & ((1 << g16_log2) - 1), piece = (blk << g16_log2) + j;
+            int n, lin;
+            window_slot(w, s, &n, &lin);
+            dst[b] = piece < u16 && u0 + b * NT < units ? s * pitch + piece * 16 : -1;
+            v[b] = *reinterpret_cast<const v4i *>(src + (long long)(n - w.n0) * t.img_bytes + (blk * block_bytes + min(lin, t.HW - 1) * t.pstride + j * 16));
+        }
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (dst[b] >= 0) *reinterpret_cast<v4i *>(win + dst[b]) = v[b];
+    }
+}
+
 }  // namespace c2i8

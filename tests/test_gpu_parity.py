@@ -1995,3 +1995,35 @@ def test_requant_at_the_ends_of_int32(lib, relu):
         nkpq = np.ascontiguousarray(x[:x.size // 21 * 21].reshape(1, 21, -1, 1))
         got = host(lib.requant_pack_layout(dev(nkpq.astype(np.int32)), 16, 1, shift, relu))
         np.testing.assert_array_equal(got, layouts.pack_layout(want[:nkpq.size].reshape(nkpq.shape), 16, 1), err_msg=f"blocked, shift {shift}")
+
+
+@pytest.mark.parametrize("dims", [(2, 64, 13, 11, 70, 3, 3, 1, 1), (5, 22, 7, 7, 33, 3, 3, 1, 1), (3, 100, 9, 14, 50, 3, 3, 2, 1), (2, 40, 12, 12, 130, 1, 1, 1, 0),
+                                  (2, 200, 8, 8, 17, 3, 3, 1, 1), (1, 16, 30, 29, 32, 5, 5, 1, 2), (70, 80, 3, 2, 96, 3, 3, 1, 1), (2, 64, 6, 40, 31, 1, 3, 2, 0)])
+def test_resident_stage_on_blocked_input(lib, dims):
+    """The stage that keeps its window in LDS, from the blocked image and into the next one, beside the stages it stands in for: every tile, one and more blocks of
+    channels, ranges over several images, depth parts, every block size of the result."""
+    N, C, H, W, K, R, S, stride, pad = dims
+    x = uniform_int8(1021, (N, C, H, W)); w = uniform_int8(1022, (K, C, R, S))
+    conv = direct.conv2d_int8(x, w, stride, pad)
+    ran = 0
+    for lay, cb in ((lib.LAYOUT_PACKED, 16), (lib.LAYOUT_PACKED, 32), (lib.LAYOUT_PACKED, 64), (lib.LAYOUT_PACKED, 48), (lib.LAYOUT_PAD_ONLY, 0)):
+        wq = lib.pack_weights(dev(w), lay, cb)
+        blk = cb if cb else -(-C // 16) * 16
+        xq = lib.pack_layout(dev(x), blk, pad)
+        for out_cb, out_pad, shift, relu in ((64, 0, 9, True), (16, 1, 8, False), (32, 0, 0, False)):
+            want = layouts.pack_layout(layouts.requant(conv, shift, relu), out_cb, out_pad)
+            for tile, pixels in [(-1, 0)] + [(t, px) for t in range(5) for px in (32, 96, 512)]:
+                buf = torch.full((want.size + 128,), 85, dtype=torch.int8, device=DEV)
+                out = buf[64:64 + want.size].view(want.shape)
+                try:
+                    lib.conv2d_int8_resident_requant(dims, lay, cb, xq, wq, out_cb, out_pad, shift, relu, out, tile, pixels)
+                except RuntimeError as e:   # (48 is no power of two; two windows of the deepest do not fit)
+                    assert tile >= 0 and "unsupported" in str(e).lower(), (cb, tile, pixels, e)
+                    continue
+                ran += tile >= 0
+                got = host(buf)
+                assert np.array_equal(got[64:-64].reshape(want.shape), want), (cb, out_cb, out_pad, tile, pixels)
+                assert (got[:64] == 85).all() and (got[-64:] == 85).all()
+            got = host(lib.conv2d_int8_packed_requant(dims, lay, cb, xq, wq, out_cb, out_pad, shift, relu))
+            assert np.array_equal(got, want), (cb, out_cb, out_pad)
+    assert ran >= 90

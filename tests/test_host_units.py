@@ -41,6 +41,11 @@ def test_window_fills_stay_inside_tensor_and_window(run_host):
     assert run_host("window_fill", ("-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include")) == (0, "ok")
 
 
+def test_blocked_window_fills_stay_inside_image_and_window(run_host):
+    """6000 random layers on blocked images of 16, 32 and 64 channels a block, the same way."""
+    assert run_host("block_fill", ("-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include")) == (0, "ok")
+
+
 def test_window_walk_against_its_definition(run_host):
     """The estimates' window sizes: 20000 random problems, up to images of 2^28 pixels, against integer divisions."""
     assert run_host("window_walk", ("-x", "c++")) == (0, "ok")
