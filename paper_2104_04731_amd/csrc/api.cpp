@@ -497,7 +497,7 @@ Route pick_route(const conv_desc_t *d, const Plan &pl, bool wt_is_packed, bool n
             // the weights' own launch: 2.4-3.2 us up to a megabyte of them
             if (C16 <= 1024) consider(DIRECT_REWRITE, C16, depth, false, 2.8 + 1.0e-6 * (double)d->K * depth + SECOND_LAUNCH_US);
             // weights streamed from blocks of 64 channels, where their estimate is well below: 320 drawn calls that come here against what ran them before
-            // this kernel, 0.84 of the time (one-shot, NHWC), 0.89 (NHWC, K no multiple of four) and 0.54 (dilated); 4 % take more than 5 % longer
+            // this kernel, 0.84 of the time (one-shot, NHWC), 0.89 (NHWC, K no multiple of four; while those results went value by value) and 0.54 (dilated); 4 % take more than 5 % longer
             const int depth64 = (d->C + 63) / 64 * 64 * d->R * d->S;
             ResidentChoice c;
             const double rewrite = 2.8 + 1.0e-6 * (double)d->K * depth64 + SECOND_LAUNCH_US;

@@ -751,7 +751,7 @@ bool stream_plan(const ResidentProblem &r, int tile, int mper, StreamPlan *out)
 // Launch time in microseconds, fitted per tile to 128000 measured launches of 13400 layers (kept weights, NCHW; a third of the
 // layers held back: mean error 4 %, 7 % for the largest tile, which leaves 208 images 256 x 28 x 28 -> 219 on the stored path: 134 us, here 118).
 // It serves NHWC and dilated calls too, from which nothing was fitted: 606 of them that it sends here take 0.64 (dilated) and 0.86
-// (NHWC) of the best other launch in the mean, 0.94 where K is not a multiple of four (results value by value, in no term; one in six loses
+// (NHWC) of the best other launch in the mean, 0.94 where K is not a multiple of four (while those results went value by value, in no term; one in six lost
 // more than 5 % there, of the others one in fifty; a term for them sent 200 calls elsewhere, at 0.999 in the mean).  A launch; per
 // round of workgroups (one per compute unit) its fixed part, its ring stages, the window bytes it begins with and those that come
 // later; the result's bytes on planes of whole 64-byte sectors and on others; what the stages of all workgroups share.
