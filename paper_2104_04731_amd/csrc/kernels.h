@@ -28,7 +28,7 @@ struct GemmProblem {
     int stride, cb, Cb, R, S, Hp, Wp;
     // Fused activation (act_out != null; split_k must be 1): instead of the int32 result, the GEMM stage
     // writes requant(result) as the next layer's blocked input [N][ceil(K/o_cb)][P+2 o_pad][Q+2 o_pad][o_cb],
-    // o_cb a power of two >= 4; the borders are not written, nor channels past the last workgroup's rows (the caller clears them);
+    // o_cb 16, 32 or 64, act_out on 16 bytes; the borders are not written, nor channels past the last workgroup's rows (the caller clears them);
     // those from K on that are, are zeros.
     int8_t *act_out;
     int act_shift, act_relu, o_cb, o_pad;
