@@ -1621,7 +1621,7 @@ def test_resident_depth_parts(lib, cfg):
                     assert np.array_equal(got[64:-64].reshape(out.shape), want_h if nhwc else want), (tile, pixels, cb, nhwc)
                     assert (got[:64] == -7).all() and (got[-64:] == -7).all(), (tile, pixels, cb, nhwc)
                     ran += 1
-    assert ran >= 20
+    assert ran > 20
 
 
 # The stage that streams the weights, tile and pixels given: every tile on NCHW and NHWC, channels that end in every part of a
