@@ -274,8 +274,7 @@ int conv2d_int8_packed_nhwc(const conv_desc_t *desc, int layout, int cb,
  * spatial padding out_pad.  in_packed, wt_packed, layout, cb as for conv2d_int8_packed (with IMPLICIT:
  * the NCHW input itself and the output of pack_weights); out_cb 16, 32 or 64; shift 0..31; all three
  * pointers 16-byte aligned (IMPLICIT: out_blocked only).  One launch; a second one before it (a clear of
- * out_blocked) when out_pad > 0 or when the last block reaches past the channels that the stage's
- * workgroups write (those from K on as zeros).  The whole depth is summed before the activation (no depth split). */
+ * out_blocked) when out_pad > 0; the last block's channels from K on come out zero.  The whole depth is summed before the activation (no depth split). */
 int conv2d_int8_packed_requant(const conv_desc_t *desc, int layout, int cb,
                                const int8_t *in_packed, const int8_t *wt_packed, int8_t *out_blocked,
                                int out_cb, int out_pad, int shift, int relu, void *stream);

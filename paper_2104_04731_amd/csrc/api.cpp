@@ -1133,15 +1133,12 @@ static int packed_requant(const conv_desc_t *desc, int layout, int cb, const int
     const long long Cbq = (desc->K + out_cb - 1) / out_cb;
     if (Hq > INT_LIMIT || Wq > INT_LIMIT) return CONV_ERR_UNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
-    // The kernel writes the interior pixels, with zeros for the channels that the last block lacks as far as the workgroups' rows of channels
-    // reach; whatever else the blocked tensor has is zero.  (A clear of its own for those channels took 3 to 7 us: 727 images 128 x 7 x 7 -> 254.)
-    auto clear = [&](int rows) {
-        if (out_pad == 0 && (desc->K + rows - 1) / rows * (long long)rows >= Cbq * out_cb) return hipSuccess;
-        return launch_fill_zero(out_blocked, (size_t)desc->N * (size_t)Cbq * (size_t)Hq * (size_t)Wq * (size_t)out_cb, st);
-    };
+    // The kernels write the interior pixels, with zeros for the channels that the last block lacks; only a border is left to a clear.
+    // (One before every ragged last block took 1.5 to 7 us: 727 images 128 x 7 x 7 -> 254.)
+    auto clear = [&] { return out_pad ? launch_fill_zero(out_blocked, (size_t)desc->N * (size_t)Cbq * (size_t)Hq * (size_t)Wq * (size_t)out_cb, st) : hipSuccess; };
     if (implicit) {
         if (how >= 0) return CONV_ERR_UNSUPPORTED;
-        if (clear(pl.pointwise || desc->K <= 32 ? 32 : 64) != hipSuccess) return CONV_ERR_DEVICE;
+        if (clear() != hipSuccess) return CONV_ERR_DEVICE;
         WindowProblem wp = window_problem(desc, pl, in_packed, wt_packed, nullptr, 1);
         int lg = 0;
         while ((1 << lg) < out_cb) ++lg;
@@ -1159,14 +1156,14 @@ static int packed_requant(const conv_desc_t *desc, int layout, int cb, const int
         ResidentChoice pick{how, pixels, 0};
         if (how >= 0 && !resident_applies(r, how, pixels)) return CONV_ERR_UNSUPPORTED;
         if (how >= 0 || choose_blocked(r, &pick)) {
-            if (clear(resident_tile_info(pick.tile).rows) != hipSuccess) return CONV_ERR_DEVICE;
+            if (clear() != hipSuccess) return CONV_ERR_DEVICE;
             return gemm_status(how >= 0 ? launch_resident_forced(r, pick.tile, pick.mper, st) : launch_resident(r, pick, st));
         }
     }
     GemmChoice c;
     rc = choose_gemm_unsplit(g, &c);
     if (rc != CONV_OK) return rc;
-    if (clear((c.tile == CONV_TILE_BAND ? band_tile_info(g) : gemm_tile_info(c.tile)).rows) != hipSuccess) return CONV_ERR_DEVICE;
+    if (clear() != hipSuccess) return CONV_ERR_DEVICE;
     return launch_choice(g, c, st);
 }
 

@@ -670,8 +670,9 @@ __device__ __forceinline__ void igemm_body(const GemmArgs &a, int block_id, int 
             for (int i = 0; i < FK; ++i) {
                 const int kb = k0 + wk * WTK + i * 32, k = kb + 16 * (lane >> 5);
                 const v4i y = act_block16(acc[i][jm], a.K - kb, lane, a.act_shift, a.act_relu);   // (channels from K on are zeros, up to the last block's end)
-                if (k < a.o_Cb << a.o_cb_log2)
-                    *reinterpret_cast<v4i *>(a.act_out + ((((size_t)n * a.o_Cb + (k >> a.o_cb_log2)) * plane + pix) << a.o_cb_log2) + (k & (o_cb - 1))) = y;
+                int8_t *dst = a.act_out + ((((size_t)n * a.o_Cb + (k >> a.o_cb_log2)) * plane + pix) << a.o_cb_log2) + (k & (o_cb - 1));
+                if (k < a.o_Cb << a.o_cb_log2) *reinterpret_cast<v4i *>(dst) = y;
+                if (TK == 32 && act_half_left(kb, a.K, a.o_cb_log2)) *reinterpret_cast<v4i *>(dst + 32) = v4i{0, 0, 0, 0};
             }
         }
         return;

@@ -28,8 +28,7 @@ struct GemmProblem {
     int stride, cb, Cb, R, S, Hp, Wp;
     // Fused activation (act_out != null; split_k must be 1): instead of the int32 result, the GEMM stage
     // writes requant(result) as the next layer's blocked input [N][ceil(K/o_cb)][P+2 o_pad][Q+2 o_pad][o_cb],
-    // o_cb 16, 32 or 64, act_out on 16 bytes; the borders are not written, nor channels past the last workgroup's rows (the caller clears them);
-    // those from K on that are, are zeros.
+    // o_cb 16, 32 or 64, act_out on 16 bytes; the borders are not written (the caller clears them), the last block's channels from K on as zeros.
     int8_t *act_out;
     int act_shift, act_relu, o_cb, o_pad;
     // Interleaving epilogue (il_d >= 2; split_k must be 1): this problem is the dense convolution on the
@@ -166,8 +165,8 @@ hipError_t launch_image_pack_weights(int K, int C, int R, int S, int stride, con
 
 // GEMM stage that unrolls the stencil itself from the NCHW input (no rewritten activations).
 // Activation in a kernel's epilogue: instead of the int32 result, requant(result) goes out as the next
-// layer's channel-blocked int8 input [N][Cb][Hp][Wp][1 << cb_log2] (interior pixels, and zeros for the channels from K
-// on that a workgroup's rows reach; the caller clears the rest).  out == nullptr: off.
+// layer's channel-blocked int8 input [N][Cb][Hp][Wp][1 << cb_log2] (interior pixels, and zeros for the last block's channels
+// from K on; the caller clears the border).  out == nullptr: off.
 struct ActOut {
     int8_t *out;
     int shift, relu, cb_log2, pad, Hp, Wp, Cb;

@@ -169,8 +169,11 @@ __device__ __forceinline__ void res_store_act(const ResidentBlockedArgs &a, cons
         for (int i = 0; i < FK; ++i) {
             const int kb = kw + i * 32, k = kb + 16 * half;
             const v4i y = act_block16(acc[i][f], K - kb, lane, a.act.shift, a.act.relu);
-            if (m < m1 && k < a.act.Cb << cbl)
-                *reinterpret_cast<v4i *>(a.act.out + (((pix + (k >> cbl) * plane) << cbl) + (k & ((1 << cbl) - 1)))) = y;
+            int8_t *dst = a.act.out + (((pix + (k >> cbl) * plane) << cbl) + (k & ((1 << cbl) - 1)));
+            if (m < m1 && k < a.act.Cb << cbl) {
+                *reinterpret_cast<v4i *>(dst) = y;
+                if (FK == 1 && act_half_left(kb, K, cbl)) *reinterpret_cast<v4i *>(dst + 32) = v4i{0, 0, 0, 0};
+            }
         }
     }
 }
