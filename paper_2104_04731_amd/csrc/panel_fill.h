@@ -80,11 +80,12 @@ struct PanelWindow {
     long long left;
     int octs;
     unsigned mg_octs;
-    bool last;      // the tensor ends within 128 bytes of its last image: a load that goes beyond what it is for could pass the end
+    bool last;      // the tensor ends within 128 bytes of the last image filled from: a load that goes beyond what it is for could pass the end
 };
 __device__ __forceinline__ PanelWindow panel_window(const VirtualImage &v, const int8_t *src, int n0, int lo, int last_slot)
 {
-    const int n1 = fast_div_any(fast_div_any(last_slot, v.Wv, v.mg_Wv), v.Hv, v.mg_Hv);
+    // (the last slot that is filled, not the last one a tap reads: without a border up to seven more are the next image's pixels)
+    const int n1 = fast_div_any(fast_div_any(lo + ((last_slot - lo + 8) & ~7) - 1, v.Wv, v.mg_Wv), v.Hv, v.mg_Hv);
     PanelWindow w;
     w.img0 = src + (long long)n0 * v.img_bytes;
     w.left = v.src_bytes - (long long)n0 * v.img_bytes;
