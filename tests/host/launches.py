@@ -1,7 +1,7 @@
 """Calls made of the library beside a stand-in for the launch (launch_recorder.cpp): what each would launch, as JSON.
 
 argv: the stand-in, the library, a JSON list of calls [dims, layout, cb, wt_is_packed] of conv2d_int8_ex, or with a tile and a depth split
-behind that, of conv2d_int8_packed.  The stand-in is loaded first, so the
+behind that, of conv2d_int8_packed, or with "requant" in the place of wt_is_packed and out_cb, out_pad behind it, of conv2d_int8_packed_requant.  The stand-in is loaded first, so the
 library's launches go to it; no memory is touched.
 """
 import ctypes
@@ -16,6 +16,10 @@ out = []
 for dims, layout, cb, packed, *forced in json.loads(sys.argv[3]):
     d = (ctypes.c_int * 9)(*dims)
     before = recorded[0]
+    if packed == "requant":
+        rc = lib.conv2d_int8_packed_requant(d, layout, cb, p, p, p, *forced, 9, 1, None)
+        out.append(dict(rc=rc, launches=recorded[0] - before, workgroups=recorded[1], kernel=name.value.decode()))
+        continue
     rc = lib.conv2d_int8_packed(d, layout, cb, p, p, p, *forced, None) if forced else lib.conv2d_int8_ex(d, layout, cb, p, p, packed, p, p, big, None)
     v = [ctypes.c_int() for _ in range(3)]
     lib.conv2d_int8_query_stage(d, 1, layout, cb, packed, 1, *map(ctypes.byref, v))

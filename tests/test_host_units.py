@@ -135,6 +135,24 @@ def test_query_tells_panels_from_stored_rewrites(lib, launches, dims):
     assert (lib.STAGE_PANEL if N > 64 else lib.STAGE_STORED) in seen
 
 
+# 1x1 layers that the estimates would send to the resident kernel, but for a stride or for more than 64 output channels.
+NOT_BLOCKED_1X1 = [(877, 32, 56, 56, 46, 1, 1, 2, 0), (322, 16, 28, 28, 159, 1, 1, 1, 0)]
+
+
+def test_fused_activations_that_take_the_resident_kernel(launches):
+    """The layers whose results are compared on the GPU do take it, one launch, or two where a border is cleared; deep and small layers, 1x1
+    layers with a stride or of many channels, blocks of no power of two and unrolled operands keep the GEMM stages."""
+    def kernels(cases):
+        got = launches([[dims, layout, cb, "requant", 64 if dims[4] > 32 else 32, pad] for dims, layout, cb in cases for pad in (0, 1)])
+        assert [c["rc"] for c in got] == [0] * len(got) and [c["launches"] for c in got] == [1, 2] * len(cases)
+        return [c["kernel"] for c in got]
+
+    assert all("conv_resident_kernel" in k and "ResidentBlockedArgs" in k for k in kernels([(dims, 1, 64 if dims[1] > 32 else 32) for dims in gpu.BLOCKED_RESIDENT]))
+    first = gpu.BLOCKED_RESIDENT[0]
+    others = [(dims, 1, 32) for dims in NOT_BLOCKED_1X1] + [((32, 256, 14, 14, 256, 3, 3, 1, 1), 1, 64), ((1, 64, 14, 14, 64, 3, 3, 1, 1), 1, 64), (first, 1, 48), (first, 2, 0)]
+    assert all("igemm" in k or "conv_band" in k for k in kernels(others))
+
+
 @pytest.mark.parametrize("dims", [(72, 500, 55, 55, 64, 3, 3, 2, 1), (575, 256, 7, 7, 357, 3, 3, 2, 1), (22, 512, 28, 28, 420, 3, 3, 1, 1)])
 def test_streaming_tiles_begin_on_whole_sectors(lib, dims):
     """Planes of whole 64-byte sectors: the library's own pixel counts cut none."""
