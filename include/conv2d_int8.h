@@ -204,21 +204,21 @@ int conv2d_int8_panel_tile_info(int tile, int *rows, int *cols);   /* past the l
 /* Which stage a call takes (host only), for tensors that start on 64 bytes. */
 typedef enum { CONV_ENTRY_ONE_SHOT = 0, CONV_ENTRY_EX = 1, CONV_ENTRY_NHWC = 2, CONV_ENTRY_DILATED = 3, CONV_ENTRY_DILATED_DIRECT = 4 } conv_entry_t;
 typedef enum {
-    CONV_STAGE_STORED = 0,           /* the rewritten operands are stored, then the GEMM stage of conv2d_int8_packed */
+    CONV_STAGE_STORED = 0,           /* rewritten operands are stored in the workspace; then the GEMM stage of conv2d_int8_packed, or (tile from
+                                        CONV_TILE_PANEL on) of the weights alone and then conv2d_int8_panel's */
     CONV_STAGE_RESIDENT = 1,         /* the stage above on the weights as they are given */
     CONV_STAGE_RESIDENT_RAW = 2,     /* ... on KCRS weights, brought into depth order on their way into LDS */
     CONV_STAGE_RESIDENT_REWRITE = 3, /* ... on weights that a launch of its own rewrites first */
     CONV_STAGE_BAND = 4,             /* the band kernel (CONV_TILE_BAND) on the NCHW tensor as it is */
     CONV_STAGE_AS_IS = 5,            /* IMPLICIT's kernels; for NHWC also the 1x1 matrix product */
     CONV_STAGE_STREAM = 6,           /* CONV_TILE_STREAM's stage on weights as they are given */
-    CONV_STAGE_STREAM_REWRITE = 7,   /* ... on weights that a launch of its own rewrites first */
-    CONV_STAGE_PANEL = 8             /* conv2d_int8_panel's stage, its panels in the workspace */
+    CONV_STAGE_STREAM_REWRITE = 7    /* ... on weights that a launch of its own rewrites first */
 } conv_stage_t;
 /* entry: which call (conv2d_int8, _ex, _nhwc, _dilated, _dilated_direct); layout, cb, wt_is_packed, dilation: its arguments,
  * those it does not have are ignored.  tile, pixels: what conv2d_int8_resident takes for the same launch (RESIDENT*: a tile
  * index, STREAM*: CONV_TILE_STREAM + t) -- with the output of pack_weights where the call reads 1x1 weights as they come, since
- * it takes raw weights of 3x3 kernels only; PANEL: CONV_TILE_PANEL + conv2d_int8_panel's tile, and its pixels; -1 and 0 for
- * the other stages. */
+ * it takes raw weights of 3x3 kernels only; STORED: CONV_TILE_PANEL + conv2d_int8_panel's tile, and its pixels, where the call ends in
+ * that stage; otherwise -1 and 0, as for the other stages. */
 #define CONV_TILE_PANEL 512
 int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int cb, int wt_is_packed, int dilation,
                             int *stage, int *tile, int *pixels);

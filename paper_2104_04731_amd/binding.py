@@ -20,9 +20,9 @@ TILE_BAND = -2   # CONV_TILE_BAND
 TILE_STREAM = 256   # CONV_TILE_STREAM: the first of these tiles
 TILE_PANEL = 512    # CONV_TILE_PANEL: query_stage's first one of conv2d_int8_panel
 ENTRY_ONE_SHOT, ENTRY_EX, ENTRY_NHWC, ENTRY_DILATED, ENTRY_DILATED_DIRECT = range(5)
-STAGE_STORED, STAGE_RESIDENT, STAGE_RESIDENT_RAW, STAGE_RESIDENT_REWRITE, STAGE_BAND, STAGE_AS_IS, STAGE_STREAM, STAGE_STREAM_REWRITE, STAGE_PANEL = range(9)
+STAGE_STORED, STAGE_RESIDENT, STAGE_RESIDENT_RAW, STAGE_RESIDENT_REWRITE, STAGE_BAND, STAGE_AS_IS, STAGE_STREAM, STAGE_STREAM_REWRITE = range(8)
 STAGE_NAMES = ("stored rewrites", "resident", "resident, raw weights", "resident, weights rewritten first", "band on NCHW", "as is", "streamed weights",
-               "streamed weights, rewritten first", "weights in panels")
+               "streamed weights, rewritten first")
 LAYOUT_NAMES = {LAYOUT_AUTO: "auto", LAYOUT_PACKED: "packed", LAYOUT_IM2COL: "im2col",
                 LAYOUT_PAD_ONLY: "pad_only", LAYOUT_IMPLICIT: "implicit",
                 LAYOUT_IMAGE_PACK: "image_pack"}

@@ -348,7 +348,7 @@ enum RouteHow : int {
     DIRECT_BAND = CONV_STAGE_BAND,
     DIRECT_STREAM = CONV_STAGE_STREAM,
     DIRECT_STREAM_REWRITE = CONV_STAGE_STREAM_REWRITE,
-    DIRECT_PANEL = CONV_STAGE_PANEL
+    DIRECT_PANEL = CONV_TILE_PANEL   // (reported as CONV_STAGE_STORED, with its tile)
 };
 struct Route {
     int how;             // DIRECT_*: resident kernel on the weights as they are / on KCRS weights / on rewritten ones, band kernel on packed ones, stream kernel on packed / rewritten ones, panel kernel
@@ -1233,9 +1233,10 @@ int conv2d_int8_query_stage(const conv_desc_t *desc, int entry, int layout, int 
         }
         if (rc != CONV_OK) return rc;
     } else return CONV_ERR_INVALID_ARG;
-    *stage = as_is ? CONV_STAGE_AS_IS : rt.how;
+    const bool panel = !as_is && rt.how == DIRECT_PANEL;
+    *stage = as_is ? CONV_STAGE_AS_IS : panel ? CONV_STAGE_STORED : rt.how;
     const bool stream = rt.how == DIRECT_STREAM || rt.how == DIRECT_STREAM_REWRITE, given = rt.how == DIRECT_BAND || rt.how == TWO_STAGE;
-    *tile = given ? -1 : rt.pick.tile + (stream ? CONV_TILE_STREAM : rt.how == DIRECT_PANEL ? CONV_TILE_PANEL : 0);
+    *tile = given ? -1 : rt.pick.tile + (stream ? CONV_TILE_STREAM : panel ? CONV_TILE_PANEL : 0);
     *pixels = given ? 0 : rt.pick.mper;
     return CONV_OK;
 }

@@ -13,8 +13,8 @@ DEV = "cuda:0"
 
 def test_growth_keeps_captured_graphs_of_stored_layers_valid(lib):
     """A graph captured while the block was small replays right after a larger layer has moved the library to a bigger
-    block (1.7 to 5.4 MB); a call that would have to grow it under capture (21 MB) is refused with nothing enqueued."""
-    small, big, huge = CONFIGS["C4a"], CONFIGS["C4a"].scaled(64), CONFIGS["C4a"].scaled(300)   # (96 and 400 images store panels of the weights alone)
+    block (1.7 to 7.5 MB); a call that would have to grow it under capture (27 MB) is refused with nothing enqueued."""
+    small, big, huge = CONFIGS["C4a"], CONFIGS["C4a"].scaled(96), CONFIGS["C4a"].scaled(400)
     for cfg in (small, big, huge):
         assert lib.query_stage(cfg.dims(), lib.ENTRY_ONE_SHOT)[0] == lib.STAGE_STORED
     x, w = small.make()
