@@ -217,8 +217,8 @@ def main():
                 "tile": f"{rows}x{cols}", "split_k": self.split, "ops": cfg.ops,
                 "op_us": round(op * 1e3, 3), "transf_in_us": round(tr * 1e3, 3) if tr else None,
                 "transf_wt_us": round(trw * 1e3, 3), "combined_us": round(comb * 1e3, 3),
-                "combined_stage": lib.STAGE_NAMES[lib.query_stage(cfg.dims(), lib.ENTRY_ONE_SHOT)[0]],
-                "prepacked_stage": lib.STAGE_NAMES[lib.query_stage(cfg.dims(), lib.ENTRY_EX, self.layout, self.cb, True)[0]],
+                "combined_stage": lib.stage_name(*lib.query_stage(cfg.dims(), lib.ENTRY_ONE_SHOT)),
+                "prepacked_stage": lib.stage_name(*lib.query_stage(cfg.dims(), lib.ENTRY_EX, self.layout, self.cb, True)),
                 "combined_weights_prepacked_us": round(pre * 1e3, 3),
                 "tops_op": round(cfg.ops / (op * 1e-3) / 1e12, 3),
                 "issued_tops_op": round((cfg.ops + 2 * o_mac) / (op * 1e-3) / 1e12, 3),

@@ -204,8 +204,9 @@ int conv2d_int8_panel_tile_info(int tile, int *rows, int *cols);   /* past the l
 /* Which stage a call takes (host only), for tensors that start on 64 bytes. */
 typedef enum { CONV_ENTRY_ONE_SHOT = 0, CONV_ENTRY_EX = 1, CONV_ENTRY_NHWC = 2, CONV_ENTRY_DILATED = 3, CONV_ENTRY_DILATED_DIRECT = 4 } conv_entry_t;
 typedef enum {
-    CONV_STAGE_STORED = 0,           /* rewritten operands are stored in the workspace; then the GEMM stage of conv2d_int8_packed, or (tile from
-                                        CONV_TILE_PANEL on) of the weights alone and then conv2d_int8_panel's */
+    CONV_STAGE_STORED = 0,           /* rewritten operands are stored in the workspace first.  Which ones the tile says: -1, what the GEMM stage of
+                                        conv2d_int8_packed reads; from CONV_TILE_PANEL on, the weights alone, and conv2d_int8_panel's stage
+                                        reads the input as it is */
     CONV_STAGE_RESIDENT = 1,         /* the stage above on the weights as they are given */
     CONV_STAGE_RESIDENT_RAW = 2,     /* ... on KCRS weights, brought into depth order on their way into LDS */
     CONV_STAGE_RESIDENT_REWRITE = 3, /* ... on weights that a launch of its own rewrites first */

@@ -338,6 +338,11 @@ def query_stage(dims, entry, layout=LAYOUT_AUTO, cb=0, wt_is_packed=False, dilat
     return tuple(x.value for x in v)
 
 
+def stage_name(stage: int, tile: int, pixels: int) -> str:
+    """query_stage's answer in words."""
+    return "weights in panels" if stage == STAGE_STORED and tile >= TILE_PANEL else STAGE_NAMES[stage]
+
+
 # ---- layout rewrites ------------------------------------------------------------------------
 def pack_layout_bytes(N, C, H, W, cb, pad) -> int:
     return int(load().pack_layout_bytes(N, C, H, W, cb, pad))

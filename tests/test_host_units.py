@@ -118,6 +118,24 @@ def test_query_names_the_streaming_tile(lib, launches, dims):
         assert lib.resident_applies(dims, 64, tile, pixels)
 
 
+@pytest.mark.parametrize("dims", [(200, 128, 28, 28, 100, 3, 3, 2, 1), (400, 256, 14, 14, 512, 3, 3, 1, 1), (64, 256, 14, 14, 512, 3, 3, 1, 1)])
+def test_query_tells_panels_from_stored_rewrites(lib, launches, dims):
+    """Kept weights and raw ones: of the calls that store operands, the tile tells those that read the input as it is from those of the GEMM stage."""
+    (N, C, H, W, K, R, S, stride, pad), tiles = dims, lib.panel_tiles()
+    M, seen = N * ((H + 2 * pad - R) // stride + 1) * ((W + 2 * pad - S) // stride + 1), set()
+    for call in launches([(dims, 1, 64, 1), (dims, 1, 64, 0)]):
+        stage, tile, pixels = call["stage"]
+        panels = stage == lib.STAGE_STORED and tile >= lib.TILE_PANEL
+        assert call["rc"] == 0 and panels == ("conv_panel_kernel" in call["kernel"]) == (lib.stage_name(stage, tile, pixels) == "weights in panels"), call
+        if panels:
+            rows, most = tiles[tile - lib.TILE_PANEL]
+            assert pixels <= most and call["launches"] == 2 and call["workgroups"] == -(-K // rows) * -(-M // pixels)
+        elif stage == lib.STAGE_STORED:
+            assert (tile, pixels) == (-1, 0) and ("igemm" in call["kernel"] or "conv_band" in call["kernel"])
+        seen.add((stage, panels))
+    assert (lib.STAGE_STORED, N > 64) in seen
+
+
 # 1x1 layers that the estimates would send to the resident kernel, but for a stride or for more than 64 output channels.
 NOT_BLOCKED_1X1 = [(877, 32, 56, 56, 46, 1, 1, 2, 0), (322, 16, 28, 28, 159, 1, 1, 1, 0)]
 
