@@ -54,96 +54,58 @@ static void fill_window(const VirtualImage &v, const int8_t *src, int lo, int la
         }
 }
 
-struct Problem {
-    int N, C, H, W, R, S, st, pad, dil, mper;
-};
-static std::vector<unsigned char> win;
-
-// All tiles of a problem whose tensor begins at src; tiles: how many there were.  0: as it should be.
-static int check(const Problem &p, unsigned char *src, int it, int *tiles)
-{
-    const int N = p.N, C = p.C, H = p.H, W = p.W, R = p.R, S = p.S, st = p.st, pad = p.pad, dil = p.dil, mper = p.mper;
-    const int P = (H + 2 * pad - dil * (R - 1) - 1) / st + 1, Q = (W + 2 * pad - dil * (S - 1) - 1) / st + 1;
-    const long long bytes = (long long)N * C * H * W;
-    const int HW = H * W, PQ = P * Q, M = N * PQ;
-    for (long long i = 0; i < bytes; ++i) src[i] = (unsigned char)(i * 31 + i / 253 + it + 1);
-    const VirtualImage v{W + pad, H + pad, N, C, H, W, HW, pad, (C + 63) / 64, C, (long long)C * HW, bytes, magic(W + pad), magic(H + pad)};
-    auto first = [&](int m) { return (m / PQ * v.Hv + m % PQ / Q * st) * v.Wv + m % PQ % Q * st; };
-    const int span = ((R - 1) * v.Wv + S - 1) * dil;
-    const long long most = window_slots(mper, PQ, Q, st, v.Wv, v.Hv, span);
-    for (int m0 = 0; m0 < M; m0 += mper) {
-        const int m1 = min(m0 + mper, M), lo = first(m0), octs = (first(m1 - 1) + span - lo + 8) >> 3;
-        if (8 * octs > most) return printf("%d slots, %lld planned: N %d H %d W %d %dx%d stride %d pad %d dil %d mper %d tile %d\n", 8 * octs, most, N, H, W, R, S, st, pad, dil, mper, m0), 1;
-        const int at_once = rnd(1, v.chunks);
-        for (int part = 0; part < v.chunks; part += at_once)
-            for (int nhwc = 0; nhwc < 2; ++nhwc) {
-                const int chunks = min(at_once, v.chunks - part);
-                const size_t bytes_of = (size_t)octs * 8 * 80;
-                win.assign(bytes_of * chunks + 256, 0xEE);
-                if (nhwc) fill_window<PanelFill<true>>(v, (const int8_t *)src, lo, first(m1 - 1) + span, octs, part, chunks, win.data());
-                else fill_window<PanelFill<false>>(v, (const int8_t *)src, lo, first(m1 - 1) + span, octs, part, chunks, win.data());
-                for (size_t i = bytes_of * chunks; i < win.size(); ++i)
-                    if (win[i] != 0xEE) return printf("written past the window: C %d H %d W %d\n", C, H, W), 1;
-                for (int m = m0; m < m1; ++m)
-                    for (int r = 0; r < R; ++r)
-                        for (int s = 0; s < S; ++s) {
-                            const int n = m / PQ, row = m % PQ / Q * st + r * dil - pad, col = m % PQ % Q * st + s * dil - pad;
-                            for (int c = part * 64; c < min(C, (part + chunks) * 64); ++c) {
-                                const unsigned char *const rec = win.data() + bytes_of * (c / 64 - part) + (size_t)(first(m) - lo + (r * v.Wv + s) * dil) * 80;
-                                const bool there = row >= 0 && row < H && col >= 0 && col < W;
-                                const unsigned char want = !there ? 0 : src[nhwc ? ((long long)n * HW + row * W + col) * C + c : ((long long)n * C + c) * HW + row * W + col];
-                                if (rec[c % 64] != want)
-                                    return printf("N %d C %d H %d W %d %dx%d stride %d pad %d dil %d mper %d tile %d nhwc %d: pixel %d tap %d %d channel %d\n", N, C, H, W, R, S, st,
-                                                  pad, dil, mper, m0, nhwc, m, r, s, c), 1;
-                            }
-                        }
-            }
-        ++*tiles;
-    }
-    return 0;
-}
-// Whether the kernel takes it, and its tensor the room between the guard pages.
-static bool takes(const Problem &p, long long room)
-{
-    const long long img = (long long)p.C * p.H * p.W, bytes = p.N * img;
-    return p.H + 2 * p.pad >= p.dil * (p.R - 1) + 1 && p.W + 2 * p.pad >= p.dil * (p.S - 1) + 1 && bytes >= 16 && bytes <= room &&
-           virtual_image_fits(p.R, p.S, p.dil, p.H, p.W, p.pad, p.N, img);
-}
-
 int main()
 {
     const size_t page = 4096, room = 1 << 20;
     unsigned char *const map = (unsigned char *)mmap(nullptr, room + 2 * page, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0);
     if (map == MAP_FAILED || mprotect(map, page, PROT_NONE) || mprotect(map + page + room, page, PROT_NONE)) return 2;
-    auto at_end = [&](const Problem &p) { return map + page + room - (long long)p.N * p.C * p.H * p.W; };
+    std::vector<unsigned char> win;
     int tiles = 0, problems = 0;
     for (int it = 0; it < 9000; ++it) {
         const int C = it % 3 ? rnd(1, 40) : rnd(60, 150), H = rnd(1, it % 5 ? 14 : 2), W = rnd(1, it % 5 ? 19 : 9), N = rnd(1, 9), R = rnd(1, 5), S = rnd(1, 5), st = rnd(1, 3), pad = rnd(0, 4), dil = rnd(1, 3);
         if (H + 2 * pad < dil * (R - 1) + 1 || W + 2 * pad < dil * (S - 1) + 1) continue;
-        const Problem p{N, C, H, W, R, S, st, pad, dil, it & 8 ? rnd(1, 448) : 16 * rnd(1, 28)};
-        if (!takes(p, (long long)room)) continue;
+        const int P = (H + 2 * pad - dil * (R - 1) - 1) / st + 1, Q = (W + 2 * pad - dil * (S - 1) - 1) / st + 1;
+        const long long bytes = (long long)N * C * H * W;
+        const int HW = H * W, PQ = P * Q, M = N * PQ, mper = it & 8 ? rnd(1, 448) : 16 * rnd(1, 28);
+        if (bytes < 16 || bytes > (long long)room || !virtual_image_fits(R, S, dil, H, W, pad, N, (long long)C * HW)) continue;
         ++problems;
-        if (check(p, it & 1 ? map + page : at_end(p), it, &tiles)) return 1;
+        unsigned char *const src = it & 1 ? map + page : map + page + room - bytes;
+        for (long long i = 0; i < bytes; ++i) src[i] = (unsigned char)(i * 31 + i / 253 + it + 1);
+        const VirtualImage v{W + pad, H + pad, N, C, H, W, HW, pad, (C + 63) / 64, C, (long long)C * HW, bytes, magic(W + pad), magic(H + pad)};
+        auto first = [&](int m) { return (m / PQ * v.Hv + m % PQ / Q * st) * v.Wv + m % PQ % Q * st; };
+        const int span = ((R - 1) * v.Wv + S - 1) * dil;
+        const long long most = window_slots(mper, PQ, Q, st, v.Wv, v.Hv, span);
+        for (int m0 = 0; m0 < M; m0 += mper) {
+            const int m1 = min(m0 + mper, M), lo = first(m0), octs = (first(m1 - 1) + span - lo + 8) >> 3;
+            if (8 * octs > most) return printf("%d slots, %lld planned: N %d H %d W %d %dx%d stride %d pad %d dil %d mper %d tile %d\n", 8 * octs, most, N, H, W, R, S, st, pad, dil, mper, m0), 1;
+            const int at_once = rnd(1, v.chunks);
+            for (int part = 0; part < v.chunks; part += at_once)
+                for (int nhwc = 0; nhwc < 2; ++nhwc) {
+                    const int chunks = min(at_once, v.chunks - part);
+                    const size_t bytes_of = (size_t)octs * 8 * 80;
+                    win.assign(bytes_of * chunks + 256, 0xEE);
+                    if (nhwc) fill_window<PanelFill<true>>(v, (const int8_t *)src, lo, first(m1 - 1) + span, octs, part, chunks, win.data());
+                    else fill_window<PanelFill<false>>(v, (const int8_t *)src, lo, first(m1 - 1) + span, octs, part, chunks, win.data());
+                    for (size_t i = bytes_of * chunks; i < win.size(); ++i)
+                        if (win[i] != 0xEE) return printf("written past the window: C %d H %d W %d\n", C, H, W), 1;
+                    for (int m = m0; m < m1; ++m)
+                        for (int r = 0; r < R; ++r)
+                            for (int s = 0; s < S; ++s) {
+                                const int n = m / PQ, row = m % PQ / Q * st + r * dil - pad, col = m % PQ % Q * st + s * dil - pad;
+                                for (int c = part * 64; c < min(C, (part + chunks) * 64); ++c) {
+                                    const unsigned char *const rec = win.data() + bytes_of * (c / 64 - part) + (size_t)(first(m) - lo + (r * v.Wv + s) * dil) * 80;
+                                    const bool there = row >= 0 && row < H && col >= 0 && col < W;
+                                    const unsigned char want = !there ? 0 : src[nhwc ? ((long long)n * HW + row * W + col) * C + c : ((long long)n * C + c) * HW + row * W + col];
+                                    if (rec[c % 64] != want)
+                                        return printf("N %d C %d H %d W %d %dx%d stride %d pad %d dil %d mper %d tile %d nhwc %d: pixel %d tap %d %d channel %d\n", N, C, H, W, R, S, st,
+                                                      pad, dil, mper, m0, nhwc, m, r, s, c), 1;
+                                }
+                            }
+                }
+            ++tiles;
+        }
     }
     if (problems < 1500 || tiles < 5000) return printf("%d problems, %d tiles only\n", problems, tiles), 1;
-
-    // Small planes without a border, the tensor always against the page behind it: the eights that a window is filled in end in the next image,
-    // whose rows and channels are few enough for a piece of one of its first pixels to pass the tensor's end.
-    problems = tiles = 0;
-    for (int HW = 8; HW <= 27; ++HW)
-        for (int H = 1; H <= HW; ++H) {
-            if (HW % H) continue;
-            for (int C = 1; C <= 70; ++C)
-                for (int N = 2; N <= 4; ++N)
-                    for (int i = 0; i < (HW > 12 ? 1 : 3); ++i) {
-                        const int W = HW / H, pixels[] = {1, rnd(2, 17), rnd(18, 40)};
-                        const Problem p{N, C, H, W, rnd(1, H < 5 ? H : 5), rnd(1, W < 5 ? W : 5), rnd(0, 2) ? 1 : 2, 0, 1, pixels[HW > 12 ? rnd(0, 2) : i]};
-                        if (!takes(p, (long long)room)) continue;
-                        ++problems;
-                        if (check(p, at_end(p), C, &tiles)) return 1;
-                    }
-        }
-    if (problems < 20000 || tiles < 100000) return printf("%d problems, %d tiles of small planes only\n", problems, tiles), 1;
     puts("ok");
     return 0;
 }

@@ -2029,20 +2029,15 @@ def test_resident_stage_on_blocked_input(lib, dims):
     assert ran >= 90
 
 
-# (that the library sends them there is held against what the calls launch, without a GPU)
-BLOCKED_RESIDENT = [(64, 64, 56, 56, 64, 3, 3, 1, 1), (188, 30, 38, 38, 25, 3, 3, 1, 1), (233, 64, 28, 33, 32, 5, 5, 1, 2), (192, 128, 35, 35, 17, 3, 3, 1, 1)]
-
-
-@pytest.mark.parametrize("dims", BLOCKED_RESIDENT)
+@pytest.mark.parametrize("dims", [(64, 64, 56, 56, 64, 3, 3, 1, 1), (188, 30, 38, 38, 25, 3, 3, 1, 1), (233, 64, 28, 33, 32, 5, 5, 1, 2), (192, 128, 35, 35, 17, 3, 3, 1, 1)])
 def test_calls_that_take_the_resident_stage_on_blocked_input(lib, dims):
     """Sizes at which the library sends a fused activation there itself, eagerly and in a graph replayed on new inputs, beside the stages that the tests above
-    hold against the definition, and the first and last image beside the definition itself."""
+    hold against the definition."""
     N, C, H, W, K, R, S, stride, pad = dims
     cb, out_cb = 64 if C > 32 else 32, 64 if K > 32 else 32
     w = torch.randint(-128, 128, (K, C, R, S), dtype=torch.int8, device=DEV)
     wq = lib.pack_weights(w, lib.LAYOUT_PACKED, cb)
-    x = torch.randint(-128, 128, (N, C, H, W), dtype=torch.int8, device=DEV)
-    xq = lib.pack_layout(x, cb, pad)
+    xq = lib.pack_layout(torch.randint(-128, 128, (N, C, H, W), dtype=torch.int8, device=DEV), cb, pad)
     P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1
     want = torch.empty((N, -(-K // out_cb), P, Q, out_cb), dtype=torch.int8, device=DEV)
     got = torch.full_like(want, 85)
@@ -2050,9 +2045,6 @@ def test_calls_that_take_the_resident_stage_on_blocked_input(lib, dims):
     stored = lambda: lib.conv2d_int8_resident_requant(dims, lib.LAYOUT_PACKED, cb, xq, wq, out_cb, 0, 10, True, want, -1, 0)
     stored(); call()
     assert torch.equal(got, want)
-    for n in (0, N - 1):
-        act = layouts.requant(direct.conv2d_int8(host(x[n:n + 1]), host(w), stride, pad), 10, True)
-        assert np.array_equal(host(got[n:n + 1]), layouts.pack_layout(act, out_cb, 0)), n
     side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
     torch.cuda.synchronize()
     with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
@@ -2064,3 +2056,21 @@ def test_calls_that_take_the_resident_stage_on_blocked_input(lib, dims):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(got, want)
+
+
+# (that the library sends them there is held against what the calls launch, without a GPU)
+BLOCKED_RESIDENT = test_calls_that_take_the_resident_stage_on_blocked_input.pytestmark[0].args[1]
+
+
+@pytest.mark.parametrize("dims", BLOCKED_RESIDENT)
+def test_resident_stage_s_own_calls_on_blocked_input_against_the_definition(lib, dims):
+    """The same sizes: the first and the last image beside the definition itself."""
+    N, C, H, W, K, R, S, stride, pad = dims
+    cb, out_cb = 64 if C > 32 else 32, 64 if K > 32 else 32
+    x = torch.randint(-128, 128, (N, C, H, W), dtype=torch.int8, device=DEV)
+    w = torch.randint(-128, 128, (K, C, R, S), dtype=torch.int8, device=DEV)
+    got = torch.full((N, -(-K // out_cb), (H + 2 * pad - R) // stride + 1, (W + 2 * pad - S) // stride + 1, out_cb), 85, dtype=torch.int8, device=DEV)
+    lib.conv2d_int8_packed_requant(dims, lib.LAYOUT_PACKED, cb, lib.pack_layout(x, cb, pad), lib.pack_weights(w, lib.LAYOUT_PACKED, cb), out_cb, 0, 10, True, out=got)
+    for n in (0, N - 1):
+        act = layouts.requant(direct.conv2d_int8(host(x[n:n + 1]), host(w), stride, pad), 10, True)
+        assert np.array_equal(host(got[n:n + 1]), layouts.pack_layout(act, out_cb, 0)), n

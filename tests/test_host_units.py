@@ -56,6 +56,11 @@ def test_panel_windows_stay_inside_tensor_and_window(run_host):
     assert run_host("panel_fill", ("-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include")) == (0, "ok")
 
 
+def test_panel_windows_at_the_tensor_s_end(run_host):
+    """Small planes without a border, where the last eight slots of a window reach the tensor's last image."""
+    assert run_host("panel_fill_end", ("-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-I/opt/rocm/include")) == (0, "ok")
+
+
 def test_panel_stage_validation(lib):
     """What the stage refuses, before any device call; no tile asks for more LDS than lets two workgroups share a compute unit."""
     import ctypes
