@@ -263,7 +263,7 @@ int pack_weights_rsc(int K, int C, int R, int S, const int8_t *src, int8_t *dst,
 
 /* The GEMM stage with an NHWC result (Sec. 5.2): as conv2d_int8_packed, but out_nhwc is int32 [N][P][Q][K],
  * written by the epilogue itself (a lane of the MFMA result holds four consecutive channels of a pixel:
- * 16-byte stores when K % 4 == 0).  PACKED, PAD_ONLY or IM2COL (IMPLICIT: CONV_ERR_UNSUPPORTED); all three
+ * 16-byte stores, whatever K is).  PACKED, PAD_ONLY or IM2COL (IMPLICIT: CONV_ERR_UNSUPPORTED); all three
  * pointers 16-byte aligned. */
 int conv2d_int8_packed_nhwc(const conv_desc_t *desc, int layout, int cb,
                             const int8_t *in_packed, const int8_t *wt_packed, int32_t *out_nhwc,

@@ -249,7 +249,7 @@ __global__ void __launch_bounds__(256) conv_pointwise_split_kernel(const PointAr
 struct PointNhwcArgs {
     const int8_t *in;   // [M][C], M = N*H*W pixels
     const int8_t *wt;   // [K][C]
-    int32_t *out;       // [M][K], K a multiple of 4, 16-byte aligned
+    int32_t *out;       // [M][K], rows of any K from any dword on
     int M, K;
 };
 constexpr int NHWC_RED_PITCH = 33;   // 16-byte slots per (wave, four-row group): 32 pixels and one of padding

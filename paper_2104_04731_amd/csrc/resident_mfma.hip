@@ -669,7 +669,7 @@ bool resident_plan(const ResidentProblem &r, int tile, int mper, ResidentPlan *o
 // the registers in rounds of loads of their own, more than twice as long where the rows of 9 C bytes do not start on dwords.
 // It was fitted before the wide fill, the depth parts and the raw weights' units in flight, and knows none of them.  What that means now, over 10000
 // one-shot, NHWC and dilated calls: near each layer's best launch 12 % mean error on raw weights (11 % high in the median), 9 % on
-// rewritten ones (6 % high), 18 % from NHWC (value-by-value stores of odd K are not in it) -- but what it chooses, tile, pixels and this
+// rewritten ones (6 % high), 18 % from NHWC (while results of K no multiple of four went value by value, in no term) -- but what it chooses, tile, pixels and this
 // kernel or the stored path, loses 1.0 % against the best of what was measured, and 0.9 % if the chosen launch's time were known
 // exactly.  Fits per tile with an error of 6 % chose worse (1.4 %: 1x1 layers, and candidates unlike the fitted ones), as did scaling this one's level (1.0 %).
 __attribute__((always_inline)) inline double resident_cost_given(const ResidentProblem &r, const ResidentShape &sh, const ResTile &d, int mper, int tiles_m, int slots)
