@@ -9,10 +9,10 @@
 //     of 8: with two workgroups per compute unit 472 us where panels take 314 (2048 images 256 x 14 x 14 -> 512, main loop alone).
 //   * the window is that of a virtual image with its border in it (panel_fill.h), so that a tap is one addition: masks instead cost 7 % of that
 //     loop.  It holds as many chunks of 64 channels as LDS has room for, filled all at once.  (Filled chunk by chunk beside the MFMAs the same
-//     layer took 496 us instead of 455: a wave's loads return in order, so its next weights wait behind pixels that come from memory.)
+//     layer took 1.09 times as long: a wave's loads return in order, so its next weights wait behind pixels that come from memory.)
 //   * two workgroups (of the smaller tiles three, four) share a compute unit: one fills or stores while the other multiplies.
 // The main loop alone keeps the matrix pipe busy all the time, and the power management lowers the clock to 1.4 - 1.5 GHz: 2.6 POP/s there where the
-// register-resident probe has 3.2.  Calls with kept weights, both launches: the layer above 539 -> 448 us, 462 images 256 x 28 x 28 -> 128 179 -> 113,
+// register-resident probe has 3.2.  Calls with kept weights, both launches: the layer above 549 -> 474 us in turn, 462 images 256 x 28 x 28 -> 128 179 -> 113,
 // 205 x 512 x 22 x 22 -> 128 90 -> 68, 675 x 512 x 14 x 14 -> 17 63 -> 42; all 2048 x 256 x 14 x 14 -> 512 needs at the probe's rate is 300.
 #include "panel_fill.h"
 #include "kernels.h"
@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(256, panel_occupancy(FM, FK)) conv_panel_kerne
 #pragma unroll
         for (int f = 0; f < FM; ++f) read_pixels(f, 0, at), read_pixels(f, 1, at);
         // While it multiplies a wave goes before the other workgroups', which fill their window or write their result beside: 0.975 of the time
-        // (2048 images 256 x 14 x 14 -> 512: 461 -> 450 us; the other way round 463).
+        // (2048 images 256 x 14 x 14 -> 512; the other way round it takes what it takes without).
         __builtin_amdgcn_s_setprio(1);
         for (int j = 0; j < steps; j += U) {
 #pragma unroll
@@ -452,7 +452,8 @@ bool panel_plan(const ResidentProblem &r, int tile, int mper, PanelPlan *out)
 // error 5 to 7 %, NHWC 3 to 4 %; the tile it picks takes 1.011 of the best one's time in the mean).  A launch; the weights' bytes; what the
 // busiest compute unit's workgroups take, one by one and as many at a time as fit, per workgroup, step, 64-byte record of the window and part of
 // the depth; the same for all of them; the result's megabytes on planes of whole 64-byte sectors (NHWC: all), of 16-byte pieces, others, and
-// of NHWC rows that are none; KCRS weights.
+// of NHWC rows that are none; KCRS weights.  None is below zero and many are 0, as a fit that is bounded there
+// leaves them: no measure of that term alone.
 struct PanelFit {
     double launch, weights, one, one_step, one_fill, one_part, round, round_step, round_fill, all_step, all_fill, sectors, pieces, odd, odd_rows, all, raw;
 };
