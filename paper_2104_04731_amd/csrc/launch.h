@@ -38,7 +38,9 @@ hipError_t launch(void (*kern)(P0, P1, P...), dim3 grid, dim3 block, size_t lds,
 
 // Table of up to N plans.  A network calls the same layers over and over, and choosing how one runs costs the host 4.5 us
 // in the middle, 11 at the 95th percentile (1233 one-shot, NHWC and dilated calls), with kept weights 7.9 and 15.7 (267): the
-// tile model 2.7, the resident kernel's candidates 2.3 (kept weights: 2.8), the stream kernel's 0.6 to 2.9 -- against the 2.4 us of a launch.  A problem is looked for from its hash's slot on, up to
+// tile model 2.7, the resident kernel's candidates 2.3 (kept weights: 2.8), the stream kernel's 0.6 to 2.9 -- against the 2.4 us of a launch.  These were taken before the panel kernel, whose
+// eight tiles with up to six pixel counts each add 0.6 to 0.8 us in the middle on another host (4000 layers of 65 to 512 channels for each kind of call, all new: 9.2 to
+// 10.1 -> 9.9 to 10.8; of 16 to 512 channels 0.4 to 0.7).  A problem is looked for from its hash's slot on, up to
 // the first empty one, so N problems never displace one another (two of 20 would meet in a direct-mapped table of 64 with a
 // probability of 95 %, and evict each other on every call); in a full table a new one replaces the plan at its hash's
 // slot.  Key: plain integers without padding, compared whole.  Meant to be thread_local: no locks, bounded, and gone with
